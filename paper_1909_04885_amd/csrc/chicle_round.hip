@@ -1066,7 +1066,9 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
         HIP_TRY(c, hipMemcpyAsync(c->chunk_owner_dev, chunk_to_solver, sizeof(int32_t) * (size_t)c->n_chunks, hipMemcpyHostToDevice, c->stream));
         HIP_TRY(c, hipMemsetAsync(c->bits_dev, 0, sizeof(unsigned) * (size_t)c->words * (size_t)K, c->stream));
         if (c->multi_dev) HIP_TRY(c, hipMemsetAsync(c->multi_dev, 0, sizeof(unsigned) * (size_t)c->words * (size_t)K, c->stream));
-        hipLaunchKernelGGL(mark_columns, egrid, dim3(256), 0, c->stream, c->chunks_dev, c->chunk_owner_dev, c->bits_dev, c->words, c->multi_dev);
+        // (few workgroups per chunk: each of them adds a bitmap of its own to the solver's at the end)
+        const dim3 mgrid(grid_for(max_nnz, 256 * 64, std::max(1, 4096 / c->n_chunks)), c->n_chunks);
+        hipLaunchKernelGGL(mark_columns, mgrid, dim3(256), 0, c->stream, c->chunks_dev, c->chunk_owner_dev, c->bits_dev, c->words, c->multi_dev);
         const int forced = batched_eligible(c) ? batched_layout(c).n_hot : 0;
         if (forced > 0)
             hipLaunchKernelGGL(force_columns, dim3(K), dim3(256), 0, c->stream, c->bits_dev, c->words, forced);
