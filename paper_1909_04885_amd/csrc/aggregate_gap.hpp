@@ -518,9 +518,9 @@ __global__ __launch_bounds__(GAP_HOT_THREADS) void gap_rows_csr_hot(const ChunkD
     }
 }
 
-// Dense rows: LPR lanes per row, strided over the d columns.  Same grid as the sparse kernel.
+// Dense rows (ld floats each, 16-byte aligned): LPR lanes per row, four columns at a time.  Same grid as the sparse kernel.
 template <int LOSS, int LPR, typename WT>
-__global__ __launch_bounds__(256) void gap_rows_dense(const ChunkDev *__restrict__ chunks, int d,
+__global__ __launch_bounds__(256) void gap_rows_dense(const ChunkDev *__restrict__ chunks, int d, int ld,
                                                       const WT *__restrict__ w, double l1,
                                                       double *part_loss, double *part_conj)
 {
@@ -530,9 +530,13 @@ __global__ __launch_bounds__(256) void gap_rows_dense(const ChunkDev *__restrict
     const ChunkDev &ch = chunks[blockIdx.y];
     double s_loss = 0.0, s_conj = 0.0;
     for (int r = blockIdx.x * GROUPS + grp; r < ch.n_rows; r += gridDim.x * GROUPS) {
-        const float *x = ch.val + (int64_t)r * d;
+        const float *x = ch.val + (int64_t)r * ld;
         WT z = 0;
-        for (int p = sub; p < d; p += LPR) z += (WT)x[p] * shared_at(w, p, l1);
+        for (int p = 4 * sub; p < d; p += 4 * LPR) {         // (w is readable up to a multiple of 64 columns, zero past d)
+            const float4_v v = *reinterpret_cast<const float4_v *>(x + p);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z += (WT)v[e] * shared_at(w, p + e, l1);
+        }
 #pragma unroll
         for (int o = LPR / 2; o > 0; o >>= 1) z += __shfl_xor(z, o, 64);
         if (sub == 0) gap_row_terms<LOSS, WT>(ch.st + r, z, s_loss, s_conj);

@@ -20,8 +20,8 @@
 #include "layout.hpp"
 #include "policies.hpp"
 #include "sdca_batched.hpp"
-#include "sdca_batched_dense.hpp"
 #include "sdca_batched_split.hpp"
+#include "sdca_dense.hpp"
 #include "sdca_rowwise.hpp"
 #include "sdca_rowwise_cluster.hpp"
 
@@ -48,6 +48,7 @@ enum State { ST_LOADING = 0, ST_READY = 1, ST_EPOCH_DONE = 2 };
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 inline int64_t pad_d(int64_t d) { return (d + 63) / 64 * 64; }
 inline int64_t tiles_cap(int64_t n_total, int32_t max_solvers) { return n_total / BATCH + max_solvers + 1; }
+inline size_t tile_bytes(bool dense) { return sizeof(float) * (size_t)(dense ? DENSE_TILE_FLOATS : TILE_FLOATS); }
 
 struct Seg {
     hipEvent_t start = nullptr, stop = nullptr;
@@ -105,8 +106,7 @@ struct chicle_ctx {
     double lambda = 0;
     double l1 = 0;             // elastic net: regulariser lambda (|w|^2 / 2 + l1 |w|_1); w64 then holds the dual image
     int32_t n_chunks = 0, max_solvers = 0;
-    bool dense = false;        // chunks stored as dense row-major matrices
-    bool api_dense = false;    // chunks arrive through chicle_load_chunk_dense
+    bool dense = false;        // chunks are dense row-major matrices, rows of dense_ld(d) floats
     int64_t total_entries = 0;
     char *arena = nullptr;
     size_t arena_bytes = 0, used = 0;
@@ -254,7 +254,7 @@ size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_sol
     s += align_up(sizeof(double) * (size_t)ld);                          // w in double
     s += align_up(sizeof(float) * (size_t)private_floats(n_total_entries_hint, ld, max_solvers, long_rows));   // private vectors
     s += 2 * align_up(sizeof(int32_t) * (size_t)d);                      // renumbering tables
-    s += 2 * align_up(sizeof(float) * (size_t)TILE_FLOATS * (size_t)tiles_cap(n_total, max_solvers));
+    s += 2 * align_up(tile_bytes(!compact) * (size_t)tiles_cap(n_total, max_solvers));
     s += align_up(sizeof(int32_t) * (size_t)tiles_cap(n_total, max_solvers));
     s += 4 * align_up(sizeof(int32_t) * (size_t)n_total);                // perm staging, announced orders (2), row -> chunk
     s += 2 * align_up(sizeof(int32_t) * (size_t)n_chunks);               // chunk_first, list_base
@@ -357,11 +357,6 @@ RoundScalars scalars(const chicle_ctx *c)
     return s;
 }
 
-// Dense rows short enough for the batched solver are stored with explicit column ids (row-major,
-// columns 0 .. d-1): twice the bytes of the dense form, and every machinery for short sparse rows
-// applies to them unchanged.
-bool dense_as_csr(int32_t d) { return d <= GRAM_MAX_ROW; }
-
 bool batched_eligible(const chicle_ctx *c)
 {
     return !c->dense && c->max_row_len <= GRAM_MAX_ROW && c->max_list <= BATCHED_MAX_LIST;
@@ -380,25 +375,36 @@ BatchedLayout batched_layout(const chicle_ctx *c)
     return L;
 }
 
-// Dense rows too wide to be stored with column ids, narrow enough for a block of 64 to sit in LDS.
-bool dense_blocked_eligible(const chicle_ctx *c)
-{
-    return c->dense && c->d <= DB_MAX_D;
-}
+// Dense rows narrow enough for two blocks of them to sit in registers.  (A caller that asks for the batched solver by name
+// gets it up to DENSE_NAMED_MAX_D columns, the limit the interface states.)
+constexpr int DENSE_NAMED_MAX_D = 320;
+bool dense_eligible(const chicle_ctx *c, int32_t max_d) { return c->dense && c->d <= max_d; }
 
-template <int LOSS>
-int launch_dense_blocked(chicle_ctx *c, const int32_t *perm)
+template <int LOSS, typename SH>
+int launch_dense_shape(chicle_ctx *c)
 {
-    const RoundScalars sc = scalars(c);
-    const int ml = std::max(c->max_list, 1);
-    const size_t sh = sizeof(float) * db_lds_floats((int)c->d) + 2 * sizeof(int) * (size_t)ml;
-    auto kern = sdca_batched_dense<LOSS>;
-    HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
-    hipLaunchKernelGGL(kern, dim3(c->K), dim3(DB_THREADS), sh, c->stream, c->chunks_dev, c->solvers_dev,
-                       c->solver_chunks_dev, c->solver_prefix_dev, perm, c->u, c->ld_v, (int)c->d, ml, sc,
-                       c->err_dev);
+    auto kern = sdca_dense<LOSS, SH>;
+    HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SH::LDS_BYTES));
+    hipLaunchKernelGGL(kern, dim3(c->K), dim3(SH::THREADS), SH::LDS_BYTES, c->stream, c->chunks_dev, c->solvers_dev,
+                       (const float *)c->tiles[c->tile_buf], c->u, c->ld_v, (int)c->d, dense_ld((int)c->d), scalars(c));
     HIP_TRY(c, hipGetLastError());
     return CHICLE_OK;
+}
+
+// The narrowest shape that holds a row: lanes per row, wavefronts, 4-column groups per lane, rows per block.
+template <int LOSS>
+int launch_dense(chicle_ctx *c)
+{
+    const int d = (int)c->d;
+    if (d <= 32) return launch_dense_shape<LOSS, DenseShape<8, 4, 1, 64>>(c);
+    if (d <= 64) return launch_dense_shape<LOSS, DenseShape<16, 4, 1, 64>>(c);
+    if (d <= 128) return launch_dense_shape<LOSS, DenseShape<32, 8, 1, 64>>(c);
+    if (d <= 256) return launch_dense_shape<LOSS, DenseShape<64, 8, 1, 64>>(c);
+    if (d <= 512) return launch_dense_shape<LOSS, DenseShape<64, 8, 2, 64>>(c);
+    if (d <= 768) return launch_dense_shape<LOSS, DenseShape<64, 8, 3, 32>>(c);
+    if (d <= 1024) return launch_dense_shape<LOSS, DenseShape<64, 8, 4, 32>>(c);
+    if (d <= 1280) return launch_dense_shape<LOSS, DenseShape<64, 8, 5, 16>>(c);
+    return launch_dense_shape<LOSS, DenseShape<64, 8, 6, 16>>(c);
 }
 
 template <int LOSS>
@@ -412,11 +418,11 @@ int launch_rowwise(chicle_ctx *c, const int32_t *perm)
         if (v_lds)
             hipLaunchKernelGGL((sdca_rowwise_dense<LOSS, 64, true>), dim3(c->K), dim3(64), sh, c->stream,
                                c->chunks_dev, c->solvers_dev, c->solver_chunks_dev, c->solver_prefix_dev,
-                               perm, c->u, c->ld_v, (int)c->d, std::max(c->max_list, 1), sc, c->err_dev);
+                               perm, c->u, c->ld_v, (int)c->d, dense_ld((int)c->d), std::max(c->max_list, 1), sc, c->err_dev);
         else
             hipLaunchKernelGGL((sdca_rowwise_dense<LOSS, 256, false>), dim3(c->K), dim3(256), sh, c->stream,
                                c->chunks_dev, c->solvers_dev, c->solver_chunks_dev, c->solver_prefix_dev,
-                               perm, c->u, c->ld_v, (int)c->d, std::max(c->max_list, 1), sc, c->err_dev);
+                               perm, c->u, c->ld_v, (int)c->d, dense_ld((int)c->d), std::max(c->max_list, 1), sc, c->err_dev);
     } else {
         const double avg = c->n_total ? (double)c->total_entries / (double)c->n_total : 0.0;
         const int ml = std::max(c->max_list, 1);
@@ -447,7 +453,12 @@ template <int LOSS>
 int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, hipStream_t stream)
 {
     const RoundScalars sc = scalars(c);
-    if (c->n_tiles > 0) {
+    if (c->dense) {
+        if (c->n_tiles > 0)
+            hipLaunchKernelGGL(gram_dense<LOSS>, dim3(c->n_tiles), dim3(GD_THREADS), 0, stream, c->chunks_dev, c->solvers_dev,
+                               c->row_chunk_dev, c->chunk_first_dev, perm, c->tile_solver_dev, c->tiles[buf],
+                               dense_ld((int)c->d), sc.c, c->err_dev);
+    } else if (c->n_tiles > 0) {
         auto kern = gram_tiles_join<LOSS>;
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)sizeof(GramShared)));
@@ -493,9 +504,14 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
     // (where every column is in the LDS-resident head there is nothing for tails to do: the head workgroups run
     // alone, and their gathers and scatters never leave LDS)
     const int n_tails = n_hot < c->d ? SPLIT_TAILS : 0;
-    const bool split = c->split_allowed && (1 + n_tails) * k_pad <= c->cu_count &&
+    const bool split = !c->dense && c->split_allowed && (1 + n_tails) * k_pad <= c->cu_count &&
                        (n_tails == 0 || sizeof(double) * (size_t)n_hot >= 2 * RING * BATCH * sizeof(RowSlot));   // a tail keeps its rows there
-    if (split) {
+    if (c->dense) {
+        seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
+        rc = launch_dense<LOSS>(c);
+        seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
+        if (rc) return rc;
+    } else if (split) {
         SplitArgs A;
         A.chunks = c->chunks_dev; A.solvers = c->solvers_dev; A.solver_chunks = c->solver_chunks_dev;
         A.solver_prefix = c->solver_prefix_dev; A.perm = perm; A.tiles = c->tiles[c->tile_buf]; A.u_all = c->u;
@@ -567,7 +583,7 @@ void launch_gap_rows_t(chicle_ctx *c, int grid_x, const WT *w, const GapScratch 
 #undef CHICLE_GAP_HOT
     } else if (c->dense)
         hipLaunchKernelGGL((gap_rows_dense<LOSS, LPRG, WT>), grid, dim3(256), 0, c->stream, c->chunks_dev,
-                           (int)c->d, w, c->l1, gs.loss, gs.conj);
+                           (int)c->d, dense_ld((int)c->d), w, c->l1, gs.loss, gs.conj);
     else
         hipLaunchKernelGGL((gap_rows_csr<LOSS, LPRG, WT>), grid, dim3(256), 0, c->stream, c->chunks_dev, w, c->l1,
                            gs.loss, gs.conj);
@@ -706,8 +722,8 @@ size_t chicle_arena_bytes(int64_t n_total, int64_t total_entries, int32_t d, int
     size_t s = fixed_bytes(n_total, d, n_chunks, max_solvers, long_rows, compact, total_entries);
     // chunk blocks: exact array bytes plus alignment slack per array and chunk
     const size_t per_chunk_slack = 8 * ALIGN + 2 * sizeof(float) * ENTRY_SLACK;
-    if (dense && !dense_as_csr(d))
-        s += sizeof(float) * (size_t)total_entries + 4 * sizeof(float) * (size_t)n_total;
+    if (dense)
+        s += sizeof(float) * (size_t)(total_entries / d + n_chunks) * (size_t)dense_ld(d) + 4 * sizeof(float) * (size_t)n_total;
     else
         s += (sizeof(int32_t) * (compact ? 2 : 1) + sizeof(float)) * ((size_t)total_entries + (size_t)n_chunks) +
              sizeof(int32_t) * ((size_t)n_total + (size_t)n_chunks) + 4 * sizeof(float) * (size_t)n_total;
@@ -731,8 +747,7 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
     if (!c) return CHICLE_ENOMEM;
     c->loss = loss; c->n_total = n_total; c->d = d; c->ld_v = pad_d(d); c->lambda = lambda;
     c->n_chunks = n_chunks; c->max_solvers = max_solvers;
-    c->api_dense = dense != 0;
-    c->dense = c->api_dense && !dense_as_csr(d);
+    c->dense = dense != 0;
     c->total_entries = total_entries;
     c->arena = (char *)device_arena; c->arena_bytes = arena_bytes;
     c->stream = (hipStream_t)hip_stream;
@@ -747,14 +762,14 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
     c->w64 = (double *)carve(c, sizeof(double) * (size_t)c->ld_v);
     c->tmp_a = (float *)carve(c, sizeof(float) * (size_t)c->ld_v);
     c->tmp_b = (float *)carve(c, sizeof(float) * (size_t)c->ld_v);
-    c->long_rows = !c->api_dense && (double)total_entries > LONG_ROW_AVG * (double)n_total;
-    c->compact = !c->api_dense;
+    c->long_rows = !c->dense && (double)total_entries > LONG_ROW_AVG * (double)n_total;
+    c->compact = !c->dense;
     c->u_capacity = private_floats(total_entries, c->ld_v, max_solvers, c->long_rows);
     c->u = (float *)carve(c, sizeof(float) * (size_t)c->u_capacity);
     c->rank_of = (int32_t *)carve(c, sizeof(int32_t) * (size_t)d);
     c->col_of = (int32_t *)carve(c, sizeof(int32_t) * (size_t)d);
-    c->tiles[0] = (float *)carve(c, sizeof(float) * (size_t)TILE_FLOATS * (size_t)c->max_tiles);
-    c->tiles[1] = (float *)carve(c, sizeof(float) * (size_t)TILE_FLOATS * (size_t)c->max_tiles);
+    c->tiles[0] = (float *)carve(c, tile_bytes(c->dense) * (size_t)c->max_tiles);
+    c->tiles[1] = (float *)carve(c, tile_bytes(c->dense) * (size_t)c->max_tiles);
     c->tile_solver_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->max_tiles);
     c->perm_stage = (int32_t *)carve(c, sizeof(int32_t) * (size_t)n_total);
     c->perm_ahead[0] = (int32_t *)carve(c, sizeof(int32_t) * (size_t)n_total);
@@ -826,7 +841,7 @@ static int load_common(chicle_ctx *c, int32_t chunk_id, int32_t n_rows, int64_t 
     if (c->rows_loaded + n_rows > c->n_total) return fail(c, CHICLE_EINVAL, "more rows than n_total");
     if (c->entries_loaded + entries > c->total_entries)
         return fail(c, CHICLE_EINVAL, "more stored entries than total_entries");
-    if (c->used + chunk_bytes(c->dense, c->compact, n_rows, entries) > c->arena_bytes)
+    if (c->used + chunk_bytes(c->dense, c->compact, n_rows, c->dense ? (int64_t)n_rows * dense_ld((int)c->d) : entries) > c->arena_bytes)
         return fail(c, CHICLE_ENOMEM, "chunk store full");
     return CHICLE_OK;
 }
@@ -877,7 +892,7 @@ int chicle_load_chunk_csr(chicle_ctx *c, int32_t chunk_id, int32_t n_rows, const
                           const int32_t *col, const float *val, const float *y, const float *alpha0)
 {
     if (!c) return CHICLE_EINVAL;
-    if (c->api_dense) return fail(c, CHICLE_EINVAL, "context holds dense chunks");
+    if (c->dense) return fail(c, CHICLE_EINVAL, "context holds dense chunks");
     return load_csr(c, chunk_id, n_rows, row_ptr, col, val, y, alpha0);
 }
 
@@ -933,16 +948,9 @@ int chicle_load_chunk_dense(chicle_ctx *c, int32_t chunk_id, int32_t n_rows, con
                             const float *y, const float *alpha0)
 {
     if (!c) return CHICLE_EINVAL;
-    if (!c->api_dense) return fail(c, CHICLE_EINVAL, "context holds CSR chunks");
+    if (!c->dense) return fail(c, CHICLE_EINVAL, "context holds CSR chunks");
     if (!X || n_rows <= 0) return fail(c, CHICLE_EINVAL, "chunk %d: X NULL or no rows", chunk_id);
     const int64_t entries = (int64_t)n_rows * c->d;
-    if (!c->dense) {                       // short dense rows: explicit column ids
-        if (entries > INT32_MAX) return fail(c, CHICLE_EINVAL, "chunk %d too large", chunk_id);
-        std::vector<int32_t> rp(n_rows + 1), cols((size_t)entries);
-        for (int32_t r = 0; r <= n_rows; ++r) rp[r] = r * c->d;
-        for (int64_t p = 0; p < entries; ++p) cols[p] = (int32_t)(p % c->d);
-        return load_csr(c, chunk_id, n_rows, rp.data(), cols.data(), X, y, alpha0);
-    }
     int rc = load_common(c, chunk_id, n_rows, entries);
     if (rc) return rc;
     rc = check_state_arrays(c, chunk_id, n_rows, y, alpha0);
@@ -959,10 +967,18 @@ int chicle_load_chunk_dense(chicle_ctx *c, int32_t chunk_id, int32_t n_rows, con
     }
     ChunkDev ch{};
     ch.n_rows = n_rows; ch.nnz = entries; ch.row_base = (int32_t)c->rows_loaded;
-    float *xd = (float *)carve(c, sizeof(float) * (size_t)entries);
+    const int ld = dense_ld((int)c->d);
+    float *xd = (float *)carve(c, sizeof(float) * (size_t)n_rows * (size_t)ld);
     if (!xd) return fail(c, CHICLE_ENOMEM, "chunk store full");
     ch.val = xd;
-    HIP_TRY(c, hipMemcpyAsync(xd, X, sizeof(float) * (size_t)entries, hipMemcpyHostToDevice, c->stream));
+    std::vector<float> padded;     // rows end in zero columns up to a multiple of four (lives until finish_load has waited)
+    const float *from = X;
+    if (ld != c->d) {
+        padded.assign((size_t)n_rows * (size_t)ld, 0.f);
+        for (int32_t r = 0; r < n_rows; ++r) std::memcpy(&padded[(size_t)r * (size_t)ld], X + (int64_t)r * c->d, sizeof(float) * (size_t)c->d);
+        from = padded.data();
+    }
+    HIP_TRY(c, hipMemcpyAsync(xd, from, sizeof(float) * (size_t)n_rows * (size_t)ld, hipMemcpyHostToDevice, c->stream));
     rc = finish_load(c, chunk_id, ch, y, alpha0, q);
     if (rc == CHICLE_OK) c->max_row_len = c->d;
     return rc;
@@ -1025,7 +1041,7 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
             tile_solver[t] = k;
     // work items of the gap kernels: blocks of 256/LPR rows inside a chunk
     const double avg = c->dense ? (double)c->d : (double)c->total_entries / (double)c->n_total;
-    c->gap_lpr = choose_lpr(avg);
+    c->gap_lpr = choose_lpr(c->dense ? avg / 4 : avg);
     const int rows_per_item = 256 / c->gap_lpr;
     std::vector<int32_t> items(c->n_chunks + 1, 0);
     for (int32_t i = 0; i < c->n_chunks; ++i)
@@ -1187,15 +1203,13 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
         c->ahead_buf = 1 - c->ahead_buf;
         c->ahead_valid = true;
     }
-    bool batched = false, dense_blocked = false;
+    bool batched = false;
     if (c->solver_kind == CHICLE_SOLVER_BATCHED) {
-        dense_blocked = dense_blocked_eligible(c);
-        if (!dense_blocked && !batched_eligible(c))
-            return fail(c, CHICLE_EINVAL, "batched solver needs sparse rows of at most %d entries and at most %d chunks per solver, or dense rows of at most %d columns", GRAM_MAX_ROW, BATCHED_MAX_LIST, DB_MAX_D);
-        batched = !dense_blocked;
+        batched = dense_eligible(c, DENSE_NAMED_MAX_D) || batched_eligible(c);
+        if (!batched)
+            return fail(c, CHICLE_EINVAL, "batched solver needs sparse rows of at most %d entries and at most %d chunks per solver, or dense rows of at most %d columns", GRAM_MAX_ROW, BATCHED_MAX_LIST, DENSE_NAMED_MAX_D);
     } else if (c->solver_kind == CHICLE_SOLVER_AUTO) {
-        batched = batched_eligible(c);
-        dense_blocked = !batched && dense_blocked_eligible(c);
+        batched = dense_eligible(c, DENSE_MAX_D) || batched_eligible(c);
     }
     seg_begin(c, CHICLE_SEG_LOCAL_EPOCH);
     int rc = CHICLE_OK;
@@ -1205,12 +1219,6 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
             rc = c->loss == CHICLE_LOSS_HINGE ? launch_batched<0>(c, perm_device, tiles_ready, perm_next_device)
                  : c->loss == CHICLE_LOSS_SQUARED ? launch_batched<1>(c, perm_device, tiles_ready, perm_next_device)
                                                   : launch_batched<2>(c, perm_device, tiles_ready, perm_next_device);
-        } else if (dense_blocked) {
-            seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
-            rc = c->loss == CHICLE_LOSS_HINGE ? launch_dense_blocked<0>(c, perm_device)
-                 : c->loss == CHICLE_LOSS_SQUARED ? launch_dense_blocked<1>(c, perm_device)
-                                                  : launch_dense_blocked<2>(c, perm_device);
-            seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
         } else {
             seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
             rc = c->loss == CHICLE_LOSS_HINGE ? launch_rowwise<0>(c, perm_device)
@@ -1506,7 +1514,7 @@ int chicle_debug_gram(chicle_ctx *c, const int32_t *perm_device, float *tiles_ou
 {
     if (!c || !perm_device) return CHICLE_EINVAL;
     if (c->state != ST_READY) return fail(c, CHICLE_ESTATE, "needs an assignment and no pending epoch");
-    if (!batched_eligible(c)) return fail(c, CHICLE_EINVAL, "batched solver not available for this data");
+    if (!batched_eligible(c) && !dense_eligible(c, GRAM_MAX_ROW)) return fail(c, CHICLE_EINVAL, "batched solver not available for this data");
     if (n_tiles_out) *n_tiles_out = c->n_tiles;
     int rc = drop_ahead(c);
     if (rc) return rc;
@@ -1517,7 +1525,20 @@ int chicle_debug_gram(chicle_ctx *c, const int32_t *perm_device, float *tiles_ou
     if (tiles_out) {
         const int64_t want = (int64_t)c->n_tiles * TILE_FLOATS;
         if (capacity_floats < want) return fail(c, CHICLE_EINVAL, "need room for %lld floats", (long long)want);
-        HIP_TRY(c, hipMemcpyAsync(tiles_out, c->tiles[c->tile_buf], sizeof(float) * (size_t)want, hipMemcpyDeviceToHost, c->stream));
+        if (c->dense) {        // in the sparse solver's layout, formed in the other tile set a few tiles at a time
+            float *out = c->tiles[1 - c->tile_buf];
+            const int at_once = (int)(c->max_tiles * DENSE_TILE_FLOATS / TILE_FLOATS);
+            for (int32_t t0 = 0; t0 < c->n_tiles; t0 += at_once) {
+                const int n = std::min(at_once, c->n_tiles - t0);
+                auto kern = c->loss == CHICLE_LOSS_HINGE ? dense_tiles_plain<0> : c->loss == CHICLE_LOSS_SQUARED ? dense_tiles_plain<1> : dense_tiles_plain<2>;
+                hipLaunchKernelGGL(kern, dim3(n), dim3(256), 0, c->stream, c->solvers_dev, c->tile_solver_dev,
+                                   (const float *)c->tiles[c->tile_buf], t0, (int)c->d, scalars(c).c, out);
+                HIP_TRY(c, hipGetLastError());
+                HIP_TRY(c, hipMemcpyAsync(tiles_out + (int64_t)t0 * TILE_FLOATS, out, sizeof(float) * (size_t)n * TILE_FLOATS, hipMemcpyDeviceToHost, c->stream));
+                HIP_TRY(c, hipStreamSynchronize(c->stream));
+            }
+        } else
+            HIP_TRY(c, hipMemcpyAsync(tiles_out, c->tiles[c->tile_buf], sizeof(float) * (size_t)want, hipMemcpyDeviceToHost, c->stream));
     }
     return check_deferred(c);
 }

@@ -48,8 +48,33 @@ __device__ __forceinline__ float logistic_step(float m, float r, float a, float 
     return ap - a;
 }
 
+// Logistic loss: a' = 1 / (1 + exp(-s)) with s the root of f(s) = m - s - r (a'(s) - a), where m = -y z and r = q / c.
+// Returns the root to within about a hundredth (the series of logistic_block take it from there), one row per lane.  f
+// decreases strictly (slope in [-1 - r/4, -1]) and, a' lying in (0, 1), its root lies in [m - r (1 - a), m + r a].
+// Newton steps inside that bracket from the previous a's own s, where the root is late in a run; a bisection step
+// whenever Newton would leave the bracket or fails to halve the last step (r can be in the hundreds, where plain
+// Newton cycles between the two flat ends of the sigmoid).
+__device__ __forceinline__ float logistic_root(float m, float r, float a)
+{
+    float lo = m - r * (1.0f - a), hi = m + r * a;
+    const float s0 = a > 1e-6f && a < 1.0f - 1e-6f ? __logf(a * __builtin_amdgcn_rcpf(1.0f - a)) : m + r * (a - 0.5f);
+    float s = fminf(fmaxf(s0, lo), hi), dx = hi - lo;
+    for (int it = 0; it < 48; ++it) {
+        const float e = __expf(-fabsf(s));
+        const float t = __builtin_amdgcn_rcpf(1.0f + e);
+        const float f = (m - s) - r * ((s >= 0.f ? t : e * t) - a);
+        if (f > 0.f) lo = s; else hi = s;
+        float step = f * __builtin_amdgcn_rcpf(fmaf(r, e * t * t, 1.0f)), to = s + step;
+        if (!(to >= lo && to <= hi) || fabsf(2.0f * step) > fabsf(dx)) { to = 0.5f * (lo + hi); step = to - s; }
+        s = to;
+        dx = step;
+        if (fabsf(dx) <= 1e-2f) break;
+    }
+    return s;
+}
+
 // One dual step of the logistic loss computed by a whole wavefront from uniform arguments (see
-// logistic_step for the equation).  f decreases strictly, so the 64 lanes evaluate it at 64 evenly spaced
+// logistic_root for the equation).  f decreases strictly, so the 64 lanes evaluate it at 64 evenly spaced
 // points of the bracket and the first lane with f <= 0 narrows the bracket 63-fold; when the bracket is so
 // narrow that a chord of f misses the root by less than fp32 resolution (|f''| <= 0.0963 r, |f'| >= 1:
 // error <= 0.012 h^2 r), the root and a' are read off the chord.  [lo, lo + w] is a bracket of the root:
@@ -81,6 +106,111 @@ __device__ __forceinline__ float logistic_step_wave(float m, float r, float a, f
     const float den = f0 - f1;
     const float th = den > 0.f ? fminf(fmaxf(f0 * __builtin_amdgcn_rcpf(den), 0.f), 1.f) : 0.5f;
     return fmaf(th, a1 - a0, a0) - a;
+}
+
+// The same equation followed through a block.  A lane keeps its row's m, and s, the root for an earlier m, with what the
+// sigmoid does there: p = a'(s) and its derivatives, from which the step for the current m follows as a series in
+//     d = x g,   x = (m - s) - r (p - a),   g = 1 / (1 + r p').
+// The root is s + ds with ds = d + c2 d^2 + c3 d^3 + c4 d^4 + ... (the inverse of f's own series: c2 = -A, c3 = 2 A^2 - B,
+// c4 = -(5 A^3 - 5 A B + C) with A, B, C = r g times p'' / 2, p''' / 6, p'''' / 24, bounded for every r because
+// r p' g < 1), and a' follows by inserting ds into the sigmoid's series: a' - a = q0 + q1 d + q2 d^2 + q3 d^3 + q4 d^4.
+// Nothing of this but d depends on the current m: what a step waits for is one multiply-add for d, three for the
+// polynomial and the lane read, where a search of the row's bracket evaluates the sigmoid at least once per step.
+struct LogisticTrack {
+    float s, g, h, c2, c3, c4, q0, q1, q2, q3, q4;      // h: d = m g + h
+    __device__ __forceinline__ void at(float root, float a, float r, bool live)
+    {
+        s = root;
+        const float e = __expf(-fabsf(s));
+        const float t = __builtin_amdgcn_rcpf(1.0f + e);
+        const float p = s >= 0.f ? t : e * t;
+        const float p1 = e * t * t;                                        // p' = p (1 - p) without cancellation
+        const float k = s >= 0.f ? (e - 1.0f) * t : (1.0f - e) * t;        // 1 - 2 p
+        const float p2 = 0.5f * p1 * k;
+        const float p3 = p1 * fmaf(-6.0f, p1, 1.0f) * (1.0f / 6.0f);
+        const float p4 = p1 * k * fmaf(-12.0f, p1, 1.0f) * (1.0f / 24.0f);
+        g = live ? __builtin_amdgcn_rcpf(fmaf(r, p1, 1.0f)) : 0.f;         // a row that takes no step: d = 0, a' - a = 0
+        const float rg = r * g, A = rg * p2, B = rg * p3;
+        c2 = -A;
+        c3 = fmaf(2.0f * A, A, -B);
+        c4 = -fmaf(5.0f * A, fmaf(A, A, -B), rg * p4);
+        q0 = live ? p - a : 0.f;
+        h = -fmaf(r, q0, s) * g;
+        q1 = p1;
+        q2 = fmaf(p1, c2, p2);
+        q3 = fmaf(p1, c3, fmaf(2.0f * p2, c2, p3));
+        q4 = fmaf(p1, c4, fmaf(p2, fmaf(c2, c2, 2.0f * c3), fmaf(3.0f * p3, c2, p4)));
+    }
+};
+// Largest |d| for which the series is used: its error in a' there is at most 1.7e-8 (r from 1e-3 to 3e3, all s; half a
+// unit in the last place of a' is 3e-8).
+constexpr float LOGISTIC_SERIES = 0.07f;
+
+// The BR steps of a block with the logistic loss: lane i owns row i; m = -y z against the private vector at the start
+// of the block, root: the root for it, r = q / c (0: a row that takes no step); coef4(jq) returns the lane's T of steps
+// 4 jq .. 4 jq + 3, and also4(jq, d0 .. d3) sees their results.  Four steps at a time: the expansions are renewed at the
+// current m, the four steps taken from the series, and then the four rows' |d| are looked at; where one was too large the
+// four are taken again, with the expansions renewed before each, or the row's bracket searched.
+template <int BR, typename COEF, typename ALSO>
+__device__ __forceinline__ float logistic_block(float m, float a, float r, float root, int lane, COEF coef4, ALSO also4)
+{
+#define CHICLE_LANE(x, j) __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j))
+    const bool live = r > 0.f;
+    LogisticTrack k;
+    float mine = 0.f;
+    k.s = root;
+    float d = 0.f;
+    auto renew = [&]() __attribute__((always_inline)) {
+        const float dc = fminf(fmaxf(d, -0.5f), 0.5f);
+        const float ds = fabsf(d) <= LOGISTIC_SERIES ? d * fmaf(d, fmaf(d, fmaf(d, k.c4, k.c3), k.c2), 1.0f) : dc;
+        k.at(k.s + ds, a, r, live);
+        d = fmaf(m, k.g, k.h);
+    };
+    auto step = [&]() __attribute__((always_inline)) {
+        const float d2 = d * d;
+        return fmaf(d, fmaf(d2, fmaf(d, k.q4, k.q3), fmaf(d, k.q2, k.q1)), k.q0);
+    };
+    k.at(root, a, r, live);
+    d = fmaf(m, k.g, k.h);
+#pragma unroll 1
+    for (int jq = 0; jq < BR / 4; ++jq) {
+        const float4_v T4 = coef4(jq);
+        if (jq > 0) renew();
+        const float m_before = m;
+        float dj[4];
+        bool bad = false;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            bad = bad || (lane == 4 * jq + e && fabsf(d) > LOGISTIC_SERIES);
+            dj[e] = CHICLE_LANE(step(), 4 * jq + e);
+            m = fmaf(dj[e], T4[e], m);
+            d = fmaf(m, k.g, k.h);
+        }
+        if (__ballot(bad)) {
+            m = m_before;
+            d = fmaf(m, k.g, k.h);
+#pragma unroll 1
+            for (int e = 0; e < 4; ++e) {
+                const int j = 4 * jq + e;
+                for (int it = 0; it < 3 && fabsf(CHICLE_LANE(d, j)) > LOGISTIC_SERIES; ++it) renew();
+                float x = CHICLE_LANE(step(), j);
+                if (fabsf(CHICLE_LANE(d, j)) > LOGISTIC_SERIES) {
+                    // f falls at least as fast as s grows: the root lies between s and s + f(s), f(s) = d / g
+                    const float sj = CHICLE_LANE(k.s, j), xj = CHICLE_LANE(d, j) / CHICLE_LANE(k.g, j);
+                    x = logistic_step_wave(CHICLE_LANE(m, j), CHICLE_LANE(r, j), CHICLE_LANE(a, j), sj + fminf(xj, 0.f), fabsf(xj), lane);
+                }
+                const float Te = e == 0 ? T4[0] : e == 1 ? T4[1] : e == 2 ? T4[2] : T4[3];
+                m = fmaf(x, Te, m);
+                d = fmaf(m, k.g, k.h);
+                if (e == 0) dj[0] = x; else if (e == 1) dj[1] = x; else if (e == 2) dj[2] = x; else dj[3] = x;
+            }
+        }
+        also4(jq, dj[0], dj[1], dj[2], dj[3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mine = lane == 4 * jq + e ? dj[e] : mine;
+    }
+#undef CHICLE_LANE
+    return mine;
 }
 
 // rw: residual at w (see above; logistic: -y x_i.w); xu = x_i . u_k.  The arguments are the same in every
@@ -280,7 +410,7 @@ template <int LOSS, int BLOCK, bool V_LDS>
 __global__ __launch_bounds__(BLOCK) void sdca_rowwise_dense(
     const ChunkDev *__restrict__ chunks, const SolverDev *__restrict__ solvers,
     const int32_t *__restrict__ solver_chunks, const int32_t *__restrict__ solver_prefix,
-    const int32_t *__restrict__ perm, float *u_all, int64_t ld_v, int d, int max_list,
+    const int32_t *__restrict__ perm, float *u_all, int64_t ld_v, int d, int ld, int max_list,
     RoundScalars sc, int *err)
 {
     extern __shared__ int lists[];
@@ -314,7 +444,7 @@ __global__ __launch_bounds__(BLOCK) void sdca_rowwise_dense(
         const RowState st = ch.st[r];
         const float q = st.q;
         if (q == 0.0f) continue;
-        const float *x = ch.val + (int64_t)r * d;
+        const float *x = ch.val + (int64_t)r * ld;
         const float y = st.y;
         const float a = st.alpha;
         const float rw = st.rw;

@@ -1,0 +1,34 @@
+"""The dense solver at the edges of the shapes it chooses from (lanes per row, columns per lane, rows per block),
+against the oracle: every loss, ragged chunks, a block of one row, an empty row, a solver without rows."""
+import numpy as np
+import pytest
+
+from harness import run_lockstep
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("loss", ["hinge", "squared", "logistic"])
+@pytest.mark.parametrize("d,n", [(1, 130), (3, 65), (32, 333), (33, 200), (64, 129), (65, 333), (128, 97), (129, 200),
+                                 (256, 333), (257, 160), (512, 200), (513, 130), (768, 97), (769, 130), (1021, 200),
+                                 (1024, 97), (1025, 130), (1280, 97), (1281, 130), (1536, 97), (1537, 70)])
+def test_dense_widths(oracle_mod, loss, d, n):
+    import torch
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    assert torch.cuda.is_available()
+    g = np.random.default_rng(d)
+    X = (g.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    X[5] = 0
+    y = g.standard_normal(n).astype(np.float32) if loss == "squared" else np.where(g.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    bounds = np.array([0, 1, 40, 64, n], dtype=np.int64)
+    p = Problem("width", loss, n, d, 0.02, y, bounds, X=X)
+    K = 4
+    table = np.array([0, 1, 1, 3], dtype=np.int32)             # one row; 63 rows; none; the rest
+    print("\ncase dense n=%d d=%d %s" % (n, d, loss), flush=True)
+    # An update is a sum of up to n steps' terms in fp32: its error is bounded by about n 2^-24 of the terms' sizes.
+    # In one to three dimensions ridge is solved after two rounds and the third's update, a difference of the
+    # solvers' parts thousands of times its own size, is below that bound relative to itself.
+    rounds = 2 if d <= 3 else 3
+    run_lockstep({"seed": 3, "rounds": rounds, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1,
+                 ahead=d % 2 == 0, tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)
