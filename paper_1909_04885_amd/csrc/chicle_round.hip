@@ -1537,8 +1537,14 @@ int chicle_debug_gram(chicle_ctx *c, const int32_t *perm_device, float *tiles_ou
                 HIP_TRY(c, hipMemcpyAsync(tiles_out + (int64_t)t0 * TILE_FLOATS, out, sizeof(float) * (size_t)n * TILE_FLOATS, hipMemcpyDeviceToHost, c->stream));
                 HIP_TRY(c, hipStreamSynchronize(c->stream));
             }
-        } else
-            HIP_TRY(c, hipMemcpyAsync(tiles_out, c->tiles[c->tile_buf], sizeof(float) * (size_t)want, hipMemcpyDeviceToHost, c->stream));
+        } else {
+            std::vector<float> raw((size_t)want);
+            HIP_TRY(c, hipMemcpyAsync(raw.data(), c->tiles[c->tile_buf], sizeof(float) * (size_t)want, hipMemcpyDeviceToHost, c->stream));
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+            for (int64_t t = 0; t < want; t += TILE_FLOATS)
+                for (int jp = 0; jp < TILE_W; ++jp)
+                    for (int i = 0; i < BATCH; ++i) tiles_out[t + jp * BATCH + i] = raw[(size_t)(t + tile_at(jp, i))];
+        }
     }
     return check_deferred(c);
 }

@@ -320,11 +320,15 @@ __global__ __launch_bounds__(GRAM_THREADS) void gram_tiles_join(
             const int i = tid & 63;
             const float si = R.scale[i] * R.sgn[BATCH + i];
 #pragma unroll
-            for (int k = 0; k < TILE_FLOATS / GRAM_THREADS; ++k) {
-                const int jp = (tid >> 6) + k * (GRAM_THREADS / 64);
-                float g = 0.f;
-                if (jp < BATCH || jp - BATCH < i) g = (float)sh.G[jp][i] * si * R.sgn[jp];
-                out[jp * BATCH + i] = g;
+            for (int k = 0; k < TILE_FLOATS / 4 / GRAM_THREADS; ++k) {
+                const int jq = (tid >> 6) + k * (GRAM_THREADS / 64);
+                float4_v v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int jp = 4 * jq + e;
+                    v[e] = jp < BATCH || jp - BATCH < i ? (float)sh.G[jp][i] * si * R.sgn[jp] : 0.f;
+                }
+                *reinterpret_cast<float4_v *>(out + tile_at(4 * jq, i)) = v;
             }
         }
         // this tile's own rows are the next tile's previous block; its own rows have arrived by now

@@ -26,7 +26,9 @@ namespace chicle {
 
 constexpr int BATCH = 64;                    // rows per block = lanes of the chain wavefront
 constexpr int TILE_W = 2 * BATCH;            // T rows: previous block (cross part), then own block
-constexpr int TILE_FLOATS = BATCH * TILE_W;  // layout [jp][i]: jp in [0,128), i in [0,64)
+constexpr int TILE_FLOATS = BATCH * TILE_W;  // T[jp][i], jp in [0,128), i in [0,64), stored as [jp / 4][i][jp % 4]:
+                                             // a lane of the chain reads four steps' coefficients at once
+__host__ __device__ inline int tile_at(int jp, int i) { return ((jp >> 2) * BATCH + i) * 4 + (jp & 3); }
 constexpr int GRAM_MAX_ROW = 48;             // longest sparse row the batched solver accepts
 constexpr int LPR = 8;                       // helper lanes per row
 constexpr int ENT = GRAM_MAX_ROW / LPR;      // entries per helper lane
@@ -71,8 +73,8 @@ struct BatchedShared {
     RowSlot rows[RING][BATCH];
     float t0[RING][BATCH], lo[RING][BATCH], hi[RING][BATCH];
     float delta[2][BATCH];
-    float Tw[2][BATCH][BATCH];   // own part of block i's T: [j][lane]
-    float Tx[2][BATCH][BATCH];   // cross part of block i+1's T: [j][lane]
+    float4_v Tw[2][BATCH / 4][BATCH];   // own part of block i's T: [j / 4][lane][j % 4]
+    float4_v Tx[2][BATCH / 4][BATCH];   // cross part of block i+1's T, likewise
     int hb;
     int dead;                    // split solver: a wait for a partner workgroup has given up
     int xflag;                   // split solver: iteration whose ring words are in xv
@@ -80,7 +82,9 @@ struct BatchedShared {
     float xv[BATCH];             // split solver: what the partner sent (steps, or partial dot products)
 };
 
-// The chain: 64 sequential steps of one block.  Lane i owns row i.
+// The chain: 64 sequential steps of one block.  Lane i owns row i.  A step is a clamp, a lane read and a multiply-add that
+// wait for each other; the lane's coefficients come from LDS four steps at a time, well ahead of their use, and the product
+// with the cross part fills the slots the lane read leaves.
 template <int LOSS>
 __device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c)
 {
@@ -89,46 +93,36 @@ __device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, 
     const float lo = sh.lo[ring][lane], hi = sh.hi[ring][lane];
     float x = 0.f;
 #pragma unroll
-    for (int j = 0; j < BATCH; ++j) {
-        const float d = clamp_step<LOSS>(t, lo, hi);
-        const float s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), j));
-        t = fmaf(s, sh.Tw[buf][j][lane], t);
-        x = fmaf(s, sh.Tx[buf][j][lane], x);
+    for (int jq = 0; jq < BATCH / 4; ++jq) {
+        const float4_v T = sh.Tw[buf][jq][lane], X = sh.Tx[buf][jq][lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float d = clamp_step<LOSS>(t, lo, hi);
+            const float s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), 4 * jq + e));
+            t = fmaf(s, T[e], t);
+            x = fmaf(s, X[e], x);
+        }
     }
     sh.delta[buf][lane] = clamp_step<LOSS>(t, lo, hi);
     x_carry = x;
 }
 
-// The same for the logistic loss, whose step has no closed form.  Lane i owns m_i = -y_i z_i; step j is
-// solved by the whole wavefront from lane j's values, then
-//     m_i += delta_j T_ij,   T_ij = -y_i y_j G_ij / c.
-// The helpers have solved every row's equation for its m at the start of the block (slot t0; the root in
-// slot lo).  The root moves in the direction of m and by no more (ds/dm = 1 / (1 + r a'(1 - a')) lies in
-// (0, 1]), so by the time of the row's turn it lies between the old root and the old root + (m - t0): a
-// bracket as narrow as the block's own corrections, for which one evaluation is usually enough.
+// The same for the logistic loss, whose step has no closed form: lane i owns m_i = -y_i z_i and
+//     m_i += delta_j T_ij,   T_ij = -y_i y_j G_ij / c
+// (logistic_block; the helpers leave m at the start of the block in slot t0 and the root for it in slot lo).
 template <>
 __device__ __forceinline__ void chain_block<2>(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c)
 {
     const int ring = i & (RING - 1), buf = i & 1;
-    const float m0 = sh.t0[ring][lane], s0 = sh.lo[ring][lane];
-    float m = m0 + x_carry;
     const RowSlot &row = sh.rows[ring][lane];
     const float a = row.alpha, r = row.len > 0 ? row.q * inv_c : 0.f;      // r = 0 marks a row to skip
-    float x = 0.f, mine = 0.f;
-#pragma unroll 2
-    for (int j = 0; j < BATCH; ++j) {
-        const float mj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), j));
-        const float aj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), j));
-        const float rj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), j));
-        const float dm = mj - __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m0), j));
-        const float sj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s0), j));
-        float d = 0.f;
-        if (rj > 0.f) d = logistic_step_wave(mj, rj, aj, sj + fminf(dm, 0.f), fabsf(dm), lane);
-        m = fmaf(d, sh.Tw[buf][j][lane], m);
-        x = fmaf(d, sh.Tx[buf][j][lane], x);
-        mine = lane == j ? d : mine;
-    }
-    sh.delta[buf][lane] = mine;
+    float x = 0.f;
+    sh.delta[buf][lane] = logistic_block<BATCH>(
+        sh.t0[ring][lane] + x_carry, a, r, sh.lo[ring][lane], lane, [&](int jq) { return sh.Tw[buf][jq][lane]; },
+        [&](int jq, float d0, float d1, float d2, float d3) {
+            const float4_v X = sh.Tx[buf][jq][lane];
+            x = fmaf(d0, X[0], fmaf(d1, X[1], fmaf(d2, X[2], fmaf(d3, X[3], x))));
+        });
     x_carry = x;
 }
 
@@ -373,7 +367,7 @@ __global__ __launch_bounds__(BATCHED_THREADS) void sdca_batched_csr(
                         } else {
                             t0 = r.rw - r.y * part;
                             const float rr = r.q * sc.inv_c;
-                            logistic_step(t0, rr, r.alpha, t0 + rr * (r.alpha - 0.5f), &lo);   // lo: the root for t0
+                            lo = logistic_root(t0, rr, r.alpha);
                         }
                     }
                     sh.t0[ring][rho] = t0; sh.lo[ring][rho] = lo; sh.hi[ring][rho] = hi;

@@ -344,7 +344,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
                         } else {
                             t0 = r_g.rw - r_g.y * part;
                             const float rr = r_g.q * sc.inv_c;
-                            logistic_step(t0, rr, r_g.alpha, t0 + rr * (r_g.alpha - 0.5f), &lo);   // lo: the root for t0
+                            lo = logistic_root(t0, rr, r_g.alpha);
                         }
                     }
                     sh.t0[ring][rho] = t0;

@@ -42,8 +42,6 @@ struct DenseRow {
 };
 constexpr int DENSE_TILE_FLOATS = BATCH * BATCH + BATCH * (int)(sizeof(DenseRow) / sizeof(float));
 
-__host__ __device__ inline int tile_at(int j, int i) { return ((j >> 2) * BATCH + i) * 4 + (j & 3); }
-
 constexpr int GD_THREADS = 256;
 constexpr int GD_COLS = 64;                      // columns of the block in LDS at a time
 constexpr int GD_LD = GD_COLS + 4;               // 16-byte aligned rows, spread over the banks

@@ -19,35 +19,6 @@
 
 namespace chicle {
 
-// Logistic loss, one dual step: a' = 1 / (1 + exp(-s)) with s the root of f(s) = m - s - r (a'(s) - a),
-// where m = -y z and r = q / c; returns a' - a.  f decreases strictly (slope in [-1 - r/4, -1]) and, a'
-// lying in (0, 1), its root lies in [m - r (1 - a), m + r a].  Newton steps from s0 inside that bracket; a
-// bisection step whenever Newton would leave it or fails to halve the last step (r can be in the
-// hundreds, where plain Newton cycles between the two flat ends of the sigmoid).  *root receives s.
-__device__ __forceinline__ float logistic_step(float m, float r, float a, float s0, float *root = nullptr)
-{
-    float lo = m - r * (1.0f - a), hi = m + r * a;
-    float s = fminf(fmaxf(s0, lo), hi), dx_old = hi - lo, dx = dx_old, ap, f, df;
-    auto eval = [&]() {
-        const float e = __expf(-fabsf(s));
-        ap = s >= 0.f ? 1.0f / (1.0f + e) : e / (1.0f + e);
-        f = (m - s) - r * (ap - a);
-        df = -(1.0f + r * ap * (1.0f - ap));
-    };
-    eval();
-    for (int it = 0; it < 48; ++it) {
-        const bool leaves = ((s - hi) * df - f) * ((s - lo) * df - f) > 0.f;
-        dx_old = dx;
-        if (leaves || fabsf(2.0f * f) > fabsf(dx_old * df)) { dx = 0.5f * (hi - lo); s = lo + dx; }
-        else { dx = f / df; s -= dx; }
-        eval();
-        if (f > 0.f) lo = s; else hi = s;
-        if (fabsf(dx) <= 1e-7f * (1.0f + fabsf(s))) break;     // the step is below fp32 resolution of s
-    }
-    if (root) *root = s;
-    return ap - a;
-}
-
 // Logistic loss: a' = 1 / (1 + exp(-s)) with s the root of f(s) = m - s - r (a'(s) - a), where m = -y z and r = q / c.
 // Returns the root to within about a hundredth (the series of logistic_block take it from there), one row per lane.  f
 // decreases strictly (slope in [-1 - r/4, -1]) and, a' lying in (0, 1), its root lies in [m - r (1 - a), m + r a].
