@@ -76,8 +76,9 @@ enum chicle_solver_kind {
                                      a solver may use all processors of its node) */
     CHICLE_SOLVER_BATCHED = 2,    /* blocks of 64 rows via their Gram matrix, same sequence of steps: sparse rows
                                      of at most 48 entries, or dense rows of at most 320 columns; else EINVAL at
-                                     the pass (AUTO takes the blocks for dense rows of up to 1536 columns).  For
-                                     sparse rows, where the columns do
+                                     the pass (AUTO takes blocks for dense rows of up to 1536 columns, and for sparse
+                                     rows of any length where the columns that several rows of a solver hold fit
+                                     the LDS of up to eight workgroups).  For sparse rows, where the columns do
                                      not all fit the part of the private vector a compute unit keeps on chip and
                                      the chip has compute units to spare, two workgroups share every solver: one
                                      owns the popular columns and runs the steps, the other owns the rest */

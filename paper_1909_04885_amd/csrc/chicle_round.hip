@@ -24,6 +24,7 @@
 #include "sdca_dense.hpp"
 #include "sdca_rowwise.hpp"
 #include "sdca_rowwise_cluster.hpp"
+#include "sdca_sparse_blocks.hpp"
 
 using namespace chicle;
 
@@ -160,11 +161,24 @@ struct chicle_ctx {
     double *slice_z_dev = nullptr;    // n_total partial dot products (float or double), zero between passes
     int gap_slices = 0, gap_slice_shift = 0;   // 0: the sliced row pass is not in use
     bool cluster_allowed = true;
+    // sparse rows longer than the batched solver takes: blocks over the columns that several rows of a solver hold
+    bool blocks_ready = false;        // laid out for the current assignment
+    int blocks_g = 1;                 // workgroups per solver
+    bool blocks_double = true;        // its private vectors are kept in double
+    int32_t *mpref_dev = nullptr;     // max_solvers x words: shared columns before each word
+    int32_t *mcount_dev = nullptr;    // shared columns per solver; one more word: segments taken
+    int64_t *place_off_dev = nullptr;
+    float *coef_dev = nullptr;        // n_total
+    unsigned long long *blocks_ring_dev = nullptr;
+    char *layout_dev = nullptr;       // tiles, segment table, places and segments (in place of the batched solver's tile sets)
+    size_t layout_bytes = 0;
+    SegRef *refs_dev = nullptr;
+    int32_t *place_dev = nullptr, *segs_dev = nullptr;
     // Sparse chunks: private vectors are stored compactly (a solver touches a small part of the columns)
     bool compact = false;
     int64_t words = 0;                // 32-column words per bitmap
     unsigned *bits_dev = nullptr;     // max_solvers x words: columns a solver's chunks contain
-    unsigned *multi_dev = nullptr;    // long rows: the same layout, columns that more than one row of the solver holds
+    unsigned *multi_dev = nullptr;    // the same layout, columns that more than one row of the solver holds
     int32_t *pref_dev = nullptr;      // max_solvers x words: set bits before each word
     int32_t *count_dev = nullptr;     // max_solvers: columns per solver
     int64_t *u_off_dev = nullptr;     // max_solvers: start of each solver's compact vector in u
@@ -231,8 +245,12 @@ int64_t private_floats(int64_t total_entries, int64_t ld, int32_t max_solvers, b
     return long_rows ? std::min(dense, total_entries + 64 * (int64_t)max_solvers) : dense;
 }
 
-// Columns [0, forced) of a compact vector are always present (the batched solver keeps them on chip and
-// addresses them by column id); at most this many.
+// Room behind the tile sets for the shared entries of long rows (shorter ones find room in the tile sets, which the solver
+// that takes rows of any length uses a quarter of): eight bytes per entry and four half-empty segments per row.
+size_t long_row_layout_bytes(int64_t n_total, int64_t total_entries)
+{
+    return sizeof(int32_t) * (2 * (size_t)total_entries + 4 * (size_t)SB_SEG_WORDS * (size_t)n_total);
+}
 
 // Slices of the sliced gap row pass at most (the shared vector in double).
 int max_slices(int32_t d)
@@ -255,6 +273,7 @@ size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_sol
     s += align_up(sizeof(float) * (size_t)private_floats(n_total_entries_hint, ld, max_solvers, long_rows));   // private vectors
     s += 2 * align_up(sizeof(int32_t) * (size_t)d);                      // renumbering tables
     s += 2 * align_up(tile_bytes(!compact) * (size_t)tiles_cap(n_total, max_solvers));
+    if (long_rows) s += align_up(long_row_layout_bytes(n_total, n_total_entries_hint));
     s += align_up(sizeof(int32_t) * (size_t)tiles_cap(n_total, max_solvers));
     s += 4 * align_up(sizeof(int32_t) * (size_t)n_total);                // perm staging, announced orders (2), row -> chunk
     s += 2 * align_up(sizeof(int32_t) * (size_t)n_chunks);               // chunk_first, list_base
@@ -271,7 +290,9 @@ size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_sol
     if (compact) {
         const size_t words = ((size_t)d + 31) / 32;
         s += 2 * align_up(sizeof(int32_t) * words * (size_t)max_solvers);          // column bitmaps, prefix counts
-        if (long_rows) s += align_up(sizeof(int32_t) * words * (size_t)max_solvers);   // columns held by several rows
+        s += 2 * align_up(sizeof(int32_t) * words * (size_t)max_solvers);          // columns held by several rows, prefix counts
+        s += align_up(sizeof(int32_t) * ((size_t)max_solvers + 1)) + align_up(sizeof(int64_t) * (size_t)max_solvers);
+        s += align_up(sizeof(float) * (size_t)n_total) + align_up(sizeof(unsigned long long) * (size_t)SB_RING_WORDS * (size_t)max_solvers);
         s += align_up(sizeof(int32_t) * (size_t)max_solvers) + align_up(sizeof(int64_t) * (size_t)max_solvers);
         s += align_up(sizeof(int32_t) * (size_t)n_chunks);
     }
@@ -553,6 +574,43 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
     return CHICLE_OK;
 }
 
+// Blocks over the shared columns (sparse rows of any length); the other columns' updates follow in a kernel of their own.
+template <int LOSS>
+int launch_blocks(chicle_ctx *c, const int32_t *perm)
+{
+    const RoundScalars sc = scalars(c);
+    const int k_pad = (c->K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
+    float *tiles = (float *)c->layout_dev;
+    seg_begin(c, CHICLE_SEG_EPOCH_GRAM);
+    clear_device_words(c, c->coef_dev, c->n_total);
+    if (c->blocks_g > 1) clear_device_words(c, c->blocks_ring_dev, 2 * (int64_t)SB_RING_WORDS * c->K);
+    if (c->n_tiles > 0) {
+        auto kern = gram_blocks<LOSS>;
+        HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(GramBlocksShared)));
+        hipLaunchKernelGGL(kern, dim3(c->n_tiles), dim3(SB_THREADS), sizeof(GramBlocksShared), c->stream, c->chunks_dev, c->solvers_dev,
+                           c->row_chunk_dev, c->chunk_first_dev, perm, c->tile_solver_dev, tiles, c->blocks_g, c->n_total,
+                           (const SegRef *)c->refs_dev, (const int32_t *)c->segs_dev, sc.c, c->err_dev);
+    }
+    seg_end(c, CHICLE_SEG_EPOCH_GRAM);
+    BlocksArgs A;
+    A.solvers = c->solvers_dev; A.chunks = c->chunks_dev; A.tiles = tiles; A.u_all = c->u; A.u_off = c->u_off_dev;
+    A.place_off = c->place_off_dev; A.place = c->place_dev; A.count = c->mcount_dev; A.refs = c->refs_dev; A.segs = c->segs_dev;
+    A.coef_out = c->coef_dev; A.n_total = c->n_total; A.G = c->blocks_g; A.k_pad = k_pad; A.sc = sc; A.err = c->err_dev;
+    A.rings = c->blocks_ring_dev;
+    auto kern = c->blocks_double ? sdca_blocks<LOSS, double> : sdca_blocks<LOSS, float>;
+    const size_t sh = sizeof(BlocksShared) + (c->blocks_double ? sizeof(double) * (size_t)SB_CAP<double> : sizeof(float) * (size_t)SB_CAP<float>);
+    HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+    seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
+    hipLaunchKernelGGL(kern, dim3(c->blocks_g * k_pad), dim3(SB_THREADS), sh, c->stream, A);
+    int max_rows = 1;
+    for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
+    hipLaunchKernelGGL(scatter_unique, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
+                       c->chunk_owner_dev, c->coef_dev, c->u, c->u_off_dev);
+    seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
+    HIP_TRY(c, hipGetLastError());
+    return CHICLE_OK;
+}
+
 // Work prepared ahead refers to the solver tables: finish it before they change.
 int drop_ahead(chicle_ctx *c)
 {
@@ -709,6 +767,51 @@ int renumber_columns(chicle_ctx *c)
     return CHICLE_OK;
 }
 
+// The shared entries of the rows, for the solver that takes rows of any length in blocks: the fewest workgroups per solver
+// whose LDS holds every solver's shared columns (more than one of them must be resident together: they wait for each
+// other).  Where these or the room do not suffice the row-wise solver remains.
+int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared)
+{
+    const int K = (int)shared.size();
+    const int k_pad = (K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
+    const int64_t most = *std::max_element(shared.begin(), shared.end());
+    auto members = [&](int cap) {          // 0: they do not fit
+        int G = 1;
+        while ((int64_t)G * cap < most) G *= 2;
+        return G <= SB_MAX_G && (G == 1 || G * k_pad <= c->cu_count) ? G : 0;
+    };
+    c->blocks_double = members(SB_CAP<double>) > 0;
+    const int G = c->blocks_double ? members(SB_CAP<double>) : members(SB_CAP<float>);
+    if (G == 0) return CHICLE_OK;
+    std::vector<int64_t> off(K);
+    int64_t places = 0;
+    for (int k = 0; k < K; ++k) { off[k] = places; places += shared[k]; }
+    const size_t tiles = align_up(tile_bytes(true) * (size_t)c->n_tiles), refs = align_up(sizeof(SegRef) * (size_t)G * (size_t)c->n_total),
+                 place = align_up(sizeof(int32_t) * (size_t)std::max<int64_t>(places, 1));
+    if (tiles + refs + place + SB_SEG_WORDS * sizeof(int32_t) > c->layout_bytes) return CHICLE_OK;
+    const size_t room = (c->layout_bytes - tiles - refs - place) / (SB_SEG_WORDS * sizeof(int32_t));
+    const int capacity = (int)std::min<size_t>(room, (size_t)INT32_MAX);
+    c->refs_dev = (SegRef *)(c->layout_dev + tiles);
+    c->place_dev = (int32_t *)(c->layout_dev + tiles + refs);
+    c->segs_dev = (int32_t *)(c->layout_dev + tiles + refs + place);
+    int *taken = c->mcount_dev + c->max_solvers;
+    HIP_TRY(c, hipMemcpyAsync(c->place_off_dev, off.data(), sizeof(int64_t) * (size_t)K, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, hipMemsetAsync(taken, 0, sizeof(int), c->stream));
+    hipLaunchKernelGGL(shared_places, dim3(grid_for(c->words, 256, 1024), K), dim3(256), 0, c->stream, c->bits_dev, c->pref_dev,
+                       c->multi_dev, c->mpref_dev, c->words, c->place_off_dev, c->place_dev);
+    int max_rows = 1;
+    for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
+    hipLaunchKernelGGL(build_segments, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
+                       c->chunk_owner_dev, c->multi_dev, c->mpref_dev, c->words, G, c->n_total, c->refs_dev, c->segs_dev, taken, capacity);
+    HIP_TRY(c, hipGetLastError());
+    int n = 0;
+    HIP_TRY(c, hipMemcpyAsync(&n, taken, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->blocks_g = G;
+    c->blocks_ready = n >= 0 && n <= capacity;
+    return CHICLE_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -770,6 +873,9 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
     c->col_of = (int32_t *)carve(c, sizeof(int32_t) * (size_t)d);
     c->tiles[0] = (float *)carve(c, tile_bytes(c->dense) * (size_t)c->max_tiles);
     c->tiles[1] = (float *)carve(c, tile_bytes(c->dense) * (size_t)c->max_tiles);
+    if (c->long_rows) (void)carve(c, long_row_layout_bytes(n_total, total_entries));
+    c->layout_dev = (char *)c->tiles[0];
+    c->layout_bytes = c->layout_dev ? (size_t)(c->arena + c->used - c->layout_dev) : 0;
     c->tile_solver_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->max_tiles);
     c->perm_stage = (int32_t *)carve(c, sizeof(int32_t) * (size_t)n_total);
     c->perm_ahead[0] = (int32_t *)carve(c, sizeof(int32_t) * (size_t)n_total);
@@ -796,12 +902,17 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
         c->words = ((int64_t)d + 31) / 32;
         c->bits_dev = (unsigned *)carve(c, sizeof(unsigned) * (size_t)c->words * (size_t)max_solvers);
         c->pref_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->words * (size_t)max_solvers);
-        if (c->long_rows) c->multi_dev = (unsigned *)carve(c, sizeof(unsigned) * (size_t)c->words * (size_t)max_solvers);
+        c->multi_dev = (unsigned *)carve(c, sizeof(unsigned) * (size_t)c->words * (size_t)max_solvers);
+        c->mpref_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->words * (size_t)max_solvers);
+        c->mcount_dev = (int32_t *)carve(c, sizeof(int32_t) * ((size_t)max_solvers + 1));
+        c->place_off_dev = (int64_t *)carve(c, sizeof(int64_t) * (size_t)max_solvers);
+        c->coef_dev = (float *)carve(c, sizeof(float) * (size_t)n_total);
+        c->blocks_ring_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * (size_t)SB_RING_WORDS * (size_t)max_solvers);
         c->count_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)max_solvers);
         c->u_off_dev = (int64_t *)carve(c, sizeof(int64_t) * (size_t)max_solvers);
         c->chunk_owner_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)n_chunks);
     }
-    if (!c->err_dev || !c->ticks_dev || !c->progress_dev || !c->split_ring_dev || (c->long_rows && (!c->cluster_ring_dev || !c->slice_z_dev)) || (c->compact && (!c->chunk_owner_dev || (c->long_rows && !c->multi_dev)))) { delete c; return CHICLE_ENOMEM; }
+    if (!c->err_dev || !c->ticks_dev || !c->progress_dev || !c->split_ring_dev || (c->long_rows && (!c->cluster_ring_dev || !c->slice_z_dev)) || (c->compact && (!c->chunk_owner_dev || !c->blocks_ring_dev))) { delete c; return CHICLE_ENOMEM; }
 
     c->chunks.assign(n_chunks, ChunkDev{});
     c->loaded.assign(n_chunks, 0);
@@ -1072,6 +1183,7 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
     c->gap_items = items[c->n_chunks];
     c->state = ST_READY;
     c->cluster = 1;
+    c->blocks_ready = false;
     if (c->compact) {
         // Compact private vectors: which columns each solver's chunks contain, where each of them lives in
         // the solver's vector, and that index for every stored entry.  The columns the batched solver keeps
@@ -1081,16 +1193,21 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
         const dim3 egrid(grid_for(max_nnz, 256, 1024), c->n_chunks);
         HIP_TRY(c, hipMemcpyAsync(c->chunk_owner_dev, chunk_to_solver, sizeof(int32_t) * (size_t)c->n_chunks, hipMemcpyHostToDevice, c->stream));
         HIP_TRY(c, hipMemsetAsync(c->bits_dev, 0, sizeof(unsigned) * (size_t)c->words * (size_t)K, c->stream));
-        if (c->multi_dev) HIP_TRY(c, hipMemsetAsync(c->multi_dev, 0, sizeof(unsigned) * (size_t)c->words * (size_t)K, c->stream));
+        // columns that several rows of a solver hold: for the solvers that take rows longer than the batched one does
+        unsigned *multi = batched_eligible(c) ? nullptr : c->multi_dev;
+        if (multi) HIP_TRY(c, hipMemsetAsync(c->multi_dev, 0, sizeof(unsigned) * (size_t)c->words * (size_t)K, c->stream));
         // (few workgroups per chunk: each of them adds a bitmap of its own to the solver's at the end)
         const dim3 mgrid(grid_for(max_nnz, 256 * 64, std::max(1, 4096 / c->n_chunks)), c->n_chunks);
-        hipLaunchKernelGGL(mark_columns, mgrid, dim3(256), 0, c->stream, c->chunks_dev, c->chunk_owner_dev, c->bits_dev, c->words, c->multi_dev);
+        hipLaunchKernelGGL(mark_columns, mgrid, dim3(256), 0, c->stream, c->chunks_dev, c->chunk_owner_dev, c->bits_dev, c->words, multi);
         const int forced = batched_eligible(c) ? batched_layout(c).n_hot : 0;
         if (forced > 0)
             hipLaunchKernelGGL(force_columns, dim3(K), dim3(256), 0, c->stream, c->bits_dev, c->words, forced);
         hipLaunchKernelGGL(prefix_columns, dim3(K), dim3(1024), 0, c->stream, c->bits_dev, c->pref_dev, c->words, c->count_dev);
+        if (multi)
+            hipLaunchKernelGGL(prefix_columns, dim3(K), dim3(1024), 0, c->stream, multi, c->mpref_dev, c->words, c->mcount_dev);
         HIP_TRY(c, hipGetLastError());
-        std::vector<int32_t> cnt(K);
+        std::vector<int32_t> cnt(K), shared(K, 0);
+        if (multi) HIP_TRY(c, hipMemcpyAsync(shared.data(), c->mcount_dev, sizeof(int32_t) * (size_t)K, hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipMemcpyAsync(cnt.data(), c->count_dev, sizeof(int32_t) * (size_t)K, hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         std::vector<int64_t> off(K);
@@ -1100,8 +1217,12 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
         c->u_used = used;
         HIP_TRY(c, hipMemcpyAsync(c->u_off_dev, off.data(), sizeof(int64_t) * (size_t)K, hipMemcpyHostToDevice, c->stream));
         hipLaunchKernelGGL(compact_indices, egrid, dim3(256), 0, c->stream, c->chunks_dev, c->chunk_owner_dev, c->bits_dev,
-                           c->pref_dev, c->words, (const unsigned *)c->multi_dev);
+                           c->pref_dev, c->words, (const unsigned *)multi);
         HIP_TRY(c, hipGetLastError());
+        if (multi) {
+            const int rc = lay_out_blocks(c, shared);
+            if (rc) return rc;
+        }
         if (forced > 0) {
             int max_rows = 1;
             for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
@@ -1219,6 +1340,10 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
             rc = c->loss == CHICLE_LOSS_HINGE ? launch_batched<0>(c, perm_device, tiles_ready, perm_next_device)
                  : c->loss == CHICLE_LOSS_SQUARED ? launch_batched<1>(c, perm_device, tiles_ready, perm_next_device)
                                                   : launch_batched<2>(c, perm_device, tiles_ready, perm_next_device);
+        } else if (c->blocks_ready && c->solver_kind == CHICLE_SOLVER_AUTO) {
+            rc = c->loss == CHICLE_LOSS_HINGE ? launch_blocks<0>(c, perm_device)
+                 : c->loss == CHICLE_LOSS_SQUARED ? launch_blocks<1>(c, perm_device)
+                                                  : launch_blocks<2>(c, perm_device);
         } else {
             seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
             rc = c->loss == CHICLE_LOSS_HINGE ? launch_rowwise<0>(c, perm_device)

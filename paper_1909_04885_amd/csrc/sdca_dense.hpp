@@ -243,7 +243,8 @@ struct DenseShape {
 };
 
 // The recurrence: lane i owns row i of the block; returns the row's step.  T: lane's coefficients, [j].
-template <int LOSS, int BR>
+// SOLVED: T holds the inverse of the squared loss's recurrence (gram_dense).
+template <int LOSS, int BR, bool SOLVED>
 __device__ __forceinline__ float dense_recurrence(const float *T_lds, float t, float lo, float hi, float a, float root, int lane)
 {
     const int i = lane & (BR - 1);
@@ -252,7 +253,7 @@ __device__ __forceinline__ float dense_recurrence(const float *T_lds, float t, f
     float4_v T4[BR / 4];
 #pragma unroll
     for (int jq = 0; jq < BR / 4; ++jq) T4[jq] = Tq[jq * BR];
-    if (LOSS == 1) {                 // no clamp: the tile holds the recurrence solved (gram_dense), a product is left
+    if (LOSS == 1 && SOLVED) {       // no clamp: the tile holds the recurrence solved (gram_dense), a product is left
         float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j0 = 0; j0 < BR; j0 += 16) {      // (lane reads in groups: a product right behind its lane read stalls)
@@ -420,7 +421,7 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
                     root = logistic_root(t, hi, a);
                 }
             }
-            const float dl = dense_recurrence<LOSS, BR>(T, t, lo, hi, a, root, lane);
+            const float dl = dense_recurrence<LOSS, BR, true>(T, t, lo, hi, a, root, lane);
             if (lane < BR) {
                 if (st_cur != nullptr) {
                     float an = a + dl;

@@ -1,0 +1,63 @@
+"""The block solver for sparse rows of any length at its edges, against the oracle: rows with more segments than
+threads, blocks whose entries are joined in parts, solvers of one row and of none, clusters of 1, 2, 4 and 8 workgroups,
+data without a single shared column, and more shared columns than eight workgroups hold (the row-wise solver's case)."""
+import numpy as np
+import pytest
+
+from harness import run_lockstep
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(g, lens, d, zipf):
+    if zipf:
+        p = (np.arange(d) + 1.0) ** -1.1
+        p /= p.sum()
+        ids = g.permutation(d)
+        return [np.sort(ids[g.choice(d, int(m), replace=False, p=p)]) for m in lens]
+    return [np.sort(g.choice(d, int(m), replace=False)) for m in lens]
+
+
+CASES = {
+    # name: (rows, columns, row lengths, Zipf columns, solvers, l1)
+    "ragged": (700, 5000, lambda g, n: np.clip(np.round(g.lognormal(np.log(30), 0.6, n)), 0, 200), True, 3, 0.0),
+    "ragged_l1": (500, 5000, lambda g, n: np.clip(np.round(g.lognormal(np.log(30), 0.6, n)), 0, 200), True, 3, 0.02),
+    "just_over": (300, 400, lambda g, n: np.where(np.arange(n) == 7, 49, 20), False, 2, 0.0),
+    "more_segments_than_threads": (200, 3000, lambda g, n: g.integers(0, 600, n), False, 2, 0.0),
+    "joined_in_parts": (150, 2500, lambda g, n: g.integers(1000, 2500, n), False, 2, 0.0),
+    "nothing_shared": (5, 100000, lambda g, n: np.full(n, 60), False, 5, 0.0),
+    "two_members": (400, 30000, lambda g, n: g.integers(100, 600, n), False, 2, 0.0),
+    "four_members": (900, 60000, lambda g, n: g.integers(200, 600, n), False, 2, 0.0),
+    "eight_members": (1800, 100000, lambda g, n: g.integers(300, 600, n), False, 2, 0.0),
+    "eight_members_in_float": (1300, 170000, lambda g, n: g.integers(900, 1000, n), False, 2, 0.0),
+    "too_many_shared": (2400, 360000, lambda g, n: g.integers(900, 1100, n), False, 2, 0.0),
+}
+
+
+@pytest.mark.parametrize("loss", ["hinge", "squared", "logistic"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_sparse_blocks(oracle_mod, name, loss):
+    import torch
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    assert torch.cuda.is_available()
+    n, d, lengths, zipf, K, l1 = CASES[name]
+    g = np.random.default_rng(23)
+    lens = np.asarray(lengths(g, n)).astype(np.int64)
+    if name != "nothing_shared":
+        lens[3] = 0
+    cols = _rows(g, lens, d, zipf)
+    rp = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(lens, out=rp[1:])
+    val = (g.standard_normal(int(rp[-1])) / np.sqrt(np.maximum(np.repeat(lens, lens), 1))).astype(np.float32)
+    y = g.standard_normal(n).astype(np.float32) if loss == "squared" else np.where(g.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    if name == "nothing_shared":
+        bounds = np.arange(n + 1, dtype=np.int64)                  # a row per solver
+        table = np.arange(n, dtype=np.int32)
+    else:
+        bounds = np.array([0, 1, n // 2 + 3, n], dtype=np.int64)   # solver 0: one row and the second half
+        table = np.array([0, K - 1, 0], dtype=np.int32)
+    p = Problem(name, loss, n, d, 0.01, y, bounds, row_ptr=rp, col=np.concatenate(cols).astype(np.int32), val=val)
+    print("\ncase blocks %s %s n=%d d=%d entries=%d longest=%d" % (name, loss, n, d, rp[-1], lens.max()), flush=True)
+    run_lockstep({"seed": 3, "rounds": 3, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1, l1=l1,
+                 ahead=loss == "squared", tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)
