@@ -173,6 +173,8 @@ struct chicle_ctx {
     char *layout_dev = nullptr;       // tiles, segment table, places and segments (in place of the batched solver's tile sets)
     size_t layout_bytes = 0;
     SegRef *refs_dev = nullptr;
+    UniqueSource *sources_dev = nullptr;   // u_used; nullptr: no room
+    int most_columns = 0;             // most columns a solver's compact vector has
     int32_t *place_dev = nullptr, *segs_dev = nullptr;
     // Sparse chunks: private vectors are stored compactly (a solver touches a small part of the columns)
     bool compact = false;
@@ -246,10 +248,11 @@ int64_t private_floats(int64_t total_entries, int64_t ld, int32_t max_solvers, b
 }
 
 // Room behind the tile sets for the shared entries of long rows (shorter ones find room in the tile sets, which the solver
-// that takes rows of any length uses a quarter of): eight bytes per entry and four half-empty segments per row.
+// that takes rows of any length uses a quarter of): eight bytes per entry and four half-empty segments per row,
+// and eight bytes per place of the private vectors.
 size_t long_row_layout_bytes(int64_t n_total, int64_t total_entries)
 {
-    return sizeof(int32_t) * (2 * (size_t)total_entries + 4 * (size_t)SB_SEG_WORDS * (size_t)n_total);
+    return sizeof(int32_t) * (4 * (size_t)total_entries + 4 * (size_t)SB_SEG_WORDS * (size_t)n_total);
 }
 
 // Slices of the sliced gap row pass at most (the shared vector in double).
@@ -602,10 +605,17 @@ int launch_blocks(chicle_ctx *c, const int32_t *perm)
     HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
     seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
     hipLaunchKernelGGL(kern, dim3(c->blocks_g * k_pad), dim3(SB_THREADS), sh, c->stream, A);
-    int max_rows = 1;
-    for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
-    hipLaunchKernelGGL(scatter_unique, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
-                       c->chunk_owner_dev, c->coef_dev, c->u, c->u_off_dev);
+    if (c->sources_dev) {
+        int lds_rows = 1;
+        for (const SolverDev &sol : c->solvers) lds_rows = std::max(lds_rows, std::min(sol.n_rows, SPREAD_LDS_ROWS));
+        hipLaunchKernelGGL(spread_unique, dim3((c->most_columns + SPREAD_PER - 1) / SPREAD_PER, c->K), dim3(256), sizeof(float) * (size_t)lds_rows,
+                           c->stream, c->solvers_dev, c->count_dev, (const UniqueSource *)c->sources_dev, c->coef_dev, c->u, c->u_off_dev, lds_rows);
+    } else {
+        int max_rows = 1;
+        for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
+        hipLaunchKernelGGL(scatter_unique, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
+                           c->chunk_owner_dev, c->solvers_dev, c->chunk_first_dev, c->coef_dev, c->u, c->u_off_dev);
+    }
     seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
     HIP_TRY(c, hipGetLastError());
     return CHICLE_OK;
@@ -770,7 +780,7 @@ int renumber_columns(chicle_ctx *c)
 // The shared entries of the rows, for the solver that takes rows of any length in blocks: the fewest workgroups per solver
 // whose LDS holds every solver's shared columns (more than one of them must be resident together: they wait for each
 // other).  Where these or the room do not suffice the row-wise solver remains.
-int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared)
+int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared, const std::vector<int32_t> &columns)
 {
     const int K = (int)shared.size();
     const int k_pad = (K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
@@ -809,6 +819,16 @@ int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared)
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->blocks_g = G;
     c->blocks_ready = n >= 0 && n <= capacity;
+    c->most_columns = *std::max_element(columns.begin(), columns.end());
+    c->sources_dev = nullptr;
+    const size_t used = tiles + refs + place + align_up((size_t)SB_SEG_WORDS * sizeof(int32_t) * (size_t)std::max(n, 1));
+    if (c->blocks_ready && used + sizeof(UniqueSource) * (size_t)c->u_used <= c->layout_bytes) {
+        c->sources_dev = (UniqueSource *)(c->layout_dev + used);
+        HIP_TRY(c, hipMemsetAsync(c->sources_dev, 0xff, sizeof(UniqueSource) * (size_t)c->u_used, c->stream));
+        hipLaunchKernelGGL(unique_sources, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
+                           c->chunk_owner_dev, c->chunk_first_dev, c->u_off_dev, c->sources_dev);
+        HIP_TRY(c, hipGetLastError());
+    }
     return CHICLE_OK;
 }
 
@@ -1220,7 +1240,7 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
                            c->pref_dev, c->words, (const unsigned *)multi);
         HIP_TRY(c, hipGetLastError());
         if (multi) {
-            const int rc = lay_out_blocks(c, shared);
+            const int rc = lay_out_blocks(c, shared, cnt);
             if (rc) return rc;
         }
         if (forced > 0) {

@@ -8,7 +8,7 @@
 //                    from the shared entries, by a hash join in LDS;
 //   sdca_blocks      per solver a cluster of G workgroups, each with a part of the shared columns' private vector in
 //                    LDS for the whole pass: gather, recurrence, scatter;
-//   scatter_unique   on the whole chip: the entries of unshared columns, from the steps the second kernel leaves.
+//   spread_unique    on the whole chip: the entries of unshared columns, from the steps the second kernel leaves.
 // A step of the row-wise solvers costs a trip to memory (1.7 us for rows of 36 entries, 2.9 us for rows of a thousand on
 // four workgroups); here 64 steps cost one recurrence (2e3 cycles) and as much again for gather and scatter.
 //
@@ -37,8 +37,8 @@ constexpr int SB_RING_WORDS = SB_MAX_G * SB_RING * BATCH;   // 64-bit words per 
 struct SegRef { int32_t begin, n; };            // a row's segments in one member's columns
 struct BlockRow {
     RowState *st;                               // nullptr: a row that takes no step
-    int32_t row;                                // context-wide row index (readable tables also where st is nullptr)
-    int32_t unused;
+    int32_t row;                                // context-wide row index (a readable one also where st is nullptr)
+    int32_t lr;                                 // ... and the solver's local one
 };
 static_assert(sizeof(BlockRow) == sizeof(DenseRow), "a tile of this solver has the size of a dense one");
 
@@ -145,22 +145,194 @@ __global__ __launch_bounds__(256) void build_segments(const ChunkDev *__restrict
 
 // ---- tiles ----------------------------------------------------------------------------------------------------------
 
-constexpr int GB_SLOTS = 8192;                  // hash slots
+constexpr int GB_SLOTS = 8192;                  // hash slots, columns in parts
 constexpr int GB_POST = 6144;                   // entries joined at a time
+constexpr int GB_EPT = 12;                      // entries per thread, all at once
+constexpr int GB_ALL = GB_EPT * SB_THREADS;     // a block of no more entries is joined at once, from registers
+constexpr int GB_ALL_SLOTS = 16384;
+constexpr int GB_DENSE_MIN = 6;                 // columns that this many rows of the block hold go through a dense product,
+constexpr int GB_DENSE = 96;                    // this many at a time (their values' place: [GB_DENSE][GB_LD])
+constexpr int GB_MARK = 0x8000;                 // cursor of such a column's slot: this and its number
 constexpr int GB_LD = BATCH + 1;
 
 struct GramBlocksShared {
-    double G[BATCH][GB_LD];                     // accumulators [j][i] (doubles: see GramShared)
-    int keys[GB_SLOTS];
-    int cursor[GB_SLOTS];                       // entries per slot, then where the slot's list goes on; at the end: where it ends
-    float post_val[GB_POST];
-    unsigned char post_row[GB_POST];
-    SegRef refs[SB_MAX_G][BATCH];
+    union {
+        struct {                                // columns in parts
+            double G[BATCH][GB_LD];             // accumulators [j][i] (doubles: see GramShared)
+            int keys[GB_SLOTS];
+            int cursor[GB_SLOTS];               // entries per slot, then where the slot's list goes on; at the end: where it ends
+            float post_val[GB_POST];
+            unsigned char post_row[GB_POST];
+            SegRef refs[SB_MAX_G][BATCH];
+        } p;
+        struct {                                // all entries at once
+            union {
+                int keys[GB_ALL_SLOTS];         // until every entry knows its slot
+                struct {
+                    double G[BATCH][GB_LD];     // from then on
+                    float A[GB_DENSE][GB_LD];   // [column][row]
+                };
+            };
+            unsigned short cursor[GB_ALL_SLOTS];
+            float post_val[GB_ALL];
+            union {
+                unsigned char post_row[GB_ALL];
+                struct { int pref[SB_MAX_G * BATCH + 1], begin[SB_MAX_G * BATCH]; };   // until the entries are loaded: segments
+            };                                  // of (member, row), running count and place
+        } a;
+    };
     float sgn[BATCH], scale[BATCH];
     int row[BATCH];
     int scan[SB_THREADS / 64];
     int total, in_part;
 };
+
+// The block's entries joined at once.  A thread holds up to twelve entries of its own in registers (a segment's eight
+// entries lie in eight neighbouring lanes), so that all their loads are in flight together and no entry is looked up
+// twice.  Columns that one row of the block holds take no part in the lists.  G is left in sh.a.G.
+__device__ __forceinline__ void join_all(GramBlocksShared &sh, int G, const int32_t *__restrict__ segs)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int n_seg = sh.a.pref[G * BATCH];
+    // an entry: its value, and first its column, then where its column is: slot | row << 14 | entries of the column << 20
+    int pk[GB_EPT];
+    float val[GB_EPT];
+    constexpr int SLOT = GB_ALL_SLOTS - 1;
+    unsigned long long rows[2] = {0, 0};         // rows of the entries until then, six bits each
+#pragma unroll
+    for (int k = 0; k < GB_EPT; ++k) {
+        const int s = (tid >> 3) + k * (SB_THREADS / 8);
+        pk[k] = -1; val[k] = 0.f;
+        if (s < n_seg) {
+            int at = 0;                          // largest with pref[at] <= s
+            for (int o = G * BATCH / 2; o > 0; o >>= 1)
+                if (sh.a.pref[at + o] <= s) at += o;
+            const int32_t *w = segs + (int64_t)(sh.a.begin[at] + s - sh.a.pref[at]) * SB_SEG_WORDS + (tid & 7);
+            pk[k] = w[0] * G + (at >> 6);
+            val[k] = __int_as_float(w[SB_SEG]);
+            rows[k / 10] |= (unsigned long long)(at & 63) << (6 * (k % 10));
+        }
+    }
+    {
+        int4 *q = reinterpret_cast<int4 *>(sh.a.keys);
+        for (int i = tid; i < GB_ALL_SLOTS / 4; i += SB_THREADS) q[i] = make_int4(-1, -1, -1, -1);
+        int4 *c = reinterpret_cast<int4 *>(sh.a.cursor);
+        for (int i = tid; i < GB_ALL_SLOTS / 8; i += SB_THREADS) c[i] = make_int4(0, 0, 0, 0);
+    }
+    __syncthreads();
+    unsigned *packed = reinterpret_cast<unsigned *>(sh.a.cursor);      // two 16-bit counters share a word
+#pragma unroll
+    for (int k = 0; k < GB_EPT; ++k) {
+        if (val[k] == 0.f) { pk[k] = -1; continue; }
+        int h = (int)(((unsigned)pk[k] * 2654435761u) >> 18);
+        for (;;) {                               // ends: three quarters as many entries as slots at most
+            const int prev = atomicCAS(&sh.a.keys[h], -1, pk[k]);
+            if (prev == -1 || prev == pk[k]) break;
+            h = (h + 1) & SLOT;
+        }
+        pk[k] = h | (int)(rows[k / 10] >> (6 * (k % 10)) & 63) << 14;
+        atomicAdd(packed + (h >> 1), (h & 1) ? 0x10000u : 1u);
+    }
+    __syncthreads();
+    // lists of the slots with two entries or more: exclusive scan, 16 slots per thread; G takes the keys' place
+    constexpr int SPT = GB_ALL_SLOTS / SB_THREADS;
+    // (the scanned word: list entries in the lower 16 bits, columns for the dense product in the upper)
+    auto weight = [](int n) { return n >= GB_DENSE_MIN ? 0x10000 : n > 1 ? n : 0; };
+    unsigned cnt[SPT / 2];
+    int sum = 0;
+#pragma unroll
+    for (int k = 0; k < SPT / 2; ++k) {
+        cnt[k] = packed[tid * (SPT / 2) + k];
+        sum += weight((int)(cnt[k] & 0xffff)) + weight((int)(cnt[k] >> 16));
+    }
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) sh.scan[wv] = incl;
+    for (int i = tid; i < BATCH * GB_LD; i += SB_THREADS) (&sh.a.G[0][0])[i] = 0.0;
+#pragma unroll
+    for (int k = 0; k < GB_EPT; ++k)             // -1 from here on: takes no part
+        if (pk[k] >= 0) {
+            const int n = sh.a.cursor[pk[k] & SLOT];
+            pk[k] = n < 2 ? -1 : pk[k] | n << 20;
+        }
+    __syncthreads();
+    int off = incl - sum;
+    for (int w = 0; w < wv; ++w) off += sh.scan[w];
+    auto start = [&](int n) {
+        const unsigned at = n >= GB_DENSE_MIN ? (unsigned)(GB_MARK | (off >> 16)) : (unsigned)(off & 0xffff);
+        off += weight(n);
+        return at;
+    };
+#pragma unroll
+    for (int k = 0; k < SPT / 2; ++k) {
+        const unsigned a = start((int)(cnt[k] & 0xffff)), b = start((int)(cnt[k] >> 16));
+        packed[tid * (SPT / 2) + k] = a | (b << 16);
+    }
+    if (tid == SB_THREADS - 1) sh.in_part = off >> 16;
+    __syncthreads();
+    // columns many rows hold (the head of a Zipf distribution: every pair of rows shares some of them): a product of
+    // dense columns on the matrix cores, 12 wavefronts for three 32 x 32 blocks times a quarter of the columns
+    const int n_dense = sh.in_part;
+    if (n_dense > 0) {
+        floatx16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        const int quad = wv % 3, j0 = quad == 2 ? 32 : 0, i0 = quad == 0 ? 0 : 32;
+        for (int d0 = 0; d0 < n_dense; d0 += GB_DENSE) {
+            __syncthreads();
+            for (int i = tid; i < GB_DENSE * GB_LD; i += SB_THREADS) (&sh.a.A[0][0])[i] = 0.f;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < GB_EPT; ++k)
+                if (pk[k] >= GB_DENSE_MIN << 20) {
+                    const int at = (sh.a.cursor[pk[k] & SLOT] & (GB_MARK - 1)) - d0;
+                    if (at >= 0 && at < GB_DENSE) sh.a.A[at][pk[k] >> 14 & 63] = val[k];
+                }
+            __syncthreads();
+            if (wv < 12) {
+                const int c0 = wv / 3 * (GB_DENSE / 4) + (lane >> 5);
+#pragma unroll 4
+                for (int c = 0; c < GB_DENSE / 4; c += 2)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sh.a.A[c0 + c][j0 + (lane & 31)], sh.a.A[c0 + c][i0 + (lane & 31)], acc, 0, 0, 0);
+            }
+        }
+        if (wv < 12) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                atomicAdd(&sh.a.G[j0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)][i0 + (lane & 31)], (double)acc[r]);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < GB_EPT; ++k) {
+        if (pk[k] < 0 || pk[k] >= GB_DENSE_MIN << 20) continue;
+        const int slot = pk[k] & SLOT;
+        const unsigned old = atomicAdd(packed + (slot >> 1), (slot & 1) ? 0x10000u : 1u);
+        const int pos = (slot & 1) ? old >> 16 : old & 0xffff;
+        sh.a.post_val[pos] = val[k];
+        sh.a.post_row[pos] = (unsigned char)(pk[k] >> 14 & 63);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < GB_EPT; ++k) {
+        if (pk[k] < 0 || pk[k] >= GB_DENSE_MIN << 20) continue;
+        // (the slot's cursor has reached its list's end)
+        const int i = pk[k] >> 14 & 63, pe = sh.a.cursor[pk[k] & SLOT], pb = pe - (pk[k] >> 20);
+        for (int p = pb; p < pe; p += 4) {       // four list members per round of LDS latency
+            int j[4];
+            float x[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) { const int pm = min(p + m, pe - 1); j[m] = sh.a.post_row[pm]; x[m] = sh.a.post_val[pm]; }
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                if (p + m < pe && j[m] < i) atomicAdd(&sh.a.G[j[m]][i], (double)(val[k] * x[m]));
+        }
+    }
+    __syncthreads();
+}
 
 // One workgroup per tile.  Entries are inserted into an open-addressing table keyed by column, counted per slot, laid
 // out as lists of (row, value) by a scan, and every entry adds its products with the earlier rows of its column's list.
@@ -178,7 +350,6 @@ __global__ __launch_bounds__(SB_THREADS) void gram_blocks(
     const SolverDev S = solvers[tile_solver[blockIdx.x]];
     float *out = tiles + (int64_t)blockIdx.x * DENSE_TILE_FLOATS;
     if (tid == 0) sh.total = 0;
-    for (int i = tid; i < BATCH * GB_LD; i += SB_THREADS) (&sh.G[0][0])[i] = 0.0;
     if (tid < BATCH) {
         const int t = ((int)blockIdx.x - S.tile_begin) * BATCH + tid;
         BlockRow row = {nullptr, 0, 0};
@@ -196,6 +367,7 @@ __global__ __launch_bounds__(SB_THREADS) void gram_blocks(
                 if (q != 0.f) {
                     row.st = ch.st + r;
                     row.row = ch.row_base + r;
+                    row.lr = lr;
                     sgn = LOSS == 1 ? 1.f : st.x;
                     scale = LOSS == 0 ? -1.f / q : LOSS == 1 ? -1.f / (c + q) : -1.f / c;
                 }
@@ -205,18 +377,45 @@ __global__ __launch_bounds__(SB_THREADS) void gram_blocks(
         reinterpret_cast<BlockRow *>(out + BATCH * BATCH)[tid] = row;
     }
     __syncthreads();
-    for (int i = tid; i < G * BATCH; i += SB_THREADS) {
-        const int r = sh.row[i & 63];
-        const SegRef ref = r >= 0 ? refs[(i >> 6) * n_total + r] : SegRef{0, 0};
-        sh.refs[i >> 6][i & 63] = ref;
-        if (ref.n) atomicAdd(&sh.total, ref.n * SB_SEG);
+    SegRef ref = {0, 0};                         // thread: (member, row)
+    static_assert(SB_MAX_G * BATCH <= SB_THREADS, "one thread per member and row");
+    if (tid < G * BATCH) {
+        const int r = sh.row[lane];
+        if (r >= 0) ref = refs[(int64_t)wv * n_total + r];
     }
+    {
+        int incl = ref.n;                        // running count over members, then rows
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) sh.scan[wv] = incl;
+        __syncthreads();
+        int before = 0;
+        for (int w = 0; w < wv; ++w) before += sh.scan[w];
+        if (tid < G * BATCH) {
+            sh.a.pref[tid + 1] = before + incl;
+            sh.a.begin[tid] = ref.begin;
+        }
+        if (tid == 0) sh.a.pref[0] = 0;
+        if (tid == SB_THREADS - 1) sh.total = (before + incl) * SB_SEG;
+    }
+    __syncthreads();
+    const int total = sh.total;
+    const bool at_once = total <= GB_ALL;
+    if (at_once) {
+        join_all(sh, G, segs);
+    } else {
+    __syncthreads();
+    if (tid < G * BATCH) sh.p.refs[wv][lane] = ref;
+    for (int i = tid; i < BATCH * GB_LD; i += SB_THREADS) (&sh.p.G[0][0])[i] = 0.0;
     __syncthreads();
     // a wavefront takes every 16th row, a lane every 64th entry of it
     auto each_entry = [&](auto f) __attribute__((always_inline)) {
         for (int i = wv; i < BATCH; i += SB_THREADS / 64)
             for (int g = 0; g < G; ++g) {
-                const SegRef ref = sh.refs[g][i];
+                const SegRef ref = sh.p.refs[g][i];
                 for (int q = lane; q < ref.n * SB_SEG; q += 64) {
                     const int32_t *w = segs + (int64_t)(ref.begin + q / SB_SEG) * SB_SEG_WORDS + q % SB_SEG;
                     const float v = __int_as_float(w[SB_SEG]);
@@ -225,7 +424,7 @@ __global__ __launch_bounds__(SB_THREADS) void gram_blocks(
             }
     };
     int lp = 0;                                  // 2^lp parts
-    while (((int64_t)GB_POST << lp) < (int64_t)sh.total && lp < 16) ++lp;
+    while (((int64_t)GB_POST << lp) < (int64_t)total && lp < 16) ++lp;
     for (unsigned part = 0; part < (1u << lp); ++part) {
         auto mine = [&](unsigned h) { return lp == 0 || (h >> (32 - lp)) == part; };
         auto slot0 = [&](unsigned h) { return (int)((h << lp) >> 19); };          // the 13 bits that follow the part's
@@ -248,24 +447,24 @@ __global__ __launch_bounds__(SB_THREADS) void gram_blocks(
                 continue;
             }
         }
-        for (int i = tid; i < GB_SLOTS; i += SB_THREADS) { sh.keys[i] = -1; sh.cursor[i] = 0; }
+        for (int i = tid; i < GB_SLOTS; i += SB_THREADS) { sh.p.keys[i] = -1; sh.p.cursor[i] = 0; }
         __syncthreads();
         each_entry([&](int, unsigned key, float) {
             const unsigned hash = key * 2654435761u;
             if (!mine(hash)) return;
             int h = slot0(hash);
             for (;;) {                           // ends: fewer entries than slots
-                const int prev = atomicCAS(&sh.keys[h], -1, (int)key);
+                const int prev = atomicCAS(&sh.p.keys[h], -1, (int)key);
                 if (prev == -1 || prev == (int)key) break;
                 h = (h + 1) & (GB_SLOTS - 1);
             }
-            atomicAdd(&sh.cursor[h], 1);
+            atomicAdd(&sh.p.cursor[h], 1);
         });
         __syncthreads();
         {                                        // exclusive scan, 8 slots per thread
             int v[GB_SLOTS / SB_THREADS], sum = 0;
 #pragma unroll
-            for (int k = 0; k < GB_SLOTS / SB_THREADS; ++k) { v[k] = sh.cursor[tid * (GB_SLOTS / SB_THREADS) + k]; sum += v[k]; }
+            for (int k = 0; k < GB_SLOTS / SB_THREADS; ++k) { v[k] = sh.p.cursor[tid * (GB_SLOTS / SB_THREADS) + k]; sum += v[k]; }
             int incl = sum;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
@@ -277,39 +476,40 @@ __global__ __launch_bounds__(SB_THREADS) void gram_blocks(
             int off = incl - sum;
             for (int w = 0; w < wv; ++w) off += sh.scan[w];
 #pragma unroll
-            for (int k = 0; k < GB_SLOTS / SB_THREADS; ++k) { sh.cursor[tid * (GB_SLOTS / SB_THREADS) + k] = off; off += v[k]; }
+            for (int k = 0; k < GB_SLOTS / SB_THREADS; ++k) { sh.p.cursor[tid * (GB_SLOTS / SB_THREADS) + k] = off; off += v[k]; }
         }
         __syncthreads();
         auto find = [&](unsigned key, unsigned hash) {
             int h = slot0(hash);
-            while (sh.keys[h] != (int)key) h = (h + 1) & (GB_SLOTS - 1);          // (it is there)
+            while (sh.p.keys[h] != (int)key) h = (h + 1) & (GB_SLOTS - 1);          // (it is there)
             return h;
         };
         each_entry([&](int i, unsigned key, float v) {
             const unsigned hash = key * 2654435761u;
             if (!mine(hash)) return;
-            const int pos = atomicAdd(&sh.cursor[find(key, hash)], 1);
-            sh.post_val[pos] = v;
-            sh.post_row[pos] = (unsigned char)i;
+            const int pos = atomicAdd(&sh.p.cursor[find(key, hash)], 1);
+            sh.p.post_val[pos] = v;
+            sh.p.post_row[pos] = (unsigned char)i;
         });
         __syncthreads();
         each_entry([&](int i, unsigned key, float v) {
             const unsigned hash = key * 2654435761u;
             if (!mine(hash)) return;
             const int h = find(key, hash);
-            const int pb = h ? sh.cursor[h - 1] : 0, pe = sh.cursor[h];
+            const int pb = h ? sh.p.cursor[h - 1] : 0, pe = sh.p.cursor[h];
             if (pe - pb < 2) return;
             for (int p = pb; p < pe; p += 4) {   // four list members per round of LDS latency
                 int j[4];
                 float x[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) { const int pk = min(p + k, pe - 1); j[k] = sh.post_row[pk]; x[k] = sh.post_val[pk]; }
+                for (int k = 0; k < 4; ++k) { const int pk = min(p + k, pe - 1); j[k] = sh.p.post_row[pk]; x[k] = sh.p.post_val[pk]; }
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    if (p + k < pe && j[k] < i) atomicAdd(&sh.G[j[k]][i], (double)(v * x[k]));
+                    if (p + k < pe && j[k] < i) atomicAdd(&sh.p.G[j[k]][i], (double)(v * x[k]));
             }
         });
         __syncthreads();
+    }
     }
     const int i = lane, jq = wv;
     const float si = sh.scale[i] * sh.sgn[i];
@@ -317,7 +517,7 @@ __global__ __launch_bounds__(SB_THREADS) void gram_blocks(
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int j = 4 * jq + e;
-        v[e] = j < i ? (float)sh.G[j][i] * si * sh.sgn[j] : 0.f;
+        v[e] = j < i ? (float)(at_once ? sh.a.G[j][i] : sh.p.G[j][i]) * si * sh.sgn[j] : 0.f;
     }
     *reinterpret_cast<float4_v *>(out + tile_at(4 * jq, i)) = v;
 }
@@ -347,7 +547,7 @@ struct BlocksArgs {
     const int32_t *place, *count;               // where shared columns lie in the compact vector; how many there are
     const SegRef *refs;
     const int32_t *segs;
-    float *coef_out;                            // per row of the context: its coefficient in the update, for scatter_unique
+    float *coef_out;                            // per row (solver by solver): its coefficient in the update, for spread_unique
     int64_t n_total;
     int G, k_pad;
     RoundScalars sc;
@@ -415,12 +615,15 @@ __global__ __launch_bounds__(SB_THREADS) void sdca_blocks(BlocksArgs A)
     };
     // segments of block b's rows (lane = row) -> LDS, with the running count
     auto publish = [&](int b, SegRef ref) __attribute__((always_inline)) {
-        int incl = ref.n;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += y;
-        }
+        int incl = ref.n;                        // running sum over the lanes, register to register
+#define CHICLE_DPP_SCAN(ctrl, rows) incl += __builtin_amdgcn_update_dpp(0, incl, ctrl, rows, 0xF, false)
+        CHICLE_DPP_SCAN(0x111, 0xF);             // row_shr 1, 2, 4, 8, then row_bcast 15 and 31
+        CHICLE_DPP_SCAN(0x112, 0xF);
+        CHICLE_DPP_SCAN(0x114, 0xF);
+        CHICLE_DPP_SCAN(0x118, 0xF);
+        CHICLE_DPP_SCAN(0x142, 0xA);
+        CHICLE_DPP_SCAN(0x143, 0xC);
+#undef CHICLE_DPP_SCAN
         sh.begin[b & 3][lane] = ref.begin;
         sh.pref[b & 3][lane + 1] = incl;
         if (lane == 0) sh.pref[b & 3][0] = 0;
@@ -468,7 +671,7 @@ __global__ __launch_bounds__(SB_THREADS) void sdca_blocks(BlocksArgs A)
                     float an = a + dl;
                     if (LOSS != 1) an = fminf(fmaxf(an, 0.f), 1.f);
                     gst(&cur_row.st->alpha, an);
-                    gst(A.coef_out + cur_row.row, coef);
+                    gst(A.coef_out + S.perm_off + cur_row.lr, coef);
                 }
                 cur_row = next_row; next_row = far_row; cur = nxt;
                 __syncthreads();                 // the steps are known
@@ -545,14 +748,15 @@ __global__ __launch_bounds__(SB_THREADS) void sdca_blocks(BlocksArgs A)
                 }
                 __syncthreads();
                 // while the recurrence runs: the next block's segments and tile, the rows of those after it
-                next_seg = load(segment(b + 1, t, next_row));
-                fetch_T(b + 1);
+                // (wavefront 1's own loads first: it waits for last block's before it asks for anything new)
                 if (resolver) {
                     publish(b + 2, refs_ahead);
                     refs_ahead = ref_of(rows_ahead);
                     rows_ahead = row_of(b + 4);
                     sh.dot[(b + 1) & 1][lane] = 0.0;      // (last read in block b - 1)
                 }
+                next_seg = load(segment(b + 1, t, next_row));
+                fetch_T(b + 1);
                 __syncthreads();
                 if (row >= 0) {
                     const float cf = sh.coef[row];
@@ -577,26 +781,81 @@ __global__ __launch_bounds__(SB_THREADS) void sdca_blocks(BlocksArgs A)
     if (g == 0) stamp_solver(A.sc, sid, 1);
 }
 
-// The updates of columns that a single row of the solver holds.  One wavefront per row.  Grid: (blocks over rows, chunk).
+// The updates of columns that a single row of the solver holds.  Where there is room, the assignment lays out for every
+// place of a solver's compact vector which of its rows writes there and the row's value (lr = -1: a shared column); the
+// update is then one stream over the vector, with the steps' coefficients in LDS.  (Row by row a scattered 4-byte store
+// per entry is bound by the compute unit's address path, about seven cycles each whichever cache it hits: 1.8 ms for 92
+// million of them, against 0.33 ms here.)
+struct UniqueSource { int32_t lr; float val; };
+constexpr int SPREAD_LDS_ROWS = 12288;           // coefficients of so many rows are staged in LDS
+constexpr int SPREAD_PER = 4096;                 // places per workgroup
+
+__global__ __launch_bounds__(256) void unique_sources(const ChunkDev *__restrict__ chunks, const int32_t *__restrict__ owner,
+                                                      const int32_t *__restrict__ chunk_first, const int64_t *__restrict__ u_off,
+                                                      UniqueSource *src)
+{
+    const ChunkDev &ch = chunks[blockIdx.y];
+    const int32_t *cid = chunk_compact_ids(ch);
+    UniqueSource *out = src + u_off[owner[blockIdx.y]];
+    const int lane = threadIdx.x & 63, first = chunk_first[blockIdx.y];
+    for (int r = blockIdx.x * 4 + (threadIdx.x >> 6); r < ch.n_rows; r += gridDim.x * 4)
+        for (int p = ch.row_ptr[r] + lane; p < ch.row_ptr[r + 1]; p += 64) {
+            const int c = cid[p];
+            if (c < 0) out[vec_index(c)] = UniqueSource{first + r, ch.val[p]};
+        }
+}
+
+// Grid: (workgroups over a solver's places, solver).
+__global__ __launch_bounds__(256) void spread_unique(const SolverDev *__restrict__ solvers, const int32_t *__restrict__ columns,
+                                                     const UniqueSource *__restrict__ src, const float *__restrict__ coef,
+                                                     float *u_all, const int64_t *__restrict__ u_off, int lds_rows)
+{
+    extern __shared__ float sp_coef[];
+    const int k = blockIdx.y, n = columns[k];
+    const int64_t base = u_off[k];
+    const SolverDev S = solvers[k];
+    const float *cf = coef + S.perm_off;
+    const int i0 = (int)blockIdx.x * SPREAD_PER, i1 = min(n, i0 + SPREAD_PER);
+    if (i0 >= n) return;
+    const bool staged = S.n_rows <= lds_rows;
+    if (staged)
+        for (int i = threadIdx.x; i < S.n_rows; i += 256) sp_coef[i] = cf[i];
+    __syncthreads();
+    const UniqueSource *s = src + base;
+    float *u = u_all + base;
+    for (int i = i0 + threadIdx.x; i < i1; i += 4 * 256) {
+        UniqueSource q[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q[j] = i + 256 * j < i1 ? s[i + 256 * j] : UniqueSource{-1, 0.f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (q[j].lr >= 0) u[i + 256 * j] = (staged ? sp_coef[q[j].lr] : cf[q[j].lr]) * q[j].val;
+    }
+}
+
+// Without that room: one wavefront per row.  Grid: (blocks over rows, chunk).
 __global__ __launch_bounds__(256) void scatter_unique(const ChunkDev *__restrict__ chunks, const int32_t *__restrict__ owner,
+                                                      const SolverDev *__restrict__ solvers, const int32_t *__restrict__ chunk_first,
                                                       const float *__restrict__ coef, float *u_all, const int64_t *__restrict__ u_off)
 {
     const ChunkDev &ch = chunks[blockIdx.y];
     const int32_t *cid = chunk_compact_ids(ch);
-    float *u = u_all + u_off[owner[blockIdx.y]];
+    const int k = owner[blockIdx.y];
+    float *u = u_all + u_off[k];
+    const float *of = coef + solvers[k].perm_off + chunk_first[blockIdx.y];
     const int lane = threadIdx.x & 63;
     for (int r = blockIdx.x * 4 + (threadIdx.x >> 6); r < ch.n_rows; r += gridDim.x * 4) {
-        const float cf = coef[ch.row_base + r];
+        const float cf = of[r];
         if (cf == 0.f) continue;
         const int e = ch.row_ptr[r + 1];
         for (int p = ch.row_ptr[r] + lane; p < e; p += 256) {
             int c[4];
             float v[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) { c[k] = p + 64 * k < e ? cid[p + 64 * k] : 0; v[k] = p + 64 * k < e ? ch.val[p + 64 * k] : 0.f; }
+            for (int j = 0; j < 4; ++j) { c[j] = p + 64 * j < e ? cid[p + 64 * j] : 0; v[j] = p + 64 * j < e ? ch.val[p + 64 * j] : 0.f; }
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (c[k] < 0) u[vec_index(c[k])] = cf * v[k];
+            for (int j = 0; j < 4; ++j)
+                if (c[j] < 0) u[vec_index(c[j])] = cf * v[j];
         }
     }
 }
