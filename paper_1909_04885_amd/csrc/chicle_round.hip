@@ -404,12 +404,17 @@ BatchedLayout batched_layout(const chicle_ctx *c)
 constexpr int DENSE_NAMED_MAX_D = 320;
 bool dense_eligible(const chicle_ctx *c, int32_t max_d) { return c->dense && c->d <= max_d; }
 
+// LDS a dense solver asks for at least: so much that no workgroup of the next pass's tile kernel, which runs beside it, is
+// placed on its compute unit.
+constexpr int DENSE_ALONE_LDS = 130 * 1024;
+
 template <int LOSS, typename SH>
 int launch_dense_shape(chicle_ctx *c)
 {
     auto kern = sdca_dense<LOSS, SH>;
-    HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SH::LDS_BYTES));
-    hipLaunchKernelGGL(kern, dim3(c->K), dim3(SH::THREADS), SH::LDS_BYTES, c->stream, c->chunks_dev, c->solvers_dev,
+    const size_t sh = std::max<size_t>(SH::LDS_BYTES, DENSE_ALONE_LDS);
+    HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+    hipLaunchKernelGGL(kern, dim3(c->K), dim3(SH::THREADS), sh, c->stream, c->chunks_dev, c->solvers_dev,
                        (const float *)c->tiles[c->tile_buf], c->u, c->ld_v, (int)c->d, dense_ld((int)c->d), scalars(c));
     HIP_TRY(c, hipGetLastError());
     return CHICLE_OK;
@@ -420,6 +425,14 @@ template <int LOSS>
 int launch_dense(chicle_ctx *c)
 {
     const int d = (int)c->d;
+    if (LOSS == 1 && d <= 64) {
+        auto kern = d <= 32 ? sdca_dense_squared<DenseShape<8, 4, 1, 64>> : sdca_dense_squared<DenseShape<16, 4, 1, 64>>;
+        HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DENSE_ALONE_LDS));
+        hipLaunchKernelGGL(kern, dim3(c->K), dim3(256), DENSE_ALONE_LDS, c->stream, c->chunks_dev, c->solvers_dev,
+                           (const float *)c->tiles[c->tile_buf], c->u, c->ld_v, d, dense_ld(d), scalars(c));
+        HIP_TRY(c, hipGetLastError());
+        return CHICLE_OK;
+    }
     if (d <= 32) return launch_dense_shape<LOSS, DenseShape<8, 4, 1, 64>>(c);
     if (d <= 64) return launch_dense_shape<LOSS, DenseShape<16, 4, 1, 64>>(c);
     if (d <= 128) return launch_dense_shape<LOSS, DenseShape<32, 8, 1, 64>>(c);

@@ -16,7 +16,7 @@
 // products 1.9e3, update 0.8e3), 32 x 1001 hinge 5.9e3, 64 x 28 squared 3.2e3.  Jobs of ten rounds of 4096 x 256 with
 // four solvers: 2.99 -> 0.72 ms (before: Gram matrix and rows of a block formed one after the other on the solver's
 // compute unit); three rounds of 20011 x 1001, logistic, eight solvers: 52.4 -> 1.43 ms (before: one row at a time);
-// fifty rounds of 500000 x 28, squared, 16 solvers: 50.4 -> 37.2 ms (before: the solver for short sparse rows, whose lanes
+// fifty rounds of 500000 x 28, squared, 16 solvers: 50.4 -> 37.2 ms, 28.1 with sdca_dense_squared (before: the solver for short sparse rows, whose lanes
 // all add to the same 28 places of LDS); 1000 x 48: 103 -> 90 us.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -199,6 +199,10 @@ __global__ __launch_bounds__(GD_THREADS) void gram_dense(
     }
 }
 
+// All four words of a load count as used here.  (Squared losses do not look at the label: the register of a word that
+// nobody uses is given to something else at once, which then waits for the load.)
+__device__ __forceinline__ void keep_loaded(const float4_v &v) { asm volatile("" ::"v"(v)); }
+
 // Sum over groups of L lanes, in the group's last lane.
 template <int L>
 __device__ __forceinline__ float group_sum_last(float v)
@@ -315,7 +319,8 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
     DenseRow row1 = {nullptr, nullptr}, row2 = row1, row3 = row1;
     RowState *st_cur = nullptr;
     float4_v cur = {0.f, 0.f, 0.f, 0.f}, nxt = {0.f, 0.f, 0.f, 0.f};
-    auto state_of = [&](const DenseRow &r) __attribute__((always_inline)) -> const RowState * { return r.st != nullptr ? r.st : chunks[0].st; };
+    const RowState *any = chunks[0].st;
+    auto state_of = [&](const DenseRow &r) __attribute__((always_inline)) -> const RowState * { return r.st != nullptr ? r.st : any; };
     // all threads: their 16-byte words of the next block's T, and where these lie in a tile
     float4_v t_in[TPT];
     auto fetch_T = [&](int b) __attribute__((always_inline)) {
@@ -430,7 +435,7 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
                 }
                 s_coef[lane] = dl * (LOSS == 1 ? 1.f : y) * sc.inv_c;      // the row's coefficient in the update
             }
-            st_cur = row1.st;
+            st_cur = b + 1 < nb ? row1.st : nullptr;
         }
         __syncthreads();
         // 3. the wavefront's part of the update; T of the next block
@@ -469,14 +474,15 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
         }
         if (CHAIN) {
             if (lane < BR) s_x[lane] = row2.x;               // (every wavefront has read the next block's)
+            keep_loaded(nxt);
             cur = nxt; row1 = row2; row2 = row3;
         }
         __syncthreads();
     };
     auto pass = [&](auto chain) __attribute__((always_inline)) {
-        for (int b = 0; b < nb; b += 2) {
+        for (int b = 0; b < nb; b += 2) {    // (an odd last block is followed by one that takes no step)
             block(chain, b, XA, XB);
-            if (b + 1 < nb) block(chain, b + 1, XB, XA);
+            block(chain, b + 1, XB, XA);
         }
     };
     if (__builtin_amdgcn_readfirstlane(wv) == 0) pass(std::true_type());
@@ -484,6 +490,168 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
 #pragma unroll
     for (int c = 0; c < UPT; ++c)
         if (tid + c * SH::THREADS < d) u_glb[tid + c * SH::THREADS] = (float)mine[c];
+    stamp_solver(sc, 1);
+}
+
+// Squared loss, rows of up to 64 columns.  With the recurrence solved in the tile nothing of a block is serial any more
+// but block after block, and a block is so short (a few hundred multiply-adds per wavefront) that it is over before a load
+// issued in the block before has returned: every load is issued three blocks ahead, into one of four register sets (the
+// loop is unrolled over them), from row addresses that were loaded three blocks before that.  Every wavefront turns the
+// dot products of its own 16 rows into their share of all 64 steps, so that the steps need no wavefront of their own and no
+// tile in LDS; three workgroup barriers per block.  500000 x 28, 16 solvers: 64 rows in 3.1e3 cycles with sdca_dense,
+// 2.2e3 here; fifty rounds 37.2 -> 28.1 ms.
+template <typename SH>
+__global__ __launch_bounds__(SH::THREADS) void sdca_dense_squared(
+    const ChunkDev *__restrict__ chunks, const SolverDev *__restrict__ solvers, const float *__restrict__ tiles, float *u_all,
+    int64_t ld_v, int d, int ld, RoundScalars sc)
+{
+    constexpr int L = SH::L, NW = SH::NW, G = SH::G, R = SH::R, I = SH::I, UW = SH::UW;
+    static_assert(SH::BR == BATCH && SH::M == 1 && UW <= SH::THREADS, "whole tiles, four columns per lane");
+    constexpr int SETS = 4, AHEAD = SETS - 1;
+    __shared__ __align__(16) float u[UW], part[NW][UW], s_step[NW][BATCH];
+    __shared__ __align__(16) float s_kb[2][BATCH][2];        // per row: c / (c + q) and residual - alpha (0, 0: no step)
+    __shared__ float s_alpha[2][BATCH];
+    __shared__ RowState *s_st[8][BATCH];
+    const SolverDev S = solvers[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    stamp_solver(sc, 0);
+    float *u_glb = u_all + (int64_t)blockIdx.x * ld_v;
+    const int nb = (S.n_rows + BATCH - 1) / BATCH;
+    const float *my_tiles = tiles + (int64_t)S.tile_begin * DENSE_TILE_FLOATS;
+    double mine = tid < d ? (double)u_glb[tid] : 0.0;        // thread: column
+    if (tid < UW) u[tid] = (float)mine;
+
+    const int row0 = wv * R + lane / L;                      // the lane's row in step it: row0 + it * G
+    const int col = 4 * (lane & (L - 1)), xo = col < ld ? col : 0;
+    auto tile_of = [&](int b) __attribute__((always_inline)) { return my_tiles + (int64_t)min(b, nb - 1) * DENSE_TILE_FLOATS; };
+    auto rows_of = [&](int b) __attribute__((always_inline)) { return reinterpret_cast<const DenseRow *>(tile_of(b) + BATCH * BATCH); };
+    const float *xp[SETS][I];
+    float4_v X[SETS][I], T[SETS][R / 4], st[SETS];
+    RowState *rec[SETS];
+    auto load_xp = [&](int b, const float *(&to)[I]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = 0; it < I; ++it) to[it] = rows_of(b)[row0 + it * G].x;
+    };
+    auto load_X = [&](const float *(&from)[I], float4_v (&to)[I]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = 0; it < I; ++it) to[it] = *(const CHICLE_GLOBAL float4_v *)(from[it] + xo);
+    };
+    auto load_T = [&](int b, float4_v (&to)[R / 4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int jq = 0; jq < R / 4; ++jq) to[jq] = *(const CHICLE_GLOBAL float4_v *)(tile_of(b) + tile_at(wv * R + 4 * jq, lane));
+    };
+    const RowState *any = chunks[0].st;
+    auto load_state = [&](RowState *r) __attribute__((always_inline)) { return gld_state(r != nullptr ? r : any); };
+    // what block b's steps need of its rows, from their state
+    auto publish = [&](int b, const float4_v &s) __attribute__((always_inline)) {
+        keep_loaded(s);
+        const bool live = s_st[b & 7][lane] != nullptr;
+        s_kb[b & 1][lane][0] = live ? sc.c / (sc.c + s.z) : 0.f;
+        s_kb[b & 1][lane][1] = live ? s.w - s.y : 0.f;
+        s_alpha[b & 1][lane] = s.y;
+    };
+    auto block = [&](auto first_wave, auto set, int b) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_wave)::value;
+        constexpr int s0 = decltype(set)::value, s1 = (s0 + 1) % SETS, s3 = (s0 + AHEAD) % SETS, s6 = (s0 + 2 * AHEAD) % SETS;
+        // loads of block b + 3, addresses of block b + 6
+        load_X(xp[s3], X[s3]);
+        load_T(b + AHEAD, T[s3]);
+        load_xp(b + 2 * AHEAD, xp[s6]);
+        if (FIRST) {
+            st[s3] = load_state(rec[s3]);
+            s_st[(b + AHEAD) & 7][lane] = b + AHEAD < nb ? rec[s3] : nullptr;
+            rec[s6] = rows_of(b + 2 * AHEAD)[lane].st;
+        }
+        // 1. dot products of the wavefront's rows, and what their unclipped steps add to all 64
+        const float4_v uu = *reinterpret_cast<const float4_v *>(u + col);
+        float p[I], acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int it = 0; it < I; ++it) {
+            p[it] = X[s0][it][0] * uu[0];
+#pragma unroll
+            for (int e = 1; e < 4; ++e) p[it] = fmaf(X[s0][it][e], uu[e], p[it]);
+            p[it] = group_sum_last<L>(p[it]);
+        }
+        float dot[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) dot[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p[j / G]), (j % G) * L + L - 1));
+        __builtin_amdgcn_sched_barrier(0);       // (a use right behind its lane read stalls)
+#pragma unroll
+        for (int j = 0; j < R; j += 2) {
+            const float4_v kb = *reinterpret_cast<const float4_v *>(&s_kb[b & 1][wv * R + j][0]);
+            acc[j & 3] = fmaf(kb[0] * (kb[1] - dot[j]), T[s0][j >> 2][j & 3], acc[j & 3]);
+            acc[(j + 1) & 3] = fmaf(kb[2] * (kb[3] - dot[j + 1]), T[s0][j >> 2][(j + 1) & 3], acc[(j + 1) & 3]);
+        }
+        s_step[wv][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+        __syncthreads();
+        // 2. the wavefront's part of the update
+        float4_v q = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int it = 0; it < I; ++it) {
+            float dl = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) dl += s_step[w][row0 + it * G];
+            const float cf = dl * sc.inv_c;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[e] = fmaf(cf, X[s0][it][e], q[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[e] = sum_over_groups<L>(q[e]);
+        if (lane < L) *reinterpret_cast<float4_v *>(&part[wv][4 * lane]) = q;
+        if (FIRST) {
+            float dl = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) dl += s_step[w][lane];
+            RowState *r = s_st[b & 7][lane];
+            if (r != nullptr) gst(&r->alpha, s_alpha[b & 1][lane] + dl);
+            publish(b + 1, st[s1]);
+        }
+        __syncthreads();
+        // 3. update of the private vector
+        if (tid < d) {
+            double s = 0.0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) s += (double)part[w][tid];
+            mine += s;
+            u[tid] = (float)mine;
+        }
+        __syncthreads();
+    };
+    auto pass = [&](auto first_wave) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_wave)::value;
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            load_xp(k, xp[k]);
+            if (FIRST) rec[k] = rows_of(k)[lane].st;
+        }
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {    // (in the order of the loop)
+            load_X(xp[k], X[k]);
+            load_T(k, T[k]);
+            load_xp(k + AHEAD, xp[(k + AHEAD) % SETS]);
+            if (FIRST) {
+                st[k] = load_state(rec[k]);
+                s_st[k][lane] = k < nb ? rec[k] : nullptr;
+                rec[(k + AHEAD) % SETS] = rows_of(k + AHEAD)[lane].st;
+            }
+        }
+        if (FIRST) publish(0, st[0]);
+        __syncthreads();
+        // whole rounds of the register sets (blocks past the end take no step): a loop left in the middle has paths that
+        // the compiler joins at its head, with the smaller counts of loads in flight
+        for (int b = 0; b < nb; b += SETS) {
+            block(first_wave, std::integral_constant<int, 0>(), b);
+            block(first_wave, std::integral_constant<int, 1>(), b + 1);
+            block(first_wave, std::integral_constant<int, 2>(), b + 2);
+            block(first_wave, std::integral_constant<int, 3>(), b + 3);
+        }
+    };
+    if (nb > 0) {
+        if (wv == 0) pass(std::true_type());
+        else pass(std::false_type());
+    }
+    if (tid < d) u_glb[tid] = (float)mine;
     stamp_solver(sc, 1);
 }
 

@@ -673,6 +673,7 @@ __global__ __launch_bounds__(SB_THREADS) void sdca_blocks(BlocksArgs A)
                     gst(&cur_row.st->alpha, an);
                     gst(A.coef_out + S.perm_off + cur_row.lr, coef);
                 }
+                keep_loaded(nxt);
                 cur_row = next_row; next_row = far_row; cur = nxt;
                 __syncthreads();                 // the steps are known
                 __syncthreads();                 // ... and added
