@@ -519,8 +519,8 @@ int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, hipStream_t stream)
     return CHICLE_OK;
 }
 
-// The batched local pass.  Tiles of `perm` come from the set prepared ahead when there is one, else
-// they are computed first on the main stream.  With perm_next, the tiles of the next pass are started
+// The batched local pass.  Tiles of `perm` come from the set prepared ahead when there is one (the main stream has
+// waited for it), else they are computed first on the main stream.  With perm_next, the tiles of the next pass are started
 // on the side stream so that they run beside this pass's chain kernel (which occupies K of the 256
 // compute units); they depend on the data and the orders only.
 template <int LOSS>
@@ -530,15 +530,12 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
     int rc;
     if (tiles_ready) {
         c->tile_buf = 1 - c->tile_buf;
-        HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_join, 0));
     } else {
-        if (c->ahead_tiles) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_join, 0));   // unused, but let it finish
         seg_begin(c, CHICLE_SEG_EPOCH_GRAM);
         rc = launch_gram<LOSS>(c, perm, c->tile_buf, c->stream);
         seg_end(c, CHICLE_SEG_EPOCH_GRAM);
         if (rc) return rc;
     }
-    c->ahead_tiles = false;
     if (perm_next) HIP_TRY(c, hipEventRecord(c->ev_fork, c->stream));   // everything enqueued so far
     const int ml = std::max(c->max_list, 1);
     const BatchedLayout lay = batched_layout(c);
@@ -1354,11 +1351,24 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
     if (c->state != ST_READY) return fail(c, CHICLE_ESTATE, c->state == ST_LOADING ? "assign first" : "aggregate before the next local epoch");
     if (!perm_device && !c->ahead_valid)
         return fail(c, CHICLE_EINVAL, "perm is NULL and the previous pass announced no orders (or an assign dropped them)");
+    bool batched = false;
+    if (c->solver_kind == CHICLE_SOLVER_BATCHED) {
+        batched = dense_eligible(c, DENSE_NAMED_MAX_D) || batched_eligible(c);
+        if (!batched)      // (nothing announced is touched by a refused call)
+            return fail(c, CHICLE_EINVAL, "batched solver needs sparse rows of at most %d entries and at most %d chunks per solver, or dense rows of at most %d columns", GRAM_MAX_ROW, BATCHED_MAX_LIST, DENSE_NAMED_MAX_D);
+    } else if (c->solver_kind == CHICLE_SOLVER_AUTO) {
+        batched = dense_eligible(c, DENSE_MAX_D) || batched_eligible(c);
+    }
     // NULL: the orders the previous call announced, from the library's own copy of them
     const bool announced = perm_device == nullptr;
-    const bool tiles_ready = announced && c->ahead_tiles;
+    const bool tiles_ready = announced && batched && c->ahead_tiles;
     if (announced) perm_device = c->perm_ahead[1 - c->ahead_buf];
     c->ahead_valid = false;
+    // Tiles prepared ahead are of the orders that the previous pass announced: this pass uses them or they are dropped,
+    // whichever solver it runs.  Either way everything from here on follows the kernel that forms them (it reads its copy
+    // of the orders, which the announcement after this one overwrites).
+    if (c->ahead_tiles) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_join, 0));
+    c->ahead_tiles = false;
     if (perm_next_device) {
         // Copied on the context's stream, so the caller's buffer is an ordinary stream-ordered input.
         HIP_TRY(c, hipMemcpyAsync(c->perm_ahead[c->ahead_buf], perm_next_device, sizeof(int32_t) * (size_t)c->n_total,
@@ -1366,14 +1376,6 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
         perm_next_device = c->perm_ahead[c->ahead_buf];
         c->ahead_buf = 1 - c->ahead_buf;
         c->ahead_valid = true;
-    }
-    bool batched = false;
-    if (c->solver_kind == CHICLE_SOLVER_BATCHED) {
-        batched = dense_eligible(c, DENSE_NAMED_MAX_D) || batched_eligible(c);
-        if (!batched)
-            return fail(c, CHICLE_EINVAL, "batched solver needs sparse rows of at most %d entries and at most %d chunks per solver, or dense rows of at most %d columns", GRAM_MAX_ROW, BATCHED_MAX_LIST, DENSE_NAMED_MAX_D);
-    } else if (c->solver_kind == CHICLE_SOLVER_AUTO) {
-        batched = dense_eligible(c, DENSE_MAX_D) || batched_eligible(c);
     }
     seg_begin(c, CHICLE_SEG_LOCAL_EPOCH);
     int rc = CHICLE_OK;

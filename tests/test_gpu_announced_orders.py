@@ -1,0 +1,68 @@
+"""Announced visiting orders where the solver kind changes between passes: every pass runs with the orders announced last,
+also when the pass between used another solver than the one that prepared tiles, or was refused.  Against the oracle."""
+import numpy as np
+import pytest
+
+from harness import TOL_DW, dw_floor, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+# solver kind of each pass; "refused": a BATCHED call that the data does not allow, between two passes
+SEQUENCES = [["auto", "rowwise", "auto", "auto"], ["auto", "rowwise", "rowwise", "auto", "rowwise", "auto"],
+             ["rowwise", "auto", "rowwise_one_cu", "auto"], ["auto", "refused", "auto", "refused", "rowwise", "auto"]]
+
+
+def _problem(kind, n):
+    from workloads.generate import Problem
+    g = np.random.default_rng(7)
+    y = np.where(g.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    bounds = np.array([0, 70, 200, n], dtype=np.int64)
+    if kind != "sparse":
+        d = kind
+        X = (g.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+        return Problem("announced", "hinge", n, d, 0.02, y, bounds, X=X)
+    d, m = 600, 20
+    col = np.concatenate([np.sort(g.choice(d, m, replace=False)) for _ in range(n)]).astype(np.int32)
+    val = (g.standard_normal(n * m) / np.sqrt(m)).astype(np.float32)
+    return Problem("announced", "hinge", n, d, 0.02, y, bounds, row_ptr=np.arange(n + 1, dtype=np.int64) * m, col=col, val=val)
+
+
+@pytest.mark.parametrize("kinds", SEQUENCES, ids=lambda s: "-".join(s))
+@pytest.mark.parametrize("kind", [28, 100, 400, "sparse"])
+def test_pass_runs_the_orders_announced_last(oracle_mod, kind, kinds):
+    import torch
+    import paper_1909_04885_amd as binding
+    assert torch.cuda.is_available()
+    p = _problem(kind, 333)
+    print("\ncase announced %s %s" % (kind, kinds), flush=True)
+    K, table = 2, np.array([0, 1, 0], dtype=np.int32)
+    o = oracle_mod.OracleCoCoA.from_problem(p)
+    g = binding.ChicleRound.from_problem(p, max_solvers=K)
+    o.assign(K, table)
+    g.assign(K, table)
+    rng = np.random.default_rng(11)
+    perms = [[rng.permutation(int(m)).astype(np.int32) for m in g.solver_rows()] for _ in range(len(kinds) + 1)]
+    announced = False
+    for r, solver in enumerate(kinds):
+        if solver == "refused":
+            if kind == 400:           # too wide for the solver by name: refused, and the announcement stands
+                g.set_solver("batched")
+                with pytest.raises(binding.ChicleError) as e:
+                    g.local_epoch_ahead(None, g.upload_perm(perms[0]))
+                assert e.value.code == -1
+            perms[r + 1] = perms[r]   # the pass that follows runs what is announced already
+            continue
+        g.set_solver(solver)
+        current, following = (None if announced else g.upload_perm(perms[r])), None
+        if r + 1 < len(kinds):
+            following = g.upload_perm(perms[r + 1])
+        g.local_epoch_ahead(current, following)
+        announced = following is not None
+        floor = dw_floor(float(np.linalg.norm(o.w)))
+        ref = o.local_epoch(perms[r])
+        for k in range(K):
+            e = rel_l2(g.get_delta_w(k), ref[k], floor)
+            assert e <= TOL_DW, "pass %d (%s) solver %d: %.3e" % (r, solver, k, e)
+        o.aggregate()
+        g.aggregate()
+    g.close()
