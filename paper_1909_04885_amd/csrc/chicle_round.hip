@@ -1504,10 +1504,13 @@ int chicle_gap_noalloc(chicle_ctx *c, double *primal, double *dual, double *gap)
 // Device -> pageable host memory.  A copy straight to pageable memory of this size runs at a fifth of the link's rate (80 MB:
 // 8 ms; to pinned memory 1.4 ms), and half of it is the pages of a fresh array being touched for the first time.  Pieces
 // therefore go through pinned memory, and several threads copy them on, each with a piece and an event of its own.
-// Vectors of less than two pieces take the plain copy.  The stream is idle up to the copy on return.
+// Vectors of less than two pieces take the plain copy, and so does everything on hipStreamPerThread: that handle means a
+// stream of its own in every thread, and the helpers' copies would not follow the caller's kernels.
+// The stream is idle up to the copy on return.
 static int read_to_host(chicle_ctx *c, void *dst, const void *src, size_t bytes)
 {
-    if (bytes >= 2 * READ_PIECE && !c->read_pinned) {
+    const bool in_pieces = bytes >= 2 * READ_PIECE && c->stream != hipStreamPerThread;
+    if (in_pieces && !c->read_pinned) {
         bool ok = hipHostMalloc((void **)&c->read_pinned, READ_PIECE * READ_THREADS, hipHostMallocDefault) == hipSuccess;
         for (int t = 0; ok && t < READ_THREADS; ++t)
             ok = c->read_ev[t] != nullptr || hipEventCreateWithFlags(&c->read_ev[t], hipEventDisableTiming) == hipSuccess;
@@ -1517,7 +1520,7 @@ static int read_to_host(chicle_ctx *c, void *dst, const void *src, size_t bytes)
             (void)hipGetLastError();
         }
     }
-    if (bytes < 2 * READ_PIECE || !c->read_pinned) {
+    if (!in_pieces || !c->read_pinned) {
         HIP_TRY(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream));
         return CHICLE_OK;
     }
