@@ -1510,6 +1510,11 @@ int chicle_gap_noalloc(chicle_ctx *c, double *primal, double *dual, double *gap)
 static int read_to_host(chicle_ctx *c, void *dst, const void *src, size_t bytes)
 {
     const bool in_pieces = bytes >= 2 * READ_PIECE && c->stream != hipStreamPerThread;
+    int before = 0;
+    if (in_pieces) {                       // the events must be of the stream's device, whichever the caller has selected
+        HIP_TRY(c, hipGetDevice(&before));
+        HIP_TRY(c, hipSetDevice(c->device));
+    }
     if (in_pieces && !c->read_pinned) {
         bool ok = hipHostMalloc((void **)&c->read_pinned, READ_PIECE * READ_THREADS, hipHostMallocDefault) == hipSuccess;
         for (int t = 0; ok && t < READ_THREADS; ++t)
@@ -1521,6 +1526,7 @@ static int read_to_host(chicle_ctx *c, void *dst, const void *src, size_t bytes)
         }
     }
     if (!in_pieces || !c->read_pinned) {
+        if (in_pieces) (void)hipSetDevice(before);
         HIP_TRY(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream));
         return CHICLE_OK;
     }
@@ -1545,8 +1551,6 @@ static int read_to_host(chicle_ctx *c, void *dst, const void *src, size_t bytes)
         for (; started < READ_THREADS - 1; ++started) others[started] = std::thread(work, started + 1);
     } catch (...) {                        // no more threads to be had: those that run do it all
     }
-    int before = 0;
-    (void)hipGetDevice(&before);
     work(0);
     (void)hipSetDevice(before);
     for (int t = 0; t < started; ++t) others[t].join();
