@@ -1122,14 +1122,23 @@ int chicle_load_chunk_dense(chicle_ctx *c, int32_t chunk_id, int32_t n_rows, con
     float *xd = (float *)carve(c, sizeof(float) * (size_t)n_rows * (size_t)ld);
     if (!xd) return fail(c, CHICLE_ENOMEM, "chunk store full");
     ch.val = xd;
-    std::vector<float> padded;     // rows end in zero columns up to a multiple of four (lives until finish_load has waited)
-    const float *from = X;
-    if (ld != c->d) {
-        padded.assign((size_t)n_rows * (size_t)ld, 0.f);
-        for (int32_t r = 0; r < n_rows; ++r) std::memcpy(&padded[(size_t)r * (size_t)ld], X + (int64_t)r * c->d, sizeof(float) * (size_t)c->d);
-        from = padded.data();
+    if (ld == c->d) {
+        HIP_TRY(c, hipMemcpyAsync(xd, X, sizeof(float) * (size_t)entries, hipMemcpyHostToDevice, c->stream));
+    } else {
+        // Rows end in zero columns up to a multiple of four.  The caller's rows go as they are into device memory that is
+        // free until the first assign (the private vectors or the tile sets), a part at a time, and from there into place:
+        // the link is as fast as for rows that need no padding, and the host holds no second copy.
+        char *part = c->layout_dev;
+        size_t bytes = c->layout_bytes;
+        if (sizeof(float) * (size_t)c->u_capacity > bytes) { part = (char *)c->u; bytes = sizeof(float) * (size_t)c->u_capacity; }
+        const int64_t room = (int64_t)(bytes / sizeof(float));
+        for (int64_t at = 0; at < entries; at += room) {
+            const int64_t m = std::min(room, entries - at);
+            HIP_TRY(c, hipMemcpyAsync(part, X + at, sizeof(float) * (size_t)m, hipMemcpyHostToDevice, c->stream));
+            hipLaunchKernelGGL(pad_rows, dim3(grid_for(m, 256, 8192)), dim3(256), 0, c->stream, (const float *)part, at, m, (int)c->d, ld, xd);
+            HIP_TRY(c, hipGetLastError());
+        }
     }
-    HIP_TRY(c, hipMemcpyAsync(xd, from, sizeof(float) * (size_t)n_rows * (size_t)ld, hipMemcpyHostToDevice, c->stream));
     rc = finish_load(c, chunk_id, ch, y, alpha0, q);
     if (rc == CHICLE_OK) c->max_row_len = c->d;
     return rc;

@@ -179,6 +179,20 @@ __global__ __launch_bounds__(256) void max_entries_beyond(const ChunkDev *__rest
     if (most > 0) atomicMax(out, most);
 }
 
+// Entries [first, first + n) of a row-major matrix with d columns, given in `in`, into rows of ld floats that end in zeros.
+__global__ __launch_bounds__(256) void pad_rows(const float *__restrict__ in, int64_t first, int64_t n, int d, int ld, float *out)
+{
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
+        const int64_t r = (first + i) / d;
+        const int k = (int)(first + i - r * d);
+        float *row = out + r * ld;
+        row[k] = in[i];
+        if (k == d - 1)
+            for (int z = d; z < ld; ++z) row[z] = 0.f;
+    }
+}
+
 // out[col_of[r]] = in[r] * scale (internal order -> caller's column ids).
 template <typename T>
 __global__ __launch_bounds__(256) void to_caller_order(const T *__restrict__ in,
