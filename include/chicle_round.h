@@ -284,6 +284,12 @@ int chicle_get_assignment(chicle_ctx *ctx, int32_t *chunk_to_solver_out, int32_t
 int chicle_debug_gram(chicle_ctx *ctx, const int32_t *perm_device, float *tiles_out,
                       int64_t capacity_floats, int32_t *n_tiles_out);
 
+/* Diagnostic: what the next local pass runs under the current assignment and solver kind (host, pure), four integers:
+ * the solver (0 row by row, 1 batched, 2 dense blocks, 3 blocks over shared columns), workgroups per solver, 1 where the
+ * blocks over shared columns keep their private vectors in float (else in double), 1 where their unshared columns are
+ * updated row by row (else as one stream).  Errors: EINVAL, ESTATE (before the first assign). */
+int chicle_debug_solver(chicle_ctx *ctx, int32_t *out);
+
 /* Wait for the stream; report any deferred kernel error. */
 int chicle_sync(chicle_ctx *ctx);
 

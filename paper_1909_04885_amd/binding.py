@@ -30,6 +30,7 @@ EXPORTS = [
     "chicle_last_kernel_ms", "chicle_last_error", "chicle_destroy",
     "chicle_solver_ms", "chicle_projected_iteration_time", "chicle_scale_out", "chicle_scale_in",
     "chicle_rebalance", "chicle_next_solver_count", "chicle_gap_noalloc", "chicle_set_l1",
+    "chicle_debug_solver",
 ]
 
 
@@ -81,6 +82,7 @@ def load_library():
         "chicle_set_alpha": (ctypes.c_int, [vp, i32, vp]),
         "chicle_get_assignment": (ctypes.c_int, [vp, vp, ctypes.POINTER(i32)]),
         "chicle_debug_gram": (ctypes.c_int, [vp, vp, vp, i64, ctypes.POINTER(i32)]),
+        "chicle_debug_solver": (ctypes.c_int, [vp, vp]),
         "chicle_sync": (ctypes.c_int, [vp]),
         "chicle_set_profiling": (ctypes.c_int, [vp, i32]),
         "chicle_last_kernel_ms": (ctypes.c_int, [vp, i32, ctypes.POINTER(ctypes.c_float)]),
@@ -361,6 +363,12 @@ class ChicleRound:
         out = np.empty((n.value, 128, 64), dtype=np.float32)
         self._check(self._L.chicle_debug_gram(self._h, ptr, _ptr(out), out.size, ctypes.byref(n)))
         return out
+
+    def debug_solver(self):
+        """(solver of the next pass, workgroups per solver, private vectors in float, unshared columns row by row)."""
+        out = np.zeros(4, dtype=np.int32)
+        self._check(self._L.chicle_debug_solver(self._h, _ptr(out)))
+        return ("rowwise", "batched", "dense", "blocks")[out[0]], int(out[1]), bool(out[2]), bool(out[3])
 
     def sync(self):
         self._check(self._L.chicle_sync(self._h))

@@ -414,6 +414,29 @@ BatchedLayout batched_layout(const chicle_ctx *c)
 constexpr int DENSE_NAMED_MAX_D = 320;
 bool dense_eligible(const chicle_ctx *c, int32_t max_d) { return c->dense && c->d <= max_d; }
 
+// The solver of the next pass.
+enum Route { ROUTE_ROWWISE = 0, ROUTE_BATCHED = 1, ROUTE_DENSE = 2, ROUTE_BLOCKS = 3 };
+Route route_of(const chicle_ctx *c)
+{
+    const bool by_name = c->solver_kind == CHICLE_SOLVER_BATCHED;
+    if (!by_name && c->solver_kind != CHICLE_SOLVER_AUTO) return ROUTE_ROWWISE;
+    if (c->dense) return dense_eligible(c, by_name ? DENSE_NAMED_MAX_D : DENSE_MAX_D) ? ROUTE_DENSE : ROUTE_ROWWISE;
+    if (batched_eligible(c)) return ROUTE_BATCHED;
+    return !by_name && c->blocks_ready ? ROUTE_BLOCKS : ROUTE_ROWWISE;
+}
+
+// Tail workgroups per solver of the batched solver, or -1: every solver on one compute unit.  Columns outside the
+// LDS-resident head, and compute units to spare: every solver gets a head workgroup and SPLIT_TAILS tail workgroups (all of
+// them must be resident together: they wait for each other).  Where every column is in the LDS-resident head there is
+// nothing for tails to do: the head workgroups run alone, and their gathers and scatters never leave LDS.
+int split_tails(const chicle_ctx *c)
+{
+    const int n_hot = batched_layout(c).n_hot, n_tails = n_hot < c->d ? SPLIT_TAILS : 0;
+    const int k_pad = (c->K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
+    return c->split_allowed && (1 + n_tails) * k_pad <= c->cu_count &&
+           (n_tails == 0 || sizeof(double) * (size_t)n_hot >= 2 * RING * BATCH * sizeof(RowSlot)) ? n_tails : -1;   // a tail keeps its rows there
+}
+
 // LDS a dense solver asks for at least: so much that no workgroup of the next pass's tile kernel, which runs beside it, is
 // placed on its compute unit.
 constexpr int DENSE_ALONE_LDS = 130 * 1024;
@@ -543,19 +566,13 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
     const int n_hot = lay.n_hot;
     const int64_t *u_off = c->compact ? c->u_off_dev : nullptr;
     const int k_pad = (c->K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
-    // Columns outside the LDS-resident head, and compute units to spare: every solver gets a head workgroup
-    // and SPLIT_TAILS tail workgroups (all of them must be resident together: they wait for each other).
-    // (where every column is in the LDS-resident head there is nothing for tails to do: the head workgroups run
-    // alone, and their gathers and scatters never leave LDS)
-    const int n_tails = n_hot < c->d ? SPLIT_TAILS : 0;
-    const bool split = !c->dense && c->split_allowed && (1 + n_tails) * k_pad <= c->cu_count &&
-                       (n_tails == 0 || sizeof(double) * (size_t)n_hot >= 2 * RING * BATCH * sizeof(RowSlot));   // a tail keeps its rows there
+    const int n_tails = split_tails(c);
     if (c->dense) {
         seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
         rc = launch_dense<LOSS>(c);
         seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
         if (rc) return rc;
-    } else if (split) {
+    } else if (n_tails >= 0) {
         SplitArgs A;
         A.chunks = c->chunks_dev; A.solvers = c->solvers_dev; A.solver_chunks = c->solver_chunks_dev;
         A.solver_prefix = c->solver_prefix_dev; A.perm = perm; A.tiles = c->tiles[c->tile_buf]; A.u_all = c->u;
@@ -1360,14 +1377,10 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
     if (c->state != ST_READY) return fail(c, CHICLE_ESTATE, c->state == ST_LOADING ? "assign first" : "aggregate before the next local epoch");
     if (!perm_device && !c->ahead_valid)
         return fail(c, CHICLE_EINVAL, "perm is NULL and the previous pass announced no orders (or an assign dropped them)");
-    bool batched = false;
-    if (c->solver_kind == CHICLE_SOLVER_BATCHED) {
-        batched = dense_eligible(c, DENSE_NAMED_MAX_D) || batched_eligible(c);
-        if (!batched)      // (nothing announced is touched by a refused call)
-            return fail(c, CHICLE_EINVAL, "batched solver needs sparse rows of at most %d entries and at most %d chunks per solver, or dense rows of at most %d columns", GRAM_MAX_ROW, BATCHED_MAX_LIST, DENSE_NAMED_MAX_D);
-    } else if (c->solver_kind == CHICLE_SOLVER_AUTO) {
-        batched = dense_eligible(c, DENSE_MAX_D) || batched_eligible(c);
-    }
+    const Route route = route_of(c);
+    if (c->solver_kind == CHICLE_SOLVER_BATCHED && route == ROUTE_ROWWISE)      // (nothing announced is touched by a refused call)
+        return fail(c, CHICLE_EINVAL, "batched solver needs sparse rows of at most %d entries and at most %d chunks per solver, or dense rows of at most %d columns", GRAM_MAX_ROW, BATCHED_MAX_LIST, DENSE_NAMED_MAX_D);
+    const bool batched = route == ROUTE_BATCHED || route == ROUTE_DENSE;
     // NULL: the orders the previous call announced, from the library's own copy of them
     const bool announced = perm_device == nullptr;
     const bool tiles_ready = announced && batched && c->ahead_tiles;
@@ -1394,7 +1407,7 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
             rc = c->loss == CHICLE_LOSS_HINGE ? launch_batched<0>(c, perm_device, tiles_ready, perm_next_device)
                  : c->loss == CHICLE_LOSS_SQUARED ? launch_batched<1>(c, perm_device, tiles_ready, perm_next_device)
                                                   : launch_batched<2>(c, perm_device, tiles_ready, perm_next_device);
-        } else if (c->blocks_ready && c->solver_kind == CHICLE_SOLVER_AUTO) {
+        } else if (route == ROUTE_BLOCKS) {
             rc = c->loss == CHICLE_LOSS_HINGE ? launch_blocks<0>(c, perm_device)
                  : c->loss == CHICLE_LOSS_SQUARED ? launch_blocks<1>(c, perm_device)
                                                   : launch_blocks<2>(c, perm_device);
@@ -1743,6 +1756,19 @@ int chicle_last_kernel_ms(chicle_ctx *c, int32_t segment, float *ms_out)
     if (!c->seg[segment].recorded) return fail(c, CHICLE_ESTATE, "segment %d was not recorded (profiling off, or not run)", segment);
     HIP_TRY(c, hipEventSynchronize(c->seg[segment].stop));
     HIP_TRY(c, hipEventElapsedTime(ms_out, c->seg[segment].start, c->seg[segment].stop));
+    return CHICLE_OK;
+}
+
+int chicle_debug_solver(chicle_ctx *c, int32_t *out)
+{
+    if (!c || !out) return CHICLE_EINVAL;
+    if (c->state == ST_LOADING) return fail(c, CHICLE_ESTATE, "no assignment yet");
+    const Route route = route_of(c);
+    const bool clustered = c->long_rows && c->cluster > 1 && c->cluster_allowed;
+    out[0] = route;
+    out[1] = route == ROUTE_BLOCKS ? c->blocks_g : route == ROUTE_BATCHED ? 1 + std::max(0, split_tails(c)) : route == ROUTE_ROWWISE && clustered ? c->cluster : 1;
+    out[2] = route == ROUTE_BLOCKS && !c->blocks_double;
+    out[3] = route == ROUTE_BLOCKS && c->sources_dev == nullptr;
     return CHICLE_OK;
 }
 

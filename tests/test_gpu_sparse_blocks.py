@@ -1,6 +1,8 @@
 """The block solver for sparse rows of any length at its edges, against the oracle: rows with more segments than
 threads, blocks whose entries are joined in parts, solvers of one row and of none, clusters of 1, 2, 4 and 8 workgroups,
-data without a single shared column, and more shared columns than eight workgroups hold (the row-wise solver's case)."""
+data without a single shared column, unshared columns with and without room for the table that streams them, and more
+shared columns than eight workgroups hold or rows than there is room to lay out (the row-wise solver's cases).  Every case
+states which solver it is to run."""
 import numpy as np
 import pytest
 
@@ -18,35 +20,46 @@ def _rows(g, lens, d, zipf):
     return [np.sort(g.choice(d, int(m), replace=False)) for m in lens]
 
 
+def _half_shared(g, n, d):
+    """48 columns out of 4000 and 48 of the row's own."""
+    return [np.sort(np.concatenate([g.choice(4000, 48, replace=False), 4000 + np.arange(48) + 48 * i])) for i in range(n)]
+
+
+# what runs: (solver, workgroups per solver, private vectors in float, unshared columns row by row)
+G1, G2, G4, G8 = [("blocks", k, False, False) for k in (1, 2, 4, 8)]
 CASES = {
-    # name: (rows, columns, row lengths, Zipf columns, solvers, l1)
-    "ragged": (700, 5000, lambda g, n: np.clip(np.round(g.lognormal(np.log(30), 0.6, n)), 0, 200), True, 3, 0.0),
-    "ragged_l1": (500, 5000, lambda g, n: np.clip(np.round(g.lognormal(np.log(30), 0.6, n)), 0, 200), True, 3, 0.02),
-    "just_over": (300, 400, lambda g, n: np.where(np.arange(n) == 7, 49, 20), False, 2, 0.0),
-    "more_segments_than_threads": (200, 3000, lambda g, n: g.integers(0, 600, n), False, 2, 0.0),
-    "joined_in_parts": (150, 2500, lambda g, n: g.integers(1000, 2500, n), False, 2, 0.0),
-    "nothing_shared": (5, 100000, lambda g, n: np.full(n, 60), False, 5, 0.0),
-    "two_members": (400, 30000, lambda g, n: g.integers(100, 600, n), False, 2, 0.0),
-    "four_members": (900, 60000, lambda g, n: g.integers(200, 600, n), False, 2, 0.0),
-    "eight_members": (1800, 100000, lambda g, n: g.integers(300, 600, n), False, 2, 0.0),
-    "eight_members_in_float": (1300, 170000, lambda g, n: g.integers(900, 1000, n), False, 2, 0.0),
-    "too_many_shared": (2400, 360000, lambda g, n: g.integers(900, 1100, n), False, 2, 0.0),
+    # name: (rows, columns, row lengths, Zipf columns, solvers, l1, what runs)
+    "ragged": (700, 5000, lambda g, n: np.clip(np.round(g.lognormal(np.log(30), 0.6, n)), 0, 200), True, 3, 0.0, G1),
+    "ragged_l1": (500, 5000, lambda g, n: np.clip(np.round(g.lognormal(np.log(30), 0.6, n)), 0, 200), True, 3, 0.02, G1),
+    "just_over": (300, 400, lambda g, n: np.where(np.arange(n) == 7, 49, 20), False, 2, 0.0, G1),
+    "more_segments_than_threads": (200, 3000, lambda g, n: g.integers(0, 600, n), False, 2, 0.0, G1),
+    "joined_in_parts": (150, 2500, lambda g, n: g.integers(1000, 2500, n), False, 2, 0.0, G1),
+    "nothing_shared": (5, 100000, lambda g, n: np.full(n, 60), False, 5, 0.0, G1),
+    "unshared_row_by_row": (3000, 148000, lambda g, n: np.full(n, 96), None, 2, 0.0, ("blocks", 1, False, True)),
+    "two_members": (400, 30000, lambda g, n: g.integers(100, 600, n), False, 2, 0.0, G2),
+    "four_members": (900, 60000, lambda g, n: g.integers(200, 600, n), False, 2, 0.0, G4),
+    "eight_members": (1800, 100000, lambda g, n: g.integers(300, 600, n), False, 2, 0.0, G8),
+    "eight_members_in_float": (1300, 170000, lambda g, n: g.integers(900, 1000, n), False, 2, 0.0, ("blocks", 8, True, False)),
+    "too_many_shared": (2400, 360000, lambda g, n: g.integers(900, 1100, n), False, 2, 0.0, ("rowwise", 4, False, False)),
+    "no_room_to_lay_out": (12000, 500, lambda g, n: np.full(n, 90), False, 2, 0.0, ("rowwise", 1, False, False)),
+    "room_to_lay_out": (12000, 500, lambda g, n: np.full(n, 80), False, 2, 0.0, G1),
+    "no_room_for_eight_members": (12000, 90000, lambda g, n: np.full(n, 80), False, 2, 0.0, ("rowwise", 1, False, False)),
 }
+LARGE = {"no_room_to_lay_out", "room_to_lay_out", "no_room_for_eight_members"}     # one loss, one round
 
 
-@pytest.mark.parametrize("loss", ["hinge", "squared", "logistic"])
-@pytest.mark.parametrize("name", list(CASES))
+@pytest.mark.parametrize("name,loss", [(n, l) for n in CASES for l in ("hinge", "squared", "logistic") if l == "hinge" or n not in LARGE])
 def test_sparse_blocks(oracle_mod, name, loss):
     import torch
     import paper_1909_04885_amd as binding
     from workloads.generate import Problem
     assert torch.cuda.is_available()
-    n, d, lengths, zipf, K, l1 = CASES[name]
+    n, d, lengths, zipf, K, l1, runs = CASES[name]
     g = np.random.default_rng(23)
     lens = np.asarray(lengths(g, n)).astype(np.int64)
-    if name != "nothing_shared":
+    if name not in ("nothing_shared", "unshared_row_by_row"):
         lens[3] = 0
-    cols = _rows(g, lens, d, zipf)
+    cols = _half_shared(g, n, d) if zipf is None else _rows(g, lens, d, zipf)
     rp = np.zeros(n + 1, dtype=np.int64)
     np.cumsum(lens, out=rp[1:])
     val = (g.standard_normal(int(rp[-1])) / np.sqrt(np.maximum(np.repeat(lens, lens), 1))).astype(np.float32)
@@ -59,5 +72,9 @@ def test_sparse_blocks(oracle_mod, name, loss):
         table = np.array([0, K - 1, 0], dtype=np.int32)
     p = Problem(name, loss, n, d, 0.01, y, bounds, row_ptr=rp, col=np.concatenate(cols).astype(np.int32), val=val)
     print("\ncase blocks %s %s n=%d d=%d entries=%d longest=%d" % (name, loss, n, d, rp[-1], lens.max()), flush=True)
-    run_lockstep({"seed": 3, "rounds": 3, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1, l1=l1,
+    chosen = binding.ChicleRound.from_problem(p, max_solvers=K)
+    chosen.assign(K, table)
+    assert chosen.debug_solver() == runs
+    chosen.close()
+    run_lockstep({"seed": 3, "rounds": 1 if name in LARGE else 3, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1, l1=l1,
                  ahead=loss == "squared", tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)
