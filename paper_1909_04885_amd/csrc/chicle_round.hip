@@ -171,7 +171,9 @@ struct chicle_ctx {
     int blocks_g = 1;                 // workgroups per solver
     bool blocks_double = true;        // its private vectors are kept in double
     int32_t *mpref_dev = nullptr;     // max_solvers x words: shared columns before each word
-    int32_t *mcount_dev = nullptr;    // shared columns per solver; one more word: segments taken
+    int32_t *mcount_dev = nullptr;    // shared columns per solver; segments taken; per solver: its segments, its longest row's
+    double *squares_dev = nullptr;    // per solver: sum over its rows of their segments squared
+    double crowding = -1.0;           // see column_crowding (< 0: not known yet)
     int64_t *place_off_dev = nullptr;
     float *coef_dev = nullptr;        // n_total
     unsigned long long *blocks_ring_dev = nullptr;
@@ -206,6 +208,7 @@ struct chicle_ctx {
     std::vector<int32_t> chunk_to_solver;
     std::vector<SolverDev> solvers;
     int max_list = 0;
+    int most_rows = 0;                // most rows a solver has
     int gap_lpr = 64, gap_items = 0, gap_hot_grid = 0;
 
     // read-out of large vectors: pinned pieces, one per copying thread (allocated by the first such read-out)
@@ -304,7 +307,7 @@ size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_sol
         const size_t words = ((size_t)d + 31) / 32;
         s += 2 * align_up(sizeof(int32_t) * words * (size_t)max_solvers);          // column bitmaps, prefix counts
         s += 2 * align_up(sizeof(int32_t) * words * (size_t)max_solvers);          // columns held by several rows, prefix counts
-        s += align_up(sizeof(int32_t) * ((size_t)max_solvers + 1)) + align_up(sizeof(int64_t) * (size_t)max_solvers);
+        s += align_up(sizeof(int32_t) * (3 * (size_t)max_solvers + 1)) + align_up(sizeof(int64_t) * (size_t)max_solvers) + align_up(sizeof(double) * (size_t)max_solvers);
         s += align_up(sizeof(float) * (size_t)n_total) + align_up(sizeof(unsigned long long) * (size_t)SB_RING_WORDS * (size_t)max_solvers);
         s += align_up(sizeof(int32_t) * (size_t)max_solvers) + align_up(sizeof(int64_t) * (size_t)max_solvers);
         s += align_up(sizeof(int32_t) * (size_t)n_chunks);
@@ -794,7 +797,7 @@ int renumber_columns(chicle_ctx *c)
 {
     int32_t *count = c->rank_of;   // the table is built in place of the counts
     HIP_TRY(c, hipMemsetAsync(count, 0, sizeof(int32_t) * (size_t)c->d, c->stream));
-    hipLaunchKernelGGL(count_columns, dim3(c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev, count);
+    hipLaunchKernelGGL(count_columns, dim3(1, c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev, count);
     HIP_TRY(c, hipGetLastError());
     std::vector<int32_t> cnt(c->d), order(c->d), rank(c->d);
     HIP_TRY(c, hipMemcpyAsync(cnt.data(), count, sizeof(int32_t) * (size_t)c->d, hipMemcpyDeviceToHost, c->stream));
@@ -814,9 +817,68 @@ int renumber_columns(chicle_ctx *c)
     return CHICLE_OK;
 }
 
+// For the average entry, the share of all rows that hold its column: 64 times this is how many of a block's rows an entry
+// meets in its column's list.  Of the data alone; formed when it is first asked for.
+int column_crowding(chicle_ctx *c, double *out)
+{
+    if (c->crowding < 0.0) {
+        int32_t *count = c->rank_of;       // (needed by no one after the columns are renumbered)
+        double *sum = c->gap_scratch.unused, s = 0.0;
+        HIP_TRY(c, hipMemsetAsync(count, 0, sizeof(int32_t) * (size_t)c->d, c->stream));
+        HIP_TRY(c, hipMemsetAsync(sum, 0, sizeof(double), c->stream));
+        hipLaunchKernelGGL(count_columns, dim3(std::max(1, 2048 / c->n_chunks), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev, count);
+        hipLaunchKernelGGL(sum_squares, dim3(grid_for(c->d, 256, 1024)), dim3(256), 0, c->stream, count, (int64_t)c->d, sum);
+        HIP_TRY(c, hipGetLastError());
+        HIP_TRY(c, hipMemcpyAsync(&s, sum, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        c->crowding = s / ((double)c->n_total * (double)std::max<int64_t>(c->entries_loaded, 1));
+    }
+    *out = c->crowding;
+    return CHICLE_OK;
+}
+
+// Microseconds a tile of so many shared entries takes where they are joined in parts (nothing worth counting where they
+// are joined at once, 26 to 51): its entries are read four times per part, and every entry walks its column's list.
+// Measured, entries and share of the rows that hold a column: 12 800 and 1/16: 174 us, 1/4: 254, 1: 1166; 64 000: 2071,
+// 3352, 9157; 256 000: 25 900, 36 600, 100 000.
+double tile_in_parts_us(double entries, double crowding)
+{
+    if (entries <= GB_ALL) return 0.0;
+    double parts = 1.0;
+    while (parts * GB_POST < entries) parts *= 2.0;
+    return 40.0 + (0.002 * parts + crowding * (0.075 + 0.9e-6 * entries)) * entries;
+}
+
+// Whether the block solver is the faster one for the entries laid out.  It is, unless tiles have to be joined in parts:
+// then their cost (spread over the chip, but no less than one of them) stands against the steps of the row-wise solver,
+// 1.7 us and more each, 2.4 and more on several workgroups per solver.  Both sides, 1024 rows that hold every column, four
+// solvers: 300 columns 1.69 ms in blocks and 0.62 row by row, 1000 columns 9.4 and 0.64; 5000, eight solvers, 139 and 0.42;
+// 256 rows of 200 out of 3200 columns, two solvers, 0.23 and 0.33.  A fifth is added for what the averages hide.
+bool blocks_pay(const chicle_ctx *c, const int32_t *segments, const int32_t *longest, const double *squares, int G, double crowding)
+{
+    double worst = 0.0, all = 0.0, chain = 0.0;
+    for (int k = 0; k < c->K; ++k) {
+        const double rows = c->solvers[k].n_rows, blocks = std::ceil(rows / BATCH);
+        if (rows == 0) continue;
+        const double per_row = segments[k] / rows, mean = SB_SEG * segments[k] / blocks;
+        // a tile's entries: spread of a sum of 64 rows, and the tile that holds the longest one
+        const double spread = blocks > 1 ? SB_SEG * std::sqrt(BATCH * std::max(0.0, squares[k] / rows - per_row * per_row)) : 0.0;
+        const double high = blocks > 1 ? mean + SB_SEG * (longest[k] - per_row) : mean;
+        const double in_parts = 0.5 * std::erfc((GB_ALL - mean) / (1.5 * spread + 1.0));
+        const double us = tile_in_parts_us(high, crowding);
+        worst = std::max(worst, us);
+        all += std::max(us, blocks * in_parts * tile_in_parts_us(std::max(mean, (double)GB_ALL) + spread, crowding));
+        chain = std::max(chain, blocks * (4.0 + 0.8e-3 * mean / G));
+    }
+    if (worst == 0.0) return true;
+    // (tiles on the whole chip at once take up to three times the time of a few: what they read again no longer fits the caches)
+    const double waves = std::ceil((double)c->K * G / c->cu_count);
+    return 1.2 * (std::max(worst, (c->n_tiles > c->cu_count ? 3.0 : 1.0) * all / c->cu_count) + chain * waves) <= c->most_rows * (c->cluster > 1 ? 2.4 : 1.7);
+}
+
 // The shared entries of the rows, for the solver that takes rows of any length in blocks: the fewest workgroups per solver
 // whose LDS holds every solver's shared columns (more than one of them must be resident together: they wait for each
-// other).  Where these or the room do not suffice the row-wise solver remains.
+// other).  Where these or the room do not suffice, or it would not be the faster one, the row-wise solver remains.
 int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared, const std::vector<int32_t> &columns)
 {
     const int K = (int)shared.size();
@@ -841,25 +903,37 @@ int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared, const std:
     c->refs_dev = (SegRef *)(c->layout_dev + tiles);
     c->place_dev = (int32_t *)(c->layout_dev + tiles + refs);
     c->segs_dev = (int32_t *)(c->layout_dev + tiles + refs + place);
-    int *taken = c->mcount_dev + c->max_solvers;
+    int *taken = c->mcount_dev + c->max_solvers, *total = taken + 1, *longest = total + c->max_solvers;
     HIP_TRY(c, hipMemcpyAsync(c->place_off_dev, off.data(), sizeof(int64_t) * (size_t)K, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipMemsetAsync(taken, 0, sizeof(int), c->stream));
+    HIP_TRY(c, hipMemsetAsync(c->squares_dev, 0, sizeof(double) * (size_t)K, c->stream));
+    HIP_TRY(c, hipMemsetAsync(taken, 0, sizeof(int) * (2 * (size_t)c->max_solvers + 1), c->stream));
     hipLaunchKernelGGL(shared_places, dim3(grid_for(c->words, 256, 1024), K), dim3(256), 0, c->stream, c->bits_dev, c->pref_dev,
                        c->multi_dev, c->mpref_dev, c->words, c->place_off_dev, c->place_dev);
     int max_rows = 1;
     for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
     hipLaunchKernelGGL(build_segments, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
-                       c->chunk_owner_dev, c->multi_dev, c->mpref_dev, c->words, G, c->n_total, c->refs_dev, c->segs_dev, taken, capacity);
+                       c->chunk_owner_dev, c->multi_dev, c->mpref_dev, c->words, G, c->n_total, c->refs_dev, c->segs_dev, taken, capacity, total, longest, c->squares_dev);
     HIP_TRY(c, hipGetLastError());
-    int n = 0;
-    HIP_TRY(c, hipMemcpyAsync(&n, taken, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    std::vector<int32_t> stat(2 * (size_t)c->max_solvers + 1);
+    std::vector<double> squares(K);
+    HIP_TRY(c, hipMemcpyAsync(squares.data(), c->squares_dev, sizeof(double) * (size_t)K, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(stat.data(), taken, sizeof(int) * stat.size(), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const int n = stat[0], *segments = &stat[1], *most_of = &stat[1 + (size_t)c->max_solvers];
+    if (n < 0 || n > capacity) return CHICLE_OK;
+    double crowding = 1.0;
+    if (!blocks_pay(c, segments, most_of, squares.data(), G, 0.0)) return CHICLE_OK;     // (not even with nothing shared twice)
+    if (!blocks_pay(c, segments, most_of, squares.data(), G, crowding)) {
+        const int rc = column_crowding(c, &crowding);
+        if (rc) return rc;
+        if (!blocks_pay(c, segments, most_of, squares.data(), G, crowding)) return CHICLE_OK;
+    }
     c->blocks_g = G;
-    c->blocks_ready = n >= 0 && n <= capacity;
+    c->blocks_ready = true;
     c->most_columns = *std::max_element(columns.begin(), columns.end());
     c->sources_dev = nullptr;
     const size_t used = tiles + refs + place + align_up((size_t)SB_SEG_WORDS * sizeof(int32_t) * (size_t)std::max(n, 1));
-    if (c->blocks_ready && used + sizeof(UniqueSource) * (size_t)c->u_used <= c->layout_bytes) {
+    if (used + sizeof(UniqueSource) * (size_t)c->u_used <= c->layout_bytes) {
         c->sources_dev = (UniqueSource *)(c->layout_dev + used);
         HIP_TRY(c, hipMemsetAsync(c->sources_dev, 0xff, sizeof(UniqueSource) * (size_t)c->u_used, c->stream));
         hipLaunchKernelGGL(unique_sources, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
@@ -961,8 +1035,9 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
         c->pref_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->words * (size_t)max_solvers);
         c->multi_dev = (unsigned *)carve(c, sizeof(unsigned) * (size_t)c->words * (size_t)max_solvers);
         c->mpref_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->words * (size_t)max_solvers);
-        c->mcount_dev = (int32_t *)carve(c, sizeof(int32_t) * ((size_t)max_solvers + 1));
+        c->mcount_dev = (int32_t *)carve(c, sizeof(int32_t) * (3 * (size_t)max_solvers + 1));
         c->place_off_dev = (int64_t *)carve(c, sizeof(int64_t) * (size_t)max_solvers);
+        c->squares_dev = (double *)carve(c, sizeof(double) * (size_t)max_solvers);
         c->coef_dev = (float *)carve(c, sizeof(float) * (size_t)n_total);
         c->blocks_ring_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * (size_t)SB_RING_WORDS * (size_t)max_solvers);
         c->count_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)max_solvers);
@@ -1245,10 +1320,13 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
     c->chunk_to_solver.assign(chunk_to_solver, chunk_to_solver + c->n_chunks);
     c->solvers = sol;
     c->max_list = max_list;
+    c->most_rows = 0;
+    for (const SolverDev &k : sol) c->most_rows = std::max(c->most_rows, k.n_rows);
     c->n_tiles = tile;
     c->gap_items = items[c->n_chunks];
     c->state = ST_READY;
-    c->cluster = 1;
+    // long rows: as many workgroups per solver as the chip has compute units for, each owning a range of columns
+    c->cluster = c->long_rows ? std::max(1, std::min(CLUSTER_MAX, c->cu_count / ((K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS))) : 1;
     c->blocks_ready = false;
     if (c->compact) {
         // Compact private vectors: which columns each solver's chunks contain, where each of them lives in
@@ -1301,9 +1379,6 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
         HIP_TRY(c, hipStreamSynchronize(c->stream));      // cnt, off and the caller's table go out of scope
     }
     if (c->long_rows) {
-        // as many workgroups per solver as the chip has compute units for, each owning a range of columns
-        const int k_pad = (K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
-        c->cluster = std::max(1, std::min(CLUSTER_MAX, c->cu_count / k_pad));
         if (c->cluster > 1 && c->split_built_for != c->cluster) {
             int max_rows = 1;
             for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);

@@ -11,11 +11,21 @@
 
 namespace chicle {
 
-// count[col] += 1 for every stored entry.  One workgroup per chunk.
+// count[col] += 1 for every stored entry.  Grid: (blocks over entries, chunk).
 __global__ __launch_bounds__(256) void count_columns(const ChunkDev *__restrict__ chunks, int *count)
 {
-    const ChunkDev &ch = chunks[blockIdx.x];
-    for (int64_t p = threadIdx.x; p < ch.nnz; p += 256) atomicAdd(&count[ch.col[p]], 1);
+    const ChunkDev &ch = chunks[blockIdx.y];
+    for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < ch.nnz; p += (int64_t)gridDim.x * 256) atomicAdd(&count[ch.col[p]], 1);
+}
+
+// *out += sum of count[0 .. n)^2.
+__global__ __launch_bounds__(256) void sum_squares(const int *__restrict__ count, int64_t n, double *out)
+{
+    double s = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) s += (double)count[i] * (double)count[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) atomicAdd(out, s);
 }
 
 // col <- rank_of[col] and insertion sort of each row by the new ids (values move with their ids).

@@ -65,17 +65,20 @@ __global__ __launch_bounds__(256) void shared_places(const unsigned *__restrict_
 }
 
 // The shared entries of every row, by member, in segments.  One wavefront per row, 4 rows per workgroup; segments are
-// taken from *next, one addition per workgroup.  Grid: (blocks over rows, chunk).
+// taken from *next, one addition per workgroup.  total[k], longest[k], squares[k]: the segments of solver k's rows, of the
+// one with the most, and the sum of their squares.  Grid: (blocks over rows, chunk).
 __global__ __launch_bounds__(256) void build_segments(const ChunkDev *__restrict__ chunks, const int32_t *__restrict__ owner,
                                                       const unsigned *__restrict__ multi, const int32_t *__restrict__ mpref,
                                                       int64_t words, int G, int64_t n_total, SegRef *refs, int32_t *segs,
-                                                      int *next, int capacity)
+                                                      int *next, int capacity, int *total, int *longest, double *squares)
 {
     __shared__ int cnt[4][SB_MAX_G], first[4][SB_MAX_G];
     const ChunkDev &ch = chunks[blockIdx.y];
     const int32_t *cid = chunk_compact_ids(ch);
     const int64_t base = (int64_t)owner[blockIdx.y] * words;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int all = 0, most = 0;                       // thread 0
+    double sq = 0.0;
     for (int r0 = blockIdx.x * 4; r0 < ch.n_rows; r0 += gridDim.x * 4) {
         const int r = r0 + wv;
         const int b = r < ch.n_rows ? ch.row_ptr[r] : 0, e = r < ch.n_rows ? ch.row_ptr[r + 1] : 0;
@@ -96,8 +99,13 @@ __global__ __launch_bounds__(256) void build_segments(const ChunkDev *__restrict
         __syncthreads();
         if (threadIdx.x == 0) {
             int sum = 0;
-            for (int w = 0; w < 4; ++w)
+            for (int w = 0; w < 4; ++w) {
+                const int before = sum;
                 for (int g = 0; g < G; ++g) { first[w][g] = sum; sum += cnt[w][g]; }
+                most = max(most, sum - before);
+                sq += (double)(sum - before) * (double)(sum - before);
+            }
+            all += sum;
             const int at = sum ? atomicAdd(next, sum) : 0;
             for (int w = 0; w < 4; ++w)
                 for (int g = 0; g < G; ++g) first[w][g] += at;
@@ -140,6 +148,11 @@ __global__ __launch_bounds__(256) void build_segments(const ChunkDev *__restrict
             }
         }
         __syncthreads();
+    }
+    if (threadIdx.x == 0 && all > 0) {
+        atomicAdd(total + owner[blockIdx.y], all);
+        atomicMax(longest + owner[blockIdx.y], most);
+        atomicAdd(squares + owner[blockIdx.y], sq);
     }
 }
 
