@@ -417,13 +417,29 @@ BatchedLayout batched_layout(const chicle_ctx *c)
 constexpr int DENSE_NAMED_MAX_D = 320;
 bool dense_eligible(const chicle_ctx *c, int32_t max_d) { return c->dense && c->d <= max_d; }
 
+// Solvers of so few rows step through them one at a time faster than the tile kernel and the block kernel get under way.
+// Dense rows, 4 to 256 solvers of 8 rows each, one row at a time / in blocks: 100 columns 22 / 24 us, 400 columns 29 / 32,
+// 1000 columns 44 / 43; of 4 rows 17 / 24, 22 / 32, 32 / 43.  Block kernels take a compute unit each, so beyond 256 solvers
+// they queue up: 1024 solvers of 16 rows of 400 columns 78 / 90.  Sparse rows of 60 entries the same (8 rows 29 / 31, 1024
+// solvers of 16 rows 50 / 80); where several workgroups share a solver a row takes longer (4 rows of 300 entries 30 / 31, 8
+// rows 39 / 32).
+bool few_rows(const chicle_ctx *c)
+{
+    const int waves = (c->K + c->cu_count - 1) / c->cu_count;
+    return c->most_rows <= (c->long_rows && c->cluster > 1 ? 4 : std::max(8, 4 * waves));
+}
+
 // The solver of the next pass.
 enum Route { ROUTE_ROWWISE = 0, ROUTE_BATCHED = 1, ROUTE_DENSE = 2, ROUTE_BLOCKS = 3 };
 Route route_of(const chicle_ctx *c)
 {
     const bool by_name = c->solver_kind == CHICLE_SOLVER_BATCHED;
     if (!by_name && c->solver_kind != CHICLE_SOLVER_AUTO) return ROUTE_ROWWISE;
-    if (c->dense) return dense_eligible(c, by_name ? DENSE_NAMED_MAX_D : DENSE_MAX_D) ? ROUTE_DENSE : ROUTE_ROWWISE;
+    if (c->dense) {
+        if (by_name) return dense_eligible(c, DENSE_NAMED_MAX_D) ? ROUTE_DENSE : ROUTE_ROWWISE;
+        // (rows of up to 48 columns stay with the solver that sums the private vector in double)
+        return dense_eligible(c, DENSE_MAX_D) && (c->d <= GRAM_MAX_ROW || !few_rows(c)) ? ROUTE_DENSE : ROUTE_ROWWISE;
+    }
     if (batched_eligible(c)) return ROUTE_BATCHED;
     return !by_name && c->blocks_ready ? ROUTE_BLOCKS : ROUTE_ROWWISE;
 }
@@ -881,6 +897,7 @@ bool blocks_pay(const chicle_ctx *c, const int32_t *segments, const int32_t *lon
 // other).  Where these or the room do not suffice, or it would not be the faster one, the row-wise solver remains.
 int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared, const std::vector<int32_t> &columns)
 {
+    if (few_rows(c)) return CHICLE_OK;
     const int K = (int)shared.size();
     const int k_pad = (K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
     const int64_t most = *std::max_element(shared.begin(), shared.end());

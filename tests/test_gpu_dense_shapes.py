@@ -32,3 +32,32 @@ def test_dense_widths(oracle_mod, loss, d, n):
     rounds = 2 if d <= 3 else 3
     run_lockstep({"seed": 3, "rounds": rounds, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1,
                  ahead=d % 2 == 0, tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)
+
+
+@pytest.mark.parametrize("d,rows,K,runs", [(48, 1, 4, "dense"), (49, 8, 4, "rowwise"), (49, 9, 4, "dense"), (400, 8, 4, "rowwise"),
+                                           (400, 9, 4, "dense"), (1536, 8, 4, "rowwise"), (1536, 9, 4, "dense"), (1537, 9, 4, "rowwise"),
+                                           (100, 8, 512, "rowwise"), (100, 9, 512, "dense"), (100, 16, 1024, "rowwise"), (100, 17, 1024, "dense")])
+def test_solvers_of_few_dense_rows_go_row_by_row(oracle_mod, d, rows, K, runs):
+    import torch
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    assert torch.cuda.is_available()
+    print("\ncase dense choice d=%d rows=%d K=%d" % (d, rows, K), flush=True)
+    g = np.random.default_rng(d)
+    n = K * rows
+    X = (g.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    y = np.where(g.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    p = Problem("choice", "hinge", n, d, 0.5 / n, y, np.arange(0, n + 1, rows, dtype=np.int64), X=X)
+    table = np.arange(K, dtype=np.int32)
+    c = binding.ChicleRound.from_problem(p, max_solvers=K)
+    c.assign(K, table)
+    assert c.debug_solver()[0] == runs
+    c.set_solver("rowwise")
+    assert c.debug_solver()[0] == "rowwise"
+    if d <= 320:
+        c.set_solver("batched")
+        assert c.debug_solver()[0] == "dense"
+    c.close()
+    if K <= 4:
+        run_lockstep({"seed": 3, "rounds": 2, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1, ahead=True,
+                     tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)

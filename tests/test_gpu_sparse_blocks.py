@@ -37,7 +37,12 @@ CASES = {
     "joined_in_many_parts": (20000, 2500, lambda g, n: g.integers(700, 900, n), False, 1, 0.0, G1),
     "parts_made_finer": (12000, 360, lambda g, n: np.full(n, 360), False, 2, 0.0, G1),
     "too_long_for_parts": (150, 2500, lambda g, n: g.integers(1000, 2500, n), False, 2, 0.0, ("rowwise", 4, False, False)),
-    "nothing_shared": (5, 100000, lambda g, n: np.full(n, 60), False, 5, 0.0, G1),
+    "nothing_shared": (45, 100000, lambda g, n: np.full(n, 60), False, 5, 0.0, G1),
+    # nine rows per solver, eight, and five and four where several workgroups share a solver
+    "rows_enough": (45, 300, lambda g, n: np.full(n, 60), False, 5, 0.0, G1),
+    "few_rows": (40, 300, lambda g, n: np.full(n, 60), False, 5, 0.0, ("rowwise", 1, False, False)),
+    "long_rows_enough": (25, 900, lambda g, n: np.full(n, 200), False, 5, 0.0, G1),
+    "few_long_rows": (20, 900, lambda g, n: np.full(n, 200), False, 5, 0.0, ("rowwise", 4, False, False)),
     "unshared_row_by_row": (3000, 148000, lambda g, n: np.full(n, 96), None, 2, 0.0, ("blocks", 1, False, True)),
     "two_members": (1600, 30000, lambda g, n: g.integers(60, 150, n), False, 2, 0.0, G2),
     "four_members": (3600, 60000, lambda g, n: g.integers(60, 150, n), False, 2, 0.0, G4),
@@ -60,16 +65,19 @@ def test_sparse_blocks(oracle_mod, name, loss):
     n, d, lengths, zipf, K, l1, runs = CASES[name]
     g = np.random.default_rng(23)
     lens = np.asarray(lengths(g, n)).astype(np.int64)
-    if name not in ("nothing_shared", "unshared_row_by_row"):
+    small = n <= 45
+    if not small and name != "unshared_row_by_row":
         lens[3] = 0
     cols = _half_shared(g, n, d) if zipf is None else _rows(g, lens, d, zipf)
+    if name == "nothing_shared":
+        cols = [np.arange(60) * 1000 + i for i in range(n)]
     rp = np.zeros(n + 1, dtype=np.int64)
     np.cumsum(lens, out=rp[1:])
     val = (g.standard_normal(int(rp[-1])) / np.sqrt(np.maximum(np.repeat(lens, lens), 1))).astype(np.float32)
     y = g.standard_normal(n).astype(np.float32) if loss == "squared" else np.where(g.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
-    if name == "nothing_shared":
-        bounds = np.arange(n + 1, dtype=np.int64)                  # a row per solver
-        table = np.arange(n, dtype=np.int32)
+    if small:
+        bounds = np.arange(n + 1, dtype=np.int64)                  # as many rows for every solver
+        table = (np.arange(n) % K).astype(np.int32)
     else:
         bounds = np.array([0, 1, n // 2 + 3, n], dtype=np.int64)   # solver 0: one row and the second half
         table = np.array([0, K - 1, 0], dtype=np.int32)
@@ -86,7 +94,7 @@ def test_sparse_blocks(oracle_mod, name, loss):
 @pytest.mark.parametrize("n,d,m,K,runs", [
     (1024, 180, 180, 4, "blocks"), (1024, 300, 300, 4, "rowwise"), (1024, 1000, 1000, 4, "rowwise"), (1024, 5000, 5000, 8, "rowwise"),
     (512, 20000, 20000, 4, "rowwise"), (1024, 30000, 5000, 4, "rowwise"), (4096, 3000, 3000, 64, "rowwise"),
-    (40, 400, 400, 4, "blocks"), (40, 2000, 2000, 4, "rowwise"),
+    (40, 400, 400, 4, "blocks"), (40, 2000, 2000, 4, "rowwise"), (16, 400, 400, 4, "rowwise"),
     # many rows per solver: tiles in parts on the whole chip against the row-wise solver's long chain
     (30000, 4000, 250, 2, "blocks"), (30000, 250, 250, 2, "blocks"), (30000, 250, 250, 64, "rowwise"),
     # one long row among short ones
