@@ -456,15 +456,16 @@ int split_tails(const chicle_ctx *c)
            (n_tails == 0 || sizeof(double) * (size_t)n_hot >= 2 * RING * BATCH * sizeof(RowSlot)) ? n_tails : -1;   // a tail keeps its rows there
 }
 
-// LDS a dense solver asks for at least: so much that no workgroup of the next pass's tile kernel, which runs beside it, is
-// placed on its compute unit.
+// LDS a dense solver asks for at least where it is to have a compute unit to itself: no other solver, and no workgroup of the
+// next pass's tile kernel, which runs beside it, is placed there.  Where there are more solvers than compute units and no
+// tiles ahead, solvers share them (512 solvers of 64 rows of 64 columns: 32 us alone, 28 sharing; 1024 of 20 rows 47 and 39).
 constexpr int DENSE_ALONE_LDS = 130 * 1024;
 
 template <int LOSS, typename SH>
-int launch_dense_shape(chicle_ctx *c)
+int launch_dense_shape(chicle_ctx *c, bool alone)
 {
     auto kern = sdca_dense<LOSS, SH>;
-    const size_t sh = std::max<size_t>(SH::LDS_BYTES, DENSE_ALONE_LDS);
+    const size_t sh = std::max<size_t>(SH::LDS_BYTES, alone ? DENSE_ALONE_LDS : 0);
     HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
     hipLaunchKernelGGL(kern, dim3(c->K), dim3(SH::THREADS), sh, c->stream, c->chunks_dev, c->solvers_dev,
                        (const float *)c->tiles[c->tile_buf], c->u, c->ld_v, (int)c->d, dense_ld((int)c->d), scalars(c));
@@ -474,26 +475,27 @@ int launch_dense_shape(chicle_ctx *c)
 
 // The narrowest shape that holds a row: lanes per row, wavefronts, 4-column groups per lane, rows per block.
 template <int LOSS>
-int launch_dense(chicle_ctx *c)
+int launch_dense(chicle_ctx *c, bool alone)
 {
     const int d = (int)c->d;
     if (LOSS == 1 && d <= 64) {
+        const int sh = alone ? DENSE_ALONE_LDS : 0;
         auto kern = d <= 32 ? sdca_dense_squared<DenseShape<8, 4, 1, 64>> : sdca_dense_squared<DenseShape<16, 4, 1, 64>>;
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DENSE_ALONE_LDS));
-        hipLaunchKernelGGL(kern, dim3(c->K), dim3(256), DENSE_ALONE_LDS, c->stream, c->chunks_dev, c->solvers_dev,
+        hipLaunchKernelGGL(kern, dim3(c->K), dim3(256), sh, c->stream, c->chunks_dev, c->solvers_dev,
                            (const float *)c->tiles[c->tile_buf], c->u, c->ld_v, d, dense_ld(d), scalars(c));
         HIP_TRY(c, hipGetLastError());
         return CHICLE_OK;
     }
-    if (d <= 32) return launch_dense_shape<LOSS, DenseShape<8, 4, 1, 64>>(c);
-    if (d <= 64) return launch_dense_shape<LOSS, DenseShape<16, 4, 1, 64>>(c);
-    if (d <= 128) return launch_dense_shape<LOSS, DenseShape<32, 8, 1, 64>>(c);
-    if (d <= 256) return launch_dense_shape<LOSS, DenseShape<64, 8, 1, 64>>(c);
-    if (d <= 512) return launch_dense_shape<LOSS, DenseShape<64, 8, 2, 64>>(c);
-    if (d <= 768) return launch_dense_shape<LOSS, DenseShape<64, 8, 3, 32>>(c);
-    if (d <= 1024) return launch_dense_shape<LOSS, DenseShape<64, 8, 4, 32>>(c);
-    if (d <= 1280) return launch_dense_shape<LOSS, DenseShape<64, 8, 5, 16>>(c);
-    return launch_dense_shape<LOSS, DenseShape<64, 8, 6, 16>>(c);
+    if (d <= 32) return launch_dense_shape<LOSS, DenseShape<8, 4, 1, 64>>(c, alone);
+    if (d <= 64) return launch_dense_shape<LOSS, DenseShape<16, 4, 1, 64>>(c, alone);
+    if (d <= 128) return launch_dense_shape<LOSS, DenseShape<32, 8, 1, 64>>(c, alone);
+    if (d <= 256) return launch_dense_shape<LOSS, DenseShape<64, 8, 1, 64>>(c, alone);
+    if (d <= 512) return launch_dense_shape<LOSS, DenseShape<64, 8, 2, 64>>(c, alone);
+    if (d <= 768) return launch_dense_shape<LOSS, DenseShape<64, 8, 3, 32>>(c, alone);
+    if (d <= 1024) return launch_dense_shape<LOSS, DenseShape<64, 8, 4, 32>>(c, alone);
+    if (d <= 1280) return launch_dense_shape<LOSS, DenseShape<64, 8, 5, 16>>(c, alone);
+    return launch_dense_shape<LOSS, DenseShape<64, 8, 6, 16>>(c, alone);
 }
 
 template <int LOSS>
@@ -588,7 +590,7 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
     const int n_tails = split_tails(c);
     if (c->dense) {
         seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
-        rc = launch_dense<LOSS>(c);
+        rc = launch_dense<LOSS>(c, perm_next != nullptr || c->K <= c->cu_count);
         seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
         if (rc) return rc;
     } else if (n_tails >= 0) {
