@@ -133,6 +133,7 @@ struct chicle_ctx {
     int32_t max_row_len = 0;
     float *tiles[2] = {nullptr, nullptr};   // Gram tiles: one set in use by the chain, one being prepared
     int tile_buf = 0;                       // set the next chain kernel reads
+    bool tiles_solved[2] = {false, false};  // dense rows, squared loss: the set holds the recurrence solved
     hipStream_t side = nullptr;             // stream of Gram kernels prepared ahead
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     // Visiting orders announced for the next pass are copied here when they are announced (two buffers: the
@@ -456,6 +457,18 @@ int split_tails(const chicle_ctx *c)
            (n_tails == 0 || sizeof(double) * (size_t)n_hot >= 2 * RING * BATCH * sizeof(RowSlot)) ? n_tails : -1;   // a tail keeps its rows there
 }
 
+// Squared loss, dense rows: whether tiles are formed with the recurrence solved (gram_dense).  The inverse costs a tile 12 us
+// more in latency and the chip 0.010 us per tile, and saves a solver 0.34 us per block.  One solver in 4 of 64 rows of 64
+// columns: 36 us solved, 24 not; of 8192 rows 180 and 201; one in 64 of 8192 rows of 28 columns 307 and 269.  Tiles formed a
+// pass ahead cost nothing while they hide behind the steps: one in 4 of 2048 rows of 28 columns 62 and 77, one in 64 96 and
+// 97, of 8192 rows 252 and 264, one in 300 977 and 713.
+bool solve_tiles(const chicle_ctx *c, bool ahead)
+{
+    if (c->loss != CHICLE_LOSS_SQUARED) return false;
+    const int blocks = (c->most_rows + BATCH - 1) / BATCH;
+    return ahead ? c->K <= 64 && blocks >= 16 + c->K : (int64_t)blocks * (34 - c->K) > 1200;
+}
+
 // LDS a dense solver asks for at least where it is to have a compute unit to itself: no other solver, and no workgroup of the
 // next pass's tile kernel, which runs beside it, is placed there.  Where there are more solvers than compute units and no
 // tiles ahead, solvers share them (512 solvers of 64 rows of 64 columns: 32 us alone, 28 sharing; 1024 of 20 rows 47 and 39).
@@ -464,7 +477,7 @@ constexpr int DENSE_ALONE_LDS = 130 * 1024;
 template <int LOSS, typename SH>
 int launch_dense_shape(chicle_ctx *c, bool alone)
 {
-    auto kern = sdca_dense<LOSS, SH>;
+    auto kern = LOSS == 1 && c->tiles_solved[c->tile_buf] ? sdca_dense<LOSS, true, SH> : sdca_dense<LOSS, false, SH>;
     const size_t sh = std::max<size_t>(SH::LDS_BYTES, alone ? DENSE_ALONE_LDS : 0);
     HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
     hipLaunchKernelGGL(kern, dim3(c->K), dim3(SH::THREADS), sh, c->stream, c->chunks_dev, c->solvers_dev,
@@ -478,7 +491,7 @@ template <int LOSS>
 int launch_dense(chicle_ctx *c, bool alone)
 {
     const int d = (int)c->d;
-    if (LOSS == 1 && d <= 64) {
+    if (LOSS == 1 && d <= 64 && c->tiles_solved[c->tile_buf]) {
         const int sh = alone ? DENSE_ALONE_LDS : 0;
         auto kern = d <= 32 ? sdca_dense_squared<DenseShape<8, 4, 1, 64>> : sdca_dense_squared<DenseShape<16, 4, 1, 64>>;
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DENSE_ALONE_LDS));
@@ -539,16 +552,17 @@ int launch_rowwise(chicle_ctx *c, const int32_t *perm)
     return CHICLE_OK;
 }
 
-// Gram tiles of the given visiting orders into tile set `buf`, on `stream`.
+// Gram tiles of the given visiting orders into tile set `buf`, on `stream` (ahead: beside the pass before theirs).
 template <int LOSS>
-int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, hipStream_t stream)
+int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, bool ahead, hipStream_t stream)
 {
     const RoundScalars sc = scalars(c);
     if (c->dense) {
+        c->tiles_solved[buf] = solve_tiles(c, ahead);
         if (c->n_tiles > 0)
             hipLaunchKernelGGL(gram_dense<LOSS>, dim3(c->n_tiles), dim3(GD_THREADS), 0, stream, c->chunks_dev, c->solvers_dev,
                                c->row_chunk_dev, c->chunk_first_dev, perm, c->tile_solver_dev, c->tiles[buf],
-                               dense_ld((int)c->d), sc.c, c->err_dev);
+                               dense_ld((int)c->d), sc.c, c->tiles_solved[buf], c->err_dev);
     } else if (c->n_tiles > 0) {
         auto kern = gram_tiles_join<LOSS>;
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -576,7 +590,7 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
         c->tile_buf = 1 - c->tile_buf;
     } else {
         seg_begin(c, CHICLE_SEG_EPOCH_GRAM);
-        rc = launch_gram<LOSS>(c, perm, c->tile_buf, c->stream);
+        rc = launch_gram<LOSS>(c, perm, c->tile_buf, false, c->stream);
         seg_end(c, CHICLE_SEG_EPOCH_GRAM);
         if (rc) return rc;
     }
@@ -623,7 +637,7 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
         // the other tile set was last read by the previous pass's chain kernel, which precedes ev_fork
         HIP_TRY(c, hipStreamWaitEvent(c->side, c->ev_fork, 0));
         if (c->profiling) (void)hipEventRecord(c->seg[CHICLE_SEG_EPOCH_GRAM].start, c->side);
-        rc = launch_gram<LOSS>(c, perm_next, 1 - c->tile_buf, c->side);
+        rc = launch_gram<LOSS>(c, perm_next, 1 - c->tile_buf, true, c->side);
         if (c->profiling) {
             (void)hipEventRecord(c->seg[CHICLE_SEG_EPOCH_GRAM].stop, c->side);
             c->seg[CHICLE_SEG_EPOCH_GRAM].recorded = true;
@@ -1875,9 +1889,9 @@ int chicle_debug_gram(chicle_ctx *c, const int32_t *perm_device, float *tiles_ou
     if (n_tiles_out) *n_tiles_out = c->n_tiles;
     int rc = drop_ahead(c);
     if (rc) return rc;
-    rc = c->loss == CHICLE_LOSS_HINGE ? launch_gram<0>(c, perm_device, c->tile_buf, c->stream)
-         : c->loss == CHICLE_LOSS_SQUARED ? launch_gram<1>(c, perm_device, c->tile_buf, c->stream)
-                                          : launch_gram<2>(c, perm_device, c->tile_buf, c->stream);
+    rc = c->loss == CHICLE_LOSS_HINGE ? launch_gram<0>(c, perm_device, c->tile_buf, false, c->stream)
+         : c->loss == CHICLE_LOSS_SQUARED ? launch_gram<1>(c, perm_device, c->tile_buf, false, c->stream)
+                                          : launch_gram<2>(c, perm_device, c->tile_buf, false, c->stream);
     if (rc) return rc;
     if (tiles_out) {
         const int64_t want = (int64_t)c->n_tiles * TILE_FLOATS;

@@ -52,7 +52,7 @@ template <int LOSS>
 __global__ __launch_bounds__(GD_THREADS) void gram_dense(
     const ChunkDev *__restrict__ chunks, const SolverDev *__restrict__ solvers, const int32_t *__restrict__ row_chunk,
     const int32_t *__restrict__ chunk_first, const int32_t *__restrict__ perm, const int32_t *__restrict__ tile_solver,
-    float *tiles, int ld, float c, int *err)
+    float *tiles, int ld, float c, bool solve, int *err)
 {
     __shared__ __align__(16) float X[BATCH * GD_LD];
     __shared__ float G[BATCH * (BATCH + 1)];
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(GD_THREADS) void gram_dense(
     }
     const int i = lane;
     const float si = r_scale[i] * r_sgn[i];
-    if (LOSS != 1) {
+    if (LOSS != 1 || !solve) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int jq = wv + 4 * k;
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(GD_THREADS) void gram_dense(
         }
         return;
     }
-    // Squared loss: the steps are not clamped, the recurrence delta_i = t_i + sum_{j < i} T_ji delta_j is a unit
+    // Squared loss (where it pays, see solve_tiles): the steps are not clamped, the recurrence delta_i = t_i + sum_{j < i} T_ji delta_j is a unit
     // triangular system and the tile holds its inverse, delta = N t: lane j follows the influence of t_j down the rows.
     // T goes to LDS by rows i (X is free), then one wavefront substitutes forward, 2016 multiply-adds.  (Shorter blocks
     // take diagonal blocks of the tile: N's are the inverses of T's.)
@@ -279,7 +279,8 @@ __device__ __forceinline__ float dense_recurrence(const float *T_lds, float t, f
     return clamp_step<LOSS>(t, lo, hi);
 }
 
-template <int LOSS, typename SH>
+// SOLVED: see dense_recurrence.
+template <int LOSS, bool SOLVED, typename SH>
 __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
     const ChunkDev *__restrict__ chunks, const SolverDev *__restrict__ solvers, const float *__restrict__ tiles, float *u_all,
     int64_t ld_v, int d, int ld, RoundScalars sc)
@@ -426,7 +427,7 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
                     root = logistic_root(t, hi, a);
                 }
             }
-            const float dl = dense_recurrence<LOSS, BR, true>(T, t, lo, hi, a, root, lane);
+            const float dl = dense_recurrence<LOSS, BR, SOLVED>(T, t, lo, hi, a, root, lane);
             if (lane < BR) {
                 if (st_cur != nullptr) {
                     float an = a + dl;

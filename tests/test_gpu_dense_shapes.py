@@ -61,3 +61,23 @@ def test_solvers_of_few_dense_rows_go_row_by_row(oracle_mod, d, rows, K, runs):
     if K <= 4:
         run_lockstep({"seed": 3, "rounds": 2, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1, ahead=True,
                      tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)
+
+
+@pytest.mark.parametrize("ahead,n", [(False, 2500), (True, 1250)])
+@pytest.mark.parametrize("d", [1, 28, 32, 33, 64, 65, 200, 511, 700, 1001, 1200, 1500])
+def test_squared_loss_with_solved_tiles(oracle_mod, d, ahead, n):
+    """Long passes of one solver, ragged last block: tiles hold the squared loss's recurrence solved, in the first pass
+    (2500 rows, orders not announced) or from the second on (1250 rows, announced)."""
+    import torch
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    assert torch.cuda.is_available()
+    print("\ncase solved tiles n=%d d=%d ahead=%s" % (n, d, ahead), flush=True)
+    g = np.random.default_rng(d)
+    X = g.standard_normal((n, d)).astype(np.float32)
+    X[n // 3] = 0
+    y = (X @ g.standard_normal(d) / np.sqrt(d) + 0.1 * g.standard_normal(n)).astype(np.float32)
+    p = Problem("solved", "squared", n, d, 0.02, y, np.array([0, 1001, n], dtype=np.int64), X=X)
+    table = np.zeros(2, dtype=np.int32)
+    run_lockstep({"seed": 5, "rounds": 3, "schedule": [(0, 1)], "K": 1}, p, oracle_mod, binding, check_alpha_every=1, ahead=ahead,
+                 tables=lambda r, Kp, tp: (1, table, table.copy()) if r == 0 else None, max_solvers=1)
