@@ -419,15 +419,16 @@ constexpr int DENSE_NAMED_MAX_D = 320;
 bool dense_eligible(const chicle_ctx *c, int32_t max_d) { return c->dense && c->d <= max_d; }
 
 // Solvers of so few rows step through them one at a time faster than the tile kernel and the block kernel get under way.
-// Dense rows, 4 to 256 solvers of 8 rows each, one row at a time / in blocks: 100 columns 22 / 24 us, 400 columns 29 / 32,
-// 1000 columns 44 / 43; of 4 rows 17 / 24, 22 / 32, 32 / 43.  Block kernels take a compute unit each, so beyond 256 solvers
-// they queue up: 1024 solvers of 16 rows of 400 columns 78 / 90.  Sparse rows of 60 entries the same (8 rows 29 / 31, 1024
-// solvers of 16 rows 50 / 80); where several workgroups share a solver a row takes longer (4 rows of 300 entries 30 / 31, 8
-// rows 39 / 32).
+// Whole rounds, row by row / in blocks.  Dense rows, four solvers of 4 rows: 64 columns 26 / 33 us, 1000 columns 42 / 56; of
+// 8 rows 1000 columns equal; logistic loss of 12 rows 39 / 44 and 69 / 66.  Sparse rows, 64 solvers: of 12 rows of 40 or 80
+// entries 56 / 63 and 59 / 67, of 16 equal; of 8 rows of 120 (several workgroups share a solver, and a row takes longer)
+// 59 / 66, of 12 equal.  Block kernels take a compute unit each, so more solvers than compute units queue up: 512 solvers of
+// 10 rows of 400 columns 162 / 176, of 12 rows of 80 entries 84 / 92.
 bool few_rows(const chicle_ctx *c)
 {
     const int waves = (c->K + c->cu_count - 1) / c->cu_count;
-    return c->most_rows <= (c->long_rows && c->cluster > 1 ? 4 : std::max(8, 4 * waves));
+    if (c->dense) return c->most_rows <= std::max(c->loss == CHICLE_LOSS_LOGISTIC ? 12 : 8, 5 * waves);
+    return c->most_rows <= (c->long_rows ? std::max(8, 4 * waves) : std::max(12, 6 * waves));
 }
 
 // The solver of the next pass.
@@ -468,6 +469,12 @@ bool solve_tiles(const chicle_ctx *c, bool ahead)
     const int blocks = (c->most_rows + BATCH - 1) / BATCH;
     return ahead ? c->K <= 64 && blocks >= 16 + c->K : (int64_t)blocks * (34 - c->K) > 1200;
 }
+
+// Whether the tiles of announced orders are formed ahead for dense rows.  The second stream costs a round about 20 us of
+// calls, which hide only behind a pass that is long enough: rounds of four solvers of 64 rows of 64 columns 33 us without, 56
+// with; of 1024 rows 56 and 59, of 256 columns 68 and 64, of 1000 columns 129 and 111; 64 solvers of 512 rows of 64 columns
+// 65 and 69, of 1024 rows 89 and 78.
+bool dense_tiles_ahead(const chicle_ctx *c) { return c->most_rows / BATCH + c->d / 64 >= 16 || c->n_tiles >= 1024; }
 
 // LDS a dense solver asks for at least where it is to have a compute unit to itself: no other solver, and no workgroup of the
 // next pass's tile kernel, which runs beside it, is placed there.  Where there are more solvers than compute units and no
@@ -1507,6 +1514,7 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
         c->ahead_buf = 1 - c->ahead_buf;
         c->ahead_valid = true;
     }
+    if (route == ROUTE_DENSE && !dense_tiles_ahead(c)) perm_next_device = nullptr;      // (they are kept all the same)
     seg_begin(c, CHICLE_SEG_LOCAL_EPOCH);
     int rc = CHICLE_OK;
     if (!c->zw_valid) rc = run_row_pass(c, nullptr, c->gap_scratch);     // x_i . w for the current w

@@ -36,7 +36,7 @@ def test_dense_widths(oracle_mod, loss, d, n):
 
 @pytest.mark.parametrize("d,rows,K,runs", [(48, 1, 4, "dense"), (49, 8, 4, "rowwise"), (49, 9, 4, "dense"), (400, 8, 4, "rowwise"),
                                            (400, 9, 4, "dense"), (1536, 8, 4, "rowwise"), (1536, 9, 4, "dense"), (1537, 9, 4, "rowwise"),
-                                           (100, 8, 512, "rowwise"), (100, 9, 512, "dense"), (100, 16, 1024, "rowwise"), (100, 17, 1024, "dense")])
+                                           (100, 10, 512, "rowwise"), (100, 11, 512, "dense"), (100, 20, 1024, "rowwise"), (100, 21, 1024, "dense")])
 def test_solvers_of_few_dense_rows_go_row_by_row(oracle_mod, d, rows, K, runs):
     import torch
     import paper_1909_04885_amd as binding

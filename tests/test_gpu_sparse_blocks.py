@@ -37,12 +37,12 @@ CASES = {
     "joined_in_many_parts": (20000, 2500, lambda g, n: g.integers(700, 900, n), False, 1, 0.0, G1),
     "parts_made_finer": (12000, 360, lambda g, n: np.full(n, 360), False, 2, 0.0, G1),
     "too_long_for_parts": (150, 2500, lambda g, n: g.integers(1000, 2500, n), False, 2, 0.0, ("rowwise", 4, False, False)),
-    "nothing_shared": (45, 100000, lambda g, n: np.full(n, 60), False, 5, 0.0, G1),
-    # nine rows per solver, eight, and five and four where several workgroups share a solver
-    "rows_enough": (45, 300, lambda g, n: np.full(n, 60), False, 5, 0.0, G1),
-    "few_rows": (40, 300, lambda g, n: np.full(n, 60), False, 5, 0.0, ("rowwise", 1, False, False)),
-    "long_rows_enough": (25, 900, lambda g, n: np.full(n, 200), False, 5, 0.0, G1),
-    "few_long_rows": (20, 900, lambda g, n: np.full(n, 200), False, 5, 0.0, ("rowwise", 4, False, False)),
+    "nothing_shared": (65, 100000, lambda g, n: np.full(n, 60), False, 5, 0.0, G1),
+    # thirteen rows per solver, twelve, and nine and eight of long rows
+    "rows_enough": (65, 300, lambda g, n: np.full(n, 60), False, 5, 0.0, G1),
+    "few_rows": (60, 300, lambda g, n: np.full(n, 60), False, 5, 0.0, ("rowwise", 1, False, False)),
+    "long_rows_enough": (45, 900, lambda g, n: np.full(n, 200), False, 5, 0.0, G1),
+    "few_long_rows": (40, 900, lambda g, n: np.full(n, 200), False, 5, 0.0, ("rowwise", 4, False, False)),
     "unshared_row_by_row": (3000, 148000, lambda g, n: np.full(n, 96), None, 2, 0.0, ("blocks", 1, False, True)),
     "two_members": (1600, 30000, lambda g, n: g.integers(60, 150, n), False, 2, 0.0, G2),
     "four_members": (3600, 60000, lambda g, n: g.integers(60, 150, n), False, 2, 0.0, G4),
@@ -65,7 +65,7 @@ def test_sparse_blocks(oracle_mod, name, loss):
     n, d, lengths, zipf, K, l1, runs = CASES[name]
     g = np.random.default_rng(23)
     lens = np.asarray(lengths(g, n)).astype(np.int64)
-    small = n <= 45
+    small = n <= 65
     if not small and name != "unshared_row_by_row":
         lens[3] = 0
     cols = _half_shared(g, n, d) if zipf is None else _rows(g, lens, d, zipf)
