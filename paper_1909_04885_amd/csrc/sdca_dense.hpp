@@ -46,6 +46,17 @@ constexpr int GD_THREADS = 256;
 constexpr int GD_COLS = 64;                      // columns of the block in LDS at a time
 constexpr int GD_LD = GD_COLS + 4;               // 16-byte aligned rows, spread over the banks
 
+// A row takes steps where its squared norm is neither zero nor beyond what a float holds (the row-wise solver's step is zero
+// there).  The two quotients by it that a float may not hold either, for norms below 6e-20, are kept finite: a clamped step
+// only needs them large, and infinity times a product of zero would be no number.
+__device__ __forceinline__ bool takes_steps(float q) { return q != 0.f && q <= 3.4028235e38f; }
+template <int LOSS>
+__device__ __forceinline__ float tile_scale(float q, float c)
+{
+    return LOSS == 0 ? fmaxf(-1.f / q, -3.4028235e38f) : LOSS == 1 ? -1.f / (c + q) : -1.f / c;
+}
+__device__ __forceinline__ float hinge_scale(float q, float c) { return fminf(c / q, 3.4028235e38f); }
+
 // One workgroup per tile.  The product is on the matrix cores (fp32 in and out): per 64 columns every wavefront
 // takes 16 of them for the three 32 x 32 blocks that hold pairs j < i (the fourth is their mirror image).
 template <int LOSS>
@@ -64,7 +75,7 @@ __global__ __launch_bounds__(GD_THREADS) void gram_dense(
     if (tid < BATCH) {
         const int t = ((int)blockIdx.x - S.tile_begin) * BATCH + tid;
         DenseRow row = {chunks[0].val, nullptr};
-        float sgn = 1.f, scale = 0.f;
+        float sgn = 0.f, scale = 0.f;            // a row that takes no step: no part in T
         if (t < S.n_rows) {
             const int lr = perm[S.perm_off + t];
             if ((unsigned)lr >= (unsigned)S.n_rows) {
@@ -76,10 +87,10 @@ __global__ __launch_bounds__(GD_THREADS) void gram_dense(
                 const float4_v st = gld_state(ch.st + r);
                 row.x = ch.val + (int64_t)r * ld;
                 const float q = st.z;
-                if (q != 0.f) {
+                if (takes_steps(q)) {
                     row.st = ch.st + r;
                     sgn = LOSS == 1 ? 1.f : st.x;
-                    scale = LOSS == 0 ? -1.f / q : LOSS == 1 ? -1.f / (c + q) : -1.f / c;
+                    scale = tile_scale<LOSS>(q, c);
                 }
             }
         }
@@ -159,7 +170,7 @@ __global__ __launch_bounds__(GD_THREADS) void gram_dense(
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int j = 4 * jq + e;
-                v[e] = j < i ? G[j * (BATCH + 1) + i] * si * r_sgn[j] : 0.f;
+                v[e] = j < i && si != 0.f && r_sgn[j] != 0.f ? G[j * (BATCH + 1) + i] * si * r_sgn[j] : 0.f;
             }
             *reinterpret_cast<float4_v *>(out + tile_at(4 * jq, i)) = v;
         }
@@ -170,7 +181,7 @@ __global__ __launch_bounds__(GD_THREADS) void gram_dense(
     // T goes to LDS by rows i (X is free), then one wavefront substitutes forward, 2016 multiply-adds.  (Shorter blocks
     // take diagonal blocks of the tile: N's are the inverses of T's.)
     float *Tt = X;                                       // [i][k], BATCH floats per row
-    for (int k = wv; k < BATCH; k += GD_THREADS / 64) Tt[i * GD_LD + k] = k < i ? G[k * (BATCH + 1) + i] * si : 0.f;
+    for (int k = wv; k < BATCH; k += GD_THREADS / 64) Tt[i * GD_LD + k] = k < i && si != 0.f && r_sgn[k] != 0.f ? G[k * (BATCH + 1) + i] * si : 0.f;
     __syncthreads();
     if (wv != 0) return;
     float x[BATCH];
@@ -417,7 +428,7 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
             float t = 0.f, lo = 0.f, hi = 0.f, root = 0.f;
             if (st_cur != nullptr) {
                 if (LOSS == 0) {
-                    t = (sc.c / q) * (rw - y * xu);
+                    t = hinge_scale(q, sc.c) * (rw - y * xu);
                     lo = -a; hi = 1.f - a;
                 } else if (LOSS == 1) {
                     t = (sc.c / (sc.c + q)) * (rw - a - xu);

@@ -377,12 +377,12 @@ __global__ __launch_bounds__(SB_THREADS) void gram_blocks(
                 const int r = lr - chunk_first[ci];
                 const float4_v st = gld_state(ch.st + r);
                 const float q = st.z;
-                if (q != 0.f) {
+                if (takes_steps(q)) {
                     row.st = ch.st + r;
                     row.row = ch.row_base + r;
                     row.lr = lr;
                     sgn = LOSS == 1 ? 1.f : st.x;
-                    scale = LOSS == 0 ? -1.f / q : LOSS == 1 ? -1.f / (c + q) : -1.f / c;
+                    scale = tile_scale<LOSS>(q, c);
                 }
             }
         }
@@ -667,7 +667,7 @@ __global__ __launch_bounds__(SB_THREADS) void sdca_blocks(BlocksArgs A)
                 float t = 0.f, lo = 0.f, hi = 0.f, root = 0.f;
                 if (cur_row.st != nullptr) {
                     if (LOSS == 0) {
-                        t = (A.sc.c / q) * (rw - y * xu);
+                        t = hinge_scale(q, A.sc.c) * (rw - y * xu);
                         lo = -a; hi = 1.f - a;
                     } else if (LOSS == 1) {
                         t = (A.sc.c / (A.sc.c + q)) * (rw - a - xu);
