@@ -1888,6 +1888,21 @@ int chicle_debug_solver(chicle_ctx *c, int32_t *out)
     return CHICLE_OK;
 }
 
+// A tile that holds the recurrence solved, N[j][i] with N = (1 - T)^-1, back to T = 1 - N^-1 in place.
+static void unsolve_tile(float *tile)
+{
+    static_assert(BATCH == 64, "64 x 64");
+    double M[BATCH][BATCH];                       // M = N^-1, both unit triangular: M N = 1, column by column
+    for (int i = 0; i < BATCH; ++i)
+        for (int j = i; j >= 0; --j) {
+            double sum = 0.0;
+            for (int k = j + 1; k <= i; ++k) sum += (double)tile[j * BATCH + k] * M[k][i];
+            M[j][i] = (j == i ? 1.0 : 0.0) - sum;
+        }
+    for (int j = 0; j < BATCH; ++j)
+        for (int i = 0; i < BATCH; ++i) tile[j * BATCH + i] = j < i ? (float)-M[j][i] : 0.f;
+}
+
 int chicle_debug_gram(chicle_ctx *c, const int32_t *perm_device, float *tiles_out, int64_t capacity_floats,
                       int32_t *n_tiles_out)
 {
@@ -1904,25 +1919,29 @@ int chicle_debug_gram(chicle_ctx *c, const int32_t *perm_device, float *tiles_ou
     if (tiles_out) {
         const int64_t want = (int64_t)c->n_tiles * TILE_FLOATS;
         if (capacity_floats < want) return fail(c, CHICLE_EINVAL, "need room for %lld floats", (long long)want);
-        if (c->dense) {        // in the sparse solver's layout, formed in the other tile set a few tiles at a time
+        if (c->dense) {        // in the sparse solver's layout, put together in the other tile set a few tiles at a time
             float *out = c->tiles[1 - c->tile_buf];
             const int at_once = (int)(c->max_tiles * DENSE_TILE_FLOATS / TILE_FLOATS);
             for (int32_t t0 = 0; t0 < c->n_tiles; t0 += at_once) {
                 const int n = std::min(at_once, c->n_tiles - t0);
-                auto kern = c->loss == CHICLE_LOSS_HINGE ? dense_tiles_plain<0> : c->loss == CHICLE_LOSS_SQUARED ? dense_tiles_plain<1> : dense_tiles_plain<2>;
+                auto kern = c->loss == CHICLE_LOSS_HINGE ? dense_tiles_out<0> : c->loss == CHICLE_LOSS_SQUARED ? dense_tiles_out<1> : dense_tiles_out<2>;
                 hipLaunchKernelGGL(kern, dim3(n), dim3(256), 0, c->stream, c->solvers_dev, c->tile_solver_dev,
                                    (const float *)c->tiles[c->tile_buf], t0, (int)c->d, scalars(c).c, out);
                 HIP_TRY(c, hipGetLastError());
                 HIP_TRY(c, hipMemcpyAsync(tiles_out + (int64_t)t0 * TILE_FLOATS, out, sizeof(float) * (size_t)n * TILE_FLOATS, hipMemcpyDeviceToHost, c->stream));
                 HIP_TRY(c, hipStreamSynchronize(c->stream));
             }
+            if (c->tiles_solved[c->tile_buf])
+                for (int64_t t = 0; t < want; t += TILE_FLOATS) unsolve_tile(tiles_out + t + BATCH * BATCH);
         } else {
-            std::vector<float> raw((size_t)want);
-            HIP_TRY(c, hipMemcpyAsync(raw.data(), c->tiles[c->tile_buf], sizeof(float) * (size_t)want, hipMemcpyDeviceToHost, c->stream));
+            HIP_TRY(c, hipMemcpyAsync(tiles_out, c->tiles[c->tile_buf], sizeof(float) * (size_t)want, hipMemcpyDeviceToHost, c->stream));
             HIP_TRY(c, hipStreamSynchronize(c->stream));
-            for (int64_t t = 0; t < want; t += TILE_FLOATS)
+            float raw[TILE_FLOATS];
+            for (int64_t t = 0; t < want; t += TILE_FLOATS) {
+                std::memcpy(raw, tiles_out + t, sizeof raw);
                 for (int jp = 0; jp < TILE_W; ++jp)
-                    for (int i = 0; i < BATCH; ++i) tiles_out[t + jp * BATCH + i] = raw[(size_t)(t + tile_at(jp, i))];
+                    for (int i = 0; i < BATCH; ++i) tiles_out[t + jp * BATCH + i] = raw[tile_at(jp, i)];
+            }
         }
     }
     return check_deferred(c);

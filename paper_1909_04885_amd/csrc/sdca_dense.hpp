@@ -667,26 +667,29 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense_squared(
     stamp_solver(sc, 1);
 }
 
-// The tiles in the layout of the sparse batched solver's ([128][64]: previous block against this one, then this one's
-// own pairs j < i), plain dot products; for inspection only.
+// For inspection: the tiles in the layout of the sparse batched solver's ([128][64]).  This block's own pairs are what
+// gram_dense has written; the pairs of the previous block against this one, which this solver does not need, are plain dot
+// products.
 template <int LOSS>
-__global__ __launch_bounds__(256) void dense_tiles_plain(const SolverDev *__restrict__ solvers, const int32_t *__restrict__ tile_solver,
-                                                         const float *__restrict__ tiles, int first, int d, float c, float *out)
+__global__ __launch_bounds__(256) void dense_tiles_out(const SolverDev *__restrict__ solvers, const int32_t *__restrict__ tile_solver,
+                                                       const float *__restrict__ tiles, int first, int d, float c, float *out)
 {
     const int64_t tile = first + (int)blockIdx.x;
     const int beta = (int)(tile - solvers[tile_solver[tile]].tile_begin);
-    const DenseRow *own = reinterpret_cast<const DenseRow *>(tiles + tile * DENSE_TILE_FLOATS + BATCH * BATCH);
-    const DenseRow *prev = reinterpret_cast<const DenseRow *>(tiles + (tile - 1) * DENSE_TILE_FLOATS + BATCH * BATCH);
+    const float *T = tiles + tile * DENSE_TILE_FLOATS;
+    const DenseRow *own = reinterpret_cast<const DenseRow *>(T + BATCH * BATCH);
+    const DenseRow *prev = reinterpret_cast<const DenseRow *>(T - DENSE_TILE_FLOATS + BATCH * BATCH);
     for (int idx = threadIdx.x; idx < TILE_FLOATS; idx += 256) {
         const int jp = idx >> 6, i = idx & 63;
         float v = 0.f;
-        if ((jp < BATCH && beta > 0) || (jp >= BATCH && jp - BATCH < i)) {
-            const DenseRow a = jp < BATCH ? prev[jp] : own[jp - BATCH], b = own[i];
+        if (jp >= BATCH) {
+            v = T[tile_at(jp - BATCH, i)];
+        } else if (beta > 0) {
+            const DenseRow a = prev[jp], b = own[i];
             if (a.st != nullptr && b.st != nullptr) {
                 double g = 0.0;
                 for (int k = 0; k < d; ++k) g += (double)a.x[k] * (double)b.x[k];
-                const float q = b.st->q;
-                v = (float)g * (LOSS == 0 ? -1.f / q : LOSS == 1 ? -1.f / (c + q) : -1.f / c) * (LOSS == 1 ? 1.f : a.st->y * b.st->y);
+                v = (float)g * tile_scale<LOSS>(b.st->q, c) * (LOSS == 1 ? 1.f : a.st->y * b.st->y);
             }
         }
         out[(int64_t)blockIdx.x * TILE_FLOATS + idx] = v;

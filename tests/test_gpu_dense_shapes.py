@@ -81,3 +81,51 @@ def test_squared_loss_with_solved_tiles(oracle_mod, d, ahead, n):
     table = np.zeros(2, dtype=np.int32)
     run_lockstep({"seed": 5, "rounds": 3, "schedule": [(0, 1)], "K": 1}, p, oracle_mod, binding, check_alpha_every=1, ahead=ahead,
                  tables=lambda r, Kp, tp: (1, table, table.copy()) if r == 0 else None, max_solvers=1)
+
+
+@pytest.mark.parametrize("loss,n,solved", [("hinge", 333, False), ("squared", 333, False), ("squared", 2400, True), ("logistic", 333, False)])
+@pytest.mark.parametrize("d", [1, 7, 16, 33, 48])
+def test_dense_tiles_match_their_definition(loss, d, n, solved):
+    """What the tile kernel of dense rows writes against x_i . x_j in double: ragged last block, an empty row."""
+    import torch
+    import paper_1909_04885_amd as binding
+    assert torch.cuda.is_available()
+    print("\ncase dense tiles n=%d d=%d %s" % (n, d, loss), flush=True)
+    g = np.random.default_rng(d)
+    X = (g.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    X[5] = 0
+    y = np.where(g.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    lam, K = 0.02, 1
+    r = binding.ChicleRound(loss, n, d, lam, 1, K, True, n * d)
+    r.load_chunk_dense(0, X, y)
+    r.assign(K, np.zeros(1, dtype=np.int32))
+    perm = g.permutation(n).astype(np.int32)
+    tiles = r.debug_gram(r.upload_perm([perm]))
+    assert tiles.shape[0] == (n + 63) // 64
+    Xd, yd = X.astype(np.float64)[perm], y.astype(np.float64)[perm]
+    q, c = (Xd ** 2).sum(1), lam * n / K
+    scale = {"hinge": -1.0 / np.where(q > 0, q, np.inf), "squared": np.where(q > 0, -1.0 / (c + q), 0.0),
+             "logistic": np.where(q > 0, -1.0 / c, 0.0)}[loss]
+    sgn = np.ones(n) if loss == "squared" else yd
+    eps = 2.0 ** -24
+    for b in range(tiles.shape[0]):
+        cur = np.arange(b * 64, min(n, b * 64 + 64))
+        for part, rows in ((0, np.arange(b * 64 - 64, b * 64) if b else cur[:0]), (64, cur)):
+            want, bound = np.zeros((64, 64)), np.zeros((64, 64))
+            if rows.size:
+                norm = np.sqrt(q[rows])[:, None] * np.sqrt(q[cur])[None, :] * np.abs(scale[cur])[None, :]
+                want[:rows.size, :cur.size] = (Xd[rows] @ Xd[cur].T) * sgn[rows][:, None] * sgn[cur][None, :] * scale[cur][None, :]
+                # d products and d - 1 sums in fp32, then three more roundings
+                bound[:rows.size, :cur.size] = (2 * d + 4) * eps * norm
+            if part:
+                want, bound = np.triu(want, 1), np.triu(bound, 1)
+                if solved:
+                    # the tile holds N = (1 - T)^-1 from 64-term sums in fp32; T is read back from it in double:
+                    # dT = M dN M with M = 1 - T, and |dN| <= |N| (bound of T + 64 eps |T|) |N| + eps |N|
+                    M = np.eye(64) - want
+                    N = np.linalg.inv(M)
+                    dN = np.abs(N) @ (bound + 64 * eps * np.abs(want)) @ np.abs(N) + eps * np.abs(N)
+                    bound = np.triu(np.abs(M) @ dN @ np.abs(M), 1) + eps * np.abs(want)
+            got = tiles[b][part:part + 64].astype(np.float64)
+            assert (np.abs(got - want) <= bound + 1e-30).all(), (b, part, np.max(np.abs(got - want) - bound))
+    r.close()
