@@ -26,12 +26,10 @@ def test_dense_widths(oracle_mod, loss, d, n):
     K = 4
     table = np.array([0, 1, 1, 3], dtype=np.int32)             # one row; 63 rows; none; the rest
     print("\ncase dense n=%d d=%d %s" % (n, d, loss), flush=True)
-    # An update is a sum of up to n steps' terms in fp32: its error is bounded by about n 2^-24 of the terms' sizes.
-    # In one to three dimensions ridge is solved after two rounds and the third's update, a difference of the
-    # solvers' parts thousands of times its own size, is below that bound relative to itself.
-    rounds = 2 if d <= 3 else 3
-    run_lockstep({"seed": 3, "rounds": rounds, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1,
-                 ahead=d % 2 == 0, tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)
+    # In one to three dimensions ridge is solved after two rounds: the third's update is a difference of the solvers' parts
+    # thousands of times its own size.
+    run_lockstep({"seed": 3, "rounds": 3, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1,
+                 cancelling=loss == "squared" and d <= 3, ahead=d % 2 == 0, tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)
 
 
 @pytest.mark.parametrize("d,rows,K,runs", [(48, 1, 4, "dense"), (49, 8, 4, "rowwise"), (49, 9, 4, "dense"), (400, 8, 4, "rowwise"),
