@@ -14,8 +14,9 @@
  *   hinge   : loss_i(z) = max(0, 1 - y_i z), y_i in {-1,+1}, s_i = y_i, a_i in [0,1]
  *   squared : loss_i(z) = (z - y_i)^2 / 2,  s_i = 1,  a_i real
  *   logistic: loss_i(z) = log(1 + exp(-y_i z)), y_i in {-1,+1}, s_i = y_i, a_i in [0,1]; its coordinate
- *             step has no closed form: the scalar equation is solved numerically (a wavefront evaluates it at
- *             64 points of a bracket and narrows the bracket 63-fold per evaluation)
+ *             step has no closed form: the scalar equation is solved numerically (row by row, a wavefront
+ *             evaluates it at 64 points of a bracket and narrows the bracket 63-fold per evaluation; in blocks,
+ *             steps follow from a series around the last root, with that search where the series does not reach)
  *
  * Data live in HBM as chunks (Section 3 "Uni-tasks", Section 4.4 "In-memory chunk data
  * format"): a chunk is one contiguous block holding a run of rows (CSR or dense) together with
@@ -38,10 +39,14 @@
  *     are renumbered by popularity (done once, at the first assign), which the get/set calls undo;
  *   - the library allocates no device memory: it carves everything out of the arena handed to
  *     chicle_create (size it with chicle_arena_bytes); the arena and the HIP stream are borrowed for
- *     the lifetime of the context; all work is enqueued on that stream; the context itself holds 32 bytes
- *     of pinned host memory, into which the gap's last kernel writes its sums;
+ *     the lifetime of the context; all work is enqueued on that stream (and, ordered with it, on one stream
+ *     of the library's own); the context itself holds 64 bytes of pinned host memory, into which the gap's
+ *     last kernel writes its sums, and from the first get_w or get_delta_w of 4 MB or more on 12 MB of it,
+ *     through which several threads copy such a vector out;
  *   - calls that return values to the host (gap, get_*) wait for the stream; the others only enqueue;
- *   - a context is not thread-safe.
+ *   - a context is not thread-safe.  Local passes of different contexts on one GPU should not run at the
+ *     same time where several workgroups share a solver (chicle_debug_solver): these wait for each other, and
+ *     if another pass keeps some of them off the chip for too long, the wait is given up (EDEVICE).
  */
 #ifndef CHICLE_ROUND_H
 #define CHICLE_ROUND_H
@@ -78,7 +83,10 @@ enum chicle_solver_kind {
                                      of at most 48 entries, or dense rows of at most 320 columns; else EINVAL at
                                      the pass (AUTO takes blocks for dense rows of up to 1536 columns, and for sparse
                                      rows of any length where the columns that several rows of a solver hold fit
-                                     the LDS of up to eight workgroups).  For sparse rows, where the columns do
+                                     the LDS of up to eight workgroups and the arena holds a second layout of the
+                                     rows; neither for solvers of a few rows, nor where rows share so many columns
+                                     that steps one at a time are faster: chicle_debug_solver tells).  For sparse
+                                     rows, where the columns do
                                      not all fit the part of the private vector a compute unit keeps on chip and
                                      the chip has compute units to spare, two workgroups share every solver: one
                                      owns the popular columns and runs the steps, the other owns the rest */
@@ -201,7 +209,9 @@ int chicle_assign(chicle_ctx *ctx, int32_t K, const int32_t *chunk_to_solver);
 
 /* Runtime of every solver's last local pass in milliseconds (host out, K entries), from the device's
  * constant-rate clock read at the start and at the end of the solver's workgroup: the task runtimes
- * the rebalancing policy learns from (Section 4.5).  Synchronises the stream.  Errors: ESTATE before
+ * the rebalancing policy learns from (Section 4.5).  What the whole chip does for all solvers together is
+ * not part of it: the tiles of the block solvers, and the update of columns that one row alone holds after
+ * blocks over shared columns.  Synchronises the stream.  Errors: ESTATE before
  * the first local epoch, EDEVICE. */
 int chicle_solver_ms(chicle_ctx *ctx, float *ms_out);
 
@@ -236,7 +246,10 @@ int chicle_local_epoch(chicle_ctx *ctx, const int32_t *perm_device);
  * after everything enqueued on the context's stream before this call, and runs beside this pass.
  * perm_device may be NULL: the pass then runs with the orders that the previous call announced, from the
  * context's copy, and uses the work prepared for them.  A non-NULL perm_device discards what was announced;
- * so does an assign.  Errors: EINVAL (perm_device NULL with nothing announced), ESTATE. */
+ * so does an assign.  (Short dense passes keep the announced orders and prepare nothing: the second stream
+ * would cost them more.)  A refused call leaves what was announced as it was.  An out-of-range entry of
+ * announced orders may be reported as soon as they are announced.
+ * Errors: EINVAL (perm_device NULL with nothing announced), ESTATE. */
 int chicle_local_epoch_ahead(chicle_ctx *ctx, const int32_t *perm_device, const int32_t *perm_next_device);
 
 /* Same as chicle_local_epoch with the orders given as a host array (copied to a staging area first). */

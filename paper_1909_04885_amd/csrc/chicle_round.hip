@@ -261,9 +261,11 @@ int64_t private_floats(int64_t total_entries, int64_t ld, int32_t max_solvers, b
     return long_rows ? std::min(dense, total_entries + 64 * (int64_t)max_solvers) : dense;
 }
 
-// Room behind the tile sets for the shared entries of long rows (shorter ones find room in the tile sets, which the solver
-// that takes rows of any length uses a quarter of): eight bytes per entry and four half-empty segments per row,
-// and eight bytes per place of the private vectors.
+// Room behind the tile sets for the shared entries of long rows: eight bytes per entry and four half-empty segments per row,
+// and eight bytes per place of the private vectors.  Contexts of up to 96 entries a row on average have only the tile sets,
+// of which the solver that takes rows of any length uses a quarter for its tiles: the rest holds about 89 shared entries a
+// row where a solver has one workgroup, 84, 75 and 57 with two, four and eight.  Rows of more (60 to 96 entries, most of
+// their columns shared) go row by row.
 size_t long_row_layout_bytes(int64_t n_total, int64_t total_entries)
 {
     return sizeof(int32_t) * (4 * (size_t)total_entries + 4 * (size_t)SB_SEG_WORDS * (size_t)n_total);

@@ -30,7 +30,7 @@ __device__ __forceinline__ float ld_l2(const float *p)
 }
 
 // Index of an entry in its solver's compact private vector, with the sign bit set where no other row of the
-// solver holds that column (long-row contexts): the gather of such an entry is known to be zero (the vector is
+// solver holds that column (contexts with a row of more than 48 entries): the gather of such an entry is known to be zero (the vector is
 // zero at the start of a pass and nothing else writes there) and its update is a plain store, not a
 // read-modify-write that fetches a whole line for four bytes.
 constexpr int UNIQUE_COLUMN = (int)0x80000000;
