@@ -172,8 +172,8 @@ struct chicle_ctx {
     int blocks_g = 1;                 // workgroups per solver
     bool blocks_double = true;        // its private vectors are kept in double
     int32_t *mpref_dev = nullptr;     // max_solvers x words: shared columns before each word
-    int32_t *mcount_dev = nullptr;    // shared columns per solver; segments taken; per solver: its segments, its longest row's
-    double *squares_dev = nullptr;    // per solver: sum over its rows of their segments squared
+    int32_t *mcount_dev = nullptr;    // shared columns per solver; one more word: segments taken
+    SegStat *seg_stat_dev = nullptr;  // per solver
     double crowding = -1.0;           // see column_crowding (< 0: not known yet)
     int64_t *place_off_dev = nullptr;
     float *coef_dev = nullptr;        // n_total
@@ -310,7 +310,7 @@ size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_sol
         const size_t words = ((size_t)d + 31) / 32;
         s += 2 * align_up(sizeof(int32_t) * words * (size_t)max_solvers);          // column bitmaps, prefix counts
         s += 2 * align_up(sizeof(int32_t) * words * (size_t)max_solvers);          // columns held by several rows, prefix counts
-        s += align_up(sizeof(int32_t) * (3 * (size_t)max_solvers + 1)) + align_up(sizeof(int64_t) * (size_t)max_solvers) + align_up(sizeof(double) * (size_t)max_solvers);
+        s += align_up(sizeof(int32_t) * ((size_t)max_solvers + 1)) + align_up(sizeof(int64_t) * (size_t)max_solvers) + align_up(sizeof(SegStat) * (size_t)max_solvers);
         s += align_up(sizeof(float) * (size_t)n_total) + align_up(sizeof(unsigned long long) * (size_t)SB_RING_WORDS * (size_t)max_solvers);
         s += align_up(sizeof(int32_t) * (size_t)max_solvers) + align_up(sizeof(int64_t) * (size_t)max_solvers);
         s += align_up(sizeof(int32_t) * (size_t)n_chunks);
@@ -858,21 +858,25 @@ int renumber_columns(chicle_ctx *c)
     return CHICLE_OK;
 }
 
-// For the average entry, the share of all rows that hold its column: 64 times this is how many of a block's rows an entry
-// meets in its column's list.  Of the data alone; formed when it is first asked for.
+// For the average entry, the share of the other rows that hold its column: 64 times this is how many of a block's rows an
+// entry meets in its column's list.  From about 4096 rows; of the data alone, and formed when it is first asked for.
 int column_crowding(chicle_ctx *c, double *out)
 {
     if (c->crowding < 0.0) {
         int32_t *count = c->rank_of;       // (needed by no one after the columns are renumbered)
-        double *sum = c->gap_scratch.unused, s = 0.0;
+        double *sums = c->gap_scratch.unused, s[2] = {0.0, 0.0};
+        const int stride = (int)std::max<int64_t>(1, c->n_total / 4096);
+        int64_t rows = 0;
+        int most = 1;
+        for (const ChunkDev &ch : c->chunks) { rows += (ch.n_rows + stride - 1) / stride; most = std::max(most, ch.n_rows); }
         HIP_TRY(c, hipMemsetAsync(count, 0, sizeof(int32_t) * (size_t)c->d, c->stream));
-        HIP_TRY(c, hipMemsetAsync(sum, 0, sizeof(double), c->stream));
-        hipLaunchKernelGGL(count_columns, dim3(std::max(1, 2048 / c->n_chunks), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev, count);
-        hipLaunchKernelGGL(sum_squares, dim3(grid_for(c->d, 256, 1024)), dim3(256), 0, c->stream, count, (int64_t)c->d, sum);
+        HIP_TRY(c, hipMemsetAsync(sums, 0, sizeof s, c->stream));
+        hipLaunchKernelGGL(count_columns_of_some, dim3(grid_for(most, stride, 256), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev, stride, count);
+        hipLaunchKernelGGL(sum_pairs, dim3(grid_for(c->d, 256, 1024)), dim3(256), 0, c->stream, count, (int64_t)c->d, sums);
         HIP_TRY(c, hipGetLastError());
-        HIP_TRY(c, hipMemcpyAsync(&s, sum, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(s, sums, sizeof s, hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
-        c->crowding = s / ((double)c->n_total * (double)std::max<int64_t>(c->entries_loaded, 1));
+        c->crowding = s[1] > 0.0 && rows > 1 ? s[0] / ((double)(rows - 1) * s[1]) : 0.0;
     }
     *out = c->crowding;
     return CHICLE_OK;
@@ -895,16 +899,16 @@ double tile_in_parts_us(double entries, double crowding)
 // 1.7 us and more each, 2.4 and more on several workgroups per solver.  Both sides, 1024 rows that hold every column, four
 // solvers: 300 columns 1.69 ms in blocks and 0.62 row by row, 1000 columns 9.4 and 0.64; 5000, eight solvers, 139 and 0.42;
 // 256 rows of 200 out of 3200 columns, two solvers, 0.23 and 0.33.  A fifth is added for what the averages hide.
-bool blocks_pay(const chicle_ctx *c, const int32_t *segments, const int32_t *longest, const double *squares, int G, double crowding)
+bool blocks_pay(const chicle_ctx *c, const std::vector<SegStat> &stat, int G, double crowding)
 {
     double worst = 0.0, all = 0.0, chain = 0.0;
     for (int k = 0; k < c->K; ++k) {
         const double rows = c->solvers[k].n_rows, blocks = std::ceil(rows / BATCH);
         if (rows == 0) continue;
-        const double per_row = segments[k] / rows, mean = SB_SEG * segments[k] / blocks;
+        const double per_row = stat[k].total / rows, mean = (double)SB_SEG * stat[k].total / blocks;
         // a tile's entries: spread of a sum of 64 rows, and the tile that holds the longest one
-        const double spread = blocks > 1 ? SB_SEG * std::sqrt(BATCH * std::max(0.0, squares[k] / rows - per_row * per_row)) : 0.0;
-        const double high = blocks > 1 ? mean + SB_SEG * (longest[k] - per_row) : mean;
+        const double spread = blocks > 1 ? SB_SEG * std::sqrt(BATCH * std::max(0.0, stat[k].squares / rows - per_row * per_row)) : 0.0;
+        const double high = blocks > 1 ? mean + SB_SEG * (stat[k].longest - per_row) : mean;
         const double in_parts = 0.5 * std::erfc((GB_ALL - mean) / (1.5 * spread + 1.0));
         const double us = tile_in_parts_us(high, crowding);
         worst = std::max(worst, us);
@@ -945,30 +949,31 @@ int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared, const std:
     c->refs_dev = (SegRef *)(c->layout_dev + tiles);
     c->place_dev = (int32_t *)(c->layout_dev + tiles + refs);
     c->segs_dev = (int32_t *)(c->layout_dev + tiles + refs + place);
-    int *taken = c->mcount_dev + c->max_solvers, *total = taken + 1, *longest = total + c->max_solvers;
+    int *taken = c->mcount_dev + c->max_solvers;
     HIP_TRY(c, hipMemcpyAsync(c->place_off_dev, off.data(), sizeof(int64_t) * (size_t)K, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->squares_dev, 0, sizeof(double) * (size_t)K, c->stream));
-    HIP_TRY(c, hipMemsetAsync(taken, 0, sizeof(int) * (2 * (size_t)c->max_solvers + 1), c->stream));
+    HIP_TRY(c, hipMemsetAsync(taken, 0, sizeof(int), c->stream));
+    HIP_TRY(c, hipMemsetAsync(c->seg_stat_dev, 0, sizeof(SegStat) * (size_t)K, c->stream));
     hipLaunchKernelGGL(shared_places, dim3(grid_for(c->words, 256, 1024), K), dim3(256), 0, c->stream, c->bits_dev, c->pref_dev,
                        c->multi_dev, c->mpref_dev, c->words, c->place_off_dev, c->place_dev);
     int max_rows = 1;
     for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
     hipLaunchKernelGGL(build_segments, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
-                       c->chunk_owner_dev, c->multi_dev, c->mpref_dev, c->words, G, c->n_total, c->refs_dev, c->segs_dev, taken, capacity, total, longest, c->squares_dev);
+                       c->chunk_owner_dev, c->multi_dev, c->mpref_dev, c->words, G, c->n_total, c->refs_dev, c->segs_dev, taken, capacity);
+    hipLaunchKernelGGL(segment_stats, dim3(c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev, c->chunk_owner_dev, (const SegRef *)c->refs_dev, G,
+                       c->n_total, c->seg_stat_dev);
     HIP_TRY(c, hipGetLastError());
-    std::vector<int32_t> stat(2 * (size_t)c->max_solvers + 1);
-    std::vector<double> squares(K);
-    HIP_TRY(c, hipMemcpyAsync(squares.data(), c->squares_dev, sizeof(double) * (size_t)K, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(stat.data(), taken, sizeof(int) * stat.size(), hipMemcpyDeviceToHost, c->stream));
+    int n = 0;
+    std::vector<SegStat> stat(K);
+    HIP_TRY(c, hipMemcpyAsync(&n, taken, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(stat.data(), c->seg_stat_dev, sizeof(SegStat) * (size_t)K, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    const int n = stat[0], *segments = &stat[1], *most_of = &stat[1 + (size_t)c->max_solvers];
     if (n < 0 || n > capacity) return CHICLE_OK;
     double crowding = 1.0;
-    if (!blocks_pay(c, segments, most_of, squares.data(), G, 0.0)) return CHICLE_OK;     // (not even with nothing shared twice)
-    if (!blocks_pay(c, segments, most_of, squares.data(), G, crowding)) {
+    if (!blocks_pay(c, stat, G, 0.0)) return CHICLE_OK;     // (not even with nothing shared twice)
+    if (!blocks_pay(c, stat, G, crowding)) {
         const int rc = column_crowding(c, &crowding);
         if (rc) return rc;
-        if (!blocks_pay(c, segments, most_of, squares.data(), G, crowding)) return CHICLE_OK;
+        if (!blocks_pay(c, stat, G, crowding)) return CHICLE_OK;
     }
     c->blocks_g = G;
     c->blocks_ready = true;
@@ -1077,9 +1082,9 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
         c->pref_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->words * (size_t)max_solvers);
         c->multi_dev = (unsigned *)carve(c, sizeof(unsigned) * (size_t)c->words * (size_t)max_solvers);
         c->mpref_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->words * (size_t)max_solvers);
-        c->mcount_dev = (int32_t *)carve(c, sizeof(int32_t) * (3 * (size_t)max_solvers + 1));
+        c->mcount_dev = (int32_t *)carve(c, sizeof(int32_t) * ((size_t)max_solvers + 1));
         c->place_off_dev = (int64_t *)carve(c, sizeof(int64_t) * (size_t)max_solvers);
-        c->squares_dev = (double *)carve(c, sizeof(double) * (size_t)max_solvers);
+        c->seg_stat_dev = (SegStat *)carve(c, sizeof(SegStat) * (size_t)max_solvers);
         c->coef_dev = (float *)carve(c, sizeof(float) * (size_t)n_total);
         c->blocks_ring_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * (size_t)SB_RING_WORDS * (size_t)max_solvers);
         c->count_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)max_solvers);

@@ -18,14 +18,26 @@ __global__ __launch_bounds__(256) void count_columns(const ChunkDev *__restrict_
     for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < ch.nnz; p += (int64_t)gridDim.x * 256) atomicAdd(&count[ch.col[p]], 1);
 }
 
-// *out += sum of count[0 .. n)^2.
-__global__ __launch_bounds__(256) void sum_squares(const int *__restrict__ count, int64_t n, double *out)
+// The same for every `stride`-th row of a chunk.  Grid: (blocks over rows, chunk).
+__global__ __launch_bounds__(256) void count_columns_of_some(const ChunkDev *__restrict__ chunks, int stride, int *count)
 {
-    double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) s += (double)count[i] * (double)count[i];
+    const ChunkDev &ch = chunks[blockIdx.y];
+    for (int64_t r = (int64_t)blockIdx.x * stride; r < ch.n_rows; r += (int64_t)gridDim.x * stride)
+        for (int p = ch.row_ptr[r] + threadIdx.x; p < ch.row_ptr[r + 1]; p += 256) atomicAdd(&count[ch.col[p]], 1);
+}
+
+// out[0] += sum of count (count - 1), out[1] += sum of count, over count[0 .. n).
+__global__ __launch_bounds__(256) void sum_pairs(const int *__restrict__ count, int64_t n, double *out)
+{
+    double pairs = 0.0, all = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const double f = (double)count[i];
+        pairs += f * (f - 1.0);
+        all += f;
+    }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if ((threadIdx.x & 63) == 0) atomicAdd(out, s);
+    for (int o = 32; o > 0; o >>= 1) { pairs += __shfl_xor(pairs, o, 64); all += __shfl_xor(all, o, 64); }
+    if ((threadIdx.x & 63) == 0 && all > 0.0) { atomicAdd(out, pairs); atomicAdd(out + 1, all); }
 }
 
 // col <- rank_of[col] and insertion sort of each row by the new ids (values move with their ids).

@@ -65,20 +65,17 @@ __global__ __launch_bounds__(256) void shared_places(const unsigned *__restrict_
 }
 
 // The shared entries of every row, by member, in segments.  One wavefront per row, 4 rows per workgroup; segments are
-// taken from *next, one addition per workgroup.  total[k], longest[k], squares[k]: the segments of solver k's rows, of the
-// one with the most, and the sum of their squares.  Grid: (blocks over rows, chunk).
+// taken from *next, one addition per workgroup.  Grid: (blocks over rows, chunk).
 __global__ __launch_bounds__(256) void build_segments(const ChunkDev *__restrict__ chunks, const int32_t *__restrict__ owner,
                                                       const unsigned *__restrict__ multi, const int32_t *__restrict__ mpref,
                                                       int64_t words, int G, int64_t n_total, SegRef *refs, int32_t *segs,
-                                                      int *next, int capacity, int *total, int *longest, double *squares)
+                                                      int *next, int capacity)
 {
     __shared__ int cnt[4][SB_MAX_G], first[4][SB_MAX_G];
     const ChunkDev &ch = chunks[blockIdx.y];
     const int32_t *cid = chunk_compact_ids(ch);
     const int64_t base = (int64_t)owner[blockIdx.y] * words;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int all = 0, most = 0;                       // thread 0
-    double sq = 0.0;
     for (int r0 = blockIdx.x * 4; r0 < ch.n_rows; r0 += gridDim.x * 4) {
         const int r = r0 + wv;
         const int b = r < ch.n_rows ? ch.row_ptr[r] : 0, e = r < ch.n_rows ? ch.row_ptr[r + 1] : 0;
@@ -99,13 +96,8 @@ __global__ __launch_bounds__(256) void build_segments(const ChunkDev *__restrict
         __syncthreads();
         if (threadIdx.x == 0) {
             int sum = 0;
-            for (int w = 0; w < 4; ++w) {
-                const int before = sum;
+            for (int w = 0; w < 4; ++w)
                 for (int g = 0; g < G; ++g) { first[w][g] = sum; sum += cnt[w][g]; }
-                most = max(most, sum - before);
-                sq += (double)(sum - before) * (double)(sum - before);
-            }
-            all += sum;
             const int at = sum ? atomicAdd(next, sum) : 0;
             for (int w = 0; w < 4; ++w)
                 for (int g = 0; g < G; ++g) first[w][g] += at;
@@ -149,11 +141,37 @@ __global__ __launch_bounds__(256) void build_segments(const ChunkDev *__restrict
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0 && all > 0) {
-        atomicAdd(total + owner[blockIdx.y], all);
-        atomicMax(longest + owner[blockIdx.y], most);
-        atomicAdd(squares + owner[blockIdx.y], sq);
+}
+
+// What the rows of a solver come to in segments: all of them, the row with the most, the sum of their squares.
+struct SegStat { double squares; int32_t total, longest; };
+// One workgroup per chunk; stat starts at zero.
+__global__ __launch_bounds__(256) void segment_stats(const ChunkDev *__restrict__ chunks, const int32_t *__restrict__ owner,
+                                                     const SegRef *__restrict__ refs, int G, int64_t n_total, SegStat *stat)
+{
+    __shared__ SegStat part[4];
+    const ChunkDev &ch = chunks[blockIdx.x];
+    SegStat s = {0.0, 0, 0};
+    for (int r = threadIdx.x; r < ch.n_rows; r += 256) {
+        int n = 0;
+        for (int g = 0; g < G; ++g) n += refs[(int64_t)g * n_total + ch.row_base + r].n;
+        s.squares += (double)n * (double)n;
+        s.total += n;
+        s.longest = max(s.longest, n);
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        s.squares += __shfl_xor(s.squares, o, 64);
+        s.total += __shfl_xor(s.total, o, 64);
+        s.longest = max(s.longest, __shfl_xor(s.longest, o, 64));
+    }
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    SegStat *out = stat + owner[blockIdx.x];
+    atomicAdd(&out->squares, part[0].squares + part[1].squares + part[2].squares + part[3].squares);
+    atomicAdd(&out->total, part[0].total + part[1].total + part[2].total + part[3].total);
+    atomicMax(&out->longest, max(max(part[0].longest, part[1].longest), max(part[2].longest, part[3].longest)));
 }
 
 // ---- tiles ----------------------------------------------------------------------------------------------------------
