@@ -262,7 +262,7 @@ struct DenseShape {
 };
 
 // The recurrence: lane i owns row i of the block; returns the row's step.  T: lane's coefficients, [j].
-// SOLVED: T holds the inverse of the squared loss's recurrence (gram_dense).
+// SOLVED: T holds the inverse of the squared loss's recurrence (gram_dense) without its unit diagonal.
 template <int LOSS, int BR, bool SOLVED>
 __device__ __forceinline__ float dense_recurrence(const float *T_lds, float t, float lo, float hi, float a, float root, int lane)
 {
@@ -283,7 +283,20 @@ __device__ __forceinline__ float dense_recurrence(const float *T_lds, float t, f
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc[j & 3] = fmaf(s[j], T4[(j0 + j) >> 2][j & 3], acc[j & 3]);
         }
-        return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+        return t + ((acc[0] + acc[1]) + (acc[2] + acc[3]));
+    }
+    if (LOSS == 1) {
+        // The other steps' influence is summed apart from the row's own t: 63 small terms added to t one after the other
+        // would each round it, three times the error of a row-wise step (2e-7 of alpha against 5e-8).  The step of row j is
+        // t_j + s_j; its t_j part does not wait for s_j.
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < BR; ++j) {
+            const float tj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), j));
+            const float sj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), j));
+            s = fmaf(sj, T4[j >> 2][j & 3], fmaf(tj, T4[j >> 2][j & 3], s));
+        }
+        return t + s;
     }
 #pragma unroll
     for (int j = 0; j < BR; ++j) {
@@ -354,6 +367,11 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
 #pragma unroll
         for (int k = 0; k < TPT; ++k) {
             const int idx = tid + k * SH::THREADS;
+            if (SOLVED) {                              // without the diagonal: t itself is added last (dense_recurrence)
+                const int e = (idx & (BR - 1)) - 4 * (idx / BR);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) t_in[k][q] = e == q ? 0.f : t_in[k][q];
+            }
             if (T4 % SH::THREADS == 0 || idx < T4) reinterpret_cast<float4_v *>(T)[idx] = t_in[k];
         }
     };

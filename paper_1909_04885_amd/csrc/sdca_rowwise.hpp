@@ -128,38 +128,41 @@ __device__ __forceinline__ float logistic_block(float m, float a, float r, float
 #define CHICLE_LANE(x, j) __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j))
     const bool live = r > 0.f;
     LogisticTrack k;
-    float mine = 0.f;
+    // the row's m is the m at the start of the block and `moved`, the sum of the steps' influence, apart: added to m one by
+    // one, each of them would round it
+    float mine = 0.f, moved = 0.f, h = 0.f;          // d = moved g + h
     k.s = root;
     float d = 0.f;
     auto renew = [&]() __attribute__((always_inline)) {
         const float dc = fminf(fmaxf(d, -0.5f), 0.5f);
         const float ds = fabsf(d) <= LOGISTIC_SERIES ? d * fmaf(d, fmaf(d, fmaf(d, k.c4, k.c3), k.c2), 1.0f) : dc;
         k.at(k.s + ds, a, r, live);
-        d = fmaf(m, k.g, k.h);
+        h = fmaf(m, k.g, k.h);
+        d = fmaf(moved, k.g, h);
     };
     auto step = [&]() __attribute__((always_inline)) {
         const float d2 = d * d;
         return fmaf(d, fmaf(d2, fmaf(d, k.q4, k.q3), fmaf(d, k.q2, k.q1)), k.q0);
     };
     k.at(root, a, r, live);
-    d = fmaf(m, k.g, k.h);
+    d = h = fmaf(m, k.g, k.h);
 #pragma unroll 1
     for (int jq = 0; jq < BR / 4; ++jq) {
         const float4_v T4 = coef4(jq);
         if (jq > 0) renew();
-        const float m_before = m;
+        const float moved_before = moved;
         float dj[4];
         bool bad = false;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             bad = bad || (lane == 4 * jq + e && fabsf(d) > LOGISTIC_SERIES);
             dj[e] = CHICLE_LANE(step(), 4 * jq + e);
-            m = fmaf(dj[e], T4[e], m);
-            d = fmaf(m, k.g, k.h);
+            moved = fmaf(dj[e], T4[e], moved);
+            d = fmaf(moved, k.g, h);
         }
         if (__ballot(bad)) {
-            m = m_before;
-            d = fmaf(m, k.g, k.h);
+            moved = moved_before;
+            d = fmaf(moved, k.g, h);
 #pragma unroll 1
             for (int e = 0; e < 4; ++e) {
                 const int j = 4 * jq + e;
@@ -168,11 +171,11 @@ __device__ __forceinline__ float logistic_block(float m, float a, float r, float
                 if (fabsf(CHICLE_LANE(d, j)) > LOGISTIC_SERIES) {
                     // f falls at least as fast as s grows: the root lies between s and s + f(s), f(s) = d / g
                     const float sj = CHICLE_LANE(k.s, j), xj = CHICLE_LANE(d, j) / CHICLE_LANE(k.g, j);
-                    x = logistic_step_wave(CHICLE_LANE(m, j), CHICLE_LANE(r, j), CHICLE_LANE(a, j), sj + fminf(xj, 0.f), fabsf(xj), lane);
+                    x = logistic_step_wave(CHICLE_LANE(m + moved, j), CHICLE_LANE(r, j), CHICLE_LANE(a, j), sj + fminf(xj, 0.f), fabsf(xj), lane);
                 }
                 const float Te = e == 0 ? T4[0] : e == 1 ? T4[1] : e == 2 ? T4[2] : T4[3];
-                m = fmaf(x, Te, m);
-                d = fmaf(m, k.g, k.h);
+                moved = fmaf(x, Te, moved);
+                d = fmaf(moved, k.g, h);
                 if (e == 0) dj[0] = x; else if (e == 1) dj[1] = x; else if (e == 2) dj[2] = x; else dj[3] = x;
             }
         }
