@@ -562,6 +562,7 @@ int launch_rowwise(chicle_ctx *c, const int32_t *perm)
 }
 
 // Gram tiles of the given visiting orders into tile set `buf`, on `stream` (ahead: beside the pass before theirs).
+constexpr int GRAM_RUN = 32;
 template <int LOSS>
 int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, bool ahead, hipStream_t stream)
 {
@@ -576,8 +577,13 @@ int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, bool ahead, hipStre
         auto kern = gram_tiles_join<LOSS>;
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)sizeof(GramShared)));
-        // each workgroup takes a contiguous run of tiles (neighbouring tiles share half their rows)
-        const int grid = std::min(c->n_tiles, 2048);
+        // Each workgroup takes a contiguous run of tiles, no more of them than GRAM_RUN: the compute units that are free (beside
+        // a pass: those its solvers leave) take their share of the tiles in as few runs as that allows.  A run begins with
+        // some 16 us of dependent loads, which 3 tiles do not hide (4688 tiles: 187 us in runs of 10, 173 in runs of 19); runs
+        // without a limit would keep the next pass's solvers off their compute units.
+        const int free = ahead ? std::max(c->cu_count / 4, c->cu_count - (1 + std::max(0, split_tails(c))) * c->K) : c->cu_count;
+        const int runs = (c->n_tiles + GRAM_RUN * free - 1) / (GRAM_RUN * free);
+        const int grid = std::min(c->n_tiles, runs * free);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(GRAM_THREADS), sizeof(GramShared), stream,
                            c->chunks_dev, c->solvers_dev, c->row_chunk_dev, c->chunk_first_dev, perm,
                            c->tile_solver_dev, c->tiles[buf], c->n_tiles, sc.c, c->err_dev);

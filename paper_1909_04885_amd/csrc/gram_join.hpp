@@ -3,17 +3,28 @@
 // A tile couples the 64 rows of one block (i) with the 64 rows of the previous block and the earlier
 // rows of the same block (jp): T[jp][i] = scale_i s_i s_j (x_i . x_j).  Columns are stored as popularity
 // ranks, so a row's entries split by a range test:
-//   - popular columns (rank < GRAM_DENSE): the window's values go into a small dense matrix in LDS and
-//     their contribution is a dense product on the matrix cores, fp32 in and out (the rows share so many
-//     of these columns that the join's lists would be long);
-//   - all other columns: a hash join in LDS.  Entries are inserted into an open-addressing table keyed
-//     by column, counted per slot, laid out as posting lists (row, value) by a scan, and every entry of
-//     a block row walks the short list of its column, adding its products with float atomics in LDS.
+//   - popular columns (rank < GRAM_DENSE): the values go into a small dense matrix in LDS and their contribution
+//     is a dense product on the matrix cores, fp32 in and out (the rows share so many of these columns that the
+//     join's lists would be long);
+//   - all other columns: a hash join in LDS by chains.  A slot holds the entry that was put there last, every entry
+//     the one that was there before it, so that putting an entry in is one exchange, and an entry meets the earlier
+//     members of its column by following its chain, adding its products with atomics in LDS.
+// Each workgroup owns a contiguous range of tiles and works through it.  The two latest blocks are kept, each with a
+// table of its own (by the parity of its number): a block is put in once, for the tile of its own and as the previous
+// block of the next.  Slots hold the block's number beside the entry's position, so the tables are never cleared: a slot
+// of an older block is an empty one.  A thread follows the chains of its three entries through both tables side by side,
+// six trips to LDS in flight; an entry is one 64-bit word (its column is told by what its slot leaves open of the hash, which
+// permutes the column numbers), because the number of LDS reads is what a chain's step costs.
+// The dense product stays in the registers of the wavefronts that write the tile out; half of them multiply while the other
+// half follows chains.
+// Three workgroup barriers per tile; the row lookups of the tiles to come (visiting order -> chunk -> row offsets, a
+// chain of dependent loads) are spread over the phases of the current one, entries are requested a tile ahead.
+// What bounds it is the longest chain among a wavefront's lanes: per tile of rows of 40 Zipf-distributed entries 18.5e3
+// cycles, of which 9e3 go into chains, 3e3 into the dense product, 1.7e3 into putting the block in and 1.5e3 into writing the
+// tile.  4688 such tiles on 256 compute units: 298 us with a table per tile that was cleared, counted, scanned and laid out
+// as lists; 251 with chains of both blocks' entries kept, 212 with one word per entry and the dense product in registers,
+// 199 with the chains of one entry at a time, 187 with slots of their own for the more frequent columns, 173 in longer runs.
 // The summation order of the join is not fixed, so tiles can differ in the last bits between runs.
-//
-// Each workgroup owns a contiguous range of tiles and works through it; the row lookups of the next
-// tile (visiting order -> chunk -> row offsets, a chain of dependent loads) are spread over the phases
-// of the current tile so that their latency is hidden.
 #pragma once
 #include <hip/hip_runtime.h>
 #include "device_types.hpp"
@@ -23,45 +34,55 @@ namespace chicle {
 
 constexpr int GRAM_DENSE = 64;                        // columns handled by the dense product
 constexpr int GRAM_THREADS = 1024;
-constexpr int GRAM_SLOTS = 8192;                      // hash slots (> window entries, so probing ends)
-constexpr int GRAM_ENTRIES = TILE_W * GRAM_MAX_ROW;   // 6144 entry positions: row slot * 48 + p
+constexpr int GRAM_DIRECT = 1024;                     // the columns that follow have a slot each,
+constexpr int GRAM_HASH_LOG2 = 11;                    // all others share these (chains, not probing: fewer than entries is fine)
+constexpr int GRAM_SLOTS = GRAM_DIRECT + (1 << GRAM_HASH_LOG2);
+constexpr int GRAM_ENTRIES = BATCH * GRAM_MAX_ROW;    // entry positions of a block
 constexpr int GRAM_EPT = GRAM_ENTRIES / GRAM_THREADS; // entry positions per thread
+constexpr int GRAM_LPR = GRAM_THREADS / BATCH;        // threads per row: thread 16 s + l takes entries l, l + 16, l + 32 of row s
+                                                      // (rows are sorted by popularity: a wavefront's k-th entries have chains of like length)
+constexpr int GRAM_POS_BITS = 12;                     // a slot: the block's number above, the entry's position below
+constexpr int GRAM_REST_BITS = 31 - GRAM_HASH_LOG2;  // of a column's hash, beside its slot
+static_assert(GRAM_ENTRIES < 1 << GRAM_POS_BITS && GRAM_EPT * GRAM_THREADS == GRAM_ENTRIES && GRAM_EPT * GRAM_LPR == GRAM_MAX_ROW, "positions");
+static_assert(GRAM_REST_BITS + GRAM_POS_BITS <= 32 && (unsigned)GRAM_SLOTS < 0xffffffffu >> GRAM_REST_BITS, "an entry is two words");
 constexpr int G_LD = BATCH + 1;                       // padded row of the accumulator tile
+constexpr int A_LD = TILE_W + 2;                      // padded row of the dense part
 
-struct GramRows {                                     // the 128 rows of a window
-    const int32_t *col[TILE_W];
-    const float *val[TILE_W];
-    int len[TILE_W];
-    float sgn[TILE_W];
-    float scale[BATCH];
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+struct GramRows {                                     // the 64 rows of a block
+    const int32_t *col[BATCH];
+    const float *val[BATCH];
+    int len[BATCH];
+    float sgn[BATCH], scale[BATCH];
 };
 
 // The accumulators are doubles: the join adds into them with LDS atomics, and on this hardware those run
-// at the rate of the LDS pipeline for doubles while they are serialised lane by lane for floats.  The
-// dense slab A is only alive from the clearing of the tables to the end of the dense product, when G is
-// not; it occupies the tail of G's storage.
+// at the rate of the LDS pipeline for doubles while they are serialised lane by lane for floats.
+// next: position of the entry that was in the slot before it, or CHAIN_END.
+struct __align__(8) GramEntry { unsigned rest_next; float val; };
+constexpr unsigned CHAIN_END = (1u << GRAM_POS_BITS) - 1u;
 struct GramShared {
-    union {
-        double G[TILE_W][G_LD];            // accumulators [jp][i]
-        struct {
-            unsigned char before_A[sizeof(double) * TILE_W * G_LD - sizeof(float) * GRAM_DENSE * TILE_W];
-            float A[GRAM_DENSE][TILE_W];   // dense part, [column][window row]
-        } d;
-    };
-    int keys[GRAM_SLOTS];                  // column per slot during insertion, then fill cursors
-    unsigned short start[GRAM_SLOTS];      // entries per slot, then exclusive scan = list begin
-    float post_val[GRAM_ENTRIES];          // posting lists grouped by slot: value ...
-    unsigned char post_row[GRAM_ENTRIES];  // ... and window row of each member
-    GramRows rows[3];                      // current tile and the two after it
-    int scan[GRAM_THREADS / 64];
+    double Gx[BATCH][G_LD];                // accumulators: previous block [jp][i] ...
+    double Go[BATCH * (BATCH - 1) / 2];    // ... and the block's own pairs j < i, at own_at(j, i)
+    float A[GRAM_DENSE][A_LD];             // dense part, [column][64 * (block & 1) + row]
+    unsigned head[2][GRAM_SLOTS];          // by block & 1: the slot's latest entry (block number 0: none yet)
+    GramEntry entry[2][GRAM_ENTRIES];      // of the two latest blocks, by block & 1; position GRAM_THREADS * k + thread
+    GramRows rows[4];                      // previous block, current one and the two after it
 };
+static_assert(sizeof(GramShared) <= LDS_BYTES, "fits a compute unit");
 
-constexpr int EMPTY_KEY = -1;
+__device__ __forceinline__ int own_at(int j, int i) { return i * (i - 1) / 2 + j; }
+// A column's slot (above GRAM_REST_BITS) and what tells it from the slot's other columns: multiplication by an odd number
+// permutes the 31-bit column numbers, the upper bits choose the slot and the lower ones are left.
+__device__ __forceinline__ unsigned gram_key(int col)
+{
+    const unsigned h = ((unsigned)col * 2654435761u) & 0x7fffffffu;
+    return col < GRAM_DENSE + GRAM_DIRECT ? (unsigned)(col - GRAM_DENSE) << GRAM_REST_BITS : h + ((unsigned)GRAM_DIRECT << GRAM_REST_BITS);
+}
 
-__device__ __forceinline__ int gram_hash(int col) { return (int)(((unsigned)col * 2654435761u) >> 19); }
-
-// Row lookups of one window, one row per thread (tid < 128), as four steps of dependent loads.
+// Row lookups of one block, one row per lane of a wavefront, as steps of dependent loads.
 struct RowLookup {
+    SolverDev S;
     int lr, ci, r;
     const int32_t *row_ptr, *colp;
     const float *valp;
@@ -82,7 +103,8 @@ __global__ __launch_bounds__(GRAM_THREADS) void gram_tiles_join(
 {
     extern __shared__ __align__(16) unsigned char gsm[];
     GramShared &sh = *reinterpret_cast<GramShared *>(gsm);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int per = (n_tiles + gridDim.x - 1) / gridDim.x;
     const int t_begin = blockIdx.x * per;
     const int t_end = min(n_tiles, t_begin + per);
@@ -90,40 +112,35 @@ __global__ __launch_bounds__(GRAM_THREADS) void gram_tiles_join(
 
     const int32_t *dummy_col = chunks[0].col;      // readable for at least GRAM_MAX_ROW entries
     const float *dummy_val = chunks[0].val;
-    RowLookup L;
-    SolverDev LS;
-    // step 1: visiting-order entry of this thread's row in window `tile`
-    auto lookup1 = [&](int tile) {
-        L.live = false; L.lr = -1;
-        if (tid >= TILE_W || tile >= t_end) return;
-        LS = solvers[tile_solver[tile]];
-        const int beta = tile - LS.tile_begin;
-        const int b = tid < BATCH ? beta - 1 : beta;
-        const int t = b * BATCH + (tid & (BATCH - 1));
-        if (b >= 0 && t < LS.n_rows) { L.lr = gld(perm + LS.perm_off + t); L.live = true; }
+    // step 1: visiting-order entry of the lane's row in tile `tile`
+    auto lookup1 = [&](RowLookup &L, int tile, bool wanted) __attribute__((always_inline)) {
+        L.live = false;
+        if (!wanted) return;
+        L.S = solvers[tile_solver[tile]];
+        const int t = (tile - L.S.tile_begin) * BATCH + lane;
+        if (t < L.S.n_rows) { L.lr = gld(perm + L.S.perm_off + t); L.live = true; }
     };
-    auto lookup2 = [&]() {       // -> chunk id
+    auto lookup2 = [&](RowLookup &L) __attribute__((always_inline)) {       // -> chunk id
         if (!L.live) return;
-        if ((unsigned)L.lr >= (unsigned)LS.n_rows) { atomicOr(err, ERR_PERM_RANGE); L.live = false; return; }
-        L.ci = gld(row_chunk + LS.perm_off + L.lr);
+        if ((unsigned)L.lr >= (unsigned)L.S.n_rows) { atomicOr(err, ERR_PERM_RANGE); L.live = false; return; }
+        L.ci = gld(row_chunk + L.S.perm_off + L.lr);
     };
-    auto lookup3 = [&]() {       // -> chunk descriptor
+    auto lookup3 = [&](RowLookup &L) __attribute__((always_inline)) {       // -> chunk descriptor
         if (!L.live) return;
         const ChunkDev &ch = chunks[L.ci];
         L.r = L.lr - gld(chunk_first + L.ci);
         L.row_ptr = ch.row_ptr; L.colp = ch.col; L.valp = ch.val; L.stp = ch.st;
     };
-    auto lookup4 = [&]() {       // -> row offsets and state
+    auto lookup4 = [&](RowLookup &L) __attribute__((always_inline)) {       // -> row offsets and state
         if (!L.live) return;
         L.rp = gld2(L.row_ptr + L.r);
         L.st = gld_state(L.stp + L.r);
     };
-    auto publish = [&](GramRows &R) {
-        if (tid >= TILE_W) return;
+    auto publish = [&](const RowLookup &L, GramRows &R) __attribute__((always_inline)) {
         int len = 0;
         float sgn = 1.f, scale = 0.f;
-        const int32_t *cp = nullptr;
-        const float *vp = nullptr;
+        const int32_t *cp = dummy_col;
+        const float *vp = dummy_val;
         if (L.live) {
             const int n = L.rp.y - L.rp.x;
             const float q = L.st.z;
@@ -133,213 +150,176 @@ __global__ __launch_bounds__(GRAM_THREADS) void gram_tiles_join(
                 scale = LOSS == 0 ? -1.f / q : LOSS == 1 ? -1.f / (c + q) : -1.f / c;
             }
         }
-        if (len == 0) { cp = dummy_col; vp = dummy_val; }
-        R.col[tid] = cp; R.val[tid] = vp; R.len[tid] = len; R.sgn[tid] = sgn;
-        if (tid >= BATCH) R.scale[tid - BATCH] = scale;
+        R.col[lane] = cp; R.val[lane] = vp; R.len[lane] = len; R.sgn[lane] = sgn; R.scale[lane] = scale;
+    };
+    // a thread's entry positions are the same in every block; loads are unconditional (a row without entries points at
+    // readable dummy data and the store keeps slack behind every chunk)
+    int e_col[GRAM_EPT], n_col[GRAM_EPT];
+    float e_val[GRAM_EPT], n_val[GRAM_EPT];
+    const int e_row = tid / GRAM_LPR, e_p = tid % GRAM_LPR;
+    auto request = [&](const GramRows &R, int (&to_c)[GRAM_EPT], float (&to_v)[GRAM_EPT]) __attribute__((always_inline)) {
+        const int32_t *cp = R.col[e_row] + e_p;
+        const float *vp = R.val[e_row] + e_p;
+#pragma unroll
+        for (int k = 0; k < GRAM_EPT; ++k) { to_c[k] = gld(cp + k * GRAM_LPR); to_v[k] = gld(vp + k * GRAM_LPR); }
+    };
+    auto clear_half = [&](int half) __attribute__((always_inline)) {        // of the dense part
+        for (int i = tid; i < GRAM_DENSE * BATCH; i += GRAM_THREADS) sh.A[i / BATCH][half * BATCH + (i & (BATCH - 1))] = 0.f;
+    };
+    // Block number `seq` (its rows in R, its entries in e_col, e_val) is put in.  key[k]: of the thread's k-th entry
+    // (NO_KEY: it is in no slot); at[k]: where its chain in its own block goes on.
+    constexpr unsigned NO_KEY = 0xffffffffu, REST = (1u << GRAM_REST_BITS) - 1u;
+    unsigned key[GRAM_EPT], at[2 * GRAM_EPT];
+    auto position = [&](unsigned slot, int seq) __attribute__((always_inline)) {       // of the entry in a slot of block seq's
+        return (int)(slot >> GRAM_POS_BITS) == seq ? slot & CHAIN_END : CHAIN_END;
+    };
+    auto insert = [&](const GramRows &R, int seq) __attribute__((always_inline)) {
+        unsigned was[GRAM_EPT];
+        const int len = R.len[e_row];
+#pragma unroll
+        for (int k = 0; k < GRAM_EPT; ++k) {       // all exchanges in flight together
+            was[k] = 0u; key[k] = NO_KEY;
+            if (e_p + k * GRAM_LPR >= len) continue;
+            if (e_col[k] < GRAM_DENSE) {
+                sh.A[e_col[k]][(seq & 1) * BATCH + e_row] = e_val[k];
+            } else {
+                key[k] = gram_key(e_col[k]);
+                was[k] = atomicExch(&sh.head[seq & 1][key[k] >> GRAM_REST_BITS], (unsigned)seq << GRAM_POS_BITS | (unsigned)(tid + k * GRAM_THREADS));
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < GRAM_EPT; ++k) {
+            at[k] = key[k] == NO_KEY ? CHAIN_END : position(was[k], seq);
+            if (key[k] != NO_KEY) sh.entry[seq & 1][tid + k * GRAM_THREADS] = GramEntry{(key[k] & REST) << GRAM_POS_BITS | at[k], e_val[k]};
+        }
     };
 
-    // Rows are known two tiles ahead (the lookups of tile + 2 are spread over the phases of the current
-    // tile), entries one tile ahead: a thread holds the same entry positions of the block rows in every
-    // tile, so the 64 rows that are "previous block" in the next tile are already in its registers and only
-    // the next tile's own rows are requested, a whole tile before they are used.
-    lookup1(t_begin); lookup2(); lookup3(); lookup4(); publish(sh.rows[0]);
-    lookup1(t_begin + 1); lookup2(); lookup3(); lookup4(); publish(sh.rows[1]);
-    __syncthreads();
-    constexpr int HALF = GRAM_EPT / 2;             // entry positions per thread in the previous block's rows
-    int e_col[GRAM_EPT], n_col[HALF];
-    float e_val[GRAM_EPT], n_val[HALF];
-#pragma unroll
-    for (int k = 0; k < GRAM_EPT; ++k) {           // first tile: all 128 rows
-        const int idx = tid + k * GRAM_THREADS;
-        const int s = idx / GRAM_MAX_ROW, p = idx - s * GRAM_MAX_ROW;
-        e_col[k] = gld(sh.rows[0].col[s] + p); e_val[k] = gld(sh.rows[0].val[s] + p);
+    // ---- start: rows of the previous block, the first, the second and the third tile's, looked up side by side by four
+    // wavefronts.  The fourth goes on looking rows up: LA two and three tiles ahead; the loop expects the third tile's at its
+    // last step.
+    int solver = tile_solver[t_begin];
+    const bool has_prev = t_begin > solvers[solver].tile_begin;
+    constexpr int RESOLVER = 3;
+    RowLookup LA;
+    LA.live = false;
+    if (wv <= RESOLVER) {
+        const int tile = t_begin - 1 + wv;
+        lookup1(LA, tile, wv == 0 ? has_prev : tile < t_end);
+        lookup2(LA); lookup3(LA);
+        if (wv < RESOLVER) { lookup4(LA); publish(LA, sh.rows[wv]); }
     }
+    for (int i = tid; i < 2 * GRAM_SLOTS; i += GRAM_THREADS) (&sh.head[0][0])[i] = 0u;
+    for (int i = tid; i < BATCH * G_LD; i += GRAM_THREADS) (&sh.Gx[0][0])[i] = 0.0;
+    for (int i = tid; i < BATCH * (BATCH - 1) / 2; i += GRAM_THREADS) sh.Go[i] = 0.0;
+    clear_half(0);
+    clear_half(1);
+    __syncthreads();
+    int seq = 2;                                   // number of the block put in last
+    request(sh.rows[0], e_col, e_val);
+    request(sh.rows[1], n_col, n_val);
+    insert(sh.rows[0], seq);
+#pragma unroll
+    for (int k = 0; k < GRAM_EPT; ++k) { e_col[k] = n_col[k]; e_val[k] = n_val[k]; }
 
     for (int tile = t_begin; tile < t_end; ++tile) {
-        const int slot = (tile - t_begin) % 3;
-        GramRows &R = sh.rows[slot];
-        // ---- request the next tile's own rows; clear the tables; lookup of tile + 2, step 1
-        bool e_live[GRAM_EPT];
+        const int slot = tile - t_begin + 1;       // rows[slot & 3]: this tile's
+        GramRows &R = sh.rows[slot & 3];
+        const GramRows &P = sh.rows[(slot - 1) & 3];
+        ++seq;
+        if (tile > t_begin) {
+            const int now = tile_solver[tile];
+            if (now != solver) {                   // another solver: the block before is not this one's previous
+                solver = now;
+                clear_half((seq - 1) & 1);
+                seq += 2;                          // (the parity of the next number, the number before it unused)
+            }
+        }
+        // ---- 1. this block's entries; the next tile's are requested; lookups
+        request(sh.rows[(slot + 1) & 3], n_col, n_val);
+        RowLookup LB = LA;                         // two tiles ahead
+        if (wv == RESOLVER) {
+            lookup4(LB);
+            lookup1(LA, tile + 3, tile + 3 < t_end);
+        }
+        insert(R, seq);
+        __syncthreads();
+
+        // ---- 2. the products: popular columns on the matrix cores, the others along the chains
+        if (wv == RESOLVER) lookup2(LA);
+        const int cur = seq & 1, old = cur ^ 1;
+        // A 16 x 4 by 4 x 16 product takes A[l % 16][l / 16] and B[l / 16][l % 16] from lane l.  The tile is 8 x 4 blocks of
+        // 16 x 16 (jp, i); of the lower half those above the diagonal are zero.  Wavefront w takes block (w / 4, w % 4) of the
+        // upper half and the same of the lower.
+        const int bj = wv >> 2, bi = wv & 3;
+        floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        auto multiply = [&]() __attribute__((always_inline)) {
+            const float *pi = &sh.A[lane >> 4][cur * BATCH + 16 * bi + (lane & 15)];
+            const float *po = &sh.A[lane >> 4][cur * BATCH + 16 * bj + (lane & 15)];
+            const float *px = &sh.A[lane >> 4][old * BATCH + 16 * bj + (lane & 15)];
+#pragma unroll
+            for (int h = 0; h < GRAM_DENSE; h += 4) {
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(px[h * A_LD], pi[h * A_LD], acc[0], 0, 0, 0);
+                if (bj <= bi) acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(po[h * A_LD], pi[h * A_LD], acc[1], 0, 0, 0);
+            }
+        };
+        if (wv < GRAM_THREADS / 128) multiply();
+        // chains k < GRAM_EPT are in the entry's own block, the others in the previous one
 #pragma unroll
         for (int k = 0; k < GRAM_EPT; ++k) {
-            const int idx = tid + k * GRAM_THREADS;
-            const int s = idx / GRAM_MAX_ROW, p = idx - s * GRAM_MAX_ROW;
-            // (loads are unconditional: a row without entries points at readable dummy data and the store
-            // keeps slack behind every chunk; e_live masks them)
-            e_live[k] = p < R.len[s];
+            const unsigned slot = key[k] != NO_KEY ? sh.head[old][key[k] >> GRAM_REST_BITS] : 0u;
+            at[GRAM_EPT + k] = position(slot, seq - 1);
         }
-        if (tile + 1 < t_end) {
-            const GramRows &N = sh.rows[(slot + 1) % 3];
 #pragma unroll
-            for (int k = 0; k < HALF; ++k) {
-                const int idx = tid + (k + HALF) * GRAM_THREADS;
-                const int s = idx / GRAM_MAX_ROW, p = idx - s * GRAM_MAX_ROW;
-                n_col[k] = gld(N.col[s] + p); n_val[k] = gld(N.val[s] + p);
-            }
-        }
-        lookup1(tile + 2);
-        {
-            // 16-byte stores: keys <- EMPTY_KEY (all ones), start <- 0, A <- 0
-            uint4 *kq = reinterpret_cast<uint4 *>(sh.keys);
-            for (int i = tid; i < GRAM_SLOTS / 4; i += GRAM_THREADS) kq[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
-            uint4 *sq = reinterpret_cast<uint4 *>(sh.start);
-            for (int i = tid; i < GRAM_SLOTS / 8; i += GRAM_THREADS) sq[i] = make_uint4(0u, 0u, 0u, 0u);
-            uint4 *aq = reinterpret_cast<uint4 *>(&sh.d.A[0][0]);
-            for (int i = tid; i < GRAM_DENSE * TILE_W / 4; i += GRAM_THREADS) aq[i] = make_uint4(0u, 0u, 0u, 0u);
-        }
-        __syncthreads();
-
-        // ---- dense part into A, the rest into the hash table (count per slot)
-        int e_slot[GRAM_EPT], first[GRAM_EPT];
-#pragma unroll
-        for (int k = 0; k < GRAM_EPT; ++k) {       // first probes of all entries in flight together
-            const int idx = tid + k * GRAM_THREADS;
-            const int s = idx / GRAM_MAX_ROW;
-            e_slot[k] = -1; first[k] = EMPTY_KEY;
-            if (e_live[k]) {
-                if (e_col[k] < GRAM_DENSE) sh.d.A[e_col[k]][s] = e_val[k];
-                else {
-                    e_slot[k] = gram_hash(e_col[k]);
-                    first[k] = atomicCAS(&sh.keys[e_slot[k]], EMPTY_KEY, e_col[k]);
+        for (int k = GRAM_EPT - 1; k >= 0; --k) {
+            unsigned own = at[k], prev = at[GRAM_EPT + k];
+            const unsigned rest = key[k] & REST;
+            while (own != CHAIN_END || prev != CHAIN_END) {
+                GramEntry a = {CHAIN_END, 0.f}, b = a;
+                if (own != CHAIN_END) a = sh.entry[cur][own];
+                if (prev != CHAIN_END) b = sh.entry[old][prev];
+                if (own != CHAIN_END && a.rest_next >> GRAM_POS_BITS == rest) {
+                    const int j = (int)(own & (GRAM_THREADS - 1)) / GRAM_LPR;
+                    if (j != e_row) atomicAdd(&sh.Go[own_at(min(j, e_row), max(j, e_row))], (double)(e_val[k] * a.val));
                 }
+                if (prev != CHAIN_END && b.rest_next >> GRAM_POS_BITS == rest)
+                    atomicAdd(&sh.Gx[(int)(prev & (GRAM_THREADS - 1)) / GRAM_LPR][e_row], (double)(e_val[k] * b.val));
+                own = a.rest_next & CHAIN_END;
+                prev = b.rest_next & CHAIN_END;
             }
         }
-#pragma unroll
-        for (int k = 0; k < GRAM_EPT; ++k) {
-            if (e_slot[k] < 0) continue;
-            int h = e_slot[k], prev = first[k];
-            while (prev != EMPTY_KEY && prev != e_col[k]) {   // ends: fewer keys than slots are inserted
-                h = (h + 1) & (GRAM_SLOTS - 1);
-                prev = atomicCAS(&sh.keys[h], EMPTY_KEY, e_col[k]);
-            }
-            e_slot[k] = h;
-            // two 16-bit counters share a word
-            atomicAdd(reinterpret_cast<unsigned int *>(sh.start) + (h >> 1), (h & 1) ? 0x10000u : 1u);
-        }
-        lookup2();
+        if (wv >= GRAM_THREADS / 128) multiply();
         __syncthreads();
 
-        // ---- exclusive scan of the slot counts (8 slots per thread), cursors into keys[]
-        {
-            const int base = tid * (GRAM_SLOTS / GRAM_THREADS);
-            static_assert(GRAM_SLOTS / GRAM_THREADS == 8, "a thread's counts are one 16-byte word");
-            const uint4 packed = *reinterpret_cast<const uint4 *>(&sh.start[base]);
-            const unsigned pw[4] = {packed.x, packed.y, packed.z, packed.w};
-            int cnt[8], sum = 0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) { cnt[j] = (pw[j >> 1] >> ((j & 1) * 16)) & 0xffffu; sum += cnt[j]; }
-            int incl = sum;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int y = __shfl_up(incl, o, 64);
-                if ((tid & 63) >= o) incl += y;
-            }
-            if ((tid & 63) == 63) sh.scan[tid >> 6] = incl;
-            __syncthreads();
-            int off = incl - sum;
-            for (int w = 0; w < (tid >> 6); ++w) off += sh.scan[w];
-            int cur[8];
-            unsigned st[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                cur[j] = off;
-                st[j >> 1] |= (unsigned)off << ((j & 1) * 16);
-                off += cnt[j];
-            }
-            *reinterpret_cast<uint4 *>(&sh.start[base]) = make_uint4(st[0], st[1], st[2], st[3]);
-            *reinterpret_cast<int4 *>(&sh.keys[base]) = make_int4(cur[0], cur[1], cur[2], cur[3]);
-            *reinterpret_cast<int4 *>(&sh.keys[base + 4]) = make_int4(cur[4], cur[5], cur[6], cur[7]);
-        }
-        lookup3();
-        __syncthreads();
-
-        // ---- fill the posting lists
-#pragma unroll
-        for (int k = 0; k < GRAM_EPT; ++k)
-            if (e_slot[k] >= 0) {
-                const int pos = atomicAdd(&sh.keys[e_slot[k]], 1);
-                sh.post_val[pos] = e_val[k];
-                sh.post_row[pos] = (unsigned char)((tid + k * GRAM_THREADS) / GRAM_MAX_ROW);
-            }
-        // ---- dense part: G[jp][i] = sum_h A[h][jp] A[h][64 + i] on the matrix cores (fp32 in and out).  A
-        //      32 x 2 by 2 x 32 product takes A[l % 32][l / 32] and B[l / 32][l % 32] from lane l; wavefront
-        //      w < 8 owns the 32 x 32 block (jp block w / 2, i block w % 2).  The block of own rows 96..127
-        //      against rows 64..95 lies above the diagonal and is not needed.
-        {
-            typedef float floatx16 __attribute__((ext_vector_type(16)));
-            const int wv = tid >> 6, lane = tid & 63;
-            const int tj = wv >> 1, ti = wv & 1;
-            const bool mine = wv < 8 && !(tj == 3 && ti == 0);
-            floatx16 acc;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-            if (mine) {
-                const float *pa = &sh.d.A[lane >> 5][32 * tj + (lane & 31)];
-                const float *pb = &sh.d.A[lane >> 5][BATCH + 32 * ti + (lane & 31)];
-#pragma unroll 8
-                for (int h = 0; h < GRAM_DENSE; h += 2)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[h * TILE_W], pb[h * TILE_W], acc, 0, 0, 0);
-            }
-            lookup4();
-            __syncthreads();                 // every read of A is done: G may take its place
-            // result layout: register r of lane l is row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
-            if (wv < 8) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    sh.G[32 * tj + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)][32 * ti + (lane & 31)] = (double)acc[r];
-            }
-        }
-        __syncthreads();
-
-        // ---- sparse part: every entry of a block row meets the other members of its column's list
-#pragma unroll
-        for (int k = HALF; k < GRAM_EPT; ++k) {                  // positions of the block rows (64 .. 127)
-            if (e_slot[k] < 0) continue;
-            const int i = (tid + k * GRAM_THREADS) / GRAM_MAX_ROW - BATCH;
-            const float a = e_val[k];
-            const int pb = sh.start[e_slot[k]], pe = sh.keys[e_slot[k]];
-            for (int p = pb; p < pe; p += 4) {          // four list members per round of LDS latency
-                int sf[4];
-                float vf[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int pj = min(p + j, pe - 1);
-                    sf[j] = sh.post_row[pj]; vf[j] = sh.post_val[pj];
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (p + j < pe && (sf[j] < BATCH || sf[j] - BATCH < i)) atomicAdd(&sh.G[sf[j]][i], (double)(a * vf[j]));
-            }
-        }
-        publish(sh.rows[(slot + 2) % 3]);
-        __syncthreads();
-
-        // ---- scale and write out, coalesced over i (a thread's i is the same for all its values)
+        // ---- 3. summed, scaled and written out (result layout of a product: register r of lane l is row 4 (l / 16) + r, column
+        // l % 16); what the next tile adds into starts from zero
         {
             float *out = tiles + (int64_t)tile * TILE_FLOATS;
-            const int i = tid & 63;
-            const float si = R.scale[i] * R.sgn[BATCH + i];
+            const int i = 16 * bi + (lane & 15), j0 = 16 * bj + 4 * (lane >> 4);
+            const float si = R.scale[i] * R.sgn[i];
+            float4_v x, o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int k = 0; k < TILE_FLOATS / 4 / GRAM_THREADS; ++k) {
-                const int jq = (tid >> 6) + k * (GRAM_THREADS / 64);
-                float4_v v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int jp = 4 * jq + e;
-                    v[e] = jp < BATCH || jp - BATCH < i ? (float)sh.G[jp][i] * si * R.sgn[jp] : 0.f;
+            for (int e = 0; e < 4; ++e) {
+                x[e] = (float)(sh.Gx[j0 + e][i] + (double)acc[0][e]) * si * P.sgn[j0 + e];
+                sh.Gx[j0 + e][i] = 0.0;
+                if (j0 + e < i) {
+                    o[e] = (float)(sh.Go[own_at(j0 + e, i)] + (double)acc[1][e]) * si * R.sgn[j0 + e];
+                    sh.Go[own_at(j0 + e, i)] = 0.0;
                 }
-                *reinterpret_cast<float4_v *>(out + tile_at(4 * jq, i)) = v;
             }
+            *reinterpret_cast<float4_v *>(out + tile_at(j0, i)) = x;
+            *reinterpret_cast<float4_v *>(out + tile_at(BATCH + j0, i)) = o;
         }
-        // this tile's own rows are the next tile's previous block; its own rows have arrived by now
+        clear_half((seq + 1) & 1);
+        if (wv == RESOLVER) {
+            publish(LB, sh.rows[(slot + 2) & 3]);
+            lookup3(LA);
+        }
 #pragma unroll
-        for (int k = 0; k < HALF; ++k) {
-            e_col[k] = e_col[k + HALF]; e_val[k] = e_val[k + HALF];
-            e_col[k + HALF] = n_col[k]; e_val[k + HALF] = n_val[k];
-        }
-        __syncthreads();     // G has been read: the next tile may clear A, which lies inside it
+        for (int k = 0; k < GRAM_EPT; ++k) { e_col[k] = n_col[k]; e_val[k] = n_val[k]; }
+        __syncthreads();
     }
 }
+static_assert(GRAM_THREADS == 64 * 16, "a wavefront per 16 x 16 block of either half of the tile");
 
 // Fill row_chunk for one (solver, chunk) list entry per workgroup.
 __global__ __launch_bounds__(256) void fill_row_chunk(const ChunkDev *__restrict__ chunks,
