@@ -24,6 +24,7 @@
 #include "sdca_batched.hpp"
 #include "sdca_batched_split.hpp"
 #include "sdca_dense.hpp"
+#include "sdca_dense_affine.hpp"
 #include "sdca_rowwise.hpp"
 #include "sdca_rowwise_cluster.hpp"
 #include "sdca_sparse_blocks.hpp"
@@ -592,6 +593,42 @@ int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, bool ahead, hipStre
     return CHICLE_OK;
 }
 
+// Rows per run of the solver for long passes over narrow dense rows (sdca_dense_affine.hpp); 0: it does not take this pass.
+// It saves 0.75 us per block of 64 rows of the longest solver and costs the pass three more kernels and one run's latency.
+// Whole rounds, solved blocks / runs of 64 rows, us: one solver of 1000 rows of 16 columns 52 / 55, of 4096 of 10 101 / 67
+// (orders announced 90 / 70), one in four of 1024 rows of 32 53 / 69, of 2048 75 / 70 (62 / 71), of 8192 168 / 88 (154 / 92).
+// Runs of 128 rows halve the chain where it is long, but each then takes its latency twice: one in eight of 25 000 rows of 32
+// columns 163 with runs of 64, 150 with 128; one in four of 8192 88 and 102.
+int affine_run(const chicle_ctx *c)
+{
+    if (!c->dense || c->loss != CHICLE_LOSS_SQUARED || c->d > AFFINE_MAX_D || c->K > 65535) return 0;      // (a grid's second dimension)
+    const int blocks = (c->most_rows + BATCH - 1) / BATCH;
+    return blocks < 48 ? 0 : blocks < 256 ? BATCH : 2 * BATCH;
+}
+
+int launch_affine(chicle_ctx *c, const int32_t *perm, int run)
+{
+    const RoundScalars sc = scalars(c);
+    float *tiles = c->tiles[c->tile_buf];
+    constexpr int per = AFFINE_UNITS * AFFINE_WAVES;
+    const dim3 grid(((c->most_rows + run - 1) / run + per - 1) / per, c->K);
+    const int d = (int)c->d;
+    seg_begin(c, CHICLE_SEG_EPOCH_GRAM);
+    static_assert(AFFINE_MAX_D == 32, "all row lengths of affine_maps");
+    auto maps = d <= 4 ? affine_maps<4> : d <= 8 ? affine_maps<8> : d <= 12 ? affine_maps<12> : d <= 16 ? affine_maps<16>
+                : d <= 20 ? affine_maps<20> : d <= 24 ? affine_maps<24> : d <= 28 ? affine_maps<28> : affine_maps<32>;
+    hipLaunchKernelGGL(maps, grid, dim3(64 * AFFINE_WAVES), 0, c->stream, c->chunks_dev, c->solvers_dev, c->row_chunk_dev, c->chunk_first_dev, perm,
+                       tiles, run, sc.c, sc.inv_c, c->err_dev);
+    seg_end(c, CHICLE_SEG_EPOCH_GRAM);
+    seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
+    auto starts = d <= 8 ? affine_starts<1> : d <= 16 ? affine_starts<2> : d <= 24 ? affine_starts<3> : affine_starts<4>;
+    hipLaunchKernelGGL(starts, dim3(c->K), dim3(64), 0, c->stream, c->solvers_dev, tiles, c->u, c->ld_v, d, run, sc);
+    hipLaunchKernelGGL(affine_steps, grid, dim3(64 * AFFINE_WAVES), 0, c->stream, c->chunks_dev, c->solvers_dev, tiles, run, dense_ld(d), sc);
+    seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
+    HIP_TRY(c, hipGetLastError());
+    return CHICLE_OK;
+}
+
 // The batched local pass.  Tiles of `perm` come from the set prepared ahead when there is one (the main stream has
 // waited for it), else they are computed first on the main stream.  With perm_next, the tiles of the next pass are started
 // on the side stream so that they run beside this pass's chain kernel (which occupies K of the 256
@@ -601,6 +638,7 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
 {
     const RoundScalars sc = scalars(c);
     int rc;
+    if (const int run = affine_run(c)) return launch_affine(c, perm, run);
     if (tiles_ready) {
         c->tile_buf = 1 - c->tile_buf;
     } else {
@@ -1527,7 +1565,7 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
         c->ahead_buf = 1 - c->ahead_buf;
         c->ahead_valid = true;
     }
-    if (route == ROUTE_DENSE && !dense_tiles_ahead(c)) perm_next_device = nullptr;      // (they are kept all the same)
+    if (route == ROUTE_DENSE && (affine_run(c) || !dense_tiles_ahead(c))) perm_next_device = nullptr;      // (they are kept all the same)
     seg_begin(c, CHICLE_SEG_LOCAL_EPOCH);
     int rc = CHICLE_OK;
     if (!c->zw_valid) rc = run_row_pass(c, nullptr, c->gap_scratch);     // x_i . w for the current w
