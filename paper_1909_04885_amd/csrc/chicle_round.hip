@@ -473,6 +473,22 @@ bool solve_tiles(const chicle_ctx *c, bool ahead)
     return ahead ? c->K <= 64 && blocks >= 16 + c->K : (int64_t)blocks * (34 - c->K) > 1200;
 }
 
+// Rows per run of the solver for long passes over narrow dense rows (sdca_dense_affine.hpp); 0: it does not take this pass.
+// It saves 0.7 us per block of 64 rows of the longest solver and costs the pass a kernel more, one run's latency and, over all
+// solvers' rows, 0.1 ns per row and column.  Whole rounds, solved blocks / runs of 64 rows, us: one solver of 1000 rows of 16
+// columns 52 / 55, of 4096 of 10 101 / 60, one in four of 1024 rows of 32 53 / 69, of 2048 75 / 70, of 3075 92 / 76, of 8192
+// 168 / 101, one in 64 of 3073 of 28 154 / 130, one in 256 of 3072 of 32 376 / 327, of 8 327 / 211.
+// Longer runs shorten the chain, and fewer maps have to be stored, but each then takes its latency several times.  Runs of 64
+// and of 128: one solver of 16384 rows of 28 columns 114 and 113, of 8192 of 32 93 and 104, one in eight of 16250 of 28 147 and
+// 133, one in 16 of 6250 of 32 110 and 119, one in 64 of 6250 of 28 191 and 178.  Of 128 and of 256: one in 16 of 31250 of 28
+// 224 and 210, one in four of 125000 394 and 294, one in two of 250000 623 and 410.
+int affine_run(const chicle_ctx *c)
+{
+    if (!c->dense || c->loss != CHICLE_LOSS_SQUARED || c->d > AFFINE_MAX_D || c->K > 65535) return 0;      // (a grid's second dimension)
+    const int blocks = (c->most_rows + BATCH - 1) / BATCH;
+    return blocks < 48 ? 0 : blocks < 192 && c->n_tiles < 4096 ? BATCH : blocks < 400 ? 2 * BATCH : 4 * BATCH;
+}
+
 // Whether the tiles of announced orders are formed ahead for dense rows.  The second stream costs a round about 20 us of
 // calls, which hide only behind a pass that is long enough: rounds of four solvers of 64 rows of 64 columns 33 us without, 56
 // with; of 1024 rows 56 and 59, of 256 columns 68 and 64, of 1000 columns 129 and 111; 64 solvers of 512 rows of 64 columns
@@ -593,37 +609,28 @@ int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, bool ahead, hipStre
     return CHICLE_OK;
 }
 
-// Rows per run of the solver for long passes over narrow dense rows (sdca_dense_affine.hpp); 0: it does not take this pass.
-// It saves 0.75 us per block of 64 rows of the longest solver and costs the pass three more kernels and one run's latency.
-// Whole rounds, solved blocks / runs of 64 rows, us: one solver of 1000 rows of 16 columns 52 / 55, of 4096 of 10 101 / 67
-// (orders announced 90 / 70), one in four of 1024 rows of 32 53 / 69, of 2048 75 / 70 (62 / 71), of 8192 168 / 88 (154 / 92).
-// Runs of 128 rows halve the chain where it is long, but each then takes its latency twice: one in eight of 25 000 rows of 32
-// columns 163 with runs of 64, 150 with 128; one in four of 8192 88 and 102.
-int affine_run(const chicle_ctx *c)
-{
-    if (!c->dense || c->loss != CHICLE_LOSS_SQUARED || c->d > AFFINE_MAX_D || c->K > 65535) return 0;      // (a grid's second dimension)
-    const int blocks = (c->most_rows + BATCH - 1) / BATCH;
-    return blocks < 48 ? 0 : blocks < 256 ? BATCH : 2 * BATCH;
-}
-
 int launch_affine(chicle_ctx *c, const int32_t *perm, int run)
 {
     const RoundScalars sc = scalars(c);
     float *tiles = c->tiles[c->tile_buf];
-    constexpr int per = AFFINE_UNITS * AFFINE_WAVES;
-    const dim3 grid(((c->most_rows + run - 1) / run + per - 1) / per, c->K);
-    const int d = (int)c->d;
+    const int units = (c->most_rows + run - 1) / run, d = (int)c->d;
+    auto grid = [&](int lanes) {                       // lanes per run
+        const int per = 64 / lanes * AFFINE_WAVES;
+        return dim3((units + per - 1) / per, c->K);
+    };
     seg_begin(c, CHICLE_SEG_EPOCH_GRAM);
     static_assert(AFFINE_MAX_D == 32, "all row lengths of affine_maps");
-    auto maps = d <= 4 ? affine_maps<4> : d <= 8 ? affine_maps<8> : d <= 12 ? affine_maps<12> : d <= 16 ? affine_maps<16>
-                : d <= 20 ? affine_maps<20> : d <= 24 ? affine_maps<24> : d <= 28 ? affine_maps<28> : affine_maps<32>;
-    hipLaunchKernelGGL(maps, grid, dim3(64 * AFFINE_WAVES), 0, c->stream, c->chunks_dev, c->solvers_dev, c->row_chunk_dev, c->chunk_first_dev, perm,
-                       tiles, run, sc.c, sc.inv_c, c->err_dev);
+    auto maps = d <= 4 ? affine_maps<4, 16, true> : d <= 8 ? affine_maps<8, 16, true> : d <= 12 ? affine_maps<12, 16, true>
+                : d < 16 ? affine_maps<16, 16, true> : d <= 16 ? affine_maps<16, 32, true> : d <= 20 ? affine_maps<20, 32, true>
+                : d <= 24 ? affine_maps<24, 32, true> : d <= 28 ? affine_maps<28, 32, true> : d < 32 ? affine_maps<32, 32, true>
+                : affine_maps<32, 32, false>;
+    hipLaunchKernelGGL(maps, grid(d < 16 ? 16 : 32), dim3(64 * AFFINE_WAVES), 0, c->stream, c->chunks_dev, c->solvers_dev, c->row_chunk_dev, c->chunk_first_dev, perm,
+                       tiles, d, run, sc.c, sc.inv_c, c->err_dev);
     seg_end(c, CHICLE_SEG_EPOCH_GRAM);
     seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
     auto starts = d <= 8 ? affine_starts<1> : d <= 16 ? affine_starts<2> : d <= 24 ? affine_starts<3> : affine_starts<4>;
     hipLaunchKernelGGL(starts, dim3(c->K), dim3(64), 0, c->stream, c->solvers_dev, tiles, c->u, c->ld_v, d, run, sc);
-    hipLaunchKernelGGL(affine_steps, grid, dim3(64 * AFFINE_WAVES), 0, c->stream, c->chunks_dev, c->solvers_dev, tiles, run, dense_ld(d), sc);
+    hipLaunchKernelGGL(affine_steps, grid(AFFINE_GROUP), dim3(64 * AFFINE_WAVES), 0, c->stream, c->chunks_dev, c->solvers_dev, tiles, run, dense_ld(d), sc);
     seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
     HIP_TRY(c, hipGetLastError());
     return CHICLE_OK;

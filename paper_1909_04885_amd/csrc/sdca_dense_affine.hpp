@@ -6,17 +6,24 @@
 //   affine_maps    P and b of every run of rows, on the whole chip: P' = P - s x (x'P), b' = b + s (k - x.b) x;
 //   affine_starts  one wavefront per solver: the private vector before every run and after the last, a d x d product per run;
 //   affine_steps   every run's steps one row after the other from its own start, on the whole chip: the new alphas.
-// Only the second kernel is a chain, of some 440 cycles per run of 128 rows; blocks of 64 rows solved by their inverse took
-// 2.2e3 (see sdca_dense_squared).  The first is bound by its multiply-adds (2 d^2 per row, of rank one updates that depend on
-// each other), the third by the dozen dependent instructions of a row.  500000 x 28, 16 solvers, a pass: 57 + 50
-// + 38 us (450 before); fifty rounds 28.2 -> 9.96 ms.
-// Precision: dot products and P are fp32; b, the starts, the private vector inside a run and the diagonal of 1 - P are summed
-// in double (P's own would round what a weak run does to its v relative to v).  The solver's update is the vector after the
-// last run, not a sum over the runs: an error in the vector shrinks with every row after it, one in a run's share would stay.
-// Errors against 64 bits, 80 jobs of 3500 to 60000 rows of 2 to 32 columns, lambda n from 0.1 to 100, three rounds, geometric
-// mean of now / blocks solved by their inverse: updates 0.88, alpha 0.91, w 0.94.  (Updates as sums over runs, or 1 - P in place
-// of P, came to 10 times as much; without the diagonal's sum in double 1.1.  Products P v in double changed nothing and took
-// 20 us more.)
+// Only the second kernel is a chain, of some 600 cycles per run; blocks of 64 rows solved by their inverse took 2.2e3 each (see
+// sdca_dense_squared).  The first is bound by its multiply-adds (2 d^2 per row in double, of rank one updates that depend on
+// each other), the third by the dozen dependent instructions of a row.  500000 x 28, 16 solvers, a pass in runs of 256 rows:
+// 86 + 33 + 47 us (450 in blocks); fifty rounds 28.2 -> 10.8 ms.
+// Precision: all is in double but what is stored (alpha, the solver's update, the rows and their state).  The update is the
+// vector after the last run, not a sum over the runs: an error in the vector shrinks with every row after it, one in a run's
+// share would stay.  It is not formed from the stored alphas, so that whatever either is off by parts w from the sum of the
+// alphas' rows: with P and the dot products in float (57 + 50 + 38 us in runs of 128 rows, 9.9 ms) by 6e-7 of w after one
+// round, here by 4e-8, the rounding of what is stored (blocks: 7e-8).
+// Errors against 64 bits over those of blocks solved by their inverse, updates and alpha, geometric means of eight jobs each of
+// 3500 to 40000 rows, three rounds (with P and the dot products in float up to 1.33 and 1.06, for lambda n from 10 on):
+//   columns  lambda n: 0.1        1            10           50           100
+//    2             0.21 0.15    0.24 0.18    0.57 0.30    0.48 0.37    0.72 0.41
+//    8             0.20 0.16    0.38 0.17    0.45 0.23    0.56 0.30    0.60 0.33
+//   17             0.27 0.17    0.35 0.18    0.42 0.22    0.53 0.27    0.56 0.30
+//   24             0.33 0.18    0.34 0.19    0.47 0.24    0.57 0.27    0.59 0.31
+//   28             0.28 0.18    0.35 0.19    0.48 0.23    0.55 0.28    0.62 0.31
+//   32             0.29 0.19    0.35 0.20    0.45 0.25    0.53 0.28    0.64 0.31
 #pragma once
 #include <hip/hip_runtime.h>
 #include "device_types.hpp"
@@ -28,15 +35,14 @@ namespace chicle {
 typedef float float2_v __attribute__((ext_vector_type(2)));
 
 constexpr int AFFINE_MAX_D = 32;
-constexpr int AFFINE_GROUP = 16;                 // rows in flight per run
-constexpr int AFFINE_UNITS = 4;                  // runs per wavefront: 16 lanes each, two columns per lane
-// Wavefronts per workgroup, each on its own: one per SIMD (workgroups of one wavefront: affine_maps 70 us for 55).
+constexpr int AFFINE_GROUP = 16;                 // affine_steps: lanes per run, two columns each, and rows in flight per run
+constexpr int AFFINE_UNITS = 64 / AFFINE_GROUP;  // ... and runs per wavefront
+// Wavefronts per workgroup, each on its own: one per SIMD (workgroups of one wavefront: affine_maps with P in float 70 us for 55).
 constexpr int AFFINE_WAVES = 4;
-// A run's place is the first of the tiles its rows have (their addresses stay with their tiles): P[k][m], zero for k = m, at
-// [m / 4][k][m % 4], then vectors of 32 doubles: b, the diagonal of 1 - P, the start; and words that nobody reads.
-constexpr int AFFINE_B = AFFINE_MAX_D * AFFINE_MAX_D, AFFINE_DIAG = AFFINE_B + 64, AFFINE_START = AFFINE_DIAG + 64,
-              AFFINE_SINK = AFFINE_START + 64;
-static_assert(AFFINE_SINK + 64 <= BATCH * BATCH, "before the rows' addresses");
+// A run's place is the first of the tiles its rows have (their addresses stay with their tiles), in doubles: P - 1 at
+// [m / 2][k][m % 2] for row k and column m, then vectors of 32: b, the start; then words that nobody reads.
+constexpr int AFFINE_B = AFFINE_MAX_D * AFFINE_MAX_D, AFFINE_START = AFFINE_B + AFFINE_MAX_D, AFFINE_SINK = AFFINE_START + AFFINE_MAX_D;
+static_assert(2 * (AFFINE_SINK + 64) <= BATCH * BATCH, "before the rows' addresses");
 static_assert(DENSE_TILE_FLOATS % 4 == 0, "16-byte aligned places");
 typedef double double2_v __attribute__((ext_vector_type(2)));
 
@@ -47,46 +53,58 @@ __device__ __forceinline__ void wave_lds_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
-// Sum over 16 lanes, in all of them.
-__device__ __forceinline__ float sum16(float v)
+// The value of another lane, by a data-parallel-primitive move.
+template <int CTRL>
+__device__ __forceinline__ double of_lane(double v)
 {
-#define CHICLE_DPP_ADD(ctrl) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xF, 0xF, true))
-    CHICLE_DPP_ADD(0xB1);                        // lanes xor 1, xor 2, then mirrored halves and rows
-    CHICLE_DPP_ADD(0x4E);
-    CHICLE_DPP_ADD(0x141);
-    CHICLE_DPP_ADD(0x140);
-#undef CHICLE_DPP_ADD
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true));
+}
+constexpr int DPP_LANE_OF_16 = 0x150;            // + r: lane r of each 16
+// Sum over 16 lanes, in all of them: lanes xor 1, xor 2, then mirrored halves and rows.
+__device__ __forceinline__ double sum16(double v)
+{
+    v += of_lane<0xB1>(v);
+    v += of_lane<0x4E>(v);
+    v += of_lane<0x141>(v);
+    v += of_lane<0x140>(v);
     return v;
 }
-// The value of lane R of each 16.
-template <int R>
-__device__ __forceinline__ float of_lane16(float v)
+// ... over 32 lanes: the other 16 by a swap.
+__device__ __forceinline__ double sum32(double v)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + R, 0xF, 0xF, true));
+    v = sum16(v);
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
 }
+// What a row's step is scaled with: c / (c + q), in double (in float it would err by as much as the rounded result).
+__device__ __forceinline__ double affine_scale(float q, float c) { return (double)c / ((double)c + (double)q); }
 
-// Grid: (groups of 16 runs, solver), four runs per wavefront.  A lane holds two columns of its run's P in registers; rows come
-// through LDS, where 16 lanes read the same words.  The lookups (order entry -> chunk -> row) are four groups deep, so that
-// each group's loads have a group's arithmetic to return in.  DK: columns, rounded up to four.
-template <int DK>
+// Grid: (groups of runs, solver), LANES lanes per run.  A lane holds one column of its run's P in registers; rows come through
+// LDS, where a run's lanes read the same words.  The lookups (order entry -> chunk -> row) are four groups of LANES rows deep,
+// so that each group's loads have a group's arithmetic to return in.  DK: columns, rounded up to four.
+// SPARE: a run has more lanes than a row has columns, and the one after the last holds b as a column of its own (a row without
+// a column there leaves P's as it is), so that no sum over lanes stands in the chain from row to row.
+template <int DK, int LANES, bool SPARE>
 __global__ __launch_bounds__(64 * AFFINE_WAVES) void affine_maps(
     const ChunkDev *__restrict__ chunks, const SolverDev *__restrict__ solvers, const int32_t *__restrict__ row_chunk,
-    const int32_t *__restrict__ chunk_first, const int32_t *__restrict__ perm, float *tiles, int run, float c, float inv_c, int *err)
+    const int32_t *__restrict__ chunk_first, const int32_t *__restrict__ perm, float *tiles, int d, int run, float c, float inv_c, int *err)
 {
-    constexpr int Q = DK / 4, LDR = AFFINE_MAX_D + 4, LDU = AFFINE_GROUP * LDR + 4;      // (runs and rows on other banks)
-    __shared__ __align__(16) float sh_x[AFFINE_WAVES][AFFINE_UNITS * LDU];
-    __shared__ __align__(16) float sh_sk[AFFINE_WAVES][AFFINE_UNITS][AFFINE_GROUP][2];
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), first = ((int)blockIdx.x * AFFINE_WAVES + wv) * AFFINE_UNITS;
-    float *s_x = sh_x[wv];
+    constexpr int Q = DK / 4, LDR = AFFINE_MAX_D + 2, LDU = LANES * LDR + 2, UNITS = 64 / LANES;      // (runs and rows on other banks)
+    __shared__ __align__(16) double sh_x[AFFINE_WAVES][UNITS * LDU];
+    __shared__ __align__(16) double sh_sk[AFFINE_WAVES][UNITS][LANES][2];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), first = ((int)blockIdx.x * AFFINE_WAVES + wv) * UNITS;
+    double *s_x = sh_x[wv];
     auto &s_sk = sh_sk[wv];
     const SolverDev S = solvers[blockIdx.y];
     const int units = (S.n_rows + run - 1) / run;
     if (first >= units) return;
-    const int lane = threadIdx.x & 63, m = lane & 15, un = lane >> 4, unit = first + un;
-    const int t0 = unit * run + m, groups = run / AFFINE_GROUP, tile_rows = (S.n_rows + BATCH - 1) / BATCH * BATCH;
+    const int lane = threadIdx.x & 63, m = lane & (LANES - 1), un = lane / LANES, unit = first + un;
+    const int t0 = unit * run + m, groups = run / LANES, tile_rows = (S.n_rows + BATCH - 1) / BATCH * BATCH;
     const int my_rows = unit < units ? S.n_rows : 0;
     float *tile0 = tiles + (int64_t)S.tile_begin * DENSE_TILE_FLOATS;
-    float *out = tile0 + (int64_t)min(unit, units - 1) * (run / BATCH) * DENSE_TILE_FLOATS;
+    double *out = reinterpret_cast<double *>(tile0 + (int64_t)min(unit, units - 1) * (run / BATCH) * DENSE_TILE_FLOATS);
     // No load or store stands behind a condition (the compiler would wait for all that are in flight), and what a load
     // returns is first looked at a group later: rows that do not exist look up a row that does.
     struct Order { int lr; bool ok; };
@@ -94,7 +112,7 @@ __global__ __launch_bounds__(64 * AFFINE_WAVES) void affine_maps(
     struct Place { const float *val; RowState *st; int first, lr; bool ok; };
     bool refused = false;
     auto order = [&](int g) __attribute__((always_inline)) {
-        const int t = t0 + g * AFFINE_GROUP;
+        const int t = t0 + g * LANES;
         return Order{perm[S.perm_off + min(t, S.n_rows - 1)], (bool)((g < groups) & (t < my_rows))};
     };
     auto chunk_of = [&](Order o) __attribute__((always_inline)) {
@@ -116,29 +134,31 @@ __global__ __launch_bounds__(64 * AFFINE_WAVES) void affine_maps(
         for (int q = 0; q < Q; ++q) x_in[q] = *(const CHICLE_GLOBAL float4_v *)(row.x + 4 * q);
         st_in = gld_state(row.st);
     };
-    for (int i = lane; i < AFFINE_UNITS * LDU; i += 64) s_x[i] = 0.f;       // (columns past the row's end stay zero)
+    for (int i = lane; i < UNITS * LDU; i += 64) s_x[i] = 0.0;       // (columns past the row's end stay zero)
     fetch(place_of(chunk_of(order(0))));
     Place next = place_of(chunk_of(order(1)));
     Chunk far = chunk_of(order(2));
     Order farther = order(3);
-    float P0[DK], P1[DK];                        // P[k][2m], P[k][2m + 1]
+    const bool holds_b = SPARE && m == d;
+    double P[DK], b = 0.0;                       // P[k][m], b[m] (SPARE: b[k] in P[k] of lane d)
 #pragma unroll
-    for (int k = 0; k < DK; ++k) { P0[k] = k == 2 * m ? 1.f : 0.f; P1[k] = k == 2 * m + 1 ? 1.f : 0.f; }
-    double b0 = 0.0, b1 = 0.0, a0 = 0.0, a1 = 0.0;      // a: the diagonal of 1 - P
-    float *mine = s_x + un * LDU;
+    for (int k = 0; k < DK; ++k) P[k] = k == m && !holds_b ? 1.0 : 0.0;
+    double *mine = s_x + un * LDU;
     wave_lds_fence();
     for (int g = 0; g < groups; ++g) {
         {
             const bool live = row_ok & takes_steps(st_in.z);
 #pragma unroll
-            for (int q = 0; q < Q; ++q) *reinterpret_cast<float4_v *>(mine + m * LDR + 4 * q) = live ? x_in[q] : float4_v{0.f, 0.f, 0.f, 0.f};
-            const float s = (c / (c + st_in.z)) * inv_c;
-            s_sk[un][m][0] = live ? s : 0.f;
-            s_sk[un][m][1] = live ? st_in.w - st_in.y : 0.f;
-            const int t = t0 + g * AFFINE_GROUP;
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; e += 2)
+                    *reinterpret_cast<double2_v *>(mine + m * LDR + 4 * q + e) = double2_v{live ? x_in[q][e] : 0.f, live ? x_in[q][e + 1] : 0.f};
+            const double s = affine_scale(st_in.z, c) * (double)inv_c, k = (double)st_in.w - (double)st_in.y;
+            *reinterpret_cast<double2_v *>(&s_sk[un][m][0]) = live ? double2_v{s, k} : double2_v{0.0, 0.0};
+            const int t = t0 + g * LANES;
             // (a tile's rows past the end too: they take no step)
-            float *tile = unit * run + g * AFFINE_GROUP < tile_rows ? tile0 + (int64_t)(t / BATCH) * DENSE_TILE_FLOATS + BATCH * BATCH + 4 * (t % BATCH)
-                                                                    : out + AFFINE_SINK + 4 * m;
+            float *tile = unit * run + g * LANES < tile_rows ? tile0 + (int64_t)(t / BATCH) * DENSE_TILE_FLOATS + BATCH * BATCH + 4 * (t % BATCH)
+                                                                    : reinterpret_cast<float *>(out + AFFINE_SINK + 2 * m);
             const DenseRow kept = {row.x, live ? row.st : nullptr};
             *(CHICLE_GLOBAL float4_v *)tile = __builtin_bit_cast(float4_v, kept);
         }
@@ -147,89 +167,80 @@ __global__ __launch_bounds__(64 * AFFINE_WAVES) void affine_maps(
         far = chunk_of(farther);
         farther = order(g + 4);
         wave_lds_fence();
-        // (a row's words are read during the arithmetic of the row before it)
-        struct Words { float4_v x[Q]; float2_v xm, sk; };
+        struct Words { double2_v x[DK / 2], sk; double xm; };
         auto read = [&](int r) __attribute__((always_inline)) {
             Words w;
 #pragma unroll
-            for (int q = 0; q < Q; ++q) w.x[q] = *reinterpret_cast<const float4_v *>(mine + r * LDR + 4 * q);
-            w.xm = *reinterpret_cast<const float2_v *>(mine + r * LDR + 2 * m);
-            w.sk = *reinterpret_cast<const float2_v *>(&s_sk[un][r][0]);
+            for (int q = 0; q < DK / 2; ++q) w.x[q] = *reinterpret_cast<const double2_v *>(mine + r * LDR + 2 * q);
+            w.xm = SPARE ? 0.0 : mine[r * LDR + m];
+            w.sk = *reinterpret_cast<const double2_v *>(&s_sk[un][r][0]);
             return w;
         };
         auto add_row = [&](const Words &w) __attribute__((always_inline)) {
-            const float4_v (&x)[Q] = w.x;
-            const float2_v xm = w.xm, sk = w.sk;
-            float d0[2] = {0.f, 0.f}, d1[2] = {0.f, 0.f};
+            double t[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int k = 0; k < DK; ++k) {
-                d0[k & 1] = fmaf(x[k >> 2][k & 3], P0[k], d0[k & 1]);
-                d1[k & 1] = fmaf(x[k >> 2][k & 3], P1[k], d1[k & 1]);
-            }
-            const float n0 = -sk.x * (d0[0] + d0[1]), n1 = -sk.x * (d1[0] + d1[1]);
-            const float p = sk.x * (sk.y - sum16(fmaf(xm.x, (float)b0, xm.y * (float)b1)));
+            for (int k = 0; k < DK; ++k) t[k & 3] = fma(w.x[k >> 1][k & 1], P[k], t[k & 3]);
+            const double n = w.sk.x * ((holds_b ? w.sk.y : 0.0) - ((t[0] + t[1]) + (t[2] + t[3])));
+            if (!SPARE) b = fma(w.xm, w.sk.x * (w.sk.y - sum32(w.xm * b)), b);
 #pragma unroll
-            for (int k = 0; k < DK; ++k) {
-                P0[k] = fmaf(x[k >> 2][k & 3], n0, P0[k]);
-                P1[k] = fmaf(x[k >> 2][k & 3], n1, P1[k]);
-            }
-            a0 = fma((double)xm.x, (double)-n0, a0);
-            a1 = fma((double)xm.y, (double)-n1, a1);
-            b0 = fma((double)xm.x, (double)p, b0);
-            b1 = fma((double)xm.y, (double)p, b1);
+            for (int k = 0; k < DK; ++k) P[k] = fma(w.x[k >> 1][k & 1], n, P[k]);
         };
-        Words even = read(0);
-        for (int r = 0; r < AFFINE_GROUP; r += 2) {
-            const Words odd = read(r + 1);
-            __builtin_amdgcn_sched_barrier(0);   // (or all reads are put first, and waited for)
-            add_row(even);
-            __builtin_amdgcn_sched_barrier(0);
-            even = read(min(r + 2, AFFINE_GROUP - 1));
-            __builtin_amdgcn_sched_barrier(0);
-            add_row(odd);
-            __builtin_amdgcn_sched_barrier(0);
+        // One wavefront per SIMD reads a row's words during the arithmetic of the row before it; two of them hide each other's
+        // reads, and a second set of words would take the registers that the second one needs.
+        if (LANES == 16) {
+            Words even = read(0);
+            for (int r = 0; r < LANES; r += 2) {
+                const Words odd = read(r + 1);
+                __builtin_amdgcn_sched_barrier(0);   // (or all reads are put first, and waited for)
+                add_row(even);
+                __builtin_amdgcn_sched_barrier(0);
+                even = read(min(r + 2, LANES - 1));
+                __builtin_amdgcn_sched_barrier(0);
+                add_row(odd);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            for (int r = 0; r < LANES; ++r) add_row(read(r));
         }
-        // the diagonal anew from its sum in double: beside the ones of a weak run, every row's rounding stays in it
-        const float p0 = (float)(1.0 - a0), p1 = (float)(1.0 - a1);
-#pragma unroll
-        for (int k = 0; k < DK; ++k) { P0[k] = k == 2 * m ? p0 : P0[k]; P1[k] = k == 2 * m + 1 ? p1 : P1[k]; }
         wave_lds_fence();
     }
     if (refused) atomicOr(err, ERR_PERM_RANGE);
     if (unit >= units) return;
 #pragma unroll
-    for (int k = 0; k < DK; ++k)
-        *(CHICLE_GLOBAL float2_v *)(out + ((m >> 1) * AFFINE_MAX_D + k) * 4 + (m & 1) * 2) = float2_v{k == 2 * m ? 0.f : P0[k], k == 2 * m + 1 ? 0.f : P1[k]};
-    *(CHICLE_GLOBAL double2_v *)(out + AFFINE_B + 4 * m) = double2_v{b0, b1};
-    *(CHICLE_GLOBAL double2_v *)(out + AFFINE_DIAG + 4 * m) = double2_v{a0, a1};
+    for (int k = 0; k < DK; ++k) {
+        *(CHICLE_GLOBAL double *)(out + ((m >> 1) * AFFINE_MAX_D + k) * 2 + (m & 1)) = holds_b ? 0.0 : k == m ? P[k] - 1.0 : P[k];
+        if (holds_b) *(CHICLE_GLOBAL double *)(out + AFFINE_B + k) = P[k];
+    }
+    if (!SPARE) *(CHICLE_GLOBAL double *)(out + AFFINE_B + m) = b;
 }
 
-// Grid: one wavefront per solver.  Lane: row of P, and half of the columns (four Q of them).  The maps of eight runs are in
+// Grid: one wavefront per solver.  Lane: row of P, and half of the columns (four Q of them).  The maps of SETS runs are in
 // flight.
 template <int Q>
 __global__ __launch_bounds__(64) void affine_starts(const SolverDev *__restrict__ solvers, float *tiles, float *u_all,
                                                     int64_t ld_v, int d, int run, RoundScalars sc)
 {
-    constexpr int SETS = 8;
-    __shared__ __align__(16) float s_v[AFFINE_MAX_D];
+    constexpr int SETS = 6;
+    __shared__ __align__(16) double s_v[AFFINE_MAX_D];
     const SolverDev S = solvers[blockIdx.x];
     stamp_solver(sc, 0);
     const int units = (S.n_rows + run - 1) / run;
     const int lane = threadIdx.x, i = lane & 31, h = lane >> 5;
     const int64_t stride = (int64_t)(run / BATCH) * DENSE_TILE_FLOATS;
     float *place = tiles + (int64_t)S.tile_begin * DENSE_TILE_FLOATS;
-    double v = i < d ? (double)u_all[(int64_t)blockIdx.x * ld_v + i] : 0.0;
-    float4_v P[SETS][Q];
-    double b[SETS], a[SETS];
+    auto place_of = [&](int at) __attribute__((always_inline)) { return reinterpret_cast<double *>(place + min(at, units - 1) * stride); };
+    const bool has = i < d;
+    double v = has ? (double)u_all[(int64_t)blockIdx.x * ld_v + i] : 0.0;
+    double2_v P[SETS][2 * Q];
+    double b[SETS];
     auto load = [&](int s, int at) __attribute__((always_inline)) {
-        const float *p = place + min(at, units - 1) * stride;
+        const double *p = place_of(at);
 #pragma unroll
-        for (int e = 0; e < Q; ++e) P[s][e] = *(const CHICLE_GLOBAL float4_v *)(p + ((h * Q + e) * AFFINE_MAX_D + i) * 4);
-        b[s] = *(const CHICLE_GLOBAL double *)(p + AFFINE_B + 2 * i);
-        a[s] = *(const CHICLE_GLOBAL double *)(p + AFFINE_DIAG + 2 * i);
+        for (int e = 0; e < 2 * Q; ++e) P[s][e] = *(const CHICLE_GLOBAL double2_v *)(p + ((h * 2 * Q + e) * AFFINE_MAX_D + i) * 2);
+        b[s] = *(const CHICLE_GLOBAL double *)(p + AFFINE_B + i);
     };
     if (units > 0) {
-        s_v[i] = (float)v;
+        s_v[i] = v;
         wave_lds_fence();
 #pragma unroll
         for (int s = 0; s < SETS; ++s) load(s, s);
@@ -237,21 +248,21 @@ __global__ __launch_bounds__(64) void affine_starts(const SolverDev *__restrict_
 #pragma unroll
             for (int s = 0; s < SETS; ++s) {     // (runs past the end change nothing)
                 const int at = u0 + s;
-                *(CHICLE_GLOBAL double *)(place + min(at, units - 1) * stride + (at < units ? AFFINE_START : AFFINE_SINK) + 2 * i) = v;
-                float part[4] = {0.f, 0.f, 0.f, 0.f};
+                *(CHICLE_GLOBAL double *)(place_of(at) + (at < units ? AFFINE_START : AFFINE_SINK) + i) = v;
+                double part[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int e = 0; e < Q; ++e) {
-                    const float4_v w = *reinterpret_cast<const float4_v *>(s_v + 4 * (h * Q + e));
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) part[k] = fmaf(P[s][e][k], w[k], part[k]);
+                for (int e = 0; e < 2 * Q; ++e) {
+                    const double2_v w = *reinterpret_cast<const double2_v *>(s_v + 2 * (h * 2 * Q + e));
+                    part[2 * (e & 1)] = fma(P[s][e][0], w[0], part[2 * (e & 1)]);
+                    part[2 * (e & 1) + 1] = fma(P[s][e][1], w[1], part[2 * (e & 1) + 1]);
                 }
-                const float sum = (part[0] + part[1]) + (part[2] + part[3]);
-                const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
-                const float Pv = __uint_as_float(both[0]) + __uint_as_float(both[1]);
-                const double dv = fma(-a[s], v, b[s]) + (double)Pv;
-                v += ((i < d) & (at < units)) ? dv : 0.0;
+                const double sum = (part[0] + part[1]) + (part[2] + part[3]);
+                const unsigned lo = (unsigned)__double2loint(sum), hi = (unsigned)__double2hiint(sum);
+                const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), u = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+                const double dv = b[s] + (__hiloint2double((int)u[0], (int)l[0]) + __hiloint2double((int)u[1], (int)l[1]));
+                v += (has & (at < units)) ? dv : 0.0;    // (the places' rows past the last column are not written)
                 wave_lds_fence();
-                s_v[i] = (float)v;
+                s_v[i] = v;
                 wave_lds_fence();
                 load(s, at + SETS);
             }
@@ -261,71 +272,72 @@ __global__ __launch_bounds__(64) void affine_starts(const SolverDev *__restrict_
     stamp_solver(sc, 1);
 }
 
-// Grid: (groups of 16 runs, solver), four runs per wavefront; lanes as in affine_maps.  The next 16 rows are loaded during the steps
-// of these.
+// Grid: (groups of 16 runs, solver), four runs per wavefront, two columns per lane.  The next 16 rows are loaded during the
+// steps of these.
 __global__ __launch_bounds__(64 * AFFINE_WAVES) void affine_steps(const ChunkDev *__restrict__ chunks, const SolverDev *__restrict__ solvers,
                                                    float *tiles, int run, int ld, RoundScalars sc)
 {
+    constexpr int GROUP = AFFINE_GROUP;
     const SolverDev S = solvers[blockIdx.y];
     const int units = (S.n_rows + run - 1) / run;
     const int first = ((int)blockIdx.x * AFFINE_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * AFFINE_UNITS;
     if (first >= units) return;
-    const int lane = threadIdx.x & 63, m = lane & 15, unit = first + (lane >> 4);
-    const int groups = run / AFFINE_GROUP, tiles_end = (S.n_rows + BATCH - 1) / BATCH;
+    const int lane = threadIdx.x & 63, m = lane & (GROUP - 1), unit = first + lane / GROUP;
+    const int groups = run / GROUP, tiles_end = (S.n_rows + BATCH - 1) / BATCH;
     const bool has = 2 * m < ld;
     const int xo = has ? 2 * m : 0;
     float *tile0 = tiles + (int64_t)S.tile_begin * DENSE_TILE_FLOATS;
-    float *place = tile0 + (int64_t)min(unit, units - 1) * (run / BATCH) * DENSE_TILE_FLOATS;
+    double *place = reinterpret_cast<double *>(tile0 + (int64_t)min(unit, units - 1) * (run / BATCH) * DENSE_TILE_FLOATS);
     auto rows_of = [&](int g) __attribute__((always_inline)) {       // of the group; past the end: any
-        const int t = unit * run + g * AFFINE_GROUP;
+        const int t = unit * run + g * GROUP;
         return reinterpret_cast<const DenseRow *>(tile0 + (int64_t)min(t / BATCH, tiles_end - 1) * DENSE_TILE_FLOATS + BATCH * BATCH) + t % BATCH;
     };
     const RowState *any = chunks[0].st;
-    const float *xp[AFFINE_GROUP];
+    const float *xp[GROUP];
     RowState *rec_next, *rec;
-    float2_v X[2][AFFINE_GROUP];
+    float2_v X[2][GROUP];
     float4_v st;
     auto load_rows = [&](int g) __attribute__((always_inline)) {
         const DenseRow *r = rows_of(g);
 #pragma unroll
-        for (int j = 0; j < AFFINE_GROUP; ++j) xp[j] = r[j].x;
+        for (int j = 0; j < GROUP; ++j) xp[j] = r[j].x;
         rec_next = r[m].st;
     };
-    auto load_x = [&](float2_v (&to)[AFFINE_GROUP]) __attribute__((always_inline)) {
+    auto load_x = [&](float2_v (&to)[GROUP]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < AFFINE_GROUP; ++j) to[j] = *(const CHICLE_GLOBAL float2_v *)(xp[j] + xo);
+        for (int j = 0; j < GROUP; ++j) to[j] = *(const CHICLE_GLOBAL float2_v *)(xp[j] + xo);
         st = gld_state(rec_next != nullptr ? rec_next : any);
         rec = rec_next;
     };
-    const double2_v start = *(const CHICLE_GLOBAL double2_v *)(place + AFFINE_START + 4 * m);
+    const double2_v start = *(const CHICLE_GLOBAL double2_v *)(place + AFFINE_START + 2 * m);
     double q0 = has ? start.x : 0.0, q1 = has ? start.y : 0.0;
     load_rows(0);
     load_x(X[0]);
     load_rows(1);
-    auto group = [&](int g, float2_v (&now)[AFFINE_GROUP], float2_v (&then)[AFFINE_GROUP]) __attribute__((always_inline)) {
+    auto group = [&](int g, float2_v (&now)[GROUP], float2_v (&then)[GROUP]) __attribute__((always_inline)) {
         // (groups past the solver's tiles read its last tile's rows: they take no step)
-        const bool live = (rec != nullptr) & (unit * run + g * AFFINE_GROUP < tiles_end * BATCH);
-        const float s0 = sc.c / (sc.c + st.z), scale = live ? s0 : 0.f, kk = live ? st.w - st.y : 0.f, alpha = st.y;
-        float *alpha_out = live ? &rec->alpha : place + AFFINE_SINK + m;
+        const bool live = (rec != nullptr) & (unit * run + g * GROUP < tiles_end * BATCH);
+        const double s0 = affine_scale(st.z, sc.c), alpha = (double)st.y;
+        const double scale = live ? s0 : 0.0, kk = live ? (double)st.w - alpha : 0.0;
+        float *alpha_out = live ? &rec->alpha : reinterpret_cast<float *>(place + AFFINE_SINK + m);
         load_x(then);
         load_rows(g + 2);
-        float delta = 0.f;
+        double delta = 0.0;
         auto step = [&](auto J) __attribute__((always_inline)) {
             constexpr int j = decltype(J)::value;
-            const float s = of_lane16<j>(scale), k = of_lane16<j>(kk);
-            const bool on = has && s != 0.f;     // (a row that takes no step may hold what is no number)
-            const float x0 = on ? now[j].x : 0.f, x1 = on ? now[j].y : 0.f;
-            const float left = k - sum16(fmaf(x0, (float)q0, x1 * (float)q1)), dl = s * left;
-            const double cf = (double)(s * sc.inv_c * left);
-            q0 = fma(cf, (double)x0, q0);
-            q1 = fma(cf, (double)x1, q1);
+            const double s = of_lane<DPP_LANE_OF_16 + j>(scale), k = of_lane<DPP_LANE_OF_16 + j>(kk);
+            const bool on = has && s != 0.0;     // (a row that takes no step may hold what is no number)
+            const double x0 = (double)(on ? now[j].x : 0.f), x1 = (double)(on ? now[j].y : 0.f);
+            const double dl = s * (k - sum16(fma(x0, q0, x1 * q1))), cf = dl * (double)sc.inv_c;
+            q0 = fma(cf, x0, q0);
+            q1 = fma(cf, x1, q1);
             delta = m == j ? dl : delta;
         };
 #define CHICLE_STEP(j) step(std::integral_constant<int, j>())
         CHICLE_STEP(0); CHICLE_STEP(1); CHICLE_STEP(2); CHICLE_STEP(3); CHICLE_STEP(4); CHICLE_STEP(5); CHICLE_STEP(6); CHICLE_STEP(7);
         CHICLE_STEP(8); CHICLE_STEP(9); CHICLE_STEP(10); CHICLE_STEP(11); CHICLE_STEP(12); CHICLE_STEP(13); CHICLE_STEP(14); CHICLE_STEP(15);
 #undef CHICLE_STEP
-        gst(alpha_out, alpha + delta);
+        gst(alpha_out, (float)(alpha + delta));
     };
     for (int g = 0; g < groups; g += 2) {
         group(g, X[0], X[1]);
