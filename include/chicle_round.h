@@ -210,8 +210,11 @@ int chicle_assign(chicle_ctx *ctx, int32_t K, const int32_t *chunk_to_solver);
 /* Runtime of every solver's last local pass in milliseconds (host out, K entries), from the device's
  * constant-rate clock read at the start and at the end of the solver's workgroup: the task runtimes
  * the rebalancing policy learns from (Section 4.5).  What the whole chip does for all solvers together is
- * not part of it: the tiles of the block solvers, and the update of columns that one row alone holds after
- * blocks over shared columns.  Synchronises the stream.  Errors: ESTATE before
+ * not part of it: the tiles of the block solvers, the update of columns that one row alone holds after
+ * blocks over shared columns, and, where long passes over narrow dense rows go in runs of rows (squared loss,
+ * up to 32 columns, from 3009 rows in the longest solver), the forming of the runs' maps and the steps inside
+ * the runs: the time is then that of the solver's chain of runs (64 to 256 rows each), the one part of the
+ * pass that takes longer the more rows the solver has.  Synchronises the stream.  Errors: ESTATE before
  * the first local epoch, EDEVICE. */
 int chicle_solver_ms(chicle_ctx *ctx, float *ms_out);
 

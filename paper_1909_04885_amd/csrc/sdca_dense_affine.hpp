@@ -246,9 +246,10 @@ __global__ __launch_bounds__(64) void affine_starts(const SolverDev *__restrict_
         for (int s = 0; s < SETS; ++s) load(s, s);
         for (int u0 = 0; u0 < units; u0 += SETS) {
 #pragma unroll
-            for (int s = 0; s < SETS; ++s) {     // (runs past the end change nothing)
+            for (int s = 0; s < SETS; ++s) {
                 const int at = u0 + s;
-                *(CHICLE_GLOBAL double *)(place_of(at) + (at < units ? AFFINE_START : AFFINE_SINK) + i) = v;
+                if (at >= units) break;          // (so that the solver's clock ends with its last run)
+                *(CHICLE_GLOBAL double *)(place_of(at) + AFFINE_START + i) = v;
                 double part[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                 for (int e = 0; e < 2 * Q; ++e) {
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(64) void affine_starts(const SolverDev *__restrict_
                 const unsigned lo = (unsigned)__double2loint(sum), hi = (unsigned)__double2hiint(sum);
                 const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), u = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
                 const double dv = b[s] + (__hiloint2double((int)u[0], (int)l[0]) + __hiloint2double((int)u[1], (int)l[1]));
-                v += (has & (at < units)) ? dv : 0.0;    // (the places' rows past the last column are not written)
+                v += has ? dv : 0.0;             // (the places' rows past the last column are not written)
                 wave_lds_fence();
                 s_v[i] = v;
                 wave_lds_fence();

@@ -126,6 +126,33 @@ def test_rows_whose_norm_a_float_can_hardly_hold(d, n, scales):
     assert np.linalg.norm(w - w_rows) <= 1e-4 * np.linalg.norm(w_rows)
 
 
+def test_solver_runtimes():
+    """The chain of a solver's runs is what its clock covers, to the run: 49 runs of 64 rows take less than 56, 14 far less, none
+    next to nothing."""
+    import torch
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    assert torch.cuda.is_available()
+    print("\ncase affine runtimes", flush=True)
+    runs = [49, 56, 14]
+    bounds = np.concatenate([[0], np.cumsum(64 * np.array(runs))]).astype(np.int64)
+    n, d = int(bounds[-1]), 16
+    g = np.random.default_rng(1)
+    X = g.standard_normal((n, d)).astype(np.float32)
+    p = Problem("runtimes", "squared", n, d, 20.0 / n, X[:, 0].copy(), bounds, X=X)
+    r = binding.ChicleRound.from_problem(p, max_solvers=4)
+    r.assign(4, np.arange(3, dtype=np.int32))
+    ms = []
+    for _ in range(25):
+        r.local_epoch(r.upload_perm([g.permutation(int(m)).astype(np.int32) for m in r.solver_rows()]))
+        ms.append(r.solver_ms())
+        r.aggregate()
+    ms = np.median(ms, axis=0)
+    print("solver ms", ms, flush=True)
+    assert ms[0] < 0.92 * ms[1] and ms[2] < 0.5 * ms[0] and 0 <= ms[3] < 0.2 * ms[2]
+    r.close()
+
+
 def test_order_entry_out_of_range_is_reported():
     import torch
     import paper_1909_04885_amd as binding
