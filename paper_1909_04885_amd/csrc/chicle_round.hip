@@ -492,8 +492,15 @@ int affine_run(const chicle_ctx *c)
 // Whether the tiles of announced orders are formed ahead for dense rows.  The second stream costs a round about 20 us of
 // calls, which hide only behind a pass that is long enough: rounds of four solvers of 64 rows of 64 columns 33 us without, 56
 // with; of 1024 rows 56 and 59, of 256 columns 68 and 64, of 1000 columns 129 and 111; 64 solvers of 512 rows of 64 columns
-// 65 and 69, of 1024 rows 89 and 78.
-bool dense_tiles_ahead(const chicle_ctx *c) { return c->most_rows / BATCH + c->d / 64 >= 16 || c->n_tiles >= 1024; }
+// 65 and 69, of 1024 rows 89 and 78.  A pass that could go in runs is solved in blocks from such tiles where they cost it
+// less: one in 32 of 3075 rows of 28 columns 104 in runs, 97 in blocks, of 4700 of 32 128 and 119, one in 64 of 4688 of 32 174
+// and 157, one in 128 of 3073 of 24 170 and 148; one in 16 of 3075 of 28 92 and 89, one in 64 of 4096 of 28 and one in 128 of
+// 6250 of 32 equal, one in 64 of 6250 of 28 178 and 202, one in 64 of 3073 of 8 96 and 117.
+bool dense_tiles_ahead(const chicle_ctx *c)
+{
+    if (affine_run(c)) return c->d > 20 && c->most_rows <= 80 * BATCH && c->n_tiles >= 1024;
+    return c->most_rows / BATCH + c->d / 64 >= 16 || c->n_tiles >= 1024;
+}
 
 // LDS a dense solver asks for at least where it is to have a compute unit to itself: no other solver, and no workgroup of the
 // next pass's tile kernel, which runs beside it, is placed there.  Where there are more solvers than compute units and no
@@ -645,10 +652,10 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
 {
     const RoundScalars sc = scalars(c);
     int rc;
-    if (const int run = affine_run(c)) return launch_affine(c, perm, run);
+    const int run = tiles_ready ? 0 : affine_run(c);
     if (tiles_ready) {
         c->tile_buf = 1 - c->tile_buf;
-    } else {
+    } else if (!run) {
         seg_begin(c, CHICLE_SEG_EPOCH_GRAM);
         rc = launch_gram<LOSS>(c, perm, c->tile_buf, false, c->stream);
         seg_end(c, CHICLE_SEG_EPOCH_GRAM);
@@ -662,7 +669,10 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
     const int64_t *u_off = c->compact ? c->u_off_dev : nullptr;
     const int k_pad = (c->K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
     const int n_tails = split_tails(c);
-    if (c->dense) {
+    if (run) {
+        rc = launch_affine(c, perm, run);
+        if (rc) return rc;
+    } else if (c->dense) {
         seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
         rc = launch_dense<LOSS>(c, perm_next != nullptr || c->K <= c->cu_count);
         seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
@@ -1572,7 +1582,7 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
         c->ahead_buf = 1 - c->ahead_buf;
         c->ahead_valid = true;
     }
-    if (route == ROUTE_DENSE && (affine_run(c) || !dense_tiles_ahead(c))) perm_next_device = nullptr;      // (they are kept all the same)
+    if (route == ROUTE_DENSE && !dense_tiles_ahead(c)) perm_next_device = nullptr;      // (they are kept all the same)
     seg_begin(c, CHICLE_SEG_LOCAL_EPOCH);
     int rc = CHICLE_OK;
     if (!c->zw_valid) rc = run_row_pass(c, nullptr, c->gap_scratch);     // x_i . w for the current w

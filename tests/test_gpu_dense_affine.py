@@ -126,6 +126,22 @@ def test_rows_whose_norm_a_float_can_hardly_hold(d, n, scales):
     assert np.linalg.norm(w - w_rows) <= 1e-4 * np.linalg.norm(w_rows)
 
 
+@pytest.mark.parametrize("ahead", [False, True])
+@pytest.mark.parametrize("d", [20, 24])
+def test_many_solvers(oracle_mod, d, ahead):
+    """1078 tiles: with orders announced, the first pass goes in runs of rows, and those of more than 20 columns that follow in
+    blocks from the tiles formed beside it."""
+    import torch
+    import paper_1909_04885_amd as binding
+    assert torch.cuda.is_available()
+    print("\ncase affine many solvers d=%d ahead=%s" % (d, ahead), flush=True)
+    K = 22
+    p = _ridge(K * 3073, d, 200.0, 13, chunks=K)
+    table = np.arange(K, dtype=np.int32)
+    run_lockstep({"seed": 2, "rounds": 4, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1, ahead=ahead,
+                 tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)
+
+
 def test_solver_runtimes():
     """The chain of a solver's runs is what its clock covers, to the run: 49 runs of 64 rows take less than 56, 14 far less, none
     next to nothing."""
