@@ -38,24 +38,20 @@ __device__ __forceinline__ void ring_put(unsigned long long *p, float v, int tag
 // The wait of a polling wavefront (all 64 lanes, one ring word each), with several polls in flight: a poll is
 // a trip to L2 and back, so with one at a time an arrival is noticed a trip and a half later on average;
 // with POLL_DEPTH of them, issued a fraction of a trip apart, the one that sees it is already on its way.
-// PROGRESS: the same polls also fetch two progress words of the other tail, and the wait ends when the ring
-// words carry `tag` and those words have reached want_added / want_gathered.  Bounded: after SPLIT_SPIN_LIMIT
-// polls the wait gives up, raises the error flag and sets *dead (LDS), which makes every later wait of the
-// workgroup return at once, so a lost partner costs one time-out, not one per block.
+// PROGRESS: the same polls also fetch a progress word of the other tail, and the wait ends when the ring
+// words carry `tag` and that word has reached want_progress.  Bounded: after SPLIT_SPIN_LIMIT polls the wait
+// gives up, raises the error flag and sets *dead (LDS), which makes every later wait of the workgroup return
+// at once, so a lost partner costs one time-out, not one per block.
 constexpr int POLL_DEPTH = 1;
 template <bool PROGRESS>
-__device__ __forceinline__ float ring_wait(const unsigned long long *word, int tag, const unsigned long long *added,
-                                           int want_added, const unsigned long long *gathered, int want_gathered,
-                                           int *dead, int *err)
+__device__ __forceinline__ float ring_wait(const unsigned long long *word, int tag, const unsigned long long *progress,
+                                           int want_progress, int *dead, int *err)
 {
-    unsigned long long v[POLL_DEPTH], a[POLL_DEPTH], g[POLL_DEPTH];
+    unsigned long long v[POLL_DEPTH], g[POLL_DEPTH];
 #define RING_POLL(k)                                                                                        \
     do {                                                                                                    \
         v[k] = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);                         \
-        if (PROGRESS) {                                                                                     \
-            a[k] = __hip_atomic_load(added, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);                    \
-            g[k] = __hip_atomic_load(gathered, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);                 \
-        }                                                                                                   \
+        if (PROGRESS) g[k] = __hip_atomic_load(progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       \
     } while (0)
 #pragma unroll
     for (int k = 0; k < POLL_DEPTH; ++k) {
@@ -67,7 +63,7 @@ __device__ __forceinline__ float ring_wait(const unsigned long long *word, int t
 #pragma unroll
         for (int k = 0; k < POLL_DEPTH; ++k) {
             bool ok = (int)(v[k] >> 32) == tag;
-            if (PROGRESS) ok = ok && (int)a[k] >= want_added && (int)g[k] >= want_gathered;
+            if (PROGRESS) ok = ok && (int)g[k] >= want_progress;
             if (__builtin_amdgcn_ballot_w64(!ok) == 0ull) return __uint_as_float((unsigned)v[k]);   // every lane's word is here
             if (POLL_DEPTH == 1) __builtin_amdgcn_s_sleep(1);
             RING_POLL(k);
@@ -233,7 +229,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             if (A.n_tails > 0 && i + 1 >= 0 && i + 1 < nb) {
                 const int t = (i + 1) % A.n_tails;                   // the tail that owns block i + 1
                 sh.xv[lane] = ring_wait<false>(x_parts + (t * SPLIT_RING + ((i + 1) & (SPLIT_RING - 1))) * BATCH + lane, i + 2,
-                                               nullptr, 0, nullptr, 0, &sh.dead, A.err);
+                                               nullptr, 0, &sh.dead, A.err);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 if (lane == 0) __hip_atomic_store(&sh.xflag, i + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
@@ -375,14 +371,19 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
 
 // ---- a tail workgroup: the unpopular columns, in memory -----------------------------------------------------
 // Tail t of n (n = 1 or 2) owns the blocks t, t + n, t + 2n, ... of its solver: for each of them, in turn, it
-// adds the block two before it (whose steps have just arrived) to the private vector, waits until that has
-// been performed, gathers the block's dot products and hands them over.  With two tails the block two before
-// is the tail's own previous block, and everything older that the other tail adds must have been performed as
-// well: each tail publishes the last block it has added, after its fence, and waits for the other's where it
-// needs it (that block was added a whole iteration earlier, so the wait is normally over when it begins).
-// In the other direction, block b must not be added before the other tail has gathered block b + 1 (which
-// sees blocks <= b - 1 only; block b reaches it through T): each tail also publishes the last block it has
-// gathered, and an add waits for that.
+// adds the block two before it (whose steps have just arrived) to the private vector, gathers the block's dot
+// products and hands them over.  Its own adds need no wait before its own gathers: one compute unit's accesses
+// to one address are served in order.  With two tails the block two before is the tail's own previous block,
+// and the tails wait for each other:
+//   - block b must not be added before the other tail has gathered block b + 1 (which sees blocks <= b - 1
+//     only; block b reaches it through T);
+//   - block b + 2 must not be gathered before the other tail's adds of b - 1 and older have been performed.
+// One progress word per tail serves both: the last block it has gathered, published once every helper
+// wavefront has waited for all its memory operations of that iteration.  In the iteration that gathers b + 1
+// these are the adds of b - 1 too, so a tail that waits for the word to say b + 1, adds block b and then
+// gathers b + 2 does so after both.  (The last block of all is added without a wait: nobody gathers after it,
+// and adds may be performed in any order.)  Block b + 1 was gathered a whole iteration earlier, so the wait is
+// normally over when it begins.
 // A tail works ahead of the head where nothing depends on the steps: it resolves its rows some blocks ahead
 // and touches their entries several iterations before either workgroup asks for them, so that both find
 // them in the L2 they share.
@@ -410,8 +411,7 @@ __device__ __forceinline__ void split_tail(unsigned char *smem, const SplitArgs 
     const int32_t *pk = A.perm + S.perm_off;
     unsigned long long *x_steps = A.xchg_all + (int64_t)sid * SPLIT_WORDS;
     unsigned long long *x_parts = x_steps + (1 + tail) * SPLIT_RING * BATCH;
-    // progress[t]: 1 + the last block tail t has added to the private vector (0: none yet);
-    // progress[2 + t]: 1 + the last block it has gathered
+    // progress[t]: 1 + the last block tail t has gathered (0: none yet), everything it added before that performed
     unsigned long long *progress = x_steps + (1 + SPLIT_MAX_TAILS) * SPLIT_RING * BATCH;
     const int nb = (S.n_rows + BATCH - 1) / BATCH;
     const int n_own = nb > tail ? (nb - tail + n_tails - 1) / n_tails : 0;      // this tail's blocks
@@ -426,14 +426,13 @@ __device__ __forceinline__ void split_tail(unsigned char *smem, const SplitArgs 
             const int ja = j - back;                                     // own block that is added this iteration
             if (ja >= 0 && ja < n_own) {
                 const int b = block_of(ja);
-                // the steps of block b; with two tails also: has the other tail performed every add before b
-                // (b - 1 is its latest), and has it gathered block b + 1?  All fetched by the same polls.
+                // the steps of block b; with two tails also: has the other tail gathered block b + 1?  Both fetched by the
+                // same polls.
                 const unsigned long long *word = x_steps + (b & (SPLIT_RING - 1)) * BATCH + lane;
                 if (n_tails == 2)
-                    sh.xv[lane] = ring_wait<true>(word, b + 1, progress + (1 - tail), b, progress + 2 + (1 - tail),
-                                                  b + 1 < nb ? b + 2 : 0, &sh.dead, A.err);
+                    sh.xv[lane] = ring_wait<true>(word, b + 1, progress + (1 - tail), b + 1 < nb ? b + 2 : 0, &sh.dead, A.err);
                 else
-                    sh.xv[lane] = ring_wait<false>(word, b + 1, nullptr, 0, nullptr, 0, &sh.dead, A.err);
+                    sh.xv[lane] = ring_wait<false>(word, b + 1, nullptr, 0, &sh.dead, A.err);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (polls still in flight are not waited for)
                 if (lane == 0) __hip_atomic_store(&sh.xflag, ja + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
@@ -507,11 +506,9 @@ __device__ __forceinline__ void split_tail(unsigned char *smem, const SplitArgs 
                     }
                 }
             }
-            // 3. ... completely, before the next block is gathered; the other tail may rely on it from here on
+            // 3. ... by every wavefront, before the next block is gathered
             hb_target += HELPER_WAVES;
             helper_barrier(&sh.hb, hb_target);
-            if (tid == 64 && ja >= 0 && ja < n_own)
-                __hip_atomic_store(progress + tail, (unsigned long long)(block_of(ja) + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // 4. gather own block j and hand the partial sums over
             if (j >= 0 && j < n_own) {
                 float got[TE];
@@ -520,10 +517,11 @@ __device__ __forceinline__ void split_tail(unsigned char *smem, const SplitArgs 
                     got[e] = 0.f;
                     if (st_v[0][e] != 0.f) got[e] = ld_l2(u + st_c[0][e]);
                 }
-                // the values are here: once all helper wavefronts have theirs, the other tail may add block b + 1
+                // The values are here, and this wavefront's adds of step 2 are performed: once that holds for all helper
+                // wavefronts, the other tail may add the block before this one and gather the block after it.
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 if (lane == 0 && atomicAdd(&sh.gcount, 1) + 1 == HELPER_WAVES * (j + 1))
-                    __hip_atomic_store(progress + 2 + tail, (unsigned long long)(block_of(j) + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(progress + tail, (unsigned long long)(block_of(j) + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 float part = 0.f;
 #pragma unroll
                 for (int e = 0; e < TE; ++e) part += st_v[0][e] * got[e];
