@@ -4,7 +4,7 @@ announced orders where the solver of the pass changes, the solvers' runtimes."""
 import numpy as np
 import pytest
 
-from harness import run_lockstep
+from harness import TOL_DW, dw_floor, rel_l2, run_lockstep
 
 pytestmark = pytest.mark.gpu
 
@@ -124,6 +124,44 @@ def test_rows_whose_norm_a_float_can_hardly_hold(d, n, scales):
     assert huge.sum() == (200 if scales[0] > 1 else 0) and (alpha[huge] == 0).all()
     assert np.max(np.abs(alpha - alpha_rows)) <= 5e-4          # the oracle tests' bound for alpha
     assert np.linalg.norm(w - w_rows) <= 1e-4 * np.linalg.norm(w_rows)
+
+
+@pytest.mark.parametrize("steps", [[1, 2, 1, 1, 2], [2, 2, 1, 2, 2, 1]], ids=str)
+def test_announced_orders_across_assignments(oracle_mod, steps):
+    """Solvers of 50 blocks (runs of rows) and of 25 (blocks, tiles formed ahead) in turn, with orders announced all the time:
+    an assignment drops them, the pass after it has its own."""
+    import torch
+    import paper_1909_04885_amd as binding
+    assert torch.cuda.is_available()
+    print("\ncase affine announced %s" % steps, flush=True)
+    n, d = 3200, 24
+    p = _ridge(n, d, 20.0, 8)
+    r = binding.ChicleRound.from_problem(p, max_solvers=2)
+    o = oracle_mod.OracleCoCoA.from_problem(p)
+    g = np.random.default_rng(4)
+    K, following = 0, None
+    for s in steps:
+        if s != K:
+            K = s
+            table = (np.arange(2) % K).astype(np.int32)
+            r.assign(K, table)
+            o.assign(K, table)
+            if following is not None:
+                with pytest.raises(binding.ChicleError) as e:
+                    r.local_epoch_ahead(None, None)
+                assert e.value.code == -1
+            following = None
+        sizes = [int(m) for m in r.solver_rows()]
+        perms = following or [g.permutation(m).astype(np.int32) for m in sizes]
+        upcoming = [g.permutation(m).astype(np.int32) for m in sizes]
+        r.local_epoch_ahead(None if following else r.upload_perm(perms), r.upload_perm(upcoming))
+        following = upcoming
+        floor = dw_floor(float(np.linalg.norm(o.w)))
+        for k, ref in enumerate(o.local_epoch(perms)):
+            assert rel_l2(r.get_delta_w(k), ref, floor) <= TOL_DW
+        o.aggregate()
+        r.aggregate()
+    r.close()
 
 
 @pytest.mark.parametrize("ahead", [False, True])

@@ -1,5 +1,6 @@
 """Gram tiles of short sparse rows against x_i . x_j in double: columns of the dense product only, with slots of their own,
-sharing slots; runs of tiles that pass from one solver to the next; solvers of less than a block; empty rows."""
+sharing slots; runs of tiles that pass from one solver to the next, short ones and ones in which the tables, the places of the
+rows and the lookups ahead are used over and over; solvers of less than a block; empty rows."""
 import numpy as np
 import pytest
 
@@ -12,6 +13,8 @@ CASES = {
     "shared_slots": (2000, 60000, 30, 48, False, 2),
     "zipf": (3000, 20000, 48, 48, True, 2),
     "runs_over_solvers": (40000, 3000, 4, 10, True, 37),
+    "long_runs": (150000, 3000, 4, 10, True, 37),
+    "long_runs_shared_slots": (140000, 200000, 0, 8, False, 300),
     "less_than_a_block": (150, 200, 0, 20, False, 7),
     "one_row": (1, 50, 7, 7, False, 1),
 }
@@ -52,6 +55,8 @@ def test_gram_tiles(name, loss):
     r.assign(K, table)
     perms = [g.permutation(m) for m in r.solver_rows()]
     tiles = r.debug_gram(r.upload_perm(perms))
+    if name.startswith("long_runs"):     # (a workgroup per compute unit takes as many tiles in turn)
+        assert tiles.shape[0] >= 8 * torch.cuda.get_device_properties(0).multi_processor_count
     X = sp.csr_matrix((val.astype(np.float64), col, rp), shape=(n, d))
     q = np.asarray(X.multiply(X).sum(axis=1)).ravel()
     c = lam * n / K
