@@ -249,8 +249,8 @@ int chicle_local_epoch(chicle_ctx *ctx, const int32_t *perm_device);
  * after everything enqueued on the context's stream before this call, and runs beside this pass.
  * perm_device may be NULL: the pass then runs with the orders that the previous call announced, from the
  * context's copy, and uses the work prepared for them.  A non-NULL perm_device discards what was announced;
- * so does an assign.  (Short dense passes keep the announced orders and prepare nothing: the second stream
- * would cost them more.)  A refused call leaves what was announced as it was.  An out-of-range entry of
+ * so does an assign.  (Short dense passes, and long ones that go in runs of rows, keep the announced orders
+ * and prepare nothing: the second stream would cost them more.)  A refused call leaves what was announced as it was.  An out-of-range entry of
  * announced orders may be reported as soon as they are announced.
  * Errors: EINVAL (perm_device NULL with nothing announced), ESTATE. */
 int chicle_local_epoch_ahead(chicle_ctx *ctx, const int32_t *perm_device, const int32_t *perm_next_device);
