@@ -28,6 +28,7 @@
 #include "sdca_rowwise.hpp"
 #include "sdca_rowwise_cluster.hpp"
 #include "sdca_sparse_blocks.hpp"
+#include "split_pairs.hpp"
 
 using namespace chicle;
 
@@ -41,9 +42,6 @@ constexpr int DENSE_V_LDS_MAX_D = 8192;
 constexpr int BATCHED_MAX_LIST = MAX_LIST_LDS;  // chunk descriptors of one solver the batched solver stages in LDS (they take
                                                // the place of columns of the private vector's LDS-resident head)
 constexpr int RENUMBER_MAX_ROW = 64;   // rows are re-sorted by one thread each: short rows only
-#ifndef SPLIT_TAILS
-#define SPLIT_TAILS 2        // tail workgroups per solver of the split batched solver (1 or 2)
-#endif
 constexpr int SLICES_MIN = 4;         // fewer slices of the shared vector than this: the plain gap row pass
 constexpr double LONG_ROW_AVG = 96.0;  // sparse rows longer than this on average: the row-wise solver uses whole workgroups per row
 
@@ -156,6 +154,8 @@ struct chicle_ctx {
     int *err_dev = nullptr;
     int *progress_dev = nullptr;      // per solver: block its batched pass has reached
     unsigned long long *split_ring_dev = nullptr;   // per solver: rings between the workgroups that share it
+    unsigned long long *pair_list[2] = {nullptr, nullptr};   // per tile set: pairs of rows for the split solver, PAIR_CAP a tile,
+    int32_t *pair_count[2] = {nullptr, nullptr};             // and how many there are
     bool split_allowed = true;        // the batched solver may spread a solver over several compute units
     int max_tail_entries = 0;         // most entries a row has outside the columns the batched solver keeps on chip
     // long sparse rows: several workgroups (a cluster) share every solver of the row-wise pass
@@ -315,6 +315,8 @@ size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_sol
         s += align_up(sizeof(float) * (size_t)n_total) + align_up(sizeof(unsigned long long) * (size_t)SB_RING_WORDS * (size_t)max_solvers);
         s += align_up(sizeof(int32_t) * (size_t)max_solvers) + align_up(sizeof(int64_t) * (size_t)max_solvers);
         s += align_up(sizeof(int32_t) * (size_t)n_chunks);
+        s += 2 * (align_up(sizeof(unsigned long long) * PAIR_CAP * (size_t)tiles_cap(n_total, max_solvers)) +
+                  align_up(sizeof(int32_t) * (size_t)tiles_cap(n_total, max_solvers)));
     }
     return s;
 }
@@ -457,8 +459,9 @@ int split_tails(const chicle_ctx *c)
 {
     const int n_hot = batched_layout(c).n_hot, n_tails = n_hot < c->d ? SPLIT_TAILS : 0;
     const int k_pad = (c->K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
+    // (chunk lists that leave the head fewer popular columns than this: the solver on one compute unit)
     return c->split_allowed && (1 + n_tails) * k_pad <= c->cu_count &&
-           (n_tails == 0 || sizeof(double) * (size_t)n_hot >= 2 * RING * BATCH * sizeof(RowSlot)) ? n_tails : -1;   // a tail keeps its rows there
+           (n_tails == 0 || sizeof(double) * (size_t)n_hot >= 2 * RING * BATCH * sizeof(RowSlot)) ? n_tails : -1;
 }
 
 // Squared loss, dense rows: whether tiles are formed with the recurrence solved (gram_dense).  The inverse costs a tile 12 us
@@ -585,7 +588,25 @@ int launch_rowwise(chicle_ctx *c, const int32_t *perm)
     return CHICLE_OK;
 }
 
-// Gram tiles of the given visiting orders into tile set `buf`, on `stream` (ahead: beside the pass before theirs).
+// The last 24 entries of a row cover every row's columns outside the LDS-resident head.
+bool short_tails(const chicle_ctx *c) { return c->compact && c->max_tail_entries <= 3 * LPR; }
+
+template <int TE>
+int launch_pairs(chicle_ctx *c, const int32_t *perm, int buf, hipStream_t stream)
+{
+    auto kern = split_pairs<TE>;
+    const size_t sh = sizeof(PairShared<TE>);
+    HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+    // runs as long as two workgroups per compute unit make them: every run looks through three blocks more than it lists
+    const int run = std::min(PAIR_RUN, (c->n_tiles + 2 * c->cu_count - 1) / (2 * c->cu_count));
+    hipLaunchKernelGGL(kern, dim3((c->n_tiles + run - 1) / run), dim3(PAIR_THREADS), sh, stream, c->chunks_dev, c->solvers_dev,
+                       c->row_chunk_dev, c->chunk_first_dev, perm, c->tile_solver_dev, c->n_tiles, run, batched_layout(c).n_hot,
+                       c->pair_list[buf], c->pair_count[buf]);
+    return CHICLE_OK;
+}
+
+// Gram tiles of the given visiting orders into tile set `buf`, on `stream` (ahead: beside the pass before theirs), and the pairs
+// that the split solver's tails leave out.
 constexpr int GRAM_RUN = 32;
 template <int LOSS>
 int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, bool ahead, hipStream_t stream)
@@ -613,6 +634,10 @@ int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, bool ahead, hipStre
         hipLaunchKernelGGL(kern, dim3(grid), dim3(GRAM_THREADS), sizeof(GramShared), stream,
                            c->chunks_dev, c->solvers_dev, c->row_chunk_dev, c->chunk_first_dev, perm,
                            c->tile_solver_dev, c->tiles[buf], c->n_tiles, sc.c, c->err_dev);
+        if (split_tails(c) > 0) {
+            const int rc = short_tails(c) ? launch_pairs<3>(c, perm, buf, stream) : launch_pairs<ENT>(c, perm, buf, stream);
+            if (rc) return rc;
+        }
     }
     HIP_TRY(c, hipGetLastError());
     return CHICLE_OK;
@@ -685,9 +710,12 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
         A.solver_prefix = c->solver_prefix_dev; A.perm = perm; A.tiles = c->tiles[c->tile_buf]; A.u_all = c->u;
         A.ld_v = c->ld_v; A.u_off = u_off; A.max_list = ml; A.n_hot = n_hot; A.hot_off = (int)hot_off; A.sc = sc;
         A.err = c->err_dev; A.n_tails = n_tails; A.xchg_all = c->split_ring_dev;
-        // a tail's helper lanes take the last 24 entries of a row where that covers every row's unpopular columns
-        const bool short_tail = c->compact && c->max_tail_entries <= 3 * LPR;
-        auto kern = short_tail ? sdca_batched_split<LOSS, 3> : sdca_batched_split<LOSS, ENT>;
+        A.pair_list = c->pair_list[c->tile_buf]; A.pair_count = c->pair_count[c->tile_buf];
+        // a tail's lanes take the last 24 entries of a row where that covers every row's unpopular columns
+        constexpr int TE_SHORT = 3 * LPR / TAIL_LPR, TE_ALL = GRAM_MAX_ROW / TAIL_LPR;
+        auto kern = short_tails(c) ? sdca_batched_split<LOSS, TE_SHORT> : sdca_batched_split<LOSS, TE_ALL>;
+        if (n_tails > 0 && tail_lists_at(short_tails(c) ? TE_SHORT : TE_ALL) + (sizeof(ChunkDev) + sizeof(int)) * (size_t)ml > sh)
+            return fail(c, CHICLE_ESTATE, "the tails' state does not fit LDS");
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
         clear_device_words(c, c->split_ring_dev, 2 * (int64_t)SPLIT_WORDS * c->K);
         seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
@@ -1153,8 +1181,12 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
         c->count_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)max_solvers);
         c->u_off_dev = (int64_t *)carve(c, sizeof(int64_t) * (size_t)max_solvers);
         c->chunk_owner_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)n_chunks);
+        for (int buf = 0; buf < 2; ++buf) {
+            c->pair_list[buf] = (unsigned long long *)carve(c, sizeof(unsigned long long) * PAIR_CAP * (size_t)c->max_tiles);
+            c->pair_count[buf] = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->max_tiles);
+        }
     }
-    if (!c->err_dev || !c->ticks_dev || !c->progress_dev || !c->split_ring_dev || (c->long_rows && (!c->cluster_ring_dev || !c->slice_z_dev)) || (c->compact && (!c->chunk_owner_dev || !c->blocks_ring_dev))) { delete c; return CHICLE_ENOMEM; }
+    if (!c->err_dev || !c->ticks_dev || !c->progress_dev || !c->split_ring_dev || (c->long_rows && (!c->cluster_ring_dev || !c->slice_z_dev)) || (c->compact && (!c->chunk_owner_dev || !c->blocks_ring_dev || !c->pair_count[1]))) { delete c; return CHICLE_ENOMEM; }
 
     c->chunks.assign(n_chunks, ChunkDev{});
     c->loaded.assign(n_chunks, 0);

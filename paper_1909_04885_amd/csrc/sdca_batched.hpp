@@ -78,15 +78,53 @@ struct BatchedShared {
     int hb;
     int dead;                    // split solver: a wait for a partner workgroup has given up
     int xflag;                   // split solver: iteration whose ring words are in xv
-    int gcount;                  // split solver, tail: helper wavefronts whose gathered values have arrived
-    float xv[BATCH];             // split solver: what the partner sent (steps, or partial dot products)
+    int over;                    // split solver: a block has more pairs than its list holds
+    float xv[BATCH];             // split solver: the unpopular columns' share of the dot products
+    double xc[BATCH];            // split solver: what comes into that through pairs of rows two and three blocks apart
+    float steps[4][BATCH];       // split solver: of the latest blocks
 };
 
 // The chain: 64 sequential steps of one block.  Lane i owns row i.  A step is a clamp, a lane read and a multiply-add that
-// wait for each other; the lane's coefficients come from LDS four steps at a time, well ahead of their use, and the product
-// with the cross part fills the slots the lane read leaves.
+// wait for each other (six issue slots with the wait states between them); the multiply-add of the step before with the cross
+// part goes into one of the slots that are left.  All the lane's own coefficients are asked for before the first step and the
+// cross part sixteen steps at a time: read four steps at a time from an LDS that eight other wavefronts keep busy, they came
+// late (six solvers of 5000 rows of 40 entries: 2.88e3 cycles a block, 2.73e3 now).
 template <int LOSS>
-__device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c)
+__device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
+{
+    const int ring = i & (RING - 1), buf = i & 1;
+    float4_v T[BATCH / 4];
+#pragma unroll
+    for (int jq = 0; jq < BATCH / 4; ++jq) T[jq] = sh.Tw[buf][jq][lane];
+    asm volatile("" ::: "memory");           // (all of them are requested here)
+    float t = sh.t0[ring][lane] + x_carry;
+    const float lo = sh.lo[ring][lane], hi = sh.hi[ring][lane];
+    constexpr int AT_ONCE = 16;
+    float x = 0.f, s = 0.f, xc = 0.f;
+#pragma unroll
+    for (int h = 0; h < BATCH; h += AT_ONCE) {
+        float4_v X[AT_ONCE / 4];
+#pragma unroll
+        for (int q = 0; q < AT_ONCE / 4; ++q) X[q] = sh.Tx[buf][h / 4 + q][lane];
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int j = h; j < h + AT_ONCE; ++j) {
+            const float d = clamp_step<LOSS>(t, lo, hi);
+            __builtin_amdgcn_sched_barrier(0);
+            x = fmaf(s, xc, x);
+            asm volatile("" : "+v"(x));      // (here, and not behind all steps)
+            __builtin_amdgcn_sched_barrier(0);
+            s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), j));
+            xc = X[(j - h) / 4][j & 3];
+            t = fmaf(s, T[j / 4][j & 3], t);
+        }
+    }
+    steps[lane] = clamp_step<LOSS>(t, lo, hi);
+    x_carry = fmaf(s, xc, x);
+}
+// The same with the coefficients read four steps at a time, for the kernel whose wavefronts have no registers to spare.
+template <int LOSS>
+__device__ __forceinline__ void chain_block_small(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
 {
     const int ring = i & (RING - 1), buf = i & 1;
     float t = sh.t0[ring][lane] + x_carry;
@@ -103,7 +141,7 @@ __device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, 
             x = fmaf(s, X[e], x);
         }
     }
-    sh.delta[buf][lane] = clamp_step<LOSS>(t, lo, hi);
+    steps[lane] = clamp_step<LOSS>(t, lo, hi);
     x_carry = x;
 }
 
@@ -111,19 +149,25 @@ __device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, 
 //     m_i += delta_j T_ij,   T_ij = -y_i y_j G_ij / c
 // (logistic_block; the helpers leave m at the start of the block in slot t0 and the root for it in slot lo).
 template <>
-__device__ __forceinline__ void chain_block<2>(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c)
+__device__ __forceinline__ void chain_block<2>(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
 {
     const int ring = i & (RING - 1), buf = i & 1;
     const RowSlot &row = sh.rows[ring][lane];
     const float a = row.alpha, r = row.len > 0 ? row.q * inv_c : 0.f;      // r = 0 marks a row to skip
     float x = 0.f;
-    sh.delta[buf][lane] = logistic_block<BATCH>(
+    steps[lane] = logistic_block<BATCH>(
         sh.t0[ring][lane] + x_carry, a, r, sh.lo[ring][lane], lane, [&](int jq) { return sh.Tw[buf][jq][lane]; },
         [&](int jq, float d0, float d1, float d2, float d3) {
             const float4_v X = sh.Tx[buf][jq][lane];
             x = fmaf(d0, X[0], fmaf(d1, X[1], fmaf(d2, X[2], fmaf(d3, X[3], x))));
         });
     x_carry = x;
+}
+
+template <>
+__device__ __forceinline__ void chain_block_small<2>(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
+{
+    chain_block<2>(sh, i, lane, x_carry, inv_c, steps);
 }
 
 // One workgroup per solver: wavefront 0 runs the chain, eight wavefronts gather and scatter, two
@@ -238,7 +282,7 @@ __global__ __launch_bounds__(BATCHED_THREADS) void sdca_batched_csr(
         if (tid == BATCHED_THREADS - 1 && i > 0)
             __hip_atomic_store(progress + sid, i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (is_chain) {
-            if (i >= 0 && i < nb) chain_block<LOSS>(sh, i, lane, x_carry, sc.inv_c);
+            if (i >= 0 && i < nb) chain_block_small<LOSS>(sh, i, lane, x_carry, sc.inv_c, sh.delta[i & 1]);
         } else if (is_service) {
             // tiles for iteration i + 1 (wavefront 9: own part of T(i+1), wavefront 10: cross part of
             // T(i+2), 16 KB each) were fetched into registers during the last iteration

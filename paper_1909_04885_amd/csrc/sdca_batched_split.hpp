@@ -1,4 +1,4 @@
-// Batched local solver with every solver spread over two or three compute units (paper Section 4.2: a
+// Batched local solver with every solver spread over three compute units (paper Section 4.2: a
 // solver may use all the processors of its node; Section 2.2: L = 1, the coordinate steps keep their order).
 //
 // One compute unit gets a memory request served every few cycles, whatever its size.  Per block of 64 steps
@@ -8,67 +8,55 @@
 // the private vector are divided:
 //   - the head workgroup keeps the popular columns [0, n_hot) in LDS, runs the recurrence, stages the tiles;
 //     its gathers and scatters touch LDS only;
-//   - one or two tail workgroups on the same L2 partition own the other columns (two: by parity), in memory.
-// For every block the tail hands the head 64 partial dot products and the head hands the tail the 64 steps,
+//   - two tail workgroups on the same L2 partition own the other columns, half of them each, in memory.
+// For every block each tail hands the head 64 partial dot products and the head hands the tails the 64 steps,
 // through rings of 64-bit words in memory.  A word carries its value together with the number of the block
 // it belongs to, so no fence is needed; every wait is bounded: a workgroup that waits too long raises the
 // error flag, stops waiting for the rest of the pass and finishes.
 //
-// The order of operations is that of the single-workgroup solver: block b's dot products see the private
-// vector with blocks <= b-2 applied, block b-1 enters through the cross part of T.
+// Block b's dot products see the private vector with blocks <= b - 2 applied in the popular columns, and with blocks
+// <= b - 4 in the others, where blocks b - 2 and b - 3 enter through pairs of rows; block b - 1 enters through the cross part of T.
 #pragma once
 #include <hip/hip_runtime.h>
 #include "device_types.hpp"
 #include "mem.hpp"
 #include "sdca_batched.hpp"
+#include "split_pairs.hpp"
 
 namespace chicle {
 
 constexpr int SPLIT_RING = 8;                  // blocks a ring holds
-constexpr int SPLIT_MAX_TAILS = 2;
-constexpr int SPLIT_WORDS = (1 + SPLIT_MAX_TAILS) * SPLIT_RING * BATCH + 8;   // 64-bit words per solver
+constexpr int SPLIT_TAILS = 2;
+constexpr int LAG = 4;                         // unpopular columns: blocks <= b - LAG are in what block b gathers
+constexpr int SPLIT_WORDS = (1 + SPLIT_TAILS) * SPLIT_RING * BATCH;      // 64-bit words per solver
 constexpr int SPLIT_SPIN_LIMIT = 1 << 22;      // polls before a wait for the partner gives up
-constexpr int SPLIT_THREADS = BATCHED_THREADS + 64;   // the single-workgroup solver's wavefronts and one that polls the rings
+constexpr int SPLIT_THREADS = BATCHED_THREADS + 128;  // the single-workgroup solver's wavefronts, one that polls the rings and one that resolves rows
 
 __device__ __forceinline__ void ring_put(unsigned long long *p, float v, int tag)
 {
     const unsigned long long w = ((unsigned long long)(unsigned)tag << 32) | (unsigned long long)__float_as_uint(v);
     __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// The wait of a polling wavefront (all 64 lanes, one ring word each), with several polls in flight: a poll is
-// a trip to L2 and back, so with one at a time an arrival is noticed a trip and a half later on average;
-// with POLL_DEPTH of them, issued a fraction of a trip apart, the one that sees it is already on its way.
-// PROGRESS: the same polls also fetch a progress word of the other tail, and the wait ends when the ring
-// words carry `tag` and that word has reached want_progress.  Bounded: after SPLIT_SPIN_LIMIT polls the wait
+// The wait of a polling wavefront: every lane for N ring words, `stride` apart, until all of them carry `tag`; the sum of
+// their values.  Bounded: after SPLIT_SPIN_LIMIT polls the wait
 // gives up, raises the error flag and sets *dead (LDS), which makes every later wait of the workgroup return
 // at once, so a lost partner costs one time-out, not one per block.
-constexpr int POLL_DEPTH = 1;
-template <bool PROGRESS>
-__device__ __forceinline__ float ring_wait(const unsigned long long *word, int tag, const unsigned long long *progress,
-                                           int want_progress, int *dead, int *err)
+template <int N>
+__device__ __forceinline__ float ring_wait(const unsigned long long *word, int stride, int tag, int *dead, int *err)
 {
-    unsigned long long v[POLL_DEPTH], g[POLL_DEPTH];
-#define RING_POLL(k)                                                                                        \
-    do {                                                                                                    \
-        v[k] = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);                         \
-        if (PROGRESS) g[k] = __hip_atomic_load(progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       \
-    } while (0)
+    for (int spins = 0;; ++spins) {
+        unsigned long long v[N];
 #pragma unroll
-    for (int k = 0; k < POLL_DEPTH; ++k) {
-        RING_POLL(k);
-        if (k + 1 < POLL_DEPTH) __builtin_amdgcn_s_sleep(2);
-    }
-    int spins = 0;
-    for (;;) {
+        for (int k = 0; k < N; ++k) v[k] = __hip_atomic_load(word + k * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool ok = true;
+        float sum = 0.f;
 #pragma unroll
-        for (int k = 0; k < POLL_DEPTH; ++k) {
-            bool ok = (int)(v[k] >> 32) == tag;
-            if (PROGRESS) ok = ok && (int)g[k] >= want_progress;
-            if (__builtin_amdgcn_ballot_w64(!ok) == 0ull) return __uint_as_float((unsigned)v[k]);   // every lane's word is here
-            if (POLL_DEPTH == 1) __builtin_amdgcn_s_sleep(1);
-            RING_POLL(k);
+        for (int k = 0; k < N; ++k) {
+            ok = ok && (int)(v[k] >> 32) == tag;
+            sum += __uint_as_float((unsigned)v[k]);
         }
-        spins += POLL_DEPTH;
+        if (__builtin_amdgcn_ballot_w64(!ok) == 0ull) return sum;              // every lane's words are here
+        __builtin_amdgcn_s_sleep(1);
         if (spins > SPLIT_SPIN_LIMIT || __hip_atomic_load(dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
             if (spins > SPLIT_SPIN_LIMIT) {
                 __hip_atomic_store(dead, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -77,18 +65,27 @@ __device__ __forceinline__ float ring_wait(const unsigned long long *word, int t
             return 0.f;
         }
     }
-#undef RING_POLL
 }
 
 // Barrier among the helper wavefronts that orders their LDS traffic only (it does not wait for loads from
 // memory that are still in flight).
-__device__ __forceinline__ void helper_barrier_lds(int *cnt, int target)
+// In two parts: work that neither side of it depends on goes between arrival and wait.
+__device__ __forceinline__ void helper_arrive_lds(int *cnt)
 {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if ((threadIdx.x & 63) == 0) atomicAdd(cnt, 1);
+}
+__device__ __forceinline__ void helper_wait_lds(const int *cnt, int target)
+{
     while (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < target)
         __builtin_amdgcn_s_sleep(1);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+__device__ __forceinline__ void helper_barrier_lds(int *cnt, int target)
+{
+    helper_arrive_lds(cnt);
+    helper_wait_lds(cnt, target);
 }
 
 // Sum over the LPR = 8 lanes that share a row, in every one of them, by data-parallel-primitive moves (the
@@ -100,6 +97,14 @@ __device__ __forceinline__ float sum_over_row_lanes(float v)
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false));   // row_half_mirror
+    return v;
+}
+
+// The same over the four lanes of a quad.
+__device__ __forceinline__ float sum_over_quad(float v)
+{
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));
     return v;
 }
 
@@ -166,6 +171,8 @@ struct SplitArgs {
     int *err;
     int n_tails;
     unsigned long long *xchg_all;
+    const unsigned long long *pair_list;     // beside the tiles (split_pairs)
+    const int32_t *pair_count;
 };
 
 // Common start of both kinds of workgroup: the solver's chunk list into LDS.
@@ -179,9 +186,21 @@ __device__ __forceinline__ void split_stage_lists(unsigned char *smem, const Spl
     }
 }
 
+// How many blocks before a block are not in what its gather sees of the unpopular columns: all workgroups of a solver
+// look through the same counts.
+__device__ __forceinline__ int split_lag(const SplitArgs &A, const SolverDev &S, int nb, int *flag)
+{
+    if (threadIdx.x == 0) *flag = 0;
+    __syncthreads();
+    for (int t = threadIdx.x; t < nb; t += SPLIT_THREADS)
+        if (A.pair_count[S.tile_begin + t] > PAIR_CAP) __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+    return __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) ? 2 : LAG;
+}
+
 // ---- the head workgroup: recurrence, tiles, the popular columns in LDS -------------------------------------
-// Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 resolve rows and stage the tiles, 11
-// fetches the tails' partial sums.  One loop per role, all with the same number of iterations and one
+// Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 stage the tiles, 11
+// fetches the tails' partial sums, 12 resolves rows.  One loop per role, all with the same number of iterations and one
 // workgroup barrier per iteration, so that the registers of one role are not kept alive through the code of
 // the others.
 template <int LOSS>
@@ -198,13 +217,14 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
     double *hot = reinterpret_cast<double *>(smem + A.hot_off);
     for (int i = tid; i < n_hot; i += SPLIT_THREADS) hot[i] = 0.0;
     if (tid == 0) { sh.hb = 0; sh.dead = 0; sh.xflag = 0; }
+    const int nb = (S.n_rows + BATCH - 1) / BATCH;
+    const bool pairs = A.n_tails > 0 && split_lag(A, S, nb, &sh.over) == LAG;
     __syncthreads();
     float *u = A.u_off ? A.u_all + A.u_off[sid] : A.u_all + (int64_t)sid * A.ld_v;
     const int32_t *pk = A.perm + S.perm_off;
     const float *my_tiles = A.tiles + (int64_t)S.tile_begin * TILE_FLOATS;
     unsigned long long *x_steps = A.xchg_all + (int64_t)sid * SPLIT_WORDS;
     unsigned long long *x_parts = x_steps + SPLIT_RING * BATCH;
-    const int nb = (S.n_rows + BATCH - 1) / BATCH;
     const int lane = tid & 63, wave = tid >> 6;
     const int hl = tid - 64, rho = hl / LPR, sub = hl & (LPR - 1);     // helper coordinates
     if (nb == 0) {                                   // a solver without rows (uniform for its workgroups)
@@ -216,28 +236,57 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
         float x_carry = 0.f;
         HEAD_ITERATIONS {
             if (i >= 0 && i < nb) {
-                chain_block<LOSS>(sh, i, lane, x_carry, sc.inv_c);
+                chain_block<LOSS>(sh, i, lane, x_carry, sc.inv_c, sh.steps[i & 3]);
                 // the tails add these steps into their columns
-                if (A.n_tails > 0) ring_put(x_steps + (i & (SPLIT_RING - 1)) * BATCH + lane, sh.delta[i & 1][lane], i + 1);
+                if (A.n_tails > 0) ring_put(x_steps + (i & (SPLIT_RING - 1)) * BATCH + lane, sh.steps[i & 3][lane], i + 1);
             }
             __syncthreads();
         }
     } else if (wave == 11) {
-        // What the tail sends for this iteration, fetched by a wavefront that has no other loads in flight
-        // (loads return in the order they were issued) and handed on through LDS.
+        // What the tails send for this iteration, fetched by a wavefront that has no other loads in flight
+        // (loads return in the order they were issued) and handed on through LDS; before it what blocks i - 1 and i - 2,
+        // whose steps are at hand, add to it through pairs.  Their number and the first 64 of them were asked for an iteration ago.
+        const int32_t *counts = A.pair_count + S.tile_begin;
+        const unsigned long long *lists = A.pair_list + (int64_t)S.tile_begin * PAIR_CAP + lane;
+        int count = 0;                                   // lane 0's
+        unsigned long long first = 0ull;
         HEAD_ITERATIONS {
             if (A.n_tails > 0 && i + 1 >= 0 && i + 1 < nb) {
-                const int t = (i + 1) % A.n_tails;                   // the tail that owns block i + 1
-                sh.xv[lane] = ring_wait<false>(x_parts + (t * SPLIT_RING + ((i + 1) & (SPLIT_RING - 1))) * BATCH + lane, i + 2,
-                                               nullptr, 0, &sh.dead, A.err);
+                sh.xc[lane] = 0.0;
+                asm volatile("" ::: "memory");
+                const int n_pairs = __builtin_amdgcn_readfirstlane(count);
+                for (int k = 0; k < n_pairs; k += 64) {
+                    const unsigned long long w = k == 0 ? first : lists[(int64_t)(i + 1) * PAIR_CAP + k];
+                    if (k + lane < n_pairs) {
+                        const unsigned at = (unsigned)(w >> 32);
+                        const int j = at & 63, b = i - 1 - (int)(at >> 12);
+                        const float coef = sh.steps[b & 3][j] * (LOSS == 1 ? 1.f : sh.rows[b & (RING - 1)][j].y) * sc.inv_c;
+                        atomicAdd(&sh.xc[at >> 6 & 63], (double)(coef * __uint_as_float((unsigned)w)));
+                    }
+                }
+                asm volatile("" ::: "memory");
+                const float corr = (float)sh.xc[lane];
+                sh.xv[lane] = corr + ring_wait<SPLIT_TAILS>(x_parts + ((i + 1) & (SPLIT_RING - 1)) * BATCH + lane, SPLIT_RING * BATCH,
+                                                            i + 2, &sh.dead, A.err);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 if (lane == 0) __hip_atomic_store(&sh.xflag, i + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
+            if (pairs && i + 2 >= 0 && i + 2 < nb) {
+                count = gld(counts + min(i + 2 + lane, nb - 1));       // (a scalar load would be waited for at the barrier)
+                first = lists[(int64_t)(i + 2) * PAIR_CAP];
+            }
+            __syncthreads();
+        }
+    } else if (wave == 12) {
+        // (one block further ahead than the tails' resolvers: the helpers ask for a block's entries three
+        // iterations before they gather it)
+        RowResolver resolver;
+        HEAD_ITERATIONS {
+            resolver.step(sh.rows, RING - 1, l_desc, l_prefix, S, pk, i + 1, 0, 1, nb, lane, A.err, true);
             __syncthreads();
         }
     } else if (wave >= 9) {
         const int sw = wave - 9;
-        RowResolver resolver;
         float4 stage[16];                                // tile part fetched ahead
         bool staged = false;
         HEAD_ITERATIONS {
@@ -247,9 +296,6 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             float4 *dst = reinterpret_cast<float4 *>(sw == 0 ? &sh.Tw[buf][0][0] : &sh.Tx[buf][0][0]);
 #pragma unroll
             for (int j = 0; j < 16; ++j) dst[lane + 64 * j] = staged ? stage[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-            // (one block further ahead than the tails' resolvers: the helpers ask for a block's entries three
-            // iterations before they gather it)
-            if (sw == 0) resolver.step(sh.rows, RING - 1, l_desc, l_prefix, S, pk, i + 1, 0, 1, nb, lane, A.err, true);
             const int tb = sw == 0 ? i + 2 : i + 3;
             staged = tb >= 0 && tb < nb;
             if (staged) {
@@ -283,18 +329,8 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             const RowSlot r_in = sh.rows[(i + 3) & (RING - 1)][rho];
             const RowSlot r_s = sh.rows[(i - 1) & (RING - 1)][rho];
             const RowSlot r_g = sh.rows[(i + 1) & (RING - 1)][rho];
-            const float dl = sh.delta[(i - 1) & 1][rho];
-            // 1. this lane's segment of the row of block i + 3 (unconditional vector loads)
-            if (has_in) {
-                const int32_t *cp = r_in.col + sub;
-                const float *vp = r_in.val + sub;
-                ld_len = r_in.len;
-#pragma unroll
-                for (int e = 0; e < ENT; ++e) { ld_c[e] = gld(cp + e * LPR); ld_v[e] = gld(vp + e * LPR); }
-            } else {
-                ld_len = 0;
-            }
-            // 2. block i - 1 is added to the head of the private vector
+            const float dl = sh.steps[(i - 1) & 3][rho];
+            // 1. block i - 1 is added to the head of the private vector
             if (has_s && r_s.len > 0 && dl != 0.f) {
                 const float coef = dl * (LOSS == 1 ? 1.f : r_s.y) * sc.inv_c;
 #pragma unroll
@@ -306,10 +342,28 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
                     gst(&r_s.st->alpha, an);
                 }
             }
-            // 3. ... completely, before block i + 1 is gathered (LDS traffic only)
+            // 2. ... completely, before block i + 1 is gathered (LDS traffic only); meanwhile this lane's segment of the row
+            //    of block i + 3 is asked for
+            helper_arrive_lds(&sh.hb);
+            if (has_in) {
+                const int32_t *cp = r_in.col + sub * ENT;
+                const float *vp = r_in.val + sub * ENT;
+                ld_len = r_in.len;
+                static_assert(ENT == 6, "a lane's entries are loaded four and two at a time");
+                const int4_a4 c4 = gld4(cp);
+                const int2_a4 c2 = gld2(cp + 4);
+                const float4_a4 v4 = gld4(vp);
+                const float2_a4 v2 = gld2(vp + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { ld_c[e] = c4[e]; ld_v[e] = v4[e]; }
+#pragma unroll
+                for (int e = 0; e < 2; ++e) { ld_c[4 + e] = c2[e]; ld_v[4 + e] = v2[e]; }
+            } else {
+                ld_len = 0;
+            }
             hb_target += HELPER_WAVES;
-            helper_barrier_lds(&sh.hb, hb_target);
-            // 4. gather block i + 1 (blocks <= i - 1 applied)
+            helper_wait_lds(&sh.hb, hb_target);
+            // 3. gather block i + 1 (blocks <= i - 1 applied)
             if (has_g) {
                 float got[ENT];
 #pragma unroll
@@ -347,13 +401,13 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
                     if (LOSS == 2) { sh.lo[ring][rho] = lo; sh.hi[ring][rho] = hi; }
                 }
             }
-            // 5. move the entry sets one stage on; the set that arrived (block i + 2) is masked to the row's
+            // 4. move the entry sets one stage on; the set that arrived (block i + 2) is masked to the row's
             //    length and to the head's columns
 #pragma unroll
             for (int e = 0; e < ENT; ++e) {
                 s_c[e] = c_c[e]; s_v[e] = c_v[e];
                 c_c[e] = g_c[e]; c_v[e] = g_v[e];
-                const bool live = sub + e * LPR < ar_len && ar_c[e] < n_hot;
+                const bool live = sub * ENT + e < ar_len && ar_c[e] < n_hot;
                 g_c[e] = live ? ar_c[e] : 0;
                 g_v[e] = live ? ar_v[e] : 0.f;
             }
@@ -370,187 +424,180 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
 }
 
 // ---- a tail workgroup: the unpopular columns, in memory -----------------------------------------------------
-// Tail t of n (n = 1 or 2) owns the blocks t, t + n, t + 2n, ... of its solver: for each of them, in turn, it
-// adds the block two before it (whose steps have just arrived) to the private vector, gathers the block's dot
-// products and hands them over.  Its own adds need no wait before its own gathers: one compute unit's accesses
-// to one address are served in order.  With two tails the block two before is the tail's own previous block,
-// and the tails wait for each other:
-//   - block b must not be added before the other tail has gathered block b + 1 (which sees blocks <= b - 1
-//     only; block b reaches it through T);
-//   - block b + 2 must not be gathered before the other tail's adds of b - 1 and older have been performed.
-// One progress word per tail serves both: the last block it has gathered, published once every helper
-// wavefront has waited for all its memory operations of that iteration.  In the iteration that gathers b + 1
-// these are the adds of b - 1 too, so a tail that waits for the word to say b + 1, adds block b and then
-// gathers b + 2 does so after both.  (The last block of all is added without a wait: nobody gathers after it,
-// and adds may be performed in any order.)  Block b + 1 was gathered a whole iteration earlier, so the wait is
-// normally over when it begins.
-// A tail works ahead of the head where nothing depends on the steps: it resolves its rows some blocks ahead
-// and touches their entries several iterations before either workgroup asks for them, so that both find
-// them in the L2 they share.
-// Wavefronts 1..8 add and gather, 9 resolves rows, 10 touches entries, 11 waits for the steps (and for the
-// other tail); wavefront 0 only keeps the barriers.  TE: entries per helper lane, taken from the end of the
-// row, where its unpopular columns are (rows are sorted by popularity): TE * LPR must cover the largest
-// number of entries a row has in the tails' columns (checked on the host).
-constexpr int TAIL_WARM = 3;                        // iterations the touches run ahead of the tail's own loads
-constexpr int TAIL_RING = 2 * RING;                 // resolved rows of the tail's blocks j - 2 .. j + TAIL_WARM + 2
+// The unpopular columns are divided over the solver's two tails (lines of 128 bytes of the private vector in turn), so that what
+// a tail adds and what it gathers meet in one compute unit, whose accesses to one address are served in the order in which
+// they are issued: nothing waits for memory but the partial sums themselves.  (Tails that took the blocks in turn and all
+// columns had to wait for each other's gathers: a trip to memory, its adds and its gather per block, which bounded the solver.)
+// Block b's gather sees blocks <= b - 4.  Block b - 1 enters through the cross part of T, and of blocks b - 2 and b - 3 only the
+// rows matter that share an unpopular column with one of block b: a handful of pairs, which depend on the data and the orders
+// only and are listed beside the tiles (split_pairs); the head adds what they give when it has the steps at hand.  So the way
+// from the steps to a tail, through its adds and its gather, and back may take as long as the chains of four blocks.  A solver
+// one of whose blocks has more pairs than its list holds (PAIR_CAP) gathers with blocks <= b - 2 added, and no pairs.
+// Two groups of four wavefronts take the blocks in turn.  In its turn, which begins when the other group has issued its
+// gathers, a group adds block b - 4, whose steps have arrived, and issues block b's gathers; while they are on their way
+// the other group has its turn.  A block's entries are asked for a turn ahead; between gather and add they wait in LDS.  Two
+// wavefronts resolve rows, one for each group, one waits for the steps; the wavefronts hand on through words in LDS that only
+// grow, there is no workgroup barrier.
+// TE: entries per lane (TAIL_LPR lanes a row), taken from the end of the row, where its unpopular columns are (rows are sorted
+// by popularity): TE * TAIL_LPR must cover the largest number of entries a row has in the tails' columns (checked on the host).
+// 32 solvers of 62500 rows of 40 entries, 1M columns: 6.9e3 cycles per block of 64 steps with blocks in turn and look-back two
+// (2.84 ms a pass), 7.7e3 with blocks in turn and look-back three, 5.1e3 now (2.15 ms); six of 5000 rows, 20k columns: 169 us
+// a pass, 126 now.  A tail waits for steps 3.9e3 of its 1.04e4 cycles per two blocks; the head's tile loads and row lookups, which
+// miss the cache, take as long as an iteration.
+constexpr int TAIL_LPR = 4, TAIL_GROUPS = 2, TAIL_WAVES = BATCH * TAIL_LPR / 64;
+constexpr int TAIL_RING = 4;                        // resolved rows of a group's blocks
+constexpr int TAIL_LINE_LOG2 = 5;                   // columns of a tail's share of the private vector that lie side by side
+
+struct TailShared {
+    RowSlot rows[TAIL_GROUPS][TAIL_RING][BATCH];
+    float xv[LAG][BATCH];                           // steps of the latest blocks
+    int steps_ready, issued, dead, over;                  // blocks whose steps are in xv; wavefronts that have issued a block's gathers
+    int rows_ready[TAIL_GROUPS], loaded[TAIL_GROUPS], bar[TAIL_GROUPS];
+};
+struct __align__(8) TailEntry { int col; float val; };          // val: with the row's label, as its step is added
+__host__ __device__ inline size_t tail_lists_at(int te)
+{
+    return sizeof(TailShared) + sizeof(TailEntry) * (size_t)(LAG * te * BATCH * TAIL_LPR);
+}
+
+__device__ __forceinline__ void raise_flag(int *flag, int v)
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(flag, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 
 template <int LOSS, int TE>
 __device__ __forceinline__ void split_tail(unsigned char *smem, const SplitArgs &A, int sid, int tail)
 {
-    BatchedShared &sh = *reinterpret_cast<BatchedShared *>(smem);
-    ChunkDev *l_desc = reinterpret_cast<ChunkDev *>(smem + sizeof(BatchedShared));
+    TailShared &sh = *reinterpret_cast<TailShared *>(smem);
+    TailEntry *kept = reinterpret_cast<TailEntry *>(smem + sizeof(TailShared));        // [block & (LAG - 1)][entry][lane of the group]
+    ChunkDev *l_desc = reinterpret_cast<ChunkDev *>(smem + tail_lists_at(TE));
     int *l_prefix = reinterpret_cast<int *>(l_desc + A.max_list);
-    RowSlot (*rows)[BATCH] = reinterpret_cast<RowSlot (*)[BATCH]>(smem + A.hot_off);     // the head's place for the popular columns
     const SolverDev S = A.solvers[sid];
     const RoundScalars &sc = A.sc;
-    const int tid = threadIdx.x, n_hot = A.n_hot, n_tails = A.n_tails;
+    const int tid = threadIdx.x, n_hot = A.n_hot;
     split_stage_lists(smem, A, S, l_desc, l_prefix);
-    if (tid == 0) { sh.hb = 0; sh.dead = 0; sh.xflag = 0; sh.gcount = 0; }
-    __syncthreads();
+    if (tid == 0) {
+        sh.steps_ready = sh.issued = sh.dead = 0;
+        for (int g = 0; g < TAIL_GROUPS; ++g) sh.rows_ready[g] = sh.loaded[g] = sh.bar[g] = 0;
+    }
+    const int nb = (S.n_rows + BATCH - 1) / BATCH;
+    const int lag = split_lag(A, S, nb, &sh.over);      // (a workgroup barrier)
+    if (nb == 0) return;
     float *u = A.u_off ? A.u_all + A.u_off[sid] : A.u_all + (int64_t)sid * A.ld_v;
     const int32_t *pk = A.perm + S.perm_off;
     unsigned long long *x_steps = A.xchg_all + (int64_t)sid * SPLIT_WORDS;
     unsigned long long *x_parts = x_steps + (1 + tail) * SPLIT_RING * BATCH;
-    // progress[t]: 1 + the last block tail t has gathered (0: none yet), everything it added before that performed
-    unsigned long long *progress = x_steps + (1 + SPLIT_MAX_TAILS) * SPLIT_RING * BATCH;
-    const int nb = (S.n_rows + BATCH - 1) / BATCH;
-    const int n_own = nb > tail ? (nb - tail + n_tails - 1) / n_tails : 0;      // this tail's blocks
-    const int back = 2 / n_tails;                                               // own iterations between gather and add
     const int lane = tid & 63, wave = tid >> 6;
-    const int hl = tid - 64, rho = hl / LPR, sub = hl & (LPR - 1);
-    if (n_own == 0) return;
-    auto block_of = [&](int j) { return tail + n_tails * j; };
-#define TAIL_ITERATIONS for (int j = -(TAIL_WARM + 3); j < n_own + back; ++j)
-    if (wave == 11) {
-        TAIL_ITERATIONS {
-            const int ja = j - back;                                     // own block that is added this iteration
-            if (ja >= 0 && ja < n_own) {
-                const int b = block_of(ja);
-                // the steps of block b; with two tails also: has the other tail gathered block b + 1?  Both fetched by the
-                // same polls.
-                const unsigned long long *word = x_steps + (b & (SPLIT_RING - 1)) * BATCH + lane;
-                if (n_tails == 2)
-                    sh.xv[lane] = ring_wait<true>(word, b + 1, progress + (1 - tail), b + 1 < nb ? b + 2 : 0, &sh.dead, A.err);
-                else
-                    sh.xv[lane] = ring_wait<false>(word, b + 1, nullptr, 0, &sh.dead, A.err);
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (polls still in flight are not waited for)
-                if (lane == 0) __hip_atomic_store(&sh.xflag, ja + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-            __syncthreads();
+    constexpr int POLLER = TAIL_GROUPS * TAIL_WAVES, RESOLVER = POLLER + 1;
+    if (wave == POLLER) {
+        for (int a = 0; a < nb; ++a) {
+            // (block a + LAG's partial sums, without which there are no steps of its own, leave after a's steps were read)
+            sh.xv[a & (LAG - 1)][lane] = ring_wait<1>(x_steps + (a & (SPLIT_RING - 1)) * BATCH + lane, 0, a + 1, &sh.dead, A.err);
+            raise_flag(&sh.steps_ready, a + 1);
         }
-    } else if (wave == 9) {
+    } else if (wave >= RESOLVER) {
+        const int grp = wave - RESOLVER;
+        if (grp >= TAIL_GROUPS) return;
+        const int n_own = (nb - grp + TAIL_GROUPS - 1) / TAIL_GROUPS;
         RowResolver resolver;
-        TAIL_ITERATIONS {
-            // publishes the rows of own block j + TAIL_WARM + 1
-            resolver.step(rows, TAIL_RING - 1, l_desc, l_prefix, S, pk, j + TAIL_WARM - 2, tail, n_tails, n_own, lane, A.err, false);
-            __syncthreads();
+        for (int x = -5; x + 3 < n_own; ++x) {
+            if (x + 3 >= TAIL_RING) wait_flag(&sh.loaded[grp], TAIL_WAVES * (x + 3 - TAIL_RING + 1));      // the slot is free
+            resolver.step(sh.rows[grp], TAIL_RING - 1, l_desc, l_prefix, S, pk, x, grp, TAIL_GROUPS, n_own, lane, A.err, false);
+            if (x + 3 >= 0) raise_flag(&sh.rows_ready[grp], x + 4);
         }
-    } else if (wave == 10) {
-        TAIL_ITERATIONS {
-            // one touch per 64 bytes of the entries of own block j + TAIL_WARM (published last iteration);
-            // nothing is kept
-            if (j + TAIL_WARM >= 0 && j + TAIL_WARM < n_own) {
-                const RowSlot &r = rows[(j + TAIL_WARM) & (TAIL_RING - 1)][lane];
-                if (r.len > 0) {
-                    float sink = 0.f;
-#pragma unroll
-                    for (int o = 0; o < GRAM_MAX_ROW; o += 16) {
-                        const int e = min(o, r.len - 1);
-                        sink += gld(r.val + e) + __int_as_float(gld(r.col + e));
-                    }
-                    sink += gld(r.val + r.len - 1) + __int_as_float(gld(r.col + r.len - 1));
-                    asm volatile("" ::"v"(sink));
-                }
-            }
-            __syncthreads();
-        }
-    } else if (wave == 0) {
-        TAIL_ITERATIONS { __syncthreads(); }
     } else {
-        // st[0]: the own block that is gathered (j); st[back]: the one that is added (j - back)
-        int in_c[TE], st_c[3][TE];
-        float in_v[TE], st_v[3][TE];
+        const int grp = wave / TAIL_WAVES, gl = tid & (TAIL_WAVES * 64 - 1), rho = gl / TAIL_LPR, sub = gl & (TAIL_LPR - 1);
+        static_assert(TE % 6 == 0, "entries are loaded four and two at a time");
+        int in_c[TE];
+        float in_v[TE], in_y = 0.f;
+        int in_n = 0;                                // entries of this lane's that are inside the row
+        auto request = [&](int b) __attribute__((always_inline)) {
+            wait_flag(&sh.rows_ready[grp], b / TAIL_GROUPS + 1);
+            const RowSlot &r = sh.rows[grp][b / TAIL_GROUPS & (TAIL_RING - 1)][rho];
+            const int at = max(r.len - TE * TAIL_LPR, 0) + sub * TE;
+            const int32_t *cp = r.col + at;
+            const float *vp = r.val + at;
+            in_n = r.len - at;
+            in_y = LOSS == 1 ? 1.f : r.y;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (lane == 0) atomicAdd(&sh.loaded[grp], 1);
 #pragma unroll
-        for (int e = 0; e < TE; ++e) {
-            in_c[e] = 0; in_v[e] = 0.f;
+            for (int e = 0; e < TE; e += 6) {
+                const int4_a4 c4 = gld4(cp + e);
+                const int2_a4 c2 = gld2(cp + e + 4);
+                const float4_a4 v4 = gld4(vp + e);
+                const float2_a4 v2 = gld2(vp + e + 4);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) { st_c[k][e] = 0; st_v[k][e] = 0.f; }
-        }
-        int in_len = 0, in_base = 0, hb_target = 0;
-        TAIL_ITERATIONS {
-            // 1. this lane's segment of the row of own block j + 1: the last TE * LPR entries
-            if (j + 1 >= 0 && j + 1 < n_own) {
-                const RowSlot &r = rows[(j + 1) & (TAIL_RING - 1)][rho];
-                in_len = r.len;
-                in_base = max(in_len - TE * LPR, 0);
-                const int32_t *cp = r.col + in_base + sub;
-                const float *vp = r.val + in_base + sub;
+                for (int q = 0; q < 4; ++q) { in_c[e + q] = c4[q]; in_v[e + q] = v4[q]; }
 #pragma unroll
-                for (int e = 0; e < TE; ++e) { in_c[e] = gld(cp + e * LPR); in_v[e] = gld(vp + e * LPR); }
-            } else {
-                in_len = 0;
+                for (int q = 0; q < 2; ++q) { in_c[e + 4 + q] = c2[q]; in_v[e + 4 + q] = v2[q]; }
             }
-            // 2. the steps of own block j - back have arrived: it is added to the private vector
-            const int ja = j - back;
-            if (ja >= 0 && ja < n_own) {
-                const RowSlot &r = rows[ja & (TAIL_RING - 1)][rho];
-                wait_flag(&sh.xflag, ja + 1);
-                const float dl = sh.xv[rho];
-                if (r.len > 0 && dl != 0.f) {
-                    const float coef = dl * (LOSS == 1 ? 1.f : r.y) * sc.inv_c;
-#pragma unroll
-                    for (int e = 0; e < TE; ++e) {
-                        const int c = back == 1 ? st_c[1][e] : st_c[2][e];
-                        const float v = back == 1 ? st_v[1][e] : st_v[2][e];
-                        if (v != 0.f) unsafeAtomicAdd(&u[c], coef * v);
-                    }
-                }
-            }
-            // 3. ... by every wavefront, before the next block is gathered
-            hb_target += HELPER_WAVES;
-            helper_barrier(&sh.hb, hb_target);
-            // 4. gather own block j and hand the partial sums over
-            if (j >= 0 && j < n_own) {
-                float got[TE];
-#pragma unroll
-                for (int e = 0; e < TE; ++e) {
-                    got[e] = 0.f;
-                    if (st_v[0][e] != 0.f) got[e] = ld_l2(u + st_c[0][e]);
-                }
-                // The values are here, and this wavefront's adds of step 2 are performed: once that holds for all helper
-                // wavefronts, the other tail may add the block before this one and gather the block after it.
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                if (lane == 0 && atomicAdd(&sh.gcount, 1) + 1 == HELPER_WAVES * (j + 1))
-                    __hip_atomic_store(progress + tail, (unsigned long long)(block_of(j) + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                float part = 0.f;
-#pragma unroll
-                for (int e = 0; e < TE; ++e) part += st_v[0][e] * got[e];
-                part = sum_over_row_lanes(part);
-                const int b = block_of(j);
-                if (sub == 0) ring_put(x_parts + (b & (SPLIT_RING - 1)) * BATCH + rho, part, b + 1);
-            }
-            // 5. move the entry sets one stage on; the incoming set is masked to the row's length and to the
-            //    tails' columns
+        };
+        if (grp < nb) request(grp);
+        int bar_target = 0;
+        for (int b = grp; b < nb + lag; b += TAIL_GROUPS) {
+            // 1. block b's entries, as far as they are inside the row and in this tail's columns; those of b + 2 are asked for
+            int g_c[TE];
+            float g_v[TE];
+            const float y = in_y;
 #pragma unroll
             for (int e = 0; e < TE; ++e) {
-                st_c[2][e] = st_c[1][e]; st_v[2][e] = st_v[1][e];
-                st_c[1][e] = st_c[0][e]; st_v[1][e] = st_v[0][e];
-                const bool live = in_base + sub + e * LPR < in_len && in_c[e] >= n_hot;
-                st_c[0][e] = live ? in_c[e] : 0;
-                st_v[0][e] = live ? in_v[e] : 0.f;
+                const bool live = b < nb && e < in_n && in_c[e] >= n_hot && (in_c[e] >> TAIL_LINE_LOG2 & 1) == tail;
+                g_c[e] = live ? in_c[e] : 0;
+                g_v[e] = live ? in_v[e] : 0.f;
             }
-            __syncthreads();
+            if (b + TAIL_GROUPS < nb) request(b + TAIL_GROUPS);
+            // 2. this group's turn: block b - lag is added
+            const int a = b - lag;
+            TailEntry *slot = kept + (size_t)(b & (LAG - 1)) * TE * (BATCH * TAIL_LPR) + gl;
+            TailEntry add[TE];
+            float coef = 0.f;
+            if (a >= 0 && a < nb) {
+                const TailEntry *from = kept + (size_t)(a & (LAG - 1)) * TE * (BATCH * TAIL_LPR) + gl;
+#pragma unroll
+                for (int e = 0; e < TE; ++e) add[e] = from[e * (BATCH * TAIL_LPR)];
+                wait_flag(&sh.steps_ready, a + 1);
+                coef = sh.xv[a & (LAG - 1)][rho] * sc.inv_c;
+            }
+            wait_flag(&sh.issued, TAIL_WAVES * b);
+            if (coef != 0.f) {
+#pragma unroll
+                for (int e = 0; e < TE; ++e)
+                    if (add[e].val != 0.f) unsafeAtomicAdd(&u[add[e].col], coef * add[e].val);
+            }
+            // 3. ... by every wavefront of the group, before block b is gathered
+            asm volatile("" ::: "memory");
+            bar_target += TAIL_WAVES;
+            helper_barrier_lds(&sh.bar[grp], bar_target);
+            float got[TE];
+#pragma unroll
+            for (int e = 0; e < TE; ++e) {
+                got[e] = 0.f;
+                if (g_v[e] != 0.f) got[e] = ld_l2(u + g_c[e]);
+            }
+            asm volatile("" ::: "memory");
+            if (lane == 0) atomicAdd(&sh.issued, 1);
+            // 4. the other group's turn; the partial sums are handed over when they are here
+            if (b < nb) {
+#pragma unroll
+                for (int e = 0; e < TE; ++e) slot[e * (BATCH * TAIL_LPR)] = TailEntry{g_c[e], g_v[e] * y};
+                float part = 0.f;
+#pragma unroll
+                for (int e = 0; e < TE; ++e) part += g_v[e] * got[e];
+                part = sum_over_quad(part);
+                if (sub == 0) ring_put(x_parts + (b & (SPLIT_RING - 1)) * BATCH + rho, part, b + 1);
+            }
         }
     }
-#undef TAIL_ITERATIONS
 }
 
 // Workgroup role * k_pad + k: role 0 is the head of solver k, roles 1 .. n_tails are its tails (k_pad is a
 // multiple of the number of L2 partitions workgroups are dealt over, so all of them share one).
 // xchg_all: SPLIT_WORDS zeroed 64-bit words per solver: the ring of steps, one ring of partial dot products
-// per tail, the tails' progress words.
-// Dynamic LDS: BatchedShared, then max_list chunk descriptors, max_list local-row prefixes, then (at byte
-// offset hot_off) n_hot doubles in the head, the resolved rows in a tail.
+// per tail.
+// Dynamic LDS: in the head BatchedShared, then max_list chunk descriptors, max_list local-row prefixes, then (at byte
+// offset hot_off) n_hot doubles; in a tail TailShared, the kept entries, then the same lists.
 template <int LOSS, int TE>
 __global__ __launch_bounds__(SPLIT_THREADS) void sdca_batched_split(SplitArgs A, int k_pad)
 {

@@ -1,0 +1,70 @@
+"""Two tail workgroups per solver, whose gathers leave out the three latest blocks: what blocks b - 2 and b - 3 add comes through
+pairs of rows.  Solvers of one to a few blocks, blocks of hundreds of pairs, blocks of more than a list holds, against the oracle."""
+import numpy as np
+import pytest
+
+from harness import TOL_DW, dw_floor, gap_tolerance, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def _uniform(g, n, d, m):
+    return [np.sort(g.choice(d, m, replace=False)) for _ in range(n)], [g.permutation(n) for _ in range(2)]
+
+
+def _groups(g, n, size=8):
+    """24 popular columns and 24 that `size` rows hold in common; half of a group two blocks behind the other half."""
+    d = 9000 + 24 * (-(-n // size))
+    cols = [np.sort(np.concatenate([g.choice(9000, 24, replace=False), 9000 + 24 * (i // size) + np.arange(24)])) for i in range(n)]
+    orders = []
+    for _ in range(2):
+        sets = np.array_split(g.permutation(-(-n // size)), max(1, n // 256))
+        order = []
+        for s in sets:                       # four blocks: first halves in two of them, second halves in the other two
+            rows = [np.arange(size * k, min(n, size * k + size)) for k in s]
+            order += [np.concatenate([r[:size // 2] for r in rows]), np.concatenate([r[size // 2:] for r in rows])]
+        orders.append(np.concatenate(order))
+    return d, cols, orders
+
+
+CASES = [("few_%d" % n, n, "hinge") for n in (1, 64, 65, 128, 129, 192, 193, 256, 257, 321, 449)]
+CASES += [(name, n, loss) for name, n in (("sets", 4000), ("too_many", 4133)) for loss in ("hinge", "squared", "logistic")]
+
+
+@pytest.mark.parametrize("name,n,loss", CASES)
+def test_pairs(oracle_mod, name, n, loss):
+    import torch
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    assert torch.cuda.is_available()
+    print("\ncase pairs %s n=%d %s" % (name, n, loss), flush=True)
+    g = np.random.default_rng(31)
+    if name == "too_many":
+        d, cols, orders = _groups(g, n)
+    else:
+        d = 60000 if n < 1000 else 16400     # (half of the columns unpopular: as many pairs as uniform columns can give)
+        cols, orders = _uniform(g, n, d, 48 if n < 1000 else 40)
+    rp = np.concatenate([[0], np.cumsum([c.size for c in cols])]).astype(np.int64)
+    col = np.concatenate(cols).astype(np.int32)
+    val = (g.standard_normal(col.size) / 7.0).astype(np.float32)
+    y = (np.where(g.random(n) < 0.5, -1.0, 1.0) if loss != "squared" else g.standard_normal(n)).astype(np.float32)
+    # (two solvers, one of which may have no rows, unless all rows are to be in one)
+    K = 1 if name == "too_many" else 2
+    p = Problem(name, loss, n, d, 1.0 / n, y, np.array([0, n], dtype=np.int64), row_ptr=rp, col=col, val=val)
+    table = np.zeros(1, dtype=np.int32)
+    o, r = oracle_mod.OracleCoCoA.from_problem(p), binding.ChicleRound.from_problem(p, max_solvers=K)
+    o.assign(K, table)
+    r.assign(K, table)
+    assert r.debug_solver()[:2] == ("batched", 3)
+    for order in orders:
+        perms = [order] + [np.empty(0, dtype=np.int64)] * (K - 1)
+        ref = o.local_epoch(perms)
+        r.local_epoch(r.upload_perm(perms))
+        e = rel_l2(r.get_delta_w(0), ref[0], dw_floor(float(np.linalg.norm(o.w))))
+        print("update %.2e" % e, flush=True)
+        assert e <= TOL_DW
+        o.aggregate()
+        r.aggregate()
+        got, want = r.gap(), o.gap()
+        assert abs(got[2] - want[2]) <= gap_tolerance(want[2], want[0])
+    r.close()
