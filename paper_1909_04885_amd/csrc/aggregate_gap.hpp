@@ -70,30 +70,60 @@ __global__ __launch_bounds__(256) void delta_w_out(const float *u_all, int64_t l
     }
 }
 
-// The merge where private vectors are stored compactly (see layout.hpp).  A workgroup takes 256 consecutive
-// words of 32 columns (8192 columns) and walks the solvers: a solver's entries for these columns are one
+// The merge where private vectors are stored compactly (see layout.hpp).  A workgroup takes 64 consecutive
+// words of 32 columns (2048 columns) and walks the solvers: a solver's entries for these columns are one
 // contiguous run of its compact vector, which the workgroup reads (and clears) with coalesced accesses into
-// LDS; each thread then picks the entries of its own word out of the run, in order, by the word's bits.
+// LDS; each thread then picks the entries of its own quarter of a word out of the run, in order, by the word's bits.  (256 words
+// to a workgroup, a thread each, left small jobs a few workgroups with long loops: six solvers over 20k columns 18.5 us, and 5 for the mirror, 7.8 now with it.)
 // u_off[k]: where solver k's compact vector starts in u.  Reads and clears only what the solvers touched.
 // Where there are few words (few workgroups), the solvers are divided over gridDim.y slices as well; the
-// slices then add their sums into the double-precision vector with atomic adds and the float mirror is
-// refreshed by a pass of its own (mirror_from_double).
-constexpr int AGG_WORDS = 256;                       // words (threads) per workgroup
-__global__ __launch_bounds__(AGG_WORDS) void aggregate_compact(double *w64, float *w32, float *u, const int64_t *__restrict__ u_off,
-                                                               const unsigned *__restrict__ bits, const int32_t *__restrict__ pref,
-                                                               int64_t words, int64_t d, int K, float inv_sigma, double l1)
+// slices then add their sums into the double-precision vector with atomic adds, and the one that is done last refreshes the
+// float mirror (tickets[blockIdx.x]: zero, and left so; a pass of its own over the mirror took 5 us).
+constexpr int AGG_THREADS = 256, AGG_WORDS = 64;     // threads and words per workgroup
+constexpr int AGG_THIN_WORDS = 256;                  // ... of aggregate_compact_thin
+static_assert(AGG_THIN_WORDS == AGG_THREADS, "a thread per word");
+template <int WORDS>
+__device__ __forceinline__ void mirror_by_last_slice(const double *w64, float *w32, int64_t d, double l1, unsigned *tickets)
 {
-    __shared__ float run[AGG_WORDS * 33];            // a run is at most all columns of the workgroup (32 per word;
-                                                     // 33: the sums are laid out one word per padded row at the end)
+    __shared__ int last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this thread's adds are performed
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(tickets + blockIdx.x, 1u) + 1u == gridDim.y;
+    __syncthreads();
+    if (!last) return;
+    if (threadIdx.x == 0) __hip_atomic_store(tickets + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int64_t c0 = (int64_t)blockIdx.x * WORDS * 32 + threadIdx.x;
+    for (int i = 0; i < WORDS * 32 / AGG_THREADS; i += 8) {
+        double x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int64_t c = c0 + (i + q) * AGG_THREADS;
+            x[q] = c < d ? __hip_atomic_load(w64 + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int64_t c = c0 + (i + q) * AGG_THREADS;
+            if (c < d) w32[c] = (float)soft_threshold(x[q], l1);
+        }
+    }
+}
+
+__global__ __launch_bounds__(AGG_THREADS) void aggregate_compact(double *w64, float *w32, float *u, const int64_t *__restrict__ u_off,
+                                                                 const unsigned *__restrict__ bits, const int32_t *__restrict__ pref,
+                                                                 int64_t words, int64_t d, int K, float inv_sigma, double l1, unsigned *tickets)
+{
+    constexpr int PER = 8, PARTS = 32 / PER;         // columns of a thread, threads of a word
+    static_assert(AGG_WORDS * PARTS == AGG_THREADS, "a thread per quarter of a word");
+    __shared__ float run[AGG_WORDS * 32];            // a run is at most all columns of the workgroup
     __shared__ unsigned touched[AGG_WORDS];
     __shared__ int run_begin, run_end;
-    const int tid = threadIdx.x;
-    const int64_t j = (int64_t)blockIdx.x * AGG_WORDS + tid;
+    const int tid = threadIdx.x, word = tid / PARTS, part = tid % PARTS;
+    const int64_t j = (int64_t)blockIdx.x * AGG_WORDS + word;
     const bool live = j < words;
-    const int last = (int)min((int64_t)AGG_WORDS, words - (int64_t)blockIdx.x * AGG_WORDS) - 1;   // last live thread
-    float acc[32];
+    const int last = (int)min((int64_t)AGG_WORDS, words - (int64_t)blockIdx.x * AGG_WORDS) - 1;   // last live word
+    float acc[PER];
 #pragma unroll
-    for (int b = 0; b < 32; ++b) acc[b] = 0.f;
+    for (int b = 0; b < PER; ++b) acc[b] = 0.f;
     unsigned any = 0;
     // (the next solver's word and prefix are requested before this solver's run is waited for)
     const int per = (K + (int)gridDim.y - 1) / (int)gridDim.y;
@@ -105,29 +135,36 @@ __global__ __launch_bounds__(AGG_WORDS) void aggregate_compact(double *w64, floa
         const int pf = pf_next;
         if (k + 1 < k1 && live) { m_next = bits[(int64_t)(k + 1) * words + j]; pf_next = pref[(int64_t)(k + 1) * words + j]; }
         if (tid == 0) run_begin = pf;
-        if (tid == last) run_end = pf + __popc(m);
+        if (word == last) run_end = pf + __popc(m);
         __syncthreads();
         const int begin = run_begin, len = run_end - begin;
         float *uk = u + u_off[k] + begin;
-        for (int i = tid; i < len; i += AGG_WORDS) { run[i] = uk[i]; uk[i] = 0.f; }
+        float x[AGG_WORDS * 32 / AGG_THREADS];       // all loads in flight
+#pragma unroll
+        for (int q = 0; q < AGG_WORDS * 32 / AGG_THREADS; ++q) x[q] = tid + q * AGG_THREADS < len ? uk[tid + q * AGG_THREADS] : 0.f;
+#pragma unroll
+        for (int q = 0; q < AGG_WORDS * 32 / AGG_THREADS; ++q)
+            if (tid + q * AGG_THREADS < len) { run[tid + q * AGG_THREADS] = x[q]; uk[tid + q * AGG_THREADS] = 0.f; }
         __syncthreads();
         any |= m;
-        int r = pf - begin;
+        int r = pf - begin + __popc(m & ((1u << (PER * part)) - 1u));
 #pragma unroll
-        for (int b = 0; b < 32; ++b)
-            if (m & (1u << b)) acc[b] += run[r++];
+        for (int b = 0; b < PER; ++b)
+            if (m & (1u << (PER * part + b))) acc[b] += run[r++];
         __syncthreads();                             // the run is overwritten by the next solver's
     }
     // the sums go through LDS so that the shared vector is updated with coalesced accesses
-    touched[tid] = any;
+    if (part == 0) touched[word] = any;
 #pragma unroll
-    for (int b = 0; b < 32; ++b) run[tid * 33 + b] = acc[b];
+    for (int b = 0; b < PER; b += 4) *reinterpret_cast<float4 *>(run + tid * PER + b) = make_float4(acc[b], acc[b + 1], acc[b + 2], acc[b + 3]);
     __syncthreads();
     const int64_t c0 = (int64_t)blockIdx.x * AGG_WORDS * 32;
-    for (int i = tid; i < AGG_WORDS * 32; i += AGG_WORDS) {
+#pragma unroll
+    for (int q = 0; q < AGG_WORDS * 32 / AGG_THREADS; ++q) {
+        const int i = tid + q * AGG_THREADS;
         const int64_t c = c0 + i;
         if (c < d && (touched[i >> 5] & (1u << (i & 31)))) {
-            const double add = (double)(run[(i >> 5) * 33 + (i & 31)] * inv_sigma);
+            const double add = (double)(run[i] * inv_sigma);
             if (gridDim.y == 1) {
                 const double x = w64[c] + add;
                 w64[c] = x;
@@ -137,6 +174,7 @@ __global__ __launch_bounds__(AGG_WORDS) void aggregate_compact(double *w64, floa
             }
         }
     }
+    if (gridDim.y > 1) mirror_by_last_slice<AGG_WORDS>(w64, w32, d, l1, tickets);
 }
 
 // The same merge for thinly occupied vectors (long rows over many columns: a solver holds a few of every
@@ -146,14 +184,14 @@ __global__ __launch_bounds__(AGG_WORDS) void aggregate_compact(double *w64, floa
 // pieces of the run, so the lines are shared inside the wavefront - and keeps its 32 sums in LDS (row tid of
 // a padded array, touched by that thread alone until the end), with no barrier inside the walk over the
 // solvers; the next solver's word and prefix are requested before this solver's entries are waited for.
-__global__ __launch_bounds__(AGG_WORDS) void aggregate_compact_thin(double *w64, float *w32, float *u, const int64_t *__restrict__ u_off,
+__global__ __launch_bounds__(AGG_THIN_WORDS) void aggregate_compact_thin(double *w64, float *w32, float *u, const int64_t *__restrict__ u_off,
                                                                     const unsigned *__restrict__ bits, const int32_t *__restrict__ pref,
-                                                                    int64_t words, int64_t d, int K, float inv_sigma, double l1)
+                                                                    int64_t words, int64_t d, int K, float inv_sigma, double l1, unsigned *tickets)
 {
-    __shared__ float sums[AGG_WORDS * 33];
-    __shared__ unsigned touched[AGG_WORDS];
+    __shared__ float sums[AGG_THIN_WORDS * 33];
+    __shared__ unsigned touched[AGG_THIN_WORDS];
     const int tid = threadIdx.x;
-    const int64_t j = (int64_t)blockIdx.x * AGG_WORDS + tid;
+    const int64_t j = (int64_t)blockIdx.x * AGG_THIN_WORDS + tid;
     const bool live = j < words;
     float *mine = sums + tid * 33;
 #pragma unroll
@@ -186,8 +224,8 @@ __global__ __launch_bounds__(AGG_WORDS) void aggregate_compact_thin(double *w64,
     }
     touched[tid] = any;
     __syncthreads();
-    const int64_t c0 = (int64_t)blockIdx.x * AGG_WORDS * 32;
-    for (int i = tid; i < AGG_WORDS * 32; i += AGG_WORDS) {
+    const int64_t c0 = (int64_t)blockIdx.x * AGG_THIN_WORDS * 32;
+    for (int i = tid; i < AGG_THIN_WORDS * 32; i += AGG_THIN_WORDS) {
         const int64_t c = c0 + i;
         if (c < d && (touched[i >> 5] & (1u << (i & 31)))) {
             const double add = (double)(sums[(i >> 5) * 33 + (i & 31)] * inv_sigma);
@@ -200,6 +238,7 @@ __global__ __launch_bounds__(AGG_WORDS) void aggregate_compact_thin(double *w64,
             }
         }
     }
+    if (gridDim.y > 1) mirror_by_last_slice<AGG_THIN_WORDS>(w64, w32, d, l1, tickets);
 }
 
 __global__ __launch_bounds__(256) void mirror_from_double(const double *__restrict__ w64, float *w32, int64_t d, double l1)
@@ -234,19 +273,124 @@ __device__ __forceinline__ double wave_sum_d(double x)
     return x;
 }
 
-// Workgroup sum of two doubles -> thread 0 writes them.  256 threads.
-__device__ __forceinline__ void block_sum2_store(double a, double b, double *out_a, double *out_b)
+// What the last kernel of the gap does beside its rows.  Its workgroups with blockIdx.y >= n_chunks sum |w|^2 and |w|_1 (n_w
+// partials); every workgroup leaves its two partial sums, and the one that leaves them last adds all of them up in a fixed
+// order: out[0] = sum loss, out[1] = sum conj, out[2] = |w|^2, out[3] = the kernels' error flag, out[4] = |w|_1.  out may be
+// host memory mapped into the device's address space.  (Kernels of their own for the norms and for the end: 500000 x 28 in
+// all 34 us, 17.9 now; 4096 x 256 16 and 6.4; sparse rows, 30000 x 20k, 24 and 18.8.)  tickets: nullptr where only the rows' residuals are wanted; else zero, and left so.  Adds to
+// one address take 13 ns each, so workgroups are counted in GAP_GROUPS groups, and the groups that are complete at
+// tickets[GAP_GROUPS * TICKET_LINE].
+constexpr int GAP_GROUPS = 32, TICKET_LINE = 32;     // (counters 128 bytes apart)
+constexpr int GAP_TICKETS = (GAP_GROUPS + 1) * TICKET_LINE;
+struct GapEnd {
+    unsigned *tickets;
+    const double *v;
+    int64_t d;
+    double *part_wsq, *part_wabs;
+    int n_w, n_chunks;
+    const int *err;
+    double *out;
+};
+// Partial sums go past the caches of the compute units and of their group, so that the last workgroup finds them.
+__device__ __forceinline__ void st_part(double *p, double x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double ld_part(const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Workgroup sums of M doubles, in all threads; N: threads.
+template <int N, int M>
+__device__ __forceinline__ void block_sum(double (&v)[M])
 {
-    __shared__ double ra[4], rb[4];
-    a = wave_sum_d(a);
-    b = wave_sum_d(b);
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) { ra[wave] = a; rb[wave] = b; }
+    __shared__ double r[M][N / 64];
+#pragma unroll
+    for (int k = 0; k < M; ++k) v[k] = wave_sum_d(v[k]);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int k = 0; k < M; ++k) r[k][threadIdx.x >> 6] = v[k];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        *out_a = ra[0] + ra[1] + ra[2] + ra[3];
-        *out_b = rb[0] + rb[1] + rb[2] + rb[3];
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+        v[k] = 0.0;
+#pragma unroll
+        for (int i = 0; i < N / 64; ++i) v[k] += r[k][i];
     }
+}
+
+// A thread's share of the sums of two partial arrays, eight loads of each in flight.
+template <int N>
+__device__ __forceinline__ void add_parts(const double *pa, const double *pb, int n, double &a, double &b)
+{
+    for (int i = threadIdx.x; i < n; i += 8 * N) {
+        double x[8], y[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            x[q] = i + q * N < n ? ld_part(pa + i + q * N) : 0.0;
+            y[q] = i + q * N < n ? ld_part(pb + i + q * N) : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) { a += x[q]; b += y[q]; }
+    }
+}
+
+// The end of a workgroup of a row pass: its sums, and those of all if it is the last.
+template <int N>
+__device__ __forceinline__ void gap_block_end(double a, double b, double *out_a, double *out_b, double *part_loss, double *part_conj, const GapEnd &E)
+{
+    __shared__ int last;
+    double own[2] = {a, b};
+    block_sum<N>(own);
+    if (threadIdx.x == 0) {
+        if (out_a) { st_part(out_a, own[0]); st_part(out_b, own[1]); }
+        if (E.tickets) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const unsigned all = gridDim.x * gridDim.y, group = (blockIdx.y * gridDim.x + blockIdx.x) % GAP_GROUPS;
+            const unsigned members = (all - group + GAP_GROUPS - 1) / GAP_GROUPS, groups = min(all, (unsigned)GAP_GROUPS);
+            unsigned *mine = E.tickets + group * TICKET_LINE, *root = E.tickets + GAP_GROUPS * TICKET_LINE;
+            last = 0;
+            if (atomicAdd(mine, 1u) + 1u == members) {
+                __hip_atomic_store(mine, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (atomicAdd(root, 1u) + 1u == groups) {
+                    __hip_atomic_store(root, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    last = 1;
+                }
+            }
+        }
+    }
+    if (!E.tickets) return;
+    __syncthreads();
+    if (!last) return;
+    double sums[4] = {0.0, 0.0, 0.0, 0.0};           // loss, conj, |w|^2, |w|_1
+    add_parts<N>(E.part_wsq, E.part_wabs, E.n_w, sums[2], sums[3]);
+    add_parts<N>(part_loss, part_conj, (int)gridDim.x * E.n_chunks, sums[0], sums[1]);
+    block_sum<N>(sums);
+    if (threadIdx.x == 0) {
+        E.out[0] = sums[0];
+        E.out[1] = sums[1];
+        E.out[2] = sums[2];
+        E.out[3] = (double)*E.err;
+        E.out[4] = sums[3];
+    }
+}
+
+// |w|^2 and |w|_1 partials in double (w = the soft-thresholded image of the double vector).
+template <int N>
+__device__ __forceinline__ void gap_w_block(double l1, double *part_loss, double *part_conj, const GapEnd &E)
+{
+    const int part = ((int)blockIdx.y - E.n_chunks) * (int)gridDim.x + (int)blockIdx.x;
+    double s = 0.0, t = 0.0;
+    if (part < E.n_w) {
+        const int64_t stride = (int64_t)E.n_w * N;
+        for (int64_t j = (int64_t)part * N + threadIdx.x; j < E.d; j += 4 * stride) {
+            double x[4];                             // four loads in flight per thread
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[q] = j + q * stride < E.d ? E.v[j + q * stride] : 0.0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double y = soft_threshold(x[q], l1);
+                s += y * y;
+                t += fabs(y);
+            }
+        }
+    }
+    gap_block_end<N>(s, t, part < E.n_w ? E.part_wsq + part : nullptr, E.part_wabs + part, part_loss, part_conj, E);
 }
 
 // Per-row loss and conjugate terms of the gap; also leaves the residual rw of every row in the chunk
@@ -281,13 +425,14 @@ __device__ __forceinline__ void gap_row_terms(RowState *st, WT z, double &s_loss
     }
 }
 
-// Grid: (workgroups per chunk, chunks).  Every group of LPR lanes walks rows of its chunk with a fixed
+// Grid: (workgroups per chunk, chunks and what GapEnd adds).  Every group of LPR lanes walks rows of its chunk with a fixed
 // stride and keeps two rows in flight.  Partial sums are indexed by the linear workgroup id.
 template <int LOSS, int LPR, typename WT>
 __global__ __launch_bounds__(256) void gap_rows_csr(const ChunkDev *__restrict__ chunks,
                                                     const WT *__restrict__ w, double l1,
-                                                    double *part_loss, double *part_conj)
+                                                    double *part_loss, double *part_conj, GapEnd E)
 {
+    if ((int)blockIdx.y >= E.n_chunks) return gap_w_block<256>(l1, part_loss, part_conj, E);
     constexpr int GROUPS = 256 / LPR;
     const int sub = threadIdx.x % LPR;
     const int grp = threadIdx.x / LPR;
@@ -322,7 +467,7 @@ __global__ __launch_bounds__(256) void gap_rows_csr(const ChunkDev *__restrict__
         }
     }
     const int part = blockIdx.y * gridDim.x + blockIdx.x;
-    block_sum2_store(s_loss, s_conj, &part_loss[part], &part_conj[part]);
+    gap_block_end<256>(s_loss, s_conj, part_loss + part, part_conj + part, part_loss, part_conj, E);
 }
 
 // ---- the row pass for long rows over a shared vector far larger than a cache ------------------------------
@@ -411,11 +556,12 @@ __global__ __launch_bounds__(256) void gap_rows_sliced(const ChunkDev *__restric
     }
 }
 
-// Grid: (workgroups per chunk, chunks); a thread per row.  Partial sums by linear workgroup id, as above.
+// Grid: (workgroups per chunk, chunks and what GapEnd adds); a thread per row.  Partial sums by linear workgroup id, as above.
 template <int LOSS, typename WT>
-__global__ __launch_bounds__(256) void gap_rows_from_z(const ChunkDev *__restrict__ chunks, WT *z,
-                                                       double *part_loss, double *part_conj)
+__global__ __launch_bounds__(256) void gap_rows_from_z(const ChunkDev *__restrict__ chunks, WT *z, double l1,
+                                                       double *part_loss, double *part_conj, GapEnd E)
 {
+    if ((int)blockIdx.y >= E.n_chunks) return gap_w_block<256>(l1, part_loss, part_conj, E);
     const ChunkDev &ch = chunks[blockIdx.y];
     double s_loss = 0.0, s_conj = 0.0;
     for (int r = blockIdx.x * 256 + threadIdx.x; r < ch.n_rows; r += gridDim.x * 256) {
@@ -424,7 +570,7 @@ __global__ __launch_bounds__(256) void gap_rows_from_z(const ChunkDev *__restric
         gap_row_terms<LOSS, WT>(ch.st + r, zi, s_loss, s_conj);
     }
     const int part = blockIdx.y * gridDim.x + blockIdx.x;
-    block_sum2_store(s_loss, s_conj, &part_loss[part], &part_conj[part]);
+    gap_block_end<256>(s_loss, s_conj, part_loss + part, part_conj + part, part_loss, part_conj, E);
 }
 
 // The same row pass where the columns are numbered by popularity: the first n_hot entries of w are
@@ -437,11 +583,11 @@ constexpr int GAP_HOT_MAX_LPR = 16;         // lanes per row at most; a lane tak
 template <int LOSS, int LPR, typename WT>
 __global__ __launch_bounds__(GAP_HOT_THREADS) void gap_rows_csr_hot(const ChunkDev *__restrict__ chunks,
                                                                     const WT *__restrict__ w, double l1, int n_hot,
-                                                                    double *part_loss, double *part_conj)
+                                                                    double *part_loss, double *part_conj, GapEnd E)
 {
+    if ((int)blockIdx.y >= E.n_chunks) return gap_w_block<GAP_HOT_THREADS>(l1, part_loss, part_conj, E);
     extern __shared__ __align__(16) unsigned char gap_hot_raw[];
     WT *hot = reinterpret_cast<WT *>(gap_hot_raw);
-    __shared__ double ra[GAP_HOT_THREADS / 64], rb[GAP_HOT_THREADS / 64];
     // LPR lanes per row, as many whole rows per wavefront as fit (LPR need not divide 64: with rows of 40
     // entries ten lanes carry a row and six rows share a wavefront; the lanes left over idle)
     constexpr int ROWS_PER_WAVE = 64 / LPR;
@@ -504,26 +650,17 @@ __global__ __launch_bounds__(GAP_HOT_THREADS) void gap_rows_csr_hot(const ChunkD
             if (two) gap_row_terms<LOSS, WT>(ch.st + r1, z1, s_loss, s_conj);
         }
     }
-    s_loss = wave_sum_d(s_loss);
-    s_conj = wave_sum_d(s_conj);
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) { ra[wave] = s_loss; rb[wave] = s_conj; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double a = 0.0, b = 0.0;
-        for (int i = 0; i < GAP_HOT_THREADS / 64; ++i) { a += ra[i]; b += rb[i]; }
-        const int part = blockIdx.y * gridDim.x + blockIdx.x;
-        part_loss[part] = a;
-        part_conj[part] = b;
-    }
+    const int part = blockIdx.y * gridDim.x + blockIdx.x;
+    gap_block_end<GAP_HOT_THREADS>(s_loss, s_conj, part_loss + part, part_conj + part, part_loss, part_conj, E);
 }
 
 // Dense rows (ld floats each, 16-byte aligned): LPR lanes per row, four columns at a time.  Same grid as the sparse kernel.
 template <int LOSS, int LPR, typename WT>
 __global__ __launch_bounds__(256) void gap_rows_dense(const ChunkDev *__restrict__ chunks, int d, int ld,
                                                       const WT *__restrict__ w, double l1,
-                                                      double *part_loss, double *part_conj)
+                                                      double *part_loss, double *part_conj, GapEnd E)
 {
+    if ((int)blockIdx.y >= E.n_chunks) return gap_w_block<256>(l1, part_loss, part_conj, E);
     constexpr int GROUPS = 256 / LPR;
     const int sub = threadIdx.x % LPR;
     const int grp = threadIdx.x / LPR;
@@ -542,50 +679,7 @@ __global__ __launch_bounds__(256) void gap_rows_dense(const ChunkDev *__restrict
         if (sub == 0) gap_row_terms<LOSS, WT>(ch.st + r, z, s_loss, s_conj);
     }
     const int part = blockIdx.y * gridDim.x + blockIdx.x;
-    block_sum2_store(s_loss, s_conj, &part_loss[part], &part_conj[part]);
-}
-
-// |w|^2 and |w|_1 partials in double (w = the soft-thresholded image of the double vector).
-__global__ __launch_bounds__(256) void wsq_partial(const double *__restrict__ v, int64_t d, double l1,
-                                                   double *part_wsq, double *part_wabs)
-{
-    double s = 0.0, t = 0.0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < d; j += 4 * stride) {
-        double x[4];                                 // four loads in flight per thread
-#pragma unroll
-        for (int q = 0; q < 4; ++q) x[q] = j + q * stride < d ? v[j + q * stride] : 0.0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const double y = soft_threshold(x[q], l1);
-            s += y * y;
-            t += fabs(y);
-        }
-    }
-    block_sum2_store(s, t, &part_wsq[blockIdx.x], &part_wabs[blockIdx.x]);
-}
-
-// out[0] = sum loss, out[1] = sum conj, out[2] = |w|^2, out[3] = the kernels' error flag, out[4] = |w|_1; one workgroup,
-// fixed summation order.  out may be host memory mapped into the device's address space.
-__global__ __launch_bounds__(256) void gap_finish(const double *part_loss, const double *part_conj,
-                                                  int n_row_parts, const double *part_wsq, const double *part_wabs,
-                                                  int n_w_parts, const int *err, double *out)
-{
-    double a = 0.0, b = 0.0, c = 0.0, e = 0.0;
-    for (int i = threadIdx.x; i < n_row_parts; i += 256) { a += part_loss[i]; b += part_conj[i]; }
-    for (int i = threadIdx.x; i < n_w_parts; i += 256) { c += part_wsq[i]; e += part_wabs[i]; }
-    __shared__ double ra[4], rb[4], rc[4], re[4];
-    a = wave_sum_d(a); b = wave_sum_d(b); c = wave_sum_d(c); e = wave_sum_d(e);
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) { ra[wave] = a; rb[wave] = b; rc[wave] = c; re[wave] = e; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        out[0] = ra[0] + ra[1] + ra[2] + ra[3];
-        out[1] = rb[0] + rb[1] + rb[2] + rb[3];
-        out[2] = rc[0] + rc[1] + rc[2] + rc[3];
-        out[3] = (double)*err;
-        out[4] = re[0] + re[1] + re[2] + re[3];
-    }
+    gap_block_end<256>(s_loss, s_conj, part_loss + part, part_conj + part, part_loss, part_conj, E);
 }
 
 }  // namespace chicle

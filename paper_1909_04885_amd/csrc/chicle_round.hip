@@ -64,6 +64,7 @@ struct Seg {
 struct GapScratch {
     double *loss = nullptr, *conj = nullptr, *wsq = nullptr, *unused = nullptr;
     int parts = 0;            // length of loss[] and conj[]
+    bool finish = false;      // the pass also forms the norms and the gap's sums
 };
 
 // Scratch of chicle_gap_noalloc: a fixed array in the code object, one copy per GPU, kept until the process
@@ -152,6 +153,7 @@ struct chicle_ctx {
     double *gap_host = nullptr;       // 4 doubles of pinned host memory the gap's last kernel writes into ...
     double *gap_host_dev = nullptr;   // ... through this device address
     int *err_dev = nullptr;
+    unsigned *tickets_dev = nullptr;  // see n_tickets
     int *progress_dev = nullptr;      // per solver: block its batched pass has reached
     unsigned long long *split_ring_dev = nullptr;   // per solver: rings between the workgroups that share it
     unsigned long long *pair_list[2] = {nullptr, nullptr};   // per tile set: pairs of rows for the split solver, PAIR_CAP a tile,
@@ -279,6 +281,9 @@ int max_slices(int32_t d)
     return (int)(((int64_t)d + (1 << shift) - 1) >> shift);
 }
 
+// Counters of workgroups that are done: the gap's, and one per workgroup's columns for the merge.  Zero between kernels.
+size_t n_tickets(int32_t d) { return GAP_TICKETS + ((size_t)d + 32 * AGG_WORDS - 1) / (32 * AGG_WORDS); }
+
 size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_solvers, bool long_rows, bool compact,
                    int64_t n_total_entries_hint)
 {
@@ -299,6 +304,7 @@ size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_sol
     s += 2 * align_up(sizeof(int32_t) * (size_t)n_chunks);               // chunk_first, list_base
     s += 2 * align_up(sizeof(double) * (size_t)std::max(GAP_PARTS, 2 * n_chunks)) + 2 * align_up(sizeof(double) * WSQ_PARTS);
     s += align_up(sizeof(int));
+    s += align_up(sizeof(unsigned) * n_tickets(d));
     s += align_up(sizeof(long long) * 2 * (size_t)max_solvers);
     s += align_up(sizeof(int) * (size_t)max_solvers);
     s += align_up(sizeof(unsigned long long) * (size_t)SPLIT_WORDS * (size_t)max_solvers);   // rings of the split batched solver
@@ -802,19 +808,38 @@ int drop_ahead(chicle_ctx *c)
     return CHICLE_OK;
 }
 
+// What the workgroups of a row pass, grid_x per chunk of `threads`, do beside the rows, and how many rows of them that adds to
+// the grid.
+GapEnd gap_end(const chicle_ctx *c, const GapScratch &gs, int grid_x, int threads, unsigned *grid_y)
+{
+    GapEnd E{};
+    E.n_chunks = c->n_chunks;
+    *grid_y = (unsigned)c->n_chunks;
+    if (!gs.finish) return E;
+    E.tickets = c->tickets_dev;
+    E.v = c->w64; E.d = (int64_t)c->d;
+    E.part_wsq = gs.wsq; E.part_wabs = gs.unused;
+    E.n_w = std::min(grid_for(c->d, threads * 8, WSQ_PARTS * 256 / threads), grid_x * (65535 - c->n_chunks));
+    E.err = c->err_dev; E.out = c->gap_host_dev;
+    *grid_y += (unsigned)((E.n_w + grid_x - 1) / grid_x);
+    return E;
+}
+
 template <int LOSS, int LPRG, typename WT>
 void launch_gap_rows_t(chicle_ctx *c, int grid_x, const WT *w, const GapScratch &gs)
 {
-    const dim3 grid(grid_x, c->n_chunks);
+    unsigned gy;
+    const GapEnd E = gap_end(c, gs, grid_x, c->gap_hot_grid > 0 ? GAP_HOT_THREADS : 256, &gy);
+    const dim3 grid(grid_x, gy);
     if (c->gap_hot_grid > 0) {
         // lanes per row: the fewest that cover the longest row with 4 entries each
         const int n_hot = (int)std::min<int64_t>(c->d, GAP_HOT_BYTES / (int)sizeof(WT));
-        const dim3 hg(c->gap_hot_grid, c->n_chunks);
+        const dim3 hg(c->gap_hot_grid, gy);
         const size_t sh = n_hot * sizeof(WT);
         const int need = (c->max_row_len + 3) / 4;
 #define CHICLE_GAP_HOT(L)                                                                                   \
         hipLaunchKernelGGL((gap_rows_csr_hot<LOSS, L, WT>), hg, dim3(GAP_HOT_THREADS), sh, c->stream,      \
-                           c->chunks_dev, w, c->l1, n_hot, gs.loss, gs.conj)
+                           c->chunks_dev, w, c->l1, n_hot, gs.loss, gs.conj, E)
         if (need <= 4) CHICLE_GAP_HOT(4);
         else if (need <= 8) CHICLE_GAP_HOT(8);
         else if (need <= 10) CHICLE_GAP_HOT(10);
@@ -823,10 +848,10 @@ void launch_gap_rows_t(chicle_ctx *c, int grid_x, const WT *w, const GapScratch 
 #undef CHICLE_GAP_HOT
     } else if (c->dense)
         hipLaunchKernelGGL((gap_rows_dense<LOSS, LPRG, WT>), grid, dim3(256), 0, c->stream, c->chunks_dev,
-                           (int)c->d, dense_ld((int)c->d), w, c->l1, gs.loss, gs.conj);
+                           (int)c->d, dense_ld((int)c->d), w, c->l1, gs.loss, gs.conj, E);
     else
         hipLaunchKernelGGL((gap_rows_csr<LOSS, LPRG, WT>), grid, dim3(256), 0, c->stream, c->chunks_dev, w, c->l1,
-                           gs.loss, gs.conj);
+                           gs.loss, gs.conj, E);
 }
 
 // Squared loss: dot products in double against the double w (its steps cancel y - z - alpha down to the
@@ -852,13 +877,13 @@ void launch_gap_lpr(chicle_ctx *c, int grid, const GapScratch &gs)
 }
 
 // The row pass of the gap: z_i = x_i . w into the chunks, loss and conjugate partial sums.
-int run_row_pass(chicle_ctx *c, int *grid_out, const GapScratch &gs)
+int run_row_pass(chicle_ctx *c, const GapScratch &gs)
 {
     // workgroups per chunk: enough to fill the chip several times over, within the partial-sum arrays
     int max_rows = 1;
     for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
     const int rows_per_wg = 2 * (256 / c->gap_lpr);
-    int gx = std::min((max_rows + rows_per_wg - 1) / rows_per_wg, std::max(1, 8192 / c->n_chunks));
+    int gx = std::min((max_rows + rows_per_wg - 1) / rows_per_wg, std::max(1, 2048 / c->n_chunks));
     gx = std::max(1, std::min(gx, gs.parts / c->n_chunks));
     // popularity-numbered columns: frequent part of w from LDS, few large workgroups per chunk
     c->gap_hot_grid = 0;
@@ -873,26 +898,27 @@ int run_row_pass(chicle_ctx *c, int *grid_out, const GapScratch &gs)
         const int segs = (max_rows + SLICE_SEG - 1) / SLICE_SEG, n_items = segs * c->n_chunks;
         const unsigned blocks = (unsigned)((c->gap_slices + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS) * (unsigned)n_items;
         gx = std::max(1, std::min((max_rows + 255) / 256, gs.parts / c->n_chunks));
-        const dim3 fg(gx, c->n_chunks);
+        unsigned gy;
+        const GapEnd E = gap_end(c, gs, gx, 256, &gy);
+        const dim3 fg(gx, gy);
         if (c->loss == CHICLE_LOSS_HINGE) {
             float *z = (float *)c->slice_z_dev;
             hipLaunchKernelGGL(gap_rows_sliced<float>, dim3(blocks), dim3(256), 0, c->stream, c->chunks_dev, (const float *)c->w, c->l1,
                                c->slice_off_dev, c->n_total, c->gap_slices, segs, n_items, z);
-            hipLaunchKernelGGL((gap_rows_from_z<0, float>), fg, dim3(256), 0, c->stream, c->chunks_dev, z, gs.loss, gs.conj);
+            hipLaunchKernelGGL((gap_rows_from_z<0, float>), fg, dim3(256), 0, c->stream, c->chunks_dev, z, c->l1, gs.loss, gs.conj, E);
         } else {
             hipLaunchKernelGGL(gap_rows_sliced<double>, dim3(blocks), dim3(256), 0, c->stream, c->chunks_dev, (const double *)c->w64, c->l1,
                                c->slice_off_dev, c->n_total, c->gap_slices, segs, n_items, c->slice_z_dev);
             if (c->loss == CHICLE_LOSS_SQUARED)
-                hipLaunchKernelGGL((gap_rows_from_z<1, double>), fg, dim3(256), 0, c->stream, c->chunks_dev, c->slice_z_dev, gs.loss, gs.conj);
+                hipLaunchKernelGGL((gap_rows_from_z<1, double>), fg, dim3(256), 0, c->stream, c->chunks_dev, c->slice_z_dev, c->l1, gs.loss, gs.conj, E);
             else
-                hipLaunchKernelGGL((gap_rows_from_z<2, double>), fg, dim3(256), 0, c->stream, c->chunks_dev, c->slice_z_dev, gs.loss, gs.conj);
+                hipLaunchKernelGGL((gap_rows_from_z<2, double>), fg, dim3(256), 0, c->stream, c->chunks_dev, c->slice_z_dev, c->l1, gs.loss, gs.conj, E);
         }
     } else if (c->loss == CHICLE_LOSS_HINGE) launch_gap_lpr<0>(c, gx, gs);
     else if (c->loss == CHICLE_LOSS_SQUARED) launch_gap_lpr<1>(c, gx, gs);
     else launch_gap_lpr<2>(c, gx, gs);
     HIP_TRY(c, hipGetLastError());
     c->zw_valid = true;
-    if (grid_out) *grid_out = gx * c->n_chunks;
     return CHICLE_OK;
 }
 
@@ -1158,6 +1184,7 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
     c->gap_scratch.wsq = (double *)carve(c, sizeof(double) * WSQ_PARTS);
     c->gap_scratch.unused = (double *)carve(c, sizeof(double) * WSQ_PARTS);
     c->err_dev = (int *)carve(c, sizeof(int));
+    c->tickets_dev = (unsigned *)carve(c, sizeof(unsigned) * n_tickets(d));
     c->ticks_dev = (long long *)carve(c, sizeof(long long) * 2 * (size_t)max_solvers);
     c->progress_dev = (int *)carve(c, sizeof(int) * (size_t)max_solvers);
     c->split_ring_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * (size_t)SPLIT_WORDS * (size_t)max_solvers);
@@ -1186,7 +1213,7 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
             c->pair_count[buf] = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->max_tiles);
         }
     }
-    if (!c->err_dev || !c->ticks_dev || !c->progress_dev || !c->split_ring_dev || (c->long_rows && (!c->cluster_ring_dev || !c->slice_z_dev)) || (c->compact && (!c->chunk_owner_dev || !c->blocks_ring_dev || !c->pair_count[1]))) { delete c; return CHICLE_ENOMEM; }
+    if (!c->err_dev || !c->tickets_dev || !c->ticks_dev || !c->progress_dev || !c->split_ring_dev || (c->long_rows && (!c->cluster_ring_dev || !c->slice_z_dev)) || (c->compact && (!c->chunk_owner_dev || !c->blocks_ring_dev || !c->pair_count[1]))) { delete c; return CHICLE_ENOMEM; }
 
     c->chunks.assign(n_chunks, ChunkDev{});
     c->loaded.assign(n_chunks, 0);
@@ -1196,6 +1223,7 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
               hipMemsetAsync(c->tmp_b, 0, sizeof(float) * (size_t)c->ld_v, c->stream) == hipSuccess &&
               hipMemsetAsync(c->u, 0, sizeof(float) * (size_t)c->u_capacity, c->stream) == hipSuccess &&
               hipMemsetAsync(c->err_dev, 0, sizeof(int), c->stream) == hipSuccess &&
+              hipMemsetAsync(c->tickets_dev, 0, sizeof(unsigned) * n_tickets(d), c->stream) == hipSuccess &&
               (!c->long_rows || hipMemsetAsync(c->slice_z_dev, 0, sizeof(double) * (size_t)n_total, c->stream) == hipSuccess) &&
               hipMemsetAsync(c->ticks_dev, 0, sizeof(long long) * 2 * (size_t)max_solvers, c->stream) == hipSuccess;
     {
@@ -1619,7 +1647,7 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
     if (route == ROUTE_DENSE && !dense_tiles_ahead(c)) perm_next_device = nullptr;      // (they are kept all the same)
     seg_begin(c, CHICLE_SEG_LOCAL_EPOCH);
     int rc = CHICLE_OK;
-    if (!c->zw_valid) rc = run_row_pass(c, nullptr, c->gap_scratch);     // x_i . w for the current w
+    if (!c->zw_valid) rc = run_row_pass(c, c->gap_scratch);     // x_i . w for the current w
     if (rc == CHICLE_OK) {
         if (batched) {
             rc = c->loss == CHICLE_LOSS_HINGE ? launch_batched<0>(c, perm_device, tiles_ready, perm_next_device)
@@ -1661,21 +1689,15 @@ int chicle_aggregate(chicle_ctx *c)
     seg_begin(c, CHICLE_SEG_AGGREGATE);
     const int64_t d4 = c->ld_v / 4;
     if (c->compact) {
-        // few words: the solvers are divided over slices too, so that the chip is filled
-        const unsigned gx = (unsigned)((c->words + AGG_WORDS - 1) / AGG_WORDS);
+        // few words: the solvers are divided over slices too, so that the chip is filled.  Thinly occupied vectors (under an
+        // eighth of the columns per solver on average): entries are picked straight from memory
+        const bool thin = c->u_used * 8 < (int64_t)c->K * (int64_t)c->d;
+        const int wg_words = thin ? AGG_THIN_WORDS : AGG_WORDS;
+        const unsigned gx = (unsigned)((c->words + wg_words - 1) / wg_words);
         const unsigned gy = (unsigned)std::max(1, std::min(c->K, (int)(1024 / gx)));
-        // thinly occupied vectors (under an eighth of the columns per solver on average): entries are picked
-        // straight from memory
-        if (c->u_used * 8 < (int64_t)c->K * (int64_t)c->d)
-            hipLaunchKernelGGL(aggregate_compact_thin, dim3(gx, gy), dim3(AGG_WORDS), 0, c->stream, c->w64, c->w,
-                               c->u, c->u_off_dev, c->bits_dev, c->pref_dev, c->words, (int64_t)c->d, c->K,
-                               (float)(1.0 / (double)c->K), c->l1);
-        else
-        hipLaunchKernelGGL(aggregate_compact, dim3(gx, gy), dim3(AGG_WORDS), 0, c->stream, c->w64, c->w,
+        hipLaunchKernelGGL(thin ? aggregate_compact_thin : aggregate_compact, dim3(gx, gy), dim3(AGG_THREADS), 0, c->stream, c->w64, c->w,
                            c->u, c->u_off_dev, c->bits_dev, c->pref_dev, c->words, (int64_t)c->d, c->K,
-                           (float)(1.0 / (double)c->K), c->l1);
-        if (gy > 1)
-            hipLaunchKernelGGL(mirror_from_double, dim3(grid_for(c->d, 256, 2048)), dim3(256), 0, c->stream, c->w64, c->w, (int64_t)c->d, c->l1);
+                           (float)(1.0 / (double)c->K), c->l1, c->tickets_dev + GAP_TICKETS);
     } else
         hipLaunchKernelGGL(aggregate_broadcast, dim3(grid_for(d4, 256, 4096)), dim3(256), 0, c->stream, c->w64, c->w,
                            c->u, c->ld_v, d4, c->K, (float)(1.0 / (double)c->K), c->l1);
@@ -1686,19 +1708,14 @@ int chicle_aggregate(chicle_ctx *c)
     return CHICLE_OK;
 }
 
-static int gap_with(chicle_ctx *c, const GapScratch &gs, double *primal, double *dual, double *gap)
+static int gap_with(chicle_ctx *c, GapScratch gs, double *primal, double *dual, double *gap)
 {
     if (c->state != ST_READY) return fail(c, CHICLE_ESTATE, "gap is defined on the aggregated state");
     seg_begin(c, CHICLE_SEG_GAP);
-    int grid = 1;
-    int rc = run_row_pass(c, &grid, gs);
-    if (rc) { seg_end(c, CHICLE_SEG_GAP); return rc; }
-    const int gw = grid_for(c->d, 256 * 8, WSQ_PARTS);
-    hipLaunchKernelGGL(wsq_partial, dim3(gw), dim3(256), 0, c->stream, c->w64, (int64_t)c->d, c->l1, gs.wsq, gs.unused);
-    hipLaunchKernelGGL(gap_finish, dim3(1), dim3(256), 0, c->stream, gs.loss, gs.conj, grid,
-                       gs.wsq, gs.unused, gw, c->err_dev, c->gap_host_dev);
+    gs.finish = true;
+    const int rc = run_row_pass(c, gs);
     seg_end(c, CHICLE_SEG_GAP);
-    HIP_TRY(c, hipGetLastError());
+    if (rc) return rc;
     // the sums and the error flag arrive in pinned host memory with the end of the kernel: no copy to wait for
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     const double *h = c->gap_host;

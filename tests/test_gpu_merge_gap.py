@@ -1,0 +1,61 @@
+"""The merge in slices of solvers, whose last slice writes the float mirror, and the gap, whose last workgroup adds everything
+up: columns at the edges of a workgroup's, one solver and many, several rounds on the same counters, after a call without the
+sums as well."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,n,m,K", [(1, 70, 1, 1), (31, 90, 3, 2), (2048, 400, 12, 3), (2049, 700, 60, 5), (70001, 3000, 20, 40), (300000, 300, 40, 30),
+                                     (40, 900, 0, 4)])
+def test_merge_and_gap(d, n, m, K):
+    import torch
+    import paper_1909_04885_amd as chicle
+    assert torch.cuda.is_available()
+    print("\ncase merge and gap d=%d n=%d m=%d K=%d" % (d, n, m, K), flush=True)
+    g = np.random.default_rng(11)
+    dense = m == 0
+    lam, l1 = 1.0 / n, 0.01
+    y = g.standard_normal(n).astype(np.float32)
+    X = np.zeros((n, d), dtype=np.float32) if dense else None
+    bounds = np.linspace(0, n, K + 1).astype(np.int64)
+    r = chicle.ChicleRound("squared", n, d, lam, K, K, dense, n * (d if dense else m))
+    if dense:
+        X[:] = g.standard_normal((n, d))
+    else:
+        col = np.concatenate([np.sort(g.choice(d, m, replace=False)) for _ in range(n)]).astype(np.int32)
+        val = g.standard_normal(n * m).astype(np.float32)
+        rp = m * np.arange(n + 1, dtype=np.int64)
+    for k in range(K):
+        a, b = bounds[k], bounds[k + 1]
+        if dense:
+            r.load_chunk_dense(k, X[a:b], y[a:b])
+        else:
+            r.load_chunk_csr(k, rp[a:b + 1] - rp[a], col[rp[a]:rp[b]], val[rp[a]:rp[b]], y[a:b])
+    r.set_l1(l1)
+    r.assign(K, np.arange(K, dtype=np.int32))
+    v = np.zeros(d)                                     # the dual image, in double
+    eps = 2.0 ** -24
+    for rnd in range(3):
+        r.local_epoch(r.upload_perm([g.permutation(int(x)) for x in r.solver_rows()]))
+        parts = [r.get_delta_w(k).astype(np.float64) for k in range(K)]
+        v += np.sum(parts, axis=0)
+        r.aggregate()
+        w = np.sign(v) * np.maximum(np.abs(v) - l1, 0.0)
+        # float sums of up to K terms, scaled, three rounds of them; the mirror's own rounding
+        slack = (rnd + 1) * (K + 2) * eps * max(1.0, np.abs(parts).sum(axis=0).max() + np.abs(v).max())
+        got = r.get_w().astype(np.float64)
+        assert np.all(np.abs(got - w) <= slack + eps * np.abs(w))
+        if rnd == 1:
+            continue                                    # the next pass runs the rows' part alone
+        for _ in range(2):
+            P, D, gap = r.gap()
+            z = X.astype(np.float64) @ w if dense else (val.astype(np.float64) * w[col]).reshape(n, m).sum(axis=1)
+            alpha = np.concatenate([r.get_alpha(k) for k in range(K)]).astype(np.float64)
+            P_ref = 0.5 * np.mean((z - y) ** 2) + lam * (0.5 * w @ w + l1 * np.abs(w).sum())
+            D_ref = -np.mean(0.5 * alpha ** 2 - alpha * y) - 0.5 * lam * (w @ w)
+            # all sums in double; w is off by the slack above, z by at most the row's entries times it
+            off = slack * (n + d + max(m, d if dense else 0) * np.abs(z - y).max()) * 8
+            assert abs(P - P_ref) <= 1e-12 * P_ref + off and abs(D - D_ref) <= 1e-12 * abs(D_ref) + off and gap == P - D
+    r.close()
