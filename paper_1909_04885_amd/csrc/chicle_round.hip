@@ -660,11 +660,17 @@ int launch_affine(chicle_ctx *c, const int32_t *perm, int run)
     };
     seg_begin(c, CHICLE_SEG_EPOCH_GRAM);
     static_assert(AFFINE_MAX_D == 32, "all row lengths of affine_maps");
-    auto maps = d <= 4 ? affine_maps<4, 16, true> : d <= 8 ? affine_maps<8, 16, true> : d <= 12 ? affine_maps<12, 16, true>
-                : d < 16 ? affine_maps<16, 16, true> : d <= 16 ? affine_maps<16, 32, true> : d <= 20 ? affine_maps<20, 32, true>
-                : d <= 24 ? affine_maps<24, 32, true> : d <= 28 ? affine_maps<28, 32, true> : d < 32 ? affine_maps<32, 32, true>
-                : affine_maps<32, 32, false>;
-    hipLaunchKernelGGL(maps, grid(d < 16 ? 16 : 32), dim3(64 * AFFINE_WAVES), 0, c->stream, c->chunks_dev, c->solvers_dev, c->row_chunk_dev, c->chunk_first_dev, perm,
+    const dim3 mg = grid(d < 16 ? 16 : 32);
+    const bool alone = (int64_t)mg.x * mg.y <= c->cu_count;      // a workgroup's wavefronts are on a SIMD each
+    auto maps = d <= 4 ? affine_maps<4, 16, true, false> : d <= 8 ? affine_maps<8, 16, true, false> : d <= 12 ? affine_maps<12, 16, true, false>
+                : d < 16 ? affine_maps<16, 16, true, false>
+                : d <= 16 ? (alone ? affine_maps<16, 32, true, true> : affine_maps<16, 32, true, false>)
+                : d <= 20 ? (alone ? affine_maps<20, 32, true, true> : affine_maps<20, 32, true, false>)
+                : d <= 24 ? (alone ? affine_maps<24, 32, true, true> : affine_maps<24, 32, true, false>)
+                : d <= 28 ? (alone ? affine_maps<28, 32, true, true> : affine_maps<28, 32, true, false>)
+                : d < 32 ? (alone ? affine_maps<32, 32, true, true> : affine_maps<32, 32, true, false>)
+                : (alone ? affine_maps<32, 32, false, true> : affine_maps<32, 32, false, false>);
+    hipLaunchKernelGGL(maps, mg, dim3(64 * AFFINE_WAVES), 0, c->stream, c->chunks_dev, c->solvers_dev, c->row_chunk_dev, c->chunk_first_dev, perm,
                        tiles, d, run, sc.c, sc.inv_c, c->err_dev);
     seg_end(c, CHICLE_SEG_EPOCH_GRAM);
     seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);

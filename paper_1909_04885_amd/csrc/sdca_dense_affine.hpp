@@ -9,7 +9,7 @@
 // Only the second kernel is a chain, of some 600 cycles per run; blocks of 64 rows solved by their inverse took 2.2e3 each (see
 // sdca_dense_squared).  The first is bound by its multiply-adds (2 d^2 per row in double, of rank one updates that depend on
 // each other), the third by the dozen dependent instructions of a row.  500000 x 28, 16 solvers, a pass in runs of 256 rows:
-// 86 + 33 + 47 us (450 in blocks); fifty rounds 28.2 -> 10.8 ms.
+// 79 + 33 + 47 us (450 in blocks); fifty rounds 28.2 -> 9.8 ms.
 // Precision: all is in double but what is stored (alpha, the solver's update, the rows and their state).  The update is the
 // vector after the last run, not a sum over the runs: an error in the vector shrinks with every row after it, one in a run's
 // share would stay.  It is not formed from the stored alphas, so that whatever either is off by parts w from the sum of the
@@ -86,7 +86,9 @@ __device__ __forceinline__ double affine_scale(float q, float c) { return (doubl
 // so that each group's loads have a group's arithmetic to return in.  DK: columns, rounded up to four.
 // SPARE: a run has more lanes than a row has columns, and the one after the last holds b as a column of its own (a row without
 // a column there leaves P's as it is), so that no sum over lanes stands in the chain from row to row.
-template <int DK, int LANES, bool SPARE>
+// ALONE: the wavefronts are no more than the SIMDs, so that nothing hides a wavefront's reads of a row's words but its own
+// arithmetic on the row before.
+template <int DK, int LANES, bool SPARE, bool ALONE>
 __global__ __launch_bounds__(64 * AFFINE_WAVES) void affine_maps(
     const ChunkDev *__restrict__ chunks, const SolverDev *__restrict__ solvers, const int32_t *__restrict__ row_chunk,
     const int32_t *__restrict__ chunk_first, const int32_t *__restrict__ perm, float *tiles, int d, int run, float c, float inv_c, int *err)
@@ -185,9 +187,10 @@ __global__ __launch_bounds__(64 * AFFINE_WAVES) void affine_maps(
 #pragma unroll
             for (int k = 0; k < DK; ++k) P[k] = fma(w.x[k >> 1][k & 1], n, P[k]);
         };
-        // One wavefront per SIMD reads a row's words during the arithmetic of the row before it; two of them hide each other's
+        // One wavefront per SIMD reads a row's words during the arithmetic of the row before it (500000 x 28 in runs of 256 rows, 977
+        // wavefronts: 86 us without, 79 with); two of them hide each other's
         // reads, and a second set of words would take the registers that the second one needs.
-        if (LANES == 16) {
+        if (LANES == 16 || ALONE) {
             Words even = read(0);
             for (int r = 0; r < LANES; r += 2) {
                 const Words odd = read(r + 1);
