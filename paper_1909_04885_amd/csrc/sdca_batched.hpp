@@ -78,6 +78,7 @@ struct BatchedShared {
     int hb;
     int dead;                    // split solver: a wait for a partner workgroup has given up
     int xflag;                   // split solver: iteration whose ring words are in xv
+    int cflag;                   // split solver: iteration whose pairs are in xc
     int over;                    // split solver: a block has more pairs than its list holds
     float xv[BATCH];             // split solver: the unpopular columns' share of the dot products
     double xc[BATCH];            // split solver: what comes into that through pairs of rows two and three blocks apart

@@ -30,7 +30,7 @@ constexpr int SPLIT_TAILS = 2;
 constexpr int LAG = 4;                         // unpopular columns: blocks <= b - LAG are in what block b gathers
 constexpr int SPLIT_WORDS = (1 + SPLIT_TAILS) * SPLIT_RING * BATCH;      // 64-bit words per solver
 constexpr int SPLIT_SPIN_LIMIT = 1 << 22;      // polls before a wait for the partner gives up
-constexpr int SPLIT_THREADS = BATCHED_THREADS + 128;  // the single-workgroup solver's wavefronts, one that polls the rings and one that resolves rows
+constexpr int SPLIT_THREADS = BATCHED_THREADS + 192;  // the single-workgroup solver's wavefronts, and one each that polls the rings, resolves rows, adds up pairs
 
 __device__ __forceinline__ void ring_put(unsigned long long *p, float v, int tag)
 {
@@ -114,6 +114,13 @@ __device__ __forceinline__ void wait_flag(const int *flag, int target)
     while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < target)
         __builtin_amdgcn_s_sleep(1);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// Everything this wavefront did in LDS before, then the word.
+__device__ __forceinline__ void raise_flag(int *flag, int v)
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(flag, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // The row resolver both kinds of workgroup run in one wavefront (one lane per row of a block).  A workgroup
@@ -200,7 +207,7 @@ __device__ __forceinline__ int split_lag(const SplitArgs &A, const SolverDev &S,
 
 // ---- the head workgroup: recurrence, tiles, the popular columns in LDS -------------------------------------
 // Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 stage the tiles, 11
-// fetches the tails' partial sums, 12 resolves rows.  One loop per role, all with the same number of iterations and one
+// fetches the tails' partial sums, 12 resolves rows, 13 adds up what comes through pairs.  One loop per role, all with the same number of iterations and one
 // workgroup barrier per iteration, so that the registers of one role are not kept alive through the code of
 // the others.
 template <int LOSS>
@@ -216,7 +223,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
     split_stage_lists(smem, A, S, l_desc, l_prefix);
     double *hot = reinterpret_cast<double *>(smem + A.hot_off);
     for (int i = tid; i < n_hot; i += SPLIT_THREADS) hot[i] = 0.0;
-    if (tid == 0) { sh.hb = 0; sh.dead = 0; sh.xflag = 0; }
+    if (tid == 0) { sh.hb = 0; sh.dead = 0; sh.xflag = 0; sh.cflag = 0; }
     const int nb = (S.n_rows + BATCH - 1) / BATCH;
     const bool pairs = A.n_tails > 0 && split_lag(A, S, nb, &sh.over) == LAG;
     __syncthreads();
@@ -244,14 +251,29 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
         }
     } else if (wave == 11) {
         // What the tails send for this iteration, fetched by a wavefront that has no other loads in flight
-        // (loads return in the order they were issued) and handed on through LDS; before it what blocks i - 1 and i - 2,
-        // whose steps are at hand, add to it through pairs.  Their number and the first 64 of them were asked for an iteration ago.
+        // (loads return in the order they were issued) and handed on through LDS.
+        HEAD_ITERATIONS {
+            if (A.n_tails > 0 && i + 1 >= 0 && i + 1 < nb) {
+                float part = ring_wait<SPLIT_TAILS>(x_parts + ((i + 1) & (SPLIT_RING - 1)) * BATCH + lane, SPLIT_RING * BATCH, i + 2, &sh.dead, A.err);
+                if (pairs) {
+                    wait_flag(&sh.cflag, i + 2);
+                    part += (float)sh.xc[lane];
+                }
+                sh.xv[lane] = part;
+                raise_flag(&sh.xflag, i + 2);
+            }
+            __syncthreads();
+        }
+    } else if (wave == 13) {
+        // What blocks i - 1 and i - 2, whose steps are at hand, add to block i + 1's dot products through pairs.  Their number and
+        // the first 64 of them were asked for an iteration ago.  (In the polling wavefront this kept the polls waiting: 5.0e3
+        // cycles an iteration, 4.7e3 now; 32 solvers of 62500 rows 2.15 and 2.02 ms.)
         const int32_t *counts = A.pair_count + S.tile_begin;
         const unsigned long long *lists = A.pair_list + (int64_t)S.tile_begin * PAIR_CAP + lane;
         int count = 0;                                   // lane 0's
         unsigned long long first = 0ull;
         HEAD_ITERATIONS {
-            if (A.n_tails > 0 && i + 1 >= 0 && i + 1 < nb) {
+            if (pairs && i + 1 >= 0 && i + 1 < nb) {
                 sh.xc[lane] = 0.0;
                 asm volatile("" ::: "memory");
                 const int n_pairs = __builtin_amdgcn_readfirstlane(count);
@@ -264,12 +286,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
                         atomicAdd(&sh.xc[at >> 6 & 63], (double)(coef * __uint_as_float((unsigned)w)));
                     }
                 }
-                asm volatile("" ::: "memory");
-                const float corr = (float)sh.xc[lane];
-                sh.xv[lane] = corr + ring_wait<SPLIT_TAILS>(x_parts + ((i + 1) & (SPLIT_RING - 1)) * BATCH + lane, SPLIT_RING * BATCH,
-                                                            i + 2, &sh.dead, A.err);
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                if (lane == 0) __hip_atomic_store(&sh.xflag, i + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                raise_flag(&sh.cflag, i + 2);
             }
             if (pairs && i + 2 >= 0 && i + 2 < nb) {
                 count = gld(counts + min(i + 2 + lane, nb - 1));       // (a scalar load would be waited for at the barrier)
@@ -441,9 +458,9 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
 // TE: entries per lane (TAIL_LPR lanes a row), taken from the end of the row, where its unpopular columns are (rows are sorted
 // by popularity): TE * TAIL_LPR must cover the largest number of entries a row has in the tails' columns (checked on the host).
 // 32 solvers of 62500 rows of 40 entries, 1M columns: 6.9e3 cycles per block of 64 steps with blocks in turn and look-back two
-// (2.84 ms a pass), 7.7e3 with blocks in turn and look-back three, 5.1e3 now (2.15 ms); six of 5000 rows, 20k columns: 169 us
-// a pass, 126 now.  A tail waits for steps 3.9e3 of its 1.04e4 cycles per two blocks; the head's tile loads and row lookups, which
-// miss the cache, take as long as an iteration.
+// (2.84 ms a pass), 7.7e3 with blocks in turn and look-back three, 4.7e3 now (2.02 ms); six of 5000 rows, 20k columns: 169 us
+// a pass, 127 now.  A tail waits for steps 3.9e3 of its 1.04e4 cycles per two blocks; the head's tile loads, which miss the
+// cache, take as long as an iteration.
 constexpr int TAIL_LPR = 4, TAIL_GROUPS = 2, TAIL_WAVES = BATCH * TAIL_LPR / 64;
 constexpr int TAIL_RING = 4;                        // resolved rows of a group's blocks
 constexpr int TAIL_LINE_LOG2 = 5;                   // columns of a tail's share of the private vector that lie side by side
@@ -458,12 +475,6 @@ struct __align__(8) TailEntry { int col; float val; };          // val: with the
 __host__ __device__ inline size_t tail_lists_at(int te)
 {
     return sizeof(TailShared) + sizeof(TailEntry) * (size_t)(LAG * te * BATCH * TAIL_LPR);
-}
-
-__device__ __forceinline__ void raise_flag(int *flag, int v)
-{
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if ((threadIdx.x & 63) == 0) __hip_atomic_store(flag, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 template <int LOSS, int TE>
