@@ -158,6 +158,7 @@ struct chicle_ctx {
     unsigned long long *split_ring_dev = nullptr;   // per solver: rings between the workgroups that share it
     unsigned long long *pair_list[2] = {nullptr, nullptr};   // per tile set: pairs of rows for the split solver, PAIR_CAP a tile,
     int32_t *pair_count[2] = {nullptr, nullptr};             // and how many there are
+    std::vector<double> shares;       // [g]: over the columns of rank 64 g and on, sum of the squared shares of the rows that hold them
     bool split_allowed = true;        // the batched solver may spread a solver over several compute units
     int max_tail_entries = 0;         // most entries a row has outside the columns the batched solver keeps on chip
     // long sparse rows: several workgroups (a cluster) share every solver of the row-wise pass
@@ -597,6 +598,20 @@ int launch_rowwise(chicle_ctx *c, const int32_t *perm)
 // The last 24 entries of a row cover every row's columns outside the LDS-resident head.
 bool short_tails(const chicle_ctx *c) { return c->compact && c->max_tail_entries <= 3 * LPR; }
 
+// Whether pairs are listed beside the tiles, for the split solver's look-back of four blocks.  It saves 0.9 us per block of the
+// longest solver.  Where the last 24 entries of a row are enough, listing costs 0.008 us per tile, which 80 solvers do not reach;
+// where not, 0.029: four rounds of 16 solvers of 12500 rows of 40 entries in uniform columns 2.93 ms without and 2.56 with, 64 of
+// 4688 rows of 44 2.99 and 3.40.  Nothing is saved where blocks have more pairs than a list holds, which the columns' shares of
+// the rows tell for rows in random order (16 solvers of 12500 rows of 48 entries in 16400 columns, 3.12 and 3.27).
+bool lists_pairs(const chicle_ctx *c)
+{
+    if (split_tails(c) <= 0) return false;
+    const int blocks = (c->most_rows + BATCH - 1) / BATCH;
+    if (!short_tails(c) && 32 * (int64_t)blocks <= c->n_tiles) return false;
+    const size_t at = (size_t)batched_layout(c).n_hot / 64;
+    return at >= c->shares.size() || (LAG - 2) * (double)(BATCH * BATCH) * c->shares[at] <= 0.85 * PAIR_CAP;
+}
+
 template <int TE>
 int launch_pairs(chicle_ctx *c, const int32_t *perm, int buf, hipStream_t stream)
 {
@@ -640,7 +655,7 @@ int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, bool ahead, hipStre
         hipLaunchKernelGGL(kern, dim3(grid), dim3(GRAM_THREADS), sizeof(GramShared), stream,
                            c->chunks_dev, c->solvers_dev, c->row_chunk_dev, c->chunk_first_dev, perm,
                            c->tile_solver_dev, c->tiles[buf], c->n_tiles, sc.c, c->err_dev);
-        if (split_tails(c) > 0) {
+        if (lists_pairs(c)) {
             const int rc = short_tails(c) ? launch_pairs<3>(c, perm, buf, stream) : launch_pairs<ENT>(c, perm, buf, stream);
             if (rc) return rc;
         }
@@ -722,7 +737,7 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
         A.solver_prefix = c->solver_prefix_dev; A.perm = perm; A.tiles = c->tiles[c->tile_buf]; A.u_all = c->u;
         A.ld_v = c->ld_v; A.u_off = u_off; A.max_list = ml; A.n_hot = n_hot; A.hot_off = (int)hot_off; A.sc = sc;
         A.err = c->err_dev; A.n_tails = n_tails; A.xchg_all = c->split_ring_dev;
-        A.pair_list = c->pair_list[c->tile_buf]; A.pair_count = c->pair_count[c->tile_buf];
+        A.lag = lists_pairs(c) ? LAG : 2; A.pair_list = c->pair_list[c->tile_buf]; A.pair_count = c->pair_count[c->tile_buf];
         // a tail's lanes take the last 24 entries of a row where that covers every row's unpopular columns
         constexpr int TE_SHORT = 3 * LPR / TAIL_LPR, TE_ALL = GRAM_MAX_ROW / TAIL_LPR;
         auto kern = short_tails(c) ? sdca_batched_split<LOSS, TE_SHORT> : sdca_batched_split<LOSS, TE_ALL>;
@@ -969,6 +984,13 @@ int renumber_columns(chicle_ctx *c)
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return cnt[a] > cnt[b]; });
     for (int32_t r = 0; r < c->d; ++r) rank[order[r]] = r;
+    c->shares.assign((size_t)c->d / 64 + 1, 0.0);
+    double sum = 0.0;
+    for (int32_t r = c->d - 1; r >= 0; --r) {
+        const double share = (double)cnt[order[r]] / (double)c->n_total;
+        sum += share * share;
+        if (r % 64 == 0) c->shares[(size_t)r / 64] = sum;
+    }
     HIP_TRY(c, hipMemcpyAsync(c->rank_of, rank.data(), sizeof(int32_t) * (size_t)c->d, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipMemcpyAsync(c->col_of, order.data(), sizeof(int32_t) * (size_t)c->d, hipMemcpyHostToDevice, c->stream));
     int max_rows = 1;

@@ -178,6 +178,7 @@ struct SplitArgs {
     int *err;
     int n_tails;
     unsigned long long *xchg_all;
+    int lag;                    // LAG, or 2: no pairs were listed
     const unsigned long long *pair_list;     // beside the tiles (split_pairs)
     const int32_t *pair_count;
 };
@@ -199,6 +200,7 @@ __device__ __forceinline__ int split_lag(const SplitArgs &A, const SolverDev &S,
 {
     if (threadIdx.x == 0) *flag = 0;
     __syncthreads();
+    if (A.lag < LAG) return A.lag;
     for (int t = threadIdx.x; t < nb; t += SPLIT_THREADS)
         if (A.pair_count[S.tile_begin + t] > PAIR_CAP) __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __syncthreads();
@@ -265,33 +267,39 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             __syncthreads();
         }
     } else if (wave == 13) {
-        // What blocks i - 1 and i - 2, whose steps are at hand, add to block i + 1's dot products through pairs.  Their number and
-        // the first 64 of them were asked for an iteration ago.  (In the polling wavefront this kept the polls waiting: 5.0e3
+        // What blocks i - 1 and i - 2, whose steps are at hand, add to block i + 1's dot products through pairs.  The pairs were
+        // asked for an iteration ago, their number two.  (In the polling wavefront this kept the polls waiting: 5.0e3
         // cycles an iteration, 4.7e3 now; 32 solvers of 62500 rows 2.15 and 2.02 ms.)
         const int32_t *counts = A.pair_count + S.tile_begin;
         const unsigned long long *lists = A.pair_list + (int64_t)S.tile_begin * PAIR_CAP + lane;
-        int count = 0;                                   // lane 0's
-        unsigned long long first = 0ull;
+        int n_now = 0, n_next = 0, far = 0;              // pairs of blocks i + 1 and i + 2; of block i + 3 in lane 0, in flight
+        unsigned long long w[PAIR_CAP / 64];
+#pragma unroll
+        for (int s = 0; s < PAIR_CAP / 64; ++s) w[s] = 0ull;
         HEAD_ITERATIONS {
+            n_next = __builtin_amdgcn_readfirstlane(far);
             if (pairs && i + 1 >= 0 && i + 1 < nb) {
                 sh.xc[lane] = 0.0;
                 asm volatile("" ::: "memory");
-                const int n_pairs = __builtin_amdgcn_readfirstlane(count);
-                for (int k = 0; k < n_pairs; k += 64) {
-                    const unsigned long long w = k == 0 ? first : lists[(int64_t)(i + 1) * PAIR_CAP + k];
-                    if (k + lane < n_pairs) {
-                        const unsigned at = (unsigned)(w >> 32);
+#pragma unroll
+                for (int s = 0; s < PAIR_CAP / 64; ++s)
+                    if (64 * s + lane < n_now) {
+                        const unsigned at = (unsigned)(w[s] >> 32);
                         const int j = at & 63, b = i - 1 - (int)(at >> 12);
                         const float coef = sh.steps[b & 3][j] * (LOSS == 1 ? 1.f : sh.rows[b & (RING - 1)][j].y) * sc.inv_c;
-                        atomicAdd(&sh.xc[at >> 6 & 63], (double)(coef * __uint_as_float((unsigned)w)));
+                        atomicAdd(&sh.xc[at >> 6 & 63], (double)(coef * __uint_as_float((unsigned)w[s])));
                     }
-                }
                 raise_flag(&sh.cflag, i + 2);
             }
+            n_now = 0;
             if (pairs && i + 2 >= 0 && i + 2 < nb) {
-                count = gld(counts + min(i + 2 + lane, nb - 1));       // (a scalar load would be waited for at the barrier)
-                first = lists[(int64_t)(i + 2) * PAIR_CAP];
+                n_now = n_next;
+#pragma unroll
+                for (int s = 0; s < PAIR_CAP / 64; ++s)
+                    if (64 * s < n_now) w[s] = lists[(int64_t)(i + 2) * PAIR_CAP + 64 * s];
             }
+            // (a scalar load would be waited for at the barrier)
+            if (pairs && i + 3 >= 0 && i + 3 < nb) far = gld(counts + min(i + 3 + lane, nb - 1));
             __syncthreads();
         }
     } else if (wave == 12) {
@@ -449,7 +457,8 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
 // rows matter that share an unpopular column with one of block b: a handful of pairs, which depend on the data and the orders
 // only and are listed beside the tiles (split_pairs); the head adds what they give when it has the steps at hand.  So the way
 // from the steps to a tail, through its adds and its gather, and back may take as long as the chains of four blocks.  A solver
-// one of whose blocks has more pairs than its list holds (PAIR_CAP) gathers with blocks <= b - 2 added, and no pairs.
+// one of whose blocks has more pairs than its list holds (PAIR_CAP) gathers with blocks <= b - 2 added, and no pairs; so do
+// all solvers where listing pairs would cost more than it saves (lists_pairs).
 // Two groups of four wavefronts take the blocks in turn.  In its turn, which begins when the other group has issued its
 // gathers, a group adds block b - 4, whose steps have arrived, and issues block b's gathers; while they are on their way
 // the other group has its turn.  A block's entries are asked for a turn ahead; between gather and add they wait in LDS.  Two

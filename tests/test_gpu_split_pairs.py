@@ -1,5 +1,6 @@
 """Two tail workgroups per solver, whose gathers leave out the three latest blocks: what blocks b - 2 and b - 3 add comes through
-pairs of rows.  Solvers of one to a few blocks, blocks of hundreds of pairs, blocks of more than a list holds, against the oracle."""
+pairs of rows.  Solvers of one to a few blocks, blocks of hundreds of pairs, blocks of more than a list holds (foreseen from
+the columns' popularity or not), against the oracle."""
 import numpy as np
 import pytest
 
@@ -28,7 +29,7 @@ def _groups(g, n, size=8):
 
 
 CASES = [("few_%d" % n, n, "hinge") for n in (1, 64, 65, 128, 129, 192, 193, 256, 257, 321, 449)]
-CASES += [(name, n, loss) for name, n in (("sets", 4000), ("too_many", 4133)) for loss in ("hinge", "squared", "logistic")]
+CASES += [(name, n, loss) for name, n in (("sets", 4000), ("not_listed", 4000), ("too_many", 4133)) for loss in ("hinge", "squared", "logistic")]
 
 
 @pytest.mark.parametrize("name,n,loss", CASES)
@@ -43,7 +44,7 @@ def test_pairs(oracle_mod, name, n, loss):
         d, cols, orders = _groups(g, n)
     else:
         d = 60000 if n < 1000 else 16400     # (half of the columns unpopular: as many pairs as uniform columns can give)
-        cols, orders = _uniform(g, n, d, 48 if n < 1000 else 40)
+        cols, orders = _uniform(g, n, d, 40 if name == "sets" else 48)
     rp = np.concatenate([[0], np.cumsum([c.size for c in cols])]).astype(np.int64)
     col = np.concatenate(cols).astype(np.int32)
     val = (g.standard_normal(col.size) / 7.0).astype(np.float32)
