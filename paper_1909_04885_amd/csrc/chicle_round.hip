@@ -134,6 +134,8 @@ struct chicle_ctx {
     float *tiles[2] = {nullptr, nullptr};   // Gram tiles: one set in use by the chain, one being prepared
     int tile_buf = 0;                       // set the next chain kernel reads
     bool tiles_solved[2] = {false, false};  // dense rows, squared loss: the set holds the recurrence solved
+    bool pairs_listed[2] = {false, false};  // short sparse rows: pairs were listed with the set (the solver kind may change
+                                            // between forming a set and using it)
     hipStream_t side = nullptr;             // stream of Gram kernels prepared ahead
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     // Visiting orders announced for the next pass are copied here when they are announced (two buffers: the
@@ -655,7 +657,8 @@ int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, bool ahead, hipStre
         hipLaunchKernelGGL(kern, dim3(grid), dim3(GRAM_THREADS), sizeof(GramShared), stream,
                            c->chunks_dev, c->solvers_dev, c->row_chunk_dev, c->chunk_first_dev, perm,
                            c->tile_solver_dev, c->tiles[buf], c->n_tiles, sc.c, c->err_dev);
-        if (lists_pairs(c)) {
+        c->pairs_listed[buf] = lists_pairs(c);
+        if (c->pairs_listed[buf]) {
             const int rc = short_tails(c) ? launch_pairs<3>(c, perm, buf, stream) : launch_pairs<ENT>(c, perm, buf, stream);
             if (rc) return rc;
         }
@@ -737,7 +740,7 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
         A.solver_prefix = c->solver_prefix_dev; A.perm = perm; A.tiles = c->tiles[c->tile_buf]; A.u_all = c->u;
         A.ld_v = c->ld_v; A.u_off = u_off; A.max_list = ml; A.n_hot = n_hot; A.hot_off = (int)hot_off; A.sc = sc;
         A.err = c->err_dev; A.n_tails = n_tails; A.xchg_all = c->split_ring_dev;
-        A.lag = lists_pairs(c) ? LAG : 2; A.pair_list = c->pair_list[c->tile_buf]; A.pair_count = c->pair_count[c->tile_buf];
+        A.lag = c->pairs_listed[c->tile_buf] ? LAG : 2; A.pair_list = c->pair_list[c->tile_buf]; A.pair_count = c->pair_count[c->tile_buf];
         // a tail's lanes take the last 24 entries of a row where that covers every row's unpopular columns
         constexpr int TE_SHORT = 3 * LPR / TAIL_LPR, TE_ALL = GRAM_MAX_ROW / TAIL_LPR;
         auto kern = short_tails(c) ? sdca_batched_split<LOSS, TE_SHORT> : sdca_batched_split<LOSS, TE_ALL>;

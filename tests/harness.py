@@ -151,3 +151,22 @@ def run_lockstep(cfg, p, oracle_mod, binding_mod, rounds=None, solver="auto", sa
         "final gap %.9e vs %.9e" % (last["gap_gpu"], last["gap_ref"])
     g.close()
     return rec
+
+
+def tail_pairs(p, rows_of_solvers, orders, n_hot=8192):
+    """For every block of 64 visited rows of every solver: pairs of its entries with entries of the blocks two and three before
+    it in the same solver that share a column outside the `n_hot` most frequent ones (no fewer than the batched solver keeps on
+    chip, so that it has at least these), and the most such entries a row has."""
+    count = np.bincount(p.col, minlength=p.d)
+    tail = np.ones(p.d, dtype=bool)
+    tail[np.argsort(-count, kind="stable")[:n_hot]] = False
+    out, longest = [], 0
+    for rows, order in zip(rows_of_solvers, orders):
+        blocks = []
+        for b in range(0, len(order), 64):
+            cols = [p.col[p.row_ptr[r]:p.row_ptr[r + 1]] for r in np.asarray(rows)[order[b:b + 64]]]
+            longest = max(longest, max(int(tail[c].sum()) for c in cols))
+            c = np.concatenate(cols)
+            blocks.append(np.bincount(c[tail[c]], minlength=p.d))
+        out.append([sum(int(blocks[b] @ blocks[a]) for a in (b - 2, b - 3) if a >= 0) for b in range(len(blocks))])
+    return out, longest

@@ -3,7 +3,7 @@ also when the pass between used another solver than the one that prepared tiles,
 import numpy as np
 import pytest
 
-from harness import TOL_DW, dw_floor, rel_l2
+from harness import TOL_DW, dw_floor, rel_l2, tail_pairs
 
 pytestmark = pytest.mark.gpu
 
@@ -66,3 +66,47 @@ def test_pass_runs_the_orders_announced_last(oracle_mod, kind, short, kinds):
         o.aggregate()
         g.aggregate()
     g.close()
+
+
+# The split batched solver reads pairs of rows beside the tiles, the solver on one compute unit only the tiles: sets formed for
+# either are used by the other.
+PAIR_SEQUENCES = [["batched_one_cu", "auto"], ["auto", "batched_one_cu", "auto", "batched"],
+                  ["batched", "batched_one_cu", "batched_one_cu", "auto", "auto"]]
+
+
+@pytest.mark.parametrize("kinds", PAIR_SEQUENCES, ids=lambda s: "-".join(s))
+def test_tiles_formed_for_the_other_batched_solver(oracle_mod, kinds):
+    import torch
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    assert torch.cuda.is_available()
+    g = np.random.default_rng(17)
+    n, half, d = 2500, 20, 8192 + 9000
+    col = np.stack([np.sort(np.concatenate([g.choice(8192, half, replace=False), 8192 + g.choice(9000, half, replace=False)])) for _ in range(n)])
+    p = Problem("announced", "hinge", n, d, 1.0 / n, np.where(g.random(n) < 0.5, 1.0, -1.0).astype(np.float32),
+                np.array([0, 1200, n], dtype=np.int64), row_ptr=2 * half * np.arange(n + 1, dtype=np.int64),
+                col=col.reshape(-1).astype(np.int32), val=(g.standard_normal(col.size) / np.sqrt(2 * half)).astype(np.float32))
+    print("\ncase announced pairs %s" % kinds, flush=True)
+    K, table = 2, np.arange(2, dtype=np.int32)
+    o = oracle_mod.OracleCoCoA.from_problem(p)
+    r = binding.ChicleRound.from_problem(p, max_solvers=K)
+    o.assign(K, table)
+    r.assign(K, table)
+    assert r.debug_solver()[:2] == ("batched", 3)
+    rows = [np.arange(*p.chunk_rows(k)) for k in range(K)]
+    perms = [[g.permutation(x.size) for x in rows] for _ in range(len(kinds) + 1)]
+    for order in perms:
+        pairs = tail_pairs(p, rows, order)[0]
+        assert all(20 < x < 400 for solver in pairs for x in solver[2:-1]), "pairs in every full block, no more than a list holds"
+    for i, kind in enumerate(kinds):
+        r.set_solver(kind)
+        r.local_epoch_ahead(None if i else r.upload_perm(perms[0]), r.upload_perm(perms[i + 1]))
+        floor = dw_floor(float(np.linalg.norm(o.w)))
+        ref = o.local_epoch(perms[i])
+        for k in range(K):
+            e = rel_l2(r.get_delta_w(k), ref[k], floor)
+            print("pass %d %s solver %d: %.2e" % (i, kind, k, e), flush=True)
+            assert e <= TOL_DW, "pass %d (%s) solver %d: %.3e" % (i, kind, k, e)
+        o.aggregate()
+        r.aggregate()
+    r.close()
