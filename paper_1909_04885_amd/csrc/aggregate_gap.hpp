@@ -295,13 +295,14 @@ __device__ __forceinline__ double wave_sum_d(double x)
     return x;
 }
 
-// What the last kernel of the gap does beside its rows.  Its workgroups with blockIdx.y >= n_chunks sum |w|^2 and |w|_1 (n_w
-// partials); every workgroup leaves its two partial sums, and the one that leaves them last adds all of them up in a fixed
-// order: out[0] = sum loss, out[1] = sum conj, out[2] = |w|^2, out[3] = the kernels' error flag, out[4] = |w|_1.  out may be
-// host memory mapped into the device's address space.  (Kernels of their own for the norms and for the end: 500000 x 28 in
-// all 34 us, 17.9 now; 4096 x 256 16 and 6.4; sparse rows, 30000 x 20k, 24 and 18.8.)  tickets: nullptr where only the rows' residuals are wanted; else zero, and left so.  Adds to
-// one address take 13 ns each, so workgroups are counted in GAP_GROUPS groups, and the groups that are complete at
-// tickets[GAP_GROUPS * TICKET_LINE].
+// What the last kernel of the gap does beside its rows.  Its grid has one dimension, whose limit no number of chunks comes
+// near: per_chunk workgroups for every chunk, one chunk after the other, then n_w that sum |w|^2 and |w|_1.  Every workgroup
+// leaves its two partial sums, and the one that leaves them last adds all of them up in a fixed order: out[0] = sum loss,
+// out[1] = sum conj, out[2] = |w|^2, out[3] = the kernels' error flag, out[4] = |w|_1.  out may be host memory mapped into the
+// device's address space.  (Kernels of their own for the norms and for the end: 500000 x 28 in all 34 us, 17.9 now; 4096 x 256
+// 16 and 6.4; sparse rows, 30000 x 20k, 24 and 18.8.)  tickets: nullptr where only the rows' residuals are wanted (n_w is zero
+// then); else zero, and left so.  Adds to one address take 13 ns each, so workgroups are counted in GAP_GROUPS groups, and the
+// groups that are complete at tickets[GAP_GROUPS * TICKET_LINE].
 constexpr int GAP_GROUPS = 32, TICKET_LINE = 32;     // (counters 128 bytes apart)
 constexpr int GAP_TICKETS = (GAP_GROUPS + 1) * TICKET_LINE;
 struct GapEnd {
@@ -309,10 +310,13 @@ struct GapEnd {
     const double *v;
     int64_t d;
     double *part_wsq, *part_wabs;
-    int n_w, n_chunks;
+    int n_w, n_chunks, per_chunk;
     const int *err;
     double *out;
 };
+// A row workgroup's chunk (n_chunks and more: a workgroup for the norms), and which of the chunk's workgroups it is.
+__device__ __forceinline__ int gap_chunk(const GapEnd &E) { return (int)(blockIdx.x / (unsigned)E.per_chunk); }
+__device__ __forceinline__ int gap_slot(const GapEnd &E) { return (int)(blockIdx.x % (unsigned)E.per_chunk); }
 // Partial sums go past the caches of the compute units and of their group, so that the last workgroup finds them.
 __device__ __forceinline__ void st_part(double *p, double x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ double ld_part(const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -360,10 +364,11 @@ __device__ __forceinline__ void gap_block_end(double a, double b, double *out_a,
     double own[2] = {a, b};
     block_sum<N>(own);
     if (threadIdx.x == 0) {
-        if (out_a) { st_part(out_a, own[0]); st_part(out_b, own[1]); }
+        st_part(out_a, own[0]);
+        st_part(out_b, own[1]);
         if (E.tickets) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            const unsigned all = gridDim.x * gridDim.y, group = (blockIdx.y * gridDim.x + blockIdx.x) % GAP_GROUPS;
+            const unsigned all = gridDim.x, group = blockIdx.x % GAP_GROUPS;
             const unsigned members = (all - group + GAP_GROUPS - 1) / GAP_GROUPS, groups = min(all, (unsigned)GAP_GROUPS);
             unsigned *mine = E.tickets + group * TICKET_LINE, *root = E.tickets + GAP_GROUPS * TICKET_LINE;
             last = 0;
@@ -381,7 +386,7 @@ __device__ __forceinline__ void gap_block_end(double a, double b, double *out_a,
     if (!last) return;
     double sums[4] = {0.0, 0.0, 0.0, 0.0};           // loss, conj, |w|^2, |w|_1
     add_parts<N>(E.part_wsq, E.part_wabs, E.n_w, sums[2], sums[3]);
-    add_parts<N>(part_loss, part_conj, (int)gridDim.x * E.n_chunks, sums[0], sums[1]);
+    add_parts<N>(part_loss, part_conj, (int)gridDim.x - E.n_w, sums[0], sums[1]);
     block_sum<N>(sums);
     if (threadIdx.x == 0) {
         E.out[0] = sums[0];
@@ -396,23 +401,21 @@ __device__ __forceinline__ void gap_block_end(double a, double b, double *out_a,
 template <int N>
 __device__ __forceinline__ void gap_w_block(double l1, double *part_loss, double *part_conj, const GapEnd &E)
 {
-    const int part = ((int)blockIdx.y - E.n_chunks) * (int)gridDim.x + (int)blockIdx.x;
+    const int part = (int)blockIdx.x - ((int)gridDim.x - E.n_w);
     double s = 0.0, t = 0.0;
-    if (part < E.n_w) {
-        const int64_t stride = (int64_t)E.n_w * N;
-        for (int64_t j = (int64_t)part * N + threadIdx.x; j < E.d; j += 4 * stride) {
-            double x[4];                             // four loads in flight per thread
+    const int64_t stride = (int64_t)E.n_w * N;
+    for (int64_t j = (int64_t)part * N + threadIdx.x; j < E.d; j += 4 * stride) {
+        double x[4];                                 // four loads in flight per thread
 #pragma unroll
-            for (int q = 0; q < 4; ++q) x[q] = j + q * stride < E.d ? E.v[j + q * stride] : 0.0;
+        for (int q = 0; q < 4; ++q) x[q] = j + q * stride < E.d ? E.v[j + q * stride] : 0.0;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double y = soft_threshold(x[q], l1);
-                s += y * y;
-                t += fabs(y);
-            }
+        for (int q = 0; q < 4; ++q) {
+            const double y = soft_threshold(x[q], l1);
+            s += y * y;
+            t += fabs(y);
         }
     }
-    gap_block_end<N>(s, t, part < E.n_w ? E.part_wsq + part : nullptr, E.part_wabs + part, part_loss, part_conj, E);
+    gap_block_end<N>(s, t, E.part_wsq + part, E.part_wabs + part, part_loss, part_conj, E);
 }
 
 // Per-row loss and conjugate terms of the gap; also leaves the residual rw of every row in the chunk
@@ -447,25 +450,25 @@ __device__ __forceinline__ void gap_row_terms(RowState *st, WT z, double &s_loss
     }
 }
 
-// Grid: (workgroups per chunk, chunks and what GapEnd adds).  Every group of LPR lanes walks rows of its chunk with a fixed
-// stride and keeps two rows in flight.  Partial sums are indexed by the linear workgroup id.
+// Grid: see GapEnd.  Every group of LPR lanes walks rows of its chunk with a fixed stride and keeps two rows in flight.
+// Partial sums are indexed by the workgroup.
 template <int LOSS, int LPR, typename WT>
 __global__ __launch_bounds__(256) void gap_rows_csr(const ChunkDev *__restrict__ chunks,
                                                     const WT *__restrict__ w, double l1,
                                                     double *part_loss, double *part_conj, GapEnd E)
 {
-    if ((int)blockIdx.y >= E.n_chunks) return gap_w_block<256>(l1, part_loss, part_conj, E);
+    if (gap_chunk(E) >= E.n_chunks) return gap_w_block<256>(l1, part_loss, part_conj, E);
     constexpr int GROUPS = 256 / LPR;
     const int sub = threadIdx.x % LPR;
     const int grp = threadIdx.x / LPR;
-    const ChunkDev &ch = chunks[blockIdx.y];
+    const ChunkDev &ch = chunks[gap_chunk(E)];
     const int n_rows = ch.n_rows;
     const int32_t *__restrict__ rp = ch.row_ptr;
     const int32_t *__restrict__ col = ch.col;
     const float *__restrict__ val = ch.val;
-    const int stride = gridDim.x * GROUPS;
+    const int stride = E.per_chunk * GROUPS;
     double s_loss = 0.0, s_conj = 0.0;
-    for (int r0 = blockIdx.x * GROUPS + grp; r0 < n_rows; r0 += 2 * stride) {
+    for (int r0 = gap_slot(E) * GROUPS + grp; r0 < n_rows; r0 += 2 * stride) {
         const int r1 = r0 + stride;
         const bool two = r1 < n_rows;
         const int b0 = rp[r0], e0 = rp[r0 + 1];
@@ -488,8 +491,7 @@ __global__ __launch_bounds__(256) void gap_rows_csr(const ChunkDev *__restrict__
             if (two) gap_row_terms<LOSS, WT>(ch.st + r1, z1, s_loss, s_conj);
         }
     }
-    const int part = blockIdx.y * gridDim.x + blockIdx.x;
-    gap_block_end<256>(s_loss, s_conj, part_loss + part, part_conj + part, part_loss, part_conj, E);
+    gap_block_end<256>(s_loss, s_conj, part_loss + blockIdx.x, part_conj + blockIdx.x, part_loss, part_conj, E);
 }
 
 // ---- the row pass for long rows over a shared vector far larger than a cache ------------------------------
@@ -578,21 +580,20 @@ __global__ __launch_bounds__(256) void gap_rows_sliced(const ChunkDev *__restric
     }
 }
 
-// Grid: (workgroups per chunk, chunks and what GapEnd adds); a thread per row.  Partial sums by linear workgroup id, as above.
+// Grid: see GapEnd; a thread per row.  Partial sums by workgroup, as above.
 template <int LOSS, typename WT>
 __global__ __launch_bounds__(256) void gap_rows_from_z(const ChunkDev *__restrict__ chunks, WT *z, double l1,
                                                        double *part_loss, double *part_conj, GapEnd E)
 {
-    if ((int)blockIdx.y >= E.n_chunks) return gap_w_block<256>(l1, part_loss, part_conj, E);
-    const ChunkDev &ch = chunks[blockIdx.y];
+    if (gap_chunk(E) >= E.n_chunks) return gap_w_block<256>(l1, part_loss, part_conj, E);
+    const ChunkDev &ch = chunks[gap_chunk(E)];
     double s_loss = 0.0, s_conj = 0.0;
-    for (int r = blockIdx.x * 256 + threadIdx.x; r < ch.n_rows; r += gridDim.x * 256) {
+    for (int r = gap_slot(E) * 256 + threadIdx.x; r < ch.n_rows; r += E.per_chunk * 256) {
         const WT zi = z[(int64_t)ch.row_base + r];
         z[(int64_t)ch.row_base + r] = (WT)0;
         gap_row_terms<LOSS, WT>(ch.st + r, zi, s_loss, s_conj);
     }
-    const int part = blockIdx.y * gridDim.x + blockIdx.x;
-    gap_block_end<256>(s_loss, s_conj, part_loss + part, part_conj + part, part_loss, part_conj, E);
+    gap_block_end<256>(s_loss, s_conj, part_loss + blockIdx.x, part_conj + blockIdx.x, part_loss, part_conj, E);
 }
 
 // The same row pass where the columns are numbered by popularity: the first n_hot entries of w are
@@ -607,7 +608,7 @@ __global__ __launch_bounds__(GAP_HOT_THREADS) void gap_rows_csr_hot(const ChunkD
                                                                     const WT *__restrict__ w, double l1, int n_hot,
                                                                     double *part_loss, double *part_conj, GapEnd E)
 {
-    if ((int)blockIdx.y >= E.n_chunks) return gap_w_block<GAP_HOT_THREADS>(l1, part_loss, part_conj, E);
+    if (gap_chunk(E) >= E.n_chunks) return gap_w_block<GAP_HOT_THREADS>(l1, part_loss, part_conj, E);
     extern __shared__ __align__(16) unsigned char gap_hot_raw[];
     WT *hot = reinterpret_cast<WT *>(gap_hot_raw);
     // LPR lanes per row, as many whole rows per wavefront as fit (LPR need not divide 64: with rows of 40
@@ -618,17 +619,17 @@ __global__ __launch_bounds__(GAP_HOT_THREADS) void gap_rows_csr_hot(const ChunkD
     const int sub = lane % LPR;
     const bool idle = lane >= ROWS_PER_WAVE * LPR;
     const int grp = (threadIdx.x >> 6) * ROWS_PER_WAVE + lane / LPR;
-    const ChunkDev &ch = chunks[blockIdx.y];
+    const ChunkDev &ch = chunks[gap_chunk(E)];
     const int n_rows = ch.n_rows;
     const int32_t *__restrict__ rp = ch.row_ptr;
     const int32_t *__restrict__ col = ch.col;
     const float *__restrict__ val = ch.val;
-    const int stride = gridDim.x * GROUPS;
+    const int stride = E.per_chunk * GROUPS;
     for (int i = threadIdx.x; i < n_hot; i += GAP_HOT_THREADS) hot[i] = shared_at(w, i, l1);
     __syncthreads();
     double s_loss = 0.0, s_conj = 0.0;
     // (the trip count is the same for all lanes of a wavefront: the shuffles below need every lane)
-    for (int rb = blockIdx.x * GROUPS; rb < n_rows; rb += 2 * stride) {
+    for (int rb = gap_slot(E) * GROUPS; rb < n_rows; rb += 2 * stride) {
         const int r0 = rb + grp;
         const int r1 = r0 + stride;
         const bool one = !idle && r0 < n_rows;
@@ -672,8 +673,7 @@ __global__ __launch_bounds__(GAP_HOT_THREADS) void gap_rows_csr_hot(const ChunkD
             if (two) gap_row_terms<LOSS, WT>(ch.st + r1, z1, s_loss, s_conj);
         }
     }
-    const int part = blockIdx.y * gridDim.x + blockIdx.x;
-    gap_block_end<GAP_HOT_THREADS>(s_loss, s_conj, part_loss + part, part_conj + part, part_loss, part_conj, E);
+    gap_block_end<GAP_HOT_THREADS>(s_loss, s_conj, part_loss + blockIdx.x, part_conj + blockIdx.x, part_loss, part_conj, E);
 }
 
 // Dense rows (ld floats each, 16-byte aligned): LPR lanes per row, four columns at a time.  Same grid as the sparse kernel.
@@ -682,13 +682,13 @@ __global__ __launch_bounds__(256) void gap_rows_dense(const ChunkDev *__restrict
                                                       const WT *__restrict__ w, double l1,
                                                       double *part_loss, double *part_conj, GapEnd E)
 {
-    if ((int)blockIdx.y >= E.n_chunks) return gap_w_block<256>(l1, part_loss, part_conj, E);
+    if (gap_chunk(E) >= E.n_chunks) return gap_w_block<256>(l1, part_loss, part_conj, E);
     constexpr int GROUPS = 256 / LPR;
     const int sub = threadIdx.x % LPR;
     const int grp = threadIdx.x / LPR;
-    const ChunkDev &ch = chunks[blockIdx.y];
+    const ChunkDev &ch = chunks[gap_chunk(E)];
     double s_loss = 0.0, s_conj = 0.0;
-    for (int r = blockIdx.x * GROUPS + grp; r < ch.n_rows; r += gridDim.x * GROUPS) {
+    for (int r = gap_slot(E) * GROUPS + grp; r < ch.n_rows; r += E.per_chunk * GROUPS) {
         const float *x = ch.val + (int64_t)r * ld;
         WT z = 0;
         for (int p = 4 * sub; p < d; p += 4 * LPR) {         // (w is readable up to a multiple of 64 columns, zero past d)
@@ -700,8 +700,7 @@ __global__ __launch_bounds__(256) void gap_rows_dense(const ChunkDev *__restrict
         for (int o = LPR / 2; o > 0; o >>= 1) z += __shfl_xor(z, o, 64);
         if (sub == 0) gap_row_terms<LOSS, WT>(ch.st + r, z, s_loss, s_conj);
     }
-    const int part = blockIdx.y * gridDim.x + blockIdx.x;
-    gap_block_end<256>(s_loss, s_conj, part_loss + part, part_conj + part, part_loss, part_conj, E);
+    gap_block_end<256>(s_loss, s_conj, part_loss + blockIdx.x, part_conj + blockIdx.x, part_loss, part_conj, E);
 }
 
 }  // namespace chicle

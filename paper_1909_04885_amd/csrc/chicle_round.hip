@@ -832,37 +832,36 @@ int drop_ahead(chicle_ctx *c)
     return CHICLE_OK;
 }
 
-// What the workgroups of a row pass, grid_x per chunk of `threads`, do beside the rows, and how many rows of them that adds to
-// the grid.
-GapEnd gap_end(const chicle_ctx *c, const GapScratch &gs, int grid_x, int threads, unsigned *grid_y)
+// What the workgroups of a row pass, `per_chunk` of `threads` for every chunk, do beside the rows, and the grid with those for
+// the norms.
+GapEnd gap_end(const chicle_ctx *c, const GapScratch &gs, int per_chunk, int threads, dim3 *grid)
 {
     GapEnd E{};
-    E.n_chunks = c->n_chunks;
-    *grid_y = (unsigned)c->n_chunks;
+    E.n_chunks = c->n_chunks; E.per_chunk = per_chunk;
+    const unsigned rows = (unsigned)per_chunk * (unsigned)c->n_chunks;
+    *grid = dim3(rows);
     if (!gs.finish) return E;
     E.tickets = c->tickets_dev;
     E.v = c->w64; E.d = (int64_t)c->d;
     E.part_wsq = gs.wsq; E.part_wabs = gs.unused;
-    E.n_w = std::min(grid_for(c->d, threads * 8, WSQ_PARTS * 256 / threads), grid_x * (65535 - c->n_chunks));
+    E.n_w = grid_for(c->d, threads * 8, WSQ_PARTS * 256 / threads);
     E.err = c->err_dev; E.out = c->gap_host_dev;
-    *grid_y += (unsigned)((E.n_w + grid_x - 1) / grid_x);
+    *grid = dim3(rows + (unsigned)E.n_w);
     return E;
 }
 
 template <int LOSS, int LPRG, typename WT>
 void launch_gap_rows_t(chicle_ctx *c, int grid_x, const WT *w, const GapScratch &gs)
 {
-    unsigned gy;
-    const GapEnd E = gap_end(c, gs, grid_x, c->gap_hot_grid > 0 ? GAP_HOT_THREADS : 256, &gy);
-    const dim3 grid(grid_x, gy);
+    dim3 grid;
+    const GapEnd E = gap_end(c, gs, grid_x, c->gap_hot_grid > 0 ? GAP_HOT_THREADS : 256, &grid);
     if (c->gap_hot_grid > 0) {
         // lanes per row: the fewest that cover the longest row with 4 entries each
         const int n_hot = (int)std::min<int64_t>(c->d, GAP_HOT_BYTES / (int)sizeof(WT));
-        const dim3 hg(c->gap_hot_grid, gy);
         const size_t sh = n_hot * sizeof(WT);
         const int need = (c->max_row_len + 3) / 4;
 #define CHICLE_GAP_HOT(L)                                                                                   \
-        hipLaunchKernelGGL((gap_rows_csr_hot<LOSS, L, WT>), hg, dim3(GAP_HOT_THREADS), sh, c->stream,      \
+        hipLaunchKernelGGL((gap_rows_csr_hot<LOSS, L, WT>), grid, dim3(GAP_HOT_THREADS), sh, c->stream,      \
                            c->chunks_dev, w, c->l1, n_hot, gs.loss, gs.conj, E)
         if (need <= 4) CHICLE_GAP_HOT(4);
         else if (need <= 8) CHICLE_GAP_HOT(8);
@@ -922,9 +921,8 @@ int run_row_pass(chicle_ctx *c, const GapScratch &gs)
         const int segs = (max_rows + SLICE_SEG - 1) / SLICE_SEG, n_items = segs * c->n_chunks;
         const unsigned blocks = (unsigned)((c->gap_slices + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS) * (unsigned)n_items;
         gx = std::max(1, std::min((max_rows + 255) / 256, gs.parts / c->n_chunks));
-        unsigned gy;
-        const GapEnd E = gap_end(c, gs, gx, 256, &gy);
-        const dim3 fg(gx, gy);
+        dim3 fg;
+        const GapEnd E = gap_end(c, gs, gx, 256, &fg);
         if (c->loss == CHICLE_LOSS_HINGE) {
             float *z = (float *)c->slice_z_dev;
             hipLaunchKernelGGL(gap_rows_sliced<float>, dim3(blocks), dim3(256), 0, c->stream, c->chunks_dev, (const float *)c->w, c->l1,

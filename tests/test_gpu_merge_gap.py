@@ -59,3 +59,42 @@ def test_merge_and_gap(d, n, m, K):
             off = slack * (n + d + max(m, d if dense else 0) * np.abs(z - y).max()) * 8
             assert abs(P - P_ref) <= 1e-12 * P_ref + off and abs(D - D_ref) <= 1e-12 * abs(D_ref) + off and gap == P - D
     r.close()
+
+
+@pytest.mark.parametrize("dense", [True, False])
+def test_gap_of_65535_chunks(dense):
+    """As many chunks of a row as a grid's second dimension has places: the norms have workgroups beside the chunks'."""
+    import torch
+    import paper_1909_04885_amd as chicle
+    assert torch.cuda.is_available()
+    print("\ncase gap of 65535 chunks, %s" % ("dense" if dense else "sparse"), flush=True)
+    g = np.random.default_rng(5)
+    n, d, m, K = 65535, 40, 8, 86
+    lam = 0.05
+    y, alpha = g.standard_normal(n).astype(np.float32), g.standard_normal(n).astype(np.float32)
+    col = np.sort(np.argsort(g.random((n, d)), axis=1)[:, :m], axis=1).astype(np.int32)
+    X = g.standard_normal((n, d)).astype(np.float32)
+    if not dense:
+        keep = np.zeros((n, d), dtype=bool)
+        np.put_along_axis(keep, col, True, axis=1)
+        X[~keep] = 0.0
+    r = chicle.ChicleRound("squared", n, d, lam, n, K, dense, n * (d if dense else m))
+    rp = np.array([0, m], dtype=np.int32)
+    for i in range(n):
+        if dense:
+            r.load_chunk_dense(i, X[i:i + 1], y[i:i + 1], alpha[i:i + 1])
+        else:
+            r.load_chunk_csr(i, rp, col[i], X[i, col[i]], y[i:i + 1], alpha[i:i + 1])
+    r.assign(K, (np.arange(n) % K).astype(np.int32))
+    w = g.standard_normal(d).astype(np.float32)
+    r.set_w(w)
+    w, z, a = w.astype(np.float64), X.astype(np.float64) @ w.astype(np.float64), alpha.astype(np.float64)
+    P_ref = 0.5 * np.mean((z - y) ** 2) + 0.5 * lam * (w @ w)
+    D_ref = -np.mean(0.5 * a ** 2 - a * y) - 0.5 * lam * (w @ w)
+    for _ in range(2):
+        P, D, gap = r.gap()
+        # doubles added in another order: n + d terms of one sign (the dual's: of at most 8 times its value)
+        tol = (n + d) * 2.0 ** -52
+        print("P %.3e D %.3e" % (abs(P / P_ref - 1), abs(D / D_ref - 1)), flush=True)
+        assert abs(P - P_ref) <= tol * P_ref and abs(D - D_ref) <= 8 * tol * abs(D_ref) and gap == P - D
+    r.close()
