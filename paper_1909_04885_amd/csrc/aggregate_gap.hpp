@@ -74,7 +74,9 @@ __global__ __launch_bounds__(256) void delta_w_out(const float *u_all, int64_t l
 // words of 32 columns (2048 columns) and walks the solvers: a solver's entries for these columns are one
 // contiguous run of its compact vector, which the workgroup reads (and clears) with coalesced accesses into
 // LDS; each thread then picks the entries of its own quarter of a word out of the run, in order, by the word's bits.  (256 words
-// to a workgroup, a thread each, left small jobs a few workgroups with long loops: six solvers over 20k columns 18.5 us, and 5 for the mirror, 7.8 now with it.)
+// to a workgroup, a thread each, left small jobs a few workgroups with long loops: six solvers over 20k columns 18.5 us, and 5
+// for the mirror, 7.8 now with it.)  The sums are in double: how many solvers a slice has depends on the number of columns, and
+// so would the roundings of a sum in float.
 // u_off[k]: where solver k's compact vector starts in u.  Reads and clears only what the solvers touched.
 // Where there are few words (few workgroups), the solvers are divided over gridDim.y slices as well; the
 // slices then add their sums into the double-precision vector with atomic adds, and the one that is done last refreshes the
@@ -114,16 +116,17 @@ __global__ __launch_bounds__(AGG_THREADS) void aggregate_compact(double *w64, fl
 {
     constexpr int PER = 8, PARTS = 32 / PER;         // columns of a thread, threads of a word
     static_assert(AGG_WORDS * PARTS == AGG_THREADS, "a thread per quarter of a word");
-    __shared__ float run[AGG_WORDS * 32];            // a run is at most all columns of the workgroup
+    __shared__ __align__(16) double sums[AGG_WORDS * 32];
+    float *run = reinterpret_cast<float *>(sums);    // a run is at most all columns of the workgroup; the sums take its place
     __shared__ unsigned touched[AGG_WORDS];
     __shared__ int run_begin, run_end;
     const int tid = threadIdx.x, word = tid / PARTS, part = tid % PARTS;
     const int64_t j = (int64_t)blockIdx.x * AGG_WORDS + word;
     const bool live = j < words;
     const int last = (int)min((int64_t)AGG_WORDS, words - (int64_t)blockIdx.x * AGG_WORDS) - 1;   // last live word
-    float acc[PER];
+    double acc[PER];
 #pragma unroll
-    for (int b = 0; b < PER; ++b) acc[b] = 0.f;
+    for (int b = 0; b < PER; ++b) acc[b] = 0.0;
     unsigned any = 0;
     // (the next solver's word and prefix are requested before this solver's run is waited for)
     const int per = (K + (int)gridDim.y - 1) / (int)gridDim.y;
@@ -150,13 +153,13 @@ __global__ __launch_bounds__(AGG_THREADS) void aggregate_compact(double *w64, fl
         int r = pf - begin + __popc(m & ((1u << (PER * part)) - 1u));
 #pragma unroll
         for (int b = 0; b < PER; ++b)
-            if (m & (1u << (PER * part + b))) acc[b] += run[r++];
+            if (m & (1u << (PER * part + b))) acc[b] += (double)run[r++];
         __syncthreads();                             // the run is overwritten by the next solver's
     }
     // the sums go through LDS so that the shared vector is updated with coalesced accesses
     if (part == 0) touched[word] = any;
 #pragma unroll
-    for (int b = 0; b < PER; b += 4) *reinterpret_cast<float4 *>(run + tid * PER + b) = make_float4(acc[b], acc[b + 1], acc[b + 2], acc[b + 3]);
+    for (int b = 0; b < PER; b += 2) *reinterpret_cast<double2 *>(sums + tid * PER + b) = make_double2(acc[b], acc[b + 1]);
     __syncthreads();
     const int64_t c0 = (int64_t)blockIdx.x * AGG_WORDS * 32;
 #pragma unroll
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(AGG_THREADS) void aggregate_compact(double *w64, fl
         const int i = tid + q * AGG_THREADS;
         const int64_t c = c0 + i;
         if (c < d && (touched[i >> 5] & (1u << (i & 31)))) {
-            const double add = (double)(run[i] * inv_sigma);
+            const double add = sums[i] * (double)inv_sigma;
             if (gridDim.y == 1) {
                 const double x = w64[c] + add;
                 w64[c] = x;

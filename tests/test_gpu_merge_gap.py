@@ -98,3 +98,36 @@ def test_gap_of_65535_chunks(dense):
         print("P %.3e D %.3e" % (abs(P / P_ref - 1), abs(D / D_ref - 1)), flush=True)
         assert abs(P - P_ref) <= tol * P_ref and abs(D - D_ref) <= 8 * tol * abs(D_ref) and gap == P - D
     r.close()
+
+
+def test_merge_adds_in_double():
+    """Sixteen solvers in slices of several, thickly occupied vectors: what reaches the shared vector is the sum of the updates in
+    double, however many of them a slice adds up."""
+    import torch
+    import paper_1909_04885_amd as chicle
+    assert torch.cuda.is_available()
+    print("\ncase merge in double", flush=True)
+    g = np.random.default_rng(23)
+    n, d, m, K = 32000, 300000, 48, 16           # (sixteen: a solver's update is its vector over K, without a rounding)
+    col = (np.arange(m) * (d // m) + g.integers(0, d // m, (n, m))).astype(np.int32)
+    val = g.standard_normal((n, m)).astype(np.float32)
+    y = np.where(g.random(n) < 0.5, -1.0, 1.0).astype(np.float32)
+    r = chicle.ChicleRound("hinge", n, d, 1.0 / n, K, K, False, n * m)
+    rows = n // K
+    for k in range(K):
+        a, b = k * rows, (k + 1) * rows
+        r.load_chunk_csr(k, m * np.arange(rows + 1), col[a:b].reshape(-1), val[a:b].reshape(-1), y[a:b])
+    r.assign(K, np.arange(K, dtype=np.int32))
+    total, size = np.zeros(d), np.zeros(d)
+    for _ in range(2):
+        r.local_epoch(r.upload_perm([g.permutation(rows) for _ in range(K)]))
+        for k in range(K):
+            part = r.get_delta_w(k).astype(np.float64)
+            total += part
+            size += np.abs(part)
+        r.aggregate()
+        # the mirror's rounding to float, and roundings of doubles
+        off = np.abs(r.get_w().astype(np.float64) - total)
+        print("beyond the bound: %d of %d columns" % (np.count_nonzero(off > 2.0 ** -24 * np.abs(total) + 2.0 ** -47 * size), d), flush=True)
+        assert np.all(off <= 2.0 ** -24 * np.abs(total) + 2.0 ** -47 * size)
+    r.close()
