@@ -110,7 +110,9 @@ __global__ __launch_bounds__(PAIR_THREADS) void split_pairs(const ChunkDev *__re
             for (int e = 0; e < 2 * TE; ++e)
                 while (at[e] != SH::END) {
                     const typename SH::Entry p = sh.entry[(q - 2 - e / TE) & 3][at[e]];
-                    if (p.rest_next >> SH::POS_BITS == (key[e % TE] & REST)) {
+                    // (a product beyond a float's range is of a row whose squared norm is too: it takes no step, and infinity
+                    // times a step of zero would be no number)
+                    if (p.rest_next >> SH::POS_BITS == (key[e % TE] & REST) && fabsf(val[e % TE] * p.val) <= 3.4028235e38f) {
                         const int k = atomicAdd(&sh.found[q & 1], 1);
                         if (k < PAIR_CAP)
                             list[(int64_t)tile * PAIR_CAP + k] = pair_word(val[e % TE] * p.val, rho, (int)(at[e] & (PAIR_THREADS - 1)) / LPR, e / TE);

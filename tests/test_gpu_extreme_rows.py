@@ -66,3 +66,51 @@ def test_rows_of_huge_norm_take_no_step(kind, loss):
     if loss != "logistic":       # (row by row the logistic step has no meaning for such a row)
         assert np.max(np.abs(alpha - alpha_rows)) <= 5e-4          # the oracle tests' bound for alpha
         assert np.linalg.norm(w - w_rows) <= 1e-4 * np.linalg.norm(w_rows)
+
+
+@pytest.mark.parametrize("loss", ["hinge", "squared"])
+def test_huge_rows_that_share_a_column_blocks_apart(loss):
+    """Short sparse rows, unpopular columns that two rows two and three blocks apart hold, both of them huge: what does not fit a
+    float is their product alone (the tiles hold products of rows of one block and the next, of which none are huge here)."""
+    import torch
+    import paper_1909_04885_amd as binding
+    from harness import tail_pairs
+    from workloads.generate import Problem
+    assert torch.cuda.is_available()
+    print("\ncase huge rows blocks apart %s" % loss, flush=True)
+    g = np.random.default_rng(13)
+    n, popular, m = 1280, 8256, 36                       # every popular column 4 or 5 times
+    common = np.arange(n * 30).reshape(n, 30) % popular
+    pairs = [(64 * a + i, 64 * b + j) for a, b in ((1, 3), (5, 8), (10, 12), (14, 17)) for i, j in ((3, 60), (40, 40))]
+    own = np.empty((n, 6), dtype=np.int64)               # unpopular columns of two rows each
+    for q in range(6):
+        partner = g.permutation(n)
+        own[partner, q] = popular + q * (n // 2) + np.arange(n) // 2
+    d = popular + 6 * (n // 2) + len(pairs)
+    for s, (a, b) in enumerate(pairs):
+        own[a, 5] = own[b, 5] = popular + 6 * (n // 2) + s
+    huge = np.unique(pairs)
+    col = np.sort(np.concatenate([common, own], axis=1), axis=1)
+    factor = np.ones(n)
+    factor[huge] = np.resize([1e20, 1e25], huge.size)
+    val = (g.standard_normal((n, m)) / np.sqrt(m) * factor[:, None]).astype(np.float32)
+    y = np.where(g.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    p = Problem("extreme", loss, n, d, 1.0 / n, y, np.array([0, n], dtype=np.int64), row_ptr=m * np.arange(n + 1, dtype=np.int64),
+                col=col.reshape(-1).astype(np.int32), val=val.reshape(-1))
+    order = np.arange(n)
+    assert sum(tail_pairs(p, [order], [order], n_hot=popular)[0][0]) >= len(pairs)
+    got = []
+    for solver in ("auto", "rowwise"):
+        r = binding.ChicleRound.from_problem(p, max_solvers=1)
+        r.assign(1, np.zeros(1, dtype=np.int32))
+        r.set_solver(solver)
+        assert solver == "rowwise" or r.debug_solver()[:2] == ("batched", 3)
+        r.local_epoch(r.upload_perm([order]))
+        r.aggregate()
+        got.append((r.get_alpha(0), r.get_w()))
+        r.close()
+    (alpha, w), (alpha_rows, w_rows) = got
+    assert np.isfinite(alpha).all() and np.isfinite(w).all()
+    assert (alpha[huge] == 0).all()
+    assert np.max(np.abs(alpha - alpha_rows)) <= 5e-4              # the oracle tests' bound for alpha
+    assert np.linalg.norm(w - w_rows) <= 1e-4 * np.linalg.norm(w_rows)
