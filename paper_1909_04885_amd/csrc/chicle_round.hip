@@ -159,7 +159,7 @@ struct chicle_ctx {
     int *progress_dev = nullptr;      // per solver: block its batched pass has reached
     unsigned long long *split_ring_dev = nullptr;   // per solver: rings between the workgroups that share it
     unsigned long long *pair_list[2] = {nullptr, nullptr};   // per tile set: pairs of rows for the split solver, PAIR_CAP a tile,
-    int32_t *pair_count[2] = {nullptr, nullptr};             // and how many there are
+    int32_t *pair_count[2] = {nullptr, nullptr};             // and how many there are (nullptr: no room, none are listed)
     std::vector<double> shares;       // [g]: over the columns of rank 64 g and on, sum of the squared shares of the rows that hold them
     bool split_allowed = true;        // the batched solver may spread a solver over several compute units
     int max_tail_entries = 0;         // most entries a row has outside the columns the batched solver keeps on chip
@@ -287,6 +287,16 @@ int max_slices(int32_t d)
 // Counters of workgroups that are done: the gap's, and one per workgroup's columns for the merge.  Zero between kernels.
 size_t n_tickets(int32_t d) { return GAP_TICKETS + ((size_t)d + 32 * AGG_WORDS - 1) / (32 * AGG_WORDS); }
 
+// Bytes of the split solver's two sets of pair lists, and of one.  They are reserved where that solver may have tails: the head
+// keeps TAILS_MIN_HOT columns or more wherever there are tails, and rows longer than it takes are the rule in contexts of long
+// rows.  (Where one of those is given short rows all the same, the lists take the place of the block solver's layout.)
+constexpr int64_t TAILS_MIN_HOT = 2 * RING * BATCH * sizeof(RowSlot) / sizeof(double);
+size_t pair_set_bytes(int64_t max_tiles) { return align_up(sizeof(unsigned long long) * PAIR_CAP * (size_t)max_tiles) + align_up(sizeof(int32_t) * (size_t)max_tiles); }
+size_t pair_bytes(int64_t max_tiles, int32_t d, bool long_rows, bool compact)
+{
+    return compact && !long_rows && d > TAILS_MIN_HOT ? 2 * pair_set_bytes(max_tiles) : 0;
+}
+
 size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_solvers, bool long_rows, bool compact,
                    int64_t n_total_entries_hint)
 {
@@ -324,10 +334,8 @@ size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_sol
         s += align_up(sizeof(float) * (size_t)n_total) + align_up(sizeof(unsigned long long) * (size_t)SB_RING_WORDS * (size_t)max_solvers);
         s += align_up(sizeof(int32_t) * (size_t)max_solvers) + align_up(sizeof(int64_t) * (size_t)max_solvers);
         s += align_up(sizeof(int32_t) * (size_t)n_chunks);
-        s += 2 * (align_up(sizeof(unsigned long long) * PAIR_CAP * (size_t)tiles_cap(n_total, max_solvers)) +
-                  align_up(sizeof(int32_t) * (size_t)tiles_cap(n_total, max_solvers)));
     }
-    return s;
+    return s + pair_bytes(tiles_cap(n_total, max_solvers), d, long_rows, compact);
 }
 
 size_t chunk_bytes(bool dense, bool compact, int64_t n_rows, int64_t entries)
@@ -470,7 +478,7 @@ int split_tails(const chicle_ctx *c)
     const int k_pad = (c->K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
     // (chunk lists that leave the head fewer popular columns than this: the solver on one compute unit)
     return c->split_allowed && (1 + n_tails) * k_pad <= c->cu_count &&
-           (n_tails == 0 || sizeof(double) * (size_t)n_hot >= 2 * RING * BATCH * sizeof(RowSlot)) ? n_tails : -1;
+           (n_tails == 0 || n_hot >= TAILS_MIN_HOT) ? n_tails : -1;
 }
 
 // Squared loss, dense rows: whether tiles are formed with the recurrence solved (gram_dense).  The inverse costs a tile 12 us
@@ -607,7 +615,7 @@ bool short_tails(const chicle_ctx *c) { return c->compact && c->max_tail_entries
 // the rows tell for rows in random order (16 solvers of 12500 rows of 48 entries in 16400 columns, 3.12 and 3.27).
 bool lists_pairs(const chicle_ctx *c)
 {
-    if (split_tails(c) <= 0) return false;
+    if (split_tails(c) <= 0 || !c->pair_list[0]) return false;
     const int blocks = (c->most_rows + BATCH - 1) / BATCH;
     if (!short_tails(c) && 32 * (int64_t)blocks <= c->n_tiles) return false;
     const size_t at = (size_t)batched_layout(c).n_hot / 64;
@@ -1197,7 +1205,8 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
     c->col_of = (int32_t *)carve(c, sizeof(int32_t) * (size_t)d);
     c->tiles[0] = (float *)carve(c, tile_bytes(c->dense) * (size_t)c->max_tiles);
     c->tiles[1] = (float *)carve(c, tile_bytes(c->dense) * (size_t)c->max_tiles);
-    if (c->long_rows) (void)carve(c, long_row_layout_bytes(n_total, total_entries));
+    char *pairs = c->long_rows ? (char *)carve(c, long_row_layout_bytes(n_total, total_entries)) : nullptr;
+    if (pairs && (d <= TAILS_MIN_HOT || 2 * pair_set_bytes(c->max_tiles) > long_row_layout_bytes(n_total, total_entries))) pairs = nullptr;
     c->layout_dev = (char *)c->tiles[0];
     c->layout_bytes = c->layout_dev ? (size_t)(c->arena + c->used - c->layout_dev) : 0;
     c->tile_solver_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->max_tiles);
@@ -1237,12 +1246,14 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
         c->count_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)max_solvers);
         c->u_off_dev = (int64_t *)carve(c, sizeof(int64_t) * (size_t)max_solvers);
         c->chunk_owner_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)n_chunks);
-        for (int buf = 0; buf < 2; ++buf) {
-            c->pair_list[buf] = (unsigned long long *)carve(c, sizeof(unsigned long long) * PAIR_CAP * (size_t)c->max_tiles);
-            c->pair_count[buf] = (int32_t *)carve(c, sizeof(int32_t) * (size_t)c->max_tiles);
-        }
     }
-    if (!c->err_dev || !c->tickets_dev || !c->ticks_dev || !c->progress_dev || !c->split_ring_dev || (c->long_rows && (!c->cluster_ring_dev || !c->slice_z_dev)) || (c->compact && (!c->chunk_owner_dev || !c->blocks_ring_dev || !c->pair_count[1]))) { delete c; return CHICLE_ENOMEM; }
+    const size_t own_pairs = pair_bytes(c->max_tiles, d, c->long_rows, c->compact);
+    if (own_pairs) pairs = (char *)carve(c, own_pairs);
+    for (int buf = 0; pairs && buf < 2; ++buf) {
+        c->pair_list[buf] = (unsigned long long *)(pairs + pair_set_bytes(c->max_tiles) * (size_t)buf);
+        c->pair_count[buf] = (int32_t *)(c->pair_list[buf] + (size_t)PAIR_CAP * (size_t)c->max_tiles);
+    }
+    if (!c->err_dev || !c->tickets_dev || !c->ticks_dev || !c->progress_dev || !c->split_ring_dev || (c->long_rows && (!c->cluster_ring_dev || !c->slice_z_dev)) || (c->compact && (!c->chunk_owner_dev || !c->blocks_ring_dev)) || (own_pairs && !pairs)) { delete c; return CHICLE_ENOMEM; }
 
     c->chunks.assign(n_chunks, ChunkDev{});
     c->loaded.assign(n_chunks, 0);

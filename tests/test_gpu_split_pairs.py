@@ -4,7 +4,7 @@ the columns' popularity or not), against the oracle."""
 import numpy as np
 import pytest
 
-from harness import TOL_DW, dw_floor, gap_tolerance, rel_l2
+from harness import TOL_DW, dw_floor, gap_tolerance, rel_l2, tail_pairs
 
 pytestmark = pytest.mark.gpu
 
@@ -26,6 +26,30 @@ def _groups(g, n, size=8):
             order += [np.concatenate([r[:size // 2] for r in rows]), np.concatenate([r[size // 2:] for r in rows])]
         orders.append(np.concatenate(order))
     return d, cols, orders
+
+
+def _shared(g, solver_rows, n_tail, holders, filler=0, n_popular=8064):
+    """Rows of 44 entries: n_tail in unpopular columns, twelve of them in columns of `holders` rows each, the rest in columns of
+    the row's own; popular columns otherwise.  `filler` rows of popular columns come first and make those the more frequent
+    ones."""
+    n = sum(solver_rows)
+    m_pop = 44 - n_tail
+    pop = (np.arange((n + filler) * 44, dtype=np.int64) * 5 % n_popular).reshape(-1, 44)
+    groups = max(1, -(-n // holders))
+    shared = np.stack([n_popular + q * groups + g.permutation(n) % groups for q in range(12)], axis=1)
+    own = n_popular + 12 * groups + np.arange(n * (n_tail - 12)).reshape(n, n_tail - 12)
+    cols = [np.sort(c) for c in pop[:filler]] + list(np.sort(np.concatenate([pop[filler:, :m_pop], shared, own], axis=1), axis=1))
+    return n_popular + 12 * groups + max(1, n * (n_tail - 12)), cols
+
+
+def _problem(g, name, loss, d, cols, bounds):
+    from workloads.generate import Problem
+    rp = np.concatenate([[0], np.cumsum([c.size for c in cols])]).astype(np.int64)
+    col = np.concatenate(cols).astype(np.int32)
+    n = len(cols)
+    y = (np.where(g.random(n) < 0.5, -1.0, 1.0) if loss != "squared" else g.standard_normal(n)).astype(np.float32)
+    return Problem(name, loss, n, d, 1.0 / n, y, np.asarray(bounds, dtype=np.int64), row_ptr=rp, col=col,
+                   val=(g.standard_normal(col.size) / 7.0).astype(np.float32))
 
 
 CASES = [("few_%d" % n, n, "hinge") for n in (1, 64, 65, 128, 129, 192, 193, 256, 257, 321, 449)]
@@ -68,4 +92,36 @@ def test_pairs(oracle_mod, name, n, loss):
         r.aggregate()
         got, want = r.gap(), o.gap()
         assert abs(got[2] - want[2]) <= gap_tolerance(want[2], want[0])
+    r.close()
+
+
+def test_pairs_in_a_context_made_for_long_rows(oracle_mod):
+    """Room announced for 120 entries a row, rows of 44: the lists take the place of the long rows' layout."""
+    import torch
+    import paper_1909_04885_amd as binding
+    assert torch.cuda.is_available()
+    print("\ncase pairs in a context made for long rows", flush=True)
+    g = np.random.default_rng(41)
+    n, K = 4000, 2
+    d, cols = _shared(g, [n], 12, 10)
+    p = _problem(g, "announced_longer", "squared", d, cols, [0, n // 2, n])
+    o = oracle_mod.OracleCoCoA.from_problem(p)
+    r = binding.ChicleRound(p.loss, n, d, p.lam, K, K, False, 120 * n)
+    for k in range(K):
+        a, b = p.chunk_rows(k)
+        r.load_chunk_csr(k, p.row_ptr[a:b + 1] - p.row_ptr[a], p.col[p.row_ptr[a]:p.row_ptr[b]], p.val[p.row_ptr[a]:p.row_ptr[b]], p.y[a:b])
+    table = np.arange(K, dtype=np.int32)
+    o.assign(K, table)
+    r.assign(K, table)
+    assert r.debug_solver()[:2] == ("batched", 3)
+    rows = [np.arange(*p.chunk_rows(k)) for k in range(K)]
+    perms = [[g.permutation(n // K) for _ in range(K)] for _ in range(3)]
+    assert all(x > 50 for order in perms for solver in tail_pairs(p, rows, order)[0] for x in solver[3:-1])
+    for i in range(2):
+        r.local_epoch_ahead(None if i else r.upload_perm(perms[0]), r.upload_perm(perms[i + 1]))
+        ref = o.local_epoch(perms[i])
+        for k in range(K):
+            assert rel_l2(r.get_delta_w(k), ref[k], dw_floor(float(np.linalg.norm(o.w)))) <= TOL_DW
+        o.aggregate()
+        r.aggregate()
     r.close()

@@ -94,6 +94,17 @@ def test_arena_bytes_and_create_argument_checks(lib):
         assert getattr(lib, fn)(None) == -1
 
 
+def test_pair_lists_are_reserved_where_the_split_solver_may_have_tails(lib):
+    n, tile = 64000, 2 * (512 * 8 + 4)               # two sets: 512 pairs and their number for 64 rows
+
+    def per_n_rows(d, entries):                      # what n rows more take, the entries being as many
+        return lib.chicle_arena_bytes(2 * n, entries, d, 4, 2, 0) - lib.chicle_arena_bytes(n, entries, d, 4, 2, 0)
+
+    short, long_rows = 40 * n, 300 * n
+    assert abs(per_n_rows(20000, short) - per_n_rows(6000, short) - tile * n // 64) <= 4 * 256
+    assert per_n_rows(20000, long_rows) == per_n_rows(6000, long_rows)
+
+
 def test_product_path_has_no_cpu_fallback():
     """Nothing in the package imports or mentions the oracle, and the binding refuses to run without a GPU."""
     pkg = os.path.join(ROOT, "paper_1909_04885_amd")
