@@ -687,12 +687,14 @@ int launch_affine(chicle_ctx *c, const int32_t *perm, int run)
     seg_begin(c, CHICLE_SEG_EPOCH_GRAM);
     static_assert(AFFINE_MAX_D == 32, "all row lengths of affine_maps");
     const dim3 mg = grid(d < 16 ? 16 : 32);
-    const bool alone = (int64_t)mg.x * mg.y <= c->cu_count;      // a workgroup's wavefronts are on a SIMD each
+    // A workgroup's wavefronts are on a SIMD each, and rows long enough (maps of 500000 rows, 16 solvers, and of 60000, one, with
+    // a row's words read ahead / not, between events, which adds some 7 us: 16 columns 65 / 64 and 47.4 / 45.7 us, 20 72 / 72
+    // and 52.7 / 51.8, 24 78 / 78 and 58.1 / 58.2, 28 86 / 91 and 64.3 / 70.2, 30 94 / 98 and 71.9 / 76.4, 32 102 / 107 and
+    // 79.8 / 83.8).
+    const bool alone = d > 24 && (int64_t)mg.x * mg.y <= c->cu_count;
     auto maps = d <= 4 ? affine_maps<4, 16, true, false> : d <= 8 ? affine_maps<8, 16, true, false> : d <= 12 ? affine_maps<12, 16, true, false>
                 : d < 16 ? affine_maps<16, 16, true, false>
-                : d <= 16 ? (alone ? affine_maps<16, 32, true, true> : affine_maps<16, 32, true, false>)
-                : d <= 20 ? (alone ? affine_maps<20, 32, true, true> : affine_maps<20, 32, true, false>)
-                : d <= 24 ? (alone ? affine_maps<24, 32, true, true> : affine_maps<24, 32, true, false>)
+                : d <= 16 ? affine_maps<16, 32, true, false> : d <= 20 ? affine_maps<20, 32, true, false> : d <= 24 ? affine_maps<24, 32, true, false>
                 : d <= 28 ? (alone ? affine_maps<28, 32, true, true> : affine_maps<28, 32, true, false>)
                 : d < 32 ? (alone ? affine_maps<32, 32, true, true> : affine_maps<32, 32, true, false>)
                 : (alone ? affine_maps<32, 32, false, true> : affine_maps<32, 32, false, false>);

@@ -87,7 +87,7 @@ __device__ __forceinline__ double affine_scale(float q, float c) { return (doubl
 // SPARE: a run has more lanes than a row has columns, and the one after the last holds b as a column of its own (a row without
 // a column there leaves P's as it is), so that no sum over lanes stands in the chain from row to row.
 // ALONE: the wavefronts are no more than the SIMDs, so that nothing hides a wavefront's reads of a row's words but its own
-// arithmetic on the row before.
+// arithmetic on the row before (rows of more than 24 columns: the shorter ones' words are here soon enough, see launch_affine).
 template <int DK, int LANES, bool SPARE, bool ALONE>
 __global__ __launch_bounds__(64 * AFFINE_WAVES) void affine_maps(
     const ChunkDev *__restrict__ chunks, const SolverDev *__restrict__ solvers, const int32_t *__restrict__ row_chunk,
