@@ -80,11 +80,11 @@ __global__ __launch_bounds__(256) void delta_w_out(const float *u_all, int64_t l
 // u_off[k]: where solver k's compact vector starts in u.  Reads and clears only what the solvers touched.
 // Where there are few words (few workgroups), the solvers are divided over gridDim.y slices as well; the
 // slices then add their sums into the double-precision vector with atomic adds, and the one that is done last refreshes the
-// float mirror (tickets[blockIdx.x]: zero, and left so; a pass of its own over the mirror took 5 us).
+// float mirror (tickets[blockIdx.x]: zero, and left so; a pass of its own over the mirror took 5 us, which these 2048 columns
+// do not).
 constexpr int AGG_THREADS = 256, AGG_WORDS = 64;     // threads and words per workgroup
 constexpr int AGG_THIN_WORDS = 256;                  // ... of aggregate_compact_thin
 static_assert(AGG_THIN_WORDS == AGG_THREADS, "a thread per word");
-template <int WORDS>
 __device__ __forceinline__ void mirror_by_last_slice(const double *w64, float *w32, int64_t d, double l1, unsigned *tickets)
 {
     __shared__ int last;
@@ -94,19 +94,17 @@ __device__ __forceinline__ void mirror_by_last_slice(const double *w64, float *w
     __syncthreads();
     if (!last) return;
     if (threadIdx.x == 0) __hip_atomic_store(tickets + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int64_t c0 = (int64_t)blockIdx.x * WORDS * 32 + threadIdx.x;
-    for (int i = 0; i < WORDS * 32 / AGG_THREADS; i += 8) {
-        double x[8];
+    const int64_t c0 = (int64_t)blockIdx.x * AGG_WORDS * 32 + threadIdx.x;
+    double x[AGG_WORDS * 32 / AGG_THREADS];          // one trip to memory
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int64_t c = c0 + (i + q) * AGG_THREADS;
-            x[q] = c < d ? __hip_atomic_load(w64 + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
-        }
+    for (int q = 0; q < AGG_WORDS * 32 / AGG_THREADS; ++q) {
+        const int64_t c = c0 + q * AGG_THREADS;
+        x[q] = c < d ? __hip_atomic_load(w64 + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+    }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int64_t c = c0 + (i + q) * AGG_THREADS;
-            if (c < d) w32[c] = (float)soft_threshold(x[q], l1);
-        }
+    for (int q = 0; q < AGG_WORDS * 32 / AGG_THREADS; ++q) {
+        const int64_t c = c0 + q * AGG_THREADS;
+        if (c < d) w32[c] = (float)soft_threshold(x[q], l1);
     }
 }
 
@@ -177,7 +175,7 @@ __global__ __launch_bounds__(AGG_THREADS) void aggregate_compact(double *w64, fl
             }
         }
     }
-    if (gridDim.y > 1) mirror_by_last_slice<AGG_WORDS>(w64, w32, d, l1, tickets);
+    if (gridDim.y > 1) mirror_by_last_slice(w64, w32, d, l1, tickets);
 }
 
 // The same merge for thinly occupied vectors (long rows over many columns: a solver holds a few of every
@@ -188,11 +186,14 @@ __global__ __launch_bounds__(AGG_THREADS) void aggregate_compact(double *w64, fl
 // a padded array, touched by that thread alone until the end), with no barrier inside the walk over the
 // solvers.  What it waits for are trips to memory, so it takes THIN_SOLVERS solvers at a time, the first THIN_FIRST entries of all
 // of them in flight together and the next ones' words and prefixes before that: 64 solvers, 20M columns, 96M entries 537 us
-// one solver at a time, 434 now (1.5 GB).
+// one solver at a time, 434 now (1.5 GB).  Further entries of a word, which only popular columns have, follow THIN_FIRST at a
+// time (one at a time: 96 solvers over 127k columns 90 us, 82 so).  The mirror is a pass of its own here: 8192 columns are
+// too many for the one workgroup that is done last (50 solvers over 252k columns 40 us with it, 29.5 so; 42 over 168k 29 and
+// 19.5).
 constexpr int THIN_SOLVERS = 4, THIN_FIRST = 8;
 __global__ __launch_bounds__(AGG_THIN_WORDS) void aggregate_compact_thin(double *w64, float *w32, float *u, const int64_t *__restrict__ u_off,
                                                                     const unsigned *__restrict__ bits, const int32_t *__restrict__ pref,
-                                                                    int64_t words, int64_t d, int K, float inv_sigma, double l1, unsigned *tickets)
+                                                                    int64_t words, int64_t d, int K, float inv_sigma, double l1)
 {
     __shared__ float sums[AGG_THIN_WORDS * 33];
     __shared__ unsigned touched[AGG_THIN_WORDS];
@@ -241,9 +242,17 @@ __global__ __launch_bounds__(AGG_THIN_WORDS) void aggregate_compact_thin(double 
                     uk[s][q] = 0.f;
                     r &= r - 1;
                 }
-            for (float *rest = uk[s] + THIN_FIRST; r; ++rest, r &= r - 1) {
-                mine[__ffs(r) - 1] += *rest;
-                *rest = 0.f;
+            for (float *rest = uk[s] + THIN_FIRST; r; rest += THIN_FIRST) {      // (words of popular columns)
+                float x[THIN_FIRST];
+#pragma unroll
+                for (int q = 0; q < THIN_FIRST; ++q) x[q] = q < __popc(r) ? rest[q] : 0.f;
+#pragma unroll
+                for (int q = 0; q < THIN_FIRST; ++q)
+                    if (r) {
+                        mine[__ffs(r) - 1] += x[q];
+                        rest[q] = 0.f;
+                        r &= r - 1;
+                    }
             }
         }
     }
@@ -263,7 +272,6 @@ __global__ __launch_bounds__(AGG_THIN_WORDS) void aggregate_compact_thin(double 
             }
         }
     }
-    if (gridDim.y > 1) mirror_by_last_slice<AGG_THIN_WORDS>(w64, w32, d, l1, tickets);
 }
 
 __global__ __launch_bounds__(256) void mirror_from_double(const double *__restrict__ w64, float *w32, int64_t d, double l1)

@@ -1737,9 +1737,15 @@ int chicle_aggregate(chicle_ctx *c)
         const int wg_words = thin ? AGG_THIN_WORDS : AGG_WORDS;
         const unsigned gx = (unsigned)((c->words + wg_words - 1) / wg_words);
         const unsigned gy = (unsigned)std::max(1, std::min(c->K, (int)(1024 / gx)));
-        hipLaunchKernelGGL(thin ? aggregate_compact_thin : aggregate_compact, dim3(gx, gy), dim3(AGG_THREADS), 0, c->stream, c->w64, c->w,
-                           c->u, c->u_off_dev, c->bits_dev, c->pref_dev, c->words, (int64_t)c->d, c->K,
-                           (float)(1.0 / (double)c->K), c->l1, c->tickets_dev + GAP_TICKETS);
+        const float inv_sigma = (float)(1.0 / (double)c->K);
+        if (thin) {
+            hipLaunchKernelGGL(aggregate_compact_thin, dim3(gx, gy), dim3(AGG_THIN_WORDS), 0, c->stream, c->w64, c->w, c->u, c->u_off_dev, c->bits_dev,
+                               c->pref_dev, c->words, (int64_t)c->d, c->K, inv_sigma, c->l1);
+            if (gy > 1)
+                hipLaunchKernelGGL(mirror_from_double, dim3(grid_for(c->d, 256, 2048)), dim3(256), 0, c->stream, c->w64, c->w, (int64_t)c->d, c->l1);
+        } else
+            hipLaunchKernelGGL(aggregate_compact, dim3(gx, gy), dim3(AGG_THREADS), 0, c->stream, c->w64, c->w, c->u, c->u_off_dev, c->bits_dev,
+                               c->pref_dev, c->words, (int64_t)c->d, c->K, inv_sigma, c->l1, c->tickets_dev + GAP_TICKETS);
     } else
         hipLaunchKernelGGL(aggregate_broadcast, dim3(grid_for(d4, 256, 4096)), dim3(256), 0, c->stream, c->w64, c->w,
                            c->u, c->ld_v, d4, c->K, (float)(1.0 / (double)c->K), c->l1);

@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d,n,m,K", [(1, 70, 1, 1), (31, 90, 3, 2), (2048, 400, 12, 3), (2049, 700, 60, 5), (70001, 3000, 20, 40), (300000, 300, 40, 30),
-                                     (40, 900, 0, 4)])
+                                     (2000000, 1200, 40, 24), (40, 900, 0, 4)])
 def test_merge_and_gap(d, n, m, K):
     import torch
     import paper_1909_04885_amd as chicle
