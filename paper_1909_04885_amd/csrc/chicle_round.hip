@@ -608,16 +608,25 @@ int launch_rowwise(chicle_ctx *c, const int32_t *perm)
 // The last 24 entries of a row cover every row's columns outside the LDS-resident head.
 bool short_tails(const chicle_ctx *c) { return c->compact && c->max_tail_entries <= 3 * LPR; }
 
-// Whether pairs are listed beside the tiles, for the split solver's look-back of four blocks.  It saves 0.9 us per block of the
-// longest solver.  Where the last 24 entries of a row are enough, listing costs 0.008 us per tile, which 80 solvers do not reach;
-// where not, 0.029: four rounds of 16 solvers of 12500 rows of 40 entries in uniform columns 2.93 ms without and 2.56 with, 64 of
-// 4688 rows of 44 2.99 and 3.40.  Nothing is saved where blocks have more pairs than a list holds, which the columns' shares of
+// Whether pairs are listed beside the tiles (ahead: of the pass after this one), for the split solver's look-back of four blocks.
+// It saves up to 0.9 us per block of the longest solver.  Lists formed ahead cost the chip what the pass leaves of it: where the
+// last 24 entries of a row are enough, 0.008 us per tile, which 80 solvers do not reach; where not, 0.029: four rounds of 16
+// solvers of 12500 rows of 40 entries in uniform columns 2.93 ms without and 2.56 with, 64 of 4688 rows of 44 2.99 and 3.40.  A
+// few blocks save less than the kernel's launch: rounds of one solver of 512 rows 74.7 us without and 78.4 with, of 768 73.8 and
+// 70.9; of 16 of 384 72.5 and 75.0, of 640 84.5 and 82.4, of 768 91.4 and 86.3.
+// Lists formed before the pass that uses them add their kernel to it, and small jobs save half a microsecond per block, from the
+// fifth or so on: passes of one solver of 512 rows 52 us without and 55 with, of 1024 69 and 68, of 2560 122 and 103; 16 of 640
+// rows 64 and 70, of 2560 152 and 159 (uniform columns: 166 and 189).  With the logistic loss, whose chain takes longer than the
+// tails, nothing: one of 2560 rows 263 and 267, 16 290 and 313; ahead it is 318 and 313, 358 and 355.
+// Nothing is saved where blocks have more pairs than a list holds, which the columns' shares of
 // the rows tell for rows in random order (16 solvers of 12500 rows of 48 entries in 16400 columns, 3.12 and 3.27).
-bool lists_pairs(const chicle_ctx *c)
+bool lists_pairs(const chicle_ctx *c, bool ahead)
 {
     if (split_tails(c) <= 0 || !c->pair_list[0]) return false;
     const int blocks = (c->most_rows + BATCH - 1) / BATCH;
-    if (!short_tails(c) && 32 * (int64_t)blocks <= c->n_tiles) return false;
+    const bool narrow = short_tails(c);
+    if (blocks < 12 || (!narrow && 32 * (int64_t)blocks <= c->n_tiles)) return false;
+    if (!ahead && (c->loss == CHICLE_LOSS_LOGISTIC || 0.5 * (blocks - 4) <= (narrow ? 6.5 + 0.0075 * c->n_tiles : 9.0 + 0.05 * c->n_tiles))) return false;
     const size_t at = (size_t)batched_layout(c).n_hot / 64;
     return at >= c->shares.size() || (LAG - 2) * (double)(BATCH * BATCH) * c->shares[at] <= 0.85 * PAIR_CAP;
 }
@@ -665,7 +674,7 @@ int launch_gram(chicle_ctx *c, const int32_t *perm, int buf, bool ahead, hipStre
         hipLaunchKernelGGL(kern, dim3(grid), dim3(GRAM_THREADS), sizeof(GramShared), stream,
                            c->chunks_dev, c->solvers_dev, c->row_chunk_dev, c->chunk_first_dev, perm,
                            c->tile_solver_dev, c->tiles[buf], c->n_tiles, sc.c, c->err_dev);
-        c->pairs_listed[buf] = lists_pairs(c);
+        c->pairs_listed[buf] = lists_pairs(c, ahead);
         if (c->pairs_listed[buf]) {
             const int rc = short_tails(c) ? launch_pairs<3>(c, perm, buf, stream) : launch_pairs<ENT>(c, perm, buf, stream);
             if (rc) return rc;

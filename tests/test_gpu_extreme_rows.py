@@ -105,8 +105,9 @@ def test_huge_rows_that_share_a_column_blocks_apart(loss):
         r.assign(1, np.zeros(1, dtype=np.int32))
         r.set_solver(solver)
         assert solver == "rowwise" or r.debug_solver()[:2] == ("batched", 3)
-        r.local_epoch(r.upload_perm([order]))
-        r.aggregate()
+        for announced in (False, True):          # (pairs are always listed with the tiles of announced orders here)
+            r.local_epoch_ahead(None if announced else r.upload_perm([order]), r.upload_perm([order]))
+            r.aggregate()
         got.append((r.get_alpha(0), r.get_w()))
         r.close()
     (alpha, w), (alpha_rows, w_rows) = got
