@@ -758,17 +758,17 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
         A.chunks = c->chunks_dev; A.solvers = c->solvers_dev; A.solver_chunks = c->solver_chunks_dev;
         A.solver_prefix = c->solver_prefix_dev; A.perm = perm; A.tiles = c->tiles[c->tile_buf]; A.u_all = c->u;
         A.ld_v = c->ld_v; A.u_off = u_off; A.max_list = ml; A.n_hot = n_hot; A.hot_off = (int)hot_off; A.sc = sc;
-        A.err = c->err_dev; A.n_tails = n_tails; A.xchg_all = c->split_ring_dev;
+        A.err = c->err_dev; A.xchg_all = c->split_ring_dev;
         A.lag = c->pairs_listed[c->tile_buf] ? LAG : 2; A.pair_list = c->pair_list[c->tile_buf]; A.pair_count = c->pair_count[c->tile_buf];
         // a tail's lanes take the last 24 entries of a row where that covers every row's unpopular columns
         constexpr int TE_SHORT = 3 * LPR / TAIL_LPR, TE_ALL = GRAM_MAX_ROW / TAIL_LPR;
-        auto kern = short_tails(c) ? sdca_batched_split<LOSS, TE_SHORT> : sdca_batched_split<LOSS, TE_ALL>;
+        auto kern = n_tails == 0 ? sdca_batched_heads<LOSS> : short_tails(c) ? sdca_batched_split<LOSS, TE_SHORT> : sdca_batched_split<LOSS, TE_ALL>;
         if (n_tails > 0 && tail_lists_at(short_tails(c) ? TE_SHORT : TE_ALL) + (sizeof(ChunkDev) + sizeof(int)) * (size_t)ml > sh)
             return fail(c, CHICLE_ESTATE, "the tails' state does not fit LDS");
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
         clear_device_words(c, c->split_ring_dev, 2 * (int64_t)SPLIT_WORDS * c->K);
         seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
-        hipLaunchKernelGGL(kern, dim3((1 + n_tails) * k_pad), dim3(SPLIT_THREADS), sh, c->stream, A, k_pad);
+        hipLaunchKernelGGL(kern, dim3((1 + n_tails) * k_pad), dim3(n_tails == 0 ? BATCHED_THREADS : SPLIT_THREADS), sh, c->stream, A, k_pad);
         seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
     } else {
         auto kern = sdca_batched_csr<LOSS>;

@@ -30,7 +30,7 @@ constexpr int SPLIT_TAILS = 2;
 constexpr int LAG = 4;                         // unpopular columns: blocks <= b - LAG are in what block b gathers
 constexpr int SPLIT_WORDS = (1 + SPLIT_TAILS) * SPLIT_RING * BATCH;      // 64-bit words per solver
 constexpr int SPLIT_SPIN_LIMIT = 1 << 22;      // polls before a wait for the partner gives up
-constexpr int SPLIT_THREADS = BATCHED_THREADS + 192;  // the single-workgroup solver's wavefronts, and one each that polls the rings, resolves rows, adds up pairs
+constexpr int SPLIT_THREADS = BATCHED_THREADS + 192;  // the single-workgroup solver's wavefronts, and one each that resolves rows, polls the rings, adds up pairs
 
 __device__ __forceinline__ void ring_put(unsigned long long *p, float v, int tag)
 {
@@ -176,7 +176,6 @@ struct SplitArgs {
     int max_list, n_hot, hot_off;
     RoundScalars sc;
     int *err;
-    int n_tails;
     unsigned long long *xchg_all;
     int lag;                    // LAG, or 2: no pairs were listed
     const unsigned long long *pair_list;     // beside the tiles (split_pairs)
@@ -184,10 +183,11 @@ struct SplitArgs {
 };
 
 // Common start of both kinds of workgroup: the solver's chunk list into LDS.
+template <int THREADS>
 __device__ __forceinline__ void split_stage_lists(unsigned char *smem, const SplitArgs &A, const SolverDev &S,
                                                   ChunkDev *l_desc, int *l_prefix)
 {
-    for (int i = threadIdx.x; i < S.n_chunks; i += SPLIT_THREADS) {
+    for (int i = threadIdx.x; i < S.n_chunks; i += THREADS) {
         l_desc[i] = A.chunks[A.solver_chunks[S.list_begin + i]];
         if (A.u_off) l_desc[i].col = chunk_compact_ids(l_desc[i]);     // compact private vector: its indices, not column ids
         l_prefix[i] = A.solver_prefix[S.list_begin + i];
@@ -208,11 +208,17 @@ __device__ __forceinline__ int split_lag(const SplitArgs &A, const SolverDev &S,
 }
 
 // ---- the head workgroup: recurrence, tiles, the popular columns in LDS -------------------------------------
-// Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 stage the tiles, 11
-// fetches the tails' partial sums, 12 resolves rows, 13 adds up what comes through pairs.  One loop per role, all with the same number of iterations and one
-// workgroup barrier per iteration, so that the registers of one role are not kept alive through the code of
+// Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 stage the tiles.  Where there are tails, 11 resolves
+// rows, 12 fetches their partial sums and 13 adds up what comes through pairs.  One loop per role, all with the same number of
+// iterations and one workgroup barrier per iteration, so that the registers of one role are not kept alive through the code of
 // the others.
-template <int LOSS>
+// TAILS: there are tails.  Else all columns are in the head and nothing is waited for but its own LDS: 9 resolves rows beside
+// its tile, since more wavefronts would take issue slots from the chain, and a row's entries go to its lanes in turn, so that
+// short rows take as many adds and reads as they have entries to a lane (sixteen bytes at a time, a lane's entries lie
+// together, and all six of its adds are issued whatever the row's length).  Five solvers of 40000 rows of 12 entries in 466
+// columns, squared loss: 1.44 us a block with the wavefronts and loads that tails need, 1.23 so; six of 30700 rows of 29 1.52
+// and 1.36; hinge loss, 40 of 5000 rows of 12 1.53 and 1.34, two of 30000 rows of 40 in 5000 columns 1.29 and 1.26.
+template <int LOSS, bool TAILS>
 __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs &A, int sid)
 {
     BatchedShared &sh = *reinterpret_cast<BatchedShared *>(smem);
@@ -222,12 +228,13 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
     const RoundScalars &sc = A.sc;
     const int tid = threadIdx.x, n_hot = A.n_hot;
     stamp_solver(sc, sid, 0);
-    split_stage_lists(smem, A, S, l_desc, l_prefix);
+    constexpr int THREADS = TAILS ? SPLIT_THREADS : BATCHED_THREADS;
+    split_stage_lists<THREADS>(smem, A, S, l_desc, l_prefix);
     double *hot = reinterpret_cast<double *>(smem + A.hot_off);
-    for (int i = tid; i < n_hot; i += SPLIT_THREADS) hot[i] = 0.0;
+    for (int i = tid; i < n_hot; i += THREADS) hot[i] = 0.0;
     if (tid == 0) { sh.hb = 0; sh.dead = 0; sh.xflag = 0; sh.cflag = 0; }
     const int nb = (S.n_rows + BATCH - 1) / BATCH;
-    const bool pairs = A.n_tails > 0 && split_lag(A, S, nb, &sh.over) == LAG;
+    const bool pairs = TAILS && split_lag(A, S, nb, &sh.over) == LAG;
     __syncthreads();
     float *u = A.u_off ? A.u_all + A.u_off[sid] : A.u_all + (int64_t)sid * A.ld_v;
     const int32_t *pk = A.perm + S.perm_off;
@@ -247,15 +254,15 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             if (i >= 0 && i < nb) {
                 chain_block<LOSS>(sh, i, lane, x_carry, sc.inv_c, sh.steps[i & 3]);
                 // the tails add these steps into their columns
-                if (A.n_tails > 0) ring_put(x_steps + (i & (SPLIT_RING - 1)) * BATCH + lane, sh.steps[i & 3][lane], i + 1);
+                if (TAILS) ring_put(x_steps + (i & (SPLIT_RING - 1)) * BATCH + lane, sh.steps[i & 3][lane], i + 1);
             }
             __syncthreads();
         }
-    } else if (wave == 11) {
+    } else if (TAILS && wave == 12) {
         // What the tails send for this iteration, fetched by a wavefront that has no other loads in flight
         // (loads return in the order they were issued) and handed on through LDS.
         HEAD_ITERATIONS {
-            if (A.n_tails > 0 && i + 1 >= 0 && i + 1 < nb) {
+            if (i + 1 >= 0 && i + 1 < nb) {
                 float part = ring_wait<SPLIT_TAILS>(x_parts + ((i + 1) & (SPLIT_RING - 1)) * BATCH + lane, SPLIT_RING * BATCH, i + 2, &sh.dead, A.err);
                 if (pairs) {
                     wait_flag(&sh.cflag, i + 2);
@@ -266,7 +273,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             }
             __syncthreads();
         }
-    } else if (wave == 13) {
+    } else if (TAILS && wave == 13) {
         // What blocks i - 1 and i - 2, whose steps are at hand, add to block i + 1's dot products through pairs.  The pairs were
         // asked for an iteration ago, their number two.  (In the polling wavefront this kept the polls waiting: 5.0e3
         // cycles an iteration, 4.7e3 now; 32 solvers of 62500 rows 2.15 and 2.02 ms.)
@@ -302,7 +309,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             if (pairs && i + 3 >= 0 && i + 3 < nb) far = gld(counts + min(i + 3 + lane, nb - 1));
             __syncthreads();
         }
-    } else if (wave == 12) {
+    } else if (TAILS && wave == 11) {
         // (one block further ahead than the tails' resolvers: the helpers ask for a block's entries three
         // iterations before they gather it)
         RowResolver resolver;
@@ -314,6 +321,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
         const int sw = wave - 9;
         float4 stage[16];                                // tile part fetched ahead
         bool staged = false;
+        RowResolver resolver;
         HEAD_ITERATIONS {
             // tiles for iteration i + 1 (wavefront 9: own part of T(i+1), wavefront 10: cross part of T(i+2),
             // 16 KB each) were fetched into registers during the last iteration
@@ -321,6 +329,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             float4 *dst = reinterpret_cast<float4 *>(sw == 0 ? &sh.Tw[buf][0][0] : &sh.Tx[buf][0][0]);
 #pragma unroll
             for (int j = 0; j < 16; ++j) dst[lane + 64 * j] = staged ? stage[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!TAILS && sw == 0) resolver.step(sh.rows, RING - 1, l_desc, l_prefix, S, pk, i + 1, 0, 1, nb, lane, A.err, true);
             const int tb = sw == 0 ? i + 2 : i + 3;
             staged = tb >= 0 && tb < nb;
             if (staged) {
@@ -332,7 +341,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             __syncthreads();
         }
     } else {
-        // Entries of a row segment (ENT entries per helper lane) travel through five stages:
+        // Entries of a row (ENT per helper lane) travel through five stages:
         // ld (loads in flight) -> ar (arrived: asked for one iteration ago) -> g (gathered this iteration) ->
         // c (its block is in the chain) -> s (scattered).  Loads get a whole iteration before anything looks at
         // them; ld and ar swap register sets from one iteration to the next (nothing moves a register that a
@@ -355,6 +364,13 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             const RowSlot r_s = sh.rows[(i - 1) & (RING - 1)][rho];
             const RowSlot r_g = sh.rows[(i + 1) & (RING - 1)][rho];
             const float dl = sh.steps[(i - 1) & 3][rho];
+            ld_len = has_in ? r_in.len : 0;
+            if (!TAILS && has_in) {                      // this lane's entries of the row of block i + 3
+                const int32_t *cp = r_in.col + sub;
+                const float *vp = r_in.val + sub;
+#pragma unroll
+                for (int e = 0; e < ENT; ++e) { ld_c[e] = gld(cp + e * LPR); ld_v[e] = gld(vp + e * LPR); }
+            }
             // 1. block i - 1 is added to the head of the private vector
             if (has_s && r_s.len > 0 && dl != 0.f) {
                 const float coef = dl * (LOSS == 1 ? 1.f : r_s.y) * sc.inv_c;
@@ -367,13 +383,12 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
                     gst(&r_s.st->alpha, an);
                 }
             }
-            // 2. ... completely, before block i + 1 is gathered (LDS traffic only); meanwhile this lane's segment of the row
-            //    of block i + 3 is asked for
+            // 2. ... completely, before block i + 1 is gathered (LDS traffic only); meanwhile, with tails, this lane's segment
+            //    of the row of block i + 3 is asked for
             helper_arrive_lds(&sh.hb);
-            if (has_in) {
+            if (TAILS && has_in) {
                 const int32_t *cp = r_in.col + sub * ENT;
                 const float *vp = r_in.val + sub * ENT;
-                ld_len = r_in.len;
                 static_assert(ENT == 6, "a lane's entries are loaded four and two at a time");
                 const int4_a4 c4 = gld4(cp);
                 const int2_a4 c2 = gld2(cp + 4);
@@ -383,8 +398,6 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
                 for (int e = 0; e < 4; ++e) { ld_c[e] = c4[e]; ld_v[e] = v4[e]; }
 #pragma unroll
                 for (int e = 0; e < 2; ++e) { ld_c[4 + e] = c2[e]; ld_v[4 + e] = v2[e]; }
-            } else {
-                ld_len = 0;
             }
             hb_target += HELPER_WAVES;
             helper_wait_lds(&sh.hb, hb_target);
@@ -406,7 +419,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
                     if (live && LOSS == 0) { scale = sc.c / r_g.q; lo = -r_g.alpha; hi = 1.f - r_g.alpha; }
                     if (live && LOSS == 1) scale = sc.c / (sc.c + r_g.q);
                     if (LOSS != 2) { sh.lo[ring][rho] = lo; sh.hi[ring][rho] = hi; }
-                    if (A.n_tails > 0) {
+                    if (TAILS) {
                         wait_flag(&sh.xflag, i + 2);
                         part += sh.xv[rho];                               // the tails' share of x_i . u
                     }
@@ -432,7 +445,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             for (int e = 0; e < ENT; ++e) {
                 s_c[e] = c_c[e]; s_v[e] = c_v[e];
                 c_c[e] = g_c[e]; c_v[e] = g_v[e];
-                const bool live = sub * ENT + e < ar_len && ar_c[e] < n_hot;
+                const bool live = (TAILS ? sub * ENT + e : sub + e * LPR) < ar_len && ar_c[e] < n_hot;
                 g_c[e] = live ? ar_c[e] : 0;
                 g_v[e] = live ? ar_v[e] : 0.f;
             }
@@ -444,7 +457,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
         }
     }
 #undef HEAD_ITERATIONS
-    for (int i = tid; i < n_hot; i += SPLIT_THREADS) u[i] = (float)hot[i];
+    for (int i = tid; i < n_hot; i += THREADS) u[i] = (float)hot[i];
     stamp_solver(sc, sid, 1);
 }
 
@@ -496,7 +509,7 @@ __device__ __forceinline__ void split_tail(unsigned char *smem, const SplitArgs 
     const SolverDev S = A.solvers[sid];
     const RoundScalars &sc = A.sc;
     const int tid = threadIdx.x, n_hot = A.n_hot;
-    split_stage_lists(smem, A, S, l_desc, l_prefix);
+    split_stage_lists<SPLIT_THREADS>(smem, A, S, l_desc, l_prefix);
     if (tid == 0) {
         sh.steps_ready = sh.issued = sh.dead = 0;
         for (int g = 0; g < TAIL_GROUPS; ++g) sh.rows_ready[g] = sh.loaded[g] = sh.bar[g] = 0;
@@ -624,8 +637,16 @@ __global__ __launch_bounds__(SPLIT_THREADS) void sdca_batched_split(SplitArgs A,
     extern __shared__ __align__(16) unsigned char smem[];
     const int role = (int)blockIdx.x / k_pad, sid = (int)blockIdx.x % k_pad;
     if (sid >= A.sc.K) return;
-    if (role == 0) split_head<LOSS>(smem, A, sid);
+    if (role == 0) split_head<LOSS, true>(smem, A, sid);
     else split_tail<LOSS, TE>(smem, A, sid, role - 1);
+}
+
+// Solvers all of whose columns are in the head: workgroup k is solver k.
+template <int LOSS>
+__global__ __launch_bounds__(BATCHED_THREADS) void sdca_batched_heads(SplitArgs A, int)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    if ((int)blockIdx.x < A.sc.K) split_head<LOSS, false>(smem, A, (int)blockIdx.x);
 }
 
 }  // namespace chicle
