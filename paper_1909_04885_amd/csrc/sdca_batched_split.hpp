@@ -30,7 +30,7 @@ constexpr int SPLIT_TAILS = 2;
 constexpr int LAG = 4;                         // unpopular columns: blocks <= b - LAG are in what block b gathers
 constexpr int SPLIT_WORDS = (1 + SPLIT_TAILS) * SPLIT_RING * BATCH;      // 64-bit words per solver
 constexpr int SPLIT_SPIN_LIMIT = 1 << 22;      // polls before a wait for the partner gives up
-constexpr int SPLIT_THREADS = BATCHED_THREADS + 192;  // the single-workgroup solver's wavefronts, and one each that resolves rows, polls the rings, adds up pairs
+constexpr int SPLIT_THREADS = BATCHED_THREADS + 192;  // the single-workgroup solver's wavefronts, and one each that polls the rings, resolves rows, adds up pairs
 
 __device__ __forceinline__ void ring_put(unsigned long long *p, float v, int tag)
 {
@@ -208,8 +208,9 @@ __device__ __forceinline__ int split_lag(const SplitArgs &A, const SolverDev &S,
 }
 
 // ---- the head workgroup: recurrence, tiles, the popular columns in LDS -------------------------------------
-// Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 stage the tiles.  Where there are tails, 11 resolves
-// rows, 12 fetches their partial sums and 13 adds up what comes through pairs.  One loop per role, all with the same number of
+// Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 stage the tiles.  Where there are tails, 11
+// fetches their partial sums, 12 resolves rows and 13 adds up what comes through pairs (12 shares a SIMD with the chain, which
+// polls would keep from issuing: six solvers of 5000 rows 1 % of the job).  One loop per role, all with the same number of
 // iterations and one workgroup barrier per iteration, so that the registers of one role are not kept alive through the code of
 // the others.
 // TAILS: there are tails.  Else all columns are in the head and nothing is waited for but its own LDS: 9 resolves rows beside
@@ -258,7 +259,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             }
             __syncthreads();
         }
-    } else if (TAILS && wave == 12) {
+    } else if (TAILS && wave == 11) {
         // What the tails send for this iteration, fetched by a wavefront that has no other loads in flight
         // (loads return in the order they were issued) and handed on through LDS.
         HEAD_ITERATIONS {
@@ -309,7 +310,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             if (pairs && i + 3 >= 0 && i + 3 < nb) far = gld(counts + min(i + 3 + lane, nb - 1));
             __syncthreads();
         }
-    } else if (TAILS && wave == 11) {
+    } else if (TAILS && wave == 12) {
         // (one block further ahead than the tails' resolvers: the helpers ask for a block's entries three
         // iterations before they gather it)
         RowResolver resolver;
@@ -325,7 +326,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
         HEAD_ITERATIONS {
             // tiles for iteration i + 1 (wavefront 9: own part of T(i+1), wavefront 10: cross part of T(i+2),
             // 16 KB each) were fetched into registers during the last iteration
-            const int buf = (i + 1) & 1;
+            const int ring = (i + 1) & (RING - 1);
             float4 *dst = reinterpret_cast<float4 *>(sw == 0 ? &sh.Tw[buf][0][0] : &sh.Tx[buf][0][0]);
 #pragma unroll
             for (int j = 0; j < 16; ++j) dst[lane + 64 * j] = staged ? stage[j] : make_float4(0.f, 0.f, 0.f, 0.f);
