@@ -71,7 +71,7 @@ __device__ __forceinline__ float clamp_step(float t, float lo, float hi)
 
 struct BatchedShared {
     RowSlot rows[RING][BATCH];
-    float t0[RING][BATCH], lo[RING][BATCH], hi[RING][BATCH];
+    float t0[2][BATCH], lo[2][BATCH], hi[2][BATCH];     // by block & 1: gathered while the block before is in the chain
     float delta[2][BATCH];
     float4_v Tw[2][BATCH / 4][BATCH];   // own part of block i's T: [j / 4][lane][j % 4]
     float4_v Tx[2][BATCH / 4][BATCH];   // cross part of block i+1's T, likewise
@@ -93,13 +93,13 @@ struct BatchedShared {
 template <int LOSS>
 __device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
 {
-    const int ring = i & (RING - 1), buf = i & 1;
+    const int buf = i & 1;
     float4_v T[BATCH / 4];
 #pragma unroll
     for (int jq = 0; jq < BATCH / 4; ++jq) T[jq] = sh.Tw[buf][jq][lane];
     asm volatile("" ::: "memory");           // (all of them are requested here)
-    float t = sh.t0[ring][lane] + x_carry;
-    const float lo = sh.lo[ring][lane], hi = sh.hi[ring][lane];
+    float t = sh.t0[buf][lane] + x_carry;
+    const float lo = sh.lo[buf][lane], hi = sh.hi[buf][lane];
     constexpr int AT_ONCE = 16;
     float x = 0.f, s = 0.f, xc = 0.f;
 #pragma unroll
@@ -127,9 +127,9 @@ __device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, 
 template <int LOSS>
 __device__ __forceinline__ void chain_block_small(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
 {
-    const int ring = i & (RING - 1), buf = i & 1;
-    float t = sh.t0[ring][lane] + x_carry;
-    const float lo = sh.lo[ring][lane], hi = sh.hi[ring][lane];
+    const int buf = i & 1;
+    float t = sh.t0[buf][lane] + x_carry;
+    const float lo = sh.lo[buf][lane], hi = sh.hi[buf][lane];
     float x = 0.f;
 #pragma unroll
     for (int jq = 0; jq < BATCH / 4; ++jq) {
@@ -152,12 +152,12 @@ __device__ __forceinline__ void chain_block_small(BatchedShared &sh, int i, int 
 template <>
 __device__ __forceinline__ void chain_block<2>(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
 {
-    const int ring = i & (RING - 1), buf = i & 1;
-    const RowSlot &row = sh.rows[ring][lane];
+    const int buf = i & 1;
+    const RowSlot &row = sh.rows[i & (RING - 1)][lane];
     const float a = row.alpha, r = row.len > 0 ? row.q * inv_c : 0.f;      // r = 0 marks a row to skip
     float x = 0.f;
     steps[lane] = logistic_block<BATCH>(
-        sh.t0[ring][lane] + x_carry, a, r, sh.lo[ring][lane], lane, [&](int jq) { return sh.Tw[buf][jq][lane]; },
+        sh.t0[buf][lane] + x_carry, a, r, sh.lo[buf][lane], lane, [&](int jq) { return sh.Tw[buf][jq][lane]; },
         [&](int jq, float d0, float d1, float d2, float d3) {
             const float4_v X = sh.Tx[buf][jq][lane];
             x = fmaf(d0, X[0], fmaf(d1, X[1], fmaf(d2, X[2], fmaf(d3, X[3], x))));
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(BATCHED_THREADS) void sdca_batched_csr(
 #pragma unroll
                 for (int o = 1; o < LPR; o <<= 1) part += __shfl_xor(part, o, 64);
                 if (sub == 0) {
-                    const int ring = (i + 1) & (RING - 1);
+                    const int buf = (i + 1) & 1;
                     float t0 = 0.f, lo = 0.f, hi = 0.f;
                     if (r.len > 0) {
                         if (LOSS == 0) {
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(BATCHED_THREADS) void sdca_batched_csr(
                             lo = logistic_root(t0, rr, r.alpha);
                         }
                     }
-                    sh.t0[ring][rho] = t0; sh.lo[ring][rho] = lo; sh.hi[ring][rho] = hi;
+                    sh.t0[buf][rho] = t0; sh.lo[buf][rho] = lo; sh.hi[buf][rho] = hi;
                 }
             }
             // 8. move the entry sets one stage on; the incoming set is masked to the row's length

@@ -326,7 +326,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
         HEAD_ITERATIONS {
             // tiles for iteration i + 1 (wavefront 9: own part of T(i+1), wavefront 10: cross part of T(i+2),
             // 16 KB each) were fetched into registers during the last iteration
-            const int ring = (i + 1) & (RING - 1);
+            const int buf = (i + 1) & 1;
             float4 *dst = reinterpret_cast<float4 *>(sw == 0 ? &sh.Tw[buf][0][0] : &sh.Tx[buf][0][0]);
 #pragma unroll
             for (int j = 0; j < 16; ++j) dst[lane + 64 * j] = staged ? stage[j] : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -414,12 +414,12 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
                 if (sub == 0) {
                     // everything that does not need the tails' share is done before it is waited for: what follows
                     // the wait is on the path between the workgroups
-                    const int ring = (i + 1) & (RING - 1);
+                    const int buf = (i + 1) & 1;
                     const bool live = r_g.len > 0;
                     float scale = 0.f, lo = 0.f, hi = 0.f;
                     if (live && LOSS == 0) { scale = sc.c / r_g.q; lo = -r_g.alpha; hi = 1.f - r_g.alpha; }
                     if (live && LOSS == 1) scale = sc.c / (sc.c + r_g.q);
-                    if (LOSS != 2) { sh.lo[ring][rho] = lo; sh.hi[ring][rho] = hi; }
+                    if (LOSS != 2) { sh.lo[buf][rho] = lo; sh.hi[buf][rho] = hi; }
                     if (TAILS) {
                         wait_flag(&sh.xflag, i + 2);
                         part += sh.xv[rho];                               // the tails' share of x_i . u
@@ -436,8 +436,8 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
                             lo = logistic_root(t0, rr, r_g.alpha);
                         }
                     }
-                    sh.t0[ring][rho] = t0;
-                    if (LOSS == 2) { sh.lo[ring][rho] = lo; sh.hi[ring][rho] = hi; }
+                    sh.t0[buf][rho] = t0;
+                    if (LOSS == 2) { sh.lo[buf][rho] = lo; sh.hi[buf][rho] = hi; }
                 }
             }
             // 4. move the entry sets one stage on; the set that arrived (block i + 2) is masked to the row's

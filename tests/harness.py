@@ -153,7 +153,7 @@ def run_lockstep(cfg, p, oracle_mod, binding_mod, rounds=None, solver="auto", sa
     return rec
 
 
-def tail_pairs(p, rows_of_solvers, orders, n_hot=8192):
+def tail_pairs(p, rows_of_solvers, orders, n_hot=8704):
     """For every block of 64 visited rows of every solver: pairs of its entries with entries of the blocks two and three before
     it in the same solver that share a column outside the `n_hot` most frequent ones (no fewer than the batched solver keeps on
     chip, so that it has at least these), and the most such entries a row has."""

@@ -81,8 +81,8 @@ def test_tiles_formed_for_the_other_batched_solver(oracle_mod, kinds):
     from workloads.generate import Problem
     assert torch.cuda.is_available()
     g = np.random.default_rng(17)
-    n, half, d = 2500, 20, 8192 + 9000
-    col = np.stack([np.sort(np.concatenate([g.choice(8192, half, replace=False), 8192 + g.choice(9000, half, replace=False)])) for _ in range(n)])
+    n, half, d = 2500, 20, 8704 + 9000
+    col = np.stack([np.sort(np.concatenate([g.choice(8704, half, replace=False), 8704 + g.choice(9000, half, replace=False)])) for _ in range(n)])
     p = Problem("announced", "hinge", n, d, 1.0 / n, np.where(g.random(n) < 0.5, 1.0, -1.0).astype(np.float32),
                 np.array([0, 1200, n], dtype=np.int64), row_ptr=2 * half * np.arange(n + 1, dtype=np.int64),
                 col=col.reshape(-1).astype(np.int32), val=(g.standard_normal(col.size) / np.sqrt(2 * half)).astype(np.float32))

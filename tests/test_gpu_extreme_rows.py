@@ -79,7 +79,7 @@ def test_huge_rows_that_share_a_column_blocks_apart(loss):
     assert torch.cuda.is_available()
     print("\ncase huge rows blocks apart %s" % loss, flush=True)
     g = np.random.default_rng(13)
-    n, popular, m = 1280, 8256, 36                       # every popular column 4 or 5 times
+    n, popular, m = 1280, 8768, 36                       # every popular column 4 or 5 times
     common = np.arange(n * 30).reshape(n, 30) % popular
     pairs = [(64 * a + i, 64 * b + j) for a, b in ((1, 3), (5, 8), (10, 12), (14, 17)) for i, j in ((3, 60), (40, 40))]
     own = np.empty((n, 6), dtype=np.int64)               # unpopular columns of two rows each

@@ -28,13 +28,13 @@ def _groups(g, n, size=8):
     return d, cols, orders
 
 
-def _shared(g, solver_rows, n_tail, holders, filler=0, n_popular=8064):
+def _shared(g, solver_rows, n_tail, holders, filler=0, n_popular=8640):
     """Rows of 44 entries: n_tail in unpopular columns, twelve of them in columns of `holders` rows each, the rest in columns of
     the row's own; popular columns otherwise.  `filler` rows of popular columns come first and make those the more frequent
     ones."""
     n = sum(solver_rows)
     m_pop = 44 - n_tail
-    pop = (np.arange((n + filler) * 44, dtype=np.int64) * 5 % n_popular).reshape(-1, 44)
+    pop = (np.arange((n + filler) * 44, dtype=np.int64) * 7 % n_popular).reshape(-1, 44)
     groups = max(1, -(-n // holders))
     shared = np.stack([n_popular + q * groups + g.permutation(n) % groups for q in range(12)], axis=1)
     own = n_popular + 12 * groups + np.arange(n * (n_tail - 12)).reshape(n, n_tail - 12)
