@@ -167,6 +167,7 @@ def tail_pairs(p, rows_of_solvers, orders, n_hot=8704):
             cols = [p.col[p.row_ptr[r]:p.row_ptr[r + 1]] for r in np.asarray(rows)[order[b:b + 64]]]
             longest = max(longest, max(int(tail[c].sum()) for c in cols))
             c = np.concatenate(cols)
-            blocks.append(np.bincount(c[tail[c]], minlength=p.d))
-        out.append([sum(int(blocks[b] @ blocks[a]) for a in (b - 2, b - 3) if a >= 0) for b in range(len(blocks))])
+            blocks.append(dict(zip(*np.unique(c[tail[c]], return_counts=True))))
+        out.append([sum(int(m) * int(blocks[a].get(c, 0)) for a in (b - 2, b - 3) if a >= 0 for c, m in blocks[b].items())
+                    for b in range(len(blocks))])
     return out, longest

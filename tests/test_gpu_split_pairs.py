@@ -1,6 +1,7 @@
 """Two tail workgroups per solver, whose gathers leave out the three latest blocks: what blocks b - 2 and b - 3 add comes through
-pairs of rows.  Solvers of one to a few blocks, blocks of hundreds of pairs, blocks of more than a list holds (foreseen from
-the columns' popularity or not), against the oracle."""
+pairs of rows.  Solvers of one to a few blocks behind a longer one that holds the same columns, tiles in runs, blocks of hundreds
+of pairs and of more than a list holds (foreseen from the columns' popularity or not), against the oracle.  Orders of all passes
+but the first are announced: their pairs are listed whatever the loss."""
 import numpy as np
 import pytest
 
@@ -11,6 +12,12 @@ pytestmark = pytest.mark.gpu
 
 def _uniform(g, n, d, m):
     return [np.sort(g.choice(d, m, replace=False)) for _ in range(n)], [g.permutation(n) for _ in range(2)]
+
+
+def _even(g, n, d, m):
+    """Every column in as many rows as any other."""
+    width = d // m
+    return list(np.stack([q * width + g.permutation(n) % width for q in range(m)], axis=1)), [g.permutation(n) for _ in range(2)]
 
 
 def _groups(g, n, size=8):
@@ -52,47 +59,90 @@ def _problem(g, name, loss, d, cols, bounds):
                    val=(g.standard_normal(col.size) / 7.0).astype(np.float32))
 
 
-CASES = [("few_%d" % n, n, "hinge") for n in (1, 64, 65, 128, 129, 192, 193, 256, 257, 321, 449)]
-CASES += [(name, n, loss) for name, n in (("sets", 4000), ("not_listed", 4000), ("too_many", 4133)) for loss in ("hinge", "squared", "logistic")]
-
-
-@pytest.mark.parametrize("name,n,loss", CASES)
-def test_pairs(oracle_mod, name, n, loss):
-    import torch
+def _run(oracle_mod, p, K, table, passes):
+    """The passes against the oracle, each announcing the next one's orders."""
     import paper_1909_04885_amd as binding
-    from workloads.generate import Problem
-    assert torch.cuda.is_available()
-    print("\ncase pairs %s n=%d %s" % (name, n, loss), flush=True)
-    g = np.random.default_rng(31)
-    if name == "too_many":
-        d, cols, orders = _groups(g, n)
-    else:
-        d = 60000 if n < 1000 else 16400     # (half of the columns unpopular: as many pairs as uniform columns can give)
-        cols, orders = _uniform(g, n, d, 40 if name == "sets" else 48)
-    rp = np.concatenate([[0], np.cumsum([c.size for c in cols])]).astype(np.int64)
-    col = np.concatenate(cols).astype(np.int32)
-    val = (g.standard_normal(col.size) / 7.0).astype(np.float32)
-    y = (np.where(g.random(n) < 0.5, -1.0, 1.0) if loss != "squared" else g.standard_normal(n)).astype(np.float32)
-    # (two solvers, one of which may have no rows, unless all rows are to be in one)
-    K = 1 if name == "too_many" else 2
-    p = Problem(name, loss, n, d, 1.0 / n, y, np.array([0, n], dtype=np.int64), row_ptr=rp, col=col, val=val)
-    table = np.zeros(1, dtype=np.int32)
     o, r = oracle_mod.OracleCoCoA.from_problem(p), binding.ChicleRound.from_problem(p, max_solvers=K)
     o.assign(K, table)
     r.assign(K, table)
     assert r.debug_solver()[:2] == ("batched", 3)
-    for order in orders:
-        perms = [order] + [np.empty(0, dtype=np.int64)] * (K - 1)
-        ref = o.local_epoch(perms)
-        r.local_epoch(r.upload_perm(perms))
-        e = rel_l2(r.get_delta_w(0), ref[0], dw_floor(float(np.linalg.norm(o.w))))
-        print("update %.2e" % e, flush=True)
-        assert e <= TOL_DW
+    for i, orders in enumerate(passes):
+        r.local_epoch_ahead(None if i else r.upload_perm(orders), r.upload_perm(passes[i + 1]) if i + 1 < len(passes) else None)
+        floor = dw_floor(float(np.linalg.norm(o.w)))
+        for k, ref in enumerate(o.local_epoch(orders)):
+            e = rel_l2(r.get_delta_w(k), ref, floor)
+            print("pass %d solver %d update %.2e" % (i, k, e), flush=True)
+            assert e <= TOL_DW
         o.aggregate()
         r.aggregate()
         got, want = r.gap(), o.gap()
         assert abs(got[2] - want[2]) <= gap_tolerance(want[2], want[0])
     r.close()
+
+
+@pytest.mark.parametrize("n_tail", [12, 30])             # the last 24 entries of a row cover its unpopular columns, and not
+@pytest.mark.parametrize("n", [1, 64, 65, 128, 129, 192, 193, 256, 257, 321, 449])
+def test_few_blocks(oracle_mod, n, n_tail):
+    """Two solvers of n rows behind one of 2048, whose last 192 visited rows are in the same unpopular columns: what must not be
+    paired across solvers would show."""
+    import torch
+    assert torch.cuda.is_available()
+    print("\ncase few blocks n=%d tails of %d" % (n, n_tail), flush=True)
+    g = np.random.default_rng(31)
+    filler, extra = 1856, 192
+    d, cols = _shared(g, [extra, n, n], n_tail, 3, filler)
+    p = _problem(g, "few", "hinge" if n % 2 else "squared", d, cols, [0, filler + extra, filler + extra + n, filler + extra + 2 * n])
+    rows = [np.arange(*p.chunk_rows(k)) for k in range(3)]
+    passes = [[np.concatenate([g.permutation(filler), filler + g.permutation(extra)]), g.permutation(n), g.permutation(n)] for _ in range(3)]
+    for orders in passes:
+        pairs, longest = tail_pairs(p, rows, orders)
+        assert (longest <= 24) == (n_tail <= 24) and max(max(x) for x in pairs) <= 512
+        assert (sum(pairs[1]) + sum(pairs[2]) > 0) == (n > 128)
+    _run(oracle_mod, p, 3, np.arange(3, dtype=np.int32), passes)
+
+
+@pytest.mark.parametrize("n_tail", [12, 30])
+def test_tiles_in_runs(oracle_mod, n_tail):
+    """Some 2200 tiles of five solvers: runs of five tiles to a workgroup, solvers that begin inside a run."""
+    import torch
+    assert torch.cuda.is_available()
+    print("\ncase tiles in runs, tails of %d" % n_tail, flush=True)
+    g = np.random.default_rng(37)
+    sizes = [40000, 29017, 30011, 25001, 16064]
+    d, cols = _shared(g, sizes, n_tail, 120)
+    p = _problem(g, "runs", "hinge", d, cols, np.concatenate([[0], np.cumsum(sizes)]))
+    passes = [[g.permutation(x) for x in sizes] for _ in range(2)]
+    pairs, longest = tail_pairs(p, [np.arange(*p.chunk_rows(k)) for k in range(5)], passes[1])
+    assert (longest <= 24) == (n_tail <= 24) and all(20 < x <= 512 for solver in pairs for x in solver[3:-1])
+    _run(oracle_mod, p, 5, np.arange(5, dtype=np.int32), passes)
+
+
+CASES = [(name, n, loss) for name, n in (("sets", 4000), ("not_listed", 4320), ("too_many", 4133)) for loss in ("hinge", "squared", "logistic")]
+
+
+@pytest.mark.parametrize("name,n,loss", CASES)
+def test_pairs(oracle_mod, name, n, loss):
+    import torch
+    assert torch.cuda.is_available()
+    print("\ncase pairs %s n=%d %s" % (name, n, loss), flush=True)
+    g = np.random.default_rng(31)
+    if name == "too_many":
+        d, cols, orders = _groups(g, n)
+    elif name == "not_listed":
+        d = 48 * 360                         # (half of the columns unpopular: as many pairs as uniform columns can give)
+        cols, orders = _even(g, n, d, 48)
+    else:
+        d = 16400
+        cols, orders = _uniform(g, n, d, 40)
+    p = _problem(g, name, loss, d, cols, [0, n])
+    most = max(max(tail_pairs(p, [np.arange(n)], [order])[0][0]) for order in orders)
+    share = np.sort(np.bincount(p.col, minlength=d))[:max(0, d - 8704)] / n
+    expected = 2 * 64 * 64 * float(share @ share)          # pairs of a block, were the rows in random order
+    assert {"sets": 100 < most <= 512 and expected < 0.85 * 512, "not_listed": expected > 0.85 * 512,
+            "too_many": most > 512 and expected < 0.85 * 512}[name]
+    # (two solvers, one of which has no rows, unless all rows are to be in one)
+    K = 1 if name == "too_many" else 2
+    _run(oracle_mod, p, K, np.zeros(1, dtype=np.int32), [[order] + [np.empty(0, dtype=np.int64)] * (K - 1) for order in orders])
 
 
 def test_pairs_in_a_context_made_for_long_rows(oracle_mod):
