@@ -88,8 +88,9 @@ enum chicle_solver_kind {
                                      that steps one at a time are faster: chicle_debug_solver tells).  For sparse
                                      rows, where the columns do
                                      not all fit the part of the private vector a compute unit keeps on chip and
-                                     the chip has compute units to spare, two workgroups share every solver: one
-                                     owns the popular columns and runs the steps, the other owns the rest */
+                                     the chip has compute units to spare, three workgroups share every solver: one
+                                     owns the popular columns and runs the steps, the other two own half of the
+                                     rest each */
     CHICLE_SOLVER_ROWWISE_ONE_CU = 3, /* row-wise with every solver on one compute unit */
     CHICLE_SOLVER_BATCHED_ONE_CU = 4  /* batched with every solver on one compute unit */
 };

@@ -60,15 +60,15 @@ struct Seg {
     bool recorded = false;
 };
 
-// Partial sums of the gap kernels: one (loss, conjugate) pair per workgroup of the row pass, |w|^2 partials.
+// Partial sums of the gap kernels: one (loss, conjugate) pair per workgroup of the row pass, |w|^2 and |w|_1 partials.
 struct GapScratch {
-    double *loss = nullptr, *conj = nullptr, *wsq = nullptr, *unused = nullptr;
+    double *loss = nullptr, *conj = nullptr, *wsq = nullptr, *wabs = nullptr;
     int parts = 0;            // length of loss[] and conj[]
     bool finish = false;      // the pass also forms the norms and the gap's sums
 };
 
 // Scratch of chicle_gap_noalloc: a fixed array in the code object, one copy per GPU, kept until the process
-// ends.  Layout: GAP_PARTS loss partials, GAP_PARTS conjugate partials, 2 * WSQ_PARTS for |w|^2.
+// ends.  Layout: GAP_PARTS loss partials, GAP_PARTS conjugate partials, WSQ_PARTS each for |w|^2 and |w|_1.
 constexpr int STATIC_SCRATCH_DOUBLES = 2 * GAP_PARTS + 2 * WSQ_PARTS;
 constexpr int MAX_DEVICES = 64;
 
@@ -152,7 +152,7 @@ struct chicle_ctx {
     int32_t *perm_stage = nullptr;
     GapScratch gap_scratch;           // in the arena
     double *static_scratch = nullptr; // this device's copy of the fixed scratch array (chicle_gap_noalloc)
-    double *gap_host = nullptr;       // 4 doubles of pinned host memory the gap's last kernel writes into ...
+    double *gap_host = nullptr;       // 5 doubles of pinned host memory the row pass's last workgroup writes into (GapEnd) ...
     double *gap_host_dev = nullptr;   // ... through this device address
     int *err_dev = nullptr;
     unsigned *tickets_dev = nullptr;  // see n_tickets
@@ -476,7 +476,7 @@ int split_tails(const chicle_ctx *c)
 {
     const int n_hot = batched_layout(c).n_hot, n_tails = n_hot < c->d ? SPLIT_TAILS : 0;
     const int k_pad = (c->K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
-    // (chunk lists that leave the head fewer popular columns than this: the solver on one compute unit)
+    // (chunk lists that leave the head fewer popular columns than the tails' state has room for: the solver on one compute unit)
     return c->split_allowed && (1 + n_tails) * k_pad <= c->cu_count &&
            (n_tails == 0 || n_hot >= TAILS_MIN_HOT) ? n_tails : -1;
 }
@@ -763,8 +763,7 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
         // a tail's lanes take the last 24 entries of a row where that covers every row's unpopular columns
         constexpr int TE_SHORT = 3 * LPR / TAIL_LPR, TE_ALL = GRAM_MAX_ROW / TAIL_LPR;
         auto kern = n_tails == 0 ? sdca_batched_heads<LOSS> : short_tails(c) ? sdca_batched_split<LOSS, TE_SHORT> : sdca_batched_split<LOSS, TE_ALL>;
-        if (n_tails > 0 && tail_lists_at(short_tails(c) ? TE_SHORT : TE_ALL) + (sizeof(ChunkDev) + sizeof(int)) * (size_t)ml > sh)
-            return fail(c, CHICLE_ESTATE, "the tails' state does not fit LDS");
+        static_assert(tail_lists_at(TE_ALL) <= sizeof(BatchedShared) + sizeof(double) * TAILS_MIN_HOT, "a tail fits the LDS of a head that has tails");
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
         clear_device_words(c, c->split_ring_dev, 2 * (int64_t)SPLIT_WORDS * c->K);
         seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
@@ -862,7 +861,7 @@ GapEnd gap_end(const chicle_ctx *c, const GapScratch &gs, int per_chunk, int thr
     if (!gs.finish) return E;
     E.tickets = c->tickets_dev;
     E.v = c->w64; E.d = (int64_t)c->d;
-    E.part_wsq = gs.wsq; E.part_wabs = gs.unused;
+    E.part_wsq = gs.wsq; E.part_wabs = gs.wabs;
     E.n_w = grid_for(c->d, threads * 8, WSQ_PARTS * 256 / threads);
     E.err = c->err_dev; E.out = c->gap_host_dev;
     *grid = dim3(rows + (unsigned)E.n_w);
@@ -921,7 +920,10 @@ void launch_gap_lpr(chicle_ctx *c, int grid, const GapScratch &gs)
 // The row pass of the gap: z_i = x_i . w into the chunks, loss and conjugate partial sums.
 int run_row_pass(chicle_ctx *c, const GapScratch &gs)
 {
-    // workgroups per chunk: enough to fill the chip several times over, within the partial-sum arrays
+    // Workgroups per chunk: enough to fill the chip several times over, within the partial-sum arrays.  (2048 in all; 8192, whose
+    // counts and partial sums the last workgroup waits for: 500000 x 28 21.6 us and 29.0, in 512 chunks 21.4 and 29.8,
+    // 200000 x 128 25.4 and 29.7, 20000 x 1000 22.4 and 23.0; 20000 sparse rows of 200 entries 32.3 and 30.0, 60000 x 1500 with
+    // the logistic loss 108 and 103.  Between events.)
     int max_rows = 1;
     for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
     const int rows_per_wg = 2 * (256 / c->gap_lpr);
@@ -1029,7 +1031,7 @@ int column_crowding(chicle_ctx *c, double *out)
 {
     if (c->crowding < 0.0) {
         int32_t *count = c->rank_of;       // (needed by no one after the columns are renumbered)
-        double *sums = c->gap_scratch.unused, s[2] = {0.0, 0.0};
+        double *sums = c->gap_scratch.wabs, s[2] = {0.0, 0.0};
         const int stride = (int)std::max<int64_t>(1, c->n_total / 4096);
         int64_t rows = 0;
         int most = 1;
@@ -1231,7 +1233,7 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
     c->gap_scratch.loss = (double *)carve(c, sizeof(double) * (size_t)c->gap_scratch.parts);
     c->gap_scratch.conj = (double *)carve(c, sizeof(double) * (size_t)c->gap_scratch.parts);
     c->gap_scratch.wsq = (double *)carve(c, sizeof(double) * WSQ_PARTS);
-    c->gap_scratch.unused = (double *)carve(c, sizeof(double) * WSQ_PARTS);
+    c->gap_scratch.wabs = (double *)carve(c, sizeof(double) * WSQ_PARTS);
     c->err_dev = (int *)carve(c, sizeof(int));
     c->tickets_dev = (unsigned *)carve(c, sizeof(unsigned) * n_tickets(d));
     c->ticks_dev = (long long *)carve(c, sizeof(long long) * 2 * (size_t)max_solvers);
@@ -1810,7 +1812,7 @@ int chicle_gap_noalloc(chicle_ctx *c, double *primal, double *dual, double *gap)
     gs.loss = c->static_scratch;
     gs.conj = gs.loss + GAP_PARTS;
     gs.wsq = gs.conj + GAP_PARTS;
-    gs.unused = gs.wsq + WSQ_PARTS;
+    gs.wabs = gs.wsq + WSQ_PARTS;
     gs.parts = GAP_PARTS;
     return gap_with(c, gs, primal, dual, gap);
 }

@@ -7,7 +7,7 @@
 // last two take about half of its requests and it waits for both inside every block.  Here the columns of
 // the private vector are divided:
 //   - the head workgroup keeps the popular columns [0, n_hot) in LDS, runs the recurrence, stages the tiles;
-//     its gathers and scatters touch LDS only;
+//     its gathers and scatters touch LDS only (where that is all columns, it is all there is: sdca_batched_heads);
 //   - two tail workgroups on the same L2 partition own the other columns, half of them each, in memory.
 // For every block each tail hands the head 64 partial dot products and the head hands the tails the 64 steps,
 // through rings of 64-bit words in memory.  A word carries its value together with the number of the block
@@ -495,7 +495,7 @@ struct TailShared {
     int rows_ready[TAIL_GROUPS], loaded[TAIL_GROUPS], bar[TAIL_GROUPS];
 };
 struct __align__(8) TailEntry { int col; float val; };          // val: with the row's label, as its step is added
-__host__ __device__ inline size_t tail_lists_at(int te)
+__host__ __device__ constexpr size_t tail_lists_at(int te)
 {
     return sizeof(TailShared) + sizeof(TailEntry) * (size_t)(LAG * te * BATCH * TAIL_LPR);
 }

@@ -17,7 +17,10 @@ namespace chicle {
 // workgroups on a compute unit.  Entries in random order are what it waits for: 31250 tiles in 354 us beside a pass, on 160
 // compute units (0.64 GB of entries looked through, 1.8 TB/s), 480 tiles in 10 us (23 in runs of twelve, which leave most of
 // the chip idle).
-constexpr int PAIR_CAP = 512;                       // 40 entries uniformly over any number of columns give at most 400
+constexpr int PAIR_CAP = 512;                       // rows of 40 entries in uniform columns, 8704 of them in the head: 376 on average
+                                                    // at most, whatever the number of columns (2 * 64 * 64 (d - 8704) (40 / d)^2).  Longer
+                                                    // chunk lists leave the head fewer, 6144 at least: up to 533, and no list where
+                                                    // that is foreseen or one overflows
 constexpr int PAIR_RUN = 12;                        // at most
 constexpr int PAIR_THREADS = 512;
 constexpr int PAIR_ROWS = (PAIR_RUN + 3) * BATCH;
