@@ -208,11 +208,12 @@ __device__ __forceinline__ int split_lag(const SplitArgs &A, const SolverDev &S,
 }
 
 // ---- the head workgroup: recurrence, tiles, the popular columns in LDS -------------------------------------
-// Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 stage the tiles.  Where there are tails, 11
-// fetches their partial sums, 12 resolves rows and 13 adds up what comes through pairs (12 shares a SIMD with the chain, which
-// polls would keep from issuing: six solvers of 5000 rows 1 % of the job).  One loop per role, all with the same number of
-// iterations and one workgroup barrier per iteration, so that the registers of one role are not kept alive through the code of
-// the others.
+// Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 stage the tiles.  Where there are tails, three more
+// fetch their partial sums, resolve rows and add up what comes through pairs.  12 is the one that shares a SIMD with the chain,
+// whose issue slots polls would take; which of the three is which was measured (polls, rows, pairs): six solvers of 5000 rows,
+// hinge loss, 129 us a pass as 11, 13, 12, 130 as 11, 12, 13, 132 as 13, 11, 12 and 135 as 12, 11, 13; 32 of 9400 rows, logistic
+// loss, 1104, 1103, 1093 and 1088.  One loop per role, all with the same number of iterations and one workgroup barrier per
+// iteration, so that the registers of one role are not kept alive through the code of the others.
 // TAILS: there are tails.  Else all columns are in the head and nothing is waited for but its own LDS: 9 resolves rows beside
 // its tile, since more wavefronts would take issue slots from the chain, and a row's entries go to its lanes in turn, so that
 // short rows take as many adds and reads as they have entries to a lane (sixteen bytes at a time, a lane's entries lie
@@ -230,6 +231,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
     const int tid = threadIdx.x, n_hot = A.n_hot;
     stamp_solver(sc, sid, 0);
     constexpr int THREADS = TAILS ? SPLIT_THREADS : BATCHED_THREADS;
+    constexpr int POLLER = LOSS == 2 ? 13 : 11, RESOLVER = LOSS == 2 ? 11 : 13, PAIRS = 12;
     split_stage_lists<THREADS>(smem, A, S, l_desc, l_prefix);
     double *hot = reinterpret_cast<double *>(smem + A.hot_off);
     for (int i = tid; i < n_hot; i += THREADS) hot[i] = 0.0;
@@ -259,7 +261,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             }
             __syncthreads();
         }
-    } else if (TAILS && wave == 11) {
+    } else if (TAILS && wave == POLLER) {
         // What the tails send for this iteration, fetched by a wavefront that has no other loads in flight
         // (loads return in the order they were issued) and handed on through LDS.
         HEAD_ITERATIONS {
@@ -274,7 +276,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             }
             __syncthreads();
         }
-    } else if (TAILS && wave == 13) {
+    } else if (TAILS && wave == PAIRS) {
         // What blocks i - 1 and i - 2, whose steps are at hand, add to block i + 1's dot products through pairs.  The pairs were
         // asked for an iteration ago, their number two.  (In the polling wavefront this kept the polls waiting: 5.0e3
         // cycles an iteration, 4.7e3 now; 32 solvers of 62500 rows 2.15 and 2.02 ms.)
@@ -310,7 +312,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             if (pairs && i + 3 >= 0 && i + 3 < nb) far = gld(counts + min(i + 3 + lane, nb - 1));
             __syncthreads();
         }
-    } else if (TAILS && wave == 12) {
+    } else if (TAILS && wave == RESOLVER) {
         // (one block further ahead than the tails' resolvers: the helpers ask for a block's entries three
         // iterations before they gather it)
         RowResolver resolver;
@@ -423,6 +425,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
                     if (TAILS) {
                         wait_flag(&sh.xflag, i + 2);
                         part += sh.xv[rho];                               // the tails' share of x_i . u
+                        asm volatile("" : "+v"(part));       // (read at once, not behind the condition below)
                     }
                     float t0 = 0.f;
                     if (live) {
