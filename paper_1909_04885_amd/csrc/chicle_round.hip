@@ -767,7 +767,7 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
         clear_device_words(c, c->split_ring_dev, 2 * (int64_t)SPLIT_WORDS * c->K);
         seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
-        hipLaunchKernelGGL(kern, dim3((1 + n_tails) * k_pad), dim3(n_tails == 0 ? BATCHED_THREADS : SPLIT_THREADS), sh, c->stream, A, k_pad);
+        hipLaunchKernelGGL(kern, dim3((1 + n_tails) * k_pad), dim3(n_tails == 0 ? HEAD_THREADS : SPLIT_THREADS), sh, c->stream, A, k_pad);
         seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
     } else {
         auto kern = sdca_batched_csr<LOSS>;
