@@ -209,8 +209,8 @@ __device__ __forceinline__ int split_lag(const SplitArgs &A, const SolverDev &S,
 }
 
 // ---- the head workgroup: recurrence, tiles, the popular columns in LDS -------------------------------------
-// Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 stage the tiles, one more resolves rows, and where there
-// are tails two more fetch their partial sums and add up what comes through pairs.  12 is the one that shares a SIMD with the
+// Wavefront 0 runs the chain, 1..8 gather and scatter (LDS only), 9..10 stage the tiles, one more (APART) or 9 resolves rows, and
+// where there are tails two more fetch their partial sums and add up what comes through pairs.  12 is the one that shares a SIMD with the
 // chain, whose issue slots polls would take; which of the three is which was measured (polls, rows, pairs): six solvers of 5000
 // rows, hinge loss, 129 us a pass as 11, 13, 12, 130 as 11, 12, 13, 132 as 13, 11, 12 and 135 as 12, 11, 13; 32 of 9400 rows,
 // logistic loss, 1104, 1103, 1093 and 1088.  One loop per role, all with the same number of iterations and one workgroup barrier
@@ -221,7 +221,8 @@ __device__ __forceinline__ int split_lag(const SplitArgs &A, const SolverDev &S,
 // all six of its adds are issued whatever the row's length).  Five solvers of 40000 rows of 12 entries in 466 columns, squared
 // loss: 1.44 us a block with the wavefronts and loads that tails need, 1.21 so; six of 30700 rows of 29 1.52 and 1.29; hinge
 // loss, 40 of 5000 rows of 12 1.53 and 1.33, two of 30000 rows of 40 in 5000 columns 1.29 and 1.23.
-template <int LOSS, bool TAILS>
+// APART: rows are resolved by a wavefront of their own (heads_resolve_apart).
+template <int LOSS, bool TAILS, bool APART>
 __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs &A, int sid)
 {
     BatchedShared &sh = *reinterpret_cast<BatchedShared *>(smem);
@@ -231,7 +232,8 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
     const RoundScalars &sc = A.sc;
     const int tid = threadIdx.x, n_hot = A.n_hot;
     stamp_solver(sc, sid, 0);
-    constexpr int THREADS = TAILS ? SPLIT_THREADS : HEAD_THREADS;
+    static_assert(APART || !TAILS, "with tails, rows are resolved apart");
+    constexpr int THREADS = TAILS ? SPLIT_THREADS : APART ? HEAD_THREADS : BATCHED_THREADS;
     constexpr int POLLER = LOSS == 2 ? 13 : 11, RESOLVER = LOSS == 2 || !TAILS ? 11 : 13, PAIRS = 12;
     split_stage_lists<THREADS>(smem, A, S, l_desc, l_prefix);
     double *hot = reinterpret_cast<double *>(smem + A.hot_off);
@@ -313,7 +315,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             if (pairs && i + 3 >= 0 && i + 3 < nb) far = gld(counts + min(i + 3 + lane, nb - 1));
             __syncthreads();
         }
-    } else if (wave == RESOLVER) {
+    } else if (APART && wave == RESOLVER) {
         // (one block further ahead than the tails' resolvers: the helpers ask for a block's entries three
         // iterations before they gather it)
         RowResolver resolver;
@@ -325,6 +327,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
         const int sw = wave - 9;
         float4 stage[16];                                // tile part fetched ahead
         bool staged = false;
+        RowResolver resolver;
         HEAD_ITERATIONS {
             // tiles for iteration i + 1 (wavefront 9: own part of T(i+1), wavefront 10: cross part of T(i+2),
             // 16 KB each) were fetched into registers during the last iteration
@@ -332,6 +335,7 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
             float4 *dst = reinterpret_cast<float4 *>(sw == 0 ? &sh.Tw[buf][0][0] : &sh.Tx[buf][0][0]);
 #pragma unroll
             for (int j = 0; j < 16; ++j) dst[lane + 64 * j] = staged ? stage[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!APART && sw == 0) resolver.step(sh.rows, RING - 1, l_desc, l_prefix, S, pk, i + 1, 0, 1, nb, lane, A.err, true);
             const int tb = sw == 0 ? i + 2 : i + 3;
             staged = tb >= 0 && tb < nb;
             if (staged) {
@@ -640,16 +644,16 @@ __global__ __launch_bounds__(SPLIT_THREADS) void sdca_batched_split(SplitArgs A,
     extern __shared__ __align__(16) unsigned char smem[];
     const int role = (int)blockIdx.x / k_pad, sid = (int)blockIdx.x % k_pad;
     if (sid >= A.sc.K) return;
-    if (role == 0) split_head<LOSS, true>(smem, A, sid);
+    if (role == 0) split_head<LOSS, true, true>(smem, A, sid);
     else split_tail<LOSS, TE>(smem, A, sid, role - 1);
 }
 
 // Solvers all of whose columns are in the head: workgroup k is solver k.
-template <int LOSS>
-__global__ __launch_bounds__(HEAD_THREADS) void sdca_batched_heads(SplitArgs A, int)
+template <int LOSS, bool APART>
+__global__ __launch_bounds__(APART ? HEAD_THREADS : BATCHED_THREADS) void sdca_batched_heads(SplitArgs A, int)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    if ((int)blockIdx.x < A.sc.K) split_head<LOSS, false>(smem, A, (int)blockIdx.x);
+    if ((int)blockIdx.x < A.sc.K) split_head<LOSS, false, APART>(smem, A, (int)blockIdx.x);
 }
 
 }  // namespace chicle

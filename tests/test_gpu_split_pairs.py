@@ -59,13 +59,13 @@ def _problem(g, name, loss, d, cols, bounds):
                    val=(g.standard_normal(col.size) / 7.0).astype(np.float32))
 
 
-def _run(oracle_mod, p, K, table, passes):
+def _run(oracle_mod, p, K, table, passes, workgroups=3):
     """The passes against the oracle, each announcing the next one's orders."""
     import paper_1909_04885_amd as binding
     o, r = oracle_mod.OracleCoCoA.from_problem(p), binding.ChicleRound.from_problem(p, max_solvers=K)
     o.assign(K, table)
     r.assign(K, table)
-    assert r.debug_solver()[:2] == ("batched", 3)
+    assert r.debug_solver()[:2] == ("batched", workgroups)
     for i, orders in enumerate(passes):
         r.local_epoch_ahead(None if i else r.upload_perm(orders), r.upload_perm(passes[i + 1]) if i + 1 < len(passes) else None)
         floor = dw_floor(float(np.linalg.norm(o.w)))
@@ -175,3 +175,22 @@ def test_pairs_in_a_context_made_for_long_rows(oracle_mod):
         o.aggregate()
         r.aggregate()
     r.close()
+
+
+@pytest.mark.parametrize("loss", ["hinge", "squared", "logistic"])
+@pytest.mark.parametrize("n", [65, 3000, 320000])
+def test_all_columns_in_the_head(oracle_mod, n, loss):
+    """No tails: rows resolved by a wavefront of their own, and beside a tile where tiles and entries are too many for the
+    caches (320000 rows, not with the logistic loss).  Rows of 1 to 48 entries, some without any."""
+    import torch
+    assert torch.cuda.is_available()
+    print("\ncase all columns in the head n=%d %s" % (n, loss), flush=True)
+    g = np.random.default_rng(43)
+    m, d, K = 48, 48 * 40, 3 if n < 1000 else 20
+    keep = np.arange(m) < g.integers(0, m + 1, n)[:, None]
+    col = np.arange(m) * 40 + g.integers(0, 40, (n, m))
+    length = keep.sum(axis=1)
+    p = _problem(g, "heads", loss, d, np.split(col[keep], np.cumsum(length)[:-1]), np.linspace(0, n, K + 1).astype(np.int64))
+    assert (32768 * (n / 64) + 8 * length.sum() > 224e6) == (n > 300000)
+    sizes = [int(np.diff(p.chunk_rows(k))[0]) for k in range(K)]
+    _run(oracle_mod, p, K, np.arange(K, dtype=np.int32), [[g.permutation(x) for x in sizes] for _ in range(2)], workgroups=1)
