@@ -624,21 +624,25 @@ bool heads_resolve_apart(const chicle_ctx *c)
 // solvers of 12500 rows of 40 entries in uniform columns 2.93 ms without and 2.56 with, 64 of 4688 rows of 44 2.99 and 3.40.  A
 // few blocks save less than the kernel's launch: rounds of one solver of 512 rows 74.7 us without and 78.4 with, of 768 73.8 and
 // 70.9; of 16 of 384 72.5 and 75.0, of 640 84.5 and 82.4, of 768 91.4 and 86.3.
-// Lists formed before the pass that uses them add their kernel to it, and small jobs save half a microsecond per block, from the
-// fifth or so on: passes of one solver of 512 rows 52 us without and 55 with, of 1024 69 and 68, of 2560 122 and 103; 16 of 640
-// rows 64 and 70, of 2560 152 and 159 (uniform columns: 166 and 189).  With the logistic loss, whose chain takes longer than the
-// tails, nothing: one of 2560 rows 263 and 267, 16 290 and 313; ahead it is 318 and 313, 358 and 355.
-// Nothing is saved where blocks have more pairs than a list holds, which the columns' shares of
-// the rows tell for rows in random order (16 solvers of 12500 rows of 48 entries in 16400 columns, 3.12 and 3.27).
+// Lists formed before the pass that uses them add their kernel to it: 4.5 us and 0.005 per tile, where the last 24 entries are not
+// enough 8 and 0.03, and up to 0.05 where blocks have hundreds of pairs; smaller jobs save 0.65 us per block, from the fifth or
+// so on.  Passes without and with: one solver of 1024 rows 69 us and 68, of 2560 122 and 103; 16 of 640 rows 64 and 70, of 2560
+// 152 and 159 (uniform columns: 166 and 189); 17 of 11000 rows of some 20 to 46 532 and 494, 71 of 2260 rows of 7 155 and 144.
+// With the logistic loss, whose chain takes longer than the tails, nothing is saved: one of 2560 rows 263 and 267, 16 290 and
+// 313; ahead it is 318 and 313, 358 and 355.
+// Nor is it where blocks have more pairs than a list holds, which the columns' shares of the rows tell for rows in random order
+// (16 solvers of 12500 rows of 48 entries in 16400 columns, 3.12 and 3.27).
 bool lists_pairs(const chicle_ctx *c, bool ahead)
 {
     if (split_tails(c) <= 0 || !c->pair_list[0]) return false;
     const int blocks = (c->most_rows + BATCH - 1) / BATCH;
     const bool narrow = short_tails(c);
     if (blocks < 12 || (!narrow && 32 * (int64_t)blocks <= c->n_tiles)) return false;
-    if (!ahead && (c->loss == CHICLE_LOSS_LOGISTIC || 0.5 * (blocks - 4) <= (narrow ? 6.5 + 0.0075 * c->n_tiles : 9.0 + 0.05 * c->n_tiles))) return false;
     const size_t at = (size_t)batched_layout(c).n_hot / 64;
-    return at >= c->shares.size() || (LAG - 2) * (double)(BATCH * BATCH) * c->shares[at] <= 0.85 * PAIR_CAP;
+    const double pairs = at < c->shares.size() ? (LAG - 2) * (double)(BATCH * BATCH) * c->shares[at] : 0.0;       // of a block
+    if (pairs > 0.85 * PAIR_CAP) return false;
+    const double us = narrow ? 4.5 + 0.005 * c->n_tiles : 8.0 + (0.03 + 6e-5 * pairs) * c->n_tiles;
+    return ahead || (c->loss != CHICLE_LOSS_LOGISTIC && 0.65 * (blocks - 4) > us);
 }
 
 template <int TE>
