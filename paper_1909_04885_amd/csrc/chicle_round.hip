@@ -430,7 +430,10 @@ BatchedLayout batched_layout(const chicle_ctx *c)
     BatchedLayout L;
     const int ml = std::max(c->max_list, 1);
     L.hot_off = (sizeof(BatchedShared) + (sizeof(ChunkDev) + sizeof(int)) * (size_t)ml + 15) & ~(size_t)15;
-    L.n_hot = (int)std::min<int64_t>((int64_t)((LDS_BYTES - L.hot_off) / sizeof(double)) & ~(int64_t)63, c->d);
+    // (A context made for long rows holds its private vectors in as many floats as entries, and these columns take their place in
+    // every solver's whether its rows hold them or not: 576 fewer there leave that much more for the columns the rows do hold.)
+    const size_t room = LDS_BYTES - L.hot_off - (c->long_rows ? sizeof(double) * 576 : 0);
+    L.n_hot = (int)std::min<int64_t>((int64_t)(room / sizeof(double)) & ~(int64_t)63, c->d);
     L.bytes = L.hot_off + sizeof(double) * (size_t)L.n_hot;
     return L;
 }

@@ -194,3 +194,28 @@ def test_all_columns_in_the_head(oracle_mod, n, loss):
     assert (32768 * (n / 64) + 8 * length.sum() > 224e6) == (n > 300000)
     sizes = [int(np.diff(p.chunk_rows(k))[0]) for k in range(K)]
     _run(oracle_mod, p, K, np.arange(K, dtype=np.int32), [[g.permutation(x) for x in sizes] for _ in range(2)], workgroups=1)
+
+
+def test_short_rows_fit_a_context_made_for_long_rows(oracle_mod):
+    """Such a context holds its private vectors in as many floats as it was announced entries: 8397 for each of twelve solvers, of
+    which the columns kept on chip take most."""
+    import torch
+    import paper_1909_04885_amd as binding
+    assert torch.cuda.is_available()
+    print("\ncase short rows in little room", flush=True)
+    g = np.random.default_rng(47)
+    n, d, m, K = 1008, 9000, 40, 12
+    cols = list(np.sort(np.argsort(g.random((n, 8000)), axis=1)[:, :m], axis=1))
+    p = _problem(g, "little_room", "hinge", d, cols, np.arange(K + 1) * (n // K))
+    o, r = oracle_mod.OracleCoCoA.from_problem(p), binding.ChicleRound(p.loss, n, d, p.lam, K, K, False, 100000)
+    for k in range(K):
+        a, b = p.chunk_rows(k)
+        r.load_chunk_csr(k, p.row_ptr[a:b + 1] - p.row_ptr[a], p.col[p.row_ptr[a]:p.row_ptr[b]], p.val[p.row_ptr[a]:p.row_ptr[b]], p.y[a:b])
+    table = np.arange(K, dtype=np.int32)
+    o.assign(K, table)
+    r.assign(K, table)
+    orders = [g.permutation(n // K) for _ in range(K)]
+    r.local_epoch(r.upload_perm(orders))
+    for k, ref in enumerate(o.local_epoch(orders)):
+        assert rel_l2(r.get_delta_w(k), ref, dw_floor(0.0)) <= TOL_DW
+    r.close()
