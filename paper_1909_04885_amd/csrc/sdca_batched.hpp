@@ -91,7 +91,7 @@ struct BatchedShared {
 // cross part sixteen steps at a time: read four steps at a time from an LDS that eight other wavefronts keep busy, they came
 // late (six solvers of 5000 rows of 40 entries: 2.88e3 cycles a block, 2.73e3 now).
 template <int LOSS>
-__device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
+__device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, float &x_carry, bool &rough, float inv_c, float *steps)
 {
     const int buf = i & 1;
     float4_v T[BATCH / 4];
@@ -125,7 +125,7 @@ __device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, 
 }
 // The same with the coefficients read four steps at a time, for the kernel whose wavefronts have no registers to spare.
 template <int LOSS>
-__device__ __forceinline__ void chain_block_small(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
+__device__ __forceinline__ void chain_block_small(BatchedShared &sh, int i, int lane, float &x_carry, bool &rough, float inv_c, float *steps)
 {
     const int buf = i & 1;
     float t = sh.t0[buf][lane] + x_carry;
@@ -149,26 +149,32 @@ __device__ __forceinline__ void chain_block_small(BatchedShared &sh, int i, int 
 // The same for the logistic loss, whose step has no closed form: lane i owns m_i = -y_i z_i and
 //     m_i += delta_j T_ij,   T_ij = -y_i y_j G_ij / c
 // (logistic_block; the helpers leave m at the start of the block in slot t0 and the root for it in slot lo).
-template <>
-__device__ __forceinline__ void chain_block<2>(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
+template <typename F>
+__device__ __forceinline__ void chain_block_logistic(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps, F block)
 {
     const int buf = i & 1;
     const RowSlot &row = sh.rows[i & (RING - 1)][lane];
     const float a = row.alpha, r = row.len > 0 ? row.q * inv_c : 0.f;      // r = 0 marks a row to skip
     float x = 0.f;
-    steps[lane] = logistic_block<BATCH>(
-        sh.t0[buf][lane] + x_carry, a, r, sh.lo[buf][lane], lane, [&](int jq) { return sh.Tw[buf][jq][lane]; },
-        [&](int jq, float d0, float d1, float d2, float d3) {
-            const float4_v X = sh.Tx[buf][jq][lane];
-            x = fmaf(d0, X[0], fmaf(d1, X[1], fmaf(d2, X[2], fmaf(d3, X[3], x))));
-        });
+    steps[lane] = block(sh.t0[buf][lane] + x_carry, a, r, sh.lo[buf][lane], [&](int jq) { return sh.Tw[buf][jq][lane]; },
+                        [&](int jq) { return sh.Tx[buf][jq][lane]; }, x);
     x_carry = x;
 }
 
 template <>
-__device__ __forceinline__ void chain_block_small<2>(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps)
+__device__ __forceinline__ void chain_block<2>(BatchedShared &sh, int i, int lane, float &x_carry, bool &rough, float inv_c, float *steps)
 {
-    chain_block<2>(sh, i, lane, x_carry, inv_c, steps);
+    chain_block_logistic(sh, i, lane, x_carry, inv_c, steps, [&](float m, float a, float r, float root, auto coef4, auto cross4, float &x) __attribute__((always_inline)) {
+        return logistic_block<BATCH, true>(m, a, r, root, lane, coef4, cross4, x, rough);
+    });
+}
+
+template <>
+__device__ __forceinline__ void chain_block_small<2>(BatchedShared &sh, int i, int lane, float &x_carry, bool &rough, float inv_c, float *steps)
+{
+    chain_block_logistic(sh, i, lane, x_carry, inv_c, steps, [&](float m, float a, float r, float root, auto coef4, auto cross4, float &x) __attribute__((always_inline)) {
+        return logistic_steps<BATCH, LOGISTIC_ROUGH, true>(m, a, r, root, lane, coef4, cross4, x, rough);
+    });
 }
 
 // One workgroup per solver: wavefront 0 runs the chain, eight wavefronts gather and scatter, two
@@ -271,6 +277,7 @@ __global__ __launch_bounds__(BATCHED_THREADS) void sdca_batched_csr(
     }
     int in_len = 0;
     float x_carry = 0.f;
+    bool rough = true;
     int hb_target = 0;
     float4 stage[16];                                // service wavefronts: tile part fetched ahead
     bool staged = false;
@@ -283,7 +290,7 @@ __global__ __launch_bounds__(BATCHED_THREADS) void sdca_batched_csr(
         if (tid == BATCHED_THREADS - 1 && i > 0)
             __hip_atomic_store(progress + sid, i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (is_chain) {
-            if (i >= 0 && i < nb) chain_block_small<LOSS>(sh, i, lane, x_carry, sc.inv_c, sh.delta[i & 1]);
+            if (i >= 0 && i < nb) chain_block_small<LOSS>(sh, i, lane, x_carry, rough, sc.inv_c, sh.delta[i & 1]);
         } else if (is_service) {
             // tiles for iteration i + 1 (wavefront 9: own part of T(i+1), wavefront 10: cross part of
             // T(i+2), 16 KB each) were fetched into registers during the last iteration

@@ -256,9 +256,10 @@ __device__ __forceinline__ void split_head(unsigned char *smem, const SplitArgs 
 #define HEAD_ITERATIONS for (int i = -6; i <= nb; ++i)
     if (wave == 0) {
         float x_carry = 0.f;
+        bool rough = true;
         HEAD_ITERATIONS {
             if (i >= 0 && i < nb) {
-                chain_block<LOSS>(sh, i, lane, x_carry, sc.inv_c, sh.steps[i & 3]);
+                chain_block<LOSS>(sh, i, lane, x_carry, rough, sc.inv_c, sh.steps[i & 3]);
                 // the tails add these steps into their columns
                 if (TAILS) ring_put(x_steps + (i & (SPLIT_RING - 1)) * BATCH + lane, sh.steps[i & 3][lane], i + 1);
             }

@@ -264,11 +264,14 @@ struct DenseShape {
 // The recurrence: lane i owns row i of the block; returns the row's step.  T: lane's coefficients, [j].
 // SOLVED: T holds the inverse of the squared loss's recurrence (gram_dense) without its unit diagonal.
 template <int LOSS, int BR, bool SOLVED>
-__device__ __forceinline__ float dense_recurrence(const float *T_lds, float t, float lo, float hi, float a, float root, int lane)
+__device__ __forceinline__ float dense_recurrence(const float *T_lds, float t, float lo, float hi, float a, float root, int lane, bool &rough)
 {
     const int i = lane & (BR - 1);
     const float4_v *Tq = reinterpret_cast<const float4_v *>(T_lds) + i;
-    if (LOSS == 2) return logistic_block<BR>(t, a, hi, root, lane, [&](int jq) { return Tq[jq * BR]; }, [](int, float, float, float, float) {});
+    if (LOSS == 2) {
+        float none = 0.f;
+        return logistic_block<BR, false>(t, a, hi, root, lane, [&](int jq) { return Tq[jq * BR]; }, [](int) { return float4_v{0.f, 0.f, 0.f, 0.f}; }, none, rough);
+    }
     float4_v T4[BR / 4];
 #pragma unroll
     for (int jq = 0; jq < BR / 4; ++jq) T4[jq] = Tq[jq * BR];
@@ -347,6 +350,7 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
     // wavefront 0 keeps the rows of blocks b + 1 and b + 2 in registers and requests those of b + 3 in block b
     DenseRow row1 = {nullptr, nullptr}, row2 = row1, row3 = row1;
     RowState *st_cur = nullptr;
+    bool rough = true;               // see logistic_block
     float4_v cur = {0.f, 0.f, 0.f, 0.f}, nxt = {0.f, 0.f, 0.f, 0.f};
     const RowState *any = chunks[0].st;
     auto state_of = [&](const DenseRow &r) __attribute__((always_inline)) -> const RowState * { return r.st != nullptr ? r.st : any; };
@@ -460,7 +464,7 @@ __global__ __launch_bounds__(SH::THREADS) void sdca_dense(
                     root = logistic_root(t, hi, a);
                 }
             }
-            const float dl = dense_recurrence<LOSS, BR, SOLVED>(T, t, lo, hi, a, root, lane);
+            const float dl = dense_recurrence<LOSS, BR, SOLVED>(T, t, lo, hi, a, root, lane, rough);
             if (lane < BR) {
                 if (st_cur != nullptr) {
                     float an = a + dl;

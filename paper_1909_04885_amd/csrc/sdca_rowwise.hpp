@@ -117,22 +117,37 @@ struct LogisticTrack {
 // unit in the last place of a' is 3e-8).
 constexpr float LOGISTIC_SERIES = 0.07f;
 
+// Rows further than this from where their series were expanded have them renewed before their group's steps.
+constexpr float LOGISTIC_NEAR = 0.05f;
+constexpr int LOGISTIC_CALM = 16, LOGISTIC_ROUGH = 4;     // steps taken before their rows' |d| are looked at
+
 // The BR steps of a block with the logistic loss: lane i owns row i; m = -y z against the private vector at the start
 // of the block, root: the root for it, r = q / c (0: a row that takes no step); coef4(jq) returns the lane's T of steps
-// 4 jq .. 4 jq + 3, and also4(jq, d0 .. d3) sees their results.  Four steps at a time: the expansions are renewed at the
-// current m, the four steps taken from the series, and then the four rows' |d| are looked at; where one was too large the
-// four are taken again, with the expansions renewed before each, or the row's bracket searched.
-template <int BR, typename COEF, typename ALSO>
-__device__ __forceinline__ float logistic_block(float m, float a, float r, float root, int lane, COEF coef4, ALSO also4)
+// 4 jq .. 4 jq + 3 (zero from the lane's own step on); CROSS: cross4(jq) returns their influence on the block after this one,
+// and x takes up what the steps add there.  GROUP steps at a
+// time: they are taken from the series, and then the rows' |d| are looked at; from the first one that was too large on, the
+// group's steps are taken again one by one, with the expansions renewed where that is needed, or the row's bracket searched.
+// Returns whether that happened in `rough`.
+// Bound by the chain of a step (series, lane read, multiply-add: some 45 cycles) and by what a group costs around its steps (two
+// comparisons with the scalar unit's answer, branches: 200 cycles).  Expansions renewed before every four steps, some 300 cycles
+// whether rows had moved or not: 300000 rows of 40 entries, 32 solvers, five rounds 6.47 ms on a run that continues and 10.8 from
+// alpha = 0; in groups of 16 3.68 and 12.5, of 8 4.02 and 10.9, of 4 4.65 and 9.4, and with 16 where nothing moves and 4 where it
+// does 3.80 and 9.4.  Three rounds of 20011 x 1001, eight solvers: 1.44 ms before, 1.08 so.  The updates' errors against 64 bits
+// are the same (160 jobs of dense and ragged rows: 1.00, alpha 1.01).
+template <int BR, int GROUP, bool CROSS, typename COEF, typename ALSO>
+__device__ __forceinline__ float logistic_steps(float m, float a, float r, float root, int lane, COEF coef4, ALSO cross4, float &x_sum, bool &rough)
 {
+    static_assert(BR % GROUP == 0 && GROUP % 4 == 0, "whole groups of coefficients");
 #define CHICLE_LANE(x, j) __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j))
     const bool live = r > 0.f;
     LogisticTrack k;
     // the row's m is the m at the start of the block and `moved`, the sum of the steps' influence, apart: added to m one by
     // one, each of them would round it
     float mine = 0.f, moved = 0.f, h = 0.f;          // d = moved g + h
+    int from = 0;                                    // rows before this one have their steps in `mine`
     k.s = root;
     float d = 0.f;
+    rough = false;
     auto renew = [&]() __attribute__((always_inline)) {
         const float dc = fminf(fmaxf(d, -0.5f), 0.5f);
         const float ds = fabsf(d) <= LOGISTIC_SERIES ? d * fmaf(d, fmaf(d, fmaf(d, k.c4, k.c3), k.c2), 1.0f) : dc;
@@ -144,28 +159,68 @@ __device__ __forceinline__ float logistic_block(float m, float a, float r, float
         const float d2 = d * d;
         return fmaf(d, fmaf(d2, fmaf(d, k.q4, k.q3), fmaf(d, k.q2, k.q1)), k.q0);
     };
+    // (a row's m does not move any more after its own step, so that its step can be read from its series later on)
+    auto keep = [&](int end) __attribute__((always_inline)) {
+        const float x = step();
+        mine = lane >= from && lane < end ? x : mine;
+        from = end;
+    };
+    // the group's rows that are further than `most` from their expansions (or no number)
+    auto beyond = [&](float most, int j0) __attribute__((always_inline)) {
+        return (unsigned)(__ballot(!(fabsf(d) <= most)) >> j0) & ((1u << GROUP) - 1u);
+    };
     k.at(root, a, r, live);
     d = h = fmaf(m, k.g, k.h);
-#pragma unroll 1
-    for (int jq = 0; jq < BR / 4; ++jq) {
-        const float4_v T4 = coef4(jq);
-        if (jq > 0) renew();
-        const float moved_before = moved;
-        float dj[4];
-        bool bad = false;
+    float4_v next[GROUP / 4], next_x[GROUP / 4];
+    auto request = [&](int jq) __attribute__((always_inline)) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            bad = bad || (lane == 4 * jq + e && fabsf(d) > LOGISTIC_SERIES);
-            dj[e] = CHICLE_LANE(step(), 4 * jq + e);
-            moved = fmaf(dj[e], T4[e], moved);
+        for (int q = 0; q < GROUP / 4; ++q) next[q] = coef4(jq + q);
+        if (CROSS)
+#pragma unroll
+            for (int q = 0; q < GROUP / 4; ++q) next_x[q] = cross4(jq + q);
+    };
+    request(0);
+#pragma unroll 1
+    for (int j0 = 0; j0 < BR; j0 += GROUP) {
+        float4_v T[GROUP / 4], X[GROUP / 4];
+#pragma unroll
+        for (int q = 0; q < GROUP / 4; ++q) { T[q] = next[q]; if (CROSS) X[q] = next_x[q]; }
+        request(min(j0 + GROUP, BR - GROUP) / 4);
+        if (beyond(LOGISTIC_NEAR, j0)) {
+            keep(j0);
+            renew();
+        }
+        const float moved_before = moved, x_before = x_sum;
+        float dj[GROUP];
+#pragma unroll
+        for (int e = 0; e < GROUP; ++e) {
+            const float own = step();
+            if (CROSS && e > 0) {                    // (in one of the slots that the lane read waits for)
+                __builtin_amdgcn_sched_barrier(0);
+                x_sum = fmaf(dj[e - 1], X[(e - 1) >> 2][(e - 1) & 3], x_sum);
+                asm volatile("" : "+v"(x_sum));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            dj[e] = CHICLE_LANE(own, j0 + e);
+            moved = fmaf(dj[e], T[e >> 2][e & 3], moved);
             d = fmaf(moved, k.g, h);
         }
-        if (__ballot(bad)) {
+        if (CROSS) x_sum = fmaf(dj[GROUP - 1], X[GROUP / 4 - 1][3], x_sum);
+        const unsigned out = beyond(LOGISTIC_SERIES, j0);
+        if (out) {                                   // the first such row's step and those after it again, one by one
+            const int first = __builtin_ctz(out);
+            rough = true;
             moved = moved_before;
+#pragma unroll
+            for (int e = 0; e < GROUP - 1; ++e)
+                if (e < first) moved = fmaf(dj[e], T[e >> 2][e & 3], moved);
             d = fmaf(moved, k.g, h);
+            keep(j0 + first);
+            float4_v Tj = coef4((j0 + first) >> 2);
 #pragma unroll 1
-            for (int e = 0; e < 4; ++e) {
-                const int j = 4 * jq + e;
+            for (int j = j0 + first; j < j0 + GROUP; ++j) {
+                const float Te = (j & 2) ? ((j & 1) ? Tj[3] : Tj[2]) : ((j & 1) ? Tj[1] : Tj[0]);
+                Tj = coef4(min(j + 1, BR - 1) >> 2);
                 for (int it = 0; it < 3 && fabsf(CHICLE_LANE(d, j)) > LOGISTIC_SERIES; ++it) renew();
                 float x = CHICLE_LANE(step(), j);
                 if (fabsf(CHICLE_LANE(d, j)) > LOGISTIC_SERIES) {
@@ -173,18 +228,30 @@ __device__ __forceinline__ float logistic_block(float m, float a, float r, float
                     const float sj = CHICLE_LANE(k.s, j), xj = CHICLE_LANE(d, j) / CHICLE_LANE(k.g, j);
                     x = logistic_step_wave(CHICLE_LANE(m + moved, j), CHICLE_LANE(r, j), CHICLE_LANE(a, j), sj + fminf(xj, 0.f), fabsf(xj), lane);
                 }
-                const float Te = e == 0 ? T4[0] : e == 1 ? T4[1] : e == 2 ? T4[2] : T4[3];
                 moved = fmaf(x, Te, moved);
                 d = fmaf(moved, k.g, h);
-                if (e == 0) dj[0] = x; else if (e == 1) dj[1] = x; else if (e == 2) dj[2] = x; else dj[3] = x;
+                mine = lane == j ? x : mine;
+            }
+            from = j0 + GROUP;
+            if (CROSS) {
+                x_sum = x_before;
+#pragma unroll
+                for (int e = 0; e < GROUP; ++e) x_sum = fmaf(e >= first ? CHICLE_LANE(mine, j0 + e) : dj[e], X[e >> 2][e & 3], x_sum);
             }
         }
-        also4(jq, dj[0], dj[1], dj[2], dj[3]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mine = lane == 4 * jq + e ? dj[e] : mine;
     }
+    keep(BR);
 #undef CHICLE_LANE
     return mine;
+}
+
+// rough: whether the solver's block before had rows that moved out of their series' range (first block: true), and then
+// whether this one has.
+template <int BR, bool CROSS, typename COEF, typename ALSO>
+__device__ __forceinline__ float logistic_block(float m, float a, float r, float root, int lane, COEF coef4, ALSO cross4, float &x_sum, bool &rough)
+{
+    if (rough) return logistic_steps<BR, LOGISTIC_ROUGH, CROSS>(m, a, r, root, lane, coef4, cross4, x_sum, rough);
+    return logistic_steps<BR, LOGISTIC_CALM, CROSS>(m, a, r, root, lane, coef4, cross4, x_sum, rough);
 }
 
 // rw: residual at w (see above; logistic: -y x_i.w); xu = x_i . u_k.  The arguments are the same in every

@@ -669,6 +669,7 @@ __global__ __launch_bounds__(SB_THREADS) void sdca_blocks(BlocksArgs A)
             unsigned long long *ring = A.rings + (int64_t)sid * SB_RING_WORDS;
             BlockRow cur_row = row_of(0), next_row = row_of(1);
             const RowState *any = A.chunks[0].st;
+            bool rough = true;                   // see logistic_block
             float4_v cur = gld_state(cur_row.st != nullptr ? cur_row.st : any);
             __syncthreads();                     // (the workers' first block is loaded)
             __syncthreads();
@@ -695,7 +696,7 @@ __global__ __launch_bounds__(SB_THREADS) void sdca_blocks(BlocksArgs A)
                         root = logistic_root(t, hi, a);
                     }
                 }
-                const float dl = dense_recurrence<LOSS, BATCH, false>(reinterpret_cast<const float *>(&sh.T[0][0]), t, lo, hi, a, root, lane);
+                const float dl = dense_recurrence<LOSS, BATCH, false>(reinterpret_cast<const float *>(&sh.T[0][0]), t, lo, hi, a, root, lane, rough);
                 const float coef = dl * (LOSS == 1 ? 1.f : y) * A.sc.inv_c;
                 sh.coef[lane] = coef;
                 if (g == 0 && cur_row.st != nullptr) {
