@@ -505,104 +505,38 @@ __global__ __launch_bounds__(256) void gap_rows_csr(const ChunkDev *__restrict__
     gap_block_end<256>(s_loss, s_conj, part_loss + blockIdx.x, part_conj + blockIdx.x, part_loss, part_conj, E);
 }
 
-// ---- the row pass for long rows over a shared vector far larger than a cache ------------------------------
-// A row of a thousand entries spread over twenty million columns makes a thousand lonely 4-byte reads of the
-// shared vector, every one of which misses the L2 cache of its compute-unit group and moves a whole line
-// over the fabric.  Here the columns are cut into slices of 2 MB of the shared vector.  Rows are sorted by
-// column, so a row's entries inside a slice are one contiguous run; off[s * n_total + row] = first entry of the
-// row (relative to its start) with column >= s << shift, for s = 0 .. S, is built once per data set.
-// Workgroup 8 i + x takes slice 8 (i / n_items) + x: the eight cache partitions (workgroups are dealt round
-// robin over them) work on eight neighbouring slices of the same rows at the same time, each partition
-// keeps its own slice of the shared vector in its L2, and the lines of entries that two neighbouring slices
-// share are fetched from memory once.  Partial dot products are added into z[row] with atomic adds; a second
-// kernel turns z into the rows' residuals and the loss and conjugate sums, and clears z for the next pass.
-constexpr int SLICE_BYTES_LOG2 = 21;
-constexpr int SLICE_SEG = 256;                      // rows per workgroup
-constexpr int SLICE_LANES = 16;                     // lanes per row
-constexpr int SLICE_ROWS_IN_FLIGHT = 8;             // rows a lane group works on at the same time
-
-// Grid: (workgroups over rows, chunks); one wavefront per row.
-__global__ __launch_bounds__(256) void slice_offsets(const ChunkDev *__restrict__ chunks, int shift, int S,
-                                                     int64_t n_total, int32_t *off)
-{
-    const ChunkDev &ch = chunks[blockIdx.y];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int r = blockIdx.x * 4 + wave; r < ch.n_rows; r += gridDim.x * 4) {
-        const int b = ch.row_ptr[r], e = ch.row_ptr[r + 1];
-        int32_t *o = off + ch.row_base + r;
-        // entry p opens every slice after its predecessor's up to its own; the row's end opens all that remain
-        for (int p = b + lane; p <= e; p += 64) {
-            const int sp = p < e ? ch.col[p] >> shift : S;
-            const int sq = p > b ? ch.col[p - 1] >> shift : -1;
-            for (int t = sq + 1; t <= sp; ++t) o[(int64_t)t * n_total] = p - b;
-        }
-    }
-}
-
-template <typename WT>
-__global__ __launch_bounds__(256) void gap_rows_sliced(const ChunkDev *__restrict__ chunks, const WT *__restrict__ w,
-                                                       double l1, const int32_t *__restrict__ off, int64_t n_total,
-                                                       int S, int segs_per_chunk, int n_items, WT *z)
-{
-    __shared__ int s_b[SLICE_SEG], s_e[SLICE_SEG];
-    const int x = (int)blockIdx.x % L2_PARTITIONS, i = (int)blockIdx.x / L2_PARTITIONS;
-    const int slice = L2_PARTITIONS * (i / n_items) + x, item = i % n_items;
-    if (slice >= S) return;
-    const ChunkDev &ch = chunks[item / segs_per_chunk];
-    const int r0 = (item % segs_per_chunk) * SLICE_SEG;
-    if (r0 >= ch.n_rows) return;
-    const int nr = min(SLICE_SEG, ch.n_rows - r0);
-    const int t = threadIdx.x;
-    if (t < nr) {
-        const int start = ch.row_ptr[r0 + t];
-        const int64_t row = (int64_t)ch.row_base + r0 + t;
-        s_b[t] = start + off[(int64_t)slice * n_total + row];
-        s_e[t] = start + off[(int64_t)(slice + 1) * n_total + row];
-    }
-    __syncthreads();
-    const int32_t *__restrict__ col = ch.col;
-    const float *__restrict__ val = ch.val;
-    const int sub = t % SLICE_LANES, grp = t / SLICE_LANES;
-    constexpr int GROUPS = 256 / SLICE_LANES, RF = SLICE_ROWS_IN_FLIGHT;
-    for (int rb = grp; rb < nr; rb += GROUPS * RF) {
-        int b[RF], e[RF], c[RF];
-        float v[RF];
-        WT acc[RF];
-#pragma unroll
-        for (int k = 0; k < RF; ++k) {
-            const int r = rb + k * GROUPS;
-            b[k] = r < nr ? s_b[r] : 0;
-            e[k] = r < nr ? s_e[r] : 0;
-            const bool has = b[k] + sub < e[k];
-            c[k] = has ? col[b[k] + sub] : 0;
-            v[k] = has ? val[b[k] + sub] : 0.f;
-        }
-#pragma unroll
-        for (int k = 0; k < RF; ++k) acc[k] = (WT)v[k] * shared_at(w, c[k], l1);
-#pragma unroll
-        for (int k = 0; k < RF; ++k)                 // runs longer than the lane group
-            for (int p = b[k] + SLICE_LANES + sub; p < e[k]; p += SLICE_LANES) acc[k] += (WT)val[p] * shared_at(w, col[p], l1);
-#pragma unroll
-        for (int k = 0; k < RF; ++k) {
-#pragma unroll
-            for (int o = SLICE_LANES / 2; o > 0; o >>= 1) acc[k] += __shfl_xor(acc[k], o, 64);
-            if (sub == 0 && e[k] > b[k]) atomicAdd(&z[(int64_t)ch.row_base + r0 + rb + k * GROUPS], acc[k]);
-        }
-    }
-}
-
-// Grid: see GapEnd; a thread per row.  Partial sums by workgroup, as above.
-template <int LOSS, typename WT>
-__global__ __launch_bounds__(256) void gap_rows_from_z(const ChunkDev *__restrict__ chunks, WT *z, double l1,
-                                                       double *part_loss, double *part_conj, GapEnd E)
+// The end of the row pass where the rows' dot products come in parts (column_dots).  Grid: see GapEnd; G threads per row, each with
+// every G-th part, a wavefront's rows side by side.  Partial sums by workgroup, as above.
+template <int LOSS, int G>
+__global__ __launch_bounds__(256) void gap_rows_from_z(const ChunkDev *__restrict__ chunks, const double *__restrict__ z, int parts, int64_t n_total,
+                                                       double l1, double *part_loss, double *part_conj, GapEnd E)
 {
     if (gap_chunk(E) >= E.n_chunks) return gap_w_block<256>(l1, part_loss, part_conj, E);
+    constexpr int ROWS = 256 / G;
+    __shared__ double s_z[G][ROWS + 1];
     const ChunkDev &ch = chunks[gap_chunk(E)];
+    const int t = threadIdx.x % ROWS, g = threadIdx.x / ROWS;
     double s_loss = 0.0, s_conj = 0.0;
-    for (int r = gap_slot(E) * 256 + threadIdx.x; r < ch.n_rows; r += E.per_chunk * 256) {
-        const WT zi = z[(int64_t)ch.row_base + r];
-        z[(int64_t)ch.row_base + r] = (WT)0;
-        gap_row_terms<LOSS, WT>(ch.st + r, zi, s_loss, s_conj);
+    for (int r0 = gap_slot(E) * ROWS; r0 < ch.n_rows; r0 += E.per_chunk * ROWS) {
+        const int r = r0 + t;
+        const double *mine = z + (int64_t)ch.row_base + min(r, ch.n_rows - 1);
+        double zi = 0.0;
+        for (int k = g; k < parts; k += 8 * G) {     // (eight loads in flight)
+            double x[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) x[q] = k + q * G < parts ? mine[(int64_t)(k + q * G) * n_total] : 0.0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) zi += x[q];
+        }
+        if (G > 1) {
+            s_z[g][t] = zi;
+            __syncthreads();
+            if (g == 0)
+#pragma unroll
+                for (int q = 1; q < G; ++q) zi += s_z[q][t];
+            __syncthreads();
+        }
+        if (g == 0 && r < ch.n_rows) gap_row_terms<LOSS, double>(ch.st + r, zi, s_loss, s_conj);
     }
     gap_block_end<256>(s_loss, s_conj, part_loss + blockIdx.x, part_conj + blockIdx.x, part_loss, part_conj, E);
 }

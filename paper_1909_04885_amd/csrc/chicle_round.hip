@@ -17,6 +17,7 @@
 
 #include "../../include/chicle_round.h"
 #include "aggregate_gap.hpp"
+#include "column_order.hpp"
 #include "device_types.hpp"
 #include "gram_join.hpp"
 #include "layout.hpp"
@@ -42,7 +43,6 @@ constexpr int DENSE_V_LDS_MAX_D = 8192;
 constexpr int BATCHED_MAX_LIST = MAX_LIST_LDS;  // chunk descriptors of one solver the batched solver stages in LDS (they take
                                                // the place of columns of the private vector's LDS-resident head)
 constexpr int RENUMBER_MAX_ROW = 64;   // rows are re-sorted by one thread each: short rows only
-constexpr int SLICES_MIN = 4;         // fewer slices of the shared vector than this: the plain gap row pass
 constexpr double LONG_ROW_AVG = 96.0;  // sparse rows longer than this on average: the row-wise solver uses whole workgroups per row
 
 enum State { ST_LOADING = 0, ST_READY = 1, ST_EPOCH_DONE = 2 };
@@ -169,9 +169,16 @@ struct chicle_ctx {
     unsigned long long *cluster_ring_dev = nullptr;
     int cluster = 1;                  // members per solver under the current assignment
     int split_built_for = 0;          // cluster size row_split_dev was built for
-    int32_t *slice_off_dev = nullptr; // long rows: (slices + 1) x n_total run boundaries of the sliced gap row pass
-    double *slice_z_dev = nullptr;    // n_total partial dot products (float or double), zero between passes
-    int gap_slices = 0, gap_slice_shift = 0;   // 0: the sliced row pass is not in use
+    // long rows: a copy of the entries by column (column_order.hpp), made at the first assignment
+    ColumnOrder columns{};            // blocks == 0: there is none
+    ColumnEntry *co_entries_dev = nullptr;
+    long long *co_off_dev = nullptr;
+    unsigned long long *co_count_dev = nullptr;
+    double *co_z_dev = nullptr;       // co_parts x n_total shares of the rows' dot products
+    float *co_coef_dev = nullptr;     // per row: its coefficient in the solvers' updates of the last pass
+    bool merge_by_columns = false;    // ... is what the merge reads after a pass of the block solver
+    bool coef_pending = false;        // such a pass has left its updates there: private vectors lack the unshared columns
+    bool private_stale = false;       // private vectors hold what has been merged from there
     bool cluster_allowed = true;
     // sparse rows longer than the batched solver takes: blocks over the columns that several rows of a solver hold
     bool blocks_ready = false;        // laid out for the current assignment
@@ -277,11 +284,25 @@ size_t long_row_layout_bytes(int64_t n_total, int64_t total_entries)
     return sizeof(int32_t) * (4 * (size_t)total_entries + 4 * (size_t)SB_SEG_WORDS * (size_t)n_total);
 }
 
-// Slices of the sliced gap row pass at most (the shared vector in double).
-int max_slices(int32_t d)
+// The copy of long rows' entries by column (column_order.hpp): blocks of rows, columns of a bucket, buckets, and parts that a
+// block's dot products are summed in.  Buckets are as wide as leaves the merge a thousand workgroups.
+int co_blocks(int64_t n_total) { return (int)((n_total + CO_ROWS - 1) / CO_ROWS); }
+int co_bucket_log2(int32_t d)
 {
-    const int shift = SLICE_BYTES_LOG2 - 3;
-    return (int)(((int64_t)d + (1 << shift) - 1) >> shift);
+    int b = CO_MAX_BUCKET_LOG2;
+    while (b > CO_MIN_BUCKET_LOG2 && (d >> b) < 1024) --b;
+    return b;
+}
+int co_buckets(int32_t d) { return (int)(((int64_t)d + (1 << co_bucket_log2(d)) - 1) >> co_bucket_log2(d)); }
+int co_parts(int64_t n_total)
+{
+    const int most = std::max(1, CO_PARTS / co_blocks(n_total));
+    return most < L2_PARTITIONS ? most : most / L2_PARTITIONS * L2_PARTITIONS;
+}
+size_t co_bytes(int64_t n_total, int64_t total_entries, int32_t d)
+{
+    return align_up(sizeof(ColumnEntry) * (size_t)total_entries) + 2 * align_up(sizeof(long long) * ((size_t)co_blocks(n_total) * (size_t)co_buckets(d) + 2)) +
+           align_up(sizeof(double) * (size_t)co_parts(n_total) * (size_t)n_total) + align_up(sizeof(float) * ((size_t)n_total + 4));
 }
 
 // Counters of workgroups that are done: the gap's, and one per workgroup's columns for the merge.  Zero between kernels.
@@ -322,7 +343,7 @@ size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_sol
     s += align_up(sizeof(int) * (size_t)max_solvers);
     s += align_up(sizeof(unsigned long long) * (size_t)SPLIT_WORDS * (size_t)max_solvers);   // rings of the split batched solver
     if (long_rows) {
-        s += align_up(sizeof(int32_t) * ((size_t)max_slices(d) + 1) * (size_t)n_total) + align_up(sizeof(double) * (size_t)n_total);
+        s += co_bytes(n_total, n_total_entries_hint, d);
         s += align_up(sizeof(int32_t) * (size_t)SPLITS_PER_ROW * (size_t)n_total);
         s += align_up(sizeof(unsigned long long) * (size_t)CLUSTER_WORDS * (size_t)max_solvers);
     }
@@ -572,6 +593,10 @@ int launch_rowwise(chicle_ctx *c, const int32_t *perm)
 {
     const RoundScalars sc = scalars(c);
     const size_t list_bytes = 2 * sizeof(int) * (size_t)std::max(c->max_list, 1);
+    if (c->private_stale) {                          // (its passes start from zero)
+        clear_device_words(c, c->u, c->u_used);
+        c->private_stale = false;
+    }
     if (c->dense) {
         const bool v_lds = c->d <= DENSE_V_LDS_MAX_D;
         const size_t sh = list_bytes + (v_lds ? sizeof(float) * (size_t)c->d : 0);
@@ -817,7 +842,24 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
     return CHICLE_OK;
 }
 
-// Blocks over the shared columns (sparse rows of any length); the other columns' updates follow in a kernel of their own.
+// The updates of the columns that one row of a solver holds, into its private vector.
+void spread_updates(chicle_ctx *c)
+{
+    if (c->sources_dev) {
+        int lds_rows = 1;
+        for (const SolverDev &sol : c->solvers) lds_rows = std::max(lds_rows, std::min(sol.n_rows, SPREAD_LDS_ROWS));
+        hipLaunchKernelGGL(spread_unique, dim3((c->most_columns + SPREAD_PER - 1) / SPREAD_PER, c->K), dim3(256), sizeof(float) * (size_t)lds_rows,
+                           c->stream, c->solvers_dev, c->count_dev, (const UniqueSource *)c->sources_dev, c->coef_dev, c->u, c->u_off_dev, lds_rows);
+    } else {
+        int max_rows = 1;
+        for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
+        hipLaunchKernelGGL(scatter_unique, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
+                           c->chunk_owner_dev, c->solvers_dev, c->chunk_first_dev, c->coef_dev, c->u, c->u_off_dev, c->private_stale);
+    }
+}
+
+// Blocks over the shared columns (sparse rows of any length); the other columns' updates follow in a kernel of their own, unless
+// the merge takes all updates from the steps' coefficients (column_merge): then only where a caller asks for a solver's update.
 template <int LOSS>
 int launch_blocks(chicle_ctx *c, const int32_t *perm)
 {
@@ -826,6 +868,7 @@ int launch_blocks(chicle_ctx *c, const int32_t *perm)
     float *tiles = (float *)c->layout_dev;
     seg_begin(c, CHICLE_SEG_EPOCH_GRAM);
     clear_device_words(c, c->coef_dev, c->n_total);
+    if (c->merge_by_columns) clear_device_words(c, c->co_coef_dev, c->n_total);
     if (c->blocks_g > 1) clear_device_words(c, c->blocks_ring_dev, 2 * (int64_t)SB_RING_WORDS * c->K);
     if (c->n_tiles > 0) {
         auto kern = gram_blocks<LOSS>;
@@ -838,24 +881,15 @@ int launch_blocks(chicle_ctx *c, const int32_t *perm)
     BlocksArgs A;
     A.solvers = c->solvers_dev; A.chunks = c->chunks_dev; A.tiles = tiles; A.u_all = c->u; A.u_off = c->u_off_dev;
     A.place_off = c->place_off_dev; A.place = c->place_dev; A.count = c->mcount_dev; A.refs = c->refs_dev; A.segs = c->segs_dev;
-    A.coef_out = c->coef_dev; A.n_total = c->n_total; A.G = c->blocks_g; A.k_pad = k_pad; A.sc = sc; A.err = c->err_dev;
+    A.coef_out = c->coef_dev; A.coef_by_row = c->merge_by_columns ? c->co_coef_dev : nullptr; A.n_total = c->n_total; A.G = c->blocks_g; A.k_pad = k_pad; A.sc = sc; A.err = c->err_dev;
     A.rings = c->blocks_ring_dev;
     auto kern = c->blocks_double ? sdca_blocks<LOSS, double> : sdca_blocks<LOSS, float>;
     const size_t sh = sizeof(BlocksShared) + (c->blocks_double ? sizeof(double) * (size_t)SB_CAP<double> : sizeof(float) * (size_t)SB_CAP<float>);
     HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
     seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
     hipLaunchKernelGGL(kern, dim3(c->blocks_g * k_pad), dim3(SB_THREADS), sh, c->stream, A);
-    if (c->sources_dev) {
-        int lds_rows = 1;
-        for (const SolverDev &sol : c->solvers) lds_rows = std::max(lds_rows, std::min(sol.n_rows, SPREAD_LDS_ROWS));
-        hipLaunchKernelGGL(spread_unique, dim3((c->most_columns + SPREAD_PER - 1) / SPREAD_PER, c->K), dim3(256), sizeof(float) * (size_t)lds_rows,
-                           c->stream, c->solvers_dev, c->count_dev, (const UniqueSource *)c->sources_dev, c->coef_dev, c->u, c->u_off_dev, lds_rows);
-    } else {
-        int max_rows = 1;
-        for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
-        hipLaunchKernelGGL(scatter_unique, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
-                           c->chunk_owner_dev, c->solvers_dev, c->chunk_first_dev, c->coef_dev, c->u, c->u_off_dev);
-    }
+    c->coef_pending = c->merge_by_columns;
+    if (!c->merge_by_columns) spread_updates(c);
     seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
     HIP_TRY(c, hipGetLastError());
     return CHICLE_OK;
@@ -958,25 +992,27 @@ int run_row_pass(chicle_ctx *c, const GapScratch &gs)
                                   gs.parts / c->n_chunks));
         c->gap_hot_grid = gx;
     }
-    if (c->gap_slices > 0) {
-        const int segs = (max_rows + SLICE_SEG - 1) / SLICE_SEG, n_items = segs * c->n_chunks;
-        const unsigned blocks = (unsigned)((c->gap_slices + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS) * (unsigned)n_items;
-        gx = std::max(1, std::min((max_rows + 255) / 256, gs.parts / c->n_chunks));
+    if (c->columns.blocks > 0) {
+        // (parts of some 4096 entries or more)
+        const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(co_parts(c->n_total), c->entries_loaded / (4096 * (int64_t)c->columns.blocks)));
+        const int per_row = parts <= 8 ? 1 : parts <= 64 ? 4 : 16;
+        gx = std::max(1, std::min((max_rows * per_row + 255) / 256, std::min(gs.parts, 2048) / c->n_chunks));
         dim3 fg;
         const GapEnd E = gap_end(c, gs, gx, 256, &fg);
+        const dim3 grid((unsigned)((parts + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS * c->columns.blocks));
+        const size_t sh = sizeof(double) * (size_t)std::min<int64_t>(CO_ROWS, c->n_total);
         if (c->loss == CHICLE_LOSS_HINGE) {
-            float *z = (float *)c->slice_z_dev;
-            hipLaunchKernelGGL(gap_rows_sliced<float>, dim3(blocks), dim3(256), 0, c->stream, c->chunks_dev, (const float *)c->w, c->l1,
-                               c->slice_off_dev, c->n_total, c->gap_slices, segs, n_items, z);
-            hipLaunchKernelGGL((gap_rows_from_z<0, float>), fg, dim3(256), 0, c->stream, c->chunks_dev, z, c->l1, gs.loss, gs.conj, E);
+            HIP_TRY(c, hipFuncSetAttribute((const void *)column_dots<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+            hipLaunchKernelGGL(column_dots<float>, grid, dim3(CO_THREADS), sh, c->stream, c->columns, parts, (const float *)c->w, c->l1, c->co_z_dev);
         } else {
-            hipLaunchKernelGGL(gap_rows_sliced<double>, dim3(blocks), dim3(256), 0, c->stream, c->chunks_dev, (const double *)c->w64, c->l1,
-                               c->slice_off_dev, c->n_total, c->gap_slices, segs, n_items, c->slice_z_dev);
-            if (c->loss == CHICLE_LOSS_SQUARED)
-                hipLaunchKernelGGL((gap_rows_from_z<1, double>), fg, dim3(256), 0, c->stream, c->chunks_dev, c->slice_z_dev, c->l1, gs.loss, gs.conj, E);
-            else
-                hipLaunchKernelGGL((gap_rows_from_z<2, double>), fg, dim3(256), 0, c->stream, c->chunks_dev, c->slice_z_dev, c->l1, gs.loss, gs.conj, E);
+            HIP_TRY(c, hipFuncSetAttribute((const void *)column_dots<double>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+            hipLaunchKernelGGL(column_dots<double>, grid, dim3(CO_THREADS), sh, c->stream, c->columns, parts, (const double *)c->w64, c->l1, c->co_z_dev);
         }
+        auto pick = [&](auto k1, auto k4, auto k16) { return per_row == 1 ? k1 : per_row == 4 ? k4 : k16; };
+        auto kern = c->loss == CHICLE_LOSS_HINGE ? pick(gap_rows_from_z<0, 1>, gap_rows_from_z<0, 4>, gap_rows_from_z<0, 16>)
+                    : c->loss == CHICLE_LOSS_SQUARED ? pick(gap_rows_from_z<1, 1>, gap_rows_from_z<1, 4>, gap_rows_from_z<1, 16>)
+                                                     : pick(gap_rows_from_z<2, 1>, gap_rows_from_z<2, 4>, gap_rows_from_z<2, 16>);
+        hipLaunchKernelGGL(kern, fg, dim3(256), 0, c->stream, c->chunks_dev, (const double *)c->co_z_dev, parts, c->n_total, c->l1, gs.loss, gs.conj, E);
     } else if (c->loss == CHICLE_LOSS_HINGE) launch_gap_lpr<0>(c, gx, gs);
     else if (c->loss == CHICLE_LOSS_SQUARED) launch_gap_lpr<1>(c, gx, gs);
     else launch_gap_lpr<2>(c, gx, gs);
@@ -1042,6 +1078,33 @@ int renumber_columns(chicle_ctx *c)
     HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->renumbered = true;
+    return CHICLE_OK;
+}
+
+// Makes that copy, once, when every chunk is in HBM and the columns have their numbers.
+int order_by_column(chicle_ctx *c)
+{
+    const int log2 = co_bucket_log2(c->d), buckets = co_buckets(c->d), blocks = co_blocks(c->n_total);
+    const int64_t n = (int64_t)buckets * blocks;
+    unsigned long long most = 0, *most_dev = c->co_count_dev + n + 1;
+    int max_rows = 1;
+    for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
+    const dim3 grid((max_rows + CO_GROUP_ROWS - 1) / CO_GROUP_ROWS, c->n_chunks);
+    const size_t words = buckets <= CO_LDS_BUCKETS ? (size_t)buckets : 0;
+    HIP_TRY(c, hipMemsetAsync(c->co_count_dev, 0, sizeof(unsigned long long) * (size_t)(n + 2), c->stream));
+    HIP_TRY(c, hipFuncSetAttribute((const void *)co_count, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(sizeof(int) * words)));
+    HIP_TRY(c, hipFuncSetAttribute((const void *)co_scatter, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(sizeof(unsigned long long) * words)));
+    hipLaunchKernelGGL(co_count, grid, dim3(256), sizeof(int) * words, c->stream, c->chunks_dev, log2, buckets, c->co_count_dev);
+    hipLaunchKernelGGL(co_scan, dim3(1), dim3(1024), 0, c->stream, c->co_count_dev, c->co_off_dev, n, buckets, most_dev);
+    hipLaunchKernelGGL(co_scatter, grid, dim3(256), sizeof(unsigned long long) * words, c->stream, c->chunks_dev, log2, buckets, c->co_count_dev,
+                       c->co_entries_dev);
+    hipLaunchKernelGGL(co_sort, dim3((unsigned)std::min<int64_t>(n, 65536)), dim3(1024), 0, c->stream, (const long long *)c->co_off_dev, n, log2, c->co_entries_dev);
+    HIP_TRY(c, hipGetLastError());
+    HIP_TRY(c, hipMemcpyAsync(&most, most_dev, sizeof most, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->columns = ColumnOrder{c->co_entries_dev, c->co_off_dev, buckets, log2, blocks, c->n_total};
+    // (a workgroup has a bucket: one that holds far more entries than the average compute unit's share would be waited for)
+    c->merge_by_columns = (double)most * c->cu_count <= 4.0 * (double)c->entries_loaded + 65536.0 * c->cu_count;
     return CHICLE_OK;
 }
 
@@ -1260,8 +1323,12 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
     c->progress_dev = (int *)carve(c, sizeof(int) * (size_t)max_solvers);
     c->split_ring_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * (size_t)SPLIT_WORDS * (size_t)max_solvers);
     if (c->long_rows) {
-        c->slice_off_dev = (int32_t *)carve(c, sizeof(int32_t) * ((size_t)max_slices(d) + 1) * (size_t)n_total);
-        c->slice_z_dev = (double *)carve(c, sizeof(double) * (size_t)n_total);
+        const size_t n_off = (size_t)co_blocks(n_total) * (size_t)co_buckets(d) + 2;
+        c->co_entries_dev = (ColumnEntry *)carve(c, sizeof(ColumnEntry) * (size_t)total_entries);
+        c->co_off_dev = (long long *)carve(c, sizeof(long long) * n_off);
+        c->co_count_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * n_off);
+        c->co_z_dev = (double *)carve(c, sizeof(double) * (size_t)co_parts(n_total) * (size_t)n_total);
+        c->co_coef_dev = (float *)carve(c, sizeof(float) * ((size_t)n_total + 4));
         c->row_split_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)SPLITS_PER_ROW * (size_t)n_total);
         c->cluster_ring_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * (size_t)CLUSTER_WORDS * (size_t)max_solvers);
     }
@@ -1286,7 +1353,7 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
         c->pair_list[buf] = (unsigned long long *)(pairs + pair_set_bytes(c->max_tiles) * (size_t)buf);
         c->pair_count[buf] = (int32_t *)(c->pair_list[buf] + (size_t)PAIR_CAP * (size_t)c->max_tiles);
     }
-    if (!c->err_dev || !c->tickets_dev || !c->ticks_dev || !c->progress_dev || !c->split_ring_dev || (c->long_rows && (!c->cluster_ring_dev || !c->slice_z_dev)) || (c->compact && (!c->chunk_owner_dev || !c->blocks_ring_dev)) || (own_pairs && !pairs)) { delete c; return CHICLE_ENOMEM; }
+    if (!c->err_dev || !c->tickets_dev || !c->ticks_dev || !c->progress_dev || !c->split_ring_dev || (c->long_rows && (!c->cluster_ring_dev || !c->co_coef_dev)) || (c->compact && (!c->chunk_owner_dev || !c->blocks_ring_dev)) || (own_pairs && !pairs)) { delete c; return CHICLE_ENOMEM; }
 
     c->chunks.assign(n_chunks, ChunkDev{});
     c->loaded.assign(n_chunks, 0);
@@ -1297,7 +1364,7 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
               hipMemsetAsync(c->u, 0, sizeof(float) * (size_t)c->u_capacity, c->stream) == hipSuccess &&
               hipMemsetAsync(c->err_dev, 0, sizeof(int), c->stream) == hipSuccess &&
               hipMemsetAsync(c->tickets_dev, 0, sizeof(unsigned) * n_tickets(d), c->stream) == hipSuccess &&
-              (!c->long_rows || hipMemsetAsync(c->slice_z_dev, 0, sizeof(double) * (size_t)n_total, c->stream) == hipSuccess) &&
+              (!c->long_rows || hipMemsetAsync(c->co_coef_dev, 0, sizeof(float) * ((size_t)n_total + 4), c->stream) == hipSuccess) &&
               hipMemsetAsync(c->ticks_dev, 0, sizeof(long long) * 2 * (size_t)max_solvers, c->stream) == hipSuccess;
     {
         int dev = 0;
@@ -1630,20 +1697,12 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
             HIP_TRY(c, hipGetLastError());
             c->split_built_for = c->cluster;
         }
-        // the sliced gap row pass, where the shared vector is several slices long (built once: data only)
-        if (c->gap_slices == 0) {
-            const int shift = SLICE_BYTES_LOG2 - (c->loss == CHICLE_LOSS_HINGE ? 2 : 3);
-            const int S = (int)(((int64_t)c->d + (1 << shift) - 1) >> shift);
-            if (S >= SLICES_MIN) {
-                int max_rows = 1;
-                for (const ChunkDev &ch : c->chunks) max_rows = std::max(max_rows, ch.n_rows);
-                hipLaunchKernelGGL(slice_offsets, dim3(grid_for(max_rows, 4, 256), c->n_chunks), dim3(256), 0, c->stream,
-                                   c->chunks_dev, shift, S, c->n_total, c->slice_off_dev);
-                HIP_TRY(c, hipGetLastError());
-                c->gap_slices = S; c->gap_slice_shift = shift;
-            }
+        if (c->columns.blocks == 0) {
+            const int rc = order_by_column(c);
+            if (rc) return rc;
         }
     }
+    c->coef_pending = c->private_stale = false;
     return clear_all_private(c);
 }
 
@@ -1761,7 +1820,14 @@ int chicle_aggregate(chicle_ctx *c)
     if (c->state != ST_EPOCH_DONE) return fail(c, CHICLE_ESTATE, "no local epoch pending");
     seg_begin(c, CHICLE_SEG_AGGREGATE);
     const int64_t d4 = c->ld_v / 4;
-    if (c->compact) {
+    if (c->coef_pending) {
+        const size_t sh = (sizeof(double) << c->columns.bucket_log2) + sizeof(float) * CO_ROWS;
+        HIP_TRY(c, hipFuncSetAttribute((const void *)column_merge, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+        hipLaunchKernelGGL(column_merge, dim3((unsigned)c->columns.buckets), dim3(CO_THREADS), sh, c->stream, c->columns, (const float *)c->co_coef_dev, c->w64,
+                           c->w, (int64_t)c->d, (float)(1.0 / (double)c->K), c->l1);
+        c->coef_pending = false;
+        c->private_stale = true;
+    } else if (c->compact) {
         // few words: the solvers are divided over slices too, so that the chip is filled.  Thinly occupied vectors (under an
         // eighth of the columns per solver on average): entries are picked straight from memory
         const bool thin = c->u_used * 8 < (int64_t)c->K * (int64_t)c->d;
@@ -1934,6 +2000,7 @@ int chicle_get_delta_w(chicle_ctx *c, int32_t solver, float *dw_out)
     if (!c || !dw_out) return CHICLE_EINVAL;
     if (c->state != ST_EPOCH_DONE) return fail(c, CHICLE_ESTATE, "updates exist only between local_epoch and aggregate");
     if (solver < -1 || solver >= c->K) return fail(c, CHICLE_EINVAL, "solver %d, K=%d", solver, c->K);
+    if (c->coef_pending) spread_updates(c);
     if (c->compact)
         hipLaunchKernelGGL(delta_w_out_compact, dim3(grid_for(c->d, 256, 4096)), dim3(256), 0, c->stream, c->u, c->u_off_dev,
                            c->bits_dev, c->pref_dev, c->words, (int64_t)c->d, c->K, solver, (float)(1.0 / (double)c->K), c->tmp_a);

@@ -579,6 +579,7 @@ struct BlocksArgs {
     const SegRef *refs;
     const int32_t *segs;
     float *coef_out;                            // per row (solver by solver): its coefficient in the update, for spread_unique
+    float *coef_by_row;                         // the same by context-wide row (nullptr: not wanted)
     int64_t n_total;
     int G, k_pad;
     RoundScalars sc;
@@ -704,6 +705,7 @@ __global__ __launch_bounds__(SB_THREADS) void sdca_blocks(BlocksArgs A)
                     if (LOSS != 1) an = fminf(fmaxf(an, 0.f), 1.f);
                     gst(&cur_row.st->alpha, an);
                     gst(A.coef_out + S.perm_off + cur_row.lr, coef);
+                    if (A.coef_by_row) gst(A.coef_by_row + cur_row.row, coef);
                 }
                 keep_loaded(nxt);
                 cur_row = next_row; next_row = far_row; cur = nxt;
@@ -866,10 +868,11 @@ __global__ __launch_bounds__(256) void spread_unique(const SolverDev *__restrict
     }
 }
 
-// Without that room: one wavefront per row.  Grid: (blocks over rows, chunk).
+// Without that room: one wavefront per row.  all: also of rows whose coefficient is zero (the vectors were not zero before).
+// Grid: (blocks over rows, chunk).
 __global__ __launch_bounds__(256) void scatter_unique(const ChunkDev *__restrict__ chunks, const int32_t *__restrict__ owner,
                                                       const SolverDev *__restrict__ solvers, const int32_t *__restrict__ chunk_first,
-                                                      const float *__restrict__ coef, float *u_all, const int64_t *__restrict__ u_off)
+                                                      const float *__restrict__ coef, float *u_all, const int64_t *__restrict__ u_off, bool all)
 {
     const ChunkDev &ch = chunks[blockIdx.y];
     const int32_t *cid = chunk_compact_ids(ch);
@@ -879,7 +882,7 @@ __global__ __launch_bounds__(256) void scatter_unique(const ChunkDev *__restrict
     const int lane = threadIdx.x & 63;
     for (int r = blockIdx.x * 4 + (threadIdx.x >> 6); r < ch.n_rows; r += gridDim.x * 4) {
         const float cf = of[r];
-        if (cf == 0.f) continue;
+        if (cf == 0.f && !all) continue;
         const int e = ch.row_ptr[r + 1];
         for (int p = ch.row_ptr[r] + lane; p < e; p += 256) {
             int c[4];

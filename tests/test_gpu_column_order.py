@@ -1,0 +1,61 @@
+"""Long rows: the copy of the entries by column that the gap's row pass and the merge stream over.  Rows on both sides of a block of
+16384, columns in several segments of 262144, a last bucket that is not full, one bucket that holds everything (merged through the
+private vectors), solvers by name in turn, updates read out between pass and merge."""
+import numpy as np
+import pytest
+
+from harness import TOL_DW, dw_floor, gap_tolerance, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("loss,n,d,length,popular,l1,by_name", [
+    ("hinge", 16400, 600011, 100, 0, 0.0, False), ("squared", 321, 5003, 130, 0, 0.0, True), ("logistic", 500, 300001, 200, 0, 0.0, False),
+    ("hinge", 700, 300001, 150, 900, 0.0, True), ("squared", 40, 20000003, 300, 0, 0.0, False), ("hinge", 321, 262145, 130, 0, 0.02, True),
+    ("squared", 2500, 40009, 400, 0, 0.0, False)])
+def test_passes_by_column(oracle_mod, loss, n, d, length, popular, l1, by_name):
+    import torch
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    assert torch.cuda.is_available()
+    print("\ncase columns %s n=%d d=%d length=%d popular=%d" % (loss, n, d, length, popular), flush=True)
+    g = np.random.default_rng(n + d)
+    lens = g.integers(length // 2, length + length // 2 + 8, n)
+    rows = [np.sort(g.choice(popular or d, min(m, popular or d), replace=False)) if popular or d < 10 ** 5
+            else np.unique(g.integers(0, d, m)) for m in lens]
+    lens, col = [len(c) for c in rows], np.concatenate(rows).astype(np.int32)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    val = (g.standard_normal(len(col)) / np.sqrt(length)).astype(np.float32)
+    y = (g.standard_normal(n) if loss == "squared" else np.where(g.random(n) < 0.5, -1, 1)).astype(np.float32)
+    bounds = np.unique(np.concatenate([np.arange(0, n, max(7, n // 9)), [n]])).astype(np.int64)
+    p = Problem("columns", loss, n, d, 20.0 / n, y, bounds, row_ptr=rp, col=col, val=val)
+    assert len(col) > 96 * n
+    K = min(5, len(bounds) - 1)
+    r = binding.ChicleRound.from_problem(p, max_solvers=K)
+    o = oracle_mod.OracleCoCoA.from_problem(p, l1=l1)
+    if l1:
+        r.set_l1(l1)
+    table = (np.arange(len(bounds) - 1) % K).astype(np.int32)
+    r.assign(K, table)
+    o.assign(K, table)
+    for k in range(4):
+        if by_name:
+            r.set_solver("rowwise" if k == 1 else "auto")
+        perms = [g.permutation(m).astype(np.int32) for m in o.rows_per_solver()]
+        floor = dw_floor(float(np.linalg.norm(o.w)))
+        r.local_epoch(r.upload_perm(perms))
+        dws = o.local_epoch(perms)
+        if k != 2:                                    # (a merge with and without a read-out before it)
+            for s in range(K):
+                err = rel_l2(r.get_delta_w(s), dws[s], floor)
+                assert err <= TOL_DW, (k, s, err)
+        o.aggregate()
+        r.aggregate()
+        P, D, G = r.gap()
+        Po, Do, Go = o.gap()[:3]
+        err = rel_l2(r.get_w(), o.w, 1e-30)
+        print("round %d w %.2e primal %.2e dual %.2e" % (k, err, abs(P - Po) / abs(Po), abs(D - Do) / max(abs(Do), 1e-30)), flush=True)
+        # the float mirror rounds w by 2^-24 of its entries; the updates' own errors, a few 2^-24 of each, come on top
+        assert err <= 1e-6
+        assert abs(P - Po) <= 1e-6 * abs(Po) and abs(G - Go) <= gap_tolerance(Go, Po)
+    r.close()
