@@ -40,10 +40,11 @@
  *   - the library allocates no device memory: it carves everything out of the arena handed to
  *     chicle_create (size it with chicle_arena_bytes); the arena and the HIP stream are borrowed for
  *     the lifetime of the context; all work is enqueued on that stream (and, ordered with it, on one stream
- *     of the library's own); the context itself holds 64 bytes of pinned host memory, into which the gap's
- *     last kernel writes its sums, and from the first get_w or get_delta_w of 4 MB or more on 12 MB of it,
- *     through which several threads copy such a vector out;
- *   - calls that return values to the host (gap, get_*) wait for the stream; the others only enqueue;
+ *     of the library's own); the context itself holds pinned host memory: 256 bytes, into which the gap's
+ *     last kernel writes its sums, as many as a vector and visiting orders of up to 1 MB each take, and from the
+ *     first get_w or get_delta_w of 4 MB or more on 12 MB, through which several threads copy such a vector out;
+ *   - calls that return values to the host (gap, get_*) wait for what was enqueued before them to be done (gap: for
+ *     the sums that its last kernel writes); the others only enqueue;
  *   - a context is not thread-safe.  Local passes of different contexts on one GPU should not run at the
  *     same time where several workgroups share a solver (chicle_debug_solver): these wait for each other, and
  *     if another pass keeps some of them off the chip for too long, the wait is given up (EDEVICE).

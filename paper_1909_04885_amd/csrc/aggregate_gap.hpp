@@ -309,8 +309,8 @@ __device__ __forceinline__ double wave_sum_d(double x)
 // What the last kernel of the gap does beside its rows.  Its grid has one dimension, whose limit no number of chunks comes
 // near: per_chunk workgroups for every chunk, one chunk after the other, then n_w that sum |w|^2 and |w|_1.  Every workgroup
 // leaves its two partial sums, and the one that leaves them last adds all of them up in a fixed order: out[0] = sum loss,
-// out[1] = sum conj, out[2] = |w|^2, out[3] = the kernels' error flag, out[4] = |w|_1.  out may be host memory mapped into the
-// device's address space.  (Kernels of their own for the norms and for the end: 500000 x 28 in all 34 us, 17.9 now; 4096 x 256
+// out[1] = sum conj, out[2] = |w|^2, out[3] = the kernels' error flag, out[4] = |w|_1, and when these are there the number of the
+// gap, seq, in out[5].  out may be host memory mapped into the device's address space.  (Kernels of their own for the norms and for the end: 500000 x 28 in all 34 us, 17.9 now; 4096 x 256
 // 16 and 6.4; sparse rows, 30000 x 20k, 24 and 18.8.)  tickets: nullptr where only the rows' residuals are wanted (n_w is zero
 // then); else zero, and left so.  Adds to one address take 13 ns each, so workgroups are counted in GAP_GROUPS groups, and the
 // groups that are complete at tickets[GAP_GROUPS * TICKET_LINE].
@@ -324,6 +324,7 @@ struct GapEnd {
     int n_w, n_chunks, per_chunk;
     const int *err;
     double *out;
+    unsigned long long seq;
 };
 // A row workgroup's chunk (n_chunks and more: a workgroup for the norms), and which of the chunk's workgroups it is.
 __device__ __forceinline__ int gap_chunk(const GapEnd &E) { return (int)(blockIdx.x / (unsigned)E.per_chunk); }
@@ -405,6 +406,7 @@ __device__ __forceinline__ void gap_block_end(double a, double b, double *out_a,
         E.out[2] = sums[2];
         E.out[3] = (double)*E.err;
         E.out[4] = sums[3];
+        __hip_atomic_store(reinterpret_cast<unsigned long long *>(E.out + 5), E.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

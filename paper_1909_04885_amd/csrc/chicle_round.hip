@@ -52,6 +52,11 @@ inline int64_t pad_d(int64_t d) { return (d + 63) / 64 * 64; }
 inline int64_t tiles_cap(int64_t n_total, int32_t max_solvers) { return n_total / BATCH + max_solvers + 1; }
 inline size_t tile_bytes(bool dense) { return sizeof(float) * (size_t)(dense ? DENSE_TILE_FLOATS : TILE_FLOATS); }
 
+// Vectors and visiting orders of at most so many bytes go through pinned memory that kernels write and read themselves: a copy and
+// a wait less each.  One round of 1000 x 48 with orders from the host: 91.5 us and 54.0; four of 1500
+// long rows over 200k columns 448 and 420.
+constexpr size_t PINNED_HEAD = 256, PINNED_MOST = size_t(1) << 20;
+constexpr int GAP_SPINS = 100000;                // reads of the word before the stream is waited for (a few milliseconds)
 constexpr size_t READ_PIECE = size_t(2) << 20;   // bytes
 constexpr int READ_THREADS = 6;
 
@@ -152,8 +157,12 @@ struct chicle_ctx {
     int32_t *perm_stage = nullptr;
     GapScratch gap_scratch;           // in the arena
     double *static_scratch = nullptr; // this device's copy of the fixed scratch array (chicle_gap_noalloc)
-    double *gap_host = nullptr;       // 5 doubles of pinned host memory the row pass's last workgroup writes into (GapEnd) ...
-    double *gap_host_dev = nullptr;   // ... through this device address
+    // Pinned host memory: what the row pass's last workgroup writes (GapEnd; 6 doubles), then a word for the error flag, and from
+    // PINNED_HEAD on a vector of up to PINNED_MOST bytes on its way out and visiting orders of as many on their way in.
+    char *pinned = nullptr, *pinned_dev = nullptr;       // (as the host and as the device sees it)
+    size_t pinned_vector = 0, pinned_orders = 0;         // where these two are; 0: there is none
+    bool orders_in_flight = false;    // the orders there may not have been taken yet
+    unsigned long long gap_seq = 0;
     int *err_dev = nullptr;
     unsigned *tickets_dev = nullptr;  // see n_tickets
     int *progress_dev = nullptr;      // per solver: block its batched pass has reached
@@ -383,20 +392,24 @@ void seg_end(chicle_ctx *c, int s)
     }
 }
 
+// The kernels' error flag, which has been read out, as a status; it is cleared.
+int flag_status(chicle_ctx *c, int flag)
+{
+    if (!flag) return CHICLE_OK;
+    HIP_TRY(c, hipMemsetAsync(c->err_dev, 0, sizeof(int), c->stream));
+    if (flag & ERR_PERM_RANGE)
+        return fail(c, CHICLE_EDEVICE, "a visiting-order entry was outside [0, rows of its solver)");
+    if (flag & ERR_PARTNER_TIMEOUT)
+        return fail(c, CHICLE_EDEVICE, "the workgroups that share a solver lost each other; the pass is invalid");
+    return fail(c, CHICLE_EDEVICE, "kernel error flag %d", flag);
+}
+
 int check_deferred(chicle_ctx *c)
 {
     int flag = 0;
     HIP_TRY(c, hipMemcpyAsync(&flag, c->err_dev, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (flag) {
-        HIP_TRY(c, hipMemsetAsync(c->err_dev, 0, sizeof(int), c->stream));
-        if (flag & ERR_PERM_RANGE)
-            return fail(c, CHICLE_EDEVICE, "a visiting-order entry was outside [0, rows of its solver)");
-        if (flag & ERR_PARTNER_TIMEOUT)
-            return fail(c, CHICLE_EDEVICE, "the workgroups that share a solver lost each other; the pass is invalid");
-        return fail(c, CHICLE_EDEVICE, "kernel error flag %d", flag);
-    }
-    return CHICLE_OK;
+    return flag_status(c, flag);
 }
 
 int grid_for(int64_t items, int per_block, int cap)
@@ -917,7 +930,7 @@ GapEnd gap_end(const chicle_ctx *c, const GapScratch &gs, int per_chunk, int thr
     E.v = c->w64; E.d = (int64_t)c->d;
     E.part_wsq = gs.wsq; E.part_wabs = gs.wabs;
     E.n_w = grid_for(c->d, threads * 8, WSQ_PARTS * 256 / threads);
-    E.err = c->err_dev; E.out = c->gap_host_dev;
+    E.err = c->err_dev; E.out = (double *)c->pinned_dev; E.seq = c->gap_seq;
     *grid = dim3(rows + (unsigned)E.n_w);
     return E;
 }
@@ -1113,7 +1126,7 @@ int order_by_column(chicle_ctx *c)
 int column_crowding(chicle_ctx *c, double *out)
 {
     if (c->crowding < 0.0) {
-        int32_t *count = c->rank_of;       // (needed by no one after the columns are renumbered)
+        int32_t *count = (int32_t *)c->tmp_a;
         double *sums = c->gap_scratch.wabs, s[2] = {0.0, 0.0};
         const int stride = (int)std::max<int64_t>(1, c->n_total / 4096);
         int64_t rows = 0;
@@ -1374,8 +1387,14 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
     }
     for (int s = 0; ok && s < CHICLE_SEG_COUNT; ++s)
         ok = hipEventCreate(&c->seg[s].start) == hipSuccess && hipEventCreate(&c->seg[s].stop) == hipSuccess;
-    ok = ok && hipHostMalloc((void **)&c->gap_host, sizeof(double) * 8, hipHostMallocMapped) == hipSuccess &&
-         hipHostGetDevicePointer((void **)&c->gap_host_dev, c->gap_host, 0) == hipSuccess;
+    {
+        size_t bytes = PINNED_HEAD;
+        if (sizeof(float) * (size_t)d <= PINNED_MOST) { c->pinned_vector = bytes; bytes += align_up(sizeof(float) * (size_t)d); }
+        if (sizeof(int32_t) * (size_t)n_total <= PINNED_MOST) { c->pinned_orders = bytes; bytes += align_up(sizeof(int32_t) * (size_t)n_total); }
+        ok = ok && hipHostMalloc((void **)&c->pinned, bytes, hipHostMallocMapped) == hipSuccess &&
+             hipHostGetDevicePointer((void **)&c->pinned_dev, c->pinned, 0) == hipSuccess;
+        if (ok) std::memset(c->pinned, 0, PINNED_HEAD);
+    }
     ok = ok && static_scratch_of_current_device(&c->static_scratch) == hipSuccess;
     ok = ok && hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) == hipSuccess &&
          hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) == hipSuccess &&
@@ -1809,8 +1828,17 @@ int chicle_local_epoch_host_perm(chicle_ctx *c, const int32_t *perm_host)
     if (!c) return CHICLE_EINVAL;
     if (c->state != ST_READY) return fail(c, CHICLE_ESTATE, c->state == ST_LOADING ? "assign first" : "aggregate before the next local epoch");
     if (!perm_host) return fail(c, CHICLE_EINVAL, "perm is NULL");
-    HIP_TRY(c, hipMemcpyAsync(c->perm_stage, perm_host, sizeof(int32_t) * (size_t)c->n_total, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if (c->pinned_orders) {
+        if (c->orders_in_flight) HIP_TRY(c, hipStreamSynchronize(c->stream));
+        std::memcpy(c->pinned + c->pinned_orders, perm_host, sizeof(int32_t) * (size_t)c->n_total);
+        c->orders_in_flight = true;
+        hipLaunchKernelGGL(copy_words, dim3(grid_for(c->n_total, 256, 1024)), dim3(256), 0, c->stream,
+                           (const int32_t *)(c->pinned_dev + c->pinned_orders), c->n_total, c->perm_stage);
+        HIP_TRY(c, hipGetLastError());
+    } else {
+        HIP_TRY(c, hipMemcpyAsync(c->perm_stage, perm_host, sizeof(int32_t) * (size_t)c->n_total, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+    }
     return chicle_local_epoch(c, c->perm_stage);
 }
 
@@ -1858,21 +1886,23 @@ static int gap_with(chicle_ctx *c, GapScratch gs, double *primal, double *dual, 
     if (c->state != ST_READY) return fail(c, CHICLE_ESTATE, "gap is defined on the aggregated state");
     seg_begin(c, CHICLE_SEG_GAP);
     gs.finish = true;
+    c->gap_seq += 1;
     const int rc = run_row_pass(c, gs);
     seg_end(c, CHICLE_SEG_GAP);
     if (rc) return rc;
-    // the sums and the error flag arrive in pinned host memory with the end of the kernel: no copy to wait for
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    const double *h = c->gap_host;
-    if (h[3] != 0.0) {
-        const int flag = (int)h[3];
-        HIP_TRY(c, hipMemsetAsync(c->err_dev, 0, sizeof(int), c->stream));
-        if (flag & ERR_PERM_RANGE)
-            return fail(c, CHICLE_EDEVICE, "a visiting-order entry was outside [0, rows of its solver)");
-        if (flag & ERR_PARTNER_TIMEOUT)
-            return fail(c, CHICLE_EDEVICE, "the workgroups that share a solver lost each other; the pass is invalid");
-        return fail(c, CHICLE_EDEVICE, "kernel error flag %d", flag);
+    // The sums and the error flag arrive in pinned host memory, and behind them the gap's number: what is waited for is that word
+    // (waiting for the stream takes some 5 us more: ten rounds of 4096 x 256 706 us and 686).  Should it be long in coming, the stream is waited for.
+    const double *h = (const double *)c->pinned;
+    const unsigned long long *arrived = (const unsigned long long *)(h + 5);
+    for (int spins = 0; __atomic_load_n(arrived, __ATOMIC_ACQUIRE) != c->gap_seq; ++spins) {
+        if (spins == GAP_SPINS) {
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+            break;
+        }
+        __builtin_ia32_pause();
     }
+    c->orders_in_flight = false;
+    if (h[3] != 0.0) return flag_status(c, (int)h[3]);
     const double n = (double)c->n_total;
     const double P = c->lambda * (0.5 * h[2] + c->l1 * h[4]) + h[0] / n;     // (the regulariser's conjugate at the dual image is |w|^2 / 2)
     const double D = -0.5 * c->lambda * h[2] - h[1] / n;
@@ -1963,6 +1993,17 @@ static int read_to_host(chicle_ctx *c, void *dst, const void *src, size_t bytes)
 // d floats in internal order on the device -> caller's order on the host.
 static int read_vector(chicle_ctx *c, const float *src_internal, float scale, float *host_out)
 {
+    if (c->pinned_vector) {
+        int *flag = (int *)(c->pinned + PINNED_HEAD / 2);
+        hipLaunchKernelGGL(to_host_in_caller_order, dim3(grid_for(c->d, 256, 1024)), dim3(256), 0, c->stream, src_internal,
+                           c->renumbered ? c->rank_of : (const int32_t *)nullptr, (int64_t)c->d, scale,
+                           (float *)(c->pinned_dev + c->pinned_vector), (const int *)c->err_dev, (int *)(c->pinned_dev + PINNED_HEAD / 2));
+        HIP_TRY(c, hipGetLastError());
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        c->orders_in_flight = false;
+        std::memcpy(host_out, c->pinned + c->pinned_vector, sizeof(float) * (size_t)c->d);
+        return flag_status(c, *flag);
+    }
     hipLaunchKernelGGL(to_caller_order<float>, dim3(grid_for(c->d, 256, 4096)), dim3(256), 0, c->stream,
                        src_internal, c->renumbered ? c->col_of : (const int32_t *)nullptr, (int64_t)c->d,
                        scale, c->tmp_b);
@@ -2219,7 +2260,7 @@ void chicle_destroy(chicle_ctx *c)
     if (!c) return;
     if (c->side) (void)hipStreamSynchronize(c->side);
     (void)hipStreamSynchronize(c->stream);
-    if (c->gap_host) (void)hipHostFree(c->gap_host);
+    if (c->pinned) (void)hipHostFree(c->pinned);
     if (c->read_pinned) (void)hipHostFree(c->read_pinned);
     for (hipEvent_t ev : c->read_ev)
         if (ev) (void)hipEventDestroy(ev);

@@ -11,6 +11,13 @@
 
 namespace chicle {
 
+// Words from host memory mapped into the device's address space.
+__global__ __launch_bounds__(256) void copy_words(const int32_t *__restrict__ in, int64_t n, int32_t *out)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) out[i] = in[i];
+}
+
 // count[col] += 1 for every stored entry.  Grid: (blocks over entries, chunk).
 __global__ __launch_bounds__(256) void count_columns(const ChunkDev *__restrict__ chunks, int *count)
 {
@@ -224,6 +231,15 @@ __global__ __launch_bounds__(256) void to_caller_order(const T *__restrict__ in,
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < d; r += stride)
         out[col_of ? col_of[r] : r] = (float)in[r] * scale;
+}
+
+// The same into host memory mapped into the device's address space, and the kernels' error flag beside it.
+__global__ __launch_bounds__(256) void to_host_in_caller_order(const float *__restrict__ in, const int32_t *__restrict__ rank_of, int64_t d,
+                                                               float scale, float *out, const int *err, int *flag)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *flag = *err;
+    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < d; c += stride) out[c] = in[rank_of ? rank_of[c] : c] * scale;
 }
 
 // out64[r] = out32[r] = in[col_of[r]] (caller's column ids -> internal order).
