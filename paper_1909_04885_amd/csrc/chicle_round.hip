@@ -308,10 +308,17 @@ int co_parts(int64_t n_total)
     const int most = std::max(1, CO_PARTS / co_blocks(n_total));
     return most < L2_PARTITIONS ? most : most / L2_PARTITIONS * L2_PARTITIONS;
 }
+// The entries; and, in whole megabytes, where buckets begin, what counts them, the parts of the dot products and the coefficients.
+size_t co_offsets_bytes(int64_t n_total, int32_t d) { return align_up(sizeof(long long) * ((size_t)co_blocks(n_total) * (size_t)co_buckets(d) + 2)); }
+size_t co_parts_bytes(int64_t n_total) { return align_up(sizeof(double) * (size_t)co_parts(n_total) * (size_t)n_total); }
+size_t co_scratch_bytes(int64_t n_total, int32_t d)
+{
+    const size_t mb = size_t(1) << 20, bytes = 2 * co_offsets_bytes(n_total, d) + co_parts_bytes(n_total) + align_up(sizeof(float) * ((size_t)n_total + 4));
+    return (bytes + mb - 1) / mb * mb;
+}
 size_t co_bytes(int64_t n_total, int64_t total_entries, int32_t d)
 {
-    return align_up(sizeof(ColumnEntry) * (size_t)total_entries) + 2 * align_up(sizeof(long long) * ((size_t)co_blocks(n_total) * (size_t)co_buckets(d) + 2)) +
-           align_up(sizeof(double) * (size_t)co_parts(n_total) * (size_t)n_total) + align_up(sizeof(float) * ((size_t)n_total + 4));
+    return align_up(sizeof(ColumnEntry) * (size_t)total_entries) + co_scratch_bytes(n_total, d);
 }
 
 // Counters of workgroups that are done: the gap's, and one per workgroup's columns for the merge.  Zero between kernels.
@@ -1336,12 +1343,13 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
     c->progress_dev = (int *)carve(c, sizeof(int) * (size_t)max_solvers);
     c->split_ring_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * (size_t)SPLIT_WORDS * (size_t)max_solvers);
     if (c->long_rows) {
-        const size_t n_off = (size_t)co_blocks(n_total) * (size_t)co_buckets(d) + 2;
         c->co_entries_dev = (ColumnEntry *)carve(c, sizeof(ColumnEntry) * (size_t)total_entries);
-        c->co_off_dev = (long long *)carve(c, sizeof(long long) * n_off);
-        c->co_count_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * n_off);
-        c->co_z_dev = (double *)carve(c, sizeof(double) * (size_t)co_parts(n_total) * (size_t)n_total);
-        c->co_coef_dev = (float *)carve(c, sizeof(float) * ((size_t)n_total + 4));
+        if (char *at = (char *)carve(c, co_scratch_bytes(n_total, d))) {
+            c->co_off_dev = (long long *)at;
+            c->co_count_dev = (unsigned long long *)(at += co_offsets_bytes(n_total, d));
+            c->co_z_dev = (double *)(at += co_offsets_bytes(n_total, d));
+            c->co_coef_dev = (float *)(at += co_parts_bytes(n_total));
+        }
         c->row_split_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)SPLITS_PER_ROW * (size_t)n_total);
         c->cluster_ring_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * (size_t)CLUSTER_WORDS * (size_t)max_solvers);
     }
