@@ -15,7 +15,8 @@
 // Cycles per block, one wavefront's clock, K = 4 .. 16: 64 x 256 hinge 5.1e3 (recurrence 2.0e3, wait for the rows and dot
 // products 1.9e3, update 0.8e3), 32 x 1001 hinge 5.9e3, 64 x 28 squared 3.2e3.  Jobs of ten rounds of 4096 x 256 with
 // four solvers: 2.99 -> 0.72 ms (before: Gram matrix and rows of a block formed one after the other on the solver's
-// compute unit); three rounds of 20011 x 1001, logistic, eight solvers: 52.4 -> 1.43 ms (before: one row at a time);
+// compute unit); three rounds of 20011 x 1001, logistic, eight solvers: 52.4 -> 1.43 ms (before: one row at a time), 1.04 with
+// series that are renewed where rows move;
 // fifty rounds of 500000 x 28, squared, 16 solvers: 50.4 -> 37.2 ms, 28.1 with sdca_dense_squared, 10.8 with sdca_dense_affine.hpp (before: the solver for
 // short sparse rows, whose lanes all add to the same 28 places of LDS); 1000 x 48: 103 -> 90 us.
 // Precision: a tile's products and the sums of a wavefront's rows in the update are fp32, the sums over wavefronts and blocks
