@@ -308,6 +308,12 @@ int chicle_debug_gram(chicle_ctx *ctx, const int32_t *perm_device, float *tiles_
  * updated row by row (else as one stream).  Errors: EINVAL, ESTATE (before the first assign). */
 int chicle_debug_solver(chicle_ctx *ctx, int32_t *out);
 
+/* Diagnostic: what the passes over the whole matrix do under the current assignment (host, pure), four integers: 1 where the rows'
+ * dot products (gap, and the residuals a local pass starts from) go over long rows' entries by column, 1 where the merge after
+ * a pass of the blocks over shared columns does, the parts that a block of rows is summed in there, and how many of the chip's
+ * L2 partitions get parts.  Errors: EINVAL, ESTATE (before the first assign). */
+int chicle_debug_passes(chicle_ctx *ctx, int32_t *out);
+
 /* Wait for the stream; report any deferred kernel error. */
 int chicle_sync(chicle_ctx *ctx);
 

@@ -30,7 +30,7 @@ EXPORTS = [
     "chicle_last_kernel_ms", "chicle_last_error", "chicle_destroy",
     "chicle_solver_ms", "chicle_projected_iteration_time", "chicle_scale_out", "chicle_scale_in",
     "chicle_rebalance", "chicle_next_solver_count", "chicle_gap_noalloc", "chicle_set_l1",
-    "chicle_debug_solver",
+    "chicle_debug_solver", "chicle_debug_passes",
 ]
 
 
@@ -83,6 +83,7 @@ def load_library():
         "chicle_get_assignment": (ctypes.c_int, [vp, vp, ctypes.POINTER(i32)]),
         "chicle_debug_gram": (ctypes.c_int, [vp, vp, vp, i64, ctypes.POINTER(i32)]),
         "chicle_debug_solver": (ctypes.c_int, [vp, vp]),
+        "chicle_debug_passes": (ctypes.c_int, [vp, vp]),
         "chicle_sync": (ctypes.c_int, [vp]),
         "chicle_set_profiling": (ctypes.c_int, [vp, i32]),
         "chicle_last_kernel_ms": (ctypes.c_int, [vp, i32, ctypes.POINTER(ctypes.c_float)]),
@@ -369,6 +370,12 @@ class ChicleRound:
         out = np.zeros(4, dtype=np.int32)
         self._check(self._L.chicle_debug_solver(self._h, _ptr(out)))
         return ("rowwise", "batched", "dense", "blocks")[out[0]], int(out[1]), bool(out[2]), bool(out[3])
+
+    def debug_passes(self):
+        """(dot products by column, merge by column, parts of the dot products, L2 partitions that get parts)."""
+        out = np.zeros(4, dtype=np.int32)
+        self._check(self._L.chicle_debug_passes(self._h, _ptr(out)))
+        return bool(out[0]), bool(out[1]), int(out[2]), int(out[3])
 
     def sync(self):
         self._check(self._L.chicle_sync(self._h))

@@ -303,10 +303,17 @@ int co_bucket_log2(int32_t d)
     return b;
 }
 int co_buckets(int32_t d) { return (int)(((int64_t)d + (1 << co_bucket_log2(d)) - 1) >> co_bucket_log2(d)); }
+// As many parts as compute units have workgroups for, in whole multiples of the L2 partitions (column_part); from 33 blocks on, where
+// that leaves fewer, the number up to CO_LEAST_PARTS that keeps the last round of workgroups fullest.
 int co_parts(int64_t n_total)
 {
-    const int most = std::max(1, CO_PARTS / co_blocks(n_total));
-    return most < L2_PARTITIONS ? most : most / L2_PARTITIONS * L2_PARTITIONS;
+    const int blocks = co_blocks(n_total), most = CO_PARTS / blocks;
+    if (most >= L2_PARTITIONS) return most / L2_PARTITIONS * L2_PARTITIONS;
+    auto rounds = [&](int parts) { return ((int64_t)blocks * parts + CO_PARTS - 1) / CO_PARTS; };
+    int best = 1;
+    for (int parts = 2; parts <= std::max(most, CO_LEAST_PARTS); ++parts)
+        if (rounds(parts) * best < rounds(best) * parts) best = parts;
+    return best;
 }
 // The entries; and, in whole megabytes, where buckets begin, what counts them, the parts of the dot products and the coefficients.
 size_t co_offsets_bytes(int64_t n_total, int32_t d) { return align_up(sizeof(long long) * ((size_t)co_blocks(n_total) * (size_t)co_buckets(d) + 2)); }
@@ -991,6 +998,13 @@ void launch_gap_lpr(chicle_ctx *c, int grid, const GapScratch &gs)
     }
 }
 
+// Parts of the dot products by column: of some 4096 entries or more.
+int dot_parts(const chicle_ctx *c)
+{
+    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(co_parts(c->n_total), c->entries_loaded / (4096 * (int64_t)c->columns.blocks)));
+    return parts < L2_PARTITIONS ? parts : parts / L2_PARTITIONS * L2_PARTITIONS;
+}
+
 // The row pass of the gap: z_i = x_i . w into the chunks, loss and conjugate partial sums.
 int run_row_pass(chicle_ctx *c, const GapScratch &gs)
 {
@@ -1013,13 +1027,12 @@ int run_row_pass(chicle_ctx *c, const GapScratch &gs)
         c->gap_hot_grid = gx;
     }
     if (c->columns.blocks > 0) {
-        // (parts of some 4096 entries or more)
-        const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(co_parts(c->n_total), c->entries_loaded / (4096 * (int64_t)c->columns.blocks)));
+        const int parts = dot_parts(c);
         const int per_row = parts <= 8 ? 1 : parts <= 64 ? 4 : 16;
         gx = std::max(1, std::min((max_rows * per_row + 255) / 256, std::min(gs.parts, 2048) / c->n_chunks));
         dim3 fg;
         const GapEnd E = gap_end(c, gs, gx, 256, &fg);
-        const dim3 grid((unsigned)((parts + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS * c->columns.blocks));
+        const dim3 grid((unsigned)(parts * c->columns.blocks));
         const size_t sh = sizeof(double) * (size_t)std::min<int64_t>(CO_ROWS, c->n_total);
         if (c->loss == CHICLE_LOSS_HINGE) {
             HIP_TRY(c, hipFuncSetAttribute((const void *)column_dots<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
@@ -2199,6 +2212,24 @@ int chicle_debug_solver(chicle_ctx *c, int32_t *out)
     out[1] = route == ROUTE_BLOCKS ? c->blocks_g : route == ROUTE_BATCHED ? 1 + std::max(0, split_tails(c)) : route == ROUTE_ROWWISE && clustered ? c->cluster : 1;
     out[2] = route == ROUTE_BLOCKS && !c->blocks_double;
     out[3] = route == ROUTE_BLOCKS && c->sources_dev == nullptr;
+    return CHICLE_OK;
+}
+
+int chicle_debug_passes(chicle_ctx *c, int32_t *out)
+{
+    if (!c || !out) return CHICLE_EINVAL;
+    if (c->state == ST_LOADING) return fail(c, CHICLE_ESTATE, "no assignment yet");
+    const bool by_column = c->columns.blocks > 0;
+    out[0] = by_column;
+    out[1] = by_column && c->merge_by_columns;
+    out[2] = by_column ? dot_parts(c) : 0;
+    out[3] = 0;
+    if (by_column) {
+        unsigned with_work = 0;
+        for (int g = 0; g < out[2] * c->columns.blocks; ++g)
+            if (column_part(g, c->columns.blocks, out[2]).part < out[2]) with_work |= 1u << (g % L2_PARTITIONS);
+        out[3] = __builtin_popcount(with_work);
+    }
     return CHICLE_OK;
 }
 

@@ -26,7 +26,8 @@ constexpr int CO_MAX_BUCKET_LOG2 = 13, CO_MIN_BUCKET_LOG2 = 10;  // columns of a
 constexpr int CO_LDS_BUCKETS = 16384;                            // so many are counted in LDS
 constexpr int CO_PIECE = 4096;                                   // entries that are sorted by column together
 constexpr int CO_GROUP_ROWS = 128;                               // rows per workgroup while the copy is made
-constexpr int CO_PARTS = 256;                                    // parts of the dot products: blocks of rows times this, or less
+constexpr int CO_PARTS = 256;                                    // workgroups of the dot products that run side by side: one to a compute unit
+constexpr int CO_LEAST_PARTS = 4;                                // parts that a block is given room for, however many blocks there are
 
 struct __align__(8) ColumnEntry { unsigned key; float val; };    // key: column in the segment, row in the block
 static_assert(CO_SEG_LOG2 >= CO_MAX_BUCKET_LOG2, "a segment is whole buckets");
@@ -195,8 +196,20 @@ __global__ __launch_bounds__(1024) void co_sort(const long long *__restrict__ of
 
 // ---- the passes -----------------------------------------------------------------------------------------------------
 
-// Grid: blocks * parts, rounded up so that the workgroups of a part, which read the same columns of w, are on one L2 partition.
-// z[part * n_total + row]: the part's share of x_row . w.  Dynamic LDS: a double per row of a block.
+// The part that a workgroup of column_dots takes.  The workgroups of a part read the same columns of w, and are on one L2 partition
+// where there are parts for all of these (whole multiples then).  Fewer parts are dealt out over the whole chip: with each of them on
+// a partition of its own the other partitions stood still (110 entries a row: 600000 rows over 2M columns, six parts then and now,
+// 270 us and 185; 1.2M rows, three, 667 and 302; 2.2M rows over 20M, one then and three now, 6472 and 1039, by rows 4223).
+struct ColumnPart { int block, part; };
+__host__ __device__ inline ColumnPart column_part(int group, int blocks, int parts)
+{
+    if (parts < L2_PARTITIONS) return {group % blocks, group / blocks};
+    const int round = group / L2_PARTITIONS;
+    return {round % blocks, round / blocks * L2_PARTITIONS + group % L2_PARTITIONS};
+}
+
+// Grid: blocks * parts (column_part).  z[part * n_total + row]: the part's share of x_row . w.  Dynamic LDS: a double per row of a
+// block.
 // (100000 rows of a thousand entries over 20M columns: 250 us, with the rows' ends 296; reading the entries alone 160.  By rows, in
 // slices of the columns that an L2 holds, 806 and 40: 26 entries of a row lie in a slice, which use under half of the lines they
 // are on.  The next entries asked for before the gathers 260, two workgroups to a compute unit 248.)
@@ -204,9 +217,8 @@ template <typename WT>
 __global__ __launch_bounds__(CO_THREADS) void column_dots(ColumnOrder C, int parts, const WT *__restrict__ w, double l1, double *z)
 {
     extern __shared__ __align__(16) double co_z[];
-    const int round = (int)blockIdx.x / L2_PARTITIONS, tid = threadIdx.x;
-    const int block = round % C.blocks, part = round / C.blocks * L2_PARTITIONS + (int)blockIdx.x % L2_PARTITIONS;
-    if (part >= parts) return;
+    const int tid = threadIdx.x;
+    const auto [block, part] = column_part((int)blockIdx.x, C.blocks, parts);
     const int64_t row0 = (int64_t)block << CO_ROWS_LOG2;
     const int rows = (int)min((int64_t)CO_ROWS, C.n_total - row0);
     for (int i = tid; i < rows; i += CO_THREADS) co_z[i] = 0.0;

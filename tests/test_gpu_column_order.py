@@ -59,3 +59,33 @@ def test_passes_by_column(oracle_mod, loss, n, d, length, popular, l1, by_name):
         assert err <= 1e-6
         assert abs(P - Po) <= 1e-6 * abs(Po) and abs(G - Go) <= gap_tolerance(Go, Po)
     r.close()
+
+
+def test_many_blocks_of_rows_use_the_whole_chip():
+    """34 blocks of rows leave a block fewer parts than there are L2 partitions: the parts are dealt out over all of these."""
+    import paper_1909_04885_amd as binding
+    n, m, d = 33 * 16384 + 129, 97, 1500000
+    print("\ncase column blocks n=%d m=%d d=%d" % (n, m, d), flush=True)
+    g = np.random.default_rng(5)
+    step = g.integers(1, d // m, n).astype(np.int32)
+    col = (g.integers(0, d, n) % (d - step * (m - 1))).astype(np.int32)[:, None] + step[:, None] * np.arange(m, dtype=np.int32)
+    val = (g.random((n, m), dtype=np.float32) - np.float32(0.5)) / 5
+    y = np.where(g.random(n) < 0.5, -1, 1).astype(np.float32)
+    bounds = np.append(np.arange(0, n, 70001), n)
+    r = binding.ChicleRound("hinge", n, d, 1.0 / n, len(bounds) - 1, 1, False, n * m)
+    for c, (b, e) in enumerate(zip(bounds[:-1], bounds[1:])):
+        r.load_chunk_csr(c, m * np.arange(e - b + 1, dtype=np.int32), col[b:e].reshape(-1), val[b:e].reshape(-1), y[b:e])
+    r.assign(1, np.zeros(len(bounds) - 1, dtype=np.int32))
+    by_column, _, parts, partitions = r.debug_passes()
+    assert by_column and 1 < parts < 8 and partitions == 8
+    w = g.standard_normal(d).astype(np.float32)
+    r.set_w(w)
+    P, D, _ = r.gap()
+    w64, z = w.astype(np.float64), np.empty(n)
+    for b, e in zip(bounds[:-1], bounds[1:]):
+        z[b:e] = np.einsum("ij,ij->i", val[b:e].astype(np.float64), w64[col[b:e]])
+    ref = 0.5 * (w64 @ w64) / n + np.maximum(0, 1 - y * z).mean()
+    print("primal %.3e dual %.3e" % (abs(P - ref) / ref, abs(D + 0.5 * (w64 @ w64) / n) / ref), flush=True)
+    # w is exact in a float here, products and sums are in double: what is left is the rounding of m + n additions
+    assert abs(P - ref) <= 2.0 ** -53 * (n + m) * ref and abs(D + 0.5 * (w64 @ w64) / n) <= 2.0 ** -53 * d * ref
+    r.close()
