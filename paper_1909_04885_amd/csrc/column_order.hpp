@@ -9,8 +9,9 @@
 //                  of a wavefront lie on a few lines of w;
 //   column_merge   a workgroup takes a bucket, and one block after the other: the block's coefficients go into LDS, and
 //                  coef[row] * val is added up in LDS, one double per column of the bucket.
-// The merge needs no private vectors: the coefficients of the steps are all it reads beside the matrix.
-// What bounds both is the matrix: eight bytes per entry once each.
+// The merge needs no private vectors: the coefficients of the steps are all it reads beside the matrix.  It reads all of a block's
+// for every bucket, though, 64 KB: what bounds the dot products is the matrix, eight bytes per entry (and the adds in LDS); the merge
+// is bound by these reads of the L2 where a bucket holds few of a block's entries (merge_pays).
 #pragma once
 #include <hip/hip_runtime.h>
 #include "aggregate_gap.hpp"

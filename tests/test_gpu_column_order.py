@@ -89,3 +89,35 @@ def test_many_blocks_of_rows_use_the_whole_chip():
     # w is exact in a float here, products and sums are in double: what is left is the rounding of m + n additions
     assert abs(P - ref) <= 2.0 ** -53 * (n + m) * ref and abs(D + 0.5 * (w64 @ w64) / n) <= 2.0 ** -53 * d * ref
     r.close()
+
+
+@pytest.mark.parametrize("n,length,d,K,by_column", [
+    (1500, 250, 200003, 7, True), (3000, 300, 5000011, 16, True), (1000, 110, 30000001, 2, False), (40000, 110, 6000007, 3, False),
+    (20000, 250, 40009, 4, False)])
+def test_merge_goes_the_cheaper_way(oracle_mod, n, length, d, K, by_column):
+    """Many columns or blocks of rows for few entries, or entries that solvers' rows share: the merge is through the private vectors."""
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    print("\ncase merge form n=%d length=%d d=%d K=%d" % (n, length, d, K), flush=True)
+    g = np.random.default_rng(n + d)
+    col = (np.sort(g.integers(0, d - length, (n, length)), axis=1) + np.arange(length)).astype(np.int32).reshape(-1)
+    val = (g.standard_normal(n * length) / np.sqrt(length)).astype(np.float32)
+    y = np.where(g.random(n) < 0.5, -1, 1).astype(np.float32)
+    bounds = np.linspace(0, n, 2 * K + 1).astype(np.int64)
+    p = Problem("form", "hinge", n, d, 20.0 / n, y, bounds, row_ptr=np.arange(n + 1, dtype=np.int64) * length, col=col, val=val)
+    r = binding.ChicleRound.from_problem(p, max_solvers=K)
+    o = oracle_mod.OracleCoCoA.from_problem(p)
+    table = (np.arange(2 * K) % K).astype(np.int32)
+    r.assign(K, table)
+    o.assign(K, table)
+    assert r.debug_solver()[0] == "blocks" and r.debug_passes()[:2] == (True, by_column)
+    for k in range(2):
+        perms = [g.permutation(m).astype(np.int32) for m in o.rows_per_solver()]
+        r.local_epoch(r.upload_perm(perms))
+        o.local_epoch(perms)
+        o.aggregate()
+        r.aggregate()
+        err = rel_l2(r.get_w(), o.w, 1e-30)
+        print("round %d w %.2e" % (k, err), flush=True)
+        assert err <= 1e-6                            # (as above)
+    r.close()
