@@ -178,9 +178,8 @@ struct chicle_ctx {
     unsigned long long *cluster_ring_dev = nullptr;
     int cluster = 1;                  // members per solver under the current assignment
     int split_built_for = 0;          // cluster size row_split_dev was built for
-    // long rows: a copy of the entries by column (column_order.hpp), made at the first assignment
+    // long rows: a copy of the entries by column (column_order.hpp), made at an assignment that leaves room for it (copy_at)
     ColumnOrder columns{};            // blocks == 0: there is none
-    ColumnEntry *co_entries_dev = nullptr;
     long long *co_off_dev = nullptr;
     unsigned long long *co_count_dev = nullptr;
     double *co_z_dev = nullptr;       // co_parts x n_total shares of the rows' dot products
@@ -203,6 +202,7 @@ struct chicle_ctx {
     unsigned long long *blocks_ring_dev = nullptr;
     char *layout_dev = nullptr;       // tiles, segment table, places and segments (in place of the batched solver's tile sets)
     size_t layout_bytes = 0;
+    size_t layout_used = 0;           // ... of the current assignment's blocks
     SegRef *refs_dev = nullptr;
     UniqueSource *sources_dev = nullptr;   // u_used; nullptr: no room
     int most_columns = 0;             // most columns a solver's compact vector has
@@ -285,7 +285,7 @@ int64_t private_floats(int64_t total_entries, int64_t ld, int32_t max_solvers, b
 }
 
 // Room behind the tile sets for the shared entries of long rows: eight bytes per entry and four half-empty segments per row,
-// and eight bytes per place of the private vectors.  Contexts of up to 96 entries a row on average have only the tile sets,
+// and eight bytes per place of the private vectors, or per entry for the copy by column (copy_at).  Contexts of up to 96 entries a row on average have only the tile sets,
 // of which the solver that takes rows of any length uses a quarter for its tiles: the rest holds about 89 shared entries a
 // row where a solver has one workgroup, 84, 75 and 57 with two, four and eight.  Rows of more (60 to 96 entries, most of
 // their columns shared) go row by row.
@@ -316,17 +316,20 @@ int co_parts(int64_t n_total)
         if (rounds(parts) * best < rounds(best) * parts) best = parts;
     return best;
 }
-// The entries; and, in whole megabytes, where buckets begin, what counts them, the parts of the dot products and the coefficients.
-size_t co_offsets_bytes(int64_t n_total, int32_t d) { return align_up(sizeof(long long) * ((size_t)co_blocks(n_total) * (size_t)co_buckets(d) + 2)); }
-size_t co_parts_bytes(int64_t n_total) { return align_up(sizeof(double) * (size_t)co_parts(n_total) * (size_t)n_total); }
-size_t co_scratch_bytes(int64_t n_total, int32_t d)
+// ... for so many entries: parts of some 4096 entries or more.
+int dot_parts(int64_t n_total, int64_t entries)
 {
-    const size_t mb = size_t(1) << 20, bytes = 2 * co_offsets_bytes(n_total, d) + co_parts_bytes(n_total) + align_up(sizeof(float) * ((size_t)n_total + 4));
-    return (bytes + mb - 1) / mb * mb;
+    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(co_parts(n_total), entries / (4096 * (int64_t)co_blocks(n_total))));
+    return parts < L2_PARTITIONS ? parts : parts / L2_PARTITIONS * L2_PARTITIONS;
 }
-size_t co_bytes(int64_t n_total, int64_t total_entries, int32_t d)
+// Where buckets begin, what counts them, the parts of the dot products and the coefficients, in whole megabytes.  (The entries
+// themselves lie in the room of the block solver's layout: copy_at.)
+size_t co_offsets_bytes(int64_t n_total, int32_t d) { return align_up(sizeof(long long) * ((size_t)co_blocks(n_total) * (size_t)co_buckets(d) + 2)); }
+size_t co_parts_bytes(int64_t n_total, int64_t entries) { return align_up(sizeof(double) * (size_t)dot_parts(n_total, entries) * (size_t)n_total); }
+size_t co_scratch_bytes(int64_t n_total, int64_t entries, int32_t d)
 {
-    return align_up(sizeof(ColumnEntry) * (size_t)total_entries) + co_scratch_bytes(n_total, d);
+    const size_t mb = size_t(1) << 20, bytes = 2 * co_offsets_bytes(n_total, d) + co_parts_bytes(n_total, entries) + align_up(sizeof(float) * ((size_t)n_total + 4));
+    return (bytes + mb - 1) / mb * mb;
 }
 
 // Counters of workgroups that are done: the gap's, and one per workgroup's columns for the merge.  Zero between kernels.
@@ -367,7 +370,7 @@ size_t fixed_bytes(int64_t n_total, int32_t d, int32_t n_chunks, int32_t max_sol
     s += align_up(sizeof(int) * (size_t)max_solvers);
     s += align_up(sizeof(unsigned long long) * (size_t)SPLIT_WORDS * (size_t)max_solvers);   // rings of the split batched solver
     if (long_rows) {
-        s += co_bytes(n_total, n_total_entries_hint, d);
+        s += align_up(co_scratch_bytes(n_total, n_total_entries_hint, d));
         s += align_up(sizeof(int32_t) * (size_t)SPLITS_PER_ROW * (size_t)n_total);
         s += align_up(sizeof(unsigned long long) * (size_t)CLUSTER_WORDS * (size_t)max_solvers);
     }
@@ -999,13 +1002,6 @@ void launch_gap_lpr(chicle_ctx *c, int grid, const GapScratch &gs)
     }
 }
 
-// Parts of the dot products by column: of some 4096 entries or more.
-int dot_parts(const chicle_ctx *c)
-{
-    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(co_parts(c->n_total), c->entries_loaded / (4096 * (int64_t)c->columns.blocks)));
-    return parts < L2_PARTITIONS ? parts : parts / L2_PARTITIONS * L2_PARTITIONS;
-}
-
 // The row pass of the gap: z_i = x_i . w into the chunks, loss and conjugate partial sums.
 int run_row_pass(chicle_ctx *c, const GapScratch &gs)
 {
@@ -1028,7 +1024,7 @@ int run_row_pass(chicle_ctx *c, const GapScratch &gs)
         c->gap_hot_grid = gx;
     }
     if (c->columns.blocks > 0) {
-        const int parts = dot_parts(c);
+        const int parts = dot_parts(c->n_total, c->entries_loaded);
         const int per_row = parts <= 8 ? 1 : parts <= 64 ? 4 : 16;
         gx = std::max(1, std::min((max_rows * per_row + 255) / 256, std::min(gs.parts, 2048) / c->n_chunks));
         dim3 fg;
@@ -1115,9 +1111,27 @@ int renumber_columns(chicle_ctx *c)
     return CHICLE_OK;
 }
 
-// Makes that copy, once, when every chunk is in HBM and the columns have their numbers.
+// Where that copy begins: it takes the end of the room for the block solver's layout, which is sized for data whose every entry is
+// shared and for a table of all unshared ones beside.  Of these two few data sets need much of both.  (An arena without a place of
+// its own for the copy is a fifth smaller.)
+size_t copy_at(const chicle_ctx *c)
+{
+    return c->layout_bytes - align_up(sizeof(ColumnEntry) * (size_t)c->entries_loaded);      // (the room is twice the copy and more)
+}
+
+// What the solvers of the current assignment keep in front of it.
+size_t layout_in_use(const chicle_ctx *c)
+{
+    if (batched_eligible(c))
+        return (size_t)((char *)c->tiles[1] - c->layout_dev) + align_up(tile_bytes(false) * (size_t)c->max_tiles) +
+               (c->pair_list[0] ? 2 * pair_set_bytes(c->max_tiles) : 0);
+    return c->blocks_ready ? c->layout_used : 0;
+}
+
+// Makes that copy, when every chunk is in HBM and the columns have their numbers; it is of the data alone.
 int order_by_column(chicle_ctx *c)
 {
+    ColumnEntry *entries = (ColumnEntry *)(c->layout_dev + copy_at(c));
     const int log2 = co_bucket_log2(c->d), buckets = co_buckets(c->d), blocks = co_blocks(c->n_total);
     const int64_t n = (int64_t)buckets * blocks;
     unsigned long long most = 0, *most_dev = c->co_count_dev + n + 1;
@@ -1131,12 +1145,12 @@ int order_by_column(chicle_ctx *c)
     hipLaunchKernelGGL(co_count, grid, dim3(256), sizeof(int) * words, c->stream, c->chunks_dev, log2, buckets, c->co_count_dev);
     hipLaunchKernelGGL(co_scan, dim3(1), dim3(1024), 0, c->stream, c->co_count_dev, c->co_off_dev, n, buckets, most_dev);
     hipLaunchKernelGGL(co_scatter, grid, dim3(256), sizeof(unsigned long long) * words, c->stream, c->chunks_dev, log2, buckets, c->co_count_dev,
-                       c->co_entries_dev);
-    hipLaunchKernelGGL(co_sort, dim3((unsigned)std::min<int64_t>(n, 65536)), dim3(1024), 0, c->stream, (const long long *)c->co_off_dev, n, log2, c->co_entries_dev);
+                       entries);
+    hipLaunchKernelGGL(co_sort, dim3((unsigned)std::min<int64_t>(n, 65536)), dim3(1024), 0, c->stream, (const long long *)c->co_off_dev, n, log2, entries);
     HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipMemcpyAsync(&most, most_dev, sizeof most, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    c->columns = ColumnOrder{c->co_entries_dev, c->co_off_dev, buckets, log2, blocks, c->n_total};
+    c->columns = ColumnOrder{entries, c->co_off_dev, buckets, log2, blocks, c->n_total};
     c->fullest_bucket = (double)most;
     return CHICLE_OK;
 }
@@ -1225,9 +1239,11 @@ bool blocks_pay(const chicle_ctx *c, const std::vector<SegStat> &stat, int G, do
 
 // The shared entries of the rows, for the solver that takes rows of any length in blocks: the fewest workgroups per solver
 // whose LDS holds every solver's shared columns (more than one of them must be resident together: they wait for each
-// other).  Where these or the room do not suffice, or it would not be the faster one, the row-wise solver remains.
-int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared, const std::vector<int32_t> &columns)
+// other).  Where these or the room of so many bytes do not suffice (the latter: *too_small), or it would not be the faster one, the
+// row-wise solver remains.
+int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared, const std::vector<int32_t> &columns, size_t layout_bytes, bool *too_small)
 {
+    *too_small = false;
     if (few_rows(c)) return CHICLE_OK;
     const int K = (int)shared.size();
     const int k_pad = (K + L2_PARTITIONS - 1) / L2_PARTITIONS * L2_PARTITIONS;
@@ -1245,8 +1261,9 @@ int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared, const std:
     for (int k = 0; k < K; ++k) { off[k] = places; places += shared[k]; }
     const size_t tiles = align_up(tile_bytes(true) * (size_t)c->n_tiles), refs = align_up(sizeof(SegRef) * (size_t)G * (size_t)c->n_total),
                  place = align_up(sizeof(int32_t) * (size_t)std::max<int64_t>(places, 1));
-    if (tiles + refs + place + SB_SEG_WORDS * sizeof(int32_t) > c->layout_bytes) return CHICLE_OK;
-    const size_t room = (c->layout_bytes - tiles - refs - place) / (SB_SEG_WORDS * sizeof(int32_t));
+    *too_small = tiles + refs + place + SB_SEG_WORDS * sizeof(int32_t) > layout_bytes;
+    if (*too_small) return CHICLE_OK;
+    const size_t room = (layout_bytes - tiles - refs - place) / (SB_SEG_WORDS * sizeof(int32_t));
     const int capacity = (int)std::min<size_t>(room, (size_t)INT32_MAX);
     c->refs_dev = (SegRef *)(c->layout_dev + tiles);
     c->place_dev = (int32_t *)(c->layout_dev + tiles + refs);
@@ -1269,7 +1286,8 @@ int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared, const std:
     HIP_TRY(c, hipMemcpyAsync(&n, taken, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipMemcpyAsync(stat.data(), c->seg_stat_dev, sizeof(SegStat) * (size_t)K, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (n < 0 || n > capacity) return CHICLE_OK;
+    *too_small = n < 0 || n > capacity;
+    if (*too_small) return CHICLE_OK;
     double crowding = 1.0;
     if (!blocks_pay(c, stat, G, 0.0)) return CHICLE_OK;     // (not even with nothing shared twice)
     if (!blocks_pay(c, stat, G, crowding)) {
@@ -1281,9 +1299,10 @@ int lay_out_blocks(chicle_ctx *c, const std::vector<int32_t> &shared, const std:
     c->blocks_ready = true;
     c->most_columns = *std::max_element(columns.begin(), columns.end());
     c->sources_dev = nullptr;
-    const size_t used = tiles + refs + place + align_up((size_t)SB_SEG_WORDS * sizeof(int32_t) * (size_t)std::max(n, 1));
-    if (used + sizeof(UniqueSource) * (size_t)c->u_used <= c->layout_bytes) {
-        c->sources_dev = (UniqueSource *)(c->layout_dev + used);
+    c->layout_used = tiles + refs + place + align_up((size_t)SB_SEG_WORDS * sizeof(int32_t) * (size_t)std::max(n, 1));
+    if (c->layout_used + sizeof(UniqueSource) * (size_t)c->u_used <= layout_bytes) {
+        c->sources_dev = (UniqueSource *)(c->layout_dev + c->layout_used);
+        c->layout_used += sizeof(UniqueSource) * (size_t)c->u_used;
         HIP_TRY(c, hipMemsetAsync(c->sources_dev, 0xff, sizeof(UniqueSource) * (size_t)c->u_used, c->stream));
         hipLaunchKernelGGL(unique_sources, dim3(grid_for(max_rows, 4, 1024), c->n_chunks), dim3(256), 0, c->stream, c->chunks_dev,
                            c->chunk_owner_dev, c->chunk_first_dev, c->u_off_dev, c->sources_dev);
@@ -1375,12 +1394,11 @@ int chicle_create(chicle_ctx **out, int32_t loss, int64_t n_total, int32_t d, do
     c->progress_dev = (int *)carve(c, sizeof(int) * (size_t)max_solvers);
     c->split_ring_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * (size_t)SPLIT_WORDS * (size_t)max_solvers);
     if (c->long_rows) {
-        c->co_entries_dev = (ColumnEntry *)carve(c, sizeof(ColumnEntry) * (size_t)total_entries);
-        if (char *at = (char *)carve(c, co_scratch_bytes(n_total, d))) {
+        if (char *at = (char *)carve(c, co_scratch_bytes(n_total, total_entries, d))) {
             c->co_off_dev = (long long *)at;
             c->co_count_dev = (unsigned long long *)(at += co_offsets_bytes(n_total, d));
             c->co_z_dev = (double *)(at += co_offsets_bytes(n_total, d));
-            c->co_coef_dev = (float *)(at += co_parts_bytes(n_total));
+            c->co_coef_dev = (float *)(at += co_parts_bytes(n_total, total_entries));
         }
         c->row_split_dev = (int32_t *)carve(c, sizeof(int32_t) * (size_t)SPLITS_PER_ROW * (size_t)n_total);
         c->cluster_ring_dev = (unsigned long long *)carve(c, sizeof(unsigned long long) * (size_t)CLUSTER_WORDS * (size_t)max_solvers);
@@ -1733,8 +1751,17 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
                            c->pref_dev, c->words, (const unsigned *)multi);
         HIP_TRY(c, hipGetLastError());
         if (multi) {
-            const int rc = lay_out_blocks(c, shared, cnt);
+            // Long rows: in front of the copy of the entries by column.  Where that leaves too little (rows of some 350 entries and
+            // more, nearly all of them in columns that two rows of the solver hold), there is no copy under this assignment: the
+            // gap goes over the rows, the merge through the private vectors.
+            bool too_small;
+            int rc = lay_out_blocks(c, shared, cnt, c->long_rows ? copy_at(c) : c->layout_bytes, &too_small);
             if (rc) return rc;
+            if (too_small && c->long_rows) {
+                c->columns.blocks = 0;
+                rc = lay_out_blocks(c, shared, cnt, c->layout_bytes, &too_small);
+                if (rc) return rc;
+            }
         }
         if (forced > 0) {
             int max_rows = 1;
@@ -1756,7 +1783,8 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
             HIP_TRY(c, hipGetLastError());
             c->split_built_for = c->cluster;
         }
-        if (c->columns.blocks == 0) {
+        if (layout_in_use(c) > copy_at(c)) c->columns.blocks = 0;
+        else if (c->columns.blocks == 0) {
             const int rc = order_by_column(c);
             if (rc) return rc;
         }
@@ -2242,7 +2270,7 @@ int chicle_debug_passes(chicle_ctx *c, int32_t *out)
     const bool by_column = c->columns.blocks > 0;
     out[0] = by_column;
     out[1] = by_column && c->merge_by_columns;
-    out[2] = by_column ? dot_parts(c) : 0;
+    out[2] = by_column ? dot_parts(c->n_total, c->entries_loaded) : 0;
     out[3] = 0;
     if (by_column) {
         unsigned with_work = 0;

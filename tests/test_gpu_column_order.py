@@ -121,3 +121,88 @@ def test_merge_goes_the_cheaper_way(oracle_mod, n, length, d, K, by_column):
         print("round %d w %.2e" % (k, err), flush=True)
         assert err <= 1e-6                            # (as above)
     r.close()
+
+
+def _uniform(n, length, d, loss, chunks, seed):
+    from workloads.generate import Problem
+    g = np.random.default_rng(seed)
+    col = (np.sort(g.integers(0, d - length, (n, length)), axis=1) + np.arange(length)).astype(np.int32).reshape(-1)
+    val = (g.standard_normal(n * length) / np.sqrt(length)).astype(np.float32)
+    y = (g.standard_normal(n) if loss == "squared" else np.where(g.random(n) < 0.5, -1, 1)).astype(np.float32)
+    return Problem("room", loss, n, d, 3.0 / n, y, np.linspace(0, n, chunks + 1).astype(np.int64), row_ptr=np.arange(n + 1, dtype=np.int64) * length,
+                   col=col, val=val), g
+
+
+def test_updates_without_the_table_of_unshared_entries(oracle_mod):
+    """Many shared entries: with the copy there is no room for the table that a solver's update is spread from.  Rows are gone through
+    instead, also those that take no step, whose places in the private vectors hold what the merge before took over the columns."""
+    import paper_1909_04885_amd as binding
+    K = 4
+    p, g = _uniform(3000, 400, 300007, "hinge", 2 * K, 11)
+    print("\ncase updates row by row", flush=True)
+    r = binding.ChicleRound.from_problem(p, max_solvers=K)
+    o = oracle_mod.OracleCoCoA.from_problem(p)
+    table = (np.arange(2 * K) % K).astype(np.int32)
+    r.assign(K, table)
+    o.assign(K, table)
+    assert r.debug_solver()[0] == "blocks" and r.debug_solver()[3] and r.debug_passes()[:2] == (True, True)
+    still = 0
+    for k in range(5):
+        perms = [g.permutation(m).astype(np.int32) for m in o.rows_per_solver()]
+        before, floor = o.alpha.copy(), dw_floor(float(np.linalg.norm(o.w)))
+        r.local_epoch(r.upload_perm(perms))
+        dws = o.local_epoch(perms)
+        still += int((o.alpha == before).sum())
+        if k != 1:
+            for s in range(K):
+                err = rel_l2(r.get_delta_w(s), dws[s], floor)
+                assert err <= TOL_DW, (k, s, err)
+        o.aggregate()
+        r.aggregate()
+        assert rel_l2(r.get_w(), o.w, 1e-30) <= 1e-6
+        P, _, G = r.gap()
+        Po, _, Go = o.gap()[:3]
+        assert abs(P - Po) <= 1e-6 * abs(Po) and abs(G - Go) <= gap_tolerance(Go, Po)
+    print("steps of zero: %d" % still, flush=True)
+    assert still > 100
+    r.close()
+
+
+@pytest.mark.parametrize("loss", ["hinge", "logistic"])
+def test_copy_gives_way_to_the_layout_and_comes_back(oracle_mod, loss):
+    """Every column in two rows of the one solver: the block solver's layout takes the copy's place.  With two solvers half of the entries
+    are shared, and the copy is made again."""
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    n, q = 800, 300
+    m, d = 2 * q, n * q
+    print("\ncase copy gives way %s" % loss, flush=True)
+    g = np.random.default_rng(12)
+    i, k = np.arange(n)[:, None], np.arange(q)[None, :]
+    col = np.sort(np.concatenate([k * n + i, k * n + (i - 1 - k) % n], axis=1), axis=1).astype(np.int32)
+    assert (np.diff(col, axis=1) > 0).all() and (np.bincount(col.reshape(-1), minlength=d) == 2).all()
+    val = (g.standard_normal(n * m) / np.sqrt(m)).astype(np.float32)
+    y = np.where(g.random(n) < 0.5, -1, 1).astype(np.float32)
+    p = Problem("room", loss, n, d, 3.0 / n, y, np.linspace(0, n, 7).astype(np.int64), row_ptr=np.arange(n + 1, dtype=np.int64) * m,
+                col=col.reshape(-1), val=val)
+    r = binding.ChicleRound.from_problem(p, max_solvers=2)
+    o = oracle_mod.OracleCoCoA.from_problem(p)
+    for K, copy in ((1, False), (2, True), (1, False)):
+        table = (np.arange(6) % K).astype(np.int32)
+        r.assign(K, table)
+        o.assign(K, table)
+        assert r.debug_solver()[0] == "blocks" and r.debug_passes()[0] == copy, (K, r.debug_solver(), r.debug_passes())
+        for k in range(2):
+            perms = [g.permutation(x).astype(np.int32) for x in o.rows_per_solver()]
+            floor = dw_floor(float(np.linalg.norm(o.w)))
+            r.local_epoch(r.upload_perm(perms))
+            dws = o.local_epoch(perms)
+            for s in range(K):
+                assert rel_l2(r.get_delta_w(s), dws[s], floor) <= TOL_DW, (K, k, s)
+            o.aggregate()
+            r.aggregate()
+            assert rel_l2(r.get_w(), o.w, 1e-30) <= 1e-6
+            P, _, G = r.gap()
+            Po, _, Go = o.gap()[:3]
+            assert abs(P - Po) <= 1e-6 * abs(Po) and abs(G - Go) <= gap_tolerance(Go, Po)
+    r.close()

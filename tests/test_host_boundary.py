@@ -141,3 +141,12 @@ def test_stored_traffic_is_tied_to_the_kernel_sources(tmp_path, monkeypatch):
     rec["source_sha256"] = "0" * 64                             # measured on other sources
     f.write_text(__import__("json").dumps(rec))
     assert rt.stored_traffic("w/full") is None
+
+
+def test_arena_of_long_rows_has_no_room_apart_for_the_entries_by_column(lib):
+    """An entry costs the matrix (8), its index in the private vectors (4), at most a float there and sixteen bytes of room for the block
+    solver's layout, which the copy by column shares; the parts of the dot products stop growing at 256."""
+    for n, d, solvers in ((16384, 2000000, 8), (100000, 20000000, 64), (600000, 2000000, 64), (3000000, 50000000, 16)):
+        base = 2000 * n                              # (past what the parts grow with)
+        more = lib.chicle_arena_bytes(n, base + 10 ** 7, d, 100, solvers, 0) - lib.chicle_arena_bytes(n, base, d, 100, solvers, 0)
+        assert more <= 32 * 10 ** 7 + 4096, (n, d, solvers, more)
