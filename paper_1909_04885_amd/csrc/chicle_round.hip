@@ -187,7 +187,7 @@ struct chicle_ctx {
     double fullest_bucket = 0.0;      // entries of the bucket that has most, over all blocks of rows
     bool merge_by_columns = false;    // ... is what the merge reads after a pass of the block solver (merge_pays)
     bool coef_pending = false;        // such a pass has left its updates there: private vectors lack the unshared columns
-    bool private_stale = false;       // private vectors hold what has been merged from there
+    bool private_stale = false;       // private vectors hold what has been merged from there, or what a failed pass has left
     bool cluster_allowed = true;
     // sparse rows longer than the batched solver takes: blocks over the columns that several rows of a solver hold
     bool blocks_ready = false;        // laid out for the current assignment
@@ -624,10 +624,6 @@ int launch_rowwise(chicle_ctx *c, const int32_t *perm)
 {
     const RoundScalars sc = scalars(c);
     const size_t list_bytes = 2 * sizeof(int) * (size_t)std::max(c->max_list, 1);
-    if (c->private_stale) {                          // (its passes start from zero)
-        clear_device_words(c, c->u, c->u_used);
-        c->private_stale = false;
-    }
     if (c->dense) {
         const bool v_lds = c->d <= DENSE_V_LDS_MAX_D;
         const size_t sh = list_bytes + (v_lds ? sizeof(float) * (size_t)c->d : 0);
@@ -919,10 +915,10 @@ int launch_blocks(chicle_ctx *c, const int32_t *perm)
     HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
     seg_begin(c, CHICLE_SEG_EPOCH_CHAIN);
     hipLaunchKernelGGL(kern, dim3(c->blocks_g * k_pad), dim3(SB_THREADS), sh, c->stream, A);
-    c->coef_pending = c->merge_by_columns;
     if (!c->merge_by_columns) spread_updates(c);
     seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
     HIP_TRY(c, hipGetLastError());
+    c->coef_pending = c->merge_by_columns;
     return CHICLE_OK;
 }
 
@@ -1867,6 +1863,13 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
     if (route == ROUTE_DENSE && !dense_tiles_ahead(c)) perm_next_device = nullptr;      // (they are kept all the same)
     seg_begin(c, CHICLE_SEG_LOCAL_EPOCH);
     int rc = CHICLE_OK;
+    c->coef_pending = false;
+    if (c->private_stale && route != ROUTE_BLOCKS) {            // (all others start from zero)
+        if (c->compact) clear_device_words(c, c->u, c->u_used);
+        else rc = clear_all_private(c);
+        if (rc) return rc;
+        c->private_stale = false;
+    }
     if (!c->zw_valid) rc = run_row_pass(c, c->gap_scratch);     // x_i . w for the current w
     if (rc == CHICLE_OK) {
         if (batched) {
@@ -1886,7 +1889,10 @@ int chicle_local_epoch_ahead(chicle_ctx *c, const int32_t *perm_device, const in
         }
     }
     seg_end(c, CHICLE_SEG_LOCAL_EPOCH);
-    if (rc) return rc;
+    if (rc) {
+        c->private_stale = true;
+        return rc;
+    }
     c->state = ST_EPOCH_DONE;
     c->epoch_ran = true;
     return CHICLE_OK;
@@ -1922,8 +1928,6 @@ int chicle_aggregate(chicle_ctx *c)
         HIP_TRY(c, hipFuncSetAttribute((const void *)column_merge, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
         hipLaunchKernelGGL(column_merge, dim3((unsigned)c->columns.buckets), dim3(CO_THREADS), sh, c->stream, c->columns, (const float *)c->co_coef_dev, c->w64,
                            c->w, (int64_t)c->d, (float)(1.0 / (double)c->K), c->l1);
-        c->coef_pending = false;
-        c->private_stale = true;
     } else if (c->compact) {
         // few words: the solvers are divided over slices too, so that the chip is filled.  Thinly occupied vectors (under an
         // eighth of the columns per solver on average): entries are picked straight from memory
@@ -1945,6 +1949,8 @@ int chicle_aggregate(chicle_ctx *c)
                            c->u, c->ld_v, d4, c->K, (float)(1.0 / (double)c->K), c->l1);
     seg_end(c, CHICLE_SEG_AGGREGATE);
     HIP_TRY(c, hipGetLastError());
+    c->private_stale = c->coef_pending;      // (the other merges clear the private vectors)
+    c->coef_pending = false;
     c->zw_valid = false;
     c->state = ST_READY;
     return CHICLE_OK;
@@ -2110,7 +2116,10 @@ int chicle_get_delta_w(chicle_ctx *c, int32_t solver, float *dw_out)
     if (!c || !dw_out) return CHICLE_EINVAL;
     if (c->state != ST_EPOCH_DONE) return fail(c, CHICLE_ESTATE, "updates exist only between local_epoch and aggregate");
     if (solver < -1 || solver >= c->K) return fail(c, CHICLE_EINVAL, "solver %d, K=%d", solver, c->K);
-    if (c->coef_pending) spread_updates(c);
+    if (c->coef_pending) {
+        spread_updates(c);
+        HIP_TRY(c, hipGetLastError());
+    }
     if (c->compact)
         hipLaunchKernelGGL(delta_w_out_compact, dim3(grid_for(c->d, 256, 4096)), dim3(256), 0, c->stream, c->u, c->u_off_dev,
                            c->bits_dev, c->pref_dev, c->words, (int64_t)c->d, c->K, solver, (float)(1.0 / (double)c->K), c->tmp_a);
