@@ -123,58 +123,20 @@ __device__ __forceinline__ void chain_block(BatchedShared &sh, int i, int lane, 
     steps[lane] = clamp_step<LOSS>(t, lo, hi);
     x_carry = fmaf(s, xc, x);
 }
-// The same with the coefficients read four steps at a time, for the kernel whose wavefronts have no registers to spare.
-template <int LOSS>
-__device__ __forceinline__ void chain_block_small(BatchedShared &sh, int i, int lane, float &x_carry, bool &rough, float inv_c, float *steps)
-{
-    const int buf = i & 1;
-    float t = sh.t0[buf][lane] + x_carry;
-    const float lo = sh.lo[buf][lane], hi = sh.hi[buf][lane];
-    float x = 0.f;
-#pragma unroll
-    for (int jq = 0; jq < BATCH / 4; ++jq) {
-        const float4_v T = sh.Tw[buf][jq][lane], X = sh.Tx[buf][jq][lane];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float d = clamp_step<LOSS>(t, lo, hi);
-            const float s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), 4 * jq + e));
-            t = fmaf(s, T[e], t);
-            x = fmaf(s, X[e], x);
-        }
-    }
-    steps[lane] = clamp_step<LOSS>(t, lo, hi);
-    x_carry = x;
-}
-
 // The same for the logistic loss, whose step has no closed form: lane i owns m_i = -y_i z_i and
 //     m_i += delta_j T_ij,   T_ij = -y_i y_j G_ij / c
 // (logistic_block; the helpers leave m at the start of the block in slot t0 and the root for it in slot lo).
-template <typename F>
-__device__ __forceinline__ void chain_block_logistic(BatchedShared &sh, int i, int lane, float &x_carry, float inv_c, float *steps, F block)
+template <>
+__device__ __forceinline__ void chain_block<2>(BatchedShared &sh, int i, int lane, float &x_carry, bool &rough, float inv_c, float *steps)
 {
     const int buf = i & 1;
     const RowSlot &row = sh.rows[i & (RING - 1)][lane];
     const float a = row.alpha, r = row.len > 0 ? row.q * inv_c : 0.f;      // r = 0 marks a row to skip
     float x = 0.f;
-    steps[lane] = block(sh.t0[buf][lane] + x_carry, a, r, sh.lo[buf][lane], [&](int jq) { return sh.Tw[buf][jq][lane]; },
-                        [&](int jq) { return sh.Tx[buf][jq][lane]; }, x);
+    steps[lane] = logistic_block<BATCH, true>(
+        sh.t0[buf][lane] + x_carry, a, r, sh.lo[buf][lane], lane, [&](int jq) { return sh.Tw[buf][jq][lane]; },
+        [&](int jq) { return sh.Tx[buf][jq][lane]; }, x, rough);
     x_carry = x;
-}
-
-template <>
-__device__ __forceinline__ void chain_block<2>(BatchedShared &sh, int i, int lane, float &x_carry, bool &rough, float inv_c, float *steps)
-{
-    chain_block_logistic(sh, i, lane, x_carry, inv_c, steps, [&](float m, float a, float r, float root, auto coef4, auto cross4, float &x) __attribute__((always_inline)) {
-        return logistic_block<BATCH, true>(m, a, r, root, lane, coef4, cross4, x, rough);
-    });
-}
-
-template <>
-__device__ __forceinline__ void chain_block_small<2>(BatchedShared &sh, int i, int lane, float &x_carry, bool &rough, float inv_c, float *steps)
-{
-    chain_block_logistic(sh, i, lane, x_carry, inv_c, steps, [&](float m, float a, float r, float root, auto coef4, auto cross4, float &x) __attribute__((always_inline)) {
-        return logistic_steps<BATCH, LOGISTIC_ROUGH, true>(m, a, r, root, lane, coef4, cross4, x, rough);
-    });
 }
 
 // One workgroup per solver: wavefront 0 runs the chain, eight wavefronts gather and scatter, two
@@ -254,44 +216,37 @@ __global__ __launch_bounds__(BATCHED_THREADS) void sdca_batched_csr(
     const int32_t *pk = perm + S.perm_off;
     const float *my_tiles = tiles + (int64_t)S.tile_begin * TILE_FLOATS;
     const int nb = (S.n_rows + BATCH - 1) / BATCH;
-    // roles: wavefront 0 runs the chain, 1..8 gather and scatter, 9..10 resolve rows and stage tiles
-    const bool is_chain = tid < 64;
-    const bool is_service = tid >= 64 + BATCH * LPR;
     const int lane = tid & 63;
-    const int hl = tid - 64, rho = hl / LPR, sub = hl & (LPR - 1);     // helper coordinates
-    const int sw = (tid - 64 - BATCH * LPR) >> 6;                     // service wavefront 0 or 1
-
-    // service pipeline registers (wavefront 9: one lane per row of a block)
-    int p_cur = -1;                                  // visiting-order entry read last iteration
-    int m_ci = -1, m_r = 0;                          // row being resolved: loads in flight
-    int2_a4 m_rp = {0, 0};
-    float4_v m_st = {0.f, 0.f, 0.f, 0.f};          // kept whole until it is used (y, alpha, q, rw)
-    // Entries of a row segment (ENT consecutive entries per helper lane) travel through four stages:
-    // in (loads in flight) -> g (gathered this iteration) -> c (its block is in the chain) -> s (scattered).
-    int in_c[ENT], g_c[ENT], c_c[ENT], s_c[ENT];
-    float in_v[ENT], g_v[ENT], c_v[ENT], s_v[ENT];
-#pragma unroll
-    for (int e = 0; e < ENT; ++e) {
-        in_c[e] = g_c[e] = c_c[e] = s_c[e] = 0;
-        in_v[e] = g_v[e] = c_v[e] = s_v[e] = 0.f;
-    }
-    int in_len = 0;
-    float x_carry = 0.f;
-    bool rough = true;
-    int hb_target = 0;
-    float4 stage[16];                                // service wavefronts: tile part fetched ahead
-    bool staged = false;
     if (nb == 0) {                                   // a solver without rows (uniform for the workgroup)
         stamp_solver(sc, sid, 1);
         return;
     }
-
-    for (int i = -5; i <= nb; ++i) {
-        if (tid == BATCHED_THREADS - 1 && i > 0)
-            __hip_atomic_store(progress + sid, i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (is_chain) {
-            if (i >= 0 && i < nb) chain_block_small<LOSS>(sh, i, lane, x_carry, rough, sc.inv_c, sh.delta[i & 1]);
-        } else if (is_service) {
+    // Roles: wavefront 0 runs the chain, 1..8 gather and scatter, 9..10 resolve rows and stage tiles.  Each has a loop of its own, with
+    // one workgroup barrier per iteration in all of them: what one role keeps from block to block takes no register in the others.
+    // (In one loop the logistic chain kept 41 registers in scratch memory and took its steps in short groups throughout.  Rounds, before
+    // and now: 100 solvers of 3000 rows of 40 entries, logistic 669 and 573 us on a run that continues, 933 and 922 from alpha = 0, hinge
+    // 512 and 508; 300 of 200 rows of 20, logistic 164 and 143, 245 and 227; 200 of 4000 of 30, logistic 1375 and 1197, 1754 and 1728.)
+#define BATCHED_ITERATIONS for (int i = -5; i <= nb; ++i)
+    if (tid < 64) {
+        float x_carry = 0.f;
+        bool rough = true;                           // see logistic_block
+        BATCHED_ITERATIONS {
+            if (i >= 0 && i < nb) chain_block<LOSS>(sh, i, lane, x_carry, rough, sc.inv_c, sh.delta[i & 1]);
+            __syncthreads();
+        }
+    } else if (tid >= 64 + BATCH * LPR) {
+        const int sw = (tid - 64 - BATCH * LPR) >> 6;                  // service wavefront 0 or 1
+        // pipeline registers (wavefront 9: one lane per row of a block)
+        int p_cur = -1;                              // visiting-order entry read last iteration
+        int m_ci = -1, m_r = 0;                      // row being resolved: loads in flight
+        int2_a4 m_rp = {0, 0};
+        float4_v m_st = {0.f, 0.f, 0.f, 0.f};        // kept whole until it is used (y, alpha, q, rw)
+        float4 stage[16];                            // tile part fetched ahead
+        bool staged = false;
+        int hb_target = 0;
+        BATCHED_ITERATIONS {
+            if (tid == BATCHED_THREADS - 1 && i > 0)
+                __hip_atomic_store(progress + sid, i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // tiles for iteration i + 1 (wavefront 9: own part of T(i+1), wavefront 10: cross part of
             // T(i+2), 16 KB each) were fetched into registers during the last iteration
             {
@@ -346,7 +301,21 @@ __global__ __launch_bounds__(BATCHED_THREADS) void sdca_batched_csr(
                     for (int j = 0; j < 16; ++j) stage[j] = src[lane + 64 * j];
                 }
             }
-        } else {
+            __syncthreads();
+        }
+    } else {
+        const int hl = tid - 64, rho = hl / LPR, sub = hl & (LPR - 1);
+        // Entries of a row segment (ENT consecutive entries per helper lane) travel through four stages:
+        // in (loads in flight) -> g (gathered this iteration) -> c (its block is in the chain) -> s (scattered).
+        int in_c[ENT], g_c[ENT], c_c[ENT], s_c[ENT];
+        float in_v[ENT], g_v[ENT], c_v[ENT], s_v[ENT];
+#pragma unroll
+        for (int e = 0; e < ENT; ++e) {
+            in_c[e] = g_c[e] = c_c[e] = s_c[e] = 0;
+            in_v[e] = g_v[e] = c_v[e] = s_v[e] = 0.f;
+        }
+        int in_len = 0, hb_target = 0;
+        BATCHED_ITERATIONS {
             // 4. fetch this lane's segment of the row of block i + 2 (unconditional vector loads; the
             //    entries beyond the row's length are masked when the set moves on)
             if (i + 2 >= 0 && i + 2 < nb) {
@@ -434,9 +403,10 @@ __global__ __launch_bounds__(BATCHED_THREADS) void sdca_batched_csr(
                 g_c[e] = live ? in_c[e] : 0;
                 g_v[e] = live ? in_v[e] : 0.f;
             }
+            __syncthreads();
         }
-        __syncthreads();
     }
+#undef BATCHED_ITERATIONS
     for (int i = tid; i < n_hot; i += BATCHED_THREADS) u[i] = (float)hot[i];
     stamp_solver(sc, sid, 1);
 }

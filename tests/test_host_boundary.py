@@ -150,3 +150,32 @@ def test_arena_of_long_rows_has_no_room_apart_for_the_entries_by_column(lib):
         base = 2000 * n                              # (past what the parts grow with)
         more = lib.chicle_arena_bytes(n, base + 10 ** 7, d, 100, solvers, 0) - lib.chicle_arena_bytes(n, base, d, 100, solvers, 0)
         assert more <= 32 * 10 ** 7 + 4096, (n, d, solvers, more)
+
+
+def test_no_kernel_keeps_registers_in_scratch_memory(lib):
+    """The kernels' metadata in the library that was built here: one whose registers do not suffice goes to memory in its inner loops."""
+    import struct
+    import msgpack
+    from paper_1909_04885_amd.binding import library_path
+    data = open(library_path(), "rb").read()
+    at = data.index(b"__CLANG_OFFLOAD_BUNDLE__")
+    count, pos, elf = struct.unpack_from("<Q", data, at + 24)[0], at + 32, None
+    for _ in range(count):
+        offset, size, name = struct.unpack_from("<3Q", data, pos)
+        if b"gfx950" in data[pos + 24:pos + 24 + name]:
+            elf = data[at + offset:at + offset + size]
+        pos += 24 + name
+    assert elf[:4] == b"\x7fELF"
+    sections, entry, number = struct.unpack_from("<Q", elf, 40)[0], *struct.unpack_from("<2H", elf, 58)
+    kernels = []
+    for i in range(number):
+        kind, offset, size = struct.unpack_from("<I", elf, sections + i * entry + 4)[0], *struct.unpack_from("<2Q", elf, sections + i * entry + 24)
+        while kind == 7 and size > 0:                # notes: length of the name, of what follows it, type
+            name, desc, what = struct.unpack_from("<3I", elf, offset)
+            start = offset + 12 + (name + 3) // 4 * 4
+            if what == 32 and elf[offset + 12:offset + 18] == b"AMDGPU":
+                kernels += msgpack.unpackb(elf[start:start + desc])["amdhsa.kernels"]
+            size -= start + (desc + 3) // 4 * 4 - offset
+            offset = start + (desc + 3) // 4 * 4
+    assert len(kernels) > 50
+    assert [k[".name"] for k in kernels if k[".private_segment_fixed_size"] > 0] == []
