@@ -481,8 +481,8 @@ struct KeptRow {
 };
 
 // Grid: see GapEnd.  Every group of LPR lanes walks rows of its chunk with a fixed stride and keeps two rows in flight.
-// Partial sums are indexed by the workgroup.
-template <int LOSS, int LPR, typename WT>
+// Partial sums are indexed by the workgroup.  ZT: what dot products are summed in.
+template <int LOSS, int LPR, typename WT, typename ZT = WT>
 __global__ __launch_bounds__(256) void gap_rows_csr(const ChunkDev *__restrict__ chunks,
                                                     const WT *__restrict__ w, double l1,
                                                     double *part_loss, double *part_conj, GapEnd E)
@@ -498,22 +498,22 @@ __global__ __launch_bounds__(256) void gap_rows_csr(const ChunkDev *__restrict__
     const float *__restrict__ val = ch.val;
     const int stride = E.per_chunk * GROUPS;
     double s_loss = 0.0, s_conj = 0.0;
-    KeptRow<WT> kept;
+    KeptRow<ZT> kept;
     int at = 0;                                  // the lane of the group that keeps the next row
     for (int r0 = gap_slot(E) * GROUPS + grp; r0 < n_rows; r0 += 2 * stride) {
         const int r1 = r0 + stride;
         const bool two = r1 < n_rows;
         const int b0 = rp[r0], e0 = rp[r0 + 1];
         const int b1 = two ? rp[r1] : 0, e1 = two ? rp[r1 + 1] : 0;
-        WT z0 = 0, z1 = 0;
+        ZT z0 = 0, z1 = 0;
         int p0 = b0 + sub, p1 = b1 + sub;
         while (p0 < e0 || p1 < e1) {           // both rows advance together: their loads overlap
             int c0 = 0, c1 = 0;
             float v0 = 0.f, v1 = 0.f;
             if (p0 < e0) { c0 = col[p0]; v0 = val[p0]; }
             if (p1 < e1) { c1 = col[p1]; v1 = val[p1]; }
-            z0 += (WT)v0 * shared_at(w, c0, l1);
-            z1 += (WT)v1 * shared_at(w, c1, l1);
+            z0 += (ZT)v0 * (ZT)shared_at(w, c0, l1);
+            z1 += (ZT)v1 * (ZT)shared_at(w, c1, l1);
             p0 += LPR; p1 += LPR;
         }
 #pragma unroll

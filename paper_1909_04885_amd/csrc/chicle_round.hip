@@ -184,6 +184,7 @@ struct chicle_ctx {
     unsigned long long *co_count_dev = nullptr;
     double *co_z_dev = nullptr;       // co_parts x n_total shares of the rows' dot products
     float *co_coef_dev = nullptr;     // per row: its coefficient in the solvers' updates of the last pass
+    bool dots_by_columns = false;     // the rows' dot products go over it (dots_pay)
     double fullest_bucket = 0.0;      // entries of the bucket that has most, over all blocks of rows
     bool merge_by_columns = false;    // ... is what the merge reads after a pass of the block solver (merge_pays)
     bool coef_pending = false;        // such a pass has left its updates there: private vectors lack the unshared columns
@@ -316,10 +317,12 @@ int co_parts(int64_t n_total)
         if (rounds(parts) * best < rounds(best) * parts) best = parts;
     return best;
 }
-// ... for so many entries: parts of some 4096 entries or more.
+// ... for so many entries: parts of some 4096 entries or more, and of two entries or more for each of the block's rows, whose sums a
+// part writes out (16000 rows of 115, 256 parts 29 us, 128 25.6, 64 24.2; 4000 of 314, 256 19, 128 16.9, 64 19.4).
 int dot_parts(int64_t n_total, int64_t entries)
 {
-    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(co_parts(n_total), entries / (4096 * (int64_t)co_blocks(n_total))));
+    const int64_t most = std::min(entries / (4096 * (int64_t)co_blocks(n_total)), entries / (2 * n_total));
+    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(co_parts(n_total), most));
     return parts < L2_PARTITIONS ? parts : parts / L2_PARTITIONS * L2_PARTITIONS;
 }
 // Where buckets begin, what counts them, the parts of the dot products and the coefficients, in whole megabytes.  (The entries
@@ -971,6 +974,9 @@ void launch_gap_rows_t(chicle_ctx *c, int grid_x, const WT *w, const GapScratch 
     } else if (c->dense)
         hipLaunchKernelGGL((gap_rows_dense<LOSS, LPRG, WT>), grid, dim3(256), 0, c->stream, c->chunks_dev,
                            (int)c->d, dense_ld((int)c->d), w, c->l1, gs.loss, gs.conj, E);
+    else if (LPRG == 64 && c->long_rows)             // (summed in double, as over the entries by column)
+        hipLaunchKernelGGL((gap_rows_csr<LOSS, 64, WT, double>), grid, dim3(256), 0, c->stream, c->chunks_dev, w, c->l1,
+                           gs.loss, gs.conj, E);
     else
         hipLaunchKernelGGL((gap_rows_csr<LOSS, LPRG, WT>), grid, dim3(256), 0, c->stream, c->chunks_dev, w, c->l1,
                            gs.loss, gs.conj, E);
@@ -1019,7 +1025,7 @@ int run_row_pass(chicle_ctx *c, const GapScratch &gs)
                                   gs.parts / c->n_chunks));
         c->gap_hot_grid = gx;
     }
-    if (c->columns.blocks > 0) {
+    if (c->dots_by_columns) {
         const int parts = dot_parts(c->n_total, c->entries_loaded);
         const int per_row = parts <= 8 ? 1 : parts <= 64 ? 4 : 16;
         gx = std::max(1, std::min((max_rows * per_row + 255) / 256, std::min(gs.parts, 2048) / c->n_chunks));
@@ -1168,6 +1174,25 @@ bool merge_pays(const chicle_ctx *c)
     const double d = 1e-6 * (double)c->d, entries = 1e-6 * (double)c->entries_loaded, columns = 1e-6 * (double)c->u_used;
     const double saved = 16.0 + 0.09 * d * c->K + 12.6 * columns + (c->sources_dev ? 0.0 : 10.0 * entries);
     return saved > 9.3 * entries + 0.73 * d + 0.0064 * (double)c->columns.buckets * (double)c->columns.blocks;
+}
+
+// Whether the rows' dot products go over the entries by column, and not row by row.  The former is two kernels, one of which writes
+// and one of which reads a double per row and part; the latter is slower per entry the larger the shared vector is, most of all where
+// an L2 partition does not hold it, or the matrix outgrows the L2s, and as slow as its longest rows.  Microseconds, fitted to 82 shapes
+// of 1000 to 200000 rows of 115 to 1046 entries, 5000 to 20M columns, hinge and squared loss; the way that used to be is kept where
+// the two are close.  By column / by row: 1000 rows of 115 over 20000 columns 15.1 / 10.1, 16000 24.2 / 17.7, 50000 30 / 36, over
+// 2M 36 / 79; 1000 of 314 over 0.1M 14.8 / 14.0, over 2M 18.3 / 21.6; 16000 over 5000 31 / 23, over 0.1M 30 / 34, over 2M 35 / 58;
+// 16000 of 1046 over 20M 115 / 327; 50000 of them over 5000 114 / 144, over 0.4M 121 / 389; logistic, 2500 of 490 over 30000 19 / 26,
+// 60000 of 120 over 10000 34 / 50.
+bool dots_pay(const chicle_ctx *c)
+{
+    const double n = (double)c->n_total, entries = 1e-6 * (double)c->entries_loaded, d = (double)c->d, blocks = co_blocks(c->n_total);
+    const double parts = dot_parts(c->n_total, c->entries_loaded);
+    const double per_entry = 2.5 + 0.6 * std::log2(std::max(1.0, d / 4096)) + 1.6 * std::log2(std::max(1.0, d / 524288));
+    const double by_row = (c->loss == CHICLE_LOSS_LOGISTIC ? 12.0 : 9.0) + per_entry * (entries + 0.004 * (double)c->entries_loaded / n) +
+                          (c->loss == CHICLE_LOSS_HINGE ? 1.5 : 3.0) * std::max(0.0, entries - 4.0);
+    const double by_column = 18.0 + std::max(1.8 * entries, 97.0 * entries / (parts * blocks)) + 2e-6 * parts * n + 0.4e-6 * d;
+    return by_column < 0.95 * by_row;
 }
 
 // For the average entry, the share of the other rows that hold its column: 64 times this is how many of a block's rows an
@@ -1785,6 +1810,7 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
             if (rc) return rc;
         }
     }
+    c->dots_by_columns = c->columns.blocks > 0 && dots_pay(c);
     c->merge_by_columns = merge_pays(c);
     c->coef_pending = c->private_stale = false;
     return clear_all_private(c);
@@ -2276,9 +2302,9 @@ int chicle_debug_passes(chicle_ctx *c, int32_t *out)
 {
     if (!c || !out) return CHICLE_EINVAL;
     if (c->state == ST_LOADING) return fail(c, CHICLE_ESTATE, "no assignment yet");
-    const bool by_column = c->columns.blocks > 0;
+    const bool by_column = c->dots_by_columns;
     out[0] = by_column;
-    out[1] = by_column && c->merge_by_columns;
+    out[1] = c->merge_by_columns;
     out[2] = by_column ? dot_parts(c->n_total, c->entries_loaded) : 0;
     out[3] = 0;
     if (by_column) {

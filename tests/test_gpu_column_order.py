@@ -1,6 +1,7 @@
 """Long rows: the copy of the entries by column that the gap's row pass and the merge stream over.  Rows on both sides of a block of
 16384, columns in several segments of 262144, a last bucket that is not full, one bucket that holds everything (merged through the
-private vectors), solvers by name in turn, updates read out between pass and merge."""
+private vectors), solvers by name in turn, updates read out between pass and merge; and the same with shorter rows, whose dot products
+are formed row by row."""
 import numpy as np
 import pytest
 
@@ -9,11 +10,17 @@ from harness import TOL_DW, dw_floor, gap_tolerance, rel_l2
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("loss,n,d,length,popular,l1,by_name", [
-    ("hinge", 16400, 600011, 100, 0, 0.0, False), ("squared", 321, 5003, 130, 0, 0.0, True), ("logistic", 500, 300001, 200, 0, 0.0, False),
-    ("hinge", 700, 300001, 150, 900, 0.0, True), ("squared", 40, 20000003, 300, 0, 0.0, False), ("hinge", 321, 262145, 130, 0, 0.02, True),
-    ("squared", 2500, 40009, 400, 0, 0.0, False)])
-def test_passes_by_column(oracle_mod, loss, n, d, length, popular, l1, by_name):
+# (dots, merge: whether these go over the entries by column)
+@pytest.mark.parametrize("loss,n,d,length,popular,l1,by_name,dots,merge", [
+    ("hinge", 16400, 600011, 100, 0, 0.0, False, False, True), ("squared", 321, 5003, 130, 0, 0.0, True, False, True),
+    ("logistic", 500, 300001, 200, 0, 0.0, False, False, True), ("hinge", 700, 300001, 150, 900, 0.0, True, False, False),
+    ("squared", 40, 20000003, 300, 0, 0.0, False, True, False), ("hinge", 321, 262145, 130, 0, 0.02, True, False, True),
+    ("squared", 2500, 40009, 400, 0, 0.0, False, False, True),
+    ("hinge", 16400, 600011, 300, 0, 0.0, False, True, None), ("squared", 500, 5003, 1200, 0, 0.0, True, True, None),
+    ("logistic", 500, 300001, 900, 0, 0.0, False, True, True), ("hinge", 700, 300001, 900, 1000, 0.0, True, True, None),
+    ("squared", 40, 20000003, 3000, 0, 0.0, False, True, False), ("hinge", 321, 262145, 1000, 0, 0.02, True, True, True),
+    ("squared", 2500, 40009, 900, 0, 0.0, False, True, None)])
+def test_passes_by_column(oracle_mod, loss, n, d, length, popular, l1, by_name, dots, merge):
     import torch
     import paper_1909_04885_amd as binding
     from workloads.generate import Problem
@@ -38,6 +45,10 @@ def test_passes_by_column(oracle_mod, loss, n, d, length, popular, l1, by_name):
     table = (np.arange(len(bounds) - 1) % K).astype(np.int32)
     r.assign(K, table)
     o.assign(K, table)
+    # (None: rows that share so much that the solver goes row by row, which the private vectors are merged after)
+    print(r.debug_solver(), r.debug_passes(), flush=True)
+    assert r.debug_passes()[0] == dots
+    assert r.debug_solver()[0] == "rowwise" if merge is None else r.debug_solver()[0] == "blocks" and r.debug_passes()[1] == merge
     for k in range(4):
         if by_name:
             r.set_solver("rowwise" if k == 1 else "auto")
@@ -91,6 +102,31 @@ def test_many_blocks_of_rows_use_the_whole_chip():
     r.close()
 
 
+@pytest.mark.parametrize("n,length,d,loss,by_column", [
+    (1000, 115, 20000, "hinge", False), (16000, 115, 20000, "hinge", False), (16000, 115, 20000, "squared", False), (60000, 115, 10000, "hinge", False),
+    (60000, 115, 10000, "logistic", True), (1500, 370, 200003, "hinge", True), (16000, 115, 4000003, "hinge", True)])
+def test_dot_products_go_the_cheaper_way(n, length, d, loss, by_column):
+    """Short rows over a shared vector that the caches hold, and few rows: row by row.  Both ways sum in double."""
+    import paper_1909_04885_amd as binding
+    print("\ncase dots %s n=%d length=%d d=%d" % (loss, n, length, d), flush=True)
+    p, g = _uniform(n, length, d, loss, 5, 16)
+    r = binding.ChicleRound.from_problem(p, max_solvers=5)
+    r.assign(5, np.arange(5, dtype=np.int32))
+    assert r.debug_passes()[0] == by_column
+    w = g.standard_normal(d).astype(np.float32)
+    r.set_w(w)
+    P = r.gap()[0]
+    w64 = w.astype(np.float64)
+    z = (p.val.astype(np.float64).reshape(n, length) * w64[p.col].reshape(n, length)).sum(axis=1)
+    y = p.y.astype(np.float64)
+    losses = 0.5 * (z - y) ** 2 if loss == "squared" else np.maximum(0, 1 - y * z) if loss == "hinge" else np.logaddexp(0, -y * z)
+    ref = 0.5 * p.lam * (w64 @ w64) + losses.mean()
+    print("primal %.3e" % (abs(P - ref) / ref), flush=True)
+    # w is exact in a float here, products and sums are in double; the terms' log and exp are good to a few units in the last place
+    assert abs(P - ref) <= 2.0 ** -53 * (n + d + length + 8) * ref
+    r.close()
+
+
 @pytest.mark.parametrize("n,length,d,K,by_column", [
     (1500, 250, 200003, 7, True), (3000, 300, 5000011, 16, True), (1000, 110, 30000001, 2, False), (40000, 110, 6000007, 3, False),
     (20000, 250, 40009, 4, False)])
@@ -110,7 +146,7 @@ def test_merge_goes_the_cheaper_way(oracle_mod, n, length, d, K, by_column):
     table = (np.arange(2 * K) % K).astype(np.int32)
     r.assign(K, table)
     o.assign(K, table)
-    assert r.debug_solver()[0] == "blocks" and r.debug_passes()[:2] == (True, by_column)
+    assert r.debug_solver()[0] == "blocks" and r.debug_passes()[1] == by_column
     for k in range(2):
         perms = [g.permutation(m).astype(np.int32) for m in o.rows_per_solver()]
         r.local_epoch(r.upload_perm(perms))
@@ -218,7 +254,7 @@ def test_failed_pass_leaves_nothing_to_the_next(then):
     p, g = _uniform(1500, 250, 200003, "squared", 4, 14)
     r = binding.ChicleRound.from_problem(p, max_solvers=2)
     r.assign(2, np.array([0, 1, 0, 1], dtype=np.int32))
-    assert r.debug_solver()[0] == "blocks" and r.debug_passes()[:2] == (True, True)
+    assert r.debug_solver()[0] == "blocks" and r.debug_passes()[1]
     orders = lambda: r.upload_perm([g.permutation(int(m)).astype(np.int32) for m in r.solver_rows()])
     alphas = lambda: np.concatenate([r.get_alpha(c) for c in range(4)]).astype(np.float64)
     for k in range(2):
