@@ -277,3 +277,36 @@ def test_failed_pass_leaves_nothing_to_the_next(then):
         # w and alpha are read out as floats: their changes carry 2^-24 of the values, which here are no larger than 50 times them
         assert np.linalg.norm(step) > 0.02 * np.linalg.norm(w0) and err <= 1e-5
     r.close()
+
+
+@pytest.mark.parametrize("loss", ["hinge", "squared"])
+def test_more_buckets_than_are_counted_in_lds(loss):
+    """Over 134 million columns: the copy's buckets are counted and filled in memory.  The last column is the last of all buckets."""
+    import paper_1909_04885_amd as binding
+    n, m, d, K = 240, 900, 16384 * 8192 + 70007, 18
+    print("\ncase many buckets %s" % loss, flush=True)
+    p, g = _uniform(n, m, d, loss, 2 * K, 15)
+    p.col[m - 1::m] = d - 1 - np.arange(n) % 3        # (columns that several rows of every solver hold, too)
+    r = binding.ChicleRound.from_problem(p, max_solvers=K)
+    alphas = lambda: np.concatenate([r.get_alpha(c) for c in range(2 * K)]).astype(np.float64)
+    held = np.unique(p.col)
+    for solvers, by_column in ((K, True), (2, False)):
+        r.assign(solvers, (np.arange(2 * K) % solvers).astype(np.int32))
+        assert r.debug_solver()[0] == "blocks" and r.debug_passes()[:2] == (True, by_column)
+        for k in range(2):
+            a0, w0 = alphas(), r.get_w()[held].astype(np.float64)
+            r.local_epoch(r.upload_perm([g.permutation(int(x)).astype(np.int32) for x in r.solver_rows()]))
+            r.aggregate()
+            a, w = alphas(), r.get_w()
+            step = np.zeros(len(held))
+            np.add.at(step, np.searchsorted(held, p.col), np.repeat((a - a0) * (1 if loss == "squared" else p.y) / (p.lam * n), m) * p.val)
+            full, w = np.count_nonzero(w), w[held].astype(np.float64)
+            err = rel_l2(w - w0, step, 1e-30)
+            z = (p.val.astype(np.float64).reshape(n, m) * w[np.searchsorted(held, p.col)].reshape(n, m)).sum(axis=1)
+            losses = 0.5 * (z - p.y) ** 2 if loss == "squared" else np.maximum(0, 1 - p.y * z)
+            P, ref = r.gap()[0], 0.5 * p.lam * (w @ w) + losses.mean()
+            print("K=%d round %d error %.2e primal %.2e, %d columns" % (solvers, k, err, abs(P - ref) / ref, full), flush=True)
+            # w and alpha are read out as floats: their changes carry 2^-24 of the values, which here are no larger than 50 times them
+            assert np.linalg.norm(step) > 0.02 * np.linalg.norm(w0) and err <= 1e-5
+            assert full <= len(held) and abs(P - ref) <= 1e-6 * ref
+    r.close()
