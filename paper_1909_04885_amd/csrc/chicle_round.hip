@@ -178,7 +178,7 @@ struct chicle_ctx {
     unsigned long long *cluster_ring_dev = nullptr;
     int cluster = 1;                  // members per solver under the current assignment
     int split_built_for = 0;          // cluster size row_split_dev was built for
-    // long rows: a copy of the entries by column (column_order.hpp), made at an assignment that leaves room for it (copy_at)
+    // long rows: a copy of the entries by column (column_order.hpp), made at an assignment that has a use and room for it (copy_at)
     ColumnOrder columns{};            // blocks == 0: there is none
     long long *co_off_dev = nullptr;
     unsigned long long *co_count_dev = nullptr;
@@ -1159,21 +1159,21 @@ int order_by_column(chicle_ctx *c)
 
 // Whether the merge takes the updates from the steps' coefficients, over the entries by column, and not from the private vectors,
 // to which the unshared entries are then spread first.  By column a workgroup reads the coefficients of every block of rows for
-// its bucket, whatever the bucket holds, and goes through its columns; through the private vectors every solver's bitmaps are gone
-// through, and every column that a solver holds is written once and read once.  What the former saves of a round, microseconds,
-// fitted to 36 shapes of 1000 to 1.1M rows of 100 to 2500 entries, 0.15M to 1000M columns and 2 to 64 solvers.  Measured, spread
-// and merge, by column / through the vectors: 100000 rows of 1000 over 20M columns, 64 solvers 343 / 747, of 150 234 / 294, 300000
-// of 150 481 / 420, 1.1M of 100 1424 / 895; 2000 of 2500 over 200M, eight solvers 814 / 703, of 1000 over 1000M 2270 / 1436;
-// 55134 of 261 over 0.29M, ten solvers (few of whose entries are in columns of their own) 75 / 22; 1500 of 370 over 0.2M, seven
-// 8 / 24.  Where there is no room for the table that the spread reads (sources_dev), spreading takes 10 us more per million entries.
+// its bucket, whatever the bucket holds, and goes through its entries and columns: where there are few buckets, or most entries are in
+// one, the chip waits for that one's workgroup.  Through the private vectors every solver's bitmaps are gone through, and every column
+// that a solver holds is written once and read once.  What the former saves of a round, microseconds, fitted to 97 shapes of 1000 to
+// 1.1M rows of 100 to 2500 entries, 5000 to 1000M columns and 2 to 64 solvers.  Measured, spread and merge, by column / through the
+// vectors: 100000 rows of 1000 over 20M columns, 64 solvers 343 / 747, of 150 234 / 294, 300000 of 150 481 / 420, 1.1M of 100 1424 /
+// 895; 2000 of 2500 over 200M, eight solvers 814 / 703, of 1000 over 1000M 2270 / 1436; 1000 of 150 over 2M, eight 48 / 43; 55134 of 261
+// over 0.29M, ten (few of whose entries are in columns of their own) 75 / 22; 1500 of 370 over 0.2M, seven 8 / 24; of 16 solvers 4000
+// of 314 over 20000 (20 buckets) 76 / 54, over 0.1M 42 / 55, 16000 over 20000 250 / 132.  Where there is no room for the table that the
+// spread reads (sources_dev), spreading takes 9 us more per million entries.
 bool merge_pays(const chicle_ctx *c)
 {
-    if (c->columns.blocks == 0) return false;
-    // (a workgroup has a bucket: one that holds far more entries than the average compute unit's share would be waited for)
-    if (c->fullest_bucket * c->cu_count > 4.0 * (double)c->entries_loaded + 65536.0 * c->cu_count) return false;
-    const double d = 1e-6 * (double)c->d, entries = 1e-6 * (double)c->entries_loaded, columns = 1e-6 * (double)c->u_used;
-    const double saved = 16.0 + 0.09 * d * c->K + 12.6 * columns + (c->sources_dev ? 0.0 : 10.0 * entries);
-    return saved > 9.3 * entries + 0.73 * d + 0.0064 * (double)c->columns.buckets * (double)c->columns.blocks;
+    const double d = 1e-6 * (double)c->d, entries = 1e-6 * (double)c->entries_loaded, held = 1e-6 * (double)c->u_used;
+    const double buckets = co_buckets(c->d), fullest = std::max(1e-6 * c->fullest_bucket, entries / buckets);    // (unknown before there is a copy)
+    const double saved = 14.5 + 0.09 * d * c->K + 13.0 * held + (c->sources_dev ? 0.0 : 9.0 * entries);
+    return saved > std::max(8.9 * entries, 930.0 * fullest) + 0.41 * d + buckets * (0.0026 + 0.0067 * co_blocks(c->n_total));
 }
 
 // Whether the rows' dot products go over the entries by column, and not row by row.  The former is two kernels, one of which writes
@@ -1805,13 +1805,13 @@ int chicle_assign(chicle_ctx *c, int32_t K, const int32_t *chunk_to_solver)
             c->split_built_for = c->cluster;
         }
         if (layout_in_use(c) > copy_at(c)) c->columns.blocks = 0;
-        else if (c->columns.blocks == 0) {
+        else if (c->columns.blocks == 0 && (dots_pay(c) || (c->blocks_ready && merge_pays(c)))) {
             const int rc = order_by_column(c);
             if (rc) return rc;
         }
     }
     c->dots_by_columns = c->columns.blocks > 0 && dots_pay(c);
-    c->merge_by_columns = merge_pays(c);
+    c->merge_by_columns = c->columns.blocks > 0 && c->blocks_ready && merge_pays(c);
     c->coef_pending = c->private_stale = false;
     return clear_all_private(c);
 }

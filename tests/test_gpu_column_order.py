@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
     ("hinge", 16400, 600011, 100, 0, 0.0, False, False, True), ("squared", 321, 5003, 130, 0, 0.0, True, False, True),
     ("logistic", 500, 300001, 200, 0, 0.0, False, False, True), ("hinge", 700, 300001, 150, 900, 0.0, True, False, False),
     ("squared", 40, 20000003, 300, 0, 0.0, False, True, False), ("hinge", 321, 262145, 130, 0, 0.02, True, False, True),
-    ("squared", 2500, 40009, 400, 0, 0.0, False, False, True),
+    ("squared", 2500, 40009, 400, 0, 0.0, False, False, False),
     ("hinge", 16400, 600011, 300, 0, 0.0, False, True, None), ("squared", 500, 5003, 1200, 0, 0.0, True, True, None),
     ("logistic", 500, 300001, 900, 0, 0.0, False, True, True), ("hinge", 700, 300001, 900, 1000, 0.0, True, True, None),
     ("squared", 40, 20000003, 3000, 0, 0.0, False, True, False), ("hinge", 321, 262145, 1000, 0, 0.02, True, True, True),
@@ -129,9 +129,10 @@ def test_dot_products_go_the_cheaper_way(n, length, d, loss, by_column):
 
 @pytest.mark.parametrize("n,length,d,K,by_column", [
     (1500, 250, 200003, 7, True), (3000, 300, 5000011, 16, True), (1000, 110, 30000001, 2, False), (40000, 110, 6000007, 3, False),
-    (20000, 250, 40009, 4, False)])
+    (20000, 250, 40009, 4, False), (4000, 310, 20011, 16, False), (10000, 120, 20011, 16, False), (1000, 110, 2000003, 8, False)])
 def test_merge_goes_the_cheaper_way(oracle_mod, n, length, d, K, by_column):
-    """Many columns or blocks of rows for few entries, or entries that solvers' rows share: the merge is through the private vectors."""
+    """Many columns or blocks of rows for few entries, few buckets for many, or entries that solvers' rows share: the merge is through the
+    private vectors."""
     import paper_1909_04885_amd as binding
     from workloads.generate import Problem
     print("\ncase merge form n=%d length=%d d=%d K=%d" % (n, length, d, K), flush=True)
