@@ -188,6 +188,7 @@ struct chicle_ctx {
     double fullest_bucket = 0.0;      // entries of the bucket that has most, over all blocks of rows
     bool merge_by_columns = false;    // ... is what the merge reads after a pass of the block solver (merge_pays)
     bool coef_pending = false;        // such a pass has left its updates there: private vectors lack the unshared columns
+    bool updates_spread = false;      // ... until a caller asked for a solver's update
     bool private_stale = false;       // private vectors hold what has been merged from there, or what a failed pass has left
     bool cluster_allowed = true;
     // sparse rows longer than the batched solver takes: blocks over the columns that several rows of a solver hold
@@ -922,6 +923,7 @@ int launch_blocks(chicle_ctx *c, const int32_t *perm)
     seg_end(c, CHICLE_SEG_EPOCH_CHAIN);
     HIP_TRY(c, hipGetLastError());
     c->coef_pending = c->merge_by_columns;
+    c->updates_spread = false;
     return CHICLE_OK;
 }
 
@@ -2142,9 +2144,10 @@ int chicle_get_delta_w(chicle_ctx *c, int32_t solver, float *dw_out)
     if (!c || !dw_out) return CHICLE_EINVAL;
     if (c->state != ST_EPOCH_DONE) return fail(c, CHICLE_ESTATE, "updates exist only between local_epoch and aggregate");
     if (solver < -1 || solver >= c->K) return fail(c, CHICLE_EINVAL, "solver %d, K=%d", solver, c->K);
-    if (c->coef_pending) {
+    if (c->coef_pending && !c->updates_spread) {
         spread_updates(c);
         HIP_TRY(c, hipGetLastError());
+        c->updates_spread = true;
     }
     if (c->compact)
         hipLaunchKernelGGL(delta_w_out_compact, dim3(grid_for(c->d, 256, 4096)), dim3(256), 0, c->stream, c->u, c->u_off_dev,
