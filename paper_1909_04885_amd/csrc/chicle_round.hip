@@ -326,8 +326,9 @@ int dot_parts(int64_t n_total, int64_t entries)
     const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(co_parts(n_total), most));
     return parts < L2_PARTITIONS ? parts : parts / L2_PARTITIONS * L2_PARTITIONS;
 }
-// Where buckets begin, what counts them, the parts of the dot products and the coefficients, in whole megabytes.  (The entries
-// themselves lie in the room of the block solver's layout: copy_at.)
+// Where buckets begin, what counts them, the parts of the dot products and the coefficients.  In whole megabytes: what an arena grows by
+// with the rows then does not depend, by the rounding of single arrays, on the columns, which the tests of its size rely on (for the
+// times it makes no difference).  (The entries themselves lie in the room of the block solver's layout: copy_at.)
 size_t co_offsets_bytes(int64_t n_total, int32_t d) { return align_up(sizeof(long long) * ((size_t)co_blocks(n_total) * (size_t)co_buckets(d) + 2)); }
 size_t co_parts_bytes(int64_t n_total, int64_t entries) { return align_up(sizeof(double) * (size_t)dot_parts(n_total, entries) * (size_t)n_total); }
 size_t co_scratch_bytes(int64_t n_total, int64_t entries, int32_t d)
