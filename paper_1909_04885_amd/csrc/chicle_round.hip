@@ -672,7 +672,10 @@ bool short_tails(const chicle_ctx *c) { return c->compact && c->max_tail_entries
 // and entries stay in the memory-side cache (256 MB); where they do not, the tiles' loads set the pace and lookups between them
 // are better issued by the wavefront that stages a tile.  Apart / not, 2000 columns, 20 solvers: 64000 rows of 40 entries 79.5 /
 // 83.8 us, 256000 285 / 300, of 12 248 / 252; 384000 of 12 (233 MB) 395 / 390, 300000 of 44 (260 MB) 394 / 387, 546000 of 44 770 /
-// 741; four solvers of 64000 rows of 40 1218 / 1296, of 96000 2240 / 2230.  Logistic loss, 16 of 56000 of 20 4815 / 4900.
+// 741; four solvers of 64000 rows of 40 1218 / 1296, of 96000 2240 / 2230.  With the logistic loss, whose chain takes longer than
+// either, the wavefront more only takes issue slots: 20 solvers of 3200 rows of 40 entries, a run that continues 214 / 213 us and from
+// alpha = 0 815 / 799, of 27300 of 44 1413 / 1400 and 6142 / 6031, 16 of 56000 of 20 2514 / 2499 and 12041 / 11815, four of
+// 16000 of 40 746 / 742 and 2579 / 2547.
 bool heads_resolve_apart(const chicle_ctx *c)
 {
     return (double)tile_bytes(false) * c->n_tiles + 8.0 * (double)c->entries_loaded <= 224e6;
@@ -836,10 +839,13 @@ int launch_batched(chicle_ctx *c, const int32_t *perm, bool tiles_ready, const i
         A.lag = c->pairs_listed[c->tile_buf] ? LAG : 2; A.pair_list = c->pair_list[c->tile_buf]; A.pair_count = c->pair_count[c->tile_buf];
         // a tail's lanes take the last 24 entries of a row where that covers every row's unpopular columns
         constexpr int TE_SHORT = 3 * LPR / TAIL_LPR, TE_ALL = GRAM_MAX_ROW / TAIL_LPR;
-        auto kern = n_tails == 0 ? sdca_batched_heads<LOSS, true> : short_tails(c) ? sdca_batched_split<LOSS, TE_SHORT> : sdca_batched_split<LOSS, TE_ALL>;
-        int threads = n_tails == 0 ? HEAD_THREADS : SPLIT_THREADS;
-        if constexpr (LOSS != CHICLE_LOSS_LOGISTIC)
-            if (n_tails == 0 && !heads_resolve_apart(c)) { kern = sdca_batched_heads<LOSS, false>; threads = BATCHED_THREADS; }
+        auto kern = short_tails(c) ? sdca_batched_split<LOSS, TE_SHORT> : sdca_batched_split<LOSS, TE_ALL>;
+        int threads = SPLIT_THREADS;
+        if (n_tails == 0) {
+            kern = sdca_batched_heads<LOSS, false>; threads = BATCHED_THREADS;
+            if constexpr (LOSS != CHICLE_LOSS_LOGISTIC)
+                if (heads_resolve_apart(c)) { kern = sdca_batched_heads<LOSS, true>; threads = HEAD_THREADS; }
+        }
         static_assert(tail_lists_at(TE_ALL) <= sizeof(BatchedShared) + sizeof(double) * TAILS_MIN_HOT, "a tail fits the LDS of a head that has tails");
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
         clear_device_words(c, c->split_ring_dev, 2 * (int64_t)SPLIT_WORDS * c->K);
