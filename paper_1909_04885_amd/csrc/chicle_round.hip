@@ -691,9 +691,13 @@ bool heads_resolve_apart(const chicle_ctx *c)
 // enough 8 and 0.03, and up to 0.05 where blocks have hundreds of pairs; smaller jobs save 0.65 us per block, from the fifth or
 // so on.  Passes without and with: one solver of 1024 rows 69 us and 68, of 2560 122 and 103; 16 of 640 rows 64 and 70, of 2560
 // 152 and 159 (uniform columns: 166 and 189); 17 of 11000 rows of some 20 to 46 532 and 494, 71 of 2260 rows of 7 155 and 144.
-// With the logistic loss, whose chain takes longer than the tails, nothing is saved: one of 2560 rows 263 and 267, 16 290 and
-// 313; ahead it is 318 and 313, 358 and 355.
-// Nor is it where blocks have more pairs than a list holds, which the columns' shares of the rows tell for rows in random order
+// With the logistic loss the chain takes longer than the tails from alpha = 0, where nothing is saved, and about as long on a run that
+// continues, where it is 0.15 to 0.3 us per block and lists formed ahead cost more of it.  Passes without and with, continuing (from
+// alpha = 0): one of 2560 rows 193 and 195, 16 of 2560 217 and 220 (494 and 506), 17 of 11000 691 and 676 (1815 and 1832), 32 of 9375
+// 745 and 721 (1902 and 1924), eight of 40000 2173 and 2008 (5120 and 5094), 71 of 2260 rows of 10 250 and 260; ahead 17 of 11000 628
+// and 585, 32 of 9375 645 and 571, eight of 40000 2140 and 1875, 32 of 3000 of 10 217 and 210; 48 of 3000 of 10 or 40 240 and 241, 309
+// and 310; 64 280 and 301, 381 and 393, 80 352 and 358, 441 and 453 (871 and 898).
+// Nothing is saved where blocks have more pairs than a list holds, which the columns' shares of the rows tell for rows in random order
 // (16 solvers of 12500 rows of 48 entries in 16400 columns, 3.12 and 3.27).
 bool lists_pairs(const chicle_ctx *c, bool ahead)
 {
@@ -705,7 +709,8 @@ bool lists_pairs(const chicle_ctx *c, bool ahead)
     const double pairs = at < c->shares.size() ? (LAG - 2) * (double)(BATCH * BATCH) * c->shares[at] : 0.0;       // of a block
     if (pairs > 0.85 * PAIR_CAP) return false;
     const double us = narrow ? 4.5 + 0.005 * c->n_tiles : 8.0 + (0.03 + 6e-5 * pairs) * c->n_tiles;
-    return ahead || (c->loss != CHICLE_LOSS_LOGISTIC && 0.65 * (blocks - 4) > us);
+    if (c->loss == CHICLE_LOSS_LOGISTIC) return ahead ? 5 * (1 + SPLIT_TAILS) * c->K <= 3 * c->cu_count : 0.15 * (blocks - 4) > us;
+    return ahead || 0.65 * (blocks - 4) > us;
 }
 
 template <int TE>
