@@ -502,14 +502,16 @@ bool dense_eligible(const chicle_ctx *c, int32_t max_d) { return c->dense && c->
 
 // Solvers of so few rows step through them one at a time faster than the tile kernel and the block kernel get under way.
 // Whole rounds, row by row / in blocks.  Dense rows, four solvers of 4 rows: 64 columns 26 / 33 us, 1000 columns 42 / 56; of
-// 8 rows 1000 columns equal; logistic loss of 12 rows 39 / 44 and 69 / 66.  Sparse rows, 64 solvers: of 12 rows of 40 or 80
+// 8 rows 1000 columns equal; logistic loss, a run that continues (from alpha = 0), of 12 rows 64 columns 34 / 36 (36 / 38), 200 40 / 42
+// (44 / 43), 400 46 / 47 (52 / 48), 1000 61 / 56 (75 / 59), 1500 73 / 65 (93 / 67), of 8 rows 50 / 56 (59 / 57) and 60 / 65 (74 / 66), of
+// 16 rows 64 columns 38 / 36.  Sparse rows, 64 solvers: of 12 rows of 40 or 80
 // entries 56 / 63 and 59 / 67, of 16 equal; of 8 rows of 120 (several workgroups share a solver, and a row takes longer)
 // 59 / 66, of 12 equal.  Block kernels take a compute unit each, so more solvers than compute units queue up: 512 solvers of
 // 10 rows of 400 columns 162 / 176, of 12 rows of 80 entries 84 / 92.
 bool few_rows(const chicle_ctx *c)
 {
     const int waves = (c->K + c->cu_count - 1) / c->cu_count;
-    if (c->dense) return c->most_rows <= std::max(c->loss == CHICLE_LOSS_LOGISTIC ? 12 : 8, 5 * waves);
+    if (c->dense) return c->most_rows <= std::max(c->loss == CHICLE_LOSS_LOGISTIC && c->d <= 512 ? 12 : 8, 5 * waves);
     return c->most_rows <= (c->long_rows ? std::max(8, 4 * waves) : std::max(12, 6 * waves));
 }
 

@@ -61,6 +61,25 @@ def test_solvers_of_few_dense_rows_go_row_by_row(oracle_mod, d, rows, K, runs):
                      tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)
 
 
+@pytest.mark.parametrize("d,rows,runs", [(512, 12, "rowwise"), (512, 13, "dense"), (513, 8, "rowwise"), (513, 9, "dense"), (1000, 12, "dense")])
+def test_few_dense_rows_logistic(oracle_mod, d, rows, runs):
+    """A step row by row takes longer the wider the row is, and a block hardly does."""
+    import paper_1909_04885_amd as binding
+    from workloads.generate import Problem
+    print("\ncase dense choice logistic d=%d rows=%d" % (d, rows), flush=True)
+    g = np.random.default_rng(d + rows)
+    n, K = 4 * rows, 4
+    X = (g.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    p = Problem("choice", "logistic", n, d, 0.5 / n, np.where(g.random(n) < 0.5, 1.0, -1.0).astype(np.float32), np.arange(0, n + 1, rows, dtype=np.int64), X=X)
+    table = np.arange(K, dtype=np.int32)
+    c = binding.ChicleRound.from_problem(p, max_solvers=K)
+    c.assign(K, table)
+    assert c.debug_solver()[0] == runs
+    c.close()
+    run_lockstep({"seed": 3, "rounds": 2, "schedule": [(0, K)], "K": K}, p, oracle_mod, binding, check_alpha_every=1, ahead=True,
+                 tables=lambda r, Kp, tp: (K, table, table.copy()) if r == 0 else None, max_solvers=K)
+
+
 @pytest.mark.parametrize("ahead,n", [(False, 2500), (True, 1250)])
 @pytest.mark.parametrize("d", [1, 28, 32, 33, 64, 65, 200, 511, 700, 1001, 1200, 1500])
 def test_squared_loss_with_solved_tiles(oracle_mod, d, ahead, n):

@@ -181,7 +181,7 @@ def test_pairs_in_a_context_made_for_long_rows(oracle_mod):
 @pytest.mark.parametrize("n", [65, 3000, 320000])
 def test_all_columns_in_the_head(oracle_mod, n, loss):
     """No tails: rows resolved by a wavefront of their own, and beside a tile where tiles and entries are too many for the
-    caches (320000 rows, not with the logistic loss).  Rows of 1 to 48 entries, some without any."""
+    caches (320000 rows; with the logistic loss always).  Rows of 1 to 48 entries, some without any."""
     import torch
     assert torch.cuda.is_available()
     print("\ncase all columns in the head n=%d %s" % (n, loss), flush=True)
