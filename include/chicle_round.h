@@ -266,8 +266,10 @@ int chicle_aggregate(chicle_ctx *ctx);
 
 /* The convergence metric that solvers report to the trainer every iteration (Section 4.1) and that the
  * evaluation follows, the duality gap (Section 5.1): P(w), D(alpha) and P - D at the current state, with the
- * objectives stated at the top of this file (host outs, any may be NULL).  Legal in READY.  Synchronises.
- * Errors: ESTATE, EDEVICE. */
+ * objectives stated at the top of this file (host outs, any may be NULL).  Legal in READY.  Returns when the sums
+ * and the kernels' error flag have arrived: everything enqueued on the context's stream before the call is done then,
+ * while the gap's own last kernel may not have ended, nor the work on the library's own stream; chicle_sync
+ * waits for the former.  Errors: ESTATE, EDEVICE. */
 int chicle_gap(chicle_ctx *ctx, double *primal, double *dual, double *gap);
 
 /* chicle_gap for callers that cannot allocate device memory or hand over a workspace for this call: code

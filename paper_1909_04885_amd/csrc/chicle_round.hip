@@ -53,8 +53,10 @@ inline int64_t tiles_cap(int64_t n_total, int32_t max_solvers) { return n_total 
 inline size_t tile_bytes(bool dense) { return sizeof(float) * (size_t)(dense ? DENSE_TILE_FLOATS : TILE_FLOATS); }
 
 // Vectors and visiting orders of at most so many bytes go through pinned memory that kernels write and read themselves: a copy and
-// a wait less each.  One round of 1000 x 48 with orders from the host: 91.5 us and 54.0; four of 1500
-// long rows over 200k columns 448 and 420.
+// a wait less each.  One round of 1000 x 48 with orders from the host: 91.5 us and 54.0; four of 1500 long rows over 200k columns 448
+// and 420.  Kernels read and write the link more slowly than copies do: rounds with orders of 262144 rows (1 MB) from the host 170 and 157, of
+// 524288 230 and 229, of 1048576 394 and 431; read-outs of 1000 columns 37 and 14, of 65536 54 and 25, of 262144 99 and 67, of 1048576 250 and
+// 237, of 2097152 389 and 457.  The line is below where they meet: what is pinned is held as long as the context.
 constexpr size_t PINNED_HEAD = 256, PINNED_MOST = size_t(1) << 20;
 constexpr int GAP_SPINS = 100000;                // reads of the word before the stream is waited for (a few milliseconds)
 constexpr size_t READ_PIECE = size_t(2) << 20;   // bytes
