@@ -1,6 +1,6 @@
 // Long sparse rows: a second copy of the entries, ordered by column inside blocks of rows, for the two passes over the matrix
 // that are not the solvers': x_i . w of every row (the gap, and the residuals the next local pass starts from), and the merge of
-// the solvers' updates, sum_i coef_i x_i.
+// the solvers' updates, sum_i coef_i x_i.  Each of the two goes over it where that is the faster way (dots_pay, merge_pays).
 //
 // By rows a row's thousand entries, spread over twenty million columns, are a thousand lonely 4-byte accesses to the shared
 // vector.  Here the rows are divided into blocks of CO_ROWS; a block's entries lie by buckets of neighbouring columns, and inside

@@ -9,8 +9,8 @@
 //   sdca_blocks      per solver a cluster of G workgroups, each with a part of the shared columns' private vector in
 //                    LDS for the whole pass: gather, recurrence, scatter;
 //   spread_unique    on the whole chip: the entries of unshared columns, from the steps the second kernel leaves.
-// Contexts of long rows merge from the steps' coefficients (column_order.hpp): there the third kernel runs only where a caller asks
-// for a solver's update.
+// Where the merge takes the updates of long rows from the steps' coefficients (merge_pays), the third kernel runs only when a caller
+// asks for a solver's update.
 // A step of the row-wise solvers costs a trip to memory (1.7 us for rows of 36 entries, 2.9 us for rows of a thousand on
 // four workgroups); here 64 steps cost one recurrence (2e3 cycles) and as much again for gather and scatter.
 //
