@@ -1179,7 +1179,7 @@ int order_by_column(chicle_ctx *c)
 // to which the unshared entries are then spread first.  By column a workgroup reads the coefficients of every block of rows for
 // its bucket, whatever the bucket holds, and goes through its entries and columns: where there are few buckets, or most entries are in
 // one, the chip waits for that one's workgroup.  Through the private vectors every solver's bitmaps are gone through, and every column
-// that a solver holds is written once and read once.  What the former saves of a round, microseconds, fitted to 97 shapes of 1000 to
+// that a solver holds is written once and read once.  What the former saves of a round, microseconds, fitted to 106 shapes of 1000 to
 // 1.1M rows of 100 to 2500 entries, 5000 to 1000M columns and 2 to 64 solvers.  Measured, spread and merge, by column / through the
 // vectors: 100000 rows of 1000 over 20M columns, 64 solvers 343 / 747, of 150 234 / 294, 300000 of 150 481 / 420, 1.1M of 100 1424 /
 // 895; 2000 of 2500 over 200M, eight solvers 814 / 703, of 1000 over 1000M 2270 / 1436; 1000 of 150 over 2M, eight 48 / 43; 55134 of 261
@@ -1196,7 +1196,7 @@ bool merge_pays(const chicle_ctx *c)
 
 // Whether the rows' dot products go over the entries by column, and not row by row.  The former is two kernels, one of which writes
 // and one of which reads a double per row and part; the latter is slower per entry the larger the shared vector is, most of all where
-// an L2 partition does not hold it, or the matrix outgrows the L2s, and as slow as its longest rows.  Microseconds, fitted to 82 shapes
+// an L2 partition does not hold it, or the matrix outgrows the L2s, and as slow as its longest rows.  Microseconds, fitted to 114 shapes
 // of 1000 to 200000 rows of 115 to 1046 entries, 5000 to 20M columns, hinge and squared loss; the way that used to be is kept where
 // the two are close.  By column / by row: 1000 rows of 115 over 20000 columns 15.1 / 10.1, 16000 24.2 / 17.7, 50000 30 / 36, over
 // 2M 36 / 79; 1000 of 314 over 0.1M 14.8 / 14.0, over 2M 18.3 / 21.6; 16000 over 5000 31 / 23, over 0.1M 30 / 34, over 2M 35 / 58;
